@@ -115,8 +115,8 @@ __device__ int accept_token(const CacheDev& Cd, const uint32_t* cls_words, const
             uint32_t wr, wt;
             wait_at(o, k, wr, wt);
             if (wr != rule) continue;
-            const uint32_t key = wt & SID_MASK;
-            // the state's planes are sorted by site (a state inside a long repetition is referenced from thousands of states)
+            const uint32_t key = Cd.site_rep ? tab(Cd.site_rep + (wt & SID_MASK)) : (wt & SID_MASK);
+            // the state's planes are sorted by site
             const uint32_t end_j = tab(Cd.pair_off + sid + 1);
             uint32_t lo_j = tab(Cd.pair_off + sid), hi_j = end_j;
             while (lo_j < hi_j) {

@@ -25,6 +25,7 @@
 #include <hip/hip_runtime.h>
 
 #include "device.hpp"
+#include "flat_map.hpp"
 #include "grammar.hpp"
 #include "tables.hpp"
 
@@ -224,8 +225,18 @@ struct VocabImpl {
     DevBuf<uint8_t> d_first_byte;               // first byte of every token id (0 for the empty ones), W * 32 entries
     // per byte set asked for so far: the sorted ranks of the tokens that contain a byte of the set (ascending, appended
     // to long_rank) and, on the device, the mask in token ids of the checkable tokens that contain none
-    struct ByteSetList { std::array<uint32_t, 8> bytes; uint32_t off, n; std::unique_ptr<DevBuf<uint32_t>> d_without; };
+    // first_byte[b]: index into long_rank of the list's first rank at or after fb_start[b] (so a range of first bytes is a
+    // range of the list without a search)
+    using ListStarts = std::array<uint32_t, 257>;
+    struct ByteSetList { std::array<uint32_t, 8> bytes; uint32_t off, n; std::unique_ptr<DevBuf<uint32_t>> d_without; ListStarts first_byte; };
     std::vector<ByteSetList> byte_lists;
+    std::vector<ListStarts> near_first_byte;    // the same for the list of every length bound d
+    ListStarts list_starts(uint32_t off, uint32_t n) const {
+        ListStarts s;
+        uint32_t i = off;
+        for (int b = 0; b <= 256; ++b) { while (i < off + n && long_rank[i] < fb_start[b]) ++i; s[(size_t)b] = i; }
+        return s;
+    }
     // The caller serialises (the mutex of the large-capacity scratch) and no kernel is in flight on the lists.
     int32_t list_of_tokens_with(const std::array<uint32_t, 8>& bytes) {
         for (size_t k = 0; k < byte_lists.size(); ++k) if (byte_lists[k].bytes == bytes) return (int32_t)k;
@@ -240,6 +251,7 @@ struct VocabImpl {
             else without[perm[r] >> 5] |= 1u << (perm[r] & 31);
         }
         bl.n = (uint32_t)long_rank.size() - bl.off;
+        bl.first_byte = list_starts(bl.off, bl.n);
         extend_long_bytes();
         bl.d_without.reset(new DevBuf<uint32_t>());
         bl.d_without->upload(without, nullptr);
@@ -279,6 +291,8 @@ struct VocabImpl {
             }
         }
         long_off[(size_t)near_depths + 1] = (uint32_t)long_rank.size();
+        near_first_byte.resize((size_t)near_depths + 1);
+        for (uint32_t d = 1; d <= near_depths; ++d) near_first_byte[d] = list_starts(long_off[d], long_off[d + 1] - long_off[d]);
         if (long_rank.empty()) long_rank.push_back(0);
         extend_long_bytes();
         d_long_rank.upload(long_rank, nullptr);
@@ -336,8 +350,20 @@ hipStream_t jit_stream() {
 // ---- cross-grammar pool -------------------------------------------------------------------------------
 // A plane is identified by (pool entry of the position's rule, canonical state, pool entry of the
 // referencing rule or -1, canonical state the referencing rule continues in or -1).
-using PlaneKey = std::array<int64_t, 5>;   // the fifth word: follow signature of the outermost rule (0 = unfiltered)
+using PlaneKey = std::array<int64_t, 5>;   // the fifth word: number of the outermost rule's follow language (0 = unfiltered)
+struct PlaneKeyHash { uint64_t operator()(const PlaneKey& k) const { uint64_t h = 0; for (int64_t w : k) { h = (h ^ (uint64_t)w) * 0x9FB21C651E98DF25ull; h ^= h >> 32; } return h; } };
 struct PoolImpl;
+struct BuildTicket;
+// A row of device memory that holds a plane (accepted; uncertain at + W words, left early at + 2 W, list of uncertain tokens).
+struct PlaneRow {
+    uint32_t* mem = nullptr;
+    PlaneKey key{};
+    int32_t refs = 0; uint64_t stamp = 0;       // live caches that use it, and when one last took it
+    bool no_uncertain = false;                  // its uncertain plane is all zero (need not be read)
+    bool in_use = false;                        // it holds a plane (listed under its key unless the build failed), else it is free
+    std::shared_ptr<BuildTicket> building;      // the build that writes it, until that is finalised
+    uint64_t build_serial = 0; uint32_t build_index = 0;   // its place in the build being planned
+};
 // One enqueued cache build.  Compile (and a fill that builds just in time) returns once the kernels are enqueued; whoever
 // needs their outcome next (statistics, planes copied to the host, the next compile or fill) finalises the ticket: waits for
 // its last event, reads the counters the device copied to pinned memory, and either marks the planes' rows as good
@@ -347,9 +373,8 @@ struct BuildTicket {
     StagingSet* staging = nullptr;
     std::shared_ptr<PoolImpl> pool;
     hipStream_t stream = nullptr;
-    std::vector<uint32_t*> rows;                                // the rows being built, with their keys in the pool
-    std::vector<PlaneKey> keys;
-    std::vector<uint32_t*> borrowed;                            // rows of other planes this build reads: kept from eviction until it is looked at
+    std::vector<PlaneRow*> rows;                                // the rows being built
+    std::vector<PlaneRow*> borrowed;                            // rows of other planes this build reads: kept from eviction until it is looked at
     int64_t partial_hits = 0;                                   // planes derived from a plane of the same structure
     int64_t executed = 0, executed_bytes = 0;
     double host_ms = 0;
@@ -371,27 +396,22 @@ struct PoolImpl {
     struct Entry { uint64_t hash; std::string text; };
     std::vector<Entry> entries;
     std::unordered_multimap<uint64_t, int> by_hash;
-    std::map<PlaneKey, uint32_t*> rows;
-    // per structure (the key without its follow signature), one row built under the follow filter: what a plane of the same
-    // structure under another follow language is derived from (section 3.3: partial cache hit)
-    std::map<std::array<int64_t, 4>, uint32_t*> by_structure;
-    std::unordered_set<const uint32_t*> no_uncertain;      // rows whose uncertain plane is all zero (need not be read)
-    // bounded-bisimulation classes of interned rules, in canonical state numbers: (entry, token-length budget) -> for
-    // canonical state c, the canonical state of its representative
-    struct ClassMemo { std::vector<int32_t> rep, base, depth; };            // by canonical state number
-    std::map<std::pair<int, int32_t>, ClassMemo> class_memo;
-    // rows in use: by how many live caches, and when last taken into a cache.  When max_bytes is reached, rows that no
-    // live cache uses are given up, least recently used first, and their memory is handed out again.
-    struct RowMeta { PlaneKey key; int32_t refs; uint64_t stamp; };
-    std::unordered_map<const uint32_t*, std::shared_ptr<BuildTicket>> building;   // rows whose build has not been finalised
+    std::deque<PlaneRow> row_store;                         // every row ever handed out (addresses stay)
+    FlatMap<PlaneKey, PlaneRow*, PlaneKeyHash> rows;        // planes that may be shared, by key
+    // per structure (the key with its follow language blanked), one row built under the follow filter: what a plane of the
+    // same structure under another follow language is derived from (section 3.3: partial cache hit)
+    FlatMap<PlaneKey, PlaneRow*, PlaneKeyHash> by_structure;
+    static PlaneKey structure_of(PlaneKey k) { k[4] = 0; return k; }
+    // descriptions of behaviour on bounded strings and of follow languages, numbered exactly, and per entry that can be
+    // shared the analysis of its rule (an identical rule of a later grammar finds it ready)
+    NodeTable nodes;
+    std::vector<std::shared_ptr<const RuleAnalysis>> analysis;
+    // When max_bytes is reached, rows that no live cache uses are given up, least recently used first, and their memory is
+    // handed out again.
     std::deque<std::shared_ptr<BuildTicket>> pending;                             // tickets not finalised yet, oldest first
-    std::unordered_map<const uint32_t*, RowMeta> meta;
-    std::vector<uint32_t*> free_rows;
+    std::vector<PlaneRow*> free_rows;
     uint64_t clock = 0;
     int64_t n_evicted = 0;
-    struct WordsHash { size_t operator()(const std::vector<uint64_t>& v) const { uint64_t h = 0x9E3779B97F4A7C15ull; for (uint64_t w : v) h = hash_combine(h, w); return (size_t)h; } };
-    std::unordered_map<std::vector<uint64_t>, uint64_t, WordsHash> follow_nodes;    // exact interning of follow-language descriptions
-    std::unordered_map<int, std::vector<uint64_t>> follow_unfold;   // per interned rule: value of (depth, canonical state), 0 = not known yet
     std::vector<void*> slabs;
     // memory to clear before the next build writes to it: freshly allocated slabs and rows taken from the free list.
     // The build enqueues the fills inside its timed region (skipped tokens rely on the zeros).
@@ -417,31 +437,23 @@ struct PoolImpl {
         if (shareable) by_hash.emplace(hash, id);
         return id;
     }
-    void take(uint32_t* row, const PlaneKey& key) {              // a cache starts using the row
-        RowMeta& m = meta[row];
-        if (m.refs == 0 && m.stamp == 0) m.key = key;
-        ++m.refs;
-        m.stamp = ++clock;
+    void take(PlaneRow* row) { ++row->refs; row->stamp = ++clock; }      // a cache starts using the row
+    void release(PlaneRow* row) { if (row->refs > 0) --row->refs; }
+    void unlist(PlaneRow* row) {                                 // nobody may take the row from the pool any more
+        PlaneRow** have = rows.find(row->key);
+        if (have && *have == row) rows.erase(row->key);
     }
-    void release(const uint32_t* row) {
-        auto it = meta.find(row);
-        if (it != meta.end() && it->second.refs > 0) --it->second.refs;
-    }
-    void forget(uint32_t* row) {                                 // the row's content is void: its memory can be reused
-        auto it = meta.find(row);
-        if (it != meta.end()) {
-            const PlaneKey& k = it->second.key;
-            auto bs = by_structure.find({k[0], k[1], k[2], k[3]});
-            if (bs != by_structure.end() && bs->second == row) by_structure.erase(bs);
-            rows.erase(k); meta.erase(it);
-        }
-        no_uncertain.erase(row);
+    void forget(PlaneRow* row) {                                 // the row's content is void: its memory can be reused
+        unlist(row);
+        PlaneRow** bs = by_structure.find(structure_of(row->key));
+        if (bs && *bs == row) by_structure.erase(structure_of(row->key));
+        row->in_use = false;
         free_rows.push_back(row);
         --n_rows;
     }
     // rows_ahead: how many rows the caller is about to ask for, this one included (sizes a new slab: what is
     // allocated is zeroed by the build that first uses it, so a small build should not pay for a large slab)
-    uint32_t* alloc_row(size_t row_bytes, size_t rows_ahead = 1) {
+    PlaneRow* alloc_row(const PlaneKey& key, size_t row_bytes, size_t rows_ahead = 1) {
         if (free_rows.empty() && slab_left < row_bytes) {
             size_t want = std::min<size_t>(std::max<size_t>({row_bytes * 64, (size_t)8 << 20, rows_ahead * row_bytes}), (size_t)256 << 20);
             want = std::max(want, row_bytes);
@@ -449,8 +461,8 @@ struct PoolImpl {
             if (max_bytes && device_bytes + want > max_bytes) want = row_bytes;
             if (max_bytes && device_bytes + want > max_bytes) {
                 // full: give up the least recently used rows that no live cache uses (a batch, so that the scan is rare)
-                std::vector<std::pair<uint64_t, uint32_t*>> idle;
-                for (auto& kv : meta) if (kv.second.refs == 0) idle.emplace_back(kv.second.stamp, const_cast<uint32_t*>(kv.first));
+                std::vector<std::pair<uint64_t, PlaneRow*>> idle;
+                for (PlaneRow& r : row_store) if (r.in_use && r.refs == 0 && r.stamp != 0) idle.emplace_back(r.stamp, &r);
                 if (idle.empty()) throw std::length_error("cross-grammar pool is full (max_bytes reached and every row is in use)");
                 const size_t batch = std::min<size_t>(idle.size(), std::max<size_t>(64, idle.size() / 8));
                 std::partial_sort(idle.begin(), idle.begin() + (long)batch, idle.end());
@@ -463,14 +475,17 @@ struct PoolImpl {
                 slab_cur = (uint8_t*)p; slab_left = want; device_bytes += want;
             }
         }
-        uint32_t* row;
+        PlaneRow* row;
         if (!free_rows.empty()) {
             row = free_rows.back(); free_rows.pop_back();
-            to_zero.emplace_back(row, row_bytes);
+            to_zero.emplace_back(row->mem, row_bytes);
         } else {
-            row = (uint32_t*)slab_cur;
+            row_store.emplace_back();
+            row = &row_store.back();
+            row->mem = (uint32_t*)slab_cur;
             slab_cur += row_bytes; slab_left -= row_bytes;
         }
+        row->key = key; row->refs = 0; row->stamp = 0; row->no_uncertain = false; row->in_use = true;
         ++n_rows;
         return row;
     }
@@ -479,14 +494,14 @@ struct PoolImpl {
 // ---- mask cache -----------------------------------------------------------------------------------------
 struct PlaneInfo {
     int32_t rule, state, parent_rule, parent_state;         // the representative it is built for
-    uint32_t* row;                                          // accepted row (uncertain at + W words, left early at + 2 W); null until built
+    PlaneRow* row;                                          // null until built
     bool no_uncertain;
     PlaneKey key;                                           // identity in the pool
     uint32_t sid; int64_t waiter_sid;                       // start of the build: position, and the waiting parent state or -1
+    int32_t site = -1;                                      // which of the rule's sites the parent is (index into site_keys), or -1
     uint64_t cost;                                          // estimate of the build work (tokens whose first byte the state reads)
     int32_t near_plane = -1, near_depth = 0;                // a plane with the same classes for every token of at most near_depth bytes
-    int32_t fb_plane = -1;                                  // a plane with the same classes for every token whose first byte is in fb_same
-    std::array<uint32_t, 8> fb_same{};
+    int32_t fb_plane = -1, fb_same = -1;                    // a plane with the same classes for every token whose first byte is in that set of the cache's
     int32_t site_plane = -1, site_list = -1;                // the same state under another site: same classes for every token outside that list
 };
 struct CacheImpl {
@@ -518,13 +533,26 @@ struct CacheImpl {
         std::mutex mu;
         bool ready = false;
         DevBuf<uint64_t> plain_row, pair_row, start_front;
-        DevBuf<uint32_t> pair_off, pair_key, start_items, start_wait_off;
+        DevBuf<uint32_t> pair_off, pair_key, site_rep, start_items, start_wait_off;
         DevBuf<uint2> start_wait;
         CacheDev cd{};
         uint32_t n_start_wait = 0;
     } on_device;
+    std::vector<std::array<uint32_t, 8>> fb_same;           // first-byte sets that planes share with the plane of their rule's start state
     std::vector<int32_t> plain_plane;                       // [sid] -> plane without context, or -1
-    std::unordered_map<uint64_t, int32_t> pair_plane;       // (sid << 32 | parent continuation sid) -> plane
+    // Planes under a referencing site: states of one class continue alike, so a rule's sites are the classes of the states
+    // referencing rules continue in.  pair_table[pair_base[sid] + k] = plane of the state under site k of its rule.
+    std::vector<uint32_t> site_rep;                         // [sid] -> the state (sid) that stands for its class
+    Rows<uint32_t> site_keys;                               // per rule: its sites (values of site_rep), ascending
+    std::vector<int32_t> pair_base, pair_table;             // pair_base[sid]: -1 for states without planes under sites
+    // plane of state sid when the referencing rule continues in state tgt, or -1
+    int32_t pair_plane(uint32_t sid, uint32_t tgt) const {
+        const int32_t base = pair_base.empty() ? -1 : pair_base[sid];
+        if (base < 0) return -1;
+        const Span<uint32_t> keys = site_keys[gram->ft.state_info[sid].rule_final & 0x7FFFFFFFu];
+        const uint32_t* k = std::lower_bound(keys.begin(), keys.end(), site_rep[tgt]);
+        return k != keys.end() && *k == site_rep[tgt] ? pair_table[(size_t)base + (size_t)(k - keys.begin())] : -1;
+    }
 };
 
 struct MatcherImpl {
@@ -705,21 +733,21 @@ void finalize_ticket(BuildTicket& T) {
         failed = S.res[1] != 0;                                     // item sets exceeded even the large-capacity lists
     }
     for (size_t k = 0; k < T.rows.size(); ++k) {
-        pool.building.erase(T.rows[k]);
+        PlaneRow* row = T.rows[k];
         if (failed) {
             // partial results: nobody may take the row from the pool any more (caches that did are failed through this
             // ticket); its memory is not handed out again while they may still hold it
-            auto it = pool.rows.find(T.keys[k]);
-            if (it != pool.rows.end() && it->second == T.rows[k]) pool.rows.erase(it);
-            continue;
+            pool.unlist(row);
+        } else {
+            const uint32_t n_acc = S.res[2 + 2 * k], n_unc = S.res[3 + 2 * k];
+            row->no_uncertain = n_unc == 0;
+            if (row->key[4] != 0) pool.by_structure.emplace(PoolImpl::structure_of(row->key), row);
+            T.n_accepted += n_acc; T.n_uncertain += n_unc;
         }
-        const uint32_t n_acc = S.res[2 + 2 * k], n_unc = S.res[3 + 2 * k];
-        if (n_unc == 0) pool.no_uncertain.insert(T.rows[k]);
-        if (T.keys[k][4] != 0) pool.by_structure.emplace(std::array<int64_t, 4>{T.keys[k][0], T.keys[k][1], T.keys[k][2], T.keys[k][3]}, T.rows[k]);
-        T.n_accepted += n_acc; T.n_uncertain += n_unc;
+        row->building.reset();
     }
     T.state = failed ? 2 : 1;
-    for (uint32_t* b : T.borrowed) pool.release(b);
+    for (PlaneRow* b : T.borrowed) pool.release(b);
     T.borrowed.clear();
     for (auto it = pool.pending.begin(); it != pool.pending.end(); ++it) if (it->get() == &T) { pool.pending.erase(it); break; }
     {
@@ -739,7 +767,7 @@ void finalize_cache(CacheImpl& cache) {
     cache.tickets.clear();
     for (int32_t k : cache.fresh_planes) {
         PlaneInfo& pi = cache.planes[(size_t)k];
-        pi.no_uncertain = pi.row && cache.pool->no_uncertain.count(pi.row) != 0;
+        pi.no_uncertain = pi.row && pi.row->no_uncertain;
     }
     cache.fresh_planes.clear();
 }
@@ -770,46 +798,43 @@ int32_t build_planes(CacheImpl& cache, const std::vector<int32_t>& todo, hipStre
     const FlatTables& ft = cache.gram->ft;
     const size_t row_bytes = plane_words(V.W) * sizeof(uint32_t);      // accepted, uncertain, left early, list of uncertain tokens
     std::vector<int32_t> build;                                 // plane indices to class now
-    std::vector<uint32_t*> build_rows;
+    std::vector<PlaneRow*> rows;                                // and the row of each
+    const uint64_t serial = ++pool.clock;                       // marks the rows of this build
     // Until the planes are known to be built, the pool must not offer their rows to anyone: whatever goes wrong
     // on the way (the pool is full, a HIP call fails, the item sets overflow), the rows this call has entered
     // are taken out of the pool again and their memory goes back to the free list.
     struct Rollback {
-        PoolImpl& pool; CacheImpl& cache; const std::vector<int32_t>& build; const std::vector<uint32_t*>& rows; hipStream_t stream;
+        PoolImpl& pool; const std::vector<PlaneRow*>& rows; hipStream_t stream;
         bool armed = true;
         ~Rollback() {
             if (!armed) return;
             (void)hipStreamSynchronize(stream);                  // no kernel of this call writes to the rows any more
-            for (size_t k = 0; k < build.size(); ++k) {
-                auto it = pool.rows.find(cache.planes[(size_t)build[k]].key);
-                if (it != pool.rows.end() && it->second == rows[k]) pool.rows.erase(it);
-                pool.free_rows.push_back(rows[k]);
-                --pool.n_rows;
-            }
+            for (PlaneRow* r : rows) pool.forget(r);
         }
-    } rollback{pool, cache, build, build_rows, stream};
+    } rollback{pool, rows, stream};
     struct ReleaseBorrowed {                                     // rows borrowed for a partial hit go back if the build is not enqueued
-        PoolImpl& pool; std::vector<uint32_t*>* rows = nullptr; bool armed = true;
-        ~ReleaseBorrowed() { if (armed && rows) for (uint32_t* r : *rows) pool.release(r); }
+        PoolImpl& pool; std::vector<PlaneRow*>* rows = nullptr; bool armed = true;
+        ~ReleaseBorrowed() { if (armed && rows) for (PlaneRow* r : *rows) pool.release(r); }
     } release_borrowed{pool};
+    build.reserve(todo.size()); rows.reserve(todo.size());
     for (size_t i = 0; i < todo.size(); ++i) {
         const int32_t k = todo[i];
         PlaneInfo& pi = cache.planes[(size_t)k];
         if (pi.row) continue;
-        auto have = pool.rows.find(pi.key);
-        if (have != pool.rows.end()) {                           // another grammar built it, or is building it
-            uint32_t* row = have->second;
-            pi.row = row; pi.no_uncertain = pool.no_uncertain.count(row) != 0; pool.take(row, pi.key); ++cache.n_built;
-            auto bt = pool.building.find(row);
-            if (bt != pool.building.end()) {
-                if (std::find(cache.tickets.begin(), cache.tickets.end(), bt->second) == cache.tickets.end()) cache.tickets.push_back(bt->second);
+        if (PlaneRow** have = pool.rows.find(pi.key)) {          // another grammar built it, or is building it
+            PlaneRow* row = *have;
+            pi.row = row; pi.no_uncertain = row->no_uncertain; pool.take(row); ++cache.n_built;
+            if (row->building) {
+                if (cache.tickets.empty() || cache.tickets.back() != row->building)
+                    if (std::find(cache.tickets.begin(), cache.tickets.end(), row->building) == cache.tickets.end()) cache.tickets.push_back(row->building);
                 cache.fresh_planes.push_back(k);
             }
             continue;
         }
-        uint32_t* row = pool.alloc_row(row_bytes, todo.size() - i);
+        PlaneRow* row = pool.alloc_row(pi.key, row_bytes, todo.size() - i);
+        row->build_serial = serial; row->build_index = (uint32_t)build.size();
         build.push_back(k);
-        build_rows.push_back(row);
+        rows.push_back(row);
         pool.rows.emplace(pi.key, row);
     }
     if (build.empty() && !with_tables) { rollback.armed = false; return XG2_OK; }
@@ -823,103 +848,107 @@ int32_t build_planes(CacheImpl& cache, const std::vector<int32_t>& todo, hipStre
     StagingSet& SS = *ticket->staging;
 
     // plan: closed start set and live first-byte ranges of every plane to build
+    const size_t n_build = build.size();
     std::vector<uint32_t> ctx_items, ctx_wait, ctx_wait_off;
     std::vector<uint4> plane_ctx, ranges;
+    plane_ctx.reserve(n_build); ctx_items.reserve(2 * n_build); ranges.reserve(2 * n_build);
     std::vector<CopyJob> copies, structure_copies;
     std::vector<FirstByteCopyJob> fb_copies;
-    std::vector<uint64_t> derive_base(build.size(), 0);          // partial hits: address of the base plane's left-early row
-    std::vector<uint32_t*> borrowed;
+    std::vector<FinishJob> finish(n_build, FinishJob{});
+    std::vector<uint8_t> takes(n_build, 0);                      // the plane takes bits from another plane once it is classed
+    std::vector<uint64_t> derive_base(n_build, 0);               // partial hits: address of the base plane's left-early row
+    std::vector<PlaneRow*> borrowed;
     release_borrowed.rows = &borrowed;
     int64_t executed = 0, executed_bytes = 0;
     EarleyChart chart(&ft);
-    std::map<int32_t, size_t> building;                         // plane index -> position in build
-    for (size_t k = 0; k < build.size(); ++k) building.emplace(build[k], k);
-    for (size_t k = 0; k < build.size(); ++k) {
+    constexpr uint32_t kNone = 0xFFFFFFFFu;
+    // wait entries of a one-item start set: nothing at the top, the waiting parent's entries inside a parent; the same
+    // for every plane with that parent
+    std::vector<uint32_t> wait_of(ft.state_info.size() + 1, kNone);   // [parent state + 1; 0: no parent] -> index into ctx_wait_off
+    // the plane `plane` takes bits from: if it is there or is being built in this call
+    auto source = [&](int32_t plane) -> PlaneRow* {
+        if (plane < 0) return nullptr;
+        const PlaneInfo& q = cache.planes[(size_t)plane];
+        if (q.row) return q.row;
+        PlaneRow** r = pool.rows.find(q.key);
+        return r ? *r : nullptr;
+    };
+    for (size_t k = 0; k < n_build; ++k) {
         const PlaneInfo& pi = cache.planes[(size_t)build[k]];
+        uint32_t* const mem = rows[k]->mem;
         // Partial cache hit (section 3.3): the pool holds a plane of the same structure built under another follow language.
         // Accepted tokens, and the tokens that leave the rule early and die, are the same; only which of the latter stay
         // uncertain depends on what may follow: those are run again, in follow mode, and nothing else is.
         if (cache.follow && cache.partial_hits && pi.key[4] != 0) {
-            auto bs = pool.by_structure.find({pi.key[0], pi.key[1], pi.key[2], pi.key[3]});
-            if (bs != pool.by_structure.end() && bs->second != build_rows[k]) {
-                uint32_t* base = bs->second;
-                pool.take(base, pi.key);                         // not to be evicted while this build reads it
+            PlaneRow** bs = pool.by_structure.find(PoolImpl::structure_of(pi.key));
+            if (bs && *bs != rows[k]) {
+                PlaneRow* base = *bs;
+                pool.take(base);                                 // not to be evicted while this build reads it
                 borrowed.push_back(base);
-                structure_copies.push_back({build_rows[k], base, nullptr, 0});
-                derive_base[k] = (uint64_t)(uintptr_t)(base + 2 * (size_t)V.W);
+                structure_copies.push_back({mem, base->mem, nullptr, 0});
+                derive_base[k] = (uint64_t)(uintptr_t)(base->mem + 2 * (size_t)V.W);
             }
         }
         const bool derived = derive_base[k] != 0;
-        // short tokens from a plane that agrees on them, if that plane is there or is being built in this call
-        uint32_t near_d = 0;
-        if (!derived && pi.near_plane >= 0 && pi.near_depth >= 1 && V.near_depths >= 1) {
-            const uint32_t* src = cache.planes[(size_t)pi.near_plane].row;
-            if (!src) {
-                auto pr = pool.rows.find(cache.planes[(size_t)pi.near_plane].key);
-                auto bi = building.find(pi.near_plane);
-                if (bi != building.end()) src = build_rows[bi->second];
-                else if (pr != pool.rows.end() && pr->second) src = pr->second;
-            }
-            if (src) {
-                near_d = std::min<uint32_t>((uint32_t)pi.near_depth, V.near_depths);
-                copies.push_back({build_rows[k], src, V.d_short_mask.p + (size_t)(near_d - 1) * V.W, 0});
-            }
-        }
-        // or the tokens with most first bytes from the plane of the rule's start state, under the same conditions
+        // short tokens from a plane that agrees on them; or the tokens with most first bytes from the plane of the rule's
+        // start state; or every token that cannot leave the plain states of the rule from the plane of the same state under
+        // another site
+        const VocabImpl::ListStarts* list = nullptr;             // the plane's own tokens come from this list, if from one
         bool by_first_byte = false;
-        if (!derived && !near_d && pi.fb_plane >= 0) {
-            const uint32_t* src = cache.planes[(size_t)pi.fb_plane].row;
-            if (!src) {
-                auto pr = pool.rows.find(cache.planes[(size_t)pi.fb_plane].key);
-                auto bi = building.find(pi.fb_plane);
-                if (bi != building.end()) src = build_rows[bi->second];
-                else if (pr != pool.rows.end() && pr->second) src = pr->second;
-            }
-            if (src) {
-                FirstByteCopyJob job{build_rows[k], src, {}};
-                for (int w = 0; w < 8; ++w) job.bytes[w] = pi.fb_same[(size_t)w];
+        FinishJob& fin = finish[k];
+        if (!derived) {
+            PlaneRow* src = nullptr;
+            if (pi.near_depth >= 1 && V.near_depths >= 1 && (src = source(pi.near_plane))) {
+                const uint32_t near_d = std::min<uint32_t>((uint32_t)pi.near_depth, V.near_depths);
+                list = &V.near_first_byte[near_d];
+                fin.m_src = src->mem; fin.m_mask = V.d_short_mask.p + (size_t)(near_d - 1) * V.W;
+            } else if ((src = source(pi.fb_plane))) {
+                FirstByteCopyJob job{mem, src->mem, {}};
+                for (int w = 0; w < 8; ++w) fin.f_bytes[w] = job.bytes[w] = cache.fb_same[(size_t)pi.fb_same][(size_t)w];
+                fin.f_src = src->mem;
                 fb_copies.push_back(job);
                 by_first_byte = true;
+            } else if ((src = source(pi.site_plane))) {
+                const VocabImpl::ByteSetList& bl = V.byte_lists[(size_t)pi.site_list];
+                list = &bl.first_byte;
+                fin.m_src = src->mem; fin.m_mask = bl.d_without->p;
             }
+            if (fin.m_src) copies.push_back({mem, fin.m_src, fin.m_mask, 0});
+            if (src) { takes[k] = src->build_serial == serial ? 2 : 1; fin.pad[0] = src->build_index; }
         }
-        // or every token that cannot leave the plain states of the rule from the plane of the same state under another site
-        const VocabImpl::ByteSetList* by_list = nullptr;
-        if (!derived && !near_d && !by_first_byte && pi.site_plane >= 0) {
-            const uint32_t* src = cache.planes[(size_t)pi.site_plane].row;
-            if (!src) {
-                auto pr = pool.rows.find(cache.planes[(size_t)pi.site_plane].key);
-                auto bi = building.find(pi.site_plane);
-                if (bi != building.end()) src = build_rows[bi->second];
-                else if (pr != pool.rows.end() && pr->second) src = pr->second;
-            }
-            if (src) {
-                by_list = &V.byte_lists[(size_t)pi.site_list];
-                copies.push_back({build_rows[k], src, by_list->d_without->p, 0});
-            }
-        }
-        if (pi.waiter_sid < 0) chart.start(pi.sid);
-        else chart.start_pair(pi.sid, (uint32_t)pi.waiter_sid);
-        const std::vector<ChartSet>& sets = chart.sets();
-        auto loc = [](int32_t o) { return o < 0 ? kRootOrigin : (uint32_t)o; };
-        bool live[257] = {false};
+        // the closed start set, and the first bytes it can read
+        bool live[257];
         const uint32_t item0 = (uint32_t)ctx_items.size();
-        for (const ChartItem& it : sets.back().scan) {
-            ctx_items.push_back(pack_item(ft.ref(it.sid), loc(it.origin)));
-            const StateInfo& si = ft.state_info[it.sid];
-            for (uint32_t e = 0; e < (si.counts & 0xFFFF); ++e) {
-                const ByteEdge& be = ft.byte_edges[si.byte_off + e];
-                for (uint32_t b = be.lohi & 0xFF; b <= ((be.lohi >> 8) & 0xFF); ++b) live[b] = true;
+        const StateInfo& s0 = ft.state_info[pi.sid];
+        const bool one_item = (s0.counts >> 16) == 0 && !(s0.rule_final >> 31);   // neither predicts nor ends its rule: the item alone
+        if (one_item) {
+            const bool inside = pi.waiter_sid >= 0;
+            ctx_items.push_back(pack_item(ft.ref(pi.sid), inside ? 0u : kRootOrigin));
+            uint32_t& w = wait_of[(size_t)(pi.waiter_sid + 1)];
+            if (w == kNone) {
+                w = (uint32_t)ctx_wait_off.size();
+                ctx_wait_off.push_back((uint32_t)(ctx_wait.size() / 2));
+                if (inside) { chart.push_triples({(uint32_t)pi.waiter_sid, -1}, kRootOrigin, ctx_wait); ctx_wait_off.push_back((uint32_t)(ctx_wait.size() / 2)); }
+                ctx_wait_off.push_back((uint32_t)(ctx_wait.size() / 2));
             }
+            plane_ctx.push_back(make_uint4(item0, 1, w, inside ? 2u : 1u));
+        } else {
+            if (pi.waiter_sid < 0) chart.start(pi.sid);
+            else chart.start_pair(pi.sid, (uint32_t)pi.waiter_sid);
+            const std::vector<ChartSet>& sets = chart.sets();
+            auto loc = [](int32_t o) { return o < 0 ? kRootOrigin : (uint32_t)o; };
+            for (const ChartItem& it : sets.back().scan) ctx_items.push_back(pack_item(ft.ref(it.sid), loc(it.origin)));
+            plane_ctx.push_back(make_uint4(item0, (uint32_t)ctx_items.size() - item0, (uint32_t)ctx_wait_off.size(), (uint32_t)sets.size()));
+            for (const ChartSet& cs : sets) {
+                ctx_wait_off.push_back((uint32_t)(ctx_wait.size() / 2));
+                for (const ChartItem& it : cs.wait) chart.push_triples(it, loc(it.origin), ctx_wait);
+            }
+            ctx_wait_off.push_back((uint32_t)(ctx_wait.size() / 2));
         }
-        plane_ctx.push_back(make_uint4(item0, (uint32_t)ctx_items.size() - item0, (uint32_t)ctx_wait_off.size(), (uint32_t)sets.size()));
         // a start set that is one item with byte edges only is walked as a plain automaton; the others need the
         // Earley steps from the first byte on and go first, so that the long workgroups do not end the launch
-        const uint32_t heavy = (ctx_items.size() - item0 == 1 && (ctx_items[item0] & (kHasByte | kHasRef)) == kHasByte) ? 0u : 1u;
-        for (const ChartSet& cs : sets) {
-            ctx_wait_off.push_back((uint32_t)(ctx_wait.size() / 2));
-            for (const ChartItem& it : cs.wait) chart.push_triples(it, loc(it.origin), ctx_wait);
-        }
-        ctx_wait_off.push_back((uint32_t)(ctx_wait.size() / 2));
+        const uint32_t n_items = (uint32_t)ctx_items.size() - item0;
+        const uint32_t heavy = (n_items == 1 && (ctx_items[item0] & (kHasByte | kHasRef)) == kHasByte) ? 0u : 1u;
         // A start set of at most two items that scan, none of them predicting, where the end of a waited-for instance
         // leads to one state of the outermost instance that does not predict either, is walked as a few automaton
         // threads; the two items and what each one's end leads to follow the plane's items.
@@ -928,7 +957,7 @@ int32_t build_planes(CacheImpl& cache, const std::vector<int32_t>& todo, hipStre
             uint32_t desc[4] = {kNoThread, 0u, kNoThread, 0u};
             uint32_t nb = 0;
             bool ok = true;
-            for (size_t q = item0; q < item0 + plane_ctx.back().y && ok; ++q) {
+            for (size_t q = item0; q < item0 + n_items && ok; ++q) {
                 const uint32_t it = ctx_items[q];
                 if (!(it & kHasByte)) continue;
                 if ((it & kHasRef) || nb == 2) { ok = false; break; }
@@ -954,53 +983,56 @@ int32_t build_planes(CacheImpl& cache, const std::vector<int32_t>& todo, hipStre
             ranges.push_back(make_uint4((uint32_t)k, 0u, V.W, kChunkDerive | kChunkHeavy));
             continue;
         }
-        if (by_first_byte) for (int b = 0; b < 256; ++b) if ((pi.fb_same[(size_t)b >> 5] >> (b & 31)) & 1u) live[b] = false;
+        const uint32_t flags = (list ? kChunkListed : 0u) | threads | (heavy ? kChunkHeavy : 0u);
+        auto add_range = [&](int b, int e) {                        // tokens whose first byte is in b .. e
+            const uint32_t lo = list ? (*list)[(size_t)b] : V.fb_start[b], hi = list ? (*list)[(size_t)e + 1] : V.fb_start[e + 1];
+            if (lo < hi) ranges.push_back(make_uint4((uint32_t)k, lo, hi, flags));
+            executed += hi - lo;
+            executed_bytes += list ? (int64_t)(V.long_bytes[hi] - V.long_bytes[lo]) : (int64_t)(V.s_off[hi] - V.s_off[lo]);
+        };
+        if (one_item && !by_first_byte) {                           // the state's own byte ranges, adjacent ones joined
+            int b = -1, e = -1;
+            for (uint32_t q = 0; q < (s0.counts & 0xFFFF); ++q) {
+                const ByteEdge& be = ft.byte_edges[s0.byte_off + q];
+                const int lo = (int)(be.lohi & 0xFF), hi = (int)((be.lohi >> 8) & 0xFF);
+                if (b >= 0 && lo == e + 1) { e = hi; continue; }
+                if (b >= 0) add_range(b, e);
+                b = lo; e = hi;
+            }
+            if (b >= 0) add_range(b, e);
+            continue;
+        }
+        std::fill(live, live + 257, false);
+        for (uint32_t q = 0; q < n_items; ++q) {
+            const StateInfo& si = ft.state_info[ctx_items[item0 + q] & kSidMask];
+            for (uint32_t e = 0; e < (si.counts & 0xFFFF); ++e) {
+                const ByteEdge& be = ft.byte_edges[si.byte_off + e];
+                for (uint32_t b = be.lohi & 0xFF; b <= ((be.lohi >> 8) & 0xFF); ++b) live[b] = true;
+            }
+        }
+        if (by_first_byte) for (int b = 0; b < 256; ++b) if ((fin.f_bytes[(size_t)b >> 5] >> (b & 31)) & 1u) live[b] = false;
         for (int b = 0; b < 256;) {
             if (!live[b]) { ++b; continue; }
             int e = b;
             while (live[e + 1]) ++e;
-            uint32_t lo = V.fb_start[b], hi = V.fb_start[e + 1], listed = 0;
-            if (near_d || by_list) {                                 // the same ranks, in the list of the tokens longer than near_d / with such bytes
-                const uint32_t* first = V.long_rank.data() + (near_d ? V.long_off[near_d] : by_list->off);
-                const uint32_t* last = V.long_rank.data() + (near_d ? V.long_off[near_d + 1] : by_list->off + by_list->n);
-                lo = (uint32_t)(std::lower_bound(first, last, lo) - V.long_rank.data());
-                hi = (uint32_t)(std::lower_bound(first, last, hi) - V.long_rank.data());
-                listed = kChunkListed;
-            }
-            if (lo < hi) ranges.push_back(make_uint4((uint32_t)k, lo, hi, listed | threads | (heavy ? kChunkHeavy : 0u)));
-            executed += hi - lo;
-            executed_bytes += listed ? (int64_t)(V.long_bytes[hi] - V.long_bytes[lo]) : (int64_t)(V.s_off[hi] - V.s_off[lo]);
+            add_range(b, e);
             b = e + 1;
         }
     }
     // The copies of derived planes and the per-plane summary go in one pass over the planes when no plane takes bits from
     // a plane that itself takes bits in this build (the separate kernels order such chains: masked copies, then
     // first-byte copies, then the summary).
-    std::vector<FinishJob> finish(build_rows.size(), FinishJob{});
-    bool finish_in_one = !build_rows.empty() && build_fusion().load();
-    {
-        std::map<const uint32_t*, size_t> at;
-        for (size_t k = 0; k < build_rows.size(); ++k) at.emplace(build_rows[k], k);
-        std::set<const uint32_t*> takes;
-        for (const CopyJob& j : copies) takes.insert(j.dst);
-        for (const FirstByteCopyJob& j : fb_copies) takes.insert(j.dst);
-        for (const CopyJob& j : copies) {
-            FinishJob& f = finish[at.at(j.dst)];
-            if (f.m_src || takes.count(j.src)) finish_in_one = false;
-            f.m_src = j.src; f.m_mask = j.mask;
-        }
-        for (const FirstByteCopyJob& j : fb_copies) {
-            FinishJob& f = finish[at.at(j.dst)];
-            if (f.f_src || takes.count(j.src)) finish_in_one = false;
-            f.f_src = j.src;
-            for (int w = 0; w < 8; ++w) f.f_bytes[w] = j.bytes[w];
-        }
+    bool finish_in_one = n_build != 0 && build_fusion().load();
+    for (size_t k = 0; k < n_build; ++k) {
+        if (takes[k] == 2 && takes[finish[k].pad[0]]) finish_in_one = false;
+        finish[k].pad[0] = 0;
     }
     // The chunk records are written on the device (k_expand_chunks) from the ranges: per range {plane, first rank, end
     // rank, flags}, the index of its first chunk and what the walk needs of its plane.  Chunks of the heavy ranges come
     // first, then the others, each group in plane order; a long range is cut so that one thread writes at most 32 chunks.
     std::vector<uint4> range_a, range_b;
     std::vector<uint32_t> range_first;
+    range_a.reserve(ranges.size() + 64); range_b.reserve(ranges.size() + 64); range_first.reserve(ranges.size() + 64);
     size_t n_chunks = 0;
     for (uint32_t pass_heavy : {kChunkHeavy, 0u})
         for (const uint4& r : ranges) {
@@ -1008,7 +1040,7 @@ int32_t build_planes(CacheImpl& cache, const std::vector<int32_t>& todo, hipStre
             const bool derive = r.w & kChunkDerive;
             const uint32_t step = derive ? kDeriveChunk : pass_heavy ? kHeavyChunk : kBuildChunk;
             const uint4& pc = plane_ctx[r.x];
-            const uint64_t row = derive ? derive_base[r.x] : (uint64_t)(uintptr_t)build_rows[r.x];
+            const uint64_t row = derive ? derive_base[r.x] : (uint64_t)(uintptr_t)rows[r.x]->mem;
             const uint4 second = derive ? make_uint4(0u, 0u, (uint32_t)row, (uint32_t)(row >> 32))
                                         : make_uint4(ctx_items[pc.x], pc.y, (uint32_t)row, (uint32_t)(row >> 32));
             for (uint32_t lo = r.y; lo < r.z; lo += 32 * step) {
@@ -1020,6 +1052,8 @@ int32_t build_planes(CacheImpl& cache, const std::vector<int32_t>& todo, hipStre
             }
         }
     if (n_chunks > 0xFFFFFFF0ull) throw std::length_error("mask cache build: too many chunks in one launch");
+    std::vector<uint32_t*> build_rows(n_build);
+    for (size_t k = 0; k < n_build; ++k) build_rows[k] = rows[k]->mem;
 
     // everything the device needs goes up in one copy: (the tables,) the plan, and a few zeroed words (overflow
     // counter and flag, bit counts per built plane).  With the tables the block stays with the cache.
@@ -1115,20 +1149,19 @@ int32_t build_planes(CacheImpl& cache, const std::vector<int32_t>& todo, hipStre
     HIP_CHECK(hipGetLastError());
     // from here on the build is under way: the planes have their rows, the ticket says what became of them
     rollback.armed = false;
-    ticket->rows = build_rows;
+    ticket->rows = rows;
     ticket->borrowed = borrowed;
     release_borrowed.armed = false;
     ticket->partial_hits = (int64_t)structure_copies.size();
     ticket->executed = executed; ticket->executed_bytes = executed_bytes;
-    for (size_t k = 0; k < build.size(); ++k) {
+    for (size_t k = 0; k < n_build; ++k) {
         PlaneInfo& pi = cache.planes[(size_t)build[k]];
-        pi.row = build_rows[k];
+        pi.row = rows[k];
         pi.no_uncertain = false;                                    // not known yet
-        pool.take(pi.row, pi.key);
-        pool.building.emplace(pi.row, ticket);
-        ticket->keys.push_back(pi.key);
-        cache.fresh_planes.push_back(build[k]);
+        pool.take(rows[k]);
+        rows[k]->building = ticket;
     }
+    cache.fresh_planes.insert(cache.fresh_planes.end(), build.begin(), build.end());
     cache.n_built += (int64_t)build.size();
     cache.tickets.push_back(ticket);
     pool.pending.push_back(ticket);
@@ -1159,9 +1192,9 @@ int32_t for_frontier_planes(const MatcherImpl& M, F&& visit) {
             for (uint32_t k = 0; k < (wi.counts >> 16); ++k) {
                 const RefEdgeP& e = FT.ref_edges[wi.ref_off + k];
                 if (e.rule != rule) continue;
-                auto pp = M.cache->pair_plane.find(((uint64_t)it.sid << 32) | e.tgt);
-                if (pp == M.cache->pair_plane.end()) return fail(XG2_EINVAL, "xg2_fill_next_token_bitmask: frontier item without a plane");
-                visit(pp->second, false);
+                const int32_t plane = M.cache->pair_plane(it.sid, e.tgt);
+                if (plane < 0) return fail(XG2_EINVAL, "xg2_fill_next_token_bitmask: frontier item without a plane");
+                visit(plane, false);
                 any_parent = true;
             }
         }
@@ -1225,18 +1258,21 @@ void ensure_cache_on_device(const std::shared_ptr<CacheImpl>& cp) {
     const size_t n_states = (size_t)C.gram->g.n_states;
     auto row_word = [&](int32_t plane, bool accepted_only) {
         const PlaneInfo& pi = C.planes[(size_t)plane];
-        return (uint64_t)(uintptr_t)pi.row | ((accepted_only || pi.no_uncertain) ? 1u : 0u);
+        return (uint64_t)(uintptr_t)pi.row->mem | ((accepted_only || pi.no_uncertain) ? 1u : 0u);
     };
     std::vector<uint64_t> plain(n_states, 0);
     for (size_t sid = 0; sid < n_states; ++sid) if (C.plain_plane[sid] >= 0) plain[sid] = row_word(C.plain_plane[sid], false);
-    std::vector<std::array<uint64_t, 3>> pairs;                 // (state, state the referencing rule continues in, row)
-    pairs.reserve(C.pair_plane.size());
-    for (auto& kv : C.pair_plane) pairs.push_back({kv.first >> 32, kv.first & 0xFFFFFFFFull, row_word(kv.second, false)});
-    std::sort(pairs.begin(), pairs.end());
-    std::vector<uint32_t> pair_off(n_states + 1, 0), pair_key(std::max<size_t>(pairs.size(), 1), 0);
-    std::vector<uint64_t> pair_row(std::max<size_t>(pairs.size(), 1), 0);
-    for (size_t k = 0; k < pairs.size(); ++k) { ++pair_off[(size_t)pairs[k][0] + 1]; pair_key[k] = (uint32_t)pairs[k][1]; pair_row[k] = pairs[k][2]; }
-    for (size_t sid = 0; sid < n_states; ++sid) pair_off[sid + 1] += pair_off[sid];
+    std::vector<uint32_t> pair_off(n_states + 1, 0), pair_key;   // per state: its rule's sites, ascending, and the planes under them
+    std::vector<uint64_t> pair_row;
+    for (size_t sid = 0; sid < n_states; ++sid) {
+        const int32_t base = C.pair_base.empty() ? -1 : C.pair_base[sid];
+        if (base >= 0) {
+            const Span<uint32_t> keys = C.site_keys[C.gram->ft.state_info[sid].rule_final & 0x7FFFFFFFu];
+            for (size_t k = 0; k < keys.size(); ++k) { pair_key.push_back(keys[k]); pair_row.push_back(row_word(C.pair_table[(size_t)base + k], false)); }
+        }
+        pair_off[sid + 1] = (uint32_t)pair_key.size();
+    }
+    if (pair_key.empty()) { pair_key.push_back(0); pair_row.push_back(0); }
     // the start state, through the host parser
     MatcherImpl M(C.gram, C.vocab);
     M.cache = cp;
@@ -1254,11 +1290,12 @@ void ensure_cache_on_device(const std::shared_ptr<CacheImpl>& cp) {
     std::vector<uint2> s_wait(M.prep.ctx.wait.size() / 2);
     for (size_t k = 0; k < s_wait.size(); ++k) s_wait[k] = make_uint2(M.prep.ctx.wait[2 * k], M.prep.ctx.wait[2 * k + 1]);
     D.plain_row.upload(plain, nullptr); D.pair_off.upload(pair_off, nullptr); D.pair_key.upload(pair_key, nullptr); D.pair_row.upload(pair_row, nullptr);
+    D.site_rep.upload(C.site_rep, nullptr);
     D.start_items.upload(s_items, nullptr); D.start_front.upload(s_front, nullptr); D.start_wait.upload(s_wait, nullptr);
     D.start_wait_off.upload(M.prep.ctx.wait_off, nullptr);
     HIP_CHECK(hipStreamSynchronize(nullptr));
     D.cd.T = C.dt;
-    D.cd.plain_row = D.plain_row.p; D.cd.pair_off = D.pair_off.p; D.cd.pair_key = D.pair_key.p; D.cd.pair_row = D.pair_row.p;
+    D.cd.plain_row = D.plain_row.p; D.cd.pair_off = D.pair_off.p; D.cd.pair_key = D.pair_key.p; D.cd.pair_row = D.pair_row.p; D.cd.site_rep = D.site_rep.p;
     D.cd.context_depth = (uint32_t)C.context_depth;
     D.cd.start_n_items = (uint32_t)s_items.size(); D.cd.start_H = M.prep.ctx.H; D.cd.start_n_front = (uint32_t)s_front.size();
     D.cd.start_flags = M.chart.last().root_done ? 1u : 0u;
@@ -1426,41 +1463,32 @@ int32_t xg2_compile_grammar(xg2_vocab* vocab, const char* ebnf, size_t len, cons
         // states that tokens cannot tell apart share planes
         std::vector<std::vector<int32_t>> rep, classes;
         std::vector<NearClasses> near((size_t)R);
+        std::vector<std::shared_ptr<const RuleAnalysis>> analysis((size_t)R);
+        const int32_t budget = (int32_t)std::max<uint32_t>(V.max_len, 1);
+        pool.analysis.resize(pool.entries.size());
         if (merge || follow) {
-            const int32_t class_budget = (int32_t)std::max<uint32_t>(V.max_len, 1);
             classes.resize((size_t)R);
             for (int r = 0; r < R; ++r) {
                 const RuleFsm& f = g.rules[(size_t)r];
-                const int n = f.n_states();
-                std::vector<int32_t> by_canon((size_t)n);             // canonical number -> state
-                for (int x = 0; x < n; ++x) by_canon[(size_t)f.canon_id[(size_t)x]] = x;
-                auto key = std::make_pair(entry[(size_t)r], class_budget);
-                auto hit = f.shareable ? pool.class_memo.find(key) : pool.class_memo.end();
-                NearClasses& nr = near[(size_t)r];
-                if (hit != pool.class_memo.end() && (int)hit->second.rep.size() == n) {
-                    // an identical rule was analysed before (this grammar or an earlier one): translate through the canonical numbers
-                    const PoolImpl::ClassMemo& cm = hit->second;
-                    classes[(size_t)r].resize((size_t)n);
-                    nr.base.resize((size_t)n); nr.depth.resize((size_t)n);
-                    for (int x = 0; x < n; ++x) {
-                        const size_t c = (size_t)f.canon_id[(size_t)x];
-                        classes[(size_t)r][(size_t)x] = by_canon[(size_t)cm.rep[c]];
-                        nr.base[(size_t)x] = cm.base[c] < 0 ? -1 : by_canon[(size_t)cm.base[c]];
-                        nr.depth[(size_t)x] = cm.depth[c];
-                    }
-                    continue;
+                const size_t n = (size_t)f.n_states();
+                std::shared_ptr<const RuleAnalysis>& known = pool.analysis[(size_t)entry[(size_t)r]];
+                if (known) analysis[(size_t)r] = known;           // an identical rule was analysed before (this grammar or an earlier one)
+                else {
+                    analysis[(size_t)r] = std::make_shared<const RuleAnalysis>(analyse_rule(g, r, budget, ref_id, pool.nodes));
+                    if (f.shareable) known = analysis[(size_t)r];
                 }
-                classes[(size_t)r] = bounded_classes_rule(g, r, class_budget, ref_id, &nr);
-                if (f.shareable) {
-                    PoolImpl::ClassMemo cm;
-                    cm.rep.resize((size_t)n); cm.base.resize((size_t)n); cm.depth.resize((size_t)n);
-                    for (int x = 0; x < n; ++x) {
-                        const size_t c = (size_t)f.canon_id[(size_t)x];
-                        cm.rep[c] = f.canon_id[(size_t)classes[(size_t)r][(size_t)x]];
-                        cm.base[c] = nr.base[(size_t)x] < 0 ? -1 : f.canon_id[(size_t)nr.base[(size_t)x]];
-                        cm.depth[c] = nr.depth[(size_t)x];
-                    }
-                    pool.class_memo.emplace(key, std::move(cm));
+                // from canonical numbers to this grammar's state numbers
+                const RuleAnalysis& A = *analysis[(size_t)r];
+                std::vector<int32_t> by_canon(n);
+                for (size_t x = 0; x < n; ++x) by_canon[(size_t)f.canon_id[x]] = (int32_t)x;
+                NearClasses& nr = near[(size_t)r];
+                classes[(size_t)r].resize(n);
+                nr.base.resize(n); nr.depth.resize(n);
+                for (size_t x = 0; x < n; ++x) {
+                    const size_t c = (size_t)f.canon_id[x];
+                    classes[(size_t)r][x] = by_canon[(size_t)A.rep[c]];
+                    nr.base[x] = A.near.base[c] < 0 ? -1 : by_canon[(size_t)A.near.base[c]];
+                    nr.depth[x] = A.near.depth[c];
                 }
             }
         }
@@ -1469,90 +1497,105 @@ int32_t xg2_compile_grammar(xg2_vocab* vocab, const char* ebnf, size_t len, cons
             rep.resize((size_t)R);
             for (int r = 0; r < R; ++r) { rep[(size_t)r].resize((size_t)g.rules[(size_t)r].n_states()); std::iota(rep[(size_t)r].begin(), rep[(size_t)r].end(), 0); }
         }
-        FollowInfo follow_info;
-        const int32_t budget = (int32_t)std::max<uint32_t>(V.max_len, 1);
-        // follow signatures are numbers the pool hands out for exact descriptions of the bounded follow language (rules named
-        // by their pool entries): equal numbers, equal structures
-        const FollowInterner intern_follow = [&pool](const std::vector<uint64_t>& desc) -> uint64_t {
-            auto it = pool.follow_nodes.find(desc);
-            if (it != pool.follow_nodes.end()) return it->second;
-            const uint64_t id = ((uint64_t)pool.follow_nodes.size() + 1) << 1;      // even: the key sets bit 0, and 0 stays "unfiltered"
-            pool.follow_nodes.emplace(desc, id);
-            return id;
-        };
-        const FollowMemo follow_memo = [&](int rule, int state, int d) -> uint64_t* {
-            const RuleFsm& f = g.rules[(size_t)rule];
-            if (!f.shareable) return nullptr;
-            std::vector<uint64_t>& slots = pool.follow_unfold[entry[(size_t)rule]];
-            const size_t n = (size_t)f.n_states();
-            if (slots.size() != ((size_t)budget + 1) * n) slots.assign(((size_t)budget + 1) * n, 0);
-            return &slots[(size_t)d * n + (size_t)f.canon_id[(size_t)state]];
-        };
-        if (follow) follow_info = follow_signatures(g, budget, &classes, &ref_id, &intern_follow, &follow_memo);
-        // reference sites of every rule, one representative per class of the state the referencing rule continues in
-        struct Site { int32_t q, waiter, x; };
-        std::vector<std::vector<Site>> sites((size_t)R);            // all sites
-        std::vector<std::map<std::pair<int, int>, Site>> site_rep((size_t)R);   // (q, class of x) -> representative
-        if (depth == 2)
+        std::unique_ptr<FollowSigs> follow_sigs;
+        if (follow) follow_sigs.reset(new FollowSigs(g, budget, analysis, classes, pool.nodes));
+        // Reference sites of every rule, one per class of the states referencing rules continue in (in the order they are
+        // met; `key` numbers them by the state that stands for the class), each with the member of the smallest canonical id.
+        struct Site { int32_t q, waiter, x; uint32_t key; };
+        Rows<Site> sites;
+        cache->site_rep.resize((size_t)g.n_states);
+        for (int q = 0; q < R; ++q)
+            for (int x = 0; x < g.rules[(size_t)q].n_states(); ++x) cache->site_rep[(size_t)g.sid(q, x)] = (uint32_t)g.sid(q, rep[(size_t)q][(size_t)x]);
+        if (depth == 2) {
+            struct Ref { int32_t q, s, tgt; };
+            std::vector<uint32_t> off((size_t)R + 1, 0);
+            for (const RuleFsm& f : g.rules) for (const RefEdge& e : f.redges.v) ++off[(size_t)e.rule + 1];
+            for (int r = 0; r < R; ++r) off[(size_t)r + 1] += off[(size_t)r];
+            std::vector<Ref> by_rule(off[(size_t)R]);
+            std::vector<uint32_t> at(off.begin(), off.end() - 1);
             for (int q = 0; q < R; ++q)
                 for (int s = 0; s < g.rules[(size_t)q].n_states(); ++s)
-                    for (auto& e : g.rules[(size_t)q].redges[(size_t)s]) {
-                        Site st{q, s, e.tgt};
-                        sites[(size_t)e.rule].push_back(st);
-                        auto key = std::make_pair(q, (int)rep[(size_t)q][(size_t)e.tgt]);
-                        auto it = site_rep[(size_t)e.rule].find(key);
-                        const RuleFsm& fq = g.rules[(size_t)q];
-                        if (it == site_rep[(size_t)e.rule].end()) site_rep[(size_t)e.rule].emplace(key, st);
-                        else if (fq.canon_id[(size_t)e.tgt] < fq.canon_id[(size_t)it->second.x]) it->second = st;
+                    for (auto& e : g.rules[(size_t)q].refs(s)) by_rule[at[(size_t)e.rule]++] = {q, s, e.tgt};
+            std::vector<uint32_t> slot((size_t)g.n_states, 0);      // [class] -> 1 + its site in `sites`, if in the current rule's row
+            for (int r = 0; r < R; ++r) {
+                const uint32_t first = sites.off.back();
+                for (uint32_t k = off[(size_t)r]; k < off[(size_t)r + 1]; ++k) {
+                    const Ref& e = by_rule[k];
+                    const uint32_t key = cache->site_rep[(size_t)g.sid(e.q, e.tgt)];
+                    const uint32_t have = slot[key];
+                    if (have <= first) { sites.v.push_back({e.q, e.s, e.tgt, key}); slot[key] = (uint32_t)sites.v.size(); }
+                    else {
+                        Site& st = sites.v[have - 1];
+                        const RuleFsm& fq = g.rules[(size_t)e.q];
+                        if (fq.canon_id[(size_t)e.tgt] < fq.canon_id[(size_t)st.x]) st = {e.q, e.s, e.tgt, key};
                     }
+                }
+                sites.end_row();
+                const size_t k0 = cache->site_keys.v.size();
+                for (const Site& st : sites[(size_t)r]) cache->site_keys.v.push_back(st.key);
+                std::sort(cache->site_keys.v.begin() + (long)k0, cache->site_keys.v.end());
+                cache->site_keys.end_row();
+            }
+        }
 
         // planes of this grammar
-        std::map<PlaneKey, int32_t> local_plane;
-        auto make_key = [&](int rp, int sp_rep, int site_q, int site_x) -> PlaneKey {
+        FlatMap<PlaneKey, int32_t, PlaneKeyHash> local_plane;
+        auto plane_for = [&](int rp, int sp_rep, const Site* site, int32_t site_index, uint64_t cost) -> int32_t {
             const RuleFsm& fp = g.rules[(size_t)rp];
             PlaneKey key{entry[(size_t)rp], fp.canon_id[(size_t)sp_rep], -1, -1, 0};
-            if (site_q >= 0) { key[2] = entry[(size_t)site_q]; key[3] = g.rules[(size_t)site_q].canon_id[(size_t)site_x]; }
+            if (site) { key[2] = entry[(size_t)site->q]; key[3] = g.rules[(size_t)site->q].canon_id[(size_t)site->x]; }
             if (follow) {
                 // a token reaches what follows the outermost rule only after the shortest way out of the plane's rules, so
                 // the plane depends on the follow language no deeper than the bytes that are left then: planes whose way out
                 // is long are shared between grammars that differ only further on
-                int64_t need = follow_info.min_suf[(size_t)rp][(size_t)sp_rep];
-                if (site_q >= 0) need += follow_info.min_suf[(size_t)site_q][(size_t)site_x];
+                int64_t need = fp.min_suf[(size_t)sp_rep];
+                if (site) need += g.rules[(size_t)site->q].min_suf[(size_t)site->x];
                 const int64_t depth_left = std::max<int64_t>(0, (int64_t)budget - std::max<int64_t>(1, need));
-                key[4] = (int64_t)(follow_info.sig[(size_t)(site_q >= 0 ? site_q : rp)][(size_t)depth_left] | 1);
+                key[4] = (int64_t)follow_sigs->sig(site ? site->q : rp, (int)depth_left);
             }
-            return key;
-        };
-        auto plane_for = [&](int rp, int sp_rep, const Site* site) -> int32_t {
-            const PlaneKey key = make_key(rp, sp_rep, site ? site->q : -1, site ? site->x : -1);
-            auto lp = local_plane.find(key);
-            if (lp != local_plane.end()) return lp->second;
-            const uint32_t sid = (uint32_t)g.sid(rp, sp_rep);
-            // cost estimate: tokens that start with a byte the state itself reads, weighted up when the start set
-            // is more than a plain automaton state
-            const StateInfo& si = ft.state_info[sid];
-            uint64_t cost = 0;
-            for (uint32_t e = 0; e < (si.counts & 0xFFFF); ++e) {
-                const ByteEdge& be = ft.byte_edges[si.byte_off + e];
-                cost += V.fb_start[((be.lohi >> 8) & 0xFF) + 1] - V.fb_start[be.lohi & 0xFF];
-            }
-            if ((si.counts >> 16) || (si.rule_final >> 31)) cost *= 4;
-            int32_t idx = (int32_t)cache->planes.size();
-            cache->planes.push_back({rp, sp_rep, site ? site->q : -1, site ? site->x : -1, nullptr, false, key, sid,
-                                     site ? (int64_t)g.sid(site->q, site->waiter) : -1, cost});
-            local_plane.emplace(key, idx);
-            return idx;
+            const auto lp = local_plane.emplace(key, (int32_t)cache->planes.size());
+            if (!lp.second) return *lp.first;
+            cache->planes.push_back({rp, sp_rep, site ? site->q : -1, site ? site->x : -1, nullptr, false, key, (uint32_t)g.sid(rp, sp_rep),
+                                     site ? (int64_t)g.sid(site->q, site->waiter) : -1, site_index, cost});
+            return *lp.first;
         };
         cache->plain_plane.assign((size_t)g.n_states, -1);
+        if (depth == 2) cache->pair_base.assign((size_t)g.n_states, -1);
         for (const Position& ps : g.positions) {
-            int sp_rep = rep[(size_t)ps.rule][(size_t)ps.state];
-            if (depth == 1 || ps.rule == g.root) cache->plain_plane[(size_t)ps.sid] = plane_for(ps.rule, sp_rep, nullptr);
-            if (depth == 2)
-                for (const Site& st : sites[(size_t)ps.rule]) {
-                    const Site& sr = site_rep[(size_t)ps.rule].at(std::make_pair(st.q, (int)rep[(size_t)st.q][(size_t)st.x]));
-                    cache->pair_plane[((uint64_t)(uint32_t)ps.sid << 32) | (uint32_t)g.sid(st.q, st.x)] = plane_for(ps.rule, sp_rep, &sr);
+            const int sp_rep = rep[(size_t)ps.rule][(size_t)ps.state];
+            const size_t rep_sid = (size_t)g.sid(ps.rule, sp_rep);
+            const bool plain = depth == 1 || ps.rule == g.root, paired = depth == 2 && !sites[(size_t)ps.rule].empty();
+            if ((plain && cache->plain_plane[rep_sid] < 0) || (paired && cache->pair_base[rep_sid] < 0)) {
+                // cost estimate: tokens that start with a byte the state itself reads, weighted up when the start set
+                // is more than a plain automaton state
+                const StateInfo& si = ft.state_info[rep_sid];
+                uint64_t cost = 0;
+                for (uint32_t e = 0; e < (si.counts & 0xFFFF); ++e) {
+                    const ByteEdge& be = ft.byte_edges[si.byte_off + e];
+                    cost += V.fb_start[((be.lohi >> 8) & 0xFF) + 1] - V.fb_start[be.lohi & 0xFF];
                 }
+                if ((si.counts >> 16) || (si.rule_final >> 31)) cost *= 4;
+                if (plain) cache->plain_plane[rep_sid] = plane_for(ps.rule, sp_rep, nullptr, -1, cost);
+                if (paired) {
+                    const Span<uint32_t> keys = cache->site_keys[(size_t)ps.rule];
+                    const size_t base = cache->pair_table.size();
+                    cache->pair_base[rep_sid] = (int32_t)base;
+                    cache->pair_table.resize(base + keys.size());
+                    for (const Site& st : sites[(size_t)ps.rule]) {
+                        const int32_t k = (int32_t)(std::lower_bound(keys.begin(), keys.end(), st.key) - keys.begin());
+                        cache->pair_table[base + (size_t)k] = plane_for(ps.rule, sp_rep, &st, k, cost);
+                    }
+                }
+            }
+            if (plain) cache->plain_plane[(size_t)ps.sid] = cache->plain_plane[rep_sid];
+            if (paired) cache->pair_base[(size_t)ps.sid] = cache->pair_base[rep_sid];
         }
+        // the plane of another state of the plane's rule in the same context, or -1
+        auto sibling = [&](const PlaneInfo& pi, int state) -> int32_t {
+            const size_t sid = (size_t)g.sid(pi.rule, state);
+            if (pi.site < 0) return cache->plain_plane[sid];
+            return cache->pair_base[sid] < 0 ? -1 : cache->pair_table[(size_t)(cache->pair_base[sid] + pi.site)];
+        };
 
         // planes that coincide with another plane of the same rule and context on all short tokens (section 3.6: the states
         // near the end of a long repetition differ from the ones inside it only on tokens long enough to reach the bound)
@@ -1560,10 +1603,8 @@ int32_t xg2_compile_grammar(xg2_vocab* vocab, const char* ebnf, size_t len, cons
             for (PlaneInfo& pi : cache->planes) {
                 const NearClasses& nr = near[(size_t)pi.rule];
                 if (nr.base.empty() || nr.base[(size_t)pi.state] < 0) continue;
-                auto lp = local_plane.find(make_key(pi.rule, nr.base[(size_t)pi.state], pi.parent_rule, pi.parent_state));
-                if (lp == local_plane.end()) continue;
-                pi.near_plane = lp->second;
-                pi.near_depth = nr.depth[(size_t)pi.state];
+                pi.near_plane = sibling(pi, nr.base[(size_t)pi.state]);
+                if (pi.near_plane >= 0) pi.near_depth = nr.depth[(size_t)pi.state];
             }
 
         // Planes of plain automaton states (byte edges only) that move like the start state of their rule on most first
@@ -1573,44 +1614,46 @@ int32_t xg2_compile_grammar(xg2_vocab* vocab, const char* ebnf, size_t len, cons
         if (merge) {
             std::vector<uint8_t> is_near_base(cache->planes.size(), 0);
             for (const PlaneInfo& pi : cache->planes) if (pi.near_plane >= 0) is_near_base[(size_t)pi.near_plane] = 1;
-            auto plain = [&](const RuleFsm& f, int x) { return f.redges[(size_t)x].empty() && !f.bedges[(size_t)x].empty(); };
-            struct FirstByteAlike { std::array<uint32_t, 8> same; bool worth; };
-            std::vector<FirstByteAlike> fb_memo;
-            std::vector<std::vector<int32_t>> fb_of((size_t)R);      // per rule and state: index into fb_memo, or -1
+            auto plain = [&](const RuleFsm& f, int x) { return f.refs(x).empty() && !f.bedges(x).empty(); };
+            constexpr int32_t kNotWorth = -1, kNotCompared = -2;
+            std::vector<int32_t> fb_of((size_t)g.n_states, kNotCompared);   // the comparison depends on the state only, not on the site
             for (size_t idx = 0; idx < cache->planes.size(); ++idx) {
                 PlaneInfo& pi = cache->planes[idx];
                 if (pi.near_plane >= 0 || is_near_base[idx]) continue;
                 const RuleFsm& f = g.rules[(size_t)pi.rule];
-                const int x = pi.state, b0 = rep[(size_t)pi.rule][0];
+                const std::vector<int32_t>& rp = rep[(size_t)pi.rule];
+                const int x = pi.state, b0 = rp[0];
                 // (a state that can end its rule brings the continuation of the referencing rule into its start set: the
                 // same one for both states if both can end, none if neither can)
-                if (x == b0 || !plain(f, x) || !plain(f, b0) || f.is_final[(size_t)x] != f.is_final[(size_t)b0]) continue;
-                // the comparison depends on the state only, not on the site: done once per state
-                std::vector<int32_t>& of = fb_of[(size_t)pi.rule];
-                if (of.empty()) of.assign((size_t)f.n_states(), -1);
-                if (of[(size_t)x] < 0) {
-                    int32_t tx[256], ty[256];
-                    std::fill(tx, tx + 256, -1); std::fill(ty, ty + 256, -1);
-                    for (auto& e : f.bedges[(size_t)x]) for (int b = e.lo; b <= e.hi; ++b) tx[b] = rep[(size_t)pi.rule][(size_t)e.tgt];
-                    for (auto& e : f.bedges[(size_t)b0]) for (int b = e.lo; b <= e.hi; ++b) ty[b] = rep[(size_t)pi.rule][(size_t)e.tgt];
+                if (x == b0 || !plain(f, x) || !plain(f, b0) || f.is_final(x) != f.is_final(b0)) continue;
+                int32_t& of = fb_of[pi.sid];
+                if (of == kNotCompared) {
+                    // both edge lists side by side: per stretch of bytes, where each of the two states goes (-1: nowhere)
                     uint64_t differ = 0, all = 0;
-                    FirstByteAlike fa{};
-                    for (int b = 0; b < 256; ++b) {
-                        const uint64_t n_b = V.fb_start[b + 1] - V.fb_start[b];
-                        if (tx[b] == ty[b]) fa.same[(size_t)b >> 5] |= 1u << (b & 31);
-                        else if (tx[b] >= 0) differ += n_b;
-                        if (tx[b] >= 0) all += n_b;
+                    std::array<uint32_t, 8> same{};
+                    const Span<ByteRange> ex = f.bedges(x), ey = f.bedges(b0);
+                    size_t ix = 0, iy = 0;
+                    for (int b = 0; b < 256;) {
+                        while (ix < ex.size() && (int)ex[ix].hi < b) ++ix;
+                        while (iy < ey.size() && (int)ey[iy].hi < b) ++iy;
+                        int end = 255;                               // last byte of the stretch
+                        int32_t tx = -1, ty = -1;
+                        if (ix < ex.size()) { if ((int)ex[ix].lo <= b) { tx = rp[(size_t)ex[ix].tgt]; end = std::min<int>(end, ex[ix].hi); } else end = std::min<int>(end, ex[ix].lo - 1); }
+                        if (iy < ey.size()) { if ((int)ey[iy].lo <= b) { ty = rp[(size_t)ey[iy].tgt]; end = std::min<int>(end, ey[iy].hi); } else end = std::min<int>(end, ey[iy].lo - 1); }
+                        const uint64_t n_b = V.fb_start[end + 1] - V.fb_start[b];
+                        if (tx == ty) for (int c = b; c <= end; ++c) same[(size_t)c >> 5] |= 1u << (c & 31);
+                        else if (tx >= 0) differ += n_b;
+                        if (tx >= 0) all += n_b;
+                        b = end + 1;
                     }
-                    fa.worth = differ * 2 <= all;                    // else too little to gain
-                    of[(size_t)x] = (int32_t)fb_memo.size();
-                    fb_memo.push_back(fa);
+                    of = kNotWorth;
+                    if (differ * 2 <= all) { of = (int32_t)cache->fb_same.size(); cache->fb_same.push_back(same); }   // else too little to gain
                 }
-                const FirstByteAlike* memo = &fb_memo[(size_t)of[(size_t)x]];
-                if (!memo->worth) continue;
-                auto lp = local_plane.find(make_key(pi.rule, b0, pi.parent_rule, pi.parent_state));
-                if (lp == local_plane.end() || cache->planes[(size_t)lp->second].near_plane >= 0) continue;
-                pi.fb_plane = lp->second;
-                pi.fb_same = memo->same;
+                if (of == kNotWorth) continue;
+                const int32_t base = sibling(pi, b0);
+                if (base < 0 || cache->planes[(size_t)base].near_plane >= 0) continue;
+                pi.fb_plane = base;
+                pi.fb_same = of;
             }
         }
 
@@ -1624,35 +1667,36 @@ int32_t xg2_compile_grammar(xg2_vocab* vocab, const char* ebnf, size_t len, cons
                 if (pi.near_plane >= 0) is_base[(size_t)pi.near_plane] = 1;
                 if (pi.fb_plane >= 0) is_base[(size_t)pi.fb_plane] = 1;
             }
-            std::map<std::pair<int32_t, int32_t>, std::vector<int32_t>> groups;      // (rule, state) -> planes with a site
-            for (size_t idx = 0; idx < cache->planes.size(); ++idx) {
-                const PlaneInfo& pi = cache->planes[idx];
-                if (pi.parent_rule < 0 || pi.near_plane >= 0 || pi.fb_plane >= 0 || is_base[idx]) continue;
-                const RuleFsm& f = g.rules[(size_t)pi.rule];
-                if (!f.redges[(size_t)pi.state].empty() || f.is_final[(size_t)pi.state] || f.bedges[(size_t)pi.state].empty()) continue;
-                groups[std::make_pair(pi.rule, pi.state)].push_back((int32_t)idx);
-            }
-            for (auto& kv : groups) {
-                if (kv.second.size() < 2) continue;
-                const RuleFsm& f = g.rules[(size_t)kv.first.first];
+            std::vector<int32_t> group;                             // eligible planes of one (rule, state): they are numbered one after the other
+            std::vector<uint8_t> seen;
+            std::vector<int> stack;
+            for (size_t idx = 0; idx < cache->planes.size();) {
+                const int32_t rule = cache->planes[idx].rule, state = cache->planes[idx].state;
+                const RuleFsm& f = g.rules[(size_t)rule];
+                group.clear();
+                for (; idx < cache->planes.size() && cache->planes[idx].rule == rule && cache->planes[idx].state == state; ++idx) {
+                    const PlaneInfo& pi = cache->planes[idx];
+                    if (pi.parent_rule >= 0 && pi.near_plane < 0 && pi.fb_plane < 0 && !is_base[idx]) group.push_back((int32_t)idx);
+                }
+                if (group.size() < 2 || !f.refs(state).empty() || f.is_final(state) || f.bedges(state).empty()) continue;
                 // plain states that cannot end the rule, reachable from the state; bytes that lead out of them
                 std::array<uint32_t, 8> out{};
-                std::vector<uint8_t> seen((size_t)f.n_states(), 0);
-                std::vector<int> stack{kv.first.second};
-                seen[(size_t)kv.first.second] = 1;
+                seen.assign((size_t)f.n_states(), 0);
+                stack.assign(1, state);
+                seen[(size_t)state] = 1;
                 while (!stack.empty()) {
                     const int q = stack.back(); stack.pop_back();
-                    for (auto& e : f.bedges[(size_t)q]) {
-                        const bool inside = f.redges[(size_t)e.tgt].empty() && !f.is_final[(size_t)e.tgt];
+                    for (auto& e : f.bedges(q)) {
+                        const bool inside = f.refs(e.tgt).empty() && !f.is_final(e.tgt);
                         if (!inside) { for (int b = e.lo; b <= e.hi; ++b) out[(size_t)b >> 5] |= 1u << (b & 31); }
                         else if (!seen[(size_t)e.tgt]) { seen[(size_t)e.tgt] = 1; stack.push_back(e.tgt); }
                     }
                 }
                 const int32_t list = V.list_of_tokens_with(out);
-                if ((uint64_t)V.byte_lists[(size_t)list].n * 2 > cache->planes[(size_t)kv.second[0]].cost) continue;   // too little to gain
-                for (size_t k = 1; k < kv.second.size(); ++k) {
-                    PlaneInfo& pi = cache->planes[(size_t)kv.second[k]];
-                    pi.site_plane = kv.second[0];
+                if ((uint64_t)V.byte_lists[(size_t)list].n * 2 > cache->planes[(size_t)group[0]].cost) continue;   // too little to gain
+                for (size_t k = 1; k < group.size(); ++k) {
+                    PlaneInfo& pi = cache->planes[(size_t)group[k]];
+                    pi.site_plane = group[0];
                     pi.site_list = list;
                 }
             }
@@ -1665,7 +1709,7 @@ int32_t xg2_compile_grammar(xg2_vocab* vocab, const char* ebnf, size_t len, cons
             std::vector<std::vector<uint32_t>> by_rule((size_t)R);
             for (int q = 0; q < R; ++q)
                 for (int s = 0; s < g.rules[(size_t)q].n_states(); ++s)
-                    for (auto& e : g.rules[(size_t)q].redges[(size_t)s])
+                    for (auto& e : g.rules[(size_t)q].refs(s))
                         by_rule[(size_t)e.rule].push_back(ft.ref((uint32_t)g.sid(q, classes[(size_t)q][(size_t)e.tgt])));
             for (auto& v : by_rule) {
                 std::sort(v.begin(), v.end());
@@ -1773,8 +1817,8 @@ int32_t xg2_mask_cache_find_plane(const xg2_mask_cache* c, const char* rule, int
     if (!parent_rule) { *k = c->p->plain_plane[(size_t)g.sid(rp, state)]; return XG2_OK; }
     int rq = find_rule(parent_rule);
     if (rq < 0 || parent_state < 0 || parent_state >= g.rules[(size_t)rq].n_states()) return fail(XG2_EINVAL, "xg2_mask_cache_find_plane: unknown parent rule or state");
-    auto it = c->p->pair_plane.find(((uint64_t)(uint32_t)g.sid(rp, state) << 32) | (uint32_t)g.sid(rq, parent_state));
-    if (it != c->p->pair_plane.end()) *k = it->second;
+    for (const RefEdge& e : g.rules[(size_t)rq].redges.v)            // only states that rq continues in after rp are sites
+        if (e.rule == rp && e.tgt == parent_state) { *k = c->p->pair_plane((uint32_t)g.sid(rp, state), (uint32_t)g.sid(rq, parent_state)); break; }
     return XG2_OK;
 }
 int32_t xg2_mask_cache_get_planes(const xg2_mask_cache* c, int32_t k, int32_t* accepted_host, int32_t* uncertain_host) {
@@ -1783,7 +1827,8 @@ int32_t xg2_mask_cache_get_planes(const xg2_mask_cache* c, int32_t k, int32_t* a
         const uint32_t W = c->p->vocab->W;
         finalize_cache(*const_cast<CacheImpl*>(c->p.get()));
         if (c->p->failed) return cache_failed();
-        const uint32_t* row = c->p->planes[(size_t)k].row;
+        const PlaneRow* pr = c->p->planes[(size_t)k].row;
+        const uint32_t* row = pr ? pr->mem : nullptr;
         if (!row) return fail(XG2_EINVAL, "xg2_mask_cache_get_planes: this plane has not been built yet (cache compiled just in time)");
         HIP_CHECK(hipDeviceSynchronize());
         if (accepted_host) HIP_CHECK(hipMemcpy(accepted_host, row, W * sizeof(uint32_t), hipMemcpyDeviceToHost));
@@ -2003,7 +2048,7 @@ int32_t fill_common(xg2_matcher* const* matchers, int32_t B, int32_t* bitmask_de
             size_t f0 = front.size();
             for (auto& pl : M.prep.planes) {
                 const PlaneInfo& pi = M.cache->planes[(size_t)pl.first];
-                uint64_t row = (uint64_t)(uintptr_t)pi.row | ((pl.second || pi.no_uncertain) ? 1u : 0u);
+                uint64_t row = (uint64_t)(uintptr_t)pi.row->mem | ((pl.second || pi.no_uncertain) ? 1u : 0u);
                 if (std::find(front.begin() + (long)f0, front.end(), row) == front.end()) front.push_back(row);
             }
             r.front_n = (uint32_t)(front.size() - f0);

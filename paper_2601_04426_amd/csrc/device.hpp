@@ -158,8 +158,9 @@ struct CacheDev {
     DevTables T;
     const uint64_t* plain_row;           // [n_states] plane of a position without context (root rule, or context depth 1), 0 = none
     const uint32_t* pair_off;            // [n_states + 1] CSR over states: the planes of the state under its referencing sites
-    const uint32_t* pair_key;            //   state id the referencing rule continues in, ascending within a state
+    const uint32_t* pair_key;            //   state id the referencing rule continues in (its class: site_rep), ascending within a state
     const uint64_t* pair_row;
+    const uint32_t* site_rep;            // [n_states] the state that stands for each state's class as a site; null: every state for itself
     uint32_t context_depth;
     uint32_t start_n_items, start_H, start_n_front, start_flags;
     const uint32_t* start_items; const uint2* start_wait; const uint32_t* start_wait_off; const uint64_t* start_front;

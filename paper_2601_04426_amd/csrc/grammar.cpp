@@ -54,11 +54,14 @@ void append_utf8(std::string& out, uint32_t cp) {
     }
 }
 
+using RuleIndex = std::unordered_map<std::string, int>;         // rule name -> declaration index
+
 class Parser {
   public:
     explicit Parser(const std::string& s) : s_(s) {}
 
-    void parse(std::vector<std::string>& order, std::map<std::string, Node>& rules) {
+    // rules[k] is the body of order[k]; index: name -> k
+    void parse(std::vector<std::string>& order, std::vector<Node>& rules, RuleIndex& index) {
         while (peek() != 0) {
             std::string nm;
             if (!name(nm)) fail("rule name expected");
@@ -70,9 +73,9 @@ class Parser {
             if (name(head) && head == "TagDispatch" && peek() == '(') body = tagdispatch();
             else { i_ = save; body = alternation(); }
             if (peek() != 0 && !at_rule_head()) fail("unexpected text after rule body");
-            if (rules.count(nm)) fail("rule " + nm + " defined twice");
+            if (!index.emplace(nm, (int)order.size()).second) fail("rule " + nm + " defined twice");
             order.push_back(nm);
-            rules.emplace(nm, std::move(body));
+            rules.push_back(std::move(body));
         }
     }
 
@@ -107,11 +110,13 @@ class Parser {
         }
         return false;
     }
-    bool at_rule_head() {
-        size_t save = i_;
-        std::string nm;
-        bool ok = false;
-        if (name(nm)) { skip(); ok = s_.compare(i_, 3, "::=") == 0; }
+    bool at_rule_head() {                                       // asked before every term: looks without copying the name
+        skip();
+        if (i_ >= s_.size() || !name_start(s_[i_])) return false;
+        const size_t save = i_;
+        while (i_ < s_.size() && name_cont(s_[i_])) ++i_;
+        skip();
+        const bool ok = s_.compare(i_, 3, "::=") == 0;
         i_ = save;
         return ok;
     }
@@ -365,7 +370,7 @@ struct Nfa {
     void rule(int a, int r, int b) { e[(size_t)a].push_back({2, ByteSet(), r, b}); }
 };
 
-void build_nfa(const Node& nd, Nfa& nfa, int s, int e, const std::map<std::string, int>& index) {
+void build_nfa(const Node& nd, Nfa& nfa, int s, int e, const RuleIndex& index) {
     switch (nd.k) {
         case NK::Lit: {
             std::string data;
@@ -531,7 +536,7 @@ Dfa subset_construction(const Nfa& nfa, int start, int end) {
 // failure links, transitions completed so that every byte is free text; completing a tag leads to
 // a state whose only edge is the tag's rule and returns to the trie root; completing a stop string
 // leads to the single final exit state.  Without stop strings every dispatching state is final.
-Dfa tagdispatch_automaton(const Node& nd, const std::map<std::string, int>& index) {
+Dfa tagdispatch_automaton(const Node& nd, const RuleIndex& index) {
     std::vector<std::string> pats;
     for (auto& t : nd.tags) pats.push_back(t.first);
     for (auto& s : nd.stops) pats.push_back(s);
@@ -756,33 +761,37 @@ Dfa minimise_canonical(const Dfa& in, const std::string& rule_name) {
 // structural hashing (Algorithm 1, Algorithm 2)
 constexpr uint64_t NODE_TAG = 0xA1, RANGE_TAG = 0xB2, REF_TAG = 0xC3;
 
-void put_u64(std::string& s, uint64_t v) { for (int k = 0; k < 8; ++k) s.push_back((char)((v >> (8 * k)) & 0xFF)); }
-
 // Algorithm 1 on one rule.  ref_hash[r] = hash of referenced rule r (kInCycleRef for the unresolved
 // in-cycle reference).  Fills canon_id and redges_by_hash, returns the hash.
 uint64_t hash_one_fsm(RuleFsm& f, const std::vector<uint64_t>& ref_hash) {
-    int n = f.n_states();
+    const int n = f.n_states();
     // phase 1: out-edges sorted (ranges by (min,max); references by hash), BFS canonical ids
-    f.redges_by_hash.assign((size_t)n, {});
-    for (int s = 0; s < n; ++s) {
-        f.redges_by_hash[(size_t)s] = f.redges[(size_t)s];
-        std::stable_sort(f.redges_by_hash[(size_t)s].begin(), f.redges_by_hash[(size_t)s].end(),
-                         [&](const RefEdge& a, const RefEdge& b) { return ref_hash[(size_t)a.rule] < ref_hash[(size_t)b.rule]; });
-    }
-    f.canon_id.assign((size_t)n, -1);
-    std::vector<int> order{0};
-    f.canon_id[0] = 0;
-    for (size_t k = 0; k < order.size(); ++k) {
-        int s = order[k];
-        auto visit = [&](int t) { if (f.canon_id[(size_t)t] < 0) { f.canon_id[(size_t)t] = (int)order.size(); order.push_back(t); } };
-        for (auto& e : f.bedges[(size_t)s]) visit(e.tgt);       // already sorted by (lo, hi)
-        for (auto& e : f.redges_by_hash[(size_t)s]) visit(e.tgt);
+    f.redges_by_hash = f.redges;
+    f.canon_id.resize((size_t)n);
+    std::vector<int> order((size_t)n);
+    if (f.body->single_refs) {
+        // With at most one reference a state there is nothing to sort, and the automaton is numbered in this very order
+        // already (minimise_canonical: targets by ascending smallest byte, then the reference).
+        for (int s = 0; s < n; ++s) order[(size_t)s] = f.canon_id[(size_t)s] = s;
+    } else {
+        for (int s = 0; s < n; ++s)
+            std::stable_sort(f.redges_by_hash.v.begin() + f.redges_by_hash.off[(size_t)s], f.redges_by_hash.v.begin() + f.redges_by_hash.off[(size_t)s + 1],
+                             [&](const RefEdge& a, const RefEdge& b) { return ref_hash[(size_t)a.rule] < ref_hash[(size_t)b.rule]; });
+        std::fill(f.canon_id.begin(), f.canon_id.end(), -1);
+        int m = 0;
+        auto visit = [&](int t) { if (f.canon_id[(size_t)t] < 0) { f.canon_id[(size_t)t] = m; order[(size_t)m++] = t; } };
+        visit(0);
+        for (int k = 0; k < m; ++k) {
+            const int s = order[(size_t)k];
+            for (auto& e : f.bedges(s)) visit(e.tgt);               // already sorted by (lo, hi)
+            for (auto& e : f.redges_by_hash[(size_t)s]) visit(e.tgt);
+        }
     }
     // phase 2
     uint64_t h = 0;
     for (int s : order) {
-        h = hash_combine(hash_combine(h, NODE_TAG), f.is_final[(size_t)s]);
-        for (auto& e : f.bedges[(size_t)s])
+        h = hash_combine(hash_combine(h, NODE_TAG), f.is_final(s));
+        for (auto& e : f.bedges(s))
             h = hash_combine(hash_combine(hash_combine(hash_combine(h, RANGE_TAG), e.lo), e.hi), (uint64_t)f.canon_id[(size_t)e.tgt]);
         for (auto& e : f.redges_by_hash[(size_t)s])
             h = hash_combine(hash_combine(hash_combine(h, REF_TAG), ref_hash[(size_t)e.rule]), (uint64_t)f.canon_id[(size_t)e.tgt]);
@@ -792,33 +801,76 @@ uint64_t hash_one_fsm(RuleFsm& f, const std::vector<uint64_t>& ref_hash) {
 
 std::atomic<uint64_t> g_unshareable_salt{1};
 
-void hash_rules(Grammar& g) {
-    int R = (int)g.rules.size();
-    // reference graph and its strongly connected components (Tarjan; components come out callee-first)
-    std::vector<std::vector<int>> refs((size_t)R);
+// Reference graph of the rules (per rule the distinct rules it references, ascending) and its strongly connected
+// components (Tarjan; components come out callee-first).
+struct RefGraph { std::vector<std::vector<int>> refs, comps; std::vector<int> comp; };
+RefGraph reference_graph(const Grammar& g) {
+    const int R = (int)g.rules.size();
+    RefGraph G;
+    G.refs.resize((size_t)R);
     for (int r = 0; r < R; ++r) {
-        std::set<int> s;
-        for (auto& es : g.rules[(size_t)r].redges) for (auto& e : es) s.insert(e.rule);
-        refs[(size_t)r].assign(s.begin(), s.end());
+        std::vector<int>& v = G.refs[(size_t)r];
+        for (auto& e : g.rules[(size_t)r].redges.v) v.push_back(e.rule);
+        std::sort(v.begin(), v.end());
+        v.erase(std::unique(v.begin(), v.end()), v.end());
     }
-    std::vector<int> idx((size_t)R, -1), low((size_t)R, 0), comp((size_t)R, -1), st;
+    std::vector<int> idx((size_t)R, -1), low((size_t)R, 0), st;
+    G.comp.assign((size_t)R, -1);
     std::vector<uint8_t> on((size_t)R, 0);
-    std::vector<std::vector<int>> comps;
     int counter = 0;
     std::function<void(int)> dfs = [&](int v) {
         idx[(size_t)v] = low[(size_t)v] = counter++;
         st.push_back(v); on[(size_t)v] = 1;
-        for (int w : refs[(size_t)v]) {
+        for (int w : G.refs[(size_t)v]) {
             if (idx[(size_t)w] < 0) { dfs(w); low[(size_t)v] = std::min(low[(size_t)v], low[(size_t)w]); }
             else if (on[(size_t)w]) low[(size_t)v] = std::min(low[(size_t)v], idx[(size_t)w]);
         }
         if (low[(size_t)v] == idx[(size_t)v]) {
-            comps.emplace_back();
-            for (;;) { int w = st.back(); st.pop_back(); on[(size_t)w] = 0; comp[(size_t)w] = (int)comps.size() - 1; comps.back().push_back(w); if (w == v) break; }
+            G.comps.emplace_back();
+            for (;;) { int w = st.back(); st.pop_back(); on[(size_t)w] = 0; G.comp[(size_t)w] = (int)G.comps.size() - 1; G.comps.back().push_back(w); if (w == v) break; }
         }
     };
     for (int r = 0; r < R; ++r) if (idx[(size_t)r] < 0) dfs(r);
+    return G;
+}
 
+// Shortest completion of every state and shortest sentence of every rule, in bytes (a byte costs 1, a reference its rule's
+// shortest sentence).  Callees first, so that one round settles a grammar without reference cycles; inside a rule states
+// are numbered breadth-first, so relaxing them from the last one back settles all but the loops in one round.
+constexpr int32_t kNoSentence = 1 << 28;
+void shortest_completions(Grammar& g, const RefGraph& G) {
+    for (RuleFsm& f : g.rules) { f.min_len = kNoSentence; f.min_suf.assign((size_t)f.n_states(), kNoSentence); }
+    auto relax = [&](RuleFsm& f) {
+        bool any = false;
+        const int n = f.n_states();
+        for (bool moved = true; moved;) {
+            moved = false;
+            for (int q = n - 1; q >= 0; --q) {
+                int32_t best = f.is_final(q) ? 0 : f.min_suf[(size_t)q];
+                for (auto& e : f.bedges(q)) best = std::min(best, f.min_suf[(size_t)e.tgt] + 1);
+                for (auto& e : f.refs(q)) best = std::min(best, f.min_suf[(size_t)e.tgt] + g.rules[(size_t)e.rule].min_len);
+                if (best < f.min_suf[(size_t)q]) { f.min_suf[(size_t)q] = best; moved = true; }
+            }
+            any |= moved;
+        }
+        f.min_len = f.min_suf[0];
+        return any;
+    };
+    for (const std::vector<int>& members : G.comps) {
+        const bool cycle = members.size() > 1 || std::binary_search(G.refs[(size_t)members[0]].begin(), G.refs[(size_t)members[0]].end(), members[0]);
+        for (bool moved = true; moved;) {
+            moved = false;
+            for (int r : members) moved |= relax(g.rules[(size_t)r]);
+            if (!cycle) break;
+        }
+    }
+}
+
+void hash_rules(Grammar& g, const RefGraph& G) {
+    const int R = (int)g.rules.size();
+    const std::vector<std::vector<int>>& refs = G.refs;
+    const std::vector<std::vector<int>>& comps = G.comps;
+    const std::vector<int>& comp = G.comp;
     std::vector<uint64_t> hash((size_t)R, 0);
     for (auto& members : comps) {
         int c = comp[(size_t)members[0]];
@@ -883,17 +935,20 @@ uint64_t hash_combine(uint64_t h, uint64_t v) {
 
 std::string serialise_rule(const Grammar& g, int32_t rule, const std::vector<uint64_t>& ref_id) {
     const RuleFsm& f = g.rules[(size_t)rule];
-    int n = f.n_states();
+    const int n = f.n_states();
     std::vector<int> by_canon((size_t)n);
     for (int s = 0; s < n; ++s) by_canon[(size_t)f.canon_id[(size_t)s]] = s;
     std::string text;
+    text.resize((size_t)n * 2 + f.body->bedges.v.size() * 7 + f.redges.v.size() * 13);
+    char* p = text.data();
+    auto put32 = [&](uint32_t v) { std::memcpy(p, &v, 4); p += 4; };
     for (int s : by_canon) {
-        text.push_back('N'); text.push_back((char)f.is_final[(size_t)s]);
-        for (auto& e : f.bedges[(size_t)s]) {
-            text.push_back('R'); text.push_back((char)e.lo); text.push_back((char)e.hi); put_u64(text, (uint64_t)f.canon_id[(size_t)e.tgt]);
-        }
+        *p++ = 'N'; *p++ = (char)f.is_final(s);
+        for (auto& e : f.bedges(s)) { *p++ = 'R'; *p++ = (char)e.lo; *p++ = (char)e.hi; put32((uint32_t)f.canon_id[(size_t)e.tgt]); }
         for (auto& e : f.redges_by_hash[(size_t)s]) {
-            text.push_back('F'); put_u64(text, ref_id[(size_t)e.rule]); put_u64(text, (uint64_t)f.canon_id[(size_t)e.tgt]);
+            *p++ = 'F';
+            std::memcpy(p, &ref_id[(size_t)e.rule], 8); p += 8;
+            put32((uint32_t)f.canon_id[(size_t)e.tgt]);
         }
     }
     return text;
@@ -901,71 +956,99 @@ std::string serialise_rule(const Grammar& g, int32_t rule, const std::vector<uin
 
 // ---- process-wide memo of lowered rule bodies ------------------------------------------------------------
 std::mutex g_body_memo_mu;
-std::unordered_map<std::string, std::shared_ptr<Dfa>> g_body_memo;
+std::unordered_map<std::string, std::shared_ptr<const RuleBody>> g_body_memo;
 
-void collect_refs(const Node& nd, const std::map<std::string, int>& index, std::vector<int>& out, bool& ok) {
+void collect_refs(const Node& nd, const RuleIndex& index, std::vector<int>& out, bool& ok) {
     auto add = [&](const std::string& name) { auto it = index.find(name); if (it == index.end()) ok = false; else out.push_back(it->second); };
     if (nd.k == NK::Ref) add(nd.name);
     for (auto& t : nd.tags) add(t.second);
     for (const Node& k : nd.kids) collect_refs(k, index, out, ok);
 }
 
-void body_key(const Node& nd, const std::map<std::string, int>& index, const std::vector<int>& ref_decl, std::string& out) {
-    auto put = [&](uint64_t v) { for (int k = 0; k < 8; ++k) out.push_back((char)((v >> (8 * k)) & 0xFF)); };
-    auto rank = [&](const std::string& name) { return (uint64_t)(std::lower_bound(ref_decl.begin(), ref_decl.end(), index.at(name)) - ref_decl.begin()); };
+void body_key(const Node& nd, const RuleIndex& index, const std::vector<int>& ref_decl, std::string& out) {
+    auto put = [&](uint32_t v) { out.append(reinterpret_cast<const char*>(&v), 4); };
+    auto rank = [&](const std::string& name) { return (uint32_t)(std::lower_bound(ref_decl.begin(), ref_decl.end(), index.at(name)) - ref_decl.begin()); };
     out.push_back((char)('A' + (int)nd.k));
     switch (nd.k) {
-        case NK::Lit: put(nd.cps.size()); for (uint32_t c : nd.cps) put(c); break;
-        case NK::Cls: put(nd.neg); put(nd.ranges.size()); for (auto& r : nd.ranges) { put(r.first); put(r.second); } break;
+        case NK::Lit: put((uint32_t)nd.cps.size()); out.append(reinterpret_cast<const char*>(nd.cps.data()), 4 * nd.cps.size()); break;
+        case NK::Cls: put(nd.neg); put((uint32_t)nd.ranges.size()); for (auto& r : nd.ranges) { put(r.first); put(r.second); } break;
         case NK::Ref: put(rank(nd.name)); break;
-        case NK::Rep: put((uint64_t)(int64_t)nd.m); put((uint64_t)(int64_t)nd.n); break;
+        case NK::Rep: put((uint32_t)nd.m); put((uint32_t)nd.n); break;
         case NK::Tag:
-            put(nd.tags.size());
-            for (auto& t : nd.tags) { put(t.first.size()); out += t.first; put(rank(t.second)); }
-            put(nd.stops.size());
-            for (auto& st : nd.stops) { put(st.size()); out += st; }
+            put((uint32_t)nd.tags.size());
+            for (auto& t : nd.tags) { put((uint32_t)t.first.size()); out += t.first; put(rank(t.second)); }
+            put((uint32_t)nd.stops.size());
+            for (auto& st : nd.stops) { put((uint32_t)st.size()); out += st; }
             break;
         default: break;
     }
-    put(nd.kids.size());
+    put((uint32_t)nd.kids.size());
     for (const Node& k : nd.kids) body_key(k, index, ref_decl, out);
+}
+
+// The minimal automaton as edge lists: maximal runs of consecutive bytes with one target, references by rank.
+std::shared_ptr<const RuleBody> body_of(const Dfa& d, const std::vector<int>& ref_decl) {
+    auto body = std::make_shared<RuleBody>();
+    const int n = d.n();
+    body->is_final.assign(d.fin.begin(), d.fin.end());
+    // maximal runs of consecutive bytes of one class: the same for every state of the automaton
+    std::vector<std::array<int, 3>> class_runs;                 // {lo, hi, class}
+    for (int b = 0; b < 256;) {
+        int e = b;
+        while (e + 1 < 256 && d.cls[(size_t)(e + 1)] == d.cls[(size_t)b]) ++e;
+        class_runs.push_back({b, e, (int)d.cls[(size_t)b]});
+        b = e + 1;
+    }
+    for (int q = 0; q < n; ++q) {
+        int lo = -1, hi = -1, tgt = -1;                          // run of bytes with one target being grown
+        for (const auto& cr : class_runs) {
+            const int t = d.at(q, cr[2]);
+            if (t == tgt && lo >= 0 && cr[0] == hi + 1) { hi = cr[1]; continue; }
+            if (lo >= 0 && tgt >= 0) body->bedges.v.push_back({(uint8_t)lo, (uint8_t)hi, tgt});
+            lo = cr[0]; hi = cr[1]; tgt = t;
+        }
+        if (lo >= 0 && tgt >= 0) body->bedges.v.push_back({(uint8_t)lo, (uint8_t)hi, tgt});
+        body->bedges.end_row();
+        for (auto& r : d.rt[(size_t)q])
+            body->redges.v.push_back({(int32_t)(std::lower_bound(ref_decl.begin(), ref_decl.end(), r.first) - ref_decl.begin()), r.second});
+        body->redges.end_row();
+        if (d.rt[(size_t)q].size() > 1) body->single_refs = false;
+    }
+    return body;
 }
 
 Grammar lower_grammar(const std::string& ebnf, const std::string& root_rule) {
     std::vector<std::string> order;
-    std::map<std::string, Node> rules;
-    Parser(ebnf).parse(order, rules);
-    std::map<std::string, int> index;
-    for (size_t i = 0; i < order.size(); ++i) index[order[i]] = (int)i;
+    std::vector<Node> rules;
+    RuleIndex index;
+    Parser(ebnf).parse(order, rules, index);
     if (!index.count(root_rule)) throw GrammarError("unknown root rule " + root_rule);
 
     // lower the rules reachable from the root
-    std::map<int, Dfa> dfas;
-    std::vector<int> todo{index[root_rule]};
+    struct Lowered { std::shared_ptr<const RuleBody> body; std::vector<int> ref_decl; };   // ref_decl: declaration indices referenced, ascending
+    std::vector<Lowered> lowered(rules.size());
+    std::vector<int> todo{index.at(root_rule)};
+    std::string key;
     while (!todo.empty()) {
         int r = todo.back(); todo.pop_back();
-        if (dfas.count(r)) continue;
-        const Node& body = rules.at(order[(size_t)r]);
+        Lowered& L = lowered[(size_t)r];
+        if (L.body) continue;
+        const Node& body = rules[(size_t)r];
         // Rule bodies recur across grammars (the same tool schema in many requests): the minimal automaton of a body is
         // kept process-wide under its structure, references written as their rank among the body's references by
         // declaration index (which is all the canonical numbering depends on).
-        std::vector<int> ref_decl;                                  // declaration indices referenced, ascending
         bool refs_ok = true;
-        collect_refs(body, index, ref_decl, refs_ok);
-        std::sort(ref_decl.begin(), ref_decl.end());
-        ref_decl.erase(std::unique(ref_decl.begin(), ref_decl.end()), ref_decl.end());
-        std::string key;
-        if (refs_ok) body_key(body, index, ref_decl, key);
-        Dfa d;
-        bool from_memo = false;
+        collect_refs(body, index, L.ref_decl, refs_ok);
+        std::sort(L.ref_decl.begin(), L.ref_decl.end());
+        L.ref_decl.erase(std::unique(L.ref_decl.begin(), L.ref_decl.end()), L.ref_decl.end());
+        key.clear();
         if (refs_ok) {
+            body_key(body, index, L.ref_decl, key);
             std::lock_guard<std::mutex> lk(g_body_memo_mu);
             auto it = g_body_memo.find(key);
-            if (it != g_body_memo.end()) { d = *it->second; from_memo = true; }
+            if (it != g_body_memo.end()) L.body = it->second;
         }
-        if (from_memo) {
-            for (auto& es : d.rt) for (auto& e : es) e.first = ref_decl[(size_t)e.first];   // rank -> declaration index here
-        } else {
+        if (!L.body) {
             Dfa raw;
             if (body.k == NK::Tag) raw = tagdispatch_automaton(body, index);
             else {
@@ -974,110 +1057,35 @@ Grammar lower_grammar(const std::string& ebnf, const std::string& root_rule) {
                 build_nfa(body, nfa, s, e, index);
                 raw = subset_construction(nfa, s, e);
             }
-            d = minimise_canonical(raw, order[(size_t)r]);
-            if (refs_ok) {
-                auto keep = std::make_shared<Dfa>(d);
-                for (auto& es : keep->rt)
-                    for (auto& e : es) e.first = (int)(std::lower_bound(ref_decl.begin(), ref_decl.end(), e.first) - ref_decl.begin());
-                std::lock_guard<std::mutex> lk(g_body_memo_mu);
-                if (g_body_memo.size() > 200000) g_body_memo.clear();   // a bound on memory, not a policy
-                g_body_memo.emplace(std::move(key), std::move(keep));
-            }
+            L.body = body_of(minimise_canonical(raw, order[(size_t)r]), L.ref_decl);
+            std::lock_guard<std::mutex> lk(g_body_memo_mu);
+            if (g_body_memo.size() > 200000) g_body_memo.clear();   // a bound on memory, not a policy
+            g_body_memo.emplace(key, L.body);
         }
-        for (auto& es : d.rt) for (auto& e : es) todo.push_back(e.first);
-        dfas.emplace(r, std::move(d));
+        // only what the minimal automaton still references is part of the grammar
+        for (auto& e : L.body->redges.v) todo.push_back(L.ref_decl[(size_t)e.rule]);
     }
     Grammar g;
-    std::map<int, int> remap;                                    // declaration index -> index in g.rules
-    for (auto& kv : dfas) { remap[kv.first] = (int)remap.size(); }
-    for (auto& kv : dfas) {
-        const Dfa& d = kv.second;
-        RuleFsm f;
-        f.name = order[(size_t)kv.first];
-        f.decl_index = kv.first;
-        int n = d.n();
-        f.is_final.assign(d.fin.begin(), d.fin.end());
-        f.bedges.resize((size_t)n);
-        f.redges.resize((size_t)n);
-        // maximal runs of consecutive bytes of one class: the same for every state of the automaton
-        std::vector<std::array<int, 3>> class_runs;                 // {lo, hi, class}
-        for (int b = 0; b < 256;) {
-            int e = b;
-            while (e + 1 < 256 && d.cls[(size_t)(e + 1)] == d.cls[(size_t)b]) ++e;
-            class_runs.push_back({b, e, (int)d.cls[(size_t)b]});
-            b = e + 1;
-        }
-        for (int q = 0; q < n; ++q) {
-            int lo = -1, hi = -1, tgt = -1;                          // run of bytes with one target being grown
-            for (const auto& cr : class_runs) {
-                const int t = d.at(q, cr[2]);
-                if (t == tgt && lo >= 0 && cr[0] == hi + 1) { hi = cr[1]; continue; }
-                if (lo >= 0 && tgt >= 0) f.bedges[(size_t)q].push_back({(uint8_t)lo, (uint8_t)hi, tgt});
-                lo = cr[0]; hi = cr[1]; tgt = t;
-            }
-            if (lo >= 0 && tgt >= 0) f.bedges[(size_t)q].push_back({(uint8_t)lo, (uint8_t)hi, tgt});
-            for (auto& r : d.rt[(size_t)q]) f.redges[(size_t)q].push_back({remap.at(r.first), r.second});
-        }
-        g.rules.push_back(std::move(f));
+    std::vector<int> remap(rules.size(), -1);                     // declaration index -> index in g.rules
+    int n_rules = 0;
+    for (size_t d = 0; d < rules.size(); ++d) if (lowered[d].body) remap[d] = n_rules++;
+    g.rules.resize((size_t)n_rules);
+    for (size_t d = 0; d < rules.size(); ++d) {
+        if (remap[d] < 0) continue;
+        RuleFsm& f = g.rules[(size_t)remap[d]];
+        f.name = std::move(order[d]);
+        f.decl_index = (int32_t)d;
+        f.body = std::move(lowered[d].body);
+        f.redges = f.body->redges;
+        for (RefEdge& e : f.redges.v) e.rule = remap[(size_t)lowered[d].ref_decl[(size_t)e.rule]];
     }
-    g.root = remap.at(index[root_rule]);
-    int R = (int)g.rules.size();
-    // nullable rules (least fixed point) and productivity (every reachable rule must derive a string)
-    auto fixed_point = [&](bool want_nullable) {
-        std::vector<uint8_t> ok((size_t)R, 0);
-        for (bool changed = true; changed;) {
-            changed = false;
-            for (int r = 0; r < R; ++r) {
-                if (ok[(size_t)r]) continue;
-                const RuleFsm& f = g.rules[(size_t)r];
-                std::vector<uint8_t> seen((size_t)f.n_states(), 0);
-                std::vector<int> stack{0};
-                seen[0] = 1;
-                bool hit = false;
-                while (!stack.empty() && !hit) {
-                    int q = stack.back(); stack.pop_back();
-                    if (f.is_final[(size_t)q]) { hit = true; break; }
-                    auto visit = [&](int t) { if (!seen[(size_t)t]) { seen[(size_t)t] = 1; stack.push_back(t); } };
-                    if (!want_nullable) for (auto& e : f.bedges[(size_t)q]) visit(e.tgt);
-                    for (auto& e : f.redges[(size_t)q]) if (ok[(size_t)e.rule]) visit(e.tgt);
-                }
-                if (hit) { ok[(size_t)r] = 1; changed = true; }
-            }
-        }
-        return ok;
-    };
-    std::vector<uint8_t> nullable = fixed_point(true), productive = fixed_point(false);
-    for (int r = 0; r < R; ++r) {
-        g.rules[(size_t)r].nullable = nullable[(size_t)r];
-        if (!productive[(size_t)r]) throw GrammarError("rule " + g.rules[(size_t)r].name + " derives no string (grammar is not reduced)");
-    }
-    // shortest sentence of every rule: relax until stable (byte edge = 1, rule edge = the rule's own minimum)
-    {
-        const int32_t INF = 1 << 28;
-        std::vector<int32_t> ml((size_t)R, INF);
-        for (bool changed = true; changed;) {
-            changed = false;
-            for (int r = 0; r < R; ++r) {
-                const RuleFsm& f = g.rules[(size_t)r];
-                std::vector<int32_t> dist((size_t)f.n_states(), INF);
-                dist[0] = 0;
-                for (bool moved = true; moved;) {                   // Bellman-Ford over the (small) automaton
-                    moved = false;
-                    for (int q = 0; q < f.n_states(); ++q) {
-                        if (dist[(size_t)q] >= INF) continue;
-                        for (auto& e : f.bedges[(size_t)q]) if (dist[(size_t)q] + 1 < dist[(size_t)e.tgt]) { dist[(size_t)e.tgt] = dist[(size_t)q] + 1; moved = true; }
-                        for (auto& e : f.redges[(size_t)q]) {
-                            int32_t c = ml[(size_t)e.rule];
-                            if (c < INF && dist[(size_t)q] + c < dist[(size_t)e.tgt]) { dist[(size_t)e.tgt] = dist[(size_t)q] + c; moved = true; }
-                        }
-                    }
-                }
-                int32_t best = INF;
-                for (int q = 0; q < f.n_states(); ++q) if (f.is_final[(size_t)q]) best = std::min(best, dist[(size_t)q]);
-                if (best < ml[(size_t)r]) { ml[(size_t)r] = best; changed = true; }
-            }
-        }
-        for (int r = 0; r < R; ++r) g.rules[(size_t)r].min_len = ml[(size_t)r];
+    g.root = remap[(size_t)index.at(root_rule)];
+    const int R = n_rules;
+    const RefGraph G = reference_graph(g);
+    shortest_completions(g, G);
+    for (RuleFsm& f : g.rules) {
+        f.nullable = f.min_len == 0;
+        if (f.min_len >= kNoSentence) throw GrammarError("rule " + f.name + " derives no string (grammar is not reduced)");
     }
     g.state_base.resize((size_t)R);
     g.n_states = 0;
@@ -1085,19 +1093,57 @@ Grammar lower_grammar(const std::string& ebnf, const std::string& root_rule) {
     g.sid_to_pos.assign((size_t)g.n_states, -1);
     for (int r = 0; r < R; ++r)
         for (int q = 0; q < g.rules[(size_t)r].n_states(); ++q)
-            if (!g.rules[(size_t)r].bedges[(size_t)q].empty()) {
+            if (!g.rules[(size_t)r].bedges(q).empty()) {
                 g.sid_to_pos[(size_t)g.sid(r, q)] = (int)g.positions.size();
                 g.positions.push_back({r, q, g.sid(r, q)});
             }
-    hash_rules(g);
+    hash_rules(g, G);
     return g;
 }
 
-std::vector<std::vector<int32_t>> bounded_classes(const Grammar& g, int32_t budget, const std::vector<uint64_t>& ref_identity) {
-    std::vector<std::vector<int32_t>> rep(g.rules.size());
-    for (size_t r = 0; r < g.rules.size(); ++r) rep[r] = bounded_classes_rule(g, (int32_t)r, budget, ref_identity);
-    return rep;
+namespace {
+// From the classes of every level (level[d * n + x], numbered below n): per state the member of its class at the budget
+// with the smallest canonical id, and (optional) the near-classes.  scans[x]: the state has byte edges.
+void class_representatives(const int32_t* level, int n, int32_t budget, const int32_t* canon_id, const std::vector<uint8_t>& scans,
+                           std::vector<int32_t>& rep_r, NearClasses* near) {
+    const int32_t* fin = level + (size_t)budget * (size_t)n;
+    std::vector<int32_t> best((size_t)n, -1);                    // class -> member with the smallest canonical id
+    for (int x = 0; x < n; ++x) {
+        int32_t& b = best[(size_t)fin[x]];
+        if (b < 0 || canon_id[x] < canon_id[b]) b = x;
+    }
+    rep_r.resize((size_t)n);
+    for (int x = 0; x < n; ++x) rep_r[(size_t)x] = best[(size_t)fin[x]];
+    if (!near) return;
+    // classes in the order of falling size (the class a long repetition collapses into comes first); each looks
+    // for the deepest level at which it still coincides with a class that is built in full
+    near->base.assign((size_t)n, -1);
+    near->depth.assign((size_t)n, 0);
+    std::vector<int32_t> weight((size_t)n, 0);                                    // by class number (< n)
+    for (int x = 0; x < n; ++x) ++weight[(size_t)fin[x]];
+    std::vector<std::array<int32_t, 3>> keyed;                                   // {-size, canonical id, state}
+    for (int c = 0; c < n; ++c) if (best[(size_t)c] >= 0) keyed.push_back({-weight[(size_t)c], canon_id[best[(size_t)c]], best[(size_t)c]});
+    std::sort(keyed.begin(), keyed.end());
+    const int32_t top = std::min<int32_t>(budget - 1, kMaxNearDepth);
+    if (top < kMinNearDepth) return;
+    // per level: class -> a class built in full (-1: none yet)
+    std::vector<int32_t> full((size_t)(top + 1) * (size_t)n, -1);
+    for (auto& k : keyed) {
+        const int32_t x = k[2];
+        if (!scans[(size_t)x]) continue;                                         // no plane
+        int32_t d = top;
+        for (; d >= kMinNearDepth; --d) {
+            const int32_t y = full[(size_t)d * (size_t)n + (size_t)level[(size_t)d * (size_t)n + (size_t)x]];
+            if (y >= 0) { near->base[(size_t)x] = y; near->depth[(size_t)x] = d; break; }
+        }
+        if (d < kMinNearDepth)
+            for (int32_t e = kMinNearDepth; e <= top; ++e) {
+                int32_t& y = full[(size_t)e * (size_t)n + (size_t)level[(size_t)e * (size_t)n + (size_t)x]];
+                if (y < 0) y = x;
+            }
+    }
 }
+}  // namespace
 
 std::vector<int32_t> bounded_classes_rule(const Grammar& g, int32_t rule, int32_t budget, const std::vector<uint64_t>& ref_identity,
                                           NearClasses* near) {
@@ -1112,7 +1158,7 @@ std::vector<int32_t> bounded_classes_rule(const Grammar& g, int32_t rule, int32_
         std::vector<std::vector<int32_t>> level(1, std::vector<int32_t>((size_t)n, 0));
         bool any_nullable_edge = false;
         for (int x = 0; x < n && !any_nullable_edge; ++x)
-            for (auto& e : f.redges[(size_t)x]) if (g.rules[(size_t)e.rule].nullable) { any_nullable_edge = true; break; }
+            for (auto& e : f.refs(x)) if (g.rules[(size_t)e.rule].nullable) { any_nullable_edge = true; break; }
         std::vector<int64_t> base, full;
         std::vector<size_t> base_off((size_t)n + 1), full_off((size_t)n + 1);
         std::vector<std::pair<int64_t, int64_t>> refs;
@@ -1141,7 +1187,7 @@ std::vector<int32_t> bounded_classes_rule(const Grammar& g, int32_t rule, int32_
         // never changes again.
         int32_t settle = 1;
         for (int x = 0; x < n; ++x)
-            for (auto& e : f.redges[(size_t)x]) {
+            for (auto& e : f.refs(x)) {
                 const RuleFsm& c = g.rules[(size_t)e.rule];
                 if (!c.nullable && c.min_len <= budget) settle = std::max(settle, c.min_len);
             }
@@ -1155,11 +1201,11 @@ std::vector<int32_t> bounded_classes_rule(const Grammar& g, int32_t rule, int32_
             for (int x = 0; x < n; ++x) {
                 base_off[(size_t)x] = base.size();
                 base.push_back(prev[(size_t)x]);
-                base.push_back(f.is_final[(size_t)x]);
+                base.push_back(f.is_final(x));
                 // maximal runs of consecutive bytes that lead to the same class (edges are sorted and disjoint)
                 {
                     int run_lo = -1, run_hi = -1; int32_t run_cls = -1;
-                    for (auto& e : f.bedges[(size_t)x]) {
+                    for (auto& e : f.bedges(x)) {
                         const int32_t c = prev[(size_t)e.tgt];
                         if (run_lo >= 0 && (int)e.lo == run_hi + 1 && c == run_cls) { run_hi = e.hi; continue; }
                         if (run_lo >= 0) { base.push_back(run_lo); base.push_back(run_hi); base.push_back(run_cls); }
@@ -1169,7 +1215,7 @@ std::vector<int32_t> bounded_classes_rule(const Grammar& g, int32_t rule, int32_
                 }
                 base.push_back(-7);
                 refs.clear();
-                for (auto& e : f.redges[(size_t)x]) {
+                for (auto& e : f.refs(x)) {
                     const RuleFsm& c = g.rules[(size_t)e.rule];
                     if (c.nullable) continue;
                     int32_t left = d - c.min_len;
@@ -1195,7 +1241,7 @@ std::vector<int32_t> bounded_classes_rule(const Grammar& g, int32_t rule, int32_
                         full.insert(full.end(), base.begin() + (long)base_off[(size_t)x], base.begin() + (long)base_off[(size_t)x + 1]);
                         full.push_back(-9);
                         refs.clear();
-                        for (auto& e : f.redges[(size_t)x])
+                        for (auto& e : f.refs(x))
                             if (g.rules[(size_t)e.rule].nullable) refs.emplace_back((int64_t)ref_identity[(size_t)e.rule], cur[(size_t)e.tgt]);
                         if (refs.size() > 1) std::sort(refs.begin(), refs.end());
                         for (auto& p : refs) { full.push_back(p.first); full.push_back(p.second); }
@@ -1212,196 +1258,207 @@ std::vector<int32_t> bounded_classes_rule(const Grammar& g, int32_t rule, int32_
             last_count = count;
             level.push_back(cur);
         }
-        const std::vector<int32_t>& fin = level.back();
-        std::vector<int32_t> best((size_t)n, -1);                // class (numbered below n) -> member with the smallest canonical id
-        for (int x = 0; x < n; ++x) {
-            int32_t& b = best[(size_t)fin[(size_t)x]];
-            if (b < 0 || f.canon_id[(size_t)x] < f.canon_id[(size_t)b]) b = x;
-        }
-        rep_r.resize((size_t)n);
-        for (int x = 0; x < n; ++x) rep_r[(size_t)x] = best[(size_t)fin[(size_t)x]];
-        if (near) {
-            // classes in the order of falling size (the class a long repetition collapses into comes first); each looks
-            // for the deepest level at which it still coincides with a class that is built in full
-            near->base.assign((size_t)n, -1);
-            near->depth.assign((size_t)n, 0);
-            std::vector<int32_t> weight((size_t)n, 0);                                    // by class number (< n)
-            for (int x = 0; x < n; ++x) ++weight[(size_t)fin[(size_t)x]];
-            std::vector<std::array<int32_t, 3>> keyed;                                   // {-size, canonical id, state}
-            for (int c = 0; c < n; ++c) if (best[(size_t)c] >= 0) keyed.push_back({-weight[(size_t)c], f.canon_id[(size_t)best[(size_t)c]], best[(size_t)c]});
-            std::sort(keyed.begin(), keyed.end());
-            std::vector<int32_t> reps;
-            for (auto& k : keyed) reps.push_back(k[2]);
-            const int32_t top = std::min<int32_t>(budget - 1, kMaxNearDepth);
-            // per level: class -> a class built in full (-1: none yet)
-            std::vector<std::vector<int32_t>> full((size_t)std::max(top + 1, 1));
-            for (int32_t e = kMinNearDepth; e <= top; ++e) full[(size_t)e].assign((size_t)n, -1);
-            for (int32_t x : reps) {
-                if (f.bedges[(size_t)x].empty()) continue;                               // no plane
-                int32_t d = top;
-                for (; d >= kMinNearDepth; --d) {
-                    const int32_t y = full[(size_t)d][(size_t)level[(size_t)d][(size_t)x]];
-                    if (y >= 0) { near->base[(size_t)x] = y; near->depth[(size_t)x] = d; break; }
-                }
-                if (d < kMinNearDepth)
-                    for (int32_t e = kMinNearDepth; e <= top; ++e) {
-                        int32_t& y = full[(size_t)e][(size_t)level[(size_t)e][(size_t)x]];
-                        if (y < 0) y = x;
-                    }
-            }
-        }
+        std::vector<int32_t> flat;                                    // [d * n + x]
+        for (auto& l : level) flat.insert(flat.end(), l.begin(), l.end());
+        std::vector<uint8_t> scans((size_t)n);
+        for (int x = 0; x < n; ++x) scans[(size_t)x] = !f.bedges(x).empty();
+        class_representatives(flat.data(), n, budget, f.canon_id.data(), scans, rep_r, near);
     }
     return rep_r;
 }
 
-FollowInfo follow_signatures(const Grammar& g, int32_t budget, const std::vector<std::vector<int32_t>>* rep,
-                             const std::vector<uint64_t>* ref_identity, const FollowInterner* intern, const FollowMemo* memo_of) {
-    const int R = (int)g.rules.size();
-    // A node of the unfolding is described by a list of words (constants, byte ranges, the values of its children).
-    // Without an interner its value is the hash of the list; with one it is the interner's number for exactly this
-    // list, so that equal values mean equal structures as long as the children's values do.
-    auto value_of = [&](std::vector<uint64_t>& desc) -> uint64_t {
-        if (intern) return (*intern)(desc);
-        uint64_t h = desc.empty() ? 0 : desc[0];
-        for (size_t k = 1; k < desc.size(); ++k) h = hash_combine(h, desc[k]);
-        return h;
-    };
-    auto rule_identity = [&](int rule) -> uint64_t { return ref_identity ? (*ref_identity)[(size_t)rule] : g.rules[(size_t)rule].hash; };
-    const int32_t INF = 1 << 28;
-    // shortest completion of every state, in bytes
-    std::vector<std::vector<int32_t>> min_suf((size_t)R);
-    for (int r = 0; r < R; ++r) {
-        const RuleFsm& f = g.rules[(size_t)r];
-        std::vector<int32_t>& d = min_suf[(size_t)r];
-        d.assign((size_t)f.n_states(), INF);
-        // shortest paths to a final state over the reversed edges (a byte costs 1, a rule its shortest sentence)
-        const int n = f.n_states();
-        std::vector<std::vector<std::pair<int32_t, int32_t>>> back((size_t)n);      // target -> (source, cost)
-        for (int q = 0; q < n; ++q) {
-            for (auto& e : f.bedges[(size_t)q]) back[(size_t)e.tgt].emplace_back(q, 1);
-            for (auto& e : f.redges[(size_t)q]) back[(size_t)e.tgt].emplace_back(q, g.rules[(size_t)e.rule].min_len);
+uint32_t NodeTable::intern(const uint32_t* w, uint32_t n) {
+    if ((used_ + 1) * 2 > slot_.size()) grow();
+    uint64_t h = n;
+    for (uint32_t k = 0; k < n; ++k) { h = (h ^ w[k]) * 0x9FB21C651E98DF25ull; h ^= h >> 32; }
+    const uint32_t h32 = (uint32_t)h, mask = (uint32_t)slot_.size() - 1;
+    for (uint32_t at = h32 & mask;; at = (at + 1) & mask) {
+        const uint32_t k = slot_[at];
+        if (!k) {
+            words_.insert(words_.end(), w, w + n);
+            end_.push_back((uint32_t)words_.size());
+            hash_.push_back(h32);
+            ++used_;
+            return slot_[at] = (uint32_t)end_.size();
         }
-        std::priority_queue<std::pair<int32_t, int32_t>, std::vector<std::pair<int32_t, int32_t>>, std::greater<>> heap;
-        for (int q = 0; q < n; ++q) if (f.is_final[(size_t)q]) { d[(size_t)q] = 0; heap.emplace(0, q); }
-        while (!heap.empty()) {
-            const auto [dist, q] = heap.top();
-            heap.pop();
-            if (dist > d[(size_t)q]) continue;
-            for (auto& [src, cost] : back[(size_t)q])
-                if (dist + cost < d[(size_t)src]) { d[(size_t)src] = dist + cost; heap.emplace(dist + cost, src); }
-        }
+        if (hash_[k - 1] != h32) continue;
+        const uint32_t lo = k > 1 ? end_[k - 2] : 0u;
+        if (end_[k - 1] - lo == n && std::equal(w, w + n, words_.data() + lo)) return k;
     }
-    // unfold(d, rule, state): structural hash of the state's behaviour on at most d bytes (0 for d = 0).  Computed on
-    // demand: only the states in which referencing rules continue, and what is within d bytes of them, are ever asked
-    // for.  States on a cycle of nullable rule edges get a fresh salt.
-    std::vector<uint8_t> cyclic((size_t)g.n_states, 1);
-    for (int r = 0; r < R; ++r) {
-        const RuleFsm& f = g.rules[(size_t)r];
-        const int n = f.n_states();
-        std::vector<int> indeg((size_t)n, 0), order;
+}
+void NodeTable::grow() {
+    std::vector<uint32_t> old;
+    old.swap(slot_);
+    slot_.assign(old.empty() ? 4096 : old.size() * 2, 0);
+    const uint32_t mask = (uint32_t)slot_.size() - 1;
+    for (uint32_t k : old) {
+        if (!k) continue;
+        uint32_t at = hash_[k - 1] & mask;
+        while (slot_[at]) at = (at + 1) & mask;
+        slot_[at] = k;
+    }
+}
+
+namespace {
+constexpr uint32_t kNodeState = 1u << 28, kNodeSite = 2u << 28, kNodeFollow = 3u << 28, kNodeFinal = 1u << 27, kNodeTooLong = 0xFFFFFFFFu;
+}
+
+RuleAnalysis analyse_rule(const Grammar& g, int32_t rule, int32_t budget, const std::vector<uint64_t>& identity, NodeTable& nodes) {
+    const RuleFsm& f = g.rules[(size_t)rule];
+    const int n = f.n_states();
+    RuleAnalysis A;
+    A.n = n;
+    A.level.assign((size_t)(budget + 1) * (size_t)n, 0);
+    std::vector<int> by_canon((size_t)n);
+    for (int x = 0; x < n; ++x) by_canon[(size_t)f.canon_id[(size_t)x]] = x;
+    // order in which a level is worked out: a state after the states its references to empty-deriving rules lead to
+    // (those stay on the same level); states that never get their turn are on or before a cycle of such references
+    std::vector<int> order;                                       // canonical numbers
+    order.reserve((size_t)n);
+    bool any_nullable = false;
+    int32_t settle = 1;
+    for (const RefEdge& e : f.redges.v) {
+        const RuleFsm& c = g.rules[(size_t)e.rule];
+        any_nullable |= c.nullable;
+        if (!c.nullable && c.min_len <= budget) settle = std::max(settle, c.min_len);
+    }
+    if (!any_nullable) for (int c = 0; c < n; ++c) order.push_back(c);
+    else {
+        std::vector<int> left((size_t)n, 0);
         std::vector<std::vector<int>> preds((size_t)n);
         for (int x = 0; x < n; ++x)
-            for (auto& e : f.redges[(size_t)x]) if (g.rules[(size_t)e.rule].nullable) { ++indeg[(size_t)x]; preds[(size_t)e.tgt].push_back(x); }
-        for (int x = 0; x < n; ++x) if (indeg[(size_t)x] == 0) order.push_back(x);
-        for (size_t k = 0; k < order.size(); ++k) for (int p : preds[(size_t)order[k]]) if (--indeg[(size_t)p] == 0) order.push_back(p);
-        for (int x : order) cyclic[(size_t)g.sid(r, x)] = 0;
+            for (auto& e : f.refs(x)) if (g.rules[(size_t)e.rule].nullable) { ++left[(size_t)x]; preds[(size_t)e.tgt].push_back(x); }
+        for (int c = 0; c < n; ++c) if (!left[(size_t)by_canon[(size_t)c]]) order.push_back(c);
+        for (size_t k = 0; k < order.size(); ++k)
+            for (int p : preds[(size_t)by_canon[(size_t)order[k]]]) if (--left[(size_t)p] == 0) order.push_back(f.canon_id[(size_t)p]);
     }
-    std::vector<std::vector<uint64_t>> unfold_memo((size_t)budget + 1);
-    std::vector<std::vector<uint8_t>> unfold_have((size_t)budget + 1);
-    std::function<uint64_t(int32_t, int, int)> unfold = [&](int32_t d, int r, int x) -> uint64_t {
-        if (d <= 0) return 0;
-        if (unfold_memo[(size_t)d].empty()) { unfold_memo[(size_t)d].assign((size_t)g.n_states, 0); unfold_have[(size_t)d].assign((size_t)g.n_states, 0); }
-        const size_t sid = (size_t)g.sid(r, x);
-        if (unfold_have[(size_t)d][sid]) return unfold_memo[(size_t)d][sid];
-        const RuleFsm& f = g.rules[(size_t)r];
-        // the unfolding of a state depends on its rule and the rules that one references, not on the grammar around it:
-        // an identical rule met before (in this grammar or an earlier one of the pool) has it ready
-        uint64_t* kept = memo_of ? (*memo_of)(r, x, d) : nullptr;
-        if (kept && *kept) {
-            unfold_memo[(size_t)d][sid] = *kept;
-            unfold_have[(size_t)d][sid] = 1;
-            return *kept;
-        }
-        uint64_t h;
-        std::vector<uint64_t> desc;
-        if (cyclic[sid]) {
-            desc = {0xC1C1ull, g_unshareable_salt.fetch_add(1)};
-            h = value_of(desc);
-        } else {
-            desc = {0x51ull, (uint64_t)f.is_final[(size_t)x]};
-            {   // maximal runs of consecutive bytes with the same unfolding (edges are sorted and disjoint)
-                int run_lo = -1, run_hi = -1; uint64_t run_h = 0;
-                for (auto& e : f.bedges[(size_t)x]) {
-                    const uint64_t u = unfold(d - 1, r, e.tgt);
-                    if (run_lo >= 0 && (int)e.lo == run_hi + 1 && u == run_h) { run_hi = e.hi; continue; }
-                    if (run_lo >= 0) { desc.push_back((uint64_t)run_lo); desc.push_back((uint64_t)run_hi); desc.push_back(run_h); }
-                    run_lo = e.lo; run_hi = e.hi; run_h = u;
+    std::vector<uint8_t> in_order((size_t)n, 0);
+    for (int c : order) in_order[(size_t)c] = 1;
+    const bool acyclic = (int)order.size() == n;
+
+    // per level, the classes numbered from 0 (a table over node numbers, stamped level by level, finds a node's class)
+    std::vector<int32_t> local((size_t)(budget + 1) * (size_t)n, 0);
+    struct Seen { uint64_t stamp; int32_t cls; };
+    static thread_local std::vector<Seen> seen;
+    static thread_local uint64_t stamp = 0;
+    std::vector<uint32_t> desc;
+    std::vector<std::pair<uint32_t, uint32_t>> refs;
+    std::vector<uint32_t> of_class;                               // once the partition has settled: number of each class on this level
+    int32_t unchanged = 0, last_count = 1;
+    for (int32_t d = 1; d <= budget; ++d) {
+        const uint32_t* prev = A.level.data() + (size_t)(d - 1) * (size_t)n;
+        uint32_t* cur = A.level.data() + (size_t)d * (size_t)n;
+        const int32_t* prev_local = local.data() + (size_t)(d - 1) * (size_t)n;
+        // Levels only refine.  Level d is a function of level d - 1 and of the levels d - m for the shortest sentences m of
+        // the referenced rules, so once the partition has not changed over max m (at least one) levels in a row it never
+        // changes again, and one state of a class speaks for all.
+        const bool settled = acyclic && unchanged >= settle;
+        if (settled) of_class.assign((size_t)last_count, 0);
+        for (int c : order) {
+            if (settled && of_class[(size_t)prev_local[c]]) { cur[c] = of_class[(size_t)prev_local[c]]; continue; }
+            const int x = by_canon[(size_t)c];
+            desc.assign(1, 0u);
+            uint32_t runs = 0;
+            {   // maximal runs of consecutive bytes with the same behaviour (edges are sorted and disjoint)
+                int run_lo = -1, run_hi = -1; uint32_t run_node = 0;
+                auto flush = [&] { if (run_lo >= 0) { desc.push_back((uint32_t)run_lo | ((uint32_t)run_hi << 8)); desc.push_back(run_node); ++runs; } };
+                for (auto& e : f.bedges(x)) {
+                    const uint32_t u = prev[f.canon_id[(size_t)e.tgt]];
+                    if (run_lo >= 0 && (int)e.lo == run_hi + 1 && u == run_node) { run_hi = e.hi; continue; }
+                    flush();
+                    run_lo = e.lo; run_hi = e.hi; run_node = u;
                 }
-                if (run_lo >= 0) { desc.push_back((uint64_t)run_lo); desc.push_back((uint64_t)run_hi); desc.push_back(run_h); }
+                flush();
             }
-            if (!f.redges[(size_t)x].empty()) {
-                std::vector<std::pair<uint64_t, uint64_t>> refs;
-                for (auto& e : f.redges[(size_t)x]) {
-                    const RuleFsm& c = g.rules[(size_t)e.rule];
-                    int32_t left = c.nullable ? d : d - c.min_len;
-                    refs.emplace_back(rule_identity(e.rule), left >= 0 ? unfold(left, r, e.tgt) : 0x7777ull);
+            if (!f.refs(x).empty()) {
+                refs.clear();
+                for (auto& e : f.refs(x)) {
+                    const RuleFsm& c2 = g.rules[(size_t)e.rule];
+                    const int32_t left = c2.nullable ? d : d - c2.min_len;
+                    refs.emplace_back((uint32_t)identity[(size_t)e.rule], left >= 0 ? A.level[(size_t)left * (size_t)n + (size_t)f.canon_id[(size_t)e.tgt]] : kNodeTooLong);
                 }
-                std::sort(refs.begin(), refs.end());
-                for (auto& p : refs) { desc.push_back(0xEFull << 56); desc.push_back(p.first); desc.push_back(p.second); }
+                if (refs.size() > 1) std::sort(refs.begin(), refs.end());
+                for (auto& p : refs) { desc.push_back(p.first); desc.push_back(p.second); }
             }
-            h = value_of(desc);
+            desc[0] = kNodeState | (f.is_final(x) ? kNodeFinal : 0u) | runs;
+            cur[c] = nodes.intern(desc.data(), (uint32_t)desc.size());
+            if (settled) of_class[(size_t)prev_local[c]] = cur[c];
         }
-        unfold_memo[(size_t)d][sid] = h;
-        unfold_have[(size_t)d][sid] = 1;
-        if (kept) *kept = h;
-        return h;
-    };
-    // reference sites of every rule
-    struct Site { int q, x; };
-    std::vector<std::vector<Site>> sites((size_t)R);
-    for (int q = 0; q < R; ++q)
-        for (int s = 0; s < g.rules[(size_t)q].n_states(); ++s)
-            for (auto& e : g.rules[(size_t)q].redges[(size_t)s]) sites[(size_t)e.rule].push_back({q, rep ? (*rep)[(size_t)q][(size_t)e.tgt] : e.tgt});
-    for (auto& v : sites) {                                         // one site per state (class) a referencing rule continues in
+        if (!acyclic) for (int c = 0; c < n; ++c) if (!in_order[(size_t)c]) cur[c] = nodes.fresh();
+        int32_t* cur_local = local.data() + (size_t)d * (size_t)n;
+        if (settled) { std::copy(prev_local, prev_local + n, cur_local); continue; }
+        if (seen.size() < nodes.size() + 1) seen.resize(std::max<size_t>(nodes.size() + 1, seen.size() * 2), Seen{0, 0});
+        ++stamp;
+        int32_t count = 0;
+        for (int c = 0; c < n; ++c) {
+            Seen& s = seen[cur[c]];
+            if (s.stamp != stamp) s = {stamp, count++};
+            cur_local[c] = s.cls;
+        }
+        unchanged = count == last_count ? unchanged + 1 : 0;
+        last_count = count;
+    }
+    std::vector<int32_t> ident((size_t)n);
+    if (acyclic) {
+        // classes and near-classes from the levels, in canonical numbers
+        std::vector<uint8_t> scans((size_t)n);
+        for (int c = 0; c < n; ++c) { ident[(size_t)c] = c; scans[(size_t)c] = !f.bedges(by_canon[(size_t)c]).empty(); }
+        class_representatives(local.data(), n, budget, ident.data(), scans, A.rep, &A.near);
+    } else {
+        // the numbers of the states on a cycle say nothing about their classes: those come from the partition itself
+        NearClasses near;
+        const std::vector<int32_t> rep = bounded_classes_rule(g, rule, budget, identity, &near);
+        A.rep.resize((size_t)n); A.near.base.resize((size_t)n); A.near.depth.resize((size_t)n);
+        for (int x = 0; x < n; ++x) {
+            const size_t c = (size_t)f.canon_id[(size_t)x];
+            A.rep[c] = f.canon_id[(size_t)rep[(size_t)x]];
+            A.near.base[c] = near.base[(size_t)x] < 0 ? -1 : f.canon_id[(size_t)near.base[(size_t)x]];
+            A.near.depth[c] = near.depth[(size_t)x];
+        }
+    }
+    return A;
+}
+
+FollowSigs::FollowSigs(const Grammar& g, int32_t budget, const std::vector<std::shared_ptr<const RuleAnalysis>>& analysis,
+                       const std::vector<std::vector<int32_t>>& rep, NodeTable& nodes)
+    : g_(g), budget_(budget), analysis_(analysis), nodes_(nodes), memo_(g.rules.size() * ((size_t)budget + 1), 0) {
+    // sites of every rule: one per class of the states referencing rules continue in
+    const size_t R = g.rules.size();
+    std::vector<std::vector<Site>> sites(R);
+    for (size_t q = 0; q < R; ++q)
+        for (const RefEdge& e : g.rules[q].redges.v) {
+            const Site s{(int32_t)q, rep[q][(size_t)e.tgt]};
+            std::vector<Site>& v = sites[(size_t)e.rule];
+            if (v.empty() || v.back().q != s.q || v.back().x != s.x) v.push_back(s);     // a long repetition lists one class again and again
+        }
+    for (auto& v : sites) {
         std::sort(v.begin(), v.end(), [](const Site& a, const Site& b) { return a.q != b.q ? a.q < b.q : a.x < b.x; });
         v.erase(std::unique(v.begin(), v.end(), [](const Site& a, const Site& b) { return a.q == b.q && a.x == b.x; }), v.end());
+        sites_.v.insert(sites_.v.end(), v.begin(), v.end());
+        sites_.end_row();
     }
-    std::vector<uint64_t> memo((size_t)R * ((size_t)budget + 1), 0);
-    std::vector<uint8_t> memo_state((size_t)R * ((size_t)budget + 1), 0);      // 0 unknown, 1 being computed, 2 known
-    std::function<uint64_t(int, int)> sig = [&](int rule, int d) -> uint64_t {
-        const size_t key = (size_t)rule * ((size_t)budget + 1) + (size_t)d;
-        if (memo_state[key] == 2) return memo[key];
-        if (memo_state[key] == 1) {                                         // cycle through rule ends
-            std::vector<uint64_t> salt{0xCCCCull, g_unshareable_salt.fetch_add(1)};
-            return value_of(salt);
+}
+
+uint32_t FollowSigs::sig(int rule, int d) {
+    const size_t key = (size_t)rule * ((size_t)budget_ + 1) + (size_t)d;
+    if (memo_[key] == kPending) return nodes_.fresh();              // cycle through rule ends
+    if (memo_[key]) return memo_[key];
+    memo_[key] = kPending;
+    std::vector<uint32_t> parts(1, kNodeFollow | (rule == g_.root ? 1u : 0u));      // the root: the input may end here
+    for (const Site& st : sites_[(size_t)rule]) {
+        const RuleFsm& f = g_.rules[(size_t)st.q];
+        const RuleAnalysis& A = *analysis_[(size_t)st.q];
+        uint32_t h = A.level[(size_t)d * (size_t)A.n + (size_t)f.canon_id[(size_t)st.x]];
+        const int32_t left = d - f.min_suf[(size_t)st.x];
+        if (left > 0) {
+            const uint32_t pair[3] = {kNodeSite, h, sig(st.q, left)};
+            h = nodes_.intern(pair, 3);
         }
-        memo_state[key] = 1;
-        std::vector<uint64_t> parts;
-        if (rule == g.root) parts.push_back(0xE0Full);                      // the input may end here
-        for (const Site& st : sites[(size_t)rule]) {
-            uint64_t h = unfold(d, st.q, st.x);
-            int32_t left = d - min_suf[(size_t)st.q][(size_t)st.x];
-            if (left > 0 || (left == 0 && d > 0 && min_suf[(size_t)st.q][(size_t)st.x] == 0)) {
-                std::vector<uint64_t> pair{0x5173ull, h, sig(st.q, left)};
-                h = value_of(pair);
-            }
-            parts.push_back(h);
-        }
-        std::sort(parts.begin(), parts.end());
-        parts.erase(std::unique(parts.begin(), parts.end()), parts.end());
-        std::vector<uint64_t> desc{0xF011ull};
-        desc.insert(desc.end(), parts.begin(), parts.end());
-        uint64_t h = value_of(desc);
-        memo_state[key] = 2;
-        memo[key] = h;
-        return h;
-    };
-    FollowInfo out;
-    out.sig.assign((size_t)R, std::vector<uint64_t>((size_t)budget + 1, 0));
-    for (int r = 0; r < R; ++r)
-        for (int32_t d = 0; d <= budget; ++d) out.sig[(size_t)r][(size_t)d] = sig(r, d);
-    out.min_suf = std::move(min_suf);
-    return out;
+        parts.push_back(h);
+    }
+    std::sort(parts.begin() + 1, parts.end());
+    parts.erase(std::unique(parts.begin() + 1, parts.end()), parts.end());
+    return memo_[key] = nodes_.intern(parts.data(), (uint32_t)parts.size());
 }
 
 std::string describe_grammar(const Grammar& g) {
@@ -1414,15 +1471,15 @@ std::string describe_grammar(const Grammar& g) {
           << ",\"shareable\":" << (f.shareable ? "true" : "false") << ",\"hash\":\"" << std::hex << f.hash << std::dec << "\",\"states\":[";
         for (int q = 0; q < f.n_states(); ++q) {
             if (q) o << ",";
-            o << "{\"final\":" << (f.is_final[(size_t)q] ? "true" : "false") << ",\"canon\":" << f.canon_id[(size_t)q] << ",\"bytes\":[";
-            for (size_t k = 0; k < f.bedges[(size_t)q].size(); ++k) {
-                auto& e = f.bedges[(size_t)q][k];
+            o << "{\"final\":" << (f.is_final(q) ? "true" : "false") << ",\"canon\":" << f.canon_id[(size_t)q] << ",\"bytes\":[";
+            for (size_t k = 0; k < f.bedges(q).size(); ++k) {
+                auto& e = f.bedges(q)[k];
                 if (k) o << ",";
                 o << "[" << (int)e.lo << "," << (int)e.hi << "," << e.tgt << "]";
             }
             o << "],\"refs\":[";
-            for (size_t k = 0; k < f.redges[(size_t)q].size(); ++k) {
-                auto& e = f.redges[(size_t)q][k];
+            for (size_t k = 0; k < f.refs(q).size(); ++k) {
+                auto& e = f.refs(q)[k];
                 if (k) o << ",";
                 o << "[\"" << g.rules[(size_t)e.rule].name << "\"," << e.tgt << "]";
             }

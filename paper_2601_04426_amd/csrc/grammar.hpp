@@ -4,6 +4,7 @@
 #pragma once
 #include <cstdint>
 #include <functional>
+#include <memory>
 #include <stdexcept>
 #include <string>
 #include <vector>
@@ -16,21 +17,53 @@ struct GrammarError : std::runtime_error { using std::runtime_error::runtime_err
 struct ByteRange { uint8_t lo, hi; int32_t tgt; };   // bytes lo..hi -> rule-local state tgt
 struct RefEdge { int32_t rule; int32_t tgt; };       // reference to Grammar::rules[rule] -> state tgt
 
+// Rows of T back to back: row i is v[off[i] .. off[i + 1]).  The automata of a grammar are thousands of short edge lists;
+// kept this way a rule costs two allocations instead of one per state, and copying or dropping one is a block copy.
+template <class T>
+struct Span {
+    const T* b; const T* e;
+    const T* begin() const { return b; }
+    const T* end() const { return e; }
+    size_t size() const { return (size_t)(e - b); }
+    bool empty() const { return b == e; }
+    const T& operator[](size_t k) const { return b[k]; }
+};
+template <class T>
+struct Rows {
+    std::vector<uint32_t> off{0};
+    std::vector<T> v;
+    Span<T> operator[](size_t i) const { return {v.data() + off[i], v.data() + off[i + 1]}; }
+    size_t size() const { return off.size() - 1; }
+    void end_row() { off.push_back((uint32_t)v.size()); }
+};
+
+// The minimal automaton of a rule body, apart from the grammar it stands in: references are written as their rank among
+// the body's references by declaration index.  Immutable and shared by every grammar that holds the same body.
+struct RuleBody {
+    std::vector<uint8_t> is_final;                    // [n_states]
+    Rows<ByteRange> bedges;                           // sorted by lo; maximal runs per target
+    Rows<RefEdge> redges;                             // sorted by rank
+    bool single_refs = true;                          // no state has more than one reference
+};
+
 struct RuleFsm {
     std::string name;
     int32_t decl_index = 0;                           // position of the rule in the EBNF text
-    std::vector<uint8_t> is_final;                    // [n_states]
-    std::vector<std::vector<ByteRange>> bedges;       // sorted by lo; maximal runs per target
-    std::vector<std::vector<RefEdge>> redges;         // sorted by referenced rule's decl_index
+    std::shared_ptr<const RuleBody> body;
+    Rows<RefEdge> redges;                             // sorted by referenced rule's decl_index
     bool nullable = false;
     int32_t min_len = 0;                              // length of the rule's shortest sentence, in bytes
+    std::vector<int32_t> min_suf;                     // [state]: bytes of the shortest completion of the rule from the state
     // structural hash (Algorithm 1, refined by Algorithm 2 inside simple reference cycles)
     uint64_t hash = 0;
     bool shareable = true;                            // false: member of a non-simple cycle, never reused
     std::vector<int32_t> canon_id;                    // Algorithm 1 phase 1: state -> canonical id
-    std::vector<std::vector<RefEdge>> redges_by_hash; // out-references in the order Algorithm 1 sorted them
+    Rows<RefEdge> redges_by_hash;                     // out-references in the order Algorithm 1 sorted them
     std::vector<int32_t> ring;                        // simple cycle through this rule, starting at it (else empty)
-    int32_t n_states() const { return (int32_t)is_final.size(); }
+    int32_t n_states() const { return (int32_t)body->is_final.size(); }
+    bool is_final(int q) const { return body->is_final[(size_t)q] != 0; }
+    Span<ByteRange> bedges(int q) const { return body->bedges[(size_t)q]; }
+    Span<RefEdge> refs(int q) const { return redges[(size_t)q]; }
 };
 
 struct Position { int32_t rule, state, sid; };
@@ -55,13 +88,12 @@ std::string describe_grammar(const Grammar& g);       // JSON
 uint64_t hash_combine(uint64_t h, uint64_t v);        // the order-sensitive hash of Algorithms 1 and 2
 
 // States of one rule that no string of at most `budget` bytes can tell apart (bounded bisimulation):
-// returns, per rule and state, the member of the state's class with the smallest canonical id.
+// returns, per state, the member of the state's class with the smallest canonical id.
 // Rule edges are compared by ref_identity[rule] (rules known to be identical may share an identity).
 // This is what makes planes independent of the bounds of a long repetition (section 3.6 observes
 // that the states inside a repetition differ minimally): tokens are at most `budget` bytes long, so
 // equivalent states have equal planes.
-std::vector<std::vector<int32_t>> bounded_classes(const Grammar& g, int32_t budget, const std::vector<uint64_t>& ref_identity);
-// One rule of the above.  The result depends only on the rule's structure and on the identities (and through them the
+// The result depends only on the rule's structure and on the identities (and through them the
 // shortest sentence and nullability) of the rules it references.
 // near (optional): for the representative x of a class, near->base[x] is the representative of another class of the
 // same rule that no string of at most near->depth[x] bytes tells apart from x (-1: none worth using), so the plane of
@@ -73,30 +105,58 @@ constexpr int32_t kMaxNearDepth = 32;
 std::vector<int32_t> bounded_classes_rule(const Grammar& g, int32_t rule, int32_t budget, const std::vector<uint64_t>& ref_identity,
                                           NearClasses* near = nullptr);
 
-// Per rule and per depth d <= budget, a 64-bit signature of everything that can follow an instance of the rule within
-// d bytes in this grammar: the set of states referencing rules continue in (as structural hashes of their
-// unfolding to the bytes that are left), recursively through rules that can end within the budget, and
-// whether the input may end (root rule).  Two rules with equal signatures reject the same uncertain
-// tokens by context expansion (section 2.2), so filtered planes can be shared across grammars
-// (section 3.3: reuse needs matching lookahead).  Rules on a reference cycle through rule ends, or behind
-// a cycle of nullable rule edges, get a process-unique signature (never shared, always sound).
-struct FollowInfo {
-    std::vector<std::vector<uint64_t>> sig;        // [rule][d], d = 0..budget: what can follow the rule within d bytes
-    std::vector<std::vector<int32_t>> min_suf;     // [rule][state]: bytes of the shortest completion of the rule from the state
+// Exact numbering of descriptions: a list of words gets the number it got before, a list not met yet the next one (from 1).
+// The lists lie back to back in one array, found through an open-addressing table.
+class NodeTable {
+  public:
+    uint32_t intern(const uint32_t* w, uint32_t n);
+    uint32_t fresh() { end_.push_back((uint32_t)words_.size()); hash_.push_back(0); return (uint32_t)end_.size(); }   // a number no list ever gets
+    uint32_t size() const { return (uint32_t)end_.size(); }
+
+  private:
+    std::vector<uint32_t> words_, end_, hash_, slot_;   // node k - 1: words [end_[k - 2], end_[k - 1]); slot: node number or 0
+    uint32_t used_ = 0;
+    void grow();
 };
-// rep (optional): per rule and state, a state that no string of at most `budget` bytes tells apart from it; sites are then
-// taken at these representatives, which leaves the follow language as it is and the work independent of repetition bounds.
-// ref_identity (optional): per rule, a number that identical rules share and different ones do not (the pool's entry);
-// without it the rule's structural hash stands in.  intern (optional): gives every distinct description (a list of words)
-// a number of its own, the same for the same list as long as the interner lives; the signatures are then such numbers
-// and comparing them is exact, not merely probable.
-using FollowInterner = std::function<uint64_t(const std::vector<uint64_t>&)>;
-// memo_of (optional, with an interner): where the value of (rule, state, depth) is kept across calls, or null for rules
-// that are not shared; a slot holding 0 is empty.
-using FollowMemo = std::function<uint64_t*(int rule, int state, int depth)>;
-FollowInfo follow_signatures(const Grammar& g, int32_t budget, const std::vector<std::vector<int32_t>>* rep = nullptr,
-                             const std::vector<uint64_t>* ref_identity = nullptr, const FollowInterner* intern = nullptr,
-                             const FollowMemo* memo_of = nullptr);
+
+// What one rule's states do on strings of at most d bytes, for every d up to the longest token.  level[d * n + c] is the
+// number (in the node table) of canonical state c's behaviour on at most d bytes: whether it is final, the byte runs with
+// the behaviours they lead to on d - 1 bytes, and the references, by identity, with what follows their shortest sentence.
+// Equal numbers, equal behaviour, across rules and grammars that share the table; states of one rule with equal numbers
+// at the budget are the classes of bounded_classes_rule (rep, near: by canonical state number too).  States on or before
+// a cycle of references to rules that derive the empty string get numbers of their own (never shared, always sound).
+struct RuleAnalysis {
+    int32_t n = 0;
+    std::vector<uint32_t> level;
+    std::vector<int32_t> rep;
+    NearClasses near;
+};
+// identity[r]: a number that identical rules share and different ones do not, for every rule that `rule` references
+RuleAnalysis analyse_rule(const Grammar& g, int32_t rule, int32_t budget, const std::vector<uint64_t>& identity, NodeTable& nodes);
+
+// What can follow an instance of a rule within d bytes in this grammar, as a number of the node table: the set of states
+// referencing rules continue in (their behaviour on the bytes that are left), recursively through rules that can end
+// within the budget, and whether the input may end (root rule).  Two rules with equal numbers reject the same uncertain
+// tokens by context expansion (section 2.2), so filtered planes can be shared across grammars (section 3.3: reuse needs
+// matching lookahead).  A rule on a reference cycle through rule ends gets a number of its own.  Computed on demand.
+class FollowSigs {
+  public:
+    // analysis[r] and rep[r] (by state number) of every rule; sites are taken at representatives, which leaves the follow
+    // language as it is and the work independent of repetition bounds
+    FollowSigs(const Grammar& g, int32_t budget, const std::vector<std::shared_ptr<const RuleAnalysis>>& analysis,
+               const std::vector<std::vector<int32_t>>& rep, NodeTable& nodes);
+    uint32_t sig(int rule, int d);
+
+  private:
+    struct Site { int32_t q, x; };
+    const Grammar& g_;
+    int32_t budget_;
+    const std::vector<std::shared_ptr<const RuleAnalysis>>& analysis_;
+    NodeTable& nodes_;
+    Rows<Site> sites_;
+    std::vector<uint32_t> memo_;                        // [rule * (budget + 1) + d]: 0 not known, kPending being computed
+    static constexpr uint32_t kPending = 0xFFFFFFFFu;
+};
 
 // Exact serialisation of one rule in Algorithm 1's canonical order; a reference to rule r is
 // written as ref_id[r].  Two rules with equal text and equal meaning of the ids are isomorphic.

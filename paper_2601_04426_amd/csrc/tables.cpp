@@ -10,6 +10,11 @@ FlatTables flatten(const Grammar& g) {
     FlatTables t;
     t.state_info.resize((size_t)g.n_states);
     t.rule_info.resize(g.rules.size());
+    {
+        size_t nb = 0, nr = 0;
+        for (const RuleFsm& f : g.rules) { nb += f.body->bedges.v.size(); nr += f.redges.v.size(); }
+        t.byte_edges.reserve(nb); t.ref_edges.reserve(nr);
+    }
     for (size_t r = 0; r < g.rules.size(); ++r) {
         const RuleFsm& f = g.rules[r];
         t.rule_info[r] = {(uint32_t)g.sid((int32_t)r, 0), f.nullable ? 1u : 0u};
@@ -17,10 +22,10 @@ FlatTables flatten(const Grammar& g) {
             StateInfo si;
             si.byte_off = (uint32_t)t.byte_edges.size();
             si.ref_off = (uint32_t)t.ref_edges.size();
-            for (auto& e : f.bedges[(size_t)q]) t.byte_edges.push_back({(uint32_t)e.lo | ((uint32_t)e.hi << 8), (uint32_t)g.sid((int32_t)r, e.tgt)});
-            for (auto& e : f.redges[(size_t)q]) t.ref_edges.push_back({(uint32_t)e.rule, (uint32_t)g.sid((int32_t)r, e.tgt)});
-            si.counts = (uint32_t)f.bedges[(size_t)q].size() | ((uint32_t)f.redges[(size_t)q].size() << 16);
-            si.rule_final = (uint32_t)r | (f.is_final[(size_t)q] ? 0x80000000u : 0u);
+            for (auto& e : f.bedges(q)) t.byte_edges.push_back({(uint32_t)e.lo | ((uint32_t)e.hi << 8), (uint32_t)g.sid((int32_t)r, e.tgt)});
+            for (auto& e : f.refs(q)) t.ref_edges.push_back({(uint32_t)e.rule, (uint32_t)g.sid((int32_t)r, e.tgt)});
+            si.counts = (uint32_t)f.bedges(q).size() | ((uint32_t)f.refs(q).size() << 16);
+            si.rule_final = (uint32_t)r | (f.is_final(q) ? 0x80000000u : 0u);
             t.state_info[(size_t)g.sid((int32_t)r, q)] = si;
         }
     }
@@ -62,57 +67,76 @@ FlatTables flatten(const Grammar& g) {
             t.dev_state[sid] = ds;
         }
     }
-    // byte classes: refine by (class so far, target) state after state.  Every edge is a byte range, so bytes between
-    // two consecutive range boundaries always behave alike: the refinement runs over those intervals, not over bytes.
+    // Byte classes: bytes that lead to the same target from every state are one class.  Every edge is a byte range, so
+    // bytes between two consecutive range boundaries always behave alike: what follows runs over those intervals.
+    // Every edge adds a 64-bit mix of (state, target) to the intervals it covers (as a difference at its two ends), so
+    // intervals that behave alike have equal sums after one pass over the edges; that intervals with equal sums behave
+    // alike is confirmed while the transitions are written below, and if it ever fails the mix is drawn anew.
     const size_t n = t.state_info.size();
     std::vector<uint8_t> is_bound(257, 0);
     is_bound[0] = 1;
     for (const ByteEdge& e : t.byte_edges) { is_bound[e.lohi & 0xFF] = 1; is_bound[((e.lohi >> 8) & 0xFF) + 1] = 1; }
     std::vector<uint32_t> iv_lo;                                    // first byte of every interval, ascending
-    std::vector<uint32_t> iv_of(256);
+    uint32_t iv_of[256];
     for (uint32_t b = 0; b < 256; ++b) {
         if (is_bound[b]) iv_lo.push_back(b);
         iv_of[b] = (uint32_t)iv_lo.size() - 1;
     }
-    const size_t m = iv_lo.size();
-    std::vector<uint32_t> cls(m, 0);
-    std::vector<int64_t> row(m);
-    struct Split { uint32_t old_class; int64_t target; uint32_t new_class; };
-    std::vector<Split> splits;
-    for (size_t sid = 0; sid < n; ++sid) {
-        const StateInfo& si = t.state_info[sid];
-        if (!(si.counts & 0xFFFF)) continue;
-        std::fill(row.begin(), row.end(), -1);
-        for (uint32_t k = 0; k < (si.counts & 0xFFFF); ++k) {
-            const ByteEdge& e = t.byte_edges[si.byte_off + k];
-            for (uint32_t j = iv_of[e.lohi & 0xFF]; j <= iv_of[(e.lohi >> 8) & 0xFF]; ++j) row[j] = e.tgt;
+    const uint32_t m = (uint32_t)iv_lo.size();
+    t.sink = (uint32_t)n;
+    std::vector<uint32_t> cls(m), cls_size;                         // interval -> class; intervals of each class
+    std::vector<uint8_t> is_first(m);                               // the interval is the first of its class
+    std::vector<uint64_t> sum(m + 1);
+    for (uint64_t salt = 0x9E3779B97F4A7C15ull;; salt += 0x632BE59BD9B4E019ull) {
+        std::fill(sum.begin(), sum.end(), 0);
+        for (size_t sid = 0; sid < n; ++sid) {
+            const StateInfo& si = t.state_info[sid];
+            for (uint32_t k = 0; k < (si.counts & 0xFFFF); ++k) {
+                const ByteEdge& e = t.byte_edges[si.byte_off + k];
+                uint64_t x = (((uint64_t)sid << 32) | e.tgt) * 0xFF51AFD7ED558CCDull + salt;
+                x ^= x >> 29; x *= 0xC4CEB9FE1A85EC53ull; x ^= x >> 32;
+                sum[iv_of[e.lohi & 0xFF]] += x;
+                sum[iv_of[(e.lohi >> 8) & 0xFF] + 1] -= x;
+            }
         }
-        splits.clear();                                             // few per state: searched linearly
-        for (size_t j = 0; j < m; ++j) {
-            const uint32_t oc = cls[j];
-            const int64_t tg = row[j];
-            int nc = -1;
-            for (const Split& sp : splits) if (sp.old_class == oc && sp.target == tg) { nc = (int)sp.new_class; break; }
-            if (nc < 0) { nc = (int)splits.size(); splits.push_back({oc, tg, (uint32_t)nc}); }
-            cls[j] = (uint32_t)nc;
+        uint32_t nc = 0;                                            // classes are numbered by their smallest byte
+        cls_size.clear();
+        std::vector<uint64_t> of_class;
+        uint64_t run = 0;
+        for (uint32_t j = 0; j < m; ++j) {
+            run += sum[j];
+            uint32_t c = 0;
+            while (c < nc && of_class[c] != run) ++c;
+            is_first[j] = c == nc;
+            if (c == nc) { of_class.push_back(run); cls_size.push_back(0); ++nc; }
+            cls[j] = c;
+            ++cls_size[c];
         }
+        if (nc > 256) throw std::logic_error("more byte classes than bytes");
+        t.n_classes = nc;
+        // one row more than there are states: the sink, which every missing edge leads to and which leads to itself, so
+        // that an automaton walk needs no "is there an edge" branch (a dead run just stays in the sink)
+        t.trans.assign((n + 1) * nc, t.sink);
+        bool alike = true;
+        for (size_t sid = 0; sid < n && alike; ++sid) {
+            const StateInfo& si = t.state_info[sid];
+            uint32_t* row = t.trans.data() + sid * nc;
+            uint32_t covered = 0, expected = 0;                     // intervals with an edge; intervals of the classes seen
+            for (uint32_t k = 0; k < (si.counts & 0xFFFF); ++k) {
+                const ByteEdge& e = t.byte_edges[si.byte_off + k];
+                const uint32_t ref = t.ref(e.tgt), j0 = iv_of[e.lohi & 0xFF], j1 = iv_of[(e.lohi >> 8) & 0xFF];
+                covered += j1 - j0 + 1;
+                for (uint32_t j = j0; j <= j1; ++j) {
+                    if (is_first[j]) { row[cls[j]] = ref; expected += cls_size[cls[j]]; }
+                    else alike &= row[cls[j]] == ref;
+                }
+            }
+            alike &= covered == expected;
+        }
+        if (alike) break;
     }
-    t.n_classes = *std::max_element(cls.begin(), cls.end()) + 1;
-    if (t.n_classes > 256) throw std::logic_error("more byte classes than bytes");
     t.byte_class_words.assign(64, 0);
     for (int b = 0; b < 256; ++b) t.byte_class_words[(size_t)b >> 2] |= cls[iv_of[(size_t)b]] << ((b & 3) * 8);
-    // one row more than there are states: the sink, which every missing edge leads to and which leads to itself, so
-    // that an automaton walk needs no "is there an edge" branch (a dead run just stays in the sink)
-    t.sink = (uint32_t)n;
-    t.trans.assign((n + 1) * t.n_classes, t.sink);
-    for (size_t sid = 0; sid < n; ++sid) {
-        const StateInfo& si = t.state_info[sid];
-        for (uint32_t k = 0; k < (si.counts & 0xFFFF); ++k) {
-            const ByteEdge& e = t.byte_edges[si.byte_off + k];
-            const uint32_t ref = t.ref(e.tgt);
-            for (uint32_t j = iv_of[e.lohi & 0xFF]; j <= iv_of[(e.lohi >> 8) & 0xFF]; ++j) t.trans[sid * t.n_classes + cls[j]] = ref;
-        }
-    }
     return t;
 }
 
