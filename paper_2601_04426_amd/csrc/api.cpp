@@ -61,6 +61,56 @@ struct DevBuf {                                    // owning device array
     }
 };
 
+// Device blocks that outlive the pool or cache they were part of: a request's planes and tables come and go, and allocating
+// and freeing them in the driver costs 50 - 350 us a block (it maps and unmaps the memory), as much as building the planes of
+// a small grammar.  Bounded (kMaxSpare bytes are kept, the rest is freed); what is kept goes back to the driver with the
+// vocabulary that owns the list, or when an allocation fails.  Work in flight may still use a block that is handed in: it is
+// waited for, which is what freeing it would have done.
+class BlockList {
+    static constexpr size_t kMaxSpare = (size_t)1 << 30;
+    struct Block { void* p; size_t n; };
+    std::mutex mu;
+    std::vector<Block> spare;
+    size_t spare_bytes = 0;
+    void drop_all() { for (Block& b : spare) (void)hipFree(b.p); spare.clear(); spare_bytes = 0; }
+
+  public:
+    ~BlockList() { drop_all(); }
+    // a block of at least n bytes, contents unspecified; *size receives what it really holds (to be given to put)
+    void* get(size_t n, size_t* size) {
+        n = (n + 0xFFFF) & ~(size_t)0xFFFF;
+        std::lock_guard<std::mutex> lk(mu);
+        size_t best = spare.size();
+        for (size_t k = 0; k < spare.size(); ++k)                   // the smallest that fits, unless it is far too large
+            if (spare[k].n >= n && spare[k].n <= 2 * n + ((size_t)1 << 20) && (best == spare.size() || spare[k].n < spare[best].n)) best = k;
+        if (best < spare.size()) {
+            void* p = spare[best].p;
+            *size = spare[best].n;
+            spare_bytes -= spare[best].n;
+            spare[best] = spare.back();
+            spare.pop_back();
+            return p;
+        }
+        void* p = nullptr;
+        if (hipMalloc(&p, n) != hipSuccess) {
+            (void)hipGetLastError();
+            drop_all();
+            HIP_CHECK(hipMalloc(&p, n));
+        }
+        *size = n;
+        return p;
+    }
+    // the caller has waited for the work in flight (wait_idle)
+    void put(void* p, size_t n) {
+        {
+            std::lock_guard<std::mutex> lk(mu);
+            if (spare_bytes + n <= kMaxSpare) { spare.push_back({p, n}); spare_bytes += n; return; }
+        }
+        (void)hipFree(p);
+    }
+    static void wait_idle() { (void)hipDeviceSynchronize(); }
+};
+
 // Pinned host memory to device memory on `stream`: small blocks by a copy kernel that reads the host memory through its
 // device-side address (less latency than the copy engine), large ones by the runtime.  bytes: a multiple of 16.
 constexpr size_t kUploadByKernelMax = (size_t)4 << 20;
@@ -131,8 +181,9 @@ struct Packer {
         reserved = (reserved + bytes + 255) & ~(size_t)255;
         return off;
     }
-    // own_dev: the device block is allocated for this upload and belongs to the caller afterwards
-    void stage(bool own_dev, StagingSet& S) {
+    // own: the device block comes from this list (null: from the staging set) and belongs to the caller afterwards
+    size_t dev_bytes = 0;
+    void stage(BlockList* own, StagingSet& S) {
         const size_t n = std::max<size_t>(total, 256), n_dev = n + reserved;
         if (S.host_cap < n) {
             if (S.host) (void)hipHostFree(S.host);
@@ -142,8 +193,8 @@ struct Packer {
             S.host_cap = cap;
         }
         host = S.host;
-        if (own_dev) {
-            HIP_CHECK(hipMalloc((void**)&dev, n_dev));
+        if (own) {
+            dev = static_cast<uint8_t*>(own->get(n_dev, &dev_bytes));
         } else {
             if (S.dev_cap < n_dev) {
                 if (S.dev) (void)hipFree(S.dev);
@@ -192,6 +243,7 @@ void require_device() {
 
 // ---- vocabulary --------------------------------------------------------------------------------------
 struct VocabImpl {
+    BlockList blocks;                           // spare device memory of the pools and caches of this vocabulary
     int32_t V = 0, eos = 0;
     uint32_t W = 0;
     std::vector<uint8_t> bytes;                 // id order
@@ -393,9 +445,40 @@ struct PoolImpl {
     size_t max_bytes = 0;
     std::mutex mu;
     std::shared_ptr<VocabImpl> vocab;           // bound at first use
-    struct Entry { uint64_t hash; std::string text; };
+    // An interned rule in its canonical form: the automaton (shared with the grammars that hold it), the canonical numbering
+    // where that is not the automaton's own, and the references with the entries they lead to.  Rules on a reference cycle
+    // are kept as the text of the whole cycle instead.
+    struct Entry { uint64_t hash; std::shared_ptr<const RuleBody> body; std::vector<int32_t> canon_id, by_canon; Rows<RefEdge> refs; std::string text; };
     std::vector<Entry> entries;
     std::unordered_multimap<uint64_t, int> by_hash;
+    bool same_rule(const Entry& e, const RuleFsm& f, const std::vector<uint64_t>& ref_id) const {
+        if (!e.body) return false;
+        const int n = f.n_states();
+        auto refs_equal = [&](int s, int t) {                        // s: the entry's state, t: the rule's
+            const Span<RefEdge> a = e.refs[(size_t)s], b = f.redges_by_hash[(size_t)t];
+            if (a.size() != b.size()) return false;
+            for (size_t k = 0; k < a.size(); ++k)
+                if ((uint64_t)a[k].rule != ref_id[(size_t)b[k].rule] || (e.canon_id.empty() ? a[k].tgt : e.canon_id[(size_t)a[k].tgt]) != f.canon_id[(size_t)b[k].tgt]) return false;
+            return true;
+        };
+        if (e.body == f.body && e.canon_id.empty()) {                // the very same automaton (which numbers its states canonically)
+            if (!f.body->single_refs) return false;
+            for (size_t k = 0; k < e.refs.v.size(); ++k)
+                if ((uint64_t)e.refs.v[k].rule != ref_id[(size_t)f.redges_by_hash.v[k].rule]) return false;
+            return true;
+        }
+        if ((int)e.body->is_final.size() != n) return false;
+        for (int c = 0; c < n; ++c) {
+            const int s = e.by_canon.empty() ? c : e.by_canon[(size_t)c], t = f.by_canon[(size_t)c];
+            if (e.body->is_final[(size_t)s] != f.body->is_final[(size_t)t]) return false;
+            const Span<ByteRange> a = e.body->bedges[(size_t)s], b = f.bedges(t);
+            if (a.size() != b.size()) return false;
+            for (size_t k = 0; k < a.size(); ++k)
+                if (a[k].lo != b[k].lo || a[k].hi != b[k].hi || (e.canon_id.empty() ? a[k].tgt : e.canon_id[(size_t)a[k].tgt]) != f.canon_id[(size_t)b[k].tgt]) return false;
+            if (!refs_equal(s, t)) return false;
+        }
+        return true;
+    }
     std::deque<PlaneRow> row_store;                         // every row ever handed out (addresses stay)
     FlatMap<PlaneKey, PlaneRow*, PlaneKeyHash> rows;        // planes that may be shared, by key
     // per structure (the key with its follow language blanked), one row built under the follow filter: what a plane of the
@@ -412,9 +495,9 @@ struct PoolImpl {
     std::vector<PlaneRow*> free_rows;
     uint64_t clock = 0;
     int64_t n_evicted = 0;
-    std::vector<void*> slabs;
-    // memory to clear before the next build writes to it: freshly allocated slabs and rows taken from the free list.
-    // The build enqueues the fills inside its timed region (skipped tokens rely on the zeros).
+    std::vector<std::pair<void*, size_t>> slabs;
+    // memory to clear before the next build writes to it: the rows handed out since the one before (neighbours as one
+    // range).  The build enqueues the clearing inside its timed region (skipped tokens rely on the zeros).
     std::vector<std::pair<void*, size_t>> to_zero;
     void flush_zero(hipStream_t stream) {
         for (auto& z : to_zero) HIP_CHECK(hipMemsetAsync(z.first, 0, z.second, stream));
@@ -423,18 +506,33 @@ struct PoolImpl {
     uint8_t* slab_cur = nullptr; size_t slab_left = 0;
     size_t device_bytes = 0;
     int64_t n_rows = 0;
-    ~PoolImpl() { for (void* s : slabs) (void)hipFree(s); }
+    ~PoolImpl() {
+        if (!slabs.empty()) BlockList::wait_idle();
+        for (auto& s : slabs) vocab->blocks.put(s.first, s.second);
+    }
 
-    // exact interning: same hash AND same serialisation
+    // exact interning: same hash AND same canonical form
     int intern(uint64_t hash, const std::string& text, bool shareable) {
         if (shareable) {
             auto range = by_hash.equal_range(hash);
             for (auto it = range.first; it != range.second; ++it)
-                if (entries[(size_t)it->second].text == text) return it->second;
+                if (!entries[(size_t)it->second].body && entries[(size_t)it->second].text == text) return it->second;
         }
-        entries.push_back({hash, shareable ? text : std::string()});
-        int id = (int)entries.size() - 1;
-        if (shareable) by_hash.emplace(hash, id);
+        return add_entry({hash, nullptr, {}, {}, {}, shareable ? text : std::string()}, shareable);
+    }
+    int intern(const RuleFsm& f, const std::vector<uint64_t>& ref_id) {      // a rule on no cycle
+        auto range = by_hash.equal_range(f.hash);
+        for (auto it = range.first; it != range.second; ++it)
+            if (same_rule(entries[(size_t)it->second], f, ref_id)) return it->second;
+        Entry e{f.hash, f.body, {}, {}, f.redges_by_hash, {}};
+        for (RefEdge& r : e.refs.v) r.rule = (int32_t)ref_id[(size_t)r.rule];
+        if (!f.body->single_refs) { e.canon_id = f.canon_id; e.by_canon = f.by_canon; }
+        return add_entry(std::move(e), true);
+    }
+    int add_entry(Entry e, bool shareable) {
+        const int id = (int)entries.size();
+        if (shareable) by_hash.emplace(e.hash, id);
+        entries.push_back(std::move(e));
         return id;
     }
     void take(PlaneRow* row) { ++row->refs; row->stamp = ++clock; }      // a cache starts using the row
@@ -451,8 +549,7 @@ struct PoolImpl {
         free_rows.push_back(row);
         --n_rows;
     }
-    // rows_ahead: how many rows the caller is about to ask for, this one included (sizes a new slab: what is
-    // allocated is zeroed by the build that first uses it, so a small build should not pay for a large slab)
+    // rows_ahead: how many rows the caller is about to ask for, this one included (sizes a new slab)
     PlaneRow* alloc_row(const PlaneKey& key, size_t row_bytes, size_t rows_ahead = 1) {
         if (free_rows.empty() && slab_left < row_bytes) {
             size_t want = std::min<size_t>(std::max<size_t>({row_bytes * 64, (size_t)8 << 20, rows_ahead * row_bytes}), (size_t)256 << 20);
@@ -468,10 +565,9 @@ struct PoolImpl {
                 std::partial_sort(idle.begin(), idle.begin() + (long)batch, idle.end());
                 for (size_t k = 0; k < batch; ++k) { forget(idle[k].second); ++n_evicted; }
             } else {
-                void* p = nullptr;
-                HIP_CHECK(hipMalloc(&p, want));
-                slabs.push_back(p);
-                to_zero.emplace_back(p, want);                       // rows are handed out as zeros
+                size_t got = 0;
+                void* p = vocab->blocks.get(want, &got);
+                slabs.emplace_back(p, got);
                 slab_cur = (uint8_t*)p; slab_left = want; device_bytes += want;
             }
         }
@@ -483,6 +579,8 @@ struct PoolImpl {
             row_store.emplace_back();
             row = &row_store.back();
             row->mem = (uint32_t*)slab_cur;
+            if (!to_zero.empty() && (uint8_t*)to_zero.back().first + to_zero.back().second == slab_cur) to_zero.back().second += row_bytes;
+            else to_zero.emplace_back(slab_cur, row_bytes);
             slab_cur += row_bytes; slab_left -= row_bytes;
         }
         row->key = key; row->refs = 0; row->stamp = 0; row->no_uncertain = false; row->in_use = true;
@@ -523,7 +621,7 @@ struct CacheImpl {
     std::shared_ptr<VocabImpl> vocab;
     std::shared_ptr<PoolImpl> pool;
     std::shared_ptr<GrammarImpl> gram;
-    uint8_t* d_tables = nullptr;                            // one device block holding all packed tables
+    uint8_t* d_tables = nullptr; size_t d_tables_bytes = 0;  // one device block holding all packed tables
     ~CacheImpl();
     DevTables dt{};
     int32_t context_depth = 2;
@@ -739,7 +837,7 @@ void finalize_ticket(BuildTicket& T) {
             // ticket); its memory is not handed out again while they may still hold it
             pool.unlist(row);
         } else {
-            const uint32_t n_acc = S.res[2 + 2 * k], n_unc = S.res[3 + 2 * k];
+            const uint32_t n_acc = S.res[4 + 2 * k], n_unc = S.res[5 + 2 * k];
             row->no_uncertain = n_unc == 0;
             if (row->key[4] != 0) pool.by_structure.emplace(PoolImpl::structure_of(row->key), row);
             T.n_accepted += n_acc; T.n_uncertain += n_unc;
@@ -780,7 +878,7 @@ CacheImpl::~CacheImpl() {
         std::lock_guard<std::mutex> lk(pool->mu);
         for (const PlaneInfo& pi : planes) if (pi.row) pool->release(pi.row);
     }
-    if (d_tables) (void)hipFree(d_tables);
+    if (d_tables) { BlockList::wait_idle(); vocab->blocks.put(d_tables, d_tables_bytes); }
 }
 
 // Enqueues the build of the planes `todo` of a cache that do not hold a row yet: rows the pool already has are taken
@@ -1057,7 +1155,7 @@ int32_t build_planes(CacheImpl& cache, const std::vector<int32_t>& todo, hipStre
 
     // everything the device needs goes up in one copy: (the tables,) the plan, and a few zeroed words (overflow
     // counter and flag, bit counts per built plane).  With the tables the block stays with the cache.
-    std::vector<uint32_t> zeros(8 + 2 * build_rows.size(), 0u);
+    std::vector<uint32_t> zeros(8 + ((2 * build_rows.size() + 3) & ~(size_t)3), 0u);
     Packer tab;
     size_t o_state = 0, o_exp = 0, o_soff = 0, o_stgt = 0, o_trans = 0, o_cls = 0;
     if (with_tables) {
@@ -1067,12 +1165,13 @@ int32_t build_planes(CacheImpl& cache, const std::vector<int32_t>& todo, hipStre
     const size_t o_range_a = tab.add(range_a), o_range_b = tab.add(range_b), o_range_first = tab.add(range_first), o_pctx = tab.add(plane_ctx), o_items = tab.add(ctx_items), o_wait = tab.add(ctx_wait),
                  o_wait_off = tab.add(ctx_wait_off), o_rows = tab.add(build_rows), o_copies = tab.add(copies), o_structure_copies = tab.add(structure_copies), o_fb_copies = tab.add(fb_copies), o_finish = tab.add(finish), o_zero = tab.add(zeros);
     const size_t o_chunks = tab.reserve(n_chunks * 2 * sizeof(uint4));
-    tab.stage(with_tables, SS);
-    if (with_tables) cache.d_tables = tab.dev;                     // the cache owns the block from here on
+    tab.stage(with_tables ? &V.blocks : nullptr, SS);
+    if (with_tables) { cache.d_tables = tab.dev; cache.d_tables_bytes = tab.dev_bytes; }                     // the cache owns the block from here on
     ticket->host_ms = ms_since(t1);
 
     SS.ensure_events();
-    SS.ensure_res(2 + 2 * build_rows.size());
+    const size_t result_words = (4 + 2 * build_rows.size() + 3) & ~(size_t)3;     // S.count[0 .. 3], then the counts: 16-byte words
+    SS.ensure_res(result_words);
     const hipEvent_t ev0 = SS.ev[0], ev1 = SS.ev[1], evk0 = SS.ev[2], evk1 = SS.ev[3];
     {
         // after the build enqueued before this one, whatever its stream
@@ -1143,8 +1242,11 @@ int32_t build_planes(CacheImpl& cache, const std::vector<int32_t>& todo, hipStre
         if (!build.empty()) launch_plane_summary(d_rows_p, (uint32_t)build_rows.size(), V.W, d_counts, stream);   // statistics, lists of uncertain tokens
     }
     HIP_CHECK(hipEventRecord(ev1, stream));                              // every plane is written, with its list of uncertain tokens
-    HIP_CHECK(hipMemcpyAsync(SS.res, S.count, 2 * sizeof(uint32_t), hipMemcpyDeviceToHost, stream));
-    if (!build_rows.empty()) HIP_CHECK(hipMemcpyAsync(SS.res + 2, d_counts, 2 * build_rows.size() * sizeof(uint32_t), hipMemcpyDeviceToHost, stream));
+    {   // overflow counter and flag, bit counts per plane: written to the pinned words by a kernel (a copy call costs more than the launch)
+        void* res_dev = nullptr;
+        HIP_CHECK(hipHostGetDevicePointer(&res_dev, SS.res, 0));
+        launch_upload(res_dev, S.count, result_words * sizeof(uint32_t), stream);
+    }
     HIP_CHECK(hipEventRecord(SS.ev[4], stream));
     HIP_CHECK(hipGetLastError());
     // from here on the build is under way: the planes have their rows, the ticket says what became of them
@@ -1445,7 +1547,7 @@ int32_t xg2_compile_grammar(xg2_vocab* vocab, const char* ebnf, size_t len, cons
                 for (int r : comp) entry[(size_t)r] = pool.intern(g.rules[(size_t)r].hash, "", false);
             } else if (first.ring.empty()) {
                 int r = comp[0];
-                entry[(size_t)r] = pool.intern(first.hash, serialise_rule(g, r, ref_id), true);
+                entry[(size_t)r] = pool.intern(first, ref_id);
             } else {
                 std::vector<uint64_t> ids = ref_id;
                 for (int r : comp) ids[(size_t)r] = kInCycleRef;
@@ -1474,20 +1576,18 @@ int32_t xg2_compile_grammar(xg2_vocab* vocab, const char* ebnf, size_t len, cons
                 std::shared_ptr<const RuleAnalysis>& known = pool.analysis[(size_t)entry[(size_t)r]];
                 if (known) analysis[(size_t)r] = known;           // an identical rule was analysed before (this grammar or an earlier one)
                 else {
-                    analysis[(size_t)r] = std::make_shared<const RuleAnalysis>(analyse_rule(g, r, budget, ref_id, pool.nodes));
+                    analysis[(size_t)r] = std::make_shared<const RuleAnalysis>(analyse_rule(g, r, budget, ref_id));
                     if (f.shareable) known = analysis[(size_t)r];
                 }
                 // from canonical numbers to this grammar's state numbers
                 const RuleAnalysis& A = *analysis[(size_t)r];
-                std::vector<int32_t> by_canon(n);
-                for (size_t x = 0; x < n; ++x) by_canon[(size_t)f.canon_id[x]] = (int32_t)x;
                 NearClasses& nr = near[(size_t)r];
                 classes[(size_t)r].resize(n);
                 nr.base.resize(n); nr.depth.resize(n);
                 for (size_t x = 0; x < n; ++x) {
                     const size_t c = (size_t)f.canon_id[x];
-                    classes[(size_t)r][x] = by_canon[(size_t)A.rep[c]];
-                    nr.base[x] = A.near.base[c] < 0 ? -1 : by_canon[(size_t)A.near.base[c]];
+                    classes[(size_t)r][x] = f.by_canon[(size_t)A.rep[c]];
+                    nr.base[x] = A.near.base[c] < 0 ? -1 : f.by_canon[(size_t)A.near.base[c]];
                     nr.depth[x] = A.near.depth[c];
                 }
             }
@@ -1498,7 +1598,7 @@ int32_t xg2_compile_grammar(xg2_vocab* vocab, const char* ebnf, size_t len, cons
             for (int r = 0; r < R; ++r) { rep[(size_t)r].resize((size_t)g.rules[(size_t)r].n_states()); std::iota(rep[(size_t)r].begin(), rep[(size_t)r].end(), 0); }
         }
         std::unique_ptr<FollowSigs> follow_sigs;
-        if (follow) follow_sigs.reset(new FollowSigs(g, budget, analysis, classes, pool.nodes));
+        if (follow) follow_sigs.reset(new FollowSigs(g, budget, analysis, classes, ref_id, pool.nodes));
         // Reference sites of every rule, one per class of the states referencing rules continue in (in the order they are
         // met; `key` numbers them by the state that stands for the class), each with the member of the smallest canonical id.
         struct Site { int32_t q, waiter, x; uint32_t key; };
@@ -1628,26 +1728,35 @@ int32_t xg2_compile_grammar(xg2_vocab* vocab, const char* ebnf, size_t len, cons
                 if (x == b0 || !plain(f, x) || !plain(f, b0) || f.is_final(x) != f.is_final(b0)) continue;
                 int32_t& of = fb_of[pi.sid];
                 if (of == kNotCompared) {
-                    // both edge lists side by side: per stretch of bytes, where each of the two states goes (-1: nowhere)
-                    uint64_t differ = 0, all = 0;
-                    std::array<uint32_t, 8> same{};
+                    // tokens whose first byte the state reads, and those of them that the start state sends elsewhere
                     const Span<ByteRange> ex = f.bedges(x), ey = f.bedges(b0);
-                    size_t ix = 0, iy = 0;
-                    for (int b = 0; b < 256;) {
-                        while (ix < ex.size() && (int)ex[ix].hi < b) ++ix;
-                        while (iy < ey.size() && (int)ey[iy].hi < b) ++iy;
-                        int end = 255;                               // last byte of the stretch
-                        int32_t tx = -1, ty = -1;
-                        if (ix < ex.size()) { if ((int)ex[ix].lo <= b) { tx = rp[(size_t)ex[ix].tgt]; end = std::min<int>(end, ex[ix].hi); } else end = std::min<int>(end, ex[ix].lo - 1); }
-                        if (iy < ey.size()) { if ((int)ey[iy].lo <= b) { ty = rp[(size_t)ey[iy].tgt]; end = std::min<int>(end, ey[iy].hi); } else end = std::min<int>(end, ey[iy].lo - 1); }
-                        const uint64_t n_b = V.fb_start[end + 1] - V.fb_start[b];
-                        if (tx == ty) for (int c = b; c <= end; ++c) same[(size_t)c >> 5] |= 1u << (c & 31);
-                        else if (tx >= 0) differ += n_b;
-                        if (tx >= 0) all += n_b;
-                        b = end + 1;
+                    uint64_t differ = 0, all = 0;
+                    size_t iy = 0;
+                    for (const ByteRange& e : ex) {
+                        all += V.fb_start[(int)e.hi + 1] - V.fb_start[e.lo];
+                        for (int b = e.lo; b <= e.hi;) {             // stretches on which the start state goes one way (-1: nowhere)
+                            while (iy < ey.size() && (int)ey[iy].hi < b) ++iy;
+                            int end = e.hi;
+                            int32_t ty = -1;
+                            if (iy < ey.size()) {
+                                if ((int)ey[iy].lo <= b) { ty = rp[(size_t)ey[iy].tgt]; end = std::min<int>(end, ey[iy].hi); }
+                                else end = std::min<int>(end, ey[iy].lo - 1);
+                            }
+                            if (ty != rp[(size_t)e.tgt]) differ += V.fb_start[end + 1] - V.fb_start[b];
+                            b = end + 1;
+                        }
                     }
                     of = kNotWorth;
-                    if (differ * 2 <= all) { of = (int32_t)cache->fb_same.size(); cache->fb_same.push_back(same); }   // else too little to gain
+                    if (differ * 2 <= all) {                         // else too little to gain
+                        int32_t tx[256], ty[256];
+                        std::fill(tx, tx + 256, -1); std::fill(ty, ty + 256, -1);
+                        for (auto& e : ex) for (int b = e.lo; b <= e.hi; ++b) tx[b] = rp[(size_t)e.tgt];
+                        for (auto& e : ey) for (int b = e.lo; b <= e.hi; ++b) ty[b] = rp[(size_t)e.tgt];
+                        std::array<uint32_t, 8> same{};
+                        for (int b = 0; b < 256; ++b) if (tx[b] == ty[b]) same[(size_t)b >> 5] |= 1u << (b & 31);
+                        of = (int32_t)cache->fb_same.size();
+                        cache->fb_same.push_back(same);
+                    }
                 }
                 if (of == kNotWorth) continue;
                 const int32_t base = sibling(pi, b0);
@@ -1961,6 +2070,7 @@ int32_t fill_common(xg2_matcher* const* matchers, int32_t B, int32_t* bitmask_de
                                            " rows and " + std::to_string(kNoAllocMaskWords) + " mask words, rows x ceil(V/32), per call)");
         } else V.ensure_device();
 
+        std::shared_ptr<BuildTicket> waited;                        // the build this call's stream waits for already
         // caches compiled just in time (section 3.5): the planes this step's frontiers need and that hold no row yet
         // are built first, on the same stream
         {
@@ -2022,6 +2132,7 @@ int32_t fill_common(xg2_matcher* const* matchers, int32_t B, int32_t* bitmask_de
                     ++C.jit_calls;
                     C.jit_tickets.push_back(ticket);
                     HIP_CHECK(hipStreamWaitEvent(stream, ticket->staging->ev[4], 0));
+                    waited = ticket;                                // builds follow one another: the latest stands for all
                 }
             }
         }
@@ -2072,7 +2183,7 @@ int32_t fill_common(xg2_matcher* const* matchers, int32_t B, int32_t* bitmask_de
             // on the device, after the latest build (the one this call issued, or one a compile call issued on another stream)
             std::lock_guard<std::mutex> ck(build_chain().mu);
             const std::shared_ptr<BuildTicket>& last = build_chain().last;
-            if (last && last->state == 0 && last->staging && last->stream != stream) HIP_CHECK(hipStreamWaitEvent(stream, last->staging->ev[4], 0));
+            if (last && last != waited && last->state == 0 && last->staging && last->stream != stream) HIP_CHECK(hipStreamWaitEvent(stream, last->staging->ev[4], 0));
         }
         std::lock_guard<std::mutex> ws_lock(fill_ws().mu);
         std::lock_guard<std::mutex> slow_lock(slow().mu);

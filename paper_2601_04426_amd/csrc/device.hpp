@@ -116,7 +116,7 @@ void launch_finish_planes(uint32_t* const* plane_ptr_dev, const FinishJob* jobs_
 // A plane in device memory: three rows of W words (accepted, uncertain, left early) and behind them the list of its
 // uncertain tokens: word 0 = how many (the list holds them if that is at most kUncListWords - 1), then their token ids.
 constexpr uint32_t kUncListWords = 64;
-constexpr size_t plane_words(uint32_t W) { return 3 * (size_t)W + kUncListWords; }
+constexpr size_t plane_words(uint32_t W) { return (3 * (size_t)W + kUncListWords + 3) & ~(size_t)3; }   // rows start 16-byte aligned
 // counts_dev[2p], counts_dev[2p + 1] = set bits of the accepted and of the uncertain row of plane p; also writes the
 // plane's list of uncertain tokens
 void launch_plane_summary(uint32_t* const* plane_ptr_dev, uint32_t n_pos, uint32_t W, uint32_t* counts_dev, hipStream_t stream);
@@ -188,7 +188,7 @@ void launch_accept(const BatchDev& D, const DevVocab& Vd, uint32_t eos_id, const
 void launch_batch_assign(const BatchDev& D, const int32_t* rows_dev, uint32_t n, uint32_t cache_idx, hipStream_t stream);
 
 // Copies `bytes` (a multiple of 16) from pinned host memory, given by its device-side address, to device memory with
-// a kernel: for the small per-call uploads this has less latency than the copy engine.
+// a kernel, or the other way: for the small per-call transfers this has less latency than the copy engine.
 void launch_upload(void* dst_dev, const void* src_host_mapped, size_t bytes, hipStream_t stream);
 
 // The entry point that allocates nothing works in a fixed device array of the library (one per GPU, kept until the

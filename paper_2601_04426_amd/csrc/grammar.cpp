@@ -768,7 +768,8 @@ uint64_t hash_one_fsm(RuleFsm& f, const std::vector<uint64_t>& ref_hash) {
     // phase 1: out-edges sorted (ranges by (min,max); references by hash), BFS canonical ids
     f.redges_by_hash = f.redges;
     f.canon_id.resize((size_t)n);
-    std::vector<int> order((size_t)n);
+    std::vector<int32_t>& order = f.by_canon;
+    order.resize((size_t)n);
     if (f.body->single_refs) {
         // With at most one reference a state there is nothing to sort, and the automaton is numbered in this very order
         // already (minimise_canonical: targets by ascending smallest byte, then the reference).
@@ -936,13 +937,11 @@ uint64_t hash_combine(uint64_t h, uint64_t v) {
 std::string serialise_rule(const Grammar& g, int32_t rule, const std::vector<uint64_t>& ref_id) {
     const RuleFsm& f = g.rules[(size_t)rule];
     const int n = f.n_states();
-    std::vector<int> by_canon((size_t)n);
-    for (int s = 0; s < n; ++s) by_canon[(size_t)f.canon_id[(size_t)s]] = s;
     std::string text;
     text.resize((size_t)n * 2 + f.body->bedges.v.size() * 7 + f.redges.v.size() * 13);
     char* p = text.data();
     auto put32 = [&](uint32_t v) { std::memcpy(p, &v, 4); p += 4; };
-    for (int s : by_canon) {
+    for (int s : f.by_canon) {
         *p++ = 'N'; *p++ = (char)f.is_final(s);
         for (auto& e : f.bedges(s)) { *p++ = 'R'; *p++ = (char)e.lo; *p++ = (char)e.hi; put32((uint32_t)f.canon_id[(size_t)e.tgt]); }
         for (auto& e : f.redges_by_hash[(size_t)s]) {
@@ -1267,35 +1266,52 @@ std::vector<int32_t> bounded_classes_rule(const Grammar& g, int32_t rule, int32_
     return rep_r;
 }
 
-uint32_t NodeTable::intern(const uint32_t* w, uint32_t n) {
-    if ((used_ + 1) * 2 > slot_.size()) grow();
-    uint64_t h = n;
-    for (uint32_t k = 0; k < n; ++k) { h = (h ^ w[k]) * 0x9FB21C651E98DF25ull; h ^= h >> 32; }
-    const uint32_t h32 = (uint32_t)h, mask = (uint32_t)slot_.size() - 1;
-    for (uint32_t at = h32 & mask;; at = (at + 1) & mask) {
-        const uint32_t k = slot_[at];
-        if (!k) {
-            words_.insert(words_.end(), w, w + n);
-            end_.push_back((uint32_t)words_.size());
-            hash_.push_back(h32);
-            ++used_;
-            return slot_[at] = (uint32_t)end_.size();
+uint32_t NodeTable::intern3(uint32_t a, uint32_t b, uint32_t c) {
+    if ((n_three_ + 1) * 2 > three_.size()) {
+        std::vector<Three> old(three_.empty() ? 4096 : three_.size() * 2, Three{0, 0, 0, 0});
+        old.swap(three_);
+        const uint32_t mask = (uint32_t)three_.size() - 1;
+        for (const Three& t : old) {
+            if (!t.id) continue;
+            uint32_t at = mix3(t.a, t.b, t.c) & mask;
+            while (three_[at].id) at = (at + 1) & mask;
+            three_[at] = t;
         }
-        if (hash_[k - 1] != h32) continue;
-        const uint32_t lo = k > 1 ? end_[k - 2] : 0u;
-        if (end_[k - 1] - lo == n && std::equal(w, w + n, words_.data() + lo)) return k;
+    }
+    const uint32_t mask = (uint32_t)three_.size() - 1;
+    for (uint32_t at = mix3(a, b, c) & mask;; at = (at + 1) & mask) {
+        Three& t = three_[at];
+        if (!t.id) { t = {++count_, a, b, c}; ++n_three_; return t.id; }
+        if (t.a == a && t.b == b && t.c == c) return t.id;
     }
 }
-void NodeTable::grow() {
-    std::vector<uint32_t> old;
-    old.swap(slot_);
-    slot_.assign(old.empty() ? 4096 : old.size() * 2, 0);
-    const uint32_t mask = (uint32_t)slot_.size() - 1;
-    for (uint32_t k : old) {
-        if (!k) continue;
-        uint32_t at = hash_[k - 1] & mask;
-        while (slot_[at]) at = (at + 1) & mask;
-        slot_[at] = k;
+
+uint32_t NodeTable::intern_long(const uint32_t* w, uint32_t n) {
+    if ((n_long_ + 1) * 2 > long_.size()) {
+        std::vector<Long> old(long_.empty() ? 1024 : long_.size() * 2, Long{0, 0, 0, 0});
+        old.swap(long_);
+        const uint32_t mask = (uint32_t)long_.size() - 1;
+        for (const Long& t : old) {
+            if (!t.id) continue;
+            uint32_t at = t.hash & mask;
+            while (long_[at].id) at = (at + 1) & mask;
+            long_[at] = t;
+        }
+    }
+    uint64_t h = n;
+    uint32_t k = 0;
+    for (; k + 1 < n; k += 2) { h = (h ^ ((uint64_t)w[k] << 32 | w[k + 1])) * 0x9FB21C651E98DF25ull; h ^= h >> 32; }
+    if (k < n) { h = (h ^ w[k]) * 0x9FB21C651E98DF25ull; h ^= h >> 32; }
+    const uint32_t h32 = (uint32_t)h, mask = (uint32_t)long_.size() - 1;
+    for (uint32_t at = h32 & mask;; at = (at + 1) & mask) {
+        Long& t = long_[at];
+        if (!t.id) {
+            t = {++count_, h32, (uint32_t)words_.size(), n};
+            ++n_long_;
+            words_.insert(words_.end(), w, w + n);
+            return t.id;
+        }
+        if (t.hash == h32 && t.n == n && std::equal(w, w + n, words_.data() + t.at)) return t.id;
     }
 }
 
@@ -1303,14 +1319,11 @@ namespace {
 constexpr uint32_t kNodeState = 1u << 28, kNodeSite = 2u << 28, kNodeFollow = 3u << 28, kNodeFinal = 1u << 27, kNodeTooLong = 0xFFFFFFFFu;
 }
 
-RuleAnalysis analyse_rule(const Grammar& g, int32_t rule, int32_t budget, const std::vector<uint64_t>& identity, NodeTable& nodes) {
+RuleAnalysis analyse_rule(const Grammar& g, int32_t rule, int32_t budget, const std::vector<uint64_t>& identity) {
     const RuleFsm& f = g.rules[(size_t)rule];
     const int n = f.n_states();
     RuleAnalysis A;
     A.n = n;
-    A.level.assign((size_t)(budget + 1) * (size_t)n, 0);
-    std::vector<int> by_canon((size_t)n);
-    for (int x = 0; x < n; ++x) by_canon[(size_t)f.canon_id[(size_t)x]] = x;
     // order in which a level is worked out: a state after the states its references to empty-deriving rules lead to
     // (those stay on the same level); states that never get their turn are on or before a cycle of such references
     std::vector<int> order;                                       // canonical numbers
@@ -1328,84 +1341,14 @@ RuleAnalysis analyse_rule(const Grammar& g, int32_t rule, int32_t budget, const 
         std::vector<std::vector<int>> preds((size_t)n);
         for (int x = 0; x < n; ++x)
             for (auto& e : f.refs(x)) if (g.rules[(size_t)e.rule].nullable) { ++left[(size_t)x]; preds[(size_t)e.tgt].push_back(x); }
-        for (int c = 0; c < n; ++c) if (!left[(size_t)by_canon[(size_t)c]]) order.push_back(c);
+        for (int c = 0; c < n; ++c) if (!left[(size_t)f.by_canon[(size_t)c]]) order.push_back(c);
         for (size_t k = 0; k < order.size(); ++k)
-            for (int p : preds[(size_t)by_canon[(size_t)order[k]]]) if (--left[(size_t)p] == 0) order.push_back(f.canon_id[(size_t)p]);
+            for (int p : preds[(size_t)f.by_canon[(size_t)order[k]]]) if (--left[(size_t)p] == 0) order.push_back(f.canon_id[(size_t)p]);
     }
-    std::vector<uint8_t> in_order((size_t)n, 0);
-    for (int c : order) in_order[(size_t)c] = 1;
-    const bool acyclic = (int)order.size() == n;
-
-    // per level, the classes numbered from 0 (a table over node numbers, stamped level by level, finds a node's class)
-    std::vector<int32_t> local((size_t)(budget + 1) * (size_t)n, 0);
-    struct Seen { uint64_t stamp; int32_t cls; };
-    static thread_local std::vector<Seen> seen;
-    static thread_local uint64_t stamp = 0;
-    std::vector<uint32_t> desc;
-    std::vector<std::pair<uint32_t, uint32_t>> refs;
-    std::vector<uint32_t> of_class;                               // once the partition has settled: number of each class on this level
-    int32_t unchanged = 0, last_count = 1;
-    for (int32_t d = 1; d <= budget; ++d) {
-        const uint32_t* prev = A.level.data() + (size_t)(d - 1) * (size_t)n;
-        uint32_t* cur = A.level.data() + (size_t)d * (size_t)n;
-        const int32_t* prev_local = local.data() + (size_t)(d - 1) * (size_t)n;
-        // Levels only refine.  Level d is a function of level d - 1 and of the levels d - m for the shortest sentences m of
-        // the referenced rules, so once the partition has not changed over max m (at least one) levels in a row it never
-        // changes again, and one state of a class speaks for all.
-        const bool settled = acyclic && unchanged >= settle;
-        if (settled) of_class.assign((size_t)last_count, 0);
-        for (int c : order) {
-            if (settled && of_class[(size_t)prev_local[c]]) { cur[c] = of_class[(size_t)prev_local[c]]; continue; }
-            const int x = by_canon[(size_t)c];
-            desc.assign(1, 0u);
-            uint32_t runs = 0;
-            {   // maximal runs of consecutive bytes with the same behaviour (edges are sorted and disjoint)
-                int run_lo = -1, run_hi = -1; uint32_t run_node = 0;
-                auto flush = [&] { if (run_lo >= 0) { desc.push_back((uint32_t)run_lo | ((uint32_t)run_hi << 8)); desc.push_back(run_node); ++runs; } };
-                for (auto& e : f.bedges(x)) {
-                    const uint32_t u = prev[f.canon_id[(size_t)e.tgt]];
-                    if (run_lo >= 0 && (int)e.lo == run_hi + 1 && u == run_node) { run_hi = e.hi; continue; }
-                    flush();
-                    run_lo = e.lo; run_hi = e.hi; run_node = u;
-                }
-                flush();
-            }
-            if (!f.refs(x).empty()) {
-                refs.clear();
-                for (auto& e : f.refs(x)) {
-                    const RuleFsm& c2 = g.rules[(size_t)e.rule];
-                    const int32_t left = c2.nullable ? d : d - c2.min_len;
-                    refs.emplace_back((uint32_t)identity[(size_t)e.rule], left >= 0 ? A.level[(size_t)left * (size_t)n + (size_t)f.canon_id[(size_t)e.tgt]] : kNodeTooLong);
-                }
-                if (refs.size() > 1) std::sort(refs.begin(), refs.end());
-                for (auto& p : refs) { desc.push_back(p.first); desc.push_back(p.second); }
-            }
-            desc[0] = kNodeState | (f.is_final(x) ? kNodeFinal : 0u) | runs;
-            cur[c] = nodes.intern(desc.data(), (uint32_t)desc.size());
-            if (settled) of_class[(size_t)prev_local[c]] = cur[c];
-        }
-        if (!acyclic) for (int c = 0; c < n; ++c) if (!in_order[(size_t)c]) cur[c] = nodes.fresh();
-        int32_t* cur_local = local.data() + (size_t)d * (size_t)n;
-        if (settled) { std::copy(prev_local, prev_local + n, cur_local); continue; }
-        if (seen.size() < nodes.size() + 1) seen.resize(std::max<size_t>(nodes.size() + 1, seen.size() * 2), Seen{0, 0});
-        ++stamp;
-        int32_t count = 0;
-        for (int c = 0; c < n; ++c) {
-            Seen& s = seen[cur[c]];
-            if (s.stamp != stamp) s = {stamp, count++};
-            cur_local[c] = s.cls;
-        }
-        unchanged = count == last_count ? unchanged + 1 : 0;
-        last_count = count;
-    }
-    std::vector<int32_t> ident((size_t)n);
-    if (acyclic) {
-        // classes and near-classes from the levels, in canonical numbers
-        std::vector<uint8_t> scans((size_t)n);
-        for (int c = 0; c < n; ++c) { ident[(size_t)c] = c; scans[(size_t)c] = !f.bedges(by_canon[(size_t)c]).empty(); }
-        class_representatives(local.data(), n, budget, ident.data(), scans, A.rep, &A.near);
-    } else {
-        // the numbers of the states on a cycle say nothing about their classes: those come from the partition itself
+    A.acyclic = (int)order.size() == n;
+    if (!A.acyclic) {
+        A.on_cycle.assign((size_t)n, 1);
+        for (int c : order) A.on_cycle[(size_t)c] = 0;
         NearClasses near;
         const std::vector<int32_t> rep = bounded_classes_rule(g, rule, budget, identity, &near);
         A.rep.resize((size_t)n); A.near.base.resize((size_t)n); A.near.depth.resize((size_t)n);
@@ -1415,13 +1358,89 @@ RuleAnalysis analyse_rule(const Grammar& g, int32_t rule, int32_t budget, const 
             A.near.base[c] = near.base[(size_t)x] < 0 ? -1 : f.canon_id[(size_t)near.base[(size_t)x]];
             A.near.depth[c] = near.depth[(size_t)x];
         }
+        return A;
     }
+    A.level.assign((size_t)(budget + 1) * (size_t)n, 0);
+    // Levels only refine, so a state that is alone in its class stays alone: it needs no further comparing, which leaves
+    // little to do after the first few levels.  The others are grouped by their signatures through a small table whose
+    // hits are confirmed word by word.
+    std::vector<uint32_t> words, begin((size_t)n + 1);            // signatures of this level, and where each state's starts
+    std::vector<std::pair<uint32_t, uint32_t>> refs;
+    struct Slot { uint32_t stamp, hash; int32_t state; uint32_t len; };
+    size_t cap = 16;
+    while (cap < (size_t)n * 2) cap <<= 1;
+    std::vector<Slot> slot(cap, Slot{0, 0, 0, 0});
+    std::vector<int32_t> members(1, n), next_members;             // states per class
+    int32_t unchanged = 0;
+    for (int32_t d = 1; d <= budget; ++d) {
+        const int32_t* prev = A.level.data() + (size_t)(d - 1) * (size_t)n;
+        int32_t* cur = A.level.data() + (size_t)d * (size_t)n;
+        // Level d is a function of level d - 1 and of the levels d - m for the shortest sentences m of the referenced rules,
+        // so once the partition has not changed over max m (at least one) levels in a row it never changes again.
+        if (unchanged >= settle) { std::copy(prev, prev + n, cur); continue; }
+        words.clear();
+        next_members.clear();
+        for (int c : order) {
+            if (members[(size_t)prev[c]] == 1) { cur[c] = (int32_t)next_members.size(); next_members.push_back(1); continue; }
+            const int x = f.by_canon[(size_t)c];
+            const uint32_t w0 = (uint32_t)words.size();
+            words.push_back(0);
+            uint32_t runs = 0;
+            {   // maximal runs of consecutive bytes that lead to the same class (edges are sorted and disjoint)
+                int run_lo = -1, run_hi = -1; int32_t run_cls = 0;
+                auto flush = [&] { words.push_back((uint32_t)run_lo | ((uint32_t)run_hi << 8)); words.push_back((uint32_t)run_cls); ++runs; };
+                for (auto& e : f.bedges(x)) {
+                    const int32_t u = prev[f.canon_id[(size_t)e.tgt]];
+                    if (run_lo >= 0 && (int)e.lo == run_hi + 1 && u == run_cls) { run_hi = e.hi; continue; }
+                    if (run_lo >= 0) flush();
+                    run_lo = e.lo; run_hi = e.hi; run_cls = u;
+                }
+                if (run_lo >= 0) flush();
+            }
+            if (!f.refs(x).empty()) {
+                refs.clear();
+                for (auto& e : f.refs(x)) {
+                    const RuleFsm& r = g.rules[(size_t)e.rule];
+                    const int32_t left = r.nullable ? d : d - r.min_len;
+                    refs.emplace_back((uint32_t)identity[(size_t)e.rule], left >= 0 ? (uint32_t)A.level[(size_t)left * (size_t)n + (size_t)f.canon_id[(size_t)e.tgt]] : kNodeTooLong);
+                }
+                if (refs.size() > 1) std::sort(refs.begin(), refs.end());
+                for (auto& p : refs) { words.push_back(p.first); words.push_back(p.second); }
+            }
+            words[w0] = (f.is_final(x) ? kNodeFinal : 0u) | runs;
+            const uint32_t len = (uint32_t)words.size() - w0;
+            begin[(size_t)c] = w0;
+            uint64_t h = len;
+            for (uint32_t k = 0; k < len; ++k) { h = (h ^ words[w0 + k]) * 0x9FB21C651E98DF25ull; h ^= h >> 32; }
+            for (size_t at = (size_t)h & (cap - 1);; at = (at + 1) & (cap - 1)) {
+                Slot& s = slot[at];
+                if (s.stamp != (uint32_t)d) {
+                    s = {(uint32_t)d, (uint32_t)h, c, len};
+                    cur[c] = (int32_t)next_members.size();
+                    next_members.push_back(1);
+                    break;
+                }
+                if (s.hash == (uint32_t)h && s.len == len && std::equal(words.begin() + w0, words.end(), words.begin() + begin[(size_t)s.state])) {
+                    cur[c] = cur[s.state];
+                    ++next_members[(size_t)cur[c]];
+                    break;
+                }
+            }
+        }
+        unchanged = next_members.size() == members.size() ? unchanged + 1 : 0;
+        members.swap(next_members);
+    }
+    // classes and near-classes from the levels, in canonical numbers
+    std::vector<int32_t> ident((size_t)n);
+    std::vector<uint8_t> scans((size_t)n);
+    for (int c = 0; c < n; ++c) { ident[(size_t)c] = c; scans[(size_t)c] = !f.bedges(f.by_canon[(size_t)c]).empty(); }
+    class_representatives(A.level.data(), n, budget, ident.data(), scans, A.rep, &A.near);
     return A;
 }
 
 FollowSigs::FollowSigs(const Grammar& g, int32_t budget, const std::vector<std::shared_ptr<const RuleAnalysis>>& analysis,
-                       const std::vector<std::vector<int32_t>>& rep, NodeTable& nodes)
-    : g_(g), budget_(budget), analysis_(analysis), nodes_(nodes), memo_(g.rules.size() * ((size_t)budget + 1), 0) {
+                       const std::vector<std::vector<int32_t>>& rep, const std::vector<uint64_t>& identity, NodeTable& nodes)
+    : g_(g), budget_(budget), analysis_(analysis), identity_(identity), nodes_(nodes), memo_(g.rules.size() * ((size_t)budget + 1), 0) {
     // sites of every rule: one per class of the states referencing rules continue in
     const size_t R = g.rules.size();
     std::vector<std::vector<Site>> sites(R);
@@ -1439,6 +1458,49 @@ FollowSigs::FollowSigs(const Grammar& g, int32_t budget, const std::vector<std::
     }
 }
 
+uint32_t FollowSigs::behaviour(int rule, int c, int d) {
+    if (d <= 0) return 0;
+    const RuleAnalysis& A = *analysis_[(size_t)rule];
+    const size_t n = (size_t)A.n;
+    if (A.number.empty()) A.number.assign((size_t)(budget_ + 1) * n, 0);
+    const size_t at = (size_t)d * n + (size_t)(A.acyclic ? A.level[(size_t)d * n + (size_t)c] : c);
+    if (A.number[at]) return A.number[at];
+    if (!A.acyclic && A.on_cycle[(size_t)c]) return A.number[at] = nodes_.fresh();
+    const RuleFsm& f = g_.rules[(size_t)rule];
+    const int x = f.by_canon[(size_t)c];
+    const Span<ByteRange> edges = f.bedges(x);
+    if (edges.size() == 1 && f.refs(x).empty()) {                   // most states are a step of a literal
+        const uint32_t next = behaviour(rule, f.canon_id[(size_t)edges[0].tgt], d - 1);
+        return A.number[at] = nodes_.intern3(kNodeState | (f.is_final(x) ? kNodeFinal : 0u) | 1u, (uint32_t)edges[0].lo | ((uint32_t)edges[0].hi << 8), next);
+    }
+    std::vector<uint32_t> desc(1, 0u);
+    desc.reserve(1 + 2 * edges.size() + 2 * f.refs(x).size());
+    uint32_t runs = 0;
+    {   // maximal runs of consecutive bytes with the same behaviour (edges are sorted and disjoint)
+        int run_lo = -1, run_hi = -1; uint32_t run_node = 0;
+        auto flush = [&] { desc.push_back((uint32_t)run_lo | ((uint32_t)run_hi << 8)); desc.push_back(run_node); ++runs; };
+        for (auto& e : edges) {
+            const uint32_t u = behaviour(rule, f.canon_id[(size_t)e.tgt], d - 1);
+            if (run_lo >= 0 && (int)e.lo == run_hi + 1 && u == run_node) { run_hi = e.hi; continue; }
+            if (run_lo >= 0) flush();
+            run_lo = e.lo; run_hi = e.hi; run_node = u;
+        }
+        if (run_lo >= 0) flush();
+    }
+    if (!f.refs(x).empty()) {
+        std::vector<std::pair<uint32_t, uint32_t>> refs;
+        for (auto& e : f.refs(x)) {
+            const RuleFsm& r = g_.rules[(size_t)e.rule];
+            const int32_t left = r.nullable ? d : d - r.min_len;
+            refs.emplace_back((uint32_t)identity_[(size_t)e.rule], left >= 0 ? behaviour(rule, f.canon_id[(size_t)e.tgt], left) : kNodeTooLong);
+        }
+        if (refs.size() > 1) std::sort(refs.begin(), refs.end());
+        for (auto& p : refs) { desc.push_back(p.first); desc.push_back(p.second); }
+    }
+    desc[0] = kNodeState | (f.is_final(x) ? kNodeFinal : 0u) | runs;
+    return A.number[at] = nodes_.intern(desc.data(), (uint32_t)desc.size());
+}
+
 uint32_t FollowSigs::sig(int rule, int d) {
     const size_t key = (size_t)rule * ((size_t)budget_ + 1) + (size_t)d;
     if (memo_[key] == kPending) return nodes_.fresh();              // cycle through rule ends
@@ -1447,8 +1509,7 @@ uint32_t FollowSigs::sig(int rule, int d) {
     std::vector<uint32_t> parts(1, kNodeFollow | (rule == g_.root ? 1u : 0u));      // the root: the input may end here
     for (const Site& st : sites_[(size_t)rule]) {
         const RuleFsm& f = g_.rules[(size_t)st.q];
-        const RuleAnalysis& A = *analysis_[(size_t)st.q];
-        uint32_t h = A.level[(size_t)d * (size_t)A.n + (size_t)f.canon_id[(size_t)st.x]];
+        uint32_t h = behaviour(st.q, f.canon_id[(size_t)st.x], d);
         const int32_t left = d - f.min_suf[(size_t)st.x];
         if (left > 0) {
             const uint32_t pair[3] = {kNodeSite, h, sig(st.q, left)};

@@ -57,7 +57,7 @@ struct RuleFsm {
     // structural hash (Algorithm 1, refined by Algorithm 2 inside simple reference cycles)
     uint64_t hash = 0;
     bool shareable = true;                            // false: member of a non-simple cycle, never reused
-    std::vector<int32_t> canon_id;                    // Algorithm 1 phase 1: state -> canonical id
+    std::vector<int32_t> canon_id, by_canon;          // Algorithm 1 phase 1: state -> canonical id, and back
     Rows<RefEdge> redges_by_hash;                     // out-references in the order Algorithm 1 sorted them
     std::vector<int32_t> ring;                        // simple cycle through this rule, starting at it (else empty)
     int32_t n_states() const { return (int32_t)body->is_final.size(); }
@@ -106,37 +106,52 @@ std::vector<int32_t> bounded_classes_rule(const Grammar& g, int32_t rule, int32_
                                           NearClasses* near = nullptr);
 
 // Exact numbering of descriptions: a list of words gets the number it got before, a list not met yet the next one (from 1).
-// The lists lie back to back in one array, found through an open-addressing table.
+// Nearly all lists have three words (a state with one byte run): those lie in the open-addressing table itself, so that a
+// look-up is one cache line; longer ones lie back to back in one array behind a table of their own.
 class NodeTable {
   public:
-    uint32_t intern(const uint32_t* w, uint32_t n);
-    uint32_t fresh() { end_.push_back((uint32_t)words_.size()); hash_.push_back(0); return (uint32_t)end_.size(); }   // a number no list ever gets
-    uint32_t size() const { return (uint32_t)end_.size(); }
+    uint32_t intern3(uint32_t a, uint32_t b, uint32_t c);
+    uint32_t intern(const uint32_t* w, uint32_t n) { return n == 3 ? intern3(w[0], w[1], w[2]) : intern_long(w, n); }
+    uint32_t fresh() { return ++count_; }               // a number no list ever gets
+    uint32_t size() const { return count_; }
 
   private:
-    std::vector<uint32_t> words_, end_, hash_, slot_;   // node k - 1: words [end_[k - 2], end_[k - 1]); slot: node number or 0
-    uint32_t used_ = 0;
-    void grow();
+    struct Three { uint32_t id, a, b, c; };             // id 0: empty slot
+    struct Long { uint32_t id, hash, at, n; };          // words_[at .. at + n)
+    std::vector<Three> three_;
+    std::vector<Long> long_;
+    std::vector<uint32_t> words_;
+    uint32_t count_ = 0, n_three_ = 0, n_long_ = 0;
+    uint32_t intern_long(const uint32_t* w, uint32_t n);
+    static uint32_t mix3(uint32_t a, uint32_t b, uint32_t c) {
+        uint64_t h = (((uint64_t)a << 32 | b) ^ ((uint64_t)c * 0x9E3779B97F4A7C15ull)) * 0x9FB21C651E98DF25ull;
+        return (uint32_t)(h ^ (h >> 32));
+    }
 };
 
-// What one rule's states do on strings of at most d bytes, for every d up to the longest token.  level[d * n + c] is the
-// number (in the node table) of canonical state c's behaviour on at most d bytes: whether it is final, the byte runs with
-// the behaviours they lead to on d - 1 bytes, and the references, by identity, with what follows their shortest sentence.
-// Equal numbers, equal behaviour, across rules and grammars that share the table; states of one rule with equal numbers
-// at the budget are the classes of bounded_classes_rule (rep, near: by canonical state number too).  States on or before
-// a cycle of references to rules that derive the empty string get numbers of their own (never shared, always sound).
+// What one rule's states do on strings of at most d bytes, for every d up to the longest token, by canonical state number.
+// level[d * n + c] is the class of state c among the rule's states: states of one class agree on whether they are final, on
+// the byte runs with the classes they lead to on d - 1 bytes, and on the references, by identity, with what follows their
+// shortest sentence.  rep and near are what bounded_classes_rule says.
 struct RuleAnalysis {
     int32_t n = 0;
-    std::vector<uint32_t> level;
+    bool acyclic = true;                               // no cycle of references to rules that derive the empty string
+    std::vector<int32_t> level;
     std::vector<int32_t> rep;
     NearClasses near;
+    // numbers of behaviours in the node table, worked out on demand (FollowSigs): [d * n + class] (by state instead of class
+    // if not acyclic), 0 = not known yet.  Belongs to the pool whose table the numbers are from.
+    mutable std::vector<uint32_t> number;
+    std::vector<uint8_t> on_cycle;                     // [canonical state], if not acyclic: on or before such a cycle
 };
 // identity[r]: a number that identical rules share and different ones do not, for every rule that `rule` references
-RuleAnalysis analyse_rule(const Grammar& g, int32_t rule, int32_t budget, const std::vector<uint64_t>& identity, NodeTable& nodes);
+RuleAnalysis analyse_rule(const Grammar& g, int32_t rule, int32_t budget, const std::vector<uint64_t>& identity);
 
 // What can follow an instance of a rule within d bytes in this grammar, as a number of the node table: the set of states
-// referencing rules continue in (their behaviour on the bytes that are left), recursively through rules that can end
-// within the budget, and whether the input may end (root rule).  Two rules with equal numbers reject the same uncertain
+// referencing rules continue in (the number of their behaviour on the bytes that are left: equal numbers, equal behaviour,
+// across rules and grammars that share the table), recursively through rules that can end within the budget, and whether
+// the input may end (root rule).  States on or before a cycle of references to rules that derive the empty string get
+// numbers of their own (never shared, always sound).  Two rules with equal numbers reject the same uncertain
 // tokens by context expansion (section 2.2), so filtered planes can be shared across grammars (section 3.3: reuse needs
 // matching lookahead).  A rule on a reference cycle through rule ends gets a number of its own.  Computed on demand.
 class FollowSigs {
@@ -144,7 +159,7 @@ class FollowSigs {
     // analysis[r] and rep[r] (by state number) of every rule; sites are taken at representatives, which leaves the follow
     // language as it is and the work independent of repetition bounds
     FollowSigs(const Grammar& g, int32_t budget, const std::vector<std::shared_ptr<const RuleAnalysis>>& analysis,
-               const std::vector<std::vector<int32_t>>& rep, NodeTable& nodes);
+               const std::vector<std::vector<int32_t>>& rep, const std::vector<uint64_t>& identity, NodeTable& nodes);
     uint32_t sig(int rule, int d);
 
   private:
@@ -152,7 +167,9 @@ class FollowSigs {
     const Grammar& g_;
     int32_t budget_;
     const std::vector<std::shared_ptr<const RuleAnalysis>>& analysis_;
+    const std::vector<uint64_t>& identity_;
     NodeTable& nodes_;
+    uint32_t behaviour(int rule, int c, int d);         // number of canonical state c's behaviour on at most d bytes
     Rows<Site> sites_;
     std::vector<uint32_t> memo_;                        // [rule * (budget + 1) + d]: 0 not known, kPending being computed
     static constexpr uint32_t kPending = 0xFFFFFFFFu;
