@@ -1101,15 +1101,19 @@ Grammar lower_grammar(const std::string& ebnf, const std::string& root_rule) {
 }
 
 namespace {
-// From the classes of every level (level[d * n + x], numbered below n): per state the member of its class at the budget
-// with the smallest canonical id, and (optional) the near-classes.  scans[x]: the state has byte edges.
-void class_representatives(const int32_t* level, int n, int32_t budget, const int32_t* canon_id, const std::vector<uint8_t>& scans,
+constexpr uint32_t kNodeState = 1u << 28, kNodeSite = 2u << 28, kNodeFollow = 3u << 28, kNodeFinal = 1u << 27, kNodeTooLong = 0xFFFFFFFFu;
+}
+
+namespace {
+// From the classes of every level (level[d * n + x], numbered below n, states by canonical number): per state the member of
+// its class at the budget with the smallest number, and (optional) the near-classes.  scans[x]: the state has byte edges.
+void class_representatives(const int32_t* level, int n, int32_t budget, const std::vector<uint8_t>& scans,
                            std::vector<int32_t>& rep_r, NearClasses* near) {
     const int32_t* fin = level + (size_t)budget * (size_t)n;
     std::vector<int32_t> best((size_t)n, -1);                    // class -> member with the smallest canonical id
     for (int x = 0; x < n; ++x) {
         int32_t& b = best[(size_t)fin[x]];
-        if (b < 0 || canon_id[x] < canon_id[b]) b = x;
+        if (b < 0) b = x;
     }
     rep_r.resize((size_t)n);
     for (int x = 0; x < n; ++x) rep_r[(size_t)x] = best[(size_t)fin[x]];
@@ -1120,15 +1124,15 @@ void class_representatives(const int32_t* level, int n, int32_t budget, const in
     near->depth.assign((size_t)n, 0);
     std::vector<int32_t> weight((size_t)n, 0);                                    // by class number (< n)
     for (int x = 0; x < n; ++x) ++weight[(size_t)fin[x]];
-    std::vector<std::array<int32_t, 3>> keyed;                                   // {-size, canonical id, state}
-    for (int c = 0; c < n; ++c) if (best[(size_t)c] >= 0) keyed.push_back({-weight[(size_t)c], canon_id[best[(size_t)c]], best[(size_t)c]});
+    std::vector<std::array<int32_t, 2>> keyed;                                   // {-size, state}
+    for (int c = 0; c < n; ++c) if (best[(size_t)c] >= 0) keyed.push_back({-weight[(size_t)c], best[(size_t)c]});
     std::sort(keyed.begin(), keyed.end());
     const int32_t top = std::min<int32_t>(budget - 1, kMaxNearDepth);
     if (top < kMinNearDepth) return;
     // per level: class -> a class built in full (-1: none yet)
     std::vector<int32_t> full((size_t)(top + 1) * (size_t)n, -1);
     for (auto& k : keyed) {
-        const int32_t x = k[2];
+        const int32_t x = k[1];
         if (!scans[(size_t)x]) continue;                                         // no plane
         int32_t d = top;
         for (; d >= kMinNearDepth; --d) {
@@ -1144,126 +1148,158 @@ void class_representatives(const int32_t* level, int n, int32_t budget, const in
 }
 }  // namespace
 
-std::vector<int32_t> bounded_classes_rule(const Grammar& g, int32_t rule, int32_t budget, const std::vector<uint64_t>& ref_identity,
-                                          NearClasses* near) {
-    std::vector<int32_t> rep_r;
+namespace {
+// level[d * n + c]: class of canonical state c among the rule's states on at most d bytes, d = 0 .. budget.  Classes keep
+// their number from level to level: a class that splits leaves it to its largest part (or to the members that were not
+// looked at), the other parts get new numbers.  So a state has to be looked at again only when the number of a state it
+// leads to has changed -- a byte later for a byte edge, its shortest sentence later for a reference, in the same level for
+// a reference to a rule that derives the empty string -- and members of its class without such a change cannot be like it
+// any more, since a new number is one nothing had before.  In a long repetition only the states near the bound ever split
+// off, so the work does not grow with the bound times the levels.
+void bounded_levels(const Grammar& g, const RuleFsm& f, int32_t budget, const std::vector<uint64_t>& identity, std::vector<int32_t>& level) {
+    const size_t n = (size_t)f.n_states();
+    level.assign((size_t)(budget + 1) * n, 0);
+    // who has to be looked at when a state's number changes: {state, how many levels later}
+    struct Pred { int32_t state, later; };
+    std::vector<uint32_t> off(n + 1, 0);
+    std::vector<Pred> preds;
+    std::vector<std::vector<int32_t>> due((size_t)budget + 1);      // per level, states to look at
+    for (size_t c = 0; c < n; ++c) due[1].push_back((int32_t)c);
     {
-        const size_t r = (size_t)rule;
-        const RuleFsm& f = g.rules[r];
-        const int n = f.n_states();
-        // level[d][x] = class of x with d bytes left; level 0 tells nothing apart.  Signatures of one level lie back to
-        // back in one buffer; states are grouped through a hash table whose hits are confirmed by comparing the
-        // signatures themselves, and classes are numbered in the order of their first state.
-        std::vector<std::vector<int32_t>> level(1, std::vector<int32_t>((size_t)n, 0));
-        bool any_nullable_edge = false;
-        for (int x = 0; x < n && !any_nullable_edge; ++x)
-            for (auto& e : f.refs(x)) if (g.rules[(size_t)e.rule].nullable) { any_nullable_edge = true; break; }
-        std::vector<int64_t> base, full;
-        std::vector<size_t> base_off((size_t)n + 1), full_off((size_t)n + 1);
-        std::vector<std::pair<int64_t, int64_t>> refs;
-        std::vector<int32_t> slot_state;                            // open addressing: slot -> first state of the class, or -1
-        auto group = [&](const std::vector<int64_t>& buf, const std::vector<size_t>& off, std::vector<int32_t>& out) -> size_t {
-            size_t cap = 16;
-            while (cap < (size_t)n * 2) cap <<= 1;
-            slot_state.assign(cap, -1);
-            size_t n_classes = 0;
-            for (int x = 0; x < n; ++x) {
-                const int64_t* sx = buf.data() + off[(size_t)x];
-                const size_t lx = off[(size_t)x + 1] - off[(size_t)x];
-                uint64_t h = 0x9E3779B97F4A7C15ull ^ lx;
-                for (size_t k = 0; k < lx; ++k) { h ^= (uint64_t)sx[k]; h *= 0xFF51AFD7ED558CCDull; h ^= h >> 32; }
-                for (size_t at = (size_t)h & (cap - 1);; at = (at + 1) & (cap - 1)) {
-                    const int32_t y = slot_state[at];
-                    if (y < 0) { slot_state[at] = x; out[(size_t)x] = (int32_t)n_classes++; break; }
-                    const size_t ly = off[(size_t)y + 1] - off[(size_t)y];
-                    if (ly == lx && std::equal(sx, sx + lx, buf.data() + off[(size_t)y])) { out[(size_t)x] = out[(size_t)y]; break; }
+        auto each = [&](auto&& use) {
+            for (size_t x = 0; x < n; ++x) {
+                int last = -1;
+                for (auto& e : f.bedges((int)x)) { if (e.tgt != last) use(x, e.tgt, 1); last = e.tgt; }
+                for (auto& e : f.refs((int)x)) {
+                    const RuleFsm& r = g.rules[(size_t)e.rule];
+                    if (r.nullable) use(x, e.tgt, 0);
+                    else if (r.min_len <= budget) use(x, e.tgt, r.min_len);
                 }
             }
-            return n_classes;
         };
-        // Levels only refine.  Level d is a function of level d - 1 and of the levels d - m for the shortest sentences m
-        // of the referenced rules, so once the partition has not changed over max m (at least one) levels in a row it
-        // never changes again.
-        int32_t settle = 1;
-        for (int x = 0; x < n; ++x)
-            for (auto& e : f.refs(x)) {
-                const RuleFsm& c = g.rules[(size_t)e.rule];
-                if (!c.nullable && c.min_len <= budget) settle = std::max(settle, c.min_len);
+        each([&](size_t, int t, int) { ++off[(size_t)f.canon_id[(size_t)t] + 1]; });
+        for (size_t c = 0; c < n; ++c) off[c + 1] += off[c];
+        preds.resize(off[n]);
+        std::vector<uint32_t> at(off.begin(), off.end() - 1);
+        each([&](size_t x, int t, int later) { preds[at[(size_t)f.canon_id[(size_t)t]]++] = {f.canon_id[x], later}; });
+        // a reference counts from the level of its shortest sentence on
+        for (size_t x = 0; x < n; ++x)
+            for (auto& e : f.refs((int)x)) {
+                const RuleFsm& r = g.rules[(size_t)e.rule];
+                if (!r.nullable && r.min_len <= budget && r.min_len > 1) due[(size_t)r.min_len].push_back(f.canon_id[x]);
             }
-        size_t last_count = 1;
-        int32_t unchanged = 0;
-        for (int32_t d = 1; d <= budget; ++d) {
-            if (unchanged >= settle) { level.push_back(level.back()); continue; }
-            const std::vector<int32_t>& prev = level.back();
-            // part of the signature that does not depend on the level being computed
-            base.clear();
-            for (int x = 0; x < n; ++x) {
-                base_off[(size_t)x] = base.size();
-                base.push_back(prev[(size_t)x]);
-                base.push_back(f.is_final(x));
-                // maximal runs of consecutive bytes that lead to the same class (edges are sorted and disjoint)
-                {
-                    int run_lo = -1, run_hi = -1; int32_t run_cls = -1;
-                    for (auto& e : f.bedges(x)) {
-                        const int32_t c = prev[(size_t)e.tgt];
-                        if (run_lo >= 0 && (int)e.lo == run_hi + 1 && c == run_cls) { run_hi = e.hi; continue; }
-                        if (run_lo >= 0) { base.push_back(run_lo); base.push_back(run_hi); base.push_back(run_cls); }
-                        run_lo = e.lo; run_hi = e.hi; run_cls = c;
-                    }
-                    if (run_lo >= 0) { base.push_back(run_lo); base.push_back(run_hi); base.push_back(run_cls); }
-                }
-                base.push_back(-7);
-                refs.clear();
-                for (auto& e : f.refs(x)) {
-                    const RuleFsm& c = g.rules[(size_t)e.rule];
-                    if (c.nullable) continue;
-                    int32_t left = d - c.min_len;
-                    refs.emplace_back((int64_t)ref_identity[(size_t)e.rule], left >= 0 ? level[(size_t)left][(size_t)e.tgt] : -1);
-                }
-                if (refs.size() > 1) std::sort(refs.begin(), refs.end());
-                for (auto& p : refs) { base.push_back(p.first); base.push_back(p.second); }
-            }
-            base_off[(size_t)n] = base.size();
-            std::vector<int32_t> cur((size_t)n, 0);
-            size_t count = 0;
-            if (!any_nullable_edge) {
-                count = group(base, base_off, cur);
-            } else {
-                // coarsest partition stable under "a nullable rule edge leads to the same class of this level"; it refines
-                // the previous level, so the iteration may start there
-                cur = prev;
-                std::vector<int32_t> nxt((size_t)n);
-                for (size_t n_classes = 0;;) {
-                    full.clear();
-                    for (int x = 0; x < n; ++x) {
-                        full_off[(size_t)x] = full.size();
-                        full.insert(full.end(), base.begin() + (long)base_off[(size_t)x], base.begin() + (long)base_off[(size_t)x + 1]);
-                        full.push_back(-9);
-                        refs.clear();
-                        for (auto& e : f.refs(x))
-                            if (g.rules[(size_t)e.rule].nullable) refs.emplace_back((int64_t)ref_identity[(size_t)e.rule], cur[(size_t)e.tgt]);
-                        if (refs.size() > 1) std::sort(refs.begin(), refs.end());
-                        for (auto& p : refs) { full.push_back(p.first); full.push_back(p.second); }
-                    }
-                    full_off[(size_t)n] = full.size();
-                    const size_t got = group(full, full_off, nxt);
-                    cur.swap(nxt);
-                    count = got;
-                    if (got == n_classes) break;
-                    n_classes = got;
-                }
-            }
-            unchanged = count == last_count ? unchanged + 1 : 0;
-            last_count = count;
-            level.push_back(cur);
-        }
-        std::vector<int32_t> flat;                                    // [d * n + x]
-        for (auto& l : level) flat.insert(flat.end(), l.begin(), l.end());
-        std::vector<uint8_t> scans((size_t)n);
-        for (int x = 0; x < n; ++x) scans[(size_t)x] = !f.bedges(x).empty();
-        class_representatives(flat.data(), n, budget, f.canon_id.data(), scans, rep_r, near);
     }
-    return rep_r;
+    std::vector<int32_t> members(n, 0), looked(n, 0);               // per class: states, and how many of them are being looked at
+    members[0] = (int32_t)n;
+    int32_t n_classes = 1;
+    struct Group { int32_t cls, size, number; };                    // equal signatures in one class
+    std::vector<Group> groups;
+    std::vector<int32_t> group_of(n);
+    std::vector<int32_t> largest(n, -1);                            // per class: its largest group of the round
+    std::vector<uint32_t> words, begin(n + 1), stamp(n, 0);
+    std::vector<std::pair<uint32_t, uint32_t>> refs;
+    struct Slot { uint32_t round, hash, len; int32_t state; };
+    size_t cap = 16;
+    while (cap < n * 2) cap <<= 1;
+    std::vector<Slot> slot(cap, Slot{0, 0, 0, 0});
+    uint32_t round = 0;
+    std::vector<int32_t> now, next;
+    for (int32_t d = 1; d <= budget; ++d) {
+        const int32_t* prev = level.data() + (size_t)(d - 1) * n;
+        int32_t* cur = level.data() + (size_t)d * n;
+        std::copy(prev, prev + n, cur);
+        now.swap(due[(size_t)d]);
+        while (!now.empty()) {
+            ++round;
+            words.clear(); groups.clear(); next.clear();
+            size_t m = 0;
+            for (int32_t c : now) if (stamp[(size_t)c] != round) { stamp[(size_t)c] = round; now[m++] = c; ++looked[(size_t)cur[c]]; }
+            now.resize(m);
+            for (int32_t c : now) {
+                const int32_t cls = cur[c];
+                if (members[(size_t)cls] == 1) { group_of[(size_t)c] = -1; continue; }       // alone already
+                const int x = f.by_canon[(size_t)c];
+                const uint32_t w0 = (uint32_t)words.size();
+                words.push_back((uint32_t)cls);
+                words.push_back(f.is_final(x));
+                uint32_t runs = 0;
+                {   // maximal runs of consecutive bytes that lead to the same class (edges are sorted and disjoint)
+                    int run_lo = -1, run_hi = -1; int32_t run_cls = 0;
+                    auto flush = [&] { words.push_back((uint32_t)run_lo | ((uint32_t)run_hi << 8)); words.push_back((uint32_t)run_cls); ++runs; };
+                    for (auto& e : f.bedges(x)) {
+                        const int32_t u = prev[f.canon_id[(size_t)e.tgt]];
+                        if (run_lo >= 0 && (int)e.lo == run_hi + 1 && u == run_cls) { run_hi = e.hi; continue; }
+                        if (run_lo >= 0) flush();
+                        run_lo = e.lo; run_hi = e.hi; run_cls = u;
+                    }
+                    if (run_lo >= 0) flush();
+                }
+                words[w0 + 1] |= runs << 1;
+                if (!f.refs(x).empty()) {
+                    refs.clear();
+                    for (auto& e : f.refs(x)) {
+                        const RuleFsm& r = g.rules[(size_t)e.rule];
+                        const int32_t left = r.nullable ? d : d - r.min_len;
+                        refs.emplace_back((uint32_t)identity[(size_t)e.rule], left >= 0 ? (uint32_t)level[(size_t)left * n + (size_t)f.canon_id[(size_t)e.tgt]] : kNodeTooLong);
+                    }
+                    if (refs.size() > 1) std::sort(refs.begin(), refs.end());
+                    for (auto& p : refs) { words.push_back(p.first); words.push_back(p.second); }
+                }
+                const uint32_t len = (uint32_t)words.size() - w0;
+                begin[(size_t)c] = w0;
+                uint64_t h = len;
+                for (uint32_t k = 0; k < len; ++k) { h = (h ^ words[w0 + k]) * 0x9FB21C651E98DF25ull; h ^= h >> 32; }
+                for (size_t at = (size_t)h & (cap - 1);; at = (at + 1) & (cap - 1)) {
+                    Slot& s = slot[at];
+                    if (s.round != round) { s = {round, (uint32_t)h, len, c}; group_of[(size_t)c] = (int32_t)groups.size(); groups.push_back({cls, 1, -1}); break; }
+                    if (s.hash == (uint32_t)h && s.len == len && std::equal(words.begin() + w0, words.end(), words.begin() + begin[(size_t)s.state])) {
+                        group_of[(size_t)c] = group_of[(size_t)s.state];
+                        ++groups[(size_t)group_of[(size_t)c]].size;
+                        break;
+                    }
+                }
+            }
+            // the number of a class stays with the members that were not looked at, else with its largest group
+            for (size_t k = 0; k < groups.size(); ++k) {
+                int32_t& best = largest[(size_t)groups[k].cls];
+                if (looked[(size_t)groups[k].cls] == members[(size_t)groups[k].cls] && (best < 0 || groups[k].size > groups[(size_t)best].size)) best = (int32_t)k;
+            }
+            for (int32_t c : now) looked[(size_t)cur[c]] = 0;
+            for (size_t k = 0; k < groups.size(); ++k) {
+                Group& G = groups[k];
+                if (largest[(size_t)G.cls] == (int32_t)k) { G.number = G.cls; continue; }
+                G.number = n_classes++;
+                members[(size_t)G.number] = G.size;
+                members[(size_t)G.cls] -= G.size;
+            }
+            for (const Group& G : groups) largest[(size_t)G.cls] = -1;
+            for (int32_t c : now) {
+                if (group_of[(size_t)c] < 0 || groups[(size_t)group_of[(size_t)c]].number == cur[c]) continue;
+                cur[c] = groups[(size_t)group_of[(size_t)c]].number;
+                for (uint32_t k = off[(size_t)c]; k < off[(size_t)c + 1]; ++k) {
+                    const Pred& p = preds[k];
+                    if (p.later == 0) next.push_back(p.state);
+                    else if (d + p.later <= budget) due[(size_t)(d + p.later)].push_back(p.state);
+                }
+            }
+            now.swap(next);
+        }
+    }
+}
+}  // namespace
+
+std::vector<int32_t> bounded_classes_rule(const Grammar& g, int32_t rule, int32_t budget, const std::vector<uint64_t>& ref_identity, NearClasses* near) {
+    const RuleFsm& f = g.rules[(size_t)rule];
+    const RuleAnalysis A = analyse_rule(g, rule, budget, ref_identity);
+    const size_t n = (size_t)f.n_states();
+    std::vector<int32_t> rep(n);
+    if (near) { near->base.resize(n); near->depth.resize(n); }
+    for (size_t x = 0; x < n; ++x) {                                // from canonical numbers to the rule's own
+        const size_t c = (size_t)f.canon_id[x];
+        rep[x] = f.by_canon[(size_t)A.rep[c]];
+        if (near) { near->base[x] = A.near.base[c] < 0 ? -1 : f.by_canon[(size_t)A.near.base[c]]; near->depth[x] = A.near.depth[c]; }
+    }
+    return rep;
 }
 
 uint32_t NodeTable::intern3(uint32_t a, uint32_t b, uint32_t c) {
@@ -1315,126 +1351,31 @@ uint32_t NodeTable::intern_long(const uint32_t* w, uint32_t n) {
     }
 }
 
-namespace {
-constexpr uint32_t kNodeState = 1u << 28, kNodeSite = 2u << 28, kNodeFollow = 3u << 28, kNodeFinal = 1u << 27, kNodeTooLong = 0xFFFFFFFFu;
-}
-
 RuleAnalysis analyse_rule(const Grammar& g, int32_t rule, int32_t budget, const std::vector<uint64_t>& identity) {
     const RuleFsm& f = g.rules[(size_t)rule];
-    const int n = f.n_states();
+    const size_t n = (size_t)f.n_states();
     RuleAnalysis A;
-    A.n = n;
-    // order in which a level is worked out: a state after the states its references to empty-deriving rules lead to
-    // (those stay on the same level); states that never get their turn are on or before a cycle of such references
-    std::vector<int> order;                                       // canonical numbers
-    order.reserve((size_t)n);
+    A.n = (int32_t)n;
     bool any_nullable = false;
-    int32_t settle = 1;
-    for (const RefEdge& e : f.redges.v) {
-        const RuleFsm& c = g.rules[(size_t)e.rule];
-        any_nullable |= c.nullable;
-        if (!c.nullable && c.min_len <= budget) settle = std::max(settle, c.min_len);
-    }
-    if (!any_nullable) for (int c = 0; c < n; ++c) order.push_back(c);
-    else {
-        std::vector<int> left((size_t)n, 0);
-        std::vector<std::vector<int>> preds((size_t)n);
-        for (int x = 0; x < n; ++x)
+    for (const RefEdge& e : f.redges.v) any_nullable |= g.rules[(size_t)e.rule].nullable;
+    if (any_nullable) {
+        // states that references to empty-deriving rules lead from only to states already taken off are off every cycle
+        std::vector<int> left(n, 0), off_cycle;
+        std::vector<std::vector<int>> preds(n);
+        for (int x = 0; x < (int)n; ++x)
             for (auto& e : f.refs(x)) if (g.rules[(size_t)e.rule].nullable) { ++left[(size_t)x]; preds[(size_t)e.tgt].push_back(x); }
-        for (int c = 0; c < n; ++c) if (!left[(size_t)f.by_canon[(size_t)c]]) order.push_back(c);
-        for (size_t k = 0; k < order.size(); ++k)
-            for (int p : preds[(size_t)f.by_canon[(size_t)order[k]]]) if (--left[(size_t)p] == 0) order.push_back(f.canon_id[(size_t)p]);
-    }
-    A.acyclic = (int)order.size() == n;
-    if (!A.acyclic) {
-        A.on_cycle.assign((size_t)n, 1);
-        for (int c : order) A.on_cycle[(size_t)c] = 0;
-        NearClasses near;
-        const std::vector<int32_t> rep = bounded_classes_rule(g, rule, budget, identity, &near);
-        A.rep.resize((size_t)n); A.near.base.resize((size_t)n); A.near.depth.resize((size_t)n);
-        for (int x = 0; x < n; ++x) {
-            const size_t c = (size_t)f.canon_id[(size_t)x];
-            A.rep[c] = f.canon_id[(size_t)rep[(size_t)x]];
-            A.near.base[c] = near.base[(size_t)x] < 0 ? -1 : f.canon_id[(size_t)near.base[(size_t)x]];
-            A.near.depth[c] = near.depth[(size_t)x];
+        for (int x = 0; x < (int)n; ++x) if (!left[(size_t)x]) off_cycle.push_back(x);
+        for (size_t k = 0; k < off_cycle.size(); ++k) for (int p : preds[(size_t)off_cycle[k]]) if (--left[(size_t)p] == 0) off_cycle.push_back(p);
+        A.acyclic = off_cycle.size() == n;
+        if (!A.acyclic) {
+            A.on_cycle.assign(n, 1);
+            for (int x : off_cycle) A.on_cycle[(size_t)f.canon_id[(size_t)x]] = 0;
         }
-        return A;
     }
-    A.level.assign((size_t)(budget + 1) * (size_t)n, 0);
-    // Levels only refine, so a state that is alone in its class stays alone: it needs no further comparing, which leaves
-    // little to do after the first few levels.  The others are grouped by their signatures through a small table whose
-    // hits are confirmed word by word.
-    std::vector<uint32_t> words, begin((size_t)n + 1);            // signatures of this level, and where each state's starts
-    std::vector<std::pair<uint32_t, uint32_t>> refs;
-    struct Slot { uint32_t stamp, hash; int32_t state; uint32_t len; };
-    size_t cap = 16;
-    while (cap < (size_t)n * 2) cap <<= 1;
-    std::vector<Slot> slot(cap, Slot{0, 0, 0, 0});
-    std::vector<int32_t> members(1, n), next_members;             // states per class
-    int32_t unchanged = 0;
-    for (int32_t d = 1; d <= budget; ++d) {
-        const int32_t* prev = A.level.data() + (size_t)(d - 1) * (size_t)n;
-        int32_t* cur = A.level.data() + (size_t)d * (size_t)n;
-        // Level d is a function of level d - 1 and of the levels d - m for the shortest sentences m of the referenced rules,
-        // so once the partition has not changed over max m (at least one) levels in a row it never changes again.
-        if (unchanged >= settle) { std::copy(prev, prev + n, cur); continue; }
-        words.clear();
-        next_members.clear();
-        for (int c : order) {
-            if (members[(size_t)prev[c]] == 1) { cur[c] = (int32_t)next_members.size(); next_members.push_back(1); continue; }
-            const int x = f.by_canon[(size_t)c];
-            const uint32_t w0 = (uint32_t)words.size();
-            words.push_back(0);
-            uint32_t runs = 0;
-            {   // maximal runs of consecutive bytes that lead to the same class (edges are sorted and disjoint)
-                int run_lo = -1, run_hi = -1; int32_t run_cls = 0;
-                auto flush = [&] { words.push_back((uint32_t)run_lo | ((uint32_t)run_hi << 8)); words.push_back((uint32_t)run_cls); ++runs; };
-                for (auto& e : f.bedges(x)) {
-                    const int32_t u = prev[f.canon_id[(size_t)e.tgt]];
-                    if (run_lo >= 0 && (int)e.lo == run_hi + 1 && u == run_cls) { run_hi = e.hi; continue; }
-                    if (run_lo >= 0) flush();
-                    run_lo = e.lo; run_hi = e.hi; run_cls = u;
-                }
-                if (run_lo >= 0) flush();
-            }
-            if (!f.refs(x).empty()) {
-                refs.clear();
-                for (auto& e : f.refs(x)) {
-                    const RuleFsm& r = g.rules[(size_t)e.rule];
-                    const int32_t left = r.nullable ? d : d - r.min_len;
-                    refs.emplace_back((uint32_t)identity[(size_t)e.rule], left >= 0 ? (uint32_t)A.level[(size_t)left * (size_t)n + (size_t)f.canon_id[(size_t)e.tgt]] : kNodeTooLong);
-                }
-                if (refs.size() > 1) std::sort(refs.begin(), refs.end());
-                for (auto& p : refs) { words.push_back(p.first); words.push_back(p.second); }
-            }
-            words[w0] = (f.is_final(x) ? kNodeFinal : 0u) | runs;
-            const uint32_t len = (uint32_t)words.size() - w0;
-            begin[(size_t)c] = w0;
-            uint64_t h = len;
-            for (uint32_t k = 0; k < len; ++k) { h = (h ^ words[w0 + k]) * 0x9FB21C651E98DF25ull; h ^= h >> 32; }
-            for (size_t at = (size_t)h & (cap - 1);; at = (at + 1) & (cap - 1)) {
-                Slot& s = slot[at];
-                if (s.stamp != (uint32_t)d) {
-                    s = {(uint32_t)d, (uint32_t)h, c, len};
-                    cur[c] = (int32_t)next_members.size();
-                    next_members.push_back(1);
-                    break;
-                }
-                if (s.hash == (uint32_t)h && s.len == len && std::equal(words.begin() + w0, words.end(), words.begin() + begin[(size_t)s.state])) {
-                    cur[c] = cur[s.state];
-                    ++next_members[(size_t)cur[c]];
-                    break;
-                }
-            }
-        }
-        unchanged = next_members.size() == members.size() ? unchanged + 1 : 0;
-        members.swap(next_members);
-    }
-    // classes and near-classes from the levels, in canonical numbers
-    std::vector<int32_t> ident((size_t)n);
-    std::vector<uint8_t> scans((size_t)n);
-    for (int c = 0; c < n; ++c) { ident[(size_t)c] = c; scans[(size_t)c] = !f.bedges(f.by_canon[(size_t)c]).empty(); }
-    class_representatives(A.level.data(), n, budget, ident.data(), scans, A.rep, &A.near);
+    bounded_levels(g, f, budget, identity, A.level);
+    std::vector<uint8_t> scans(n);
+    for (size_t c = 0; c < n; ++c) scans[c] = !f.bedges(f.by_canon[c]).empty();
+    class_representatives(A.level.data(), (int)n, budget, scans, A.rep, &A.near);
     return A;
 }
 

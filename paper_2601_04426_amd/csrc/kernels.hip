@@ -965,11 +965,14 @@ __global__ __launch_bounds__(64) void k_recheck_slow(FillBatch F, DevVocab Vd, i
 }
 
 // ---- matchers on the device ------------------------------------------------------------------------
-// k_accept: one wavefront per matcher slot.  The lanes bring the slot's context into LDS, lane 0 takes the sampled token
-// through the recogniser and writes the slot's next context and frontier planes (accept_core.hpp) into an LDS staging
-// area, with its item lists, the renumbering table and the frontier staging in LDS too, and the lanes copy the result
-// out.  A token or context too large for that runs again with everything in device memory.  A slot whose capacity is
-// exceeded gets a sticky error and answers XG2_EOVERFLOW until it is reset.
+// k_accept: one wavefront per matcher slot.  The kernel lasts as long as its slowest slot, and a slot is one chain of
+// dependent steps, so the wavefront works on one slot as a whole (WaveAccept below): items, wait entries and expansions lie
+// across the lanes, a set's look-ups in the transition table are one gather, a prediction is one load, and what remains in
+// order are list insertions in registers.  (With lane 0 doing everything on lists in LDS the same steps took 16 us at 16 - 64
+// slots and 24 us at 1,024; one lane per slot 458 us.)  A token or context that does not fit across 64 lanes takes the
+// recogniser of accept_core.hpp on lane 0, with its lists, the renumbering table and the frontier staging in LDS, and one
+// too large for that the same with everything in device memory.  A slot whose capacity is exceeded gets a sticky error and
+// answers XG2_EOVERFLOW until it is reset.
 constexpr int ACCEPT_K = 64, ACCEPT_WM = 256, ACCEPT_MAXLEN = 48;  // lane 0's item lists
 struct OneLaneStore {
     static constexpr int K = ACCEPT_K, WM = ACCEPT_WM, MAXLEN = ACCEPT_MAXLEN, WORDS = 2 * ACCEPT_K + 2 * ACCEPT_WM + ACCEPT_MAXLEN + 1;
@@ -1032,6 +1035,231 @@ __global__ __launch_bounds__(256) void k_batch_assign(BatchDev D, const int32_t*
 }
 
 constexpr uint32_t ACC_KI = kSlotItems, ACC_KH = kSlotSets, ACC_KW = kSlotWaits, ACC_KF = kSlotPlanes;     // the slot capacities the LDS staging is laid out for
+
+__device__ __forceinline__ uint32_t lane_value(uint32_t v, uint32_t k) { return (uint32_t)__builtin_amdgcn_readlane((int)v, (int)k); }
+// A value that is the same in all lanes, as the compiler cannot know where it came from memory.
+__device__ __forceinline__ uint32_t same_in_all(uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); }
+// A load whose address is the same in all lanes, from memory that no kernel writes while this one runs: the scalar cache
+// serves it, and the compiler knows that the value is uniform.
+template <class P>
+__device__ __forceinline__ P uniform_load(const P* p) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    return *(const __attribute__((address_space(4))) P*)p;
+#else
+    return *p;
+#endif
+}
+__device__ __forceinline__ uint32_t next_bit(unsigned long long& m) { const uint32_t j = (uint32_t)__ffsll((long long)m) - 1; m &= m - 1; return j; }
+
+// The Earley steps of earley_core.hpp with one wavefront per token: lane k holds item k of the set at hand together with the
+// state it goes to on the next byte (looked up when the item is entered: it is the lookahead and the next scanner step in
+// one).  Control flow is the same in all lanes; values picked out of a lane are wave-uniform.
+struct WaveAccept {
+    static constexpr uint32_t N = 64;
+    const DevTables T;
+    const uint2* wait; const uint32_t* off;       // LDS: wait entries of every set so far, and where each set's start
+    const uint32_t lane;
+    uint32_t item, to;                            // the set under construction: lane k < n holds item k, and where it goes on the next byte
+    uint32_t n;
+    uint32_t w_rule, w_tgt, n_w;                  // its wait entries so far: lane k < n_w holds entry k
+    uint32_t set_idx, la;                         // its number; class of the next byte, or NO_TARGET after the last one
+    bool full, root_done;
+
+    __device__ __forceinline__ bool add(uint32_t v, uint32_t v_to) {
+        if (__ballot(lane < n && item == v)) return false;
+        if (n == N) { full = true; return false; }
+        if (lane == n) { item = v; to = v_to; }
+        ++n;
+        return true;
+    }
+    __device__ __forceinline__ void add_wait(uint32_t rule, uint32_t tgt) {
+        if (__ballot(lane < n_w && w_tgt == tgt && w_rule == rule)) return;
+        if (n_w == N) { full = true; return; }
+        if (lane == n_w) { w_rule = rule; w_tgt = tgt; }
+        ++n_w;
+    }
+    // where a state goes on the next byte (a gather over the lanes that ask)
+    __device__ __forceinline__ uint32_t next_of(bool mine, uint32_t ref) const {
+        uint32_t t = NO_TARGET;
+        if (mine && (ref & F_BYTE) && la != NO_TARGET) t = tab(T.trans + (ref & SID_MASK) * T.n_classes + la);
+        return t;
+    }
+    // byte edges only, not final, and none of them for the next byte: the item can do nothing
+    __device__ __forceinline__ bool is_inert(uint32_t ref, uint32_t t) const { return (ref & (F_BYTE | F_REF | F_FINAL)) == F_BYTE && t == T.sink; }
+    __device__ __forceinline__ void expand(uint32_t ref, uint32_t origin) {
+        const uint4 d = uniform_load(T.state + (ref & SID_MASK));
+        const uint32_t* e = T.exp_list + d.y;
+        const uint32_t* e2 = e + d.z;
+        const uint32_t most = d.z > d.w ? d.z : d.w;
+        for (uint32_t base = 0; base < most; base += N) {
+            const bool has_item = base + lane < d.z, has_wait = base + lane < d.w;
+            uint32_t w = 0, rule = 0, tgt = 0;
+            if (has_item) w = tab(e + base + lane);
+            if (has_wait) { rule = tab(e2 + 2 * (base + lane)); tgt = tab(e2 + 2 * (base + lane) + 1); }
+            const uint32_t t = next_of(has_item, w);
+            for (unsigned long long m = __ballot(has_item && !is_inert(w, t)); m;) {
+                const uint32_t j = next_bit(m), v = lane_value(w, j);
+                add((v & REF_MASK) | (((v & EXP_CURRENT) ? set_idx : origin) << REF_BITS), lane_value(t, j));
+            }
+            for (unsigned long long m = __ballot(has_wait); m;) {
+                const uint32_t j = next_bit(m), v = lane_value(tgt, j);
+                add_wait(lane_value(rule, j), (v & REF_MASK) | (((v & EXP_CURRENT) ? set_idx : origin) << REF_BITS));
+            }
+        }
+    }
+    // the lanes of m each enter the state `ref` with their origin
+    __device__ __forceinline__ void enter(unsigned long long m, uint32_t ref, uint32_t origin) {
+        const uint32_t t = next_of((m >> lane) & 1, ref);
+        m &= ~__ballot(is_inert(ref, t));
+        while (m) {
+            const uint32_t j = next_bit(m), r = lane_value(ref, j), o = lane_value(origin, j);
+            if ((r & (F_BYTE | F_FINAL)) || !(r & F_REF)) { if (!add(r | (o << REF_BITS), lane_value(t, j))) continue; }
+            if (r & F_REF) expand(r, o);
+        }
+    }
+    // One byte: scanner and completer over the set held in (cur_item, cur_to, cur_n).  False: nothing survives.
+    __device__ __forceinline__ bool step(uint32_t cur_item, uint32_t cur_to, uint32_t cur_n) {
+        n = 0; n_w = 0; root_done = false;
+        enter(__ballot(lane < cur_n && (cur_item & F_BYTE) && cur_to != T.sink), cur_to, cur_item >> REF_BITS);
+        unsigned long long done = 0;
+        for (;;) {
+            unsigned long long m = __ballot(lane < n && (item & F_FINAL) && (item >> REF_BITS) != set_idx) & ~done;
+            if (!m) break;
+            done |= m;
+            uint32_t rule_of = 0;
+            if (((m >> lane) & 1) && (item >> REF_BITS) != ROOT_ORIGIN) rule_of = tab(&T.state[item & SID_MASK].x);
+            const uint32_t held = item;                             // entering below only appends
+            while (m) {
+                const uint32_t j = next_bit(m), o = lane_value(held, j) >> REF_BITS;
+                if (o == ROOT_ORIGIN) { root_done = true; continue; }
+                const uint32_t rule = lane_value(rule_of, j), lo = same_in_all(off[o]), hi = same_in_all(off[o + 1]);
+                for (uint32_t base = lo; base < hi; base += N) {
+                    uint2 w = make_uint2(0, 0);
+                    if (base + lane < hi) w = wait[base + lane];
+                    const unsigned long long hit = __ballot(base + lane < hi && w.x == rule);
+                    if (hit) enter(hit, w.y & REF_MASK, w.y >> REF_BITS);
+                }
+            }
+        }
+        return n != 0 || n_w != 0;
+    }
+};
+
+// The slot's next state from token `tok16` (1 .. 16 bytes), written to the slot's other buffer; results in out_n (items, sets,
+// planes, root can end).  ACC_RETRY: something does not fit across the lanes, nothing has been written that counts.
+__device__ __forceinline__ int accept_wave(const BatchDev& D, const CacheDev* Cp, const uint8_t* cls_bytes, uint32_t b, const FillRow& r, size_t slot, uint4 tok16, uint32_t n_bytes,
+                                           uint32_t in_item, uint2* wait, uint32_t* off, uint32_t* pair_sid, uint32_t* pair_tgt, uint32_t lane, uint32_t out_n[4]) {
+    const DevTables T = uniform_load(&Cp->T);
+    const bool depth1 = uniform_load(&Cp->context_depth) == 1;
+    const uint32_t H = r.H, n_sets = H + n_bytes;
+    if (n_sets > 64 || r.item_n > 64) return ACC_RETRY;
+    // classes of the token's bytes, one a lane
+    const uint32_t words[4] = {tok16.x, tok16.y, tok16.z, tok16.w};
+    const uint32_t byte = (words[(lane >> 2) & 3] >> (8 * (lane & 3))) & 0xFF, cls_of = cls_bytes[byte];
+    uint32_t n_wait = same_in_all(off[H]);
+    if (n_wait > 64) return ACC_RETRY;
+    WaveAccept A{T, wait, off, lane, 0, 0, 0, 0, 0, 0, 0, 0, false, false};
+    uint32_t cur = in_item, cur_n = r.item_n;
+    A.la = lane_value(cls_of, 0);
+    uint32_t cur_to = A.next_of(lane < cur_n, cur);
+    for (uint32_t i = 0; i < n_bytes; ++i) {
+        A.set_idx = H + i;
+        A.la = i + 1 < n_bytes ? lane_value(cls_of, i + 1) : NO_TARGET;
+        const bool alive = A.step(cur, cur_to, cur_n);
+        if (A.full) return ACC_RETRY;
+        if (!alive) return ACC_REJECTED;
+        if (n_wait + A.n_w > 64) return ACC_RETRY;
+        if (lane < A.n_w) wait[n_wait + lane] = make_uint2(A.w_rule, A.w_tgt);
+        n_wait += A.n_w;
+        if (lane == 0) off[H + i + 1] = n_wait;
+        __syncthreads();                                            // one wave: orders the LDS traffic
+        cur = A.item; cur_to = A.to; cur_n = A.n;
+    }
+    // Which sets are still reachable: the current one, the origins of its items, and on from there through the wait entries
+    // (an entry's origin is never above its own set, so one pass downwards settles it).  Entry e is lane e's, set s lane s's.
+    const uint2 my_wait = lane < n_wait ? wait[lane] : make_uint2(0, 0);
+    const uint32_t my_off = lane <= n_sets ? off[lane] : 0u, w_origin = my_wait.y >> REF_BITS;
+    uint32_t my_set = 0;
+    for (uint32_t s = 1; s < n_sets; ++s) my_set += lane_value(my_off, s) <= lane ? 1u : 0u;
+    const bool scans = lane < cur_n && (cur & F_BYTE);              // final-only items have done their work in the closure
+    unsigned long long reach = 1ull << (n_sets - 1);
+    for (unsigned long long m = __ballot(scans && (cur >> REF_BITS) != ROOT_ORIGIN); m;) reach |= 1ull << (lane_value(cur, next_bit(m)) >> REF_BITS);
+    for (uint32_t s = n_sets; s-- > 0;) {
+        if (!((reach >> s) & 1)) continue;
+        for (unsigned long long m = __ballot(lane < n_wait && my_set == s && w_origin != ROOT_ORIGIN); m;) reach |= 1ull << lane_value(w_origin, next_bit(m));
+    }
+    // renumbered in their old order: the wait entries and starts of the sets that are kept, the items that can scan
+    auto renumber = [&](uint32_t o) { return o == ROOT_ORIGIN ? ROOT_ORIGIN : (uint32_t)__popcll(reach & ((1ull << o) - 1)); };
+    const uint32_t newH = (uint32_t)__popcll(reach);
+    const unsigned long long below = (1ull << lane) - 1;
+    const bool keep = lane < n_wait && ((reach >> my_set) & 1);
+    const unsigned long long kept = __ballot(keep), scanning = __ballot(scans);
+    if (keep) D.wait[slot * D.KW + (uint32_t)__popcll(kept & below)] = make_uint2(my_wait.x, (my_wait.y & REF_MASK) | (renumber(w_origin) << REF_BITS));
+    if (lane < n_sets && ((reach >> lane) & 1))
+        D.wait_off[slot * (D.KH + 1) + renumber(lane)] = (uint32_t)__popcll(my_off < 64 ? kept & ((1ull << my_off) - 1) : kept);
+    if (lane == 0) D.wait_off[slot * (D.KH + 1) + newH] = (uint32_t)__popcll(kept);
+    if (scans) D.items[slot * D.KI + (uint32_t)__popcll(scanning & below)] = (cur & REF_MASK) | (renumber(cur >> REF_BITS) << REF_BITS);
+    // the frontier's planes: of every item alone (root instance, or context depth 1), else under every entry of the item's
+    // origin that waits for its rule; the pairs are listed in LDS and looked up one a lane
+    constexpr uint32_t ALONE = 0xFFFFFFFFu;
+    const bool alone = (cur >> REF_BITS) == ROOT_ORIGIN || depth1;
+    uint32_t rule_of = 0;
+    if (scans && !alone) rule_of = tab(&T.state[cur & SID_MASK].x);
+    uint32_t n_pairs = 0;
+    for (unsigned long long m = scanning; m;) {
+        const uint32_t j = next_bit(m), v = lane_value(cur, j), o = v >> REF_BITS;
+        if (o == ROOT_ORIGIN || depth1) {
+            if (n_pairs >= 64) return ACC_RETRY;
+            if (lane == 0) { pair_sid[n_pairs] = v; pair_tgt[n_pairs] = ALONE; }
+            ++n_pairs;
+            continue;
+        }
+        const uint32_t rule = lane_value(rule_of, j);
+        const bool mine = lane < n_wait && my_set == o && my_wait.x == rule;
+        const unsigned long long hit = __ballot(mine);
+        if (!hit) return ACC_NO_PLANE;
+        if (n_pairs + (uint32_t)__popcll(hit) > 64) return ACC_RETRY;
+        if (mine) { const uint32_t at = n_pairs + (uint32_t)__popcll(hit & below); pair_sid[at] = v; pair_tgt[at] = my_wait.y; }
+        n_pairs += (uint32_t)__popcll(hit);
+    }
+    __syncthreads();
+    uint64_t row = 0;
+    const uint32_t* pair_off = uniform_load(&Cp->pair_off);
+    const uint64_t* pair_row = uniform_load(&Cp->pair_row);
+    const uint32_t* site_of_off = uniform_load(&Cp->site_of_off);
+    const uint2* site_of = uniform_load(&Cp->site_of);
+    if (lane < n_pairs) {
+        const uint32_t v = pair_sid[lane], t = pair_tgt[lane], sid = v & SID_MASK;
+        if (t == ALONE) {
+            row = tab(uniform_load(&Cp->plain_row) + sid);
+            // the root instance: leaving the rule leaves the grammar, so its uncertain tokens are never allowed
+            if (row && (v >> REF_BITS) == ROOT_ORIGIN) row |= 1u;
+        } else {
+            const uint32_t rule = tab(&T.state[sid].x), base = tab(pair_off + sid), end = tab(pair_off + sid + 1);
+            const uint32_t k1 = tab(site_of_off + (t & SID_MASK) + 1);
+            for (uint32_t k = tab(site_of_off + (t & SID_MASK)); k < k1; ++k) {
+                const uint2 s = tab(site_of + k);
+                if (s.x == rule) { if (base + s.y < end) row = tab(pair_row + base + s.y); break; }
+            }
+        }
+    }
+    if (__ballot(lane < n_pairs && row == 0)) return ACC_NO_PLANE;
+    // each plane once; where it is listed with and without its uncertain tokens, they count
+    uint32_t nf = 0;
+    uint64_t front = 0;
+    for (uint32_t p = 0; p < n_pairs; ++p) {
+        const uint64_t v = ((uint64_t)lane_value((uint32_t)(row >> 32), p) << 32) | lane_value((uint32_t)row, p);
+        const bool same = lane < nf && (front & ~(uint64_t)1) == (v & ~(uint64_t)1);
+        if (__ballot(same)) { if (same) front &= v | ~(uint64_t)1; continue; }
+        if (nf >= D.KF) return ACC_OVERFLOW;
+        if (lane == nf) front = v;
+        ++nf;
+    }
+    if (lane < nf) D.front[(size_t)b * D.KF + lane] = front;
+    out_n[0] = (uint32_t)__popcll(scanning); out_n[1] = newH; out_n[2] = nf; out_n[3] = A.root_done ? 1u : 0u;
+    return ACC_OK;
+}
+
 __global__ __launch_bounds__(64) void k_accept(BatchDev D, DevVocab Vd, uint32_t eos_id, const int32_t* token_ids, int32_t* status) {
     __shared__ uint32_t in_items[ACC_KI], in_wait_off[ACC_KH + 1], out_items[ACC_KI], out_wait_off[ACC_KH + 1];
     __shared__ uint2 in_wait[ACC_KW], out_wait[ACC_KW];
@@ -1042,9 +1270,12 @@ __global__ __launch_bounds__(64) void k_accept(BatchDev D, DevVocab Vd, uint32_t
     __shared__ int sh_acc;
     __shared__ uint32_t sh_out[4];                                 // n_items, H, n_front, root_done
     const uint32_t lane = threadIdx.x, b = blockIdx.x;              // one wavefront per slot: everything below is the same in all lanes
-    const int32_t tok = token_ids[b];
+    const int32_t tok = (int32_t)same_in_all((uint32_t)token_ids[b]);
     int32_t code = kAccOk;
     FillRow r = D.rows[b];
+    r.item_off = same_in_all(r.item_off); r.item_n = same_in_all(r.item_n); r.wait_base = same_in_all(r.wait_base);
+    r.waitoff_off = same_in_all(r.waitoff_off); r.H = same_in_all(r.H); r.tables_idx = same_in_all(r.tables_idx);
+    r.flags = same_in_all(r.flags); r.pad[0] = same_in_all(r.pad[0]); r.pad[1] = same_in_all(r.pad[1]);
     if (tok == kTokenReset) start_sequence(D, b, r.tables_idx, lane, 64);
     else if (tok < 0) code = kAccOk;                                 // nothing for this slot
     else if (r.pad[1]) code = kAccOverflow;                          // unusable until reset
@@ -1053,48 +1284,69 @@ __global__ __launch_bounds__(64) void k_accept(BatchDev D, DevVocab Vd, uint32_t
         if (!(r.flags & 1u)) code = kAccRejected;
         else if (lane == 0) D.rows[b].flags = r.flags | 2u;          // the sequence ends here
     } else {
-        const uint32_t rank = Vd.rank[tok];
+        const uint32_t rank = uniform_load(Vd.rank + tok);
         if (rank >= Vd.n_sorted) code = kAccRejected;                // special and empty tokens are never allowed
         else {
-            const uint32_t off = Vd.off[rank];
-            const int n = (int)(Vd.off[rank + 1] - off);
             const uint32_t nb = r.pad[0] ^ 1u;
-            const CacheDev Cd = D.caches[r.tables_idx];             // by value: no reload after every store
+            const CacheDev* const Cp = D.caches + r.tables_idx;
             const size_t slot = (size_t)nb * D.B + b;
-            // the byte classes and the slot's context into LDS
-            cls_words[lane] = Cd.T.byte_class_words[lane];
-            const uint32_t n_wait_in = D.wait_off[r.waitoff_off + r.H];
-            for (uint32_t k = lane; k < r.item_n; k += 64) in_items[k] = D.items[r.item_off + k];
-            for (uint32_t k = lane; k <= r.H; k += 64) in_wait_off[k] = D.wait_off[r.waitoff_off + k];
-            for (uint32_t k = lane; k < n_wait_in; k += 64) in_wait[k] = D.wait[r.wait_base + k];
+            // the byte classes and the first 64 of everything in the slot's context, without waiting for the counts (a slot
+            // has room for that many and more)
+            const uint32_t my_item = D.items[r.item_off + lane], my_off = D.wait_off[r.waitoff_off + lane];
+            const uint2 my_wait = D.wait[r.wait_base + lane];
+            const uint32_t off = uniform_load(Vd.off + rank);
+            const int n = (int)(uniform_load(Vd.off + rank + 1) - off);
+            const uint4 tok16 = uniform_load(Vd.tok16 + rank);
+            cls_words[lane] = tab(uniform_load(&Cp->T.byte_class_words) + lane);
+            in_wait[lane] = my_wait;
+            in_wait_off[lane] = my_off;
             __syncthreads();
-            if (lane == 0) {
-                MatcherIn in{in_items, r.item_n, in_wait, in_wait_off, r.H};
-                MatcherOut out{out_items, out_wait, out_wait_off, out_front, ACC_KI, ACC_KH, ACC_KW, ACC_KF, 0, 0, 0, 0};
-                OneLaneStore st;
-                st.init(lists);
-                OneLaneScratchX<ACC_KH + ACCEPT_MAXLEN, ACC_KF> x{x_map, x_front};
-                int acc = accept_token(Cd, cls_words, in, Vd.bytes + off, n, st, x, out);
-                if (acc == ACC_RETRY) {
-                    // lists in device memory, results straight to the slot's other buffer
-                    MatcherIn gin{D.items + r.item_off, r.item_n, D.wait + r.wait_base, D.wait_off + r.waitoff_off, r.H};
-                    MatcherOut gout{D.items + slot * D.KI, D.wait + slot * D.KW, D.wait_off + slot * (D.KH + 1), D.front + (size_t)b * D.KF,
-                                    D.KI, D.KH, D.KW, D.KF, 0, 0, 0, 0};
-                    GlobalStore gs;
-                    gs.init(D.slow_mem + b, D.B);
-                    GlobalScratchX gx{D.slow_map + b, D.slow_front + b, D.B, D.KH + kSlowMaxLen + 1, D.KF};
-                    acc = accept_token(Cd, cls_words, gin, Vd.bytes + off, n, gs, gx, gout);
-                    out.n_items = gout.n_items; out.H = gout.H; out.n_front = gout.n_front; out.root_done = gout.root_done;
-                    if (acc == ACC_OK) acc = -1;                     // done, nothing to copy out
+            uint32_t got[4] = {0, 0, 0, 0};
+            int acc = ACC_RETRY;
+            if (n <= 16 && r.H + (uint32_t)n <= 64)
+                acc = accept_wave(D, Cp, reinterpret_cast<const uint8_t*>(cls_words), b, r, slot, tok16, (uint32_t)n, my_item, in_wait, in_wait_off,
+                                  out_items, lists, lane, got);
+            bool copied = acc == ACC_OK;
+            if (acc == ACC_RETRY) {
+                // lane 0, with the slot's whole context in LDS
+                __syncthreads();
+                for (uint32_t k = lane; k < r.item_n; k += 64) in_items[k] = D.items[r.item_off + k];
+                for (uint32_t k = lane; k <= r.H; k += 64) in_wait_off[k] = D.wait_off[r.waitoff_off + k];
+                const uint32_t n_wait_in = D.wait_off[r.waitoff_off + r.H];
+                for (uint32_t k = lane; k < n_wait_in; k += 64) in_wait[k] = D.wait[r.wait_base + k];
+                __syncthreads();
+                if (lane == 0) {
+                    const CacheDev Cd = *Cp;
+                    MatcherIn in{in_items, r.item_n, in_wait, in_wait_off, r.H};
+                    MatcherOut out{out_items, out_wait, out_wait_off, out_front, ACC_KI, ACC_KH, ACC_KW, ACC_KF, 0, 0, 0, 0};
+                    OneLaneStore st;
+                    st.init(lists);
+                    OneLaneScratchX<ACC_KH + ACCEPT_MAXLEN, ACC_KF> x{x_map, x_front};
+                    int a = accept_token(Cd, cls_words, in, Vd.bytes + off, n, st, x, out);
+                    if (a == ACC_RETRY) {
+                        // lists in device memory, results straight to the slot's other buffer
+                        MatcherIn gin{D.items + r.item_off, r.item_n, D.wait + r.wait_base, D.wait_off + r.waitoff_off, r.H};
+                        MatcherOut gout{D.items + slot * D.KI, D.wait + slot * D.KW, D.wait_off + slot * (D.KH + 1), D.front + (size_t)b * D.KF,
+                                        D.KI, D.KH, D.KW, D.KF, 0, 0, 0, 0};
+                        GlobalStore gs;
+                        gs.init(D.slow_mem + b, D.B);
+                        GlobalScratchX gx{D.slow_map + b, D.slow_front + b, D.B, D.KH + kSlowMaxLen + 1, D.KF};
+                        a = accept_token(Cd, cls_words, gin, Vd.bytes + off, n, gs, gx, gout);
+                        out.n_items = gout.n_items; out.H = gout.H; out.n_front = gout.n_front; out.root_done = gout.root_done;
+                        if (a == ACC_OK) a = -1;                     // done, nothing to copy out
+                    }
+                    sh_acc = a;
+                    sh_out[0] = out.n_items; sh_out[1] = out.H; sh_out[2] = out.n_front; sh_out[3] = out.root_done;
                 }
-                sh_acc = acc;
-                sh_out[0] = out.n_items; sh_out[1] = out.H; sh_out[2] = out.n_front; sh_out[3] = out.root_done;
+                __syncthreads();
+                acc = sh_acc;
+                copied = acc == -1;
+                if (copied) acc = ACC_OK;
+                for (int k = 0; k < 4; ++k) got[k] = sh_out[k];
             }
-            __syncthreads();
-            const int acc = sh_acc;
-            if (acc == ACC_OK || acc == -1) {
-                const uint32_t n_items = sh_out[0], H = sh_out[1], n_front = sh_out[2];
-                if (acc == ACC_OK) {
+            if (acc == ACC_OK) {
+                const uint32_t n_items = got[0], H = got[1], n_front = got[2];
+                if (!copied) {
                     for (uint32_t k = lane; k < n_items; k += 64) D.items[slot * D.KI + k] = out_items[k];
                     for (uint32_t k = lane; k <= H; k += 64) D.wait_off[slot * (D.KH + 1) + k] = out_wait_off[k];
                     const uint32_t n_wait = out_wait_off[H];
@@ -1105,7 +1357,7 @@ __global__ __launch_bounds__(64) void k_accept(BatchDev D, DevVocab Vd, uint32_t
                     r.front_n = n_front;
                     r.item_off = (uint32_t)(slot * D.KI); r.item_n = n_items;
                     r.wait_base = (uint32_t)(slot * D.KW); r.waitoff_off = (uint32_t)(slot * (D.KH + 1)); r.H = H;
-                    r.flags = sh_out[3];
+                    r.flags = got[3];
                     r.pad[0] = nb;
                     D.rows[b] = r;
                 }
