@@ -615,6 +615,9 @@ struct CacheImpl {
     std::vector<std::shared_ptr<BuildTicket>> jit_tickets;  // builds issued by fill calls whose device time has not been added up yet
     double host_lower_ms = 0;                               // EBNF -> tables and plan, of the compile call
     int64_t compile_built = 0;
+    // Some state's expansion alone has more items than the short lists of the re-check hold: in such a grammar many candidates
+    // of a row may outgrow them, and the fill leaves those to a launch of its own instead of to the row's workgroup.
+    bool wide = false;
     std::vector<uint32_t> site_off, site_tgt;               // per rule: states in which referencing rules continue
     int64_t n_built = 0, jit_calls = 0;                     // planes holding a row; build launches issued by fill
     double jit_device_ms = 0;
@@ -671,6 +674,14 @@ struct MatcherImpl {
         chart.start(gram->ft.root_start);
     }
 };
+
+constexpr uint32_t kWideExpansion = 12;
+// How many lanes of the large-capacity scratch each row of a fill gets for itself (its workgroup has six wavefronts; the
+// sequential way of a row needs two), or 0 if the rows are too many or a grammar is wide: k_recheck_slow is launched then.
+inline uint32_t lanes_per_row(uint32_t n_lanes, size_t B, bool wide) {
+    const size_t per = n_lanes / B;
+    return wide || per < 2 ? 0u : (uint32_t)std::min<size_t>(per, 6);
+}
 
 // ---- fill workspace: pinned staging ring + device mirror ---------------------------------------------------
 constexpr uint32_t kUnresolvedCap = 255;                    // (row, token) pairs a fill call can report as undecided
@@ -1343,6 +1354,7 @@ struct BatchImpl {
     std::vector<std::shared_ptr<CacheImpl>> caches;
     std::vector<uint8_t> assigned;
     int32_t n_assigned = 0;
+    bool wide = false;                                      // some cache is
 };
 
 struct xg2_batch { std::unique_ptr<BatchImpl> p; };
@@ -1544,6 +1556,7 @@ int32_t xg2_compile_grammar(xg2_vocab* vocab, const char* ebnf, size_t len, cons
         cache->gram = make_grammar(ebnf, len, root_rule);
         const Grammar& g = cache->gram->g;
         const FlatTables& ft = cache->gram->ft;
+        for (const DevState& ds : ft.dev_state) cache->wide |= ds.n_items > kWideExpansion;
         VocabImpl& V = *vocab->p;
         V.ensure_device();
         cache->pool = pool_h ? pool_h->p : std::make_shared<PoolImpl>();
@@ -2266,8 +2279,11 @@ int32_t fill_common(xg2_matcher* const* matchers, int32_t B, int32_t* bitmask_de
         F.tables = reinterpret_cast<const DevTables*>(dev + o_tabs);
         F.eos_id = (uint32_t)V.eos;
         S.count = reinterpret_cast<uint32_t*>(dev + o_zero);               // this call's overflow counter and flag, zero on arrival
+        bool wide = false;
+        for (auto& t : table_idx) wide |= t.first->wide;
+        F.own_lanes = lanes_per_row(S.n_lanes, (size_t)B, wide);
         launch_fill(F, V.dv, bitmask_dev, row_stride_words, S, stream);
-        launch_recheck_slow(F, V.dv, bitmask_dev, row_stride_words, S, stream);
+        if (!F.own_lanes) launch_recheck_slow(F, V.dv, bitmask_dev, row_stride_words, S, stream);
         HIP_CHECK(hipGetLastError());
         fill_ws().last_flags = S.count;
         fill_ws().last_counts = F.row_count;
@@ -2459,6 +2475,7 @@ int32_t xg2_batch_assign(xg2_batch* batch, const int32_t* rows_host, int32_t n, 
         if (ci == Bt.caches.size()) {
             if (ci >= BatchImpl::kMaxCaches) return fail(XG2_EOVERFLOW, "xg2_batch_assign: too many different caches in one batch");
             Bt.caches.push_back(cache->p);                      // kept alive while the batch lives
+            Bt.wide |= cache->p->wide;
             HIP_CHECK(hipMemcpyAsync(Bt.caches_dev.p + ci, &od.cd, sizeof(CacheDev), hipMemcpyHostToDevice, stream));
             HIP_CHECK(hipMemcpyAsync(Bt.tables_dev.p + ci, &od.cd.T, sizeof(DevTables), hipMemcpyHostToDevice, stream));
         }
@@ -2511,9 +2528,10 @@ int32_t xg2_batch_fill_next_token_bitmask(xg2_batch* batch, int32_t* bitmask_dev
         Bt.flag_turn ^= 1;
         F.zero_words = Bt.flag_words.p + 4 * Bt.flag_turn;
         S.mark_rows = Bt.d.rows;                                // an undecided pair makes its slot unusable: the next accept says so
+        F.own_lanes = lanes_per_row(S.n_lanes, (size_t)Bt.B, Bt.wide);
         HIP_CHECK(hipEventRecord(fill_ws().t_begin, stream));
         launch_fill(F, V.dv, bitmask_dev, row_stride_words, S, stream);
-        launch_recheck_slow(F, V.dv, bitmask_dev, row_stride_words, S, stream);
+        if (!F.own_lanes) launch_recheck_slow(F, V.dv, bitmask_dev, row_stride_words, S, stream);
         HIP_CHECK(hipGetLastError());
         HIP_CHECK(hipEventRecord(fill_ws().t_end, stream));
         fill_ws().last_flags = S.count; fill_ws().last_counts = F.row_count; fill_ws().last_B = Bt.B; fill_ws().last_stream = stream;

@@ -142,8 +142,10 @@ struct FillBatch {
     uint32_t* cand_words;                // [B * W]
     uint32_t* work_list;                 // [B * W], row b's list starts at b * W
     uint32_t* row_count;                 // [B], written by the fill kernel: candidate tokens of the row
-    uint32_t* zero_words;                // if not null: four words the large-capacity kernel clears for the next call (the overflow
-                                         // list's length and flag, where no upload brings them in as zeros: two sets take turns)
+    uint32_t* zero_words;                // if not null: four words the fill kernel clears for the next call (the overflow list's length
+                                         // and flag, where no upload brings them in as zeros: two sets take turns)
+    uint32_t own_lanes;                  // lanes of the large-capacity scratch that are a row's own: it then decides every token itself;
+                                         // 0: what outgrows the short lists is left to k_recheck_slow
 };
 void launch_fill(const FillBatch& F, const DevVocab& Vd, int32_t* bitmask_dev, int64_t row_stride_words,
                  const SlowScratch& S, hipStream_t stream);

@@ -688,19 +688,140 @@ __global__ __launch_bounds__(256) void k_finish_planes(uint32_t* const* plane_pt
     }
 }
 
+// ---- one token, one wavefront -----------------------------------------------------------------------
+__device__ __forceinline__ uint32_t lane_value(uint32_t v, uint32_t k) { return (uint32_t)__builtin_amdgcn_readlane((int)v, (int)k); }
+// A value that is the same in all lanes, as the compiler cannot know where it came from memory.
+__device__ __forceinline__ uint32_t same_in_all(uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); }
+// A load whose address is the same in all lanes, from memory that no kernel writes while this one runs: the scalar cache
+// serves it, and the compiler knows that the value is uniform.
+template <class P>
+__device__ __forceinline__ P uniform_load(const P* p) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    return *(const __attribute__((address_space(4))) P*)p;
+#else
+    return *p;
+#endif
+}
+__device__ __forceinline__ uint32_t next_bit(unsigned long long& m) { const uint32_t j = (uint32_t)__ffsll((long long)m) - 1; m &= m - 1; return j; }
+
+// The Earley steps of earley_core.hpp with one wavefront per token: lane k holds item k of the set at hand together with the
+// state it goes to on the next byte (looked up when the item is entered: it is the lookahead and the next scanner step in
+// one).  Control flow is the same in all lanes; values picked out of a lane are wave-uniform.
+struct WaveScan {
+    static constexpr uint32_t N = 64;
+    const DevTables T;
+    const uint2* ctx_wait; const uint32_t* ctx_off; const uint32_t H;   // LDS: wait entries of the context's H sets, and where each set's start
+    const uint2* own_wait; const uint32_t* own_off;                     // LDS: the same for the sets made during the token (numbered from H)
+    const uint32_t lane;
+    const uint32_t max_items;                     // at most N: more is an overflow
+    uint32_t item, to;                            // the set under construction: lane k < n holds item k, and where it goes on the next byte
+    uint32_t n;
+    uint32_t w_rule, w_tgt, n_w;                  // its wait entries so far: lane k < n_w holds entry k
+    uint32_t set_idx, la;                         // its number; class of the next byte, or NO_TARGET after the last one
+    bool full, root_done;
+
+    __device__ __forceinline__ bool add(uint32_t v, uint32_t v_to) {
+        if (__ballot(lane < n && item == v)) return false;
+        if (n == max_items) { full = true; return false; }
+        if (lane == n) { item = v; to = v_to; }
+        ++n;
+        return true;
+    }
+    __device__ __forceinline__ void add_wait(uint32_t rule, uint32_t tgt) {
+        if (__ballot(lane < n_w && w_tgt == tgt && w_rule == rule)) return;
+        if (n_w == N) { full = true; return; }
+        if (lane == n_w) { w_rule = rule; w_tgt = tgt; }
+        ++n_w;
+    }
+    // where a state goes on the next byte (a gather over the lanes that ask)
+    __device__ __forceinline__ uint32_t next_of(bool mine, uint32_t ref) const {
+        uint32_t t = NO_TARGET;
+        if (mine && (ref & F_BYTE) && la != NO_TARGET) t = tab(T.trans + (ref & SID_MASK) * T.n_classes + la);
+        return t;
+    }
+    // byte edges only, not final, and none of them for the next byte: the item can do nothing
+    __device__ __forceinline__ bool is_inert(uint32_t ref, uint32_t t) const { return (ref & (F_BYTE | F_REF | F_FINAL)) == F_BYTE && t == T.sink; }
+    __device__ __forceinline__ void expand(uint32_t ref, uint32_t origin) {
+        const uint4 d = uniform_load(T.state + (ref & SID_MASK));
+        const uint32_t* e = T.exp_list + d.y;
+        const uint32_t* e2 = e + d.z;
+        const uint32_t most = d.z > d.w ? d.z : d.w;
+        for (uint32_t base = 0; base < most; base += N) {
+            const bool has_item = base + lane < d.z, has_wait = base + lane < d.w;
+            uint32_t w = 0, rule = 0, tgt = 0;
+            if (has_item) w = tab(e + base + lane);
+            if (has_wait) { rule = tab(e2 + 2 * (base + lane)); tgt = tab(e2 + 2 * (base + lane) + 1); }
+            const uint32_t t = next_of(has_item, w);
+            for (unsigned long long m = __ballot(has_item && !is_inert(w, t)); m;) {
+                const uint32_t j = next_bit(m), v = lane_value(w, j);
+                add((v & REF_MASK) | (((v & EXP_CURRENT) ? set_idx : origin) << REF_BITS), lane_value(t, j));
+            }
+            for (unsigned long long m = __ballot(has_wait); m;) {
+                const uint32_t j = next_bit(m), v = lane_value(tgt, j);
+                add_wait(lane_value(rule, j), (v & REF_MASK) | (((v & EXP_CURRENT) ? set_idx : origin) << REF_BITS));
+            }
+        }
+    }
+    // the lanes of m each enter the state `ref` with their origin
+    __device__ __forceinline__ void enter(unsigned long long m, uint32_t ref, uint32_t origin) {
+        const uint32_t t = next_of((m >> lane) & 1, ref);
+        m &= ~__ballot(is_inert(ref, t));
+        while (m) {
+            const uint32_t j = next_bit(m), r = lane_value(ref, j), o = lane_value(origin, j);
+            if ((r & (F_BYTE | F_FINAL)) || !(r & F_REF)) { if (!add(r | (o << REF_BITS), lane_value(t, j))) continue; }
+            if (r & F_REF) expand(r, o);
+        }
+    }
+    // One byte: scanner and completer over the set held in (cur_item, cur_to, cur_n).  False: nothing survives.
+    __device__ __forceinline__ bool step(uint32_t cur_item, uint32_t cur_to, uint32_t cur_n) {
+        n = 0; n_w = 0; root_done = false;
+        enter(__ballot(lane < cur_n && (cur_item & F_BYTE) && cur_to != T.sink), cur_to, cur_item >> REF_BITS);
+        unsigned long long done = 0;
+        for (;;) {
+            unsigned long long m = __ballot(lane < n && (item & F_FINAL) && (item >> REF_BITS) != set_idx) & ~done;
+            if (!m) break;
+            done |= m;
+            uint32_t rule_of = 0;
+            if (((m >> lane) & 1) && (item >> REF_BITS) != ROOT_ORIGIN) rule_of = tab(&T.state[item & SID_MASK].x);
+            const uint32_t held = item;                             // entering below only appends
+            while (m) {
+                const uint32_t j = next_bit(m), o = lane_value(held, j) >> REF_BITS;
+                if (o == ROOT_ORIGIN) { root_done = true; continue; }
+                const bool own = o >= H;
+                const uint2* wait = own ? own_wait : ctx_wait;
+                const uint32_t* off = own ? own_off + (o - H) : ctx_off + o;
+                const uint32_t rule = lane_value(rule_of, j), lo = same_in_all(off[0]), hi = same_in_all(off[1]);
+                for (uint32_t base = lo; base < hi; base += N) {
+                    uint2 w = make_uint2(0, 0);
+                    if (base + lane < hi) w = wait[base + lane];
+                    const unsigned long long hit = __ballot(base + lane < hi && w.x == rule);
+                    if (hit) enter(hit, w.y & REF_MASK, w.y >> REF_BITS);
+                }
+            }
+        }
+        return n != 0 || n_w != 0;
+    }
+};
+
 // ---- fill ------------------------------------------------------------------------------------------
 // k_fill: one workgroup per row, in two teams of wavefronts that work side by side.
 //   The union team streams: per mask word the OR of the accepted rows of the row's frontier planes, plus the
 //   end-of-sequence bit, stored with 16-byte accesses.
 //   The re-check team takes the uncertain tokens of the frontier planes from the short list every plane carries behind
-//   its three rows (written by k_plane_summary), one token per lane, and runs the Earley routine from the row's full
-//   context; what survives is kept in LDS until the union is stored, and OR-ed in afterwards.
+//   its three rows (written by k_plane_summary) and runs the Earley routine from the row's full context; what survives
+//   is kept in LDS until the union is stored, and OR-ed in afterwards.
 // The two teams need nothing from each other until that point, so the latency of the re-check (a chain of dependent
 // table loads) hides behind the streaming and the other way round.  A token that another frontier plane accepts is in
-// the mask anyway and is not parsed: its lane looks the bit up in the accepted rows itself and does not wait for the union.
+// the mask anyway and is not parsed: its bit is looked up in the accepted rows, without waiting for the union.
+// Most rows have no candidate and a few have a handful, but the launch lasts as long as its slowest row.  A row with few
+// candidates (FILL_WAVE_TOKENS) gives each a wavefront (WaveScan: a byte costs about one gather, where a lane of its own
+// takes several dependent accesses), the union team joining in when it is done; a row with more gives each a lane.
 // A row with a frontier plane whose uncertain tokens do not fit its list (or with more candidates than the LDS list
 // holds) takes the sequential way: the union team also reads the uncertain rows and lists the words with candidates,
 // the re-check team starts when the union is done.
+// A token that outgrows the short lists (or 16 bytes) is tried by a wavefront, then with lists in device memory, by the
+// row's own workgroup (own_lanes): a second launch for the few such tokens cost 2.5 - 4 us on every call.  Where they are
+// many (a grammar with wide expansions, see launch_fill's caller) they are left to k_recheck_slow.
 // Four wavefronts stream, two re-check with half of their lanes at work (measured: fewer lanes per wavefront, more
 // wavefronts or another split of the six gain nothing; a larger workgroup lowers the number of rows a compute unit holds).
 constexpr int FILL_OR_WAVES = 4, FILL_RECHECK_WAVES = 2;
@@ -711,7 +832,9 @@ constexpr int FILL_THREADS = 64 * (FILL_OR_WAVES + FILL_RECHECK_WAVES);
 constexpr int FILL_BLOCK = 5;                          // steps of the union whose loads are issued together
 constexpr int FILL_K = 8, FILL_WM = 12;
 constexpr uint32_t FILL_SPARSE_CAP = 512;              // candidates of a row that the side-by-side way handles
-constexpr uint32_t FILL_NONE = 0xFFFFFFFFu;
+constexpr uint32_t FILL_NONE = 0xFFFFFFFFu, FILL_OVER = 0x80000000u;   // what became of a candidate: rejected; did not fit the lists tried
+constexpr uint32_t FILL_WAVE_TOKENS = 24;              // up to that many candidates get a wavefront each (six at a time, ~3 us each; a lane each: ~12 us for any number)
+constexpr uint32_t FILL_CTX_WAITS = 128, FILL_CTX_SETS = 64, FILL_OWN_WAITS = 128, FILL_WAVE_BYTES = 64;   // what a wavefront's parse has room for
 using FillStore = LdsStore<FILL_K, FILL_WM, FILL_COLS>;
 
 __device__ __forceinline__ DevCtx row_ctx(const FillBatch& F, const FillRow& r) {
@@ -742,19 +865,87 @@ __device__ __forceinline__ void list_candidates(const FillBatch& F, uint32_t* n_
     }
 }
 
-// One candidate token of row b against the row's full context.  A token the short lists cannot decide goes to the
-// large-capacity list and counts as rejected here.
-__device__ __forceinline__ bool recheck_token(const DevVocab& Vd, const SlowScratch& S, const DevTables& T, const uint32_t* cls_words, const DevCtx& C,
-                                              uint32_t b, uint32_t id, FillStore& st) {
+constexpr int RECHECK_NO = 0, RECHECK_YES = 1, RECHECK_OVER = 2;
+// One candidate token, one lane, against the row's full context.
+__device__ __forceinline__ int recheck_lane(const DevVocab& Vd, const DevTables& T, const uint32_t* cls_words, const DevCtx& C, uint32_t id, FillStore& st) {
     const uint32_t rank = Vd.rank[id];
-    if (rank >= Vd.n_sorted) return false;
+    if (rank >= Vd.n_sorted) return RECHECK_NO;
     const int n = (int)(Vd.off[rank + 1] - Vd.off[rank]);
     RegBytes tok;
     tok.v = Vd.tok16[rank];
     st.reset();
     const int res = scan_token(T, cls_words, C, tok, n, st);
-    if (res & RES_OVERFLOW) { push_overflow(S, b, id); return false; }
-    return (res & RES_ALIVE) != 0;
+    return (res & RES_OVERFLOW) ? RECHECK_OVER : (res & RES_ALIVE) ? RECHECK_YES : RECHECK_NO;
+}
+
+// A row's context in LDS for the wavefronts that parse from it, and each wavefront's room for what its token adds.
+struct FillCtx { uint2 wait[FILL_CTX_WAITS]; uint32_t off[FILL_CTX_SETS + 1]; uint32_t cls_words[64]; };
+struct FillOwn { uint2 wait[FILL_OWN_WAITS]; uint32_t off[FILL_WAVE_BYTES + 1]; };
+__device__ __forceinline__ void wave_sync() {                       // orders a wavefront's LDS traffic (which completes in order) for the compiler
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+// One candidate token (the same in all lanes), one wavefront.  *large: it would not have fitted the short lists of a lane.
+__device__ __forceinline__ int recheck_wave(const DevVocab& Vd, const SlowScratch& S, const DevTables& T, const FillCtx& X, FillOwn& own, uint32_t H, uint32_t item_n, uint32_t my_item,
+                                            uint32_t id, uint32_t lane, bool* large) {
+    const uint32_t rank = uniform_load(Vd.rank + id);
+    if (rank >= Vd.n_sorted) return RECHECK_NO;
+    const uint32_t at = uniform_load(Vd.off + rank), n_bytes = uniform_load(Vd.off + rank + 1) - at;
+    const uint4 tok16 = uniform_load(Vd.tok16 + rank);
+    if (n_bytes > FILL_WAVE_BYTES) return RECHECK_OVER;
+    const uint32_t words[4] = {tok16.x, tok16.y, tok16.z, tok16.w};
+    uint32_t byte = (words[(lane >> 2) & 3] >> (8 * (lane & 3))) & 0xFF;
+    if (n_bytes > 16) byte = lane < n_bytes ? tab(Vd.bytes + at + lane) : 0u;
+    const uint32_t cls_of = reinterpret_cast<const uint8_t*>(X.cls_words)[byte];
+    const uint32_t max_items = S.k_cap < WaveScan::N ? S.k_cap : WaveScan::N, max_waits = S.wm_cap < FILL_OWN_WAITS ? S.wm_cap : FILL_OWN_WAITS;
+    WaveScan A{T, X.wait, X.off, H, own.wait, own.off, lane, max_items, 0, 0, 0, 0, 0, 0, 0, 0, false, false};
+    if (item_n > max_items) return RECHECK_OVER;
+    A.la = lane_value(cls_of, 0);
+    uint32_t cur = my_item, cur_n = item_n, cur_to = A.next_of(lane < cur_n, cur), n_own = 0, most = item_n;
+    if (lane == 0) own.off[0] = 0;
+    for (uint32_t i = 0; i < n_bytes; ++i) {
+        A.set_idx = H + i;
+        A.la = i + 1 < n_bytes ? lane_value(cls_of, i + 1) : NO_TARGET;
+        wave_sync();
+        const bool alive = A.step(cur, cur_to, cur_n);
+        if (A.full) return RECHECK_OVER;
+        if (!alive) return RECHECK_NO;
+        if (n_own + A.n_w > max_waits) return RECHECK_OVER;
+        wave_sync();
+        if (lane < A.n_w) own.wait[n_own + lane] = make_uint2(A.w_rule, A.w_tgt);
+        n_own += A.n_w;
+        if (lane == 0) own.off[i + 1] = n_own;
+        cur = A.item; cur_to = A.to; cur_n = A.n;
+        if (cur_n > most) most = cur_n;
+    }
+    *large = most > (uint32_t)FILL_K || n_own > (uint32_t)FILL_WM || n_bytes > 16;
+    return RECHECK_YES;
+}
+
+// One (row, token) pair that outgrew every shorter list: one lane, item lists in device memory (lane gl of the scratch).  A
+// pair that even these cannot decide keeps its bit 0, and the call must not pass for complete: the pair goes to the host's
+// list (it can decide it with its own parser), a slot on the device is marked unusable.
+__device__ __forceinline__ bool recheck_large(const FillBatch& F, const DevVocab& Vd, const SlowScratch& S, const FillRow& r, uint32_t b, uint32_t id, uint32_t gl) {
+    const uint32_t rank = Vd.rank[id];
+    if (rank >= Vd.n_sorted) return false;
+    const uint32_t off = Vd.off[rank];
+    const int n = (int)(Vd.off[rank + 1] - off);
+    const DevTables T = F.tables[r.tables_idx];
+    MemBytes tok{Vd.bytes + off};
+    GlobalStore st;
+    st.init(S.mem + gl, S.n_lanes, S.k_cap, S.wm_cap);
+    st.reset();
+    const int res = scan_token<GlobalStore, false, MemBytes>(T, T.byte_class_words, row_ctx(F, r), tok, n, st);
+    if (!(res & RES_OVERFLOW)) return (res & RES_ALIVE) != 0;
+    atomicOr(S.count + 1, 2u);
+    if (S.mark_rows) S.mark_rows[b].pad[1] = 2u;
+    if (S.unresolved) {                                              // plain stores only: the list is host memory
+        const uint32_t at = atomicAdd(S.count + 2, 1u);
+        S.unresolved[0] = 1u;
+        if (at < S.unresolved_cap) { S.unresolved[2 + 2 * at] = b; S.unresolved[3 + 2 * at] = id; }
+        else S.unresolved[1] = 1u;
+    }
+    return false;
 }
 
 // Entry with the smallest index whose inclusive prefix sum exceeds t (every lane of the wave calls this; incl is the
@@ -770,19 +961,82 @@ __device__ __forceinline__ uint32_t prefix_owner(uint32_t incl, uint32_t t) {
     return lo;
 }
 
-// A thread of the union team handles WORDS consecutive mask words per step (4: 16-byte loads and stores, needs
-// W % 4 == 0 and a 16-byte aligned bitmask row; 1: any layout).
-template <int WORDS>
-__global__ __launch_bounds__(FILL_THREADS) void k_fill(FillBatch F, DevVocab Vd, int32_t* bitmask, long long row_stride, SlowScratch S) {
+// Four consecutive mask words from a word boundary (a row of any W, at any word address); words at or beyond W read as 0 and
+// are not written.
+typedef uint32_t Words4 __attribute__((ext_vector_type(4), aligned(4)));
+__device__ __forceinline__ void load4(const uint32_t* row, uint32_t w, uint32_t W, uint32_t (&v)[4]) {
+    if (w + 4 <= W) {
+        const Words4 x = *(const __attribute__((address_space(1))) Words4*)(row + w);
+        v[0] = x.x; v[1] = x.y; v[2] = x.z; v[3] = x.w;
+    } else {
+        _Pragma("unroll") for (uint32_t c = 0; c < 4; ++c) v[c] = w + c < W ? tab(row + w + c) : 0u;
+    }
+}
+__device__ __forceinline__ void store4(uint32_t* row, uint32_t w, uint32_t W, const uint32_t (&v)[4]) {
+    if (w + 4 <= W) {
+        Words4 x; x.x = v[0]; x.y = v[1]; x.z = v[2]; x.w = v[3];
+        *(__attribute__((address_space(1))) Words4*)(row + w) = x;
+    } else {
+        _Pragma("unroll") for (uint32_t c = 0; c < 4; ++c) if (w + c < W) row[w + c] = v[c];
+    }
+}
+
+// The union of a row: BLOCK steps at a time, first every load of the block (plane after plane, so that a thread has several
+// independent loads in flight), then the stores.  UNC: also the uncertain rows, whose tokens that no plane accepts are listed.
+template <int BLOCK, bool UNC>
+__device__ __forceinline__ void fill_union(const FillBatch& F, uint32_t W, uint32_t b, uint32_t front_off, uint32_t front_n, bool live, bool eos, uint32_t* out, uint32_t* n_listed, uint32_t* n_cand) {
+    const uint32_t eos_word = F.eos_id >> 5, eos_bit = 1u << (F.eos_id & 31);
+    const uint32_t n_vec = (W + 3) / 4, n_steps = (n_vec + FILL_OR_THREADS - 1) / FILL_OR_THREADS;      // same for every thread: the ballots see whole waves
+    for (uint32_t step0 = 0; step0 < n_steps; step0 += BLOCK) {
+        uint32_t acc[BLOCK][4] = {}, unc[UNC ? BLOCK : 1][4] = {};
+        if (live)
+            for (uint32_t k = 0; k < front_n; ++k) {
+                const uint64_t pa = uniform_load(F.front_planes + front_off + k);
+                const uint32_t* row = reinterpret_cast<const uint32_t*>(pa & ~(uint64_t)1);
+#pragma unroll
+                for (int s = 0; s < BLOCK; ++s) {
+                    const uint32_t v = (step0 + s) * FILL_OR_THREADS + threadIdx.x;
+                    if (v >= n_vec) continue;
+                    uint32_t x[4];
+                    load4(row, 4 * v, W, x);
+                    _Pragma("unroll") for (int c = 0; c < 4; ++c) acc[s][c] |= x[c];
+                    if (UNC && !(pa & 1)) {
+                        load4(row + W, 4 * v, W, x);
+                        _Pragma("unroll") for (int c = 0; c < 4; ++c) unc[s][c] |= x[c];
+                    }
+                }
+            }
+#pragma unroll
+        for (int s = 0; s < BLOCK; ++s) {
+            if (step0 + s >= n_steps) break;                        // same for every thread
+            const uint32_t v = (step0 + s) * FILL_OR_THREADS + threadIdx.x;
+            if (UNC) {
+                uint32_t cand[4], any = 0;
+                _Pragma("unroll") for (int c = 0; c < 4; ++c) { cand[c] = v < n_vec ? (unc[s][c] & ~acc[s][c]) : 0u; any |= cand[c]; }
+                if (__any(any != 0))                                // candidates are few: most wavefronts have none
+                    _Pragma("unroll") for (int c = 0; c < 4; ++c) list_candidates(F, n_listed, n_cand, cand[c], b * W, v * 4 + c);
+            }
+            if (eos && eos_word / 4 == v) {
+                _Pragma("unroll") for (int c = 0; c < 4; ++c) if (eos_word % 4 == (uint32_t)c) acc[s][c] |= eos_bit;
+            }
+            if (v < n_vec) store4(out, 4 * v, W, acc[s]);
+        }
+    }
+}
+
+// Six wavefronts a SIMD at least: a compute unit then holds four rows, i.e. the device 1,024 at once.
+__global__ __launch_bounds__(FILL_THREADS) __attribute__((amdgpu_waves_per_eu(6))) void k_fill(FillBatch F, DevVocab Vd, int32_t* bitmask, long long row_stride, SlowScratch S) {
     __shared__ uint32_t lds_store[FillStore::SLOTS * FILL_COLS];
     __shared__ uint32_t sh_surv[FILL_SPARSE_CAP];
-    __shared__ uint32_t sh_cls[FILL_RECHECK_WAVES][64];               // byte classes of the row's grammar, a copy per wavefront of the re-check team
-    __shared__ uint32_t n_listed, n_cand;
-    const uint32_t b = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const FillRow r = F.rows[b];
+    __shared__ FillCtx ctx;
+    __shared__ FillOwn sh_own[FILL_THREADS / 64];
+    __shared__ uint32_t n_listed, n_cand, n_over, next_token;
+    const uint32_t b = blockIdx.x, lane = threadIdx.x & 63, wave = same_in_all(threadIdx.x >> 6);
+    const FillRow r = uniform_load(F.rows + b);
     const uint32_t front_off = r.front_off, front_n = r.front_n, flags = r.flags;
     const bool live = !(flags & 2u);
-    if (threadIdx.x == 0) { n_listed = 0; n_cand = 0; }
+    if (threadIdx.x == 0) { n_listed = 0; n_cand = 0; n_over = 0; next_token = 0; }
+    if (F.zero_words && b == 0 && threadIdx.x < 4) F.zero_words[threadIdx.x] = 0;      // the words the next call counts in
     // the plan, worked out by every wavefront for itself: lane k looks at frontier plane k
     uint64_t addr = 1;
     uint32_t n_unc = 0;
@@ -791,10 +1045,32 @@ __global__ __launch_bounds__(FILL_THREADS) void k_fill(FillBatch F, DevVocab Vd,
         if (!(addr & 1)) n_unc = tab(reinterpret_cast<const uint32_t*>(addr) + 3 * (size_t)Vd.W);
     }
     const bool no_list = n_unc > kUncListWords - 1;                   // more uncertain tokens than the plane's list holds
-    uint32_t incl = no_list ? 0u : n_unc;
-    for (int d = 1; d < 64; d <<= 1) { const uint32_t up = (uint32_t)__shfl_up((int)incl, d); if ((int)lane >= d) incl += up; }
-    const uint32_t total = (uint32_t)__shfl((int)incl, 63);
+    uint32_t incl = no_list ? 0u : n_unc, total = 0;
+    const bool some_list = __any(incl != 0);
+    if (some_list) {
+        for (int d = 1; d < 64; d <<= 1) { const uint32_t up = (uint32_t)__shfl_up((int)incl, d); if ((int)lane >= d) incl += up; }
+        total = lane_value(incl, 63);
+    }
     const bool listed_way = live && front_n != 0 && (front_n > 64 || __any(no_list) || total > FILL_SPARSE_CAP);
+    const bool parses = listed_way || total != 0;
+    // whether wavefronts can parse from this row's context, and then the context in LDS
+    bool ctx_fits = false;
+    uint32_t n_wait = 0, my_item = 0;
+    if (parses && F.own_lanes && r.item_n <= WaveScan::N && r.H <= FILL_CTX_SETS) {
+        n_wait = uniform_load(F.ctx_wait_off + r.waitoff_off + r.H);
+        ctx_fits = n_wait <= FILL_CTX_WAITS;
+        if (ctx_fits) {
+            if (lane < r.item_n) my_item = tab(F.ctx_items + r.item_off + lane);
+            if (wave >= FILL_OR_WAVES) {
+                const uint32_t t = threadIdx.x - FILL_OR_THREADS;
+                if (t < n_wait) ctx.wait[t] = tab(F.ctx_wait + r.wait_base + t);
+                if (t <= r.H) ctx.off[t] = tab(F.ctx_wait_off + r.waitoff_off + t);
+            }
+        }
+    }
+    static_assert(64 * FILL_RECHECK_WAVES >= FILL_CTX_WAITS && 64 * FILL_RECHECK_WAVES > FILL_CTX_SETS, "the re-check team copies a context in one step");
+    const bool wave_way = ctx_fits && !listed_way && total <= FILL_WAVE_TOKENS;
+    if (parses && wave == FILL_OR_WAVES) ctx.cls_words[lane] = tab(uniform_load(&F.tables[r.tables_idx].byte_class_words) + lane);
     uint32_t* out = reinterpret_cast<uint32_t*>(bitmask) + (long long)b * row_stride;
     FillStore st;
     const uint32_t col = (wave - FILL_OR_WAVES) * FILL_RECHECK_LANES + lane;      // re-check team: this lane's place among the lanes at work
@@ -803,66 +1079,12 @@ __global__ __launch_bounds__(FILL_THREADS) void k_fill(FillBatch F, DevVocab Vd,
     __syncthreads();
 
     if (wave < FILL_OR_WAVES) {
-        const uint32_t eos_word = F.eos_id >> 5, eos_bit = 1u << (F.eos_id & 31);
-        const uint32_t n_steps = (Vd.W / WORDS + FILL_OR_THREADS - 1) / FILL_OR_THREADS;   // same for every thread: the ballots see whole waves
-        // FILL_BLOCK steps at a time: first every load of the block (plane after plane, so that a thread has several
-        // independent loads in flight), then the candidates and the stores
-        for (uint32_t step0 = 0; step0 < n_steps; step0 += FILL_BLOCK) {
-            uint32_t acc[FILL_BLOCK][WORDS], unc[FILL_BLOCK][WORDS];
-#pragma unroll
-            for (int s = 0; s < FILL_BLOCK; ++s)
-#pragma unroll
-                for (int c = 0; c < WORDS; ++c) { acc[s][c] = 0; unc[s][c] = 0; }
-            if (live)
-                for (uint32_t k = 0; k < front_n; ++k) {
-                    const uint64_t pa = F.front_planes[front_off + k];
-                    const uint32_t* row = reinterpret_cast<const uint32_t*>(pa & ~(uint64_t)1);
-                    const bool with_unc = listed_way && !(pa & 1);
-#pragma unroll
-                    for (int s = 0; s < FILL_BLOCK; ++s) {
-                        const uint32_t v = (step0 + s) * FILL_OR_THREADS + threadIdx.x;
-                        if (v >= Vd.W / WORDS) continue;
-                        if (WORDS == 4) {
-                            const uint4 a = tab(reinterpret_cast<const uint4*>(row) + v);
-                            acc[s][0] |= a.x; acc[s][1 % WORDS] |= a.y; acc[s][2 % WORDS] |= a.z; acc[s][3 % WORDS] |= a.w;
-                            if (with_unc) {
-                                const uint4 u = tab(reinterpret_cast<const uint4*>(row + Vd.W) + v);
-                                unc[s][0] |= u.x; unc[s][1 % WORDS] |= u.y; unc[s][2 % WORDS] |= u.z; unc[s][3 % WORDS] |= u.w;
-                            }
-                        } else {
-                            acc[s][0] |= tab(row + v);
-                            if (with_unc) unc[s][0] |= tab(row + Vd.W + v);
-                        }
-                    }
-                }
-#pragma unroll
-            for (int s = 0; s < FILL_BLOCK; ++s) {
-                if (step0 + s >= n_steps) break;                        // same for every thread
-                const uint32_t v = (step0 + s) * FILL_OR_THREADS + threadIdx.x;
-                const bool in_row = v < Vd.W / WORDS;
-                uint32_t cand[WORDS], any = 0;
-#pragma unroll
-                for (int c = 0; c < WORDS; ++c) {
-                    cand[c] = in_row ? (unc[s][c] & ~acc[s][c]) : 0u;
-                    any |= cand[c];
-                    if ((flags & 3u) && eos_word == v * WORDS + c) acc[s][c] |= eos_bit;
-                }
-                if (listed_way && __any(any != 0)) {                    // candidates are few: most wavefronts have none
-#pragma unroll
-                    for (int c = 0; c < WORDS; ++c) list_candidates(F, &n_listed, &n_cand, cand[c], b * Vd.W, v * WORDS + c);
-                }
-                if (in_row) {
-                    if (WORDS == 4) reinterpret_cast<uint4*>(out)[v] = make_uint4(acc[s][0], acc[s][1 % WORDS], acc[s][2 % WORDS], acc[s][3 % WORDS]);
-                    else out[v] = acc[s][0];
-                }
-            }
-        }
-    } else if (!listed_way && total != 0) {
-        // side by side with the union: candidate t is entry t - (tokens of the planes before) of its plane's list
-        const DevTables T = F.tables[r.tables_idx];
+        if (listed_way) fill_union<2, true>(F, Vd.W, b, front_off, front_n, live, (flags & 3u) != 0, out, &n_listed, &n_cand);
+        else fill_union<FILL_BLOCK, false>(F, Vd.W, b, front_off, front_n, live, (flags & 3u) != 0, out, &n_listed, &n_cand);
+    } else if (!listed_way && total != 0 && !wave_way) {
+        // side by side with the union, a lane per candidate: candidate t is entry t - (tokens of the planes before) of its plane's list
+        const DevTables T = uniform_load(F.tables + r.tables_idx);
         const DevCtx C = row_ctx(F, r);
-        sh_cls[wave - FILL_OR_WAVES][lane] = T.byte_class_words[lane];
-        __builtin_amdgcn_wave_barrier();                              // one wave: its LDS operations complete in order
         for (uint32_t t0 = 0; t0 < total; t0 += FILL_COLS) {
             const uint32_t t = t0 + col;
             const bool mine = at_work && t < total;
@@ -877,7 +1099,49 @@ __global__ __launch_bounds__(FILL_THREADS) void k_fill(FillBatch F, DevVocab Vd,
                 const uint32_t p_lo = (uint32_t)__shfl((int)(uint32_t)addr, (int)k2), p_hi = (uint32_t)__shfl((int)(uint32_t)(addr >> 32), (int)k2);
                 accepted |= tab(reinterpret_cast<const uint32_t*>((((uint64_t)p_hi << 32) | p_lo) & ~(uint64_t)1) + (id >> 5)) >> (id & 31);
             }
-            if (mine) sh_surv[t] = !(accepted & 1u) && recheck_token(Vd, S, T, sh_cls[wave - FILL_OR_WAVES], C, b, id, st) ? id : FILL_NONE;
+            if (mine) {
+                const int res = (accepted & 1u) ? RECHECK_NO : recheck_lane(Vd, T, ctx.cls_words, C, id, st);
+                sh_surv[t] = res == RECHECK_YES ? id : res == RECHECK_OVER ? (id | FILL_OVER) : FILL_NONE;
+                if (res == RECHECK_OVER) atomicAdd(&n_over, 1u);
+            }
+        }
+    }
+    bool waves_parse = wave_way && total != 0;
+    if (!listed_way && total != 0 && !wave_way) {                   // (the same for the whole row)
+        __syncthreads();
+        waves_parse = ctx_fits && n_over != 0;
+    }
+    if (waves_parse) {
+        // a wavefront per candidate, the union team joining in when its row is stored; or per token that did not fit a lane's lists
+        const DevTables T = uniform_load(F.tables + r.tables_idx);
+        for (;;) {
+            // The wavefront stays together from token to token: with nothing between "lane 0 stores a result" below and "lane 0
+            // takes the next token" here the compiler may send the other lanes round the loop without lane 0.
+            wave_sync();
+            uint32_t t = 0;
+            if (lane == 0) t = atomicAdd(&next_token, 1u);
+            wave_sync();
+            t = same_in_all(t);
+            if (t >= total) break;
+            uint32_t id;
+            bool accepts = false;
+            if (wave_way) {
+                const uint32_t k = (uint32_t)__ffsll((long long)__ballot(incl > t)) - 1;
+                const uint64_t a_k = ((uint64_t)lane_value((uint32_t)(addr >> 32), k) << 32) | lane_value((uint32_t)addr, k);
+                id = uniform_load(reinterpret_cast<const uint32_t*>(a_k) + 3 * (size_t)Vd.W + 1 + (t - (lane_value(incl, k) - lane_value(n_unc, k))));
+                if (lane < front_n) accepts = (tab(reinterpret_cast<const uint32_t*>(addr & ~(uint64_t)1) + (id >> 5)) >> (id & 31)) & 1u;
+            } else {
+                const uint32_t v = same_in_all(sh_surv[t]);
+                if (v == FILL_NONE || !(v & FILL_OVER)) continue;
+                id = v & ~FILL_OVER;
+            }
+            bool large = !wave_way;
+            const int res = __any(accepts) ? RECHECK_NO : recheck_wave(Vd, S, T, ctx, sh_own[wave], r.H, r.item_n, my_item, id, lane, &large);
+            if (lane == 0) {
+                sh_surv[t] = res == RECHECK_YES ? id : res == RECHECK_OVER ? (id | FILL_OVER) : FILL_NONE;
+                if (large && res != RECHECK_OVER) atomicAdd(S.count, 1u);
+                if (res == RECHECK_OVER && wave_way) atomicAdd(&n_over, 1u);
+            }
         }
     }
     __syncthreads();
@@ -885,9 +1149,19 @@ __global__ __launch_bounds__(FILL_THREADS) void k_fill(FillBatch F, DevVocab Vd,
     if (!listed_way) {
         for (uint32_t t = threadIdx.x; t < total; t += FILL_THREADS) {
             const uint32_t id = sh_surv[t];
-            if (id != FILL_NONE) atomicOr(out + (id >> 5), 1u << (id & 31));
+            if (id == FILL_NONE) continue;
+            if (!(id & FILL_OVER)) atomicOr(out + (id >> 5), 1u << (id & 31));
+            else if (!F.own_lanes) push_overflow(S, b, id & ~FILL_OVER);
         }
         if (threadIdx.x == 0) F.row_count[b] = total;                   // every row writes its count: nothing to clear beforehand
+        // what did not fit there either: one lane of every wavefront that has a lane of the large-capacity scratch
+        if (n_over != 0 && lane == 0 && wave < F.own_lanes)
+            for (uint32_t t = wave; t < total; t += F.own_lanes) {
+                const uint32_t id = sh_surv[t];
+                if (id == FILL_NONE || !(id & FILL_OVER)) continue;
+                atomicAdd(S.count, 1u);
+                if (recheck_large(F, Vd, S, r, b, id & ~FILL_OVER, b * F.own_lanes + wave)) atomicOr(out + ((id & ~FILL_OVER) >> 5), 1u << (id & 31));
+            }
         return;
     }
     if (threadIdx.x == 0) F.row_count[b] = n_cand;
@@ -897,26 +1171,36 @@ __global__ __launch_bounds__(FILL_THREADS) void k_fill(FillBatch F, DevVocab Vd,
     const uint32_t count = n_listed;
     const uint32_t* wlist = F.work_list + b * Vd.W;
     const uint32_t* cands = F.cand_words + b * Vd.W;
-    const DevTables T = F.tables[r.tables_idx];
+    const DevTables T = uniform_load(F.tables + r.tables_idx);
     const DevCtx C = row_ctx(F, r);
-    sh_cls[wave - FILL_OR_WAVES][lane] = T.byte_class_words[lane];
-    __builtin_amdgcn_wave_barrier();
     for (uint32_t base = (wave - FILL_OR_WAVES) * FILL_RECHECK_LANES; base < count; base += FILL_COLS) {
         uint32_t idx = 0, cand = 0;
         if (lane < FILL_RECHECK_LANES && base + lane < count) { idx = wlist[base + lane]; cand = cands[idx]; }
         uint32_t pre = (uint32_t)__popc(cand);
         for (int d = 1; d < 64; d <<= 1) { const uint32_t up = (uint32_t)__shfl_up((int)pre, d); if ((int)lane >= d) pre += up; }
-        const uint32_t n_tok = (uint32_t)__shfl((int)pre, 63);
+        const uint32_t n_tok = lane_value(pre, 63);
         for (uint32_t t0 = 0; t0 < n_tok; t0 += FILL_RECHECK_LANES) {
             const uint32_t my = t0 + lane;
             const uint32_t j = prefix_owner(pre, my);
             uint32_t c = (uint32_t)__shfl((int)cand, (int)j);
             const uint32_t end_j = (uint32_t)__shfl((int)pre, (int)j), w = (uint32_t)__shfl((int)idx, (int)j);
+            bool over = false;
+            uint32_t id = 0;
             if (lane < FILL_RECHECK_LANES && my < n_tok) {
                 uint32_t skip = my - (end_j - (uint32_t)__popc(c));
                 while (skip--) c &= c - 1;                             // drop the lowest set bits that other lanes take
-                const uint32_t bit = __ffs(c) - 1;
-                if (recheck_token(Vd, S, T, sh_cls[wave - FILL_OR_WAVES], C, b, w * 32 + bit, st)) atomicOr(out + w, 1u << bit);
+                id = w * 32 + (uint32_t)__ffs(c) - 1;
+                const int res = recheck_lane(Vd, T, ctx.cls_words, C, id, st);
+                if (res == RECHECK_YES) atomicOr(out + w, 1u << (id & 31));
+                over = res == RECHECK_OVER;
+            }
+            if (!F.own_lanes) { if (over) push_overflow(S, b, id); continue; }
+            for (unsigned long long m = __ballot(over); m;) {
+                const uint32_t id2 = lane_value(id, next_bit(m));
+                if (lane == 0) {
+                    atomicAdd(S.count, 1u);
+                    if (recheck_large(F, Vd, S, r, b, id2, b * F.own_lanes + (wave - FILL_OR_WAVES))) atomicOr(out + (id2 >> 5), 1u << (id2 & 31));
+                }
             }
         }
     }
@@ -925,13 +1209,10 @@ __global__ __launch_bounds__(FILL_THREADS) void k_fill(FillBatch F, DevVocab Vd,
 __global__ __launch_bounds__(64) void k_recheck_slow(FillBatch F, DevVocab Vd, int32_t* bitmask, long long row_stride, SlowScratch S) {
     __shared__ uint32_t lds[MidStore::SLOTS * 64];
     const uint32_t gl = blockIdx.x * 64 + threadIdx.x;
-    if (F.zero_words && gl < 4) F.zero_words[gl] = 0;                   // the words the next call counts in
     uint32_t count = S.count[0];
     if (count > S.list_cap) count = S.list_cap;
     MidStore mid;
     mid.init(lds + threadIdx.x);
-    GlobalStore st;
-    st.init(S.mem + gl, S.n_lanes, S.k_cap, S.wm_cap);
     for (uint32_t idx = gl; idx < count; idx += S.n_lanes) {
         const uint32_t b = S.list[2 * idx], id = S.list[2 * idx + 1];
         const FillRow r = F.rows[b];
@@ -939,34 +1220,23 @@ __global__ __launch_bounds__(64) void k_recheck_slow(FillBatch F, DevVocab Vd, i
         if (rank >= Vd.n_sorted) continue;
         const uint32_t off = Vd.off[rank];
         const int n = (int)(Vd.off[rank + 1] - off);
-        const DevTables T = F.tables[r.tables_idx];
-        MemBytes tok{Vd.bytes + off};
-        mid.reset();
-        int res = S.k_cap >= (uint32_t)MidStore::K ? scan_token<MidStore, false, MemBytes>(T, T.byte_class_words, row_ctx(F, r), tok, n, mid) : RES_OVERFLOW;
-        if (res & RES_OVERFLOW) {
-            st.reset();
-            res = scan_token<GlobalStore, false, MemBytes>(T, T.byte_class_words, row_ctx(F, r), tok, n, st);
+        bool alive;
+        int res = RES_OVERFLOW;
+        if (S.k_cap >= (uint32_t)MidStore::K) {
+            const DevTables T = F.tables[r.tables_idx];
+            MemBytes tok{Vd.bytes + off};
+            mid.reset();
+            res = scan_token<MidStore, false, MemBytes>(T, T.byte_class_words, row_ctx(F, r), tok, n, mid);
         }
-        if (res & RES_OVERFLOW) {
-            // undecided: the bit stays 0, and the call must not pass for complete.  The pair goes to the host's list (it
-            // can decide it with its own parser), a slot on the device is marked unusable.
-            atomicOr(S.count + 1, 2u);
-            if (S.mark_rows) S.mark_rows[b].pad[1] = 2u;
-            if (S.unresolved) {                                      // plain stores only: the list is host memory
-                const uint32_t at = atomicAdd(S.count + 2, 1u);
-                S.unresolved[0] = 1u;
-                if (at < S.unresolved_cap) { S.unresolved[2 + 2 * at] = b; S.unresolved[3 + 2 * at] = id; }
-                else S.unresolved[1] = 1u;
-            }
-            continue;
-        }
-        if (res & RES_ALIVE) atomicOr(reinterpret_cast<uint32_t*>(bitmask) + (long long)b * row_stride + (id >> 5), 1u << (id & 31));
+        if (res & RES_OVERFLOW) alive = recheck_large(F, Vd, S, r, b, id, gl);
+        else alive = (res & RES_ALIVE) != 0;
+        if (alive) atomicOr(reinterpret_cast<uint32_t*>(bitmask) + (long long)b * row_stride + (id >> 5), 1u << (id & 31));
     }
 }
 
 // ---- matchers on the device ------------------------------------------------------------------------
 // k_accept: one wavefront per matcher slot.  The kernel lasts as long as its slowest slot, and a slot is one chain of
-// dependent steps, so the wavefront works on one slot as a whole (WaveAccept below): items, wait entries and expansions lie
+// dependent steps, so the wavefront works on one slot as a whole (WaveScan above): items, wait entries and expansions lie
 // across the lanes, a set's look-ups in the transition table are one gather, a prediction is one load, and what remains in
 // order are list insertions in registers.  (With lane 0 doing everything on lists in LDS the same steps took 16 us at 16 - 64
 // slots and 24 us at 1,024; one lane per slot 458 us.)  A token or context that does not fit across 64 lanes takes the
@@ -1036,115 +1306,6 @@ __global__ __launch_bounds__(256) void k_batch_assign(BatchDev D, const int32_t*
 
 constexpr uint32_t ACC_KI = kSlotItems, ACC_KH = kSlotSets, ACC_KW = kSlotWaits, ACC_KF = kSlotPlanes;     // the slot capacities the LDS staging is laid out for
 
-__device__ __forceinline__ uint32_t lane_value(uint32_t v, uint32_t k) { return (uint32_t)__builtin_amdgcn_readlane((int)v, (int)k); }
-// A value that is the same in all lanes, as the compiler cannot know where it came from memory.
-__device__ __forceinline__ uint32_t same_in_all(uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); }
-// A load whose address is the same in all lanes, from memory that no kernel writes while this one runs: the scalar cache
-// serves it, and the compiler knows that the value is uniform.
-template <class P>
-__device__ __forceinline__ P uniform_load(const P* p) {
-#if defined(__HIP_DEVICE_COMPILE__)
-    return *(const __attribute__((address_space(4))) P*)p;
-#else
-    return *p;
-#endif
-}
-__device__ __forceinline__ uint32_t next_bit(unsigned long long& m) { const uint32_t j = (uint32_t)__ffsll((long long)m) - 1; m &= m - 1; return j; }
-
-// The Earley steps of earley_core.hpp with one wavefront per token: lane k holds item k of the set at hand together with the
-// state it goes to on the next byte (looked up when the item is entered: it is the lookahead and the next scanner step in
-// one).  Control flow is the same in all lanes; values picked out of a lane are wave-uniform.
-struct WaveAccept {
-    static constexpr uint32_t N = 64;
-    const DevTables T;
-    const uint2* wait; const uint32_t* off;       // LDS: wait entries of every set so far, and where each set's start
-    const uint32_t lane;
-    uint32_t item, to;                            // the set under construction: lane k < n holds item k, and where it goes on the next byte
-    uint32_t n;
-    uint32_t w_rule, w_tgt, n_w;                  // its wait entries so far: lane k < n_w holds entry k
-    uint32_t set_idx, la;                         // its number; class of the next byte, or NO_TARGET after the last one
-    bool full, root_done;
-
-    __device__ __forceinline__ bool add(uint32_t v, uint32_t v_to) {
-        if (__ballot(lane < n && item == v)) return false;
-        if (n == N) { full = true; return false; }
-        if (lane == n) { item = v; to = v_to; }
-        ++n;
-        return true;
-    }
-    __device__ __forceinline__ void add_wait(uint32_t rule, uint32_t tgt) {
-        if (__ballot(lane < n_w && w_tgt == tgt && w_rule == rule)) return;
-        if (n_w == N) { full = true; return; }
-        if (lane == n_w) { w_rule = rule; w_tgt = tgt; }
-        ++n_w;
-    }
-    // where a state goes on the next byte (a gather over the lanes that ask)
-    __device__ __forceinline__ uint32_t next_of(bool mine, uint32_t ref) const {
-        uint32_t t = NO_TARGET;
-        if (mine && (ref & F_BYTE) && la != NO_TARGET) t = tab(T.trans + (ref & SID_MASK) * T.n_classes + la);
-        return t;
-    }
-    // byte edges only, not final, and none of them for the next byte: the item can do nothing
-    __device__ __forceinline__ bool is_inert(uint32_t ref, uint32_t t) const { return (ref & (F_BYTE | F_REF | F_FINAL)) == F_BYTE && t == T.sink; }
-    __device__ __forceinline__ void expand(uint32_t ref, uint32_t origin) {
-        const uint4 d = uniform_load(T.state + (ref & SID_MASK));
-        const uint32_t* e = T.exp_list + d.y;
-        const uint32_t* e2 = e + d.z;
-        const uint32_t most = d.z > d.w ? d.z : d.w;
-        for (uint32_t base = 0; base < most; base += N) {
-            const bool has_item = base + lane < d.z, has_wait = base + lane < d.w;
-            uint32_t w = 0, rule = 0, tgt = 0;
-            if (has_item) w = tab(e + base + lane);
-            if (has_wait) { rule = tab(e2 + 2 * (base + lane)); tgt = tab(e2 + 2 * (base + lane) + 1); }
-            const uint32_t t = next_of(has_item, w);
-            for (unsigned long long m = __ballot(has_item && !is_inert(w, t)); m;) {
-                const uint32_t j = next_bit(m), v = lane_value(w, j);
-                add((v & REF_MASK) | (((v & EXP_CURRENT) ? set_idx : origin) << REF_BITS), lane_value(t, j));
-            }
-            for (unsigned long long m = __ballot(has_wait); m;) {
-                const uint32_t j = next_bit(m), v = lane_value(tgt, j);
-                add_wait(lane_value(rule, j), (v & REF_MASK) | (((v & EXP_CURRENT) ? set_idx : origin) << REF_BITS));
-            }
-        }
-    }
-    // the lanes of m each enter the state `ref` with their origin
-    __device__ __forceinline__ void enter(unsigned long long m, uint32_t ref, uint32_t origin) {
-        const uint32_t t = next_of((m >> lane) & 1, ref);
-        m &= ~__ballot(is_inert(ref, t));
-        while (m) {
-            const uint32_t j = next_bit(m), r = lane_value(ref, j), o = lane_value(origin, j);
-            if ((r & (F_BYTE | F_FINAL)) || !(r & F_REF)) { if (!add(r | (o << REF_BITS), lane_value(t, j))) continue; }
-            if (r & F_REF) expand(r, o);
-        }
-    }
-    // One byte: scanner and completer over the set held in (cur_item, cur_to, cur_n).  False: nothing survives.
-    __device__ __forceinline__ bool step(uint32_t cur_item, uint32_t cur_to, uint32_t cur_n) {
-        n = 0; n_w = 0; root_done = false;
-        enter(__ballot(lane < cur_n && (cur_item & F_BYTE) && cur_to != T.sink), cur_to, cur_item >> REF_BITS);
-        unsigned long long done = 0;
-        for (;;) {
-            unsigned long long m = __ballot(lane < n && (item & F_FINAL) && (item >> REF_BITS) != set_idx) & ~done;
-            if (!m) break;
-            done |= m;
-            uint32_t rule_of = 0;
-            if (((m >> lane) & 1) && (item >> REF_BITS) != ROOT_ORIGIN) rule_of = tab(&T.state[item & SID_MASK].x);
-            const uint32_t held = item;                             // entering below only appends
-            while (m) {
-                const uint32_t j = next_bit(m), o = lane_value(held, j) >> REF_BITS;
-                if (o == ROOT_ORIGIN) { root_done = true; continue; }
-                const uint32_t rule = lane_value(rule_of, j), lo = same_in_all(off[o]), hi = same_in_all(off[o + 1]);
-                for (uint32_t base = lo; base < hi; base += N) {
-                    uint2 w = make_uint2(0, 0);
-                    if (base + lane < hi) w = wait[base + lane];
-                    const unsigned long long hit = __ballot(base + lane < hi && w.x == rule);
-                    if (hit) enter(hit, w.y & REF_MASK, w.y >> REF_BITS);
-                }
-            }
-        }
-        return n != 0 || n_w != 0;
-    }
-};
-
 // The slot's next state from token `tok16` (1 .. 16 bytes), written to the slot's other buffer; results in out_n (items, sets,
 // planes, root can end).  ACC_RETRY: something does not fit across the lanes, nothing has been written that counts.
 __device__ __forceinline__ int accept_wave(const BatchDev& D, const CacheDev* Cp, const uint8_t* cls_bytes, uint32_t b, const FillRow& r, size_t slot, uint4 tok16, uint32_t n_bytes,
@@ -1158,7 +1319,7 @@ __device__ __forceinline__ int accept_wave(const BatchDev& D, const CacheDev* Cp
     const uint32_t byte = (words[(lane >> 2) & 3] >> (8 * (lane & 3))) & 0xFF, cls_of = cls_bytes[byte];
     uint32_t n_wait = same_in_all(off[H]);
     if (n_wait > 64) return ACC_RETRY;
-    WaveAccept A{T, wait, off, lane, 0, 0, 0, 0, 0, 0, 0, 0, false, false};
+    WaveScan A{T, wait, off, H, wait, off + H, lane, 64, 0, 0, 0, 0, 0, 0, 0, 0, false, false};
     uint32_t cur = in_item, cur_n = r.item_n;
     A.la = lane_value(cls_of, 0);
     uint32_t cur_to = A.next_of(lane < cur_n, cur);
@@ -1563,9 +1724,7 @@ void launch_finish_planes(uint32_t* const* plane_ptr_dev, const FinishJob* jobs_
 void launch_fill(const FillBatch& F, const DevVocab& Vd, int32_t* bitmask_dev, int64_t row_stride_words,
                  const SlowScratch& S, hipStream_t stream) {
     if (F.B == 0) return;
-    const bool wide = Vd.W % 4 == 0 && row_stride_words % 4 == 0 && ((uintptr_t)bitmask_dev & 15) == 0;   // plane rows are 16-byte aligned when W % 4 == 0
-    if (wide) hipLaunchKernelGGL(k_fill<4>, dim3(F.B), dim3(FILL_THREADS), 0, stream, F, Vd, bitmask_dev, (long long)row_stride_words, S);
-    else hipLaunchKernelGGL(k_fill<1>, dim3(F.B), dim3(FILL_THREADS), 0, stream, F, Vd, bitmask_dev, (long long)row_stride_words, S);
+    hipLaunchKernelGGL(k_fill, dim3(F.B), dim3(FILL_THREADS), 0, stream, F, Vd, bitmask_dev, (long long)row_stride_words, S);
 }
 
 void launch_recheck_slow(const FillBatch& F, const DevVocab& Vd, int32_t* bitmask_dev, int64_t row_stride_words,
