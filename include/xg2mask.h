@@ -221,12 +221,13 @@ int32_t xg2_fill_next_token_bitmask(xg2_matcher* const* matchers, int32_t B, int
  * which keeps the previous call's contents (what must start at zero is cleared by the call itself): calls whose device work
  * overlaps on one GPU race, so keep them on one stream or order them with events.  Arguments, bitmask layout and errors are
  * otherwise those of xg2_fill_next_token_bitmask; xg2_fill_last_status and xg2_fill_last_recheck_tokens work after it (they
- * wait for the stream), xg2_fill_last_device_us does not (no events are recorded).                                          */
+ * wait for the device), xg2_fill_last_device_us does not (no time stamps are taken).                                        */
 int32_t xg2_fill_next_token_bitmask_noalloc(xg2_matcher* const* matchers, int32_t B, int32_t* bitmask_dev,
                                             int64_t row_stride_words, void* hip_stream);
 
 /* Measurement aid: device time in microseconds of the work the latest fill call of this process enqueued
- * (context upload, plane union, re-check), from HIP events on its stream.  Waits for that work.   */
+ * (context upload, plane union, re-check): from the start of its first kernel to the end of its last, as these kernels
+ * read the device's constant-rate clock; the time it takes to launch them is not in it.  Waits for the device.        */
 int32_t xg2_fill_last_device_us(float* out);
 
 /* What became of the re-checks of the latest fill call of this process (waits for its device work): how

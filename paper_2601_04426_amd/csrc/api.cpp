@@ -111,16 +111,25 @@ class BlockList {
     static void wait_idle() { (void)hipDeviceSynchronize(); }
 };
 
+// Whether the event that says that a launch is done may ride on the launch itself (hipExtLaunchKernel; 1 us on the host and
+// in the queue, where a recorded event is a packet of its own and takes 3): not while the stream is captured into a graph.
+inline bool events_ride(hipStream_t stream) {
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &st) != hipSuccess) { (void)hipGetLastError(); return false; }
+    return st == hipStreamCaptureStatusNone;
+}
+
 // Pinned host memory to device memory on `stream`: small blocks by a copy kernel that reads the host memory through its
 // device-side address (less latency than the copy engine), large ones by the runtime.  bytes: a multiple of 16.
 constexpr size_t kUploadByKernelMax = (size_t)4 << 20;
-inline void upload_pinned(void* dev, void* host, size_t bytes, hipStream_t stream) {
+inline void upload_pinned(void* dev, void* host, size_t bytes, hipStream_t stream, uint64_t* stamp = nullptr, hipEvent_t done = nullptr) {
     if (bytes <= kUploadByKernelMax) {
         void* mapped = nullptr;
         HIP_CHECK(hipHostGetDevicePointer(&mapped, host, 0));
-        launch_upload(dev, mapped, bytes, stream);
+        launch_upload(dev, mapped, bytes, stream, stamp, done);
     } else {
         HIP_CHECK(hipMemcpyAsync(dev, host, bytes, hipMemcpyHostToDevice, stream));
+        if (done) HIP_CHECK(hipEventRecord(done, stream));
     }
 }
 
@@ -236,9 +245,12 @@ struct NoAllocHost {
 NoAllocHost& noalloc_host() { static NoAllocHost* h = new NoAllocHost(); return *h; }
 
 void require_device() {
+    static std::atomic<bool> found{false};                  // devices do not go away
+    if (found.load(std::memory_order_relaxed)) return;
     int n = 0;
     hipError_t e = hipGetDeviceCount(&n);
     if (e != hipSuccess || n <= 0) throw HipError("no HIP device available (the mask cache runs on the GPU only)");
+    found.store(true, std::memory_order_relaxed);
 }
 
 // ---- vocabulary --------------------------------------------------------------------------------------
@@ -379,7 +391,7 @@ struct SlowImpl {
     void ensure() {
         s.k_cap = k_cap; s.wm_cap = wm_cap;
         if (ready) return;
-        s.n_lanes = 64 * 64;
+        s.n_lanes = kSlowLanes;
         s.list_cap = 1u << 20;
         mem.alloc((size_t)s.n_lanes * kSlowSlots);
         list.alloc((size_t)s.list_cap * 2);
@@ -696,24 +708,47 @@ struct FillWorkspace {
     FillSlot slots[4];
     int next = 0;
     DevBuf<uint32_t> cand_words, work_list, row_count;
-    hipEvent_t t_begin = nullptr, t_end = nullptr;          // around the device work of the latest fill
+    DevBuf<uint64_t> stamps;                                // when the latest fill's kernels started and ended (FillBatch::stamps)
+    uint32_t stamps_from = 0, n_stamps = 0;                 // which of them it wrote
+    double stamps_per_us = 0;
     const uint32_t* last_flags = nullptr;                   // device: overflow-list length and flag of the latest fill
     int32_t last_B = 0;                                     // rows of the latest fill
     const uint32_t* last_counts = nullptr;                  // device: their candidate-word counts
-    hipStream_t last_stream = nullptr;
-    bool timed = false;                                     // the latest fill recorded its events
+    bool timed = false;                                     // the latest fill wrote time stamps
     bool any = false;                                       // there has been a fill
     // the latest fill whose undecided pairs nobody has looked at yet: its slot and its matchers
     struct Pending { bool active = false; FillSlot* slot = nullptr; std::vector<MatcherImpl*> matchers; } pending;
     // waits for the device work of the latest fill
     void wait_last() {
-        if (timed) HIP_CHECK(hipEventSynchronize(t_end));
-        else HIP_CHECK(hipStreamSynchronize(last_stream));
+        HIP_CHECK(hipDeviceSynchronize());                  // its stream may be gone by now
     }
     void ensure_scratch(size_t words, size_t rows) {
         if (row_count.n < rows) row_count.alloc(rows * 2);
-        if (!t_begin) { HIP_CHECK(hipEventCreate(&t_begin)); HIP_CHECK(hipEventCreate(&t_end)); }
+        const size_t n = kStampsRows + kStampsPerRow * rows + kSlowLanes / 64;
+        if (stamps.n < n) stamps.alloc(n * 2);
         if (cand_words.n < words) { cand_words.alloc(words * 5 / 4); work_list.alloc(words * 5 / 4); }
+    }
+    // the latest fill is F, preceded by an upload kernel or not
+    void stamped(const FillBatch& F, const SlowScratch& S, bool uploaded) {
+        stamps_from = uploaded ? 0 : kStampsRows;
+        n_stamps = kStampsRows + kStampsPerRow * F.B + (F.own_lanes ? 0 : S.n_lanes / 64);
+    }
+    // microseconds from the first of them to the last
+    float stamped_us() {
+        if (stamps_per_us == 0) {
+            int dev = 0, khz = 0;
+            HIP_CHECK(hipGetDevice(&dev));
+            HIP_CHECK(hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, dev));
+            stamps_per_us = khz * 1e-3;
+        }
+        std::vector<uint64_t> t(n_stamps);
+        HIP_CHECK(hipMemcpy(t.data(), stamps.p, n_stamps * sizeof(uint64_t), hipMemcpyDeviceToHost));
+        uint64_t first = ~(uint64_t)0, last = 0;
+        for (size_t k = stamps_from; k < t.size(); ++k) {
+            first = std::min(first, t[k]);
+            last = std::max(last, t[k]);
+        }
+        return (float)((double)(last - first) / stamps_per_us);
     }
     FillSlot& acquire(size_t bytes) {
         FillSlot& s = slots[next];
@@ -2251,8 +2286,9 @@ int32_t fill_common(xg2_matcher* const* matchers, int32_t B, int32_t* bitmask_de
             NH.next ^= 1;
             if (NH.in_flight[k]) { HIP_CHECK(hipEventSynchronize(NH.done[k])); NH.in_flight[k] = false; }   // the call before last has read it
             pack(NH.host[k]);
-            upload_pinned(dev, NH.host[k], total, stream);
-            HIP_CHECK(hipEventRecord(NH.done[k], stream));
+            const bool ride = events_ride(stream);
+            upload_pinned(dev, NH.host[k], total, stream, nullptr, ride ? NH.done[k] : nullptr);
+            if (!ride) HIP_CHECK(hipEventRecord(NH.done[k], stream));
             NH.in_flight[k] = true;
         } else {
             slow().ensure();
@@ -2265,8 +2301,8 @@ int32_t fill_common(xg2_matcher* const* matchers, int32_t B, int32_t* bitmask_de
             HIP_CHECK(hipHostGetDevicePointer(&res_dev, slot->res_host, 0));
             S.unresolved = static_cast<uint32_t*>(res_dev); S.unresolved_cap = kUnresolvedCap;
             fill_ws().ensure_scratch((size_t)B * V.W, (size_t)B);
-            HIP_CHECK(hipEventRecord(fill_ws().t_begin, stream));
-            upload_pinned(slot->dev, slot->host, total, stream);
+            F.stamps = fill_ws().stamps.p;
+            upload_pinned(slot->dev, slot->host, total, stream, F.stamps);
             dev = slot->dev;
             F.cand_words = fill_ws().cand_words.p; F.work_list = fill_ws().work_list.p;
             F.row_count = fill_ws().row_count.p;
@@ -2282,18 +2318,18 @@ int32_t fill_common(xg2_matcher* const* matchers, int32_t B, int32_t* bitmask_de
         bool wide = false;
         for (auto& t : table_idx) wide |= t.first->wide;
         F.own_lanes = lanes_per_row(S.n_lanes, (size_t)B, wide);
-        launch_fill(F, V.dv, bitmask_dev, row_stride_words, S, stream);
+        const bool ride = slot && F.own_lanes && events_ride(stream);    // (k_fill is the last launch)
+        launch_fill(F, V.dv, bitmask_dev, row_stride_words, S, stream, ride ? slot->done : nullptr);
         if (!F.own_lanes) launch_recheck_slow(F, V.dv, bitmask_dev, row_stride_words, S, stream);
         HIP_CHECK(hipGetLastError());
         fill_ws().last_flags = S.count;
         fill_ws().last_counts = F.row_count;
         fill_ws().last_B = B;
-        fill_ws().last_stream = stream;
         fill_ws().timed = !no_alloc;
         fill_ws().any = true;
         if (!no_alloc) {
-            HIP_CHECK(hipEventRecord(fill_ws().t_end, stream));
-            HIP_CHECK(hipEventRecord(slot->done, stream));
+            if (!ride) HIP_CHECK(hipEventRecord(slot->done, stream));
+            fill_ws().stamped(F, S, total <= kUploadByKernelMax);
             slot->in_flight = true;
             FillWorkspace::Pending& pd = fill_ws().pending;
             pd.active = true; pd.slot = slot;
@@ -2372,11 +2408,9 @@ int32_t xg2_fill_last_device_us(float* out) {
     return guarded([&]() -> int32_t {
         if (!out) return fail(XG2_EINVAL, "xg2_fill_last_device_us: null out");
         std::lock_guard<std::mutex> ws_lock(fill_ws().mu);
-        if (!fill_ws().timed) return fail(XG2_EINVAL, "xg2_fill_last_device_us: the latest fill call recorded no events (none yet, or the one that allocates nothing)");
-        HIP_CHECK(hipEventSynchronize(fill_ws().t_end));
-        float ms = 0.f;
-        HIP_CHECK(hipEventElapsedTime(&ms, fill_ws().t_begin, fill_ws().t_end));
-        *out = ms * 1e3f;
+        if (!fill_ws().timed) return fail(XG2_EINVAL, "xg2_fill_last_device_us: the latest fill call took no time stamps (none yet, or the one that allocates nothing)");
+        fill_ws().wait_last();
+        *out = fill_ws().stamped_us();
         return XG2_OK;
     });
 }
@@ -2523,18 +2557,19 @@ int32_t xg2_batch_fill_next_token_bitmask(xg2_batch* batch, int32_t* bitmask_dev
         F.tables = Bt.d.tables;
         F.eos_id = (uint32_t)V.eos;
         F.cand_words = fill_ws().cand_words.p; F.work_list = fill_ws().work_list.p; F.row_count = fill_ws().row_count.p;
-        // nothing is uploaded: two sets of counter words take turns, each call's last kernel clears the set of the next call
+        // nothing is uploaded: two sets of counter words take turns, each fill kernel clears the set of the next call
         S.count = Bt.flag_words.p + 4 * Bt.flag_turn;
         Bt.flag_turn ^= 1;
         F.zero_words = Bt.flag_words.p + 4 * Bt.flag_turn;
         S.mark_rows = Bt.d.rows;                                // an undecided pair makes its slot unusable: the next accept says so
         F.own_lanes = lanes_per_row(S.n_lanes, (size_t)Bt.B, Bt.wide);
-        HIP_CHECK(hipEventRecord(fill_ws().t_begin, stream));
+        // no event is recorded: the two that used to time the call held up the kernels behind it by 6 - 7 us a step
+        F.stamps = fill_ws().stamps.p;
         launch_fill(F, V.dv, bitmask_dev, row_stride_words, S, stream);
         if (!F.own_lanes) launch_recheck_slow(F, V.dv, bitmask_dev, row_stride_words, S, stream);
         HIP_CHECK(hipGetLastError());
-        HIP_CHECK(hipEventRecord(fill_ws().t_end, stream));
-        fill_ws().last_flags = S.count; fill_ws().last_counts = F.row_count; fill_ws().last_B = Bt.B; fill_ws().last_stream = stream;
+        fill_ws().stamped(F, S, false);
+        fill_ws().last_flags = S.count; fill_ws().last_counts = F.row_count; fill_ws().last_B = Bt.B;
         fill_ws().timed = true; fill_ws().any = true;
         return XG2_OK;
     });

@@ -75,6 +75,7 @@ struct SlowScratch {                     // large-capacity per-lane Earley scrat
 };
 constexpr uint32_t kSlowK = 256, kSlowWM = 1024, kSlowMaxLen = 1024;
 constexpr uint32_t kSlowSearchBudget = 1u << 20;     // list entries one token may compare against in the device-memory lists
+constexpr uint32_t kSlowLanes = 64 * 64;                      // lanes of the large-capacity scratch (the fixed array's has fewer)
 constexpr uint32_t kSlowSlots = 2 * kSlowK + 2 * kSlowWM + kSlowMaxLen + 1;
 
 constexpr uint32_t kChunkListed = 1u, kChunkHeavy = 2u, kChunkThreads = 4u, kChunkDerive = 8u;   // bits of chunk[c].w
@@ -146,9 +147,13 @@ struct FillBatch {
                                          // and flag, where no upload brings them in as zeros: two sets take turns)
     uint32_t own_lanes;                  // lanes of the large-capacity scratch that are a row's own: it then decides every token itself;
                                          // 0: what outgrows the short lists is left to k_recheck_slow
+    uint64_t* stamps;                    // if not null: when the call's work started and ended, on the device's constant-rate clock:
+                                         // [0] the upload kernel's start; kStampsPerRow words for each row (start, end of each of
+                                         // its wavefronts); the end of each workgroup of k_recheck_slow
 };
+constexpr uint32_t kStampsRows = 1, kStampsPerRow = 7;
 void launch_fill(const FillBatch& F, const DevVocab& Vd, int32_t* bitmask_dev, int64_t row_stride_words,
-                 const SlowScratch& S, hipStream_t stream);
+                 const SlowScratch& S, hipStream_t stream, hipEvent_t done = nullptr);
 void launch_recheck_slow(const FillBatch& F, const DevVocab& Vd, int32_t* bitmask_dev, int64_t row_stride_words,
                          const SlowScratch& S, hipStream_t stream);
 
@@ -193,7 +198,7 @@ void launch_batch_assign(const BatchDev& D, const int32_t* rows_dev, uint32_t n,
 
 // Copies `bytes` (a multiple of 16) from pinned host memory, given by its device-side address, to device memory with
 // a kernel, or the other way: for the small per-call transfers this has less latency than the copy engine.
-void launch_upload(void* dst_dev, const void* src_host_mapped, size_t bytes, hipStream_t stream);
+void launch_upload(void* dst_dev, const void* src_host_mapped, size_t bytes, hipStream_t stream, uint64_t* stamp = nullptr, hipEvent_t done = nullptr);
 
 // The entry point that allocates nothing works in a fixed device array of the library (one per GPU, kept until the
 // process ends) instead of buffers that grow with the batch: staging of the per-row records, candidate words and

@@ -18,6 +18,8 @@
 #include <cstdlib>
 #include <mutex>
 
+#include <hip/hip_ext.h>
+
 #include "device.hpp"
 #include "earley_core.hpp"
 #include "accept_core.hpp"
@@ -497,7 +499,8 @@ __global__ __launch_bounds__(64) void k_build_slow(DevTables T, DevVocab Vd, Bui
 
 // Copies n 16-byte words from pinned host memory (read through its device address) to device memory: the per-call plan,
 // tables and per-row records travel this way, without a trip through the copy engine.
-__global__ __launch_bounds__(256) void k_upload(uint4* dst, const uint4* src, size_t n) {
+__global__ __launch_bounds__(256) void k_upload(uint4* dst, const uint4* src, size_t n, uint64_t* stamp) {
+    if (stamp && blockIdx.x == 0 && threadIdx.x == 0) *stamp = wall_clock64();
     for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (size_t)gridDim.x * 256) dst[i] = src[i];
 }
 
@@ -1032,6 +1035,8 @@ __global__ __launch_bounds__(FILL_THREADS) __attribute__((amdgpu_waves_per_eu(6)
     __shared__ FillOwn sh_own[FILL_THREADS / 64];
     __shared__ uint32_t n_listed, n_cand, n_over, next_token;
     const uint32_t b = blockIdx.x, lane = threadIdx.x & 63, wave = same_in_all(threadIdx.x >> 6);
+    if (F.stamps && threadIdx.x == 0) F.stamps[kStampsRows + kStampsPerRow * b] = wall_clock64();
+    auto stamp_end = [&]() { if (F.stamps && lane == 0) F.stamps[kStampsRows + kStampsPerRow * b + 1 + wave] = wall_clock64(); };
     const FillRow r = uniform_load(F.rows + b);
     const uint32_t front_off = r.front_off, front_n = r.front_n, flags = r.flags;
     const bool live = !(flags & 2u);
@@ -1162,10 +1167,11 @@ __global__ __launch_bounds__(FILL_THREADS) __attribute__((amdgpu_waves_per_eu(6)
                 atomicAdd(S.count, 1u);
                 if (recheck_large(F, Vd, S, r, b, id & ~FILL_OVER, b * F.own_lanes + wave)) atomicOr(out + ((id & ~FILL_OVER) >> 5), 1u << (id & 31));
             }
+        stamp_end();
         return;
     }
     if (threadIdx.x == 0) F.row_count[b] = n_cand;
-    if (wave < FILL_OR_WAVES) return;
+    if (wave < FILL_OR_WAVES) { stamp_end(); return; }
     // the sequential way: each wave of the re-check team takes as many listed words at a time as it has lanes at work
     // and spreads their set bits densely over those lanes
     const uint32_t count = n_listed;
@@ -1204,6 +1210,7 @@ __global__ __launch_bounds__(FILL_THREADS) __attribute__((amdgpu_waves_per_eu(6)
             }
         }
     }
+    stamp_end();
 }
 
 __global__ __launch_bounds__(64) void k_recheck_slow(FillBatch F, DevVocab Vd, int32_t* bitmask, long long row_stride, SlowScratch S) {
@@ -1232,6 +1239,7 @@ __global__ __launch_bounds__(64) void k_recheck_slow(FillBatch F, DevVocab Vd, i
         else alive = (res & RES_ALIVE) != 0;
         if (alive) atomicOr(reinterpret_cast<uint32_t*>(bitmask) + (long long)b * row_stride + (id >> 5), 1u << (id & 31));
     }
+    if (F.stamps && threadIdx.x == 0) F.stamps[kStampsRows + kStampsPerRow * F.B + blockIdx.x] = wall_clock64();
 }
 
 // ---- matchers on the device ------------------------------------------------------------------------
@@ -1678,11 +1686,14 @@ void launch_batch_assign(const BatchDev& D, const int32_t* rows_dev, uint32_t n,
     hipLaunchKernelGGL(k_batch_assign, dim3((n + 255) / 256), dim3(256), 0, stream, D, rows_dev, n, cache_idx);
 }
 
-void launch_upload(void* dst_dev, const void* src_host_mapped, size_t bytes, hipStream_t stream) {
+void launch_upload(void* dst_dev, const void* src_host_mapped, size_t bytes, hipStream_t stream, uint64_t* stamp, hipEvent_t done) {
     const size_t n = bytes / sizeof(uint4);
     if (!n) return;
     const uint32_t grid = (uint32_t)std::min<size_t>((n + 255) / 256, 2048);
-    hipLaunchKernelGGL(k_upload, dim3(grid), dim3(256), 0, stream, static_cast<uint4*>(dst_dev), static_cast<const uint4*>(src_host_mapped), n);
+    uint4* dst = static_cast<uint4*>(dst_dev);
+    const uint4* src = static_cast<const uint4*>(src_host_mapped);
+    if (done) hipExtLaunchKernelGGL(k_upload, dim3(grid), dim3(256), 0, stream, nullptr, done, 0, dst, src, n, stamp);
+    else hipLaunchKernelGGL(k_upload, dim3(grid), dim3(256), 0, stream, dst, src, n, stamp);
 }
 
 void launch_copy_masked(const CopyJob* jobs_dev, uint32_t n_jobs, uint32_t W, hipStream_t stream) {
@@ -1722,9 +1733,10 @@ void launch_finish_planes(uint32_t* const* plane_ptr_dev, const FinishJob* jobs_
 }
 
 void launch_fill(const FillBatch& F, const DevVocab& Vd, int32_t* bitmask_dev, int64_t row_stride_words,
-                 const SlowScratch& S, hipStream_t stream) {
+                 const SlowScratch& S, hipStream_t stream, hipEvent_t done) {
     if (F.B == 0) return;
-    hipLaunchKernelGGL(k_fill, dim3(F.B), dim3(FILL_THREADS), 0, stream, F, Vd, bitmask_dev, (long long)row_stride_words, S);
+    if (done) hipExtLaunchKernelGGL(k_fill, dim3(F.B), dim3(FILL_THREADS), 0, stream, nullptr, done, 0, F, Vd, bitmask_dev, (long long)row_stride_words, S);
+    else hipLaunchKernelGGL(k_fill, dim3(F.B), dim3(FILL_THREADS), 0, stream, F, Vd, bitmask_dev, (long long)row_stride_words, S);
 }
 
 void launch_recheck_slow(const FillBatch& F, const DevVocab& Vd, int32_t* bitmask_dev, int64_t row_stride_words,
