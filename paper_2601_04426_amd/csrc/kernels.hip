@@ -1538,61 +1538,84 @@ __global__ __launch_bounds__(64) void k_accept(BatchDev D, DevVocab Vd, uint32_t
 }
 
 // ---- apply -----------------------------------------------------------------------------------------
-// One 16-byte vector per thread per step: 4 fp32 or 8 bf16.  A vector whose tokens are all allowed is
-// left alone (no read, no write); one whose tokens are all disallowed is overwritten without a read;
-// only mixed vectors are read, merged and written back.
-constexpr int APPLY_THREADS = 256, APPLY_VECS = 4;
+// One wavefront per 2,048 tokens of a row (APPLY_WAVE), counted from the 128-byte boundary of memory at or before the row's
+// begin, so that rows of any length and base are accessed in whole aligned cache lines.  Each lane takes one mask word: a
+// piece that is allowed as a whole (most of free text) ends there, after one coalesced load.  Then 16-byte vectors (4 fp32 or
+// 8 bf16), 64 a step, their bits from the lane that holds the word: a vector whose tokens are all allowed is left alone (no
+// read, no write); one whose tokens are all disallowed is overwritten without a read; only mixed vectors are read, merged and
+// written back, all reads before the first store.  Vectors that the row shares with its neighbours are done by the element.
+// Bound by memory (a large copy moves 5.4 TB/s on this card, a large fill 6.9), and where nothing is masked by instructions
+// issued, which is why a mask word is loaded once and not once per vector.  With a mask look-up per vector, and rows off a
+// 16-byte boundary done by the element, against now, us at 1,024 rows of V = 151,936 / 151,937, bf16: nothing masked 9.8 / 130
+// -> 6.2 / 7.3; nearly everything 80 / 204 -> 52 / 53; 5 % of the tokens 107 / 252 -> 97 / 98 (four
+// fifths of the 64-byte sectors hold a masked token and are read and written).
+constexpr int APPLY_WAVE = 64 * 32, APPLY_WAVES = 4;
+template <class E> struct ApplyE;
+template <> struct ApplyE<uint32_t> { static constexpr uint32_t NINF = 0xFF800000u, NINF_WORD = 0xFF800000u; };
+template <> struct ApplyE<uint16_t> { static constexpr uint16_t NINF = 0xFF80; static constexpr uint32_t NINF_WORD = 0xFF80FF80u; };
+typedef uint32_t Vec4 __attribute__((ext_vector_type(4)));
 
-template <int EPV /* elements per 16-byte vector */>
-__global__ __launch_bounds__(APPLY_THREADS) void k_apply_vec(uint4* logits, long long row_stride_vecs, int n_vecs,
-                                                             const uint32_t* bitmask, long long bm_stride) {
+template <class E, bool STREAM>
+__global__ __launch_bounds__(64 * APPLY_WAVES) void k_apply_vec(E* logits, long long row_stride, int V, const uint32_t* bitmask, long long bm_stride) {
+    constexpr int EPV = 16 / sizeof(E), STEPS = 32 / EPV, LINE = 128 / sizeof(E);
+    constexpr uint32_t ALL = (1u << EPV) - 1, NI = ApplyE<E>::NINF_WORD;
     const long long b = blockIdx.y;
-    uint4* row = logits + b * row_stride_vecs;
-    const uint32_t* bm = bitmask + b * bm_stride;
-    const int v0 = blockIdx.x * (APPLY_THREADS * APPLY_VECS) + threadIdx.x;
+    E* const row = logits + b * row_stride;
+    const uint32_t* const bm = bitmask + b * bm_stride;
+    const int lane = threadIdx.x & 63, wave = (int)same_in_all(threadIdx.x >> 6);
+    const int before = (int)(reinterpret_cast<uintptr_t>(row) & 127) / (int)sizeof(E);       // elements between the boundary and the row
+    const long long e0 = ((long long)blockIdx.x * (blockDim.x >> 6) + wave) * APPLY_WAVE - before;   // the wavefront's first element
+    if (e0 >= V) return;
+    // this lane's 32 tokens from e0 + 32 * lane on; what lies outside the row counts as allowed
+    const int first = (int)e0 + 32 * lane, shift = (int)(e0 & 31), at = first >> 5, last = (V - 1) >> 5;    // (an arithmetic shift: rounds down)
+    uint32_t word = at >= 0 && at <= last ? bm[at] : ~0u;
+    if (shift != 0) {                                                // (the same in all lanes)
+        const uint32_t next = at + 1 >= 0 && at + 1 <= last ? bm[at + 1] : ~0u;
+        word = (word >> shift) | (next << (32 - shift));
+    }
+    if (first < 0) word |= first <= -32 ? ~0u : (1u << -first) - 1;
+    if (first + 32 > V) word |= first >= V ? ~0u : ~0u << (V - first);
+    if (__ballot(word != ~0u) == 0) return;
+    E* const piece = row + e0;
+    Vec4 x[STEPS];
+    uint32_t bits[STEPS];
 #pragma unroll
-    for (int j = 0; j < APPLY_VECS; ++j) {
-        const int v = v0 + j * APPLY_THREADS;
-        if (v >= n_vecs) break;
-        const int e0 = v * EPV;
-        const uint32_t bits = (bm[e0 >> 5] >> (e0 & 31)) & ((1u << EPV) - 1);
-        if (bits == (1u << EPV) - 1) continue;
-        uint4 x;
-        if (EPV == 4) {
-            const uint32_t NINF = 0xFF800000u;
-            if (bits == 0) x = make_uint4(NINF, NINF, NINF, NINF);
-            else {
-                x = row[v];
-                if (!(bits & 1)) x.x = NINF;
-                if (!(bits & 2)) x.y = NINF;
-                if (!(bits & 4)) x.z = NINF;
-                if (!(bits & 8)) x.w = NINF;
-            }
+    for (int j = 0; j < STEPS; ++j) {
+        const int v = j * 64 + lane;
+        bits[j] = ((uint32_t)__shfl((int)word, v / STEPS) >> (v % STEPS * EPV)) & ALL;
+        x[j] = Vec4{NI, NI, NI, NI};
+        const int e = (int)e0 + v * EPV;
+        if (bits[j] != 0 && bits[j] != ALL && e >= 0 && e + EPV <= V) x[j] = reinterpret_cast<const Vec4*>(piece)[v];
+    }
+#pragma unroll
+    for (int j = 0; j < STEPS; ++j) {
+        if (bits[j] == ALL) continue;
+        const int v = j * 64 + lane, e = (int)e0 + v * EPV;
+        if (e < 0 || e + EPV > V) {                                  // shared with a neighbour
+            for (int c = 0; c < EPV; ++c) if (!((bits[j] >> c) & 1)) row[e + c] = ApplyE<E>::NINF;
+            continue;
+        }
+        if (sizeof(E) == 4) {
+            _Pragma("unroll") for (int c = 0; c < 4; ++c) if (!((bits[j] >> c) & 1)) x[j][c] = NI;
         } else {
-            const uint32_t NINF2 = 0xFF80FF80u;
-            if (bits == 0) x = make_uint4(NINF2, NINF2, NINF2, NINF2);
-            else {
-                x = row[v];
-                auto merge = [](uint32_t w, uint32_t two) {
-                    if (!(two & 1)) w = (w & 0xFFFF0000u) | 0xFF80u;
-                    if (!(two & 2)) w = (w & 0x0000FFFFu) | 0xFF800000u;
-                    return w;
-                };
-                x.x = merge(x.x, bits); x.y = merge(x.y, bits >> 2); x.z = merge(x.z, bits >> 4); x.w = merge(x.w, bits >> 6);
+            _Pragma("unroll") for (int c = 0; c < 4; ++c) {
+                if (!((bits[j] >> (2 * c)) & 1)) x[j][c] = (x[j][c] & 0xFFFF0000u) | 0xFF80u;
+                if (!((bits[j] >> (2 * c)) & 2)) x[j][c] = (x[j][c] & 0x0000FFFFu) | 0xFF800000u;
             }
         }
-        row[v] = x;
+        Vec4* const to = reinterpret_cast<Vec4*>(piece) + v;
+        if (STREAM) __builtin_nontemporal_store(x[j], to);
+        else *to = x[j];
     }
 }
 
-// Any alignment, any stride; also the tail after the last whole vector.
-template <typename E>
-__global__ __launch_bounds__(256) void k_apply_scalar(E* logits, long long row_stride, int v_begin, int V,
-                                                      const uint32_t* bitmask, long long bm_stride, E ninf) {
+// Logits that do not lie at a multiple of their own size (or rows too long to count in 32 bits above).
+template <class E>
+__global__ __launch_bounds__(256) void k_apply_scalar(E* logits, long long row_stride, int V, const uint32_t* bitmask, long long bm_stride) {
     const long long b = blockIdx.y;
-    const int v = v_begin + blockIdx.x * 256 + threadIdx.x;
+    const int v = blockIdx.x * 256 + threadIdx.x;
     if (v >= V) return;
-    if (!((bitmask[b * bm_stride + (v >> 5)] >> (v & 31)) & 1u)) logits[b * row_stride + v] = ninf;
+    if (!((bitmask[b * bm_stride + (v >> 5)] >> (v & 31)) & 1u)) logits[b * row_stride + v] = ApplyE<E>::NINF;
 }
 
 }  // namespace
@@ -1744,33 +1767,33 @@ void launch_recheck_slow(const FillBatch& F, const DevVocab& Vd, int32_t* bitmas
     hipLaunchKernelGGL(k_recheck_slow, dim3(S.n_lanes / 64), dim3(64), 0, stream, F, Vd, bitmask_dev, (long long)row_stride_words, S);
 }
 
+// Ordinary stores leave the logits in the last-level cache (256 MB), where the next pass over them finds them; logits that do
+// not fit there push each other out, and streaming stores take them straight to memory.  Ordinary / streaming, us, nearly
+// everything masked: 205 MB 33 / 39, 233 MB 39 / 40, 266 MB (below the line) 46 / 51, 273 MB (above) 57 / 46, 311 MB 70 / 52.
+constexpr long long APPLY_STREAM_BYTES = 256ll << 20;
+
+template <class E>
+static void launch_apply_as(E* logits, int32_t B, int32_t V, int64_t row_stride_elems, const uint32_t* bm, int64_t bm_row_stride_words, hipStream_t stream) {
+    if (reinterpret_cast<uintptr_t>(logits) % sizeof(E) != 0 || V > 1 << 30) {
+        hipLaunchKernelGGL(k_apply_scalar<E>, dim3(V / 256 + (V % 256 != 0), B), dim3(256), 0, stream, logits, (long long)row_stride_elems, V, bm, (long long)bm_row_stride_words);
+        return;
+    }
+    // a row that begins `before` elements behind a 128-byte boundary has that much more to cover
+    const uint32_t pieces = ((uint32_t)V + 128 / sizeof(E) - 1 + APPLY_WAVE - 1) / APPLY_WAVE;
+    // few pieces: a workgroup each, to reach as many compute units (one row, V = 32,000, fp32: 3.7 us against 4.0); many: four share one
+    // (1,024 rows, V = 151,936, bf16, nothing masked: 6.2 us against 17.5, which is how long it takes to start the workgroups)
+    const uint32_t waves = (uint64_t)pieces * (uint32_t)B <= 512 ? 1 : APPLY_WAVES;
+    auto* const kernel = (long long)B * V * (int)sizeof(E) > APPLY_STREAM_BYTES ? k_apply_vec<E, true> : k_apply_vec<E, false>;
+    hipLaunchKernelGGL(kernel, dim3((pieces + waves - 1) / waves, B), dim3(64 * waves), 0, stream, logits, (long long)row_stride_elems, V, bm,
+                       (long long)bm_row_stride_words);
+}
+
 void launch_apply(void* logits_dev, int32_t dtype, int32_t B, int32_t V, int64_t row_stride_elems,
                   const int32_t* bitmask_dev, int64_t bm_row_stride_words, hipStream_t stream) {
     if (B == 0 || V == 0) return;
-    const int esize = dtype == 0 ? 4 : 2;
-    const int epv = 16 / esize;
-    const bool aligned = (reinterpret_cast<uintptr_t>(logits_dev) % 16 == 0) && ((row_stride_elems * esize) % 16 == 0);
-    const int n_vecs = aligned ? V / epv : 0;
     const uint32_t* bm = reinterpret_cast<const uint32_t*>(bitmask_dev);
-    if (n_vecs > 0) {
-        dim3 grid((n_vecs + APPLY_THREADS * APPLY_VECS - 1) / (APPLY_THREADS * APPLY_VECS), B);
-        if (dtype == 0)
-            hipLaunchKernelGGL(k_apply_vec<4>, grid, dim3(APPLY_THREADS), 0, stream, (uint4*)logits_dev,
-                               (long long)(row_stride_elems / 4), n_vecs, bm, (long long)bm_row_stride_words);
-        else
-            hipLaunchKernelGGL(k_apply_vec<8>, grid, dim3(APPLY_THREADS), 0, stream, (uint4*)logits_dev,
-                               (long long)(row_stride_elems / 8), n_vecs, bm, (long long)bm_row_stride_words);
-    }
-    const int v_begin = n_vecs * epv;
-    if (v_begin < V) {
-        dim3 grid((V - v_begin + 255) / 256, B);
-        if (dtype == 0)
-            hipLaunchKernelGGL(k_apply_scalar<uint32_t>, grid, dim3(256), 0, stream, (uint32_t*)logits_dev, (long long)row_stride_elems,
-                               v_begin, V, bm, (long long)bm_row_stride_words, 0xFF800000u);
-        else
-            hipLaunchKernelGGL(k_apply_scalar<uint16_t>, grid, dim3(256), 0, stream, (uint16_t*)logits_dev, (long long)row_stride_elems,
-                               v_begin, V, bm, (long long)bm_row_stride_words, (uint16_t)0xFF80);
-    }
+    if (dtype == 0) launch_apply_as((uint32_t*)logits_dev, B, V, row_stride_elems, bm, bm_row_stride_words, stream);
+    else launch_apply_as((uint16_t*)logits_dev, B, V, row_stride_elems, bm, bm_row_stride_words, stream);
 }
 
 }  // namespace xg2
