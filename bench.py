@@ -33,13 +33,13 @@ HBM_PEAK_GBS = 8000.0
 # with.  The same counters read 303,890 (FETCH_SIZE) and 607,744 (WRITE_SIZE) for a device-to-device copy of 607,744 KiB,
 # hence the scale factors to KiB.  The summaries under profiles/ hold the commands and the full tables.
 PMC = {
-    "sources_sha256": "236e9418d43ccc896bf41a1fa618f043c5f6b0f15c010edf8f2233fc1ca770e9",
+    "sources_sha256": "4370a2d718e07cdcfec22a920224906e3a18f7dee6a01a7c2c89bdd8421c45c9",
     "fetch_scale": 2.00, "write_scale": 1.00,
-    "k_build": (11030.4, 4800.5),
-    "k_fill": (3308.2, 19191.9),
-    "k_apply_vec<8>": (97590.3, 303872.0),
-    "k_apply_vec<4>": (180438.0, 605533.3),
-    "k_build_tagdispatch": (144657.9, 689897.5),
+    "k_build": (11012.6, 4800.5),
+    "k_fill": (3353.4, 19285.9),
+    "k_apply_vec<bf16>": (97593.4, 303892.9),
+    "k_apply_vec<fp32>": (179377.8, 605724.9),
+    "k_build_tagdispatch": (144034.6, 689897.5),
     # wave instructions of one k_build launch (rocprofv3 --pmc SQ_INSTS_VALU; SQ_INSTS_SALU + SQ_INSTS_SMEM + SQ_INSTS_BRANCH)
     "k_build_valu_instructions": 12898560.0, "k_build_scalar_and_branch_instructions": 17288610.0,
     "k_build_tagdispatch_valu_instructions": 848041696.0, "k_build_tagdispatch_scalar_and_branch_instructions": 1115408341.0,
@@ -331,7 +331,7 @@ def main() -> int:
         t = med(acc[key]) * 1e-6
         gbs = moved[e] / t / 1e9
         out[name] = {"kernel": "k_apply_vec", "bound": "hbm", "achieved": gbs, "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                     "frac": gbs / HBM_PEAK_GBS, "traffic": measured_traffic("k_apply_vec<8>" if e == 2 else "k_apply_vec<4>", default_workload),
+                     "frac": gbs / HBM_PEAK_GBS, "traffic": measured_traffic("k_apply_vec<bf16>" if e == 2 else "k_apply_vec<fp32>", default_workload),
                      "algorithmic_bytes_per_launch": moved[e],
                      "accounting": "bytes the kernel has to move for this bitmask: bitmask read + 16 B written per fully masked vector + 32 B read and "
                                    "written per mixed vector (last step's bitmask)",
