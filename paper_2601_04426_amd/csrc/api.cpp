@@ -24,6 +24,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include "block_list.hpp"
 #include "device.hpp"
 #include "flat_map.hpp"
 #include "grammar.hpp"
@@ -61,55 +62,38 @@ struct DevBuf {                                    // owning device array
     }
 };
 
-// Device blocks that outlive the pool or cache they were part of: a request's planes and tables come and go, and allocating
-// and freeing them in the driver costs 50 - 350 us a block (it maps and unmaps the memory), as much as building the planes of
-// a small grammar.  Bounded (kMaxSpare bytes are kept, the rest is freed); what is kept goes back to the driver with the
-// vocabulary that owns the list, or when an allocation fails.  Work in flight may still use a block that is handed in: it is
-// waited for, which is what freeing it would have done.
-class BlockList {
-    static constexpr size_t kMaxSpare = (size_t)1 << 30;
-    struct Block { void* p; size_t n; };
-    std::mutex mu;
-    std::vector<Block> spare;
-    size_t spare_bytes = 0;
-    void drop_all() { for (Block& b : spare) (void)hipFree(b.p); spare.clear(); spare_bytes = 0; }
-
-  public:
-    ~BlockList() { drop_all(); }
-    // a block of at least n bytes, contents unspecified; *size receives what it really holds (to be given to put)
-    void* get(size_t n, size_t* size) {
-        n = (n + 0xFFFF) & ~(size_t)0xFFFF;
-        std::lock_guard<std::mutex> lk(mu);
-        size_t best = spare.size();
-        for (size_t k = 0; k < spare.size(); ++k)                   // the smallest that fits, unless it is far too large
-            if (spare[k].n >= n && spare[k].n <= 2 * n + ((size_t)1 << 20) && (best == spare.size() || spare[k].n < spare[best].n)) best = k;
-        if (best < spare.size()) {
-            void* p = spare[best].p;
-            *size = spare[best].n;
-            spare_bytes -= spare[best].n;
-            spare[best] = spare.back();
-            spare.pop_back();
-            return p;
-        }
+// The device's memory as BlockListOf wants it.  The wait is a small block allocated and freed (1.4 us on an idle device, where
+// hipDeviceSynchronize takes 0.3): hipFree waits for the device too, but leaves a capture alone that another thread makes in
+// thread-local mode or anybody in relaxed mode; hipDeviceSynchronize breaks every capture there is.
+struct HipMemory {
+    int device() { int d = 0; HIP_CHECK(hipGetDevice(&d)); return d; }
+    void* alloc(size_t n) {
         void* p = nullptr;
-        if (hipMalloc(&p, n) != hipSuccess) {
-            (void)hipGetLastError();
-            drop_all();
-            HIP_CHECK(hipMalloc(&p, n));
-        }
-        *size = n;
-        return p;
+        if (hipMalloc(&p, n) == hipSuccess) return p;
+        (void)hipGetLastError();
+        return nullptr;
     }
-    // the caller has waited for the work in flight (wait_idle)
-    void put(void* p, size_t n) {
-        {
-            std::lock_guard<std::mutex> lk(mu);
-            if (spare_bytes + n <= kMaxSpare) { spare.push_back({p, n}); spare_bytes += n; return; }
-        }
-        (void)hipFree(p);
+    bool free(void* p) {
+        if (hipFree(p) == hipSuccess) return true;
+        (void)hipGetLastError();
+        return false;
     }
-    static void wait_idle() { (void)hipDeviceSynchronize(); }
+    bool wait(int device) {
+        int current = 0;
+        if (hipGetDevice(&current) != hipSuccess || (current != device && hipSetDevice(device) != hipSuccess)) { (void)hipGetLastError(); return false; }
+        void* p = alloc(16);
+        const bool done = p && free(p);
+        if (current != device) (void)hipSetDevice(current);
+        return done;
+    }
 };
+using BlockList = BlockListOf<HipMemory>;
+using Block = BlockList::Block;
+inline Block get_block(BlockList& list, size_t n) {
+    const Block b = list.get(n);
+    if (!b.p) throw HipError("no device memory left");
+    return b;
+}
 
 // Whether the event that says that a launch is done may ride on the launch itself (hipExtLaunchKernel; 1 us on the host and
 // in the queue, where a recorded event is a packet of its own and takes 3): not while the stream is captured into a graph.
@@ -191,7 +175,7 @@ struct Packer {
         return off;
     }
     // own: the device block comes from this list (null: from the staging set) and belongs to the caller afterwards
-    size_t dev_bytes = 0;
+    Block dev_block;
     void stage(BlockList* own, StagingSet& S) {
         const size_t n = std::max<size_t>(total, 256), n_dev = n + reserved;
         if (S.host_cap < n) {
@@ -203,7 +187,8 @@ struct Packer {
         }
         host = S.host;
         if (own) {
-            dev = static_cast<uint8_t*>(own->get(n_dev, &dev_bytes));
+            dev_block = get_block(*own, n_dev);
+            dev = static_cast<uint8_t*>(dev_block.p);
         } else {
             if (S.dev_cap < n_dev) {
                 if (S.dev) (void)hipFree(S.dev);
@@ -507,7 +492,7 @@ struct PoolImpl {
     std::vector<PlaneRow*> free_rows;
     uint64_t clock = 0;
     int64_t n_evicted = 0;
-    std::vector<std::pair<void*, size_t>> slabs;
+    std::vector<Block> slabs;
     // memory to clear before the next build writes to it: the rows handed out since the one before (neighbours as one
     // range).  The build enqueues the clearing inside its timed region (skipped tokens rely on the zeros).
     std::vector<std::pair<void*, size_t>> to_zero;
@@ -519,8 +504,7 @@ struct PoolImpl {
     size_t device_bytes = 0;
     int64_t n_rows = 0;
     ~PoolImpl() {
-        if (!slabs.empty()) BlockList::wait_idle();
-        for (auto& s : slabs) vocab->blocks.put(s.first, s.second);
+        for (const Block& b : slabs) vocab->blocks.put(b);
     }
 
     // exact interning: same hash AND same canonical form
@@ -577,10 +561,8 @@ struct PoolImpl {
                 std::partial_sort(idle.begin(), idle.begin() + (long)batch, idle.end());
                 for (size_t k = 0; k < batch; ++k) { forget(idle[k].second); ++n_evicted; }
             } else {
-                size_t got = 0;
-                void* p = vocab->blocks.get(want, &got);
-                slabs.emplace_back(p, got);
-                slab_cur = (uint8_t*)p; slab_left = want; device_bytes += want;
+                slabs.push_back(get_block(vocab->blocks, want));
+                slab_cur = (uint8_t*)slabs.back().p; slab_left = want; device_bytes += want;
             }
         }
         PlaneRow* row;
@@ -636,7 +618,7 @@ struct CacheImpl {
     std::shared_ptr<VocabImpl> vocab;
     std::shared_ptr<PoolImpl> pool;
     std::shared_ptr<GrammarImpl> gram;
-    uint8_t* d_tables = nullptr; size_t d_tables_bytes = 0;  // one device block holding all packed tables
+    Block d_tables;                                         // holds all packed tables
     ~CacheImpl();
     DevTables dt{};
     int32_t context_depth = 2;
@@ -924,7 +906,7 @@ CacheImpl::~CacheImpl() {
         std::lock_guard<std::mutex> lk(pool->mu);
         for (const PlaneInfo& pi : planes) if (pi.row) pool->release(pi.row);
     }
-    if (d_tables) { BlockList::wait_idle(); vocab->blocks.put(d_tables, d_tables_bytes); }
+    if (d_tables.p) vocab->blocks.put(d_tables);
 }
 
 // Enqueues the build of the planes `todo` of a cache that do not hold a row yet: rows the pool already has are taken
@@ -1212,7 +1194,7 @@ int32_t build_planes(CacheImpl& cache, const std::vector<int32_t>& todo, hipStre
                  o_wait_off = tab.add(ctx_wait_off), o_rows = tab.add(build_rows), o_copies = tab.add(copies), o_structure_copies = tab.add(structure_copies), o_fb_copies = tab.add(fb_copies), o_finish = tab.add(finish), o_zero = tab.add(zeros);
     const size_t o_chunks = tab.reserve(n_chunks * 2 * sizeof(uint4));
     tab.stage(with_tables ? &V.blocks : nullptr, SS);
-    if (with_tables) { cache.d_tables = tab.dev; cache.d_tables_bytes = tab.dev_bytes; }                     // the cache owns the block from here on
+    if (with_tables) cache.d_tables = tab.dev_block;              // the cache owns the block from here on
     ticket->host_ms = ms_since(t1);
 
     SS.ensure_events();

@@ -1,0 +1,104 @@
+// Device blocks kept between the pools and caches of a vocabulary.  What touches the device goes through Memory, so that the
+// rules of keeping and handing out can be run on the host.
+#pragma once
+#include <cstddef>
+#include <cstdint>
+#include <mutex>
+#include <vector>
+
+namespace xg2 {
+
+// A request's planes and tables come and go, and allocating and freeing them in the driver costs 50 - 350 us a block (it maps
+// and unmaps the memory), as much as building the planes of a small grammar.  Bounded (kMaxSpare bytes are kept, the rest is
+// freed); what is kept goes back to the driver with the vocabulary that owns the list, or when an allocation fails.
+// Work in flight may still use a block that is handed in, so it is handed out again only after a wait for its device, which is
+// what freeing it would have done; where the wait fails (another thread is capturing a stream), the block is held until one
+// succeeds.
+//
+// Memory: int device() (the current one), void* alloc(size_t) on it (null: none left), bool free(void*) (waits for the
+// block's device, as hipFree does; false: the block is still allocated), bool wait(int device) (false: work may be in flight).
+template <class Memory>
+class BlockListOf {
+  public:
+    struct Block { void* p = nullptr; size_t n = 0; int device = 0; };
+    static constexpr size_t kMaxSpare = (size_t)1 << 30;
+
+    explicit BlockListOf(Memory mem = Memory()) : mem_(mem) {}
+    BlockListOf(const BlockListOf&) = delete;
+    BlockListOf& operator=(const BlockListOf&) = delete;
+    ~BlockListOf() { drop_all(); }
+
+    // a block of at least n bytes, contents unspecified (n: what it really holds); p null if there is no memory left
+    Block get(size_t n) {
+        n = (n + 0xFFFF) & ~(size_t)0xFFFF;
+        Block b;
+        b.device = mem_.device();
+        if (take(n, b) || (release_held() && take(n, b))) return b;
+        b.p = mem_.alloc(n);
+        if (!b.p) {
+            drop_all();
+            b.p = mem_.alloc(n);
+        }
+        b.n = b.p ? n : 0;
+        return b;
+    }
+    void put(const Block& b) {
+        bool room;
+        { std::lock_guard<std::mutex> lk(mu_); room = kept_bytes_ + b.n <= kMaxSpare; }
+        if (!room && mem_.free(b.p)) return;
+        const bool idle = mem_.wait(b.device);
+        std::lock_guard<std::mutex> lk(mu_);
+        kept_bytes_ += b.n;
+        (idle ? spare_ : held_).push_back(b);
+    }
+    size_t spare_blocks() { std::lock_guard<std::mutex> lk(mu_); return spare_.size(); }
+    size_t held_blocks() { std::lock_guard<std::mutex> lk(mu_); return held_.size(); }
+
+  private:
+    Memory mem_;
+    std::mutex mu_;                                  // not held while the device is waited for
+    std::vector<Block> spare_, held_;                // nothing in flight uses them; work in flight may
+    size_t kept_bytes_ = 0;                          // of both
+
+    bool take(size_t n, Block& b) {
+        std::lock_guard<std::mutex> lk(mu_);
+        size_t best = spare_.size();
+        for (size_t k = 0; k < spare_.size(); ++k)                  // the smallest that fits, unless it is far too large
+            if (spare_[k].device == b.device && spare_[k].n >= n && spare_[k].n <= 2 * n + ((size_t)1 << 20) && (best == spare_.size() || spare_[k].n < spare_[best].n)) best = k;
+        if (best == spare_.size()) return false;
+        b = spare_[best];
+        kept_bytes_ -= b.n;
+        spare_[best] = spare_.back();
+        spare_.pop_back();
+        return true;
+    }
+    bool release_held() {                            // whether any of the held blocks is free to use now
+        std::vector<Block> held;
+        { std::lock_guard<std::mutex> lk(mu_); held.swap(held_); }
+        bool any = false;
+        for (const Block& b : held) {
+            const bool idle = mem_.wait(b.device);
+            any |= idle;
+            std::lock_guard<std::mutex> lk(mu_);
+            (idle ? spare_ : held_).push_back(b);
+        }
+        return any;
+    }
+    void drop_all() {
+        std::vector<Block> all;
+        {
+            std::lock_guard<std::mutex> lk(mu_);
+            all.swap(spare_);
+            all.insert(all.end(), held_.begin(), held_.end());
+            held_.clear();
+        }
+        for (const Block& b : all) {
+            const bool freed = mem_.free(b.p);
+            std::lock_guard<std::mutex> lk(mu_);
+            if (freed) kept_bytes_ -= b.n;
+            else held_.push_back(b);
+        }
+    }
+};
+
+}  // namespace xg2
