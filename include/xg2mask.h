@@ -136,7 +136,11 @@ int32_t xg2_grammar_num_positions(const xg2_grammar*, int32_t* out);
  * compiled with the same pool and vocabulary.  max_bytes bounds the device memory of the pool
  * (0 = unbounded).  When it is reached, planes that no live mask cache uses are given up, least
  * recently used first, and built again if a later grammar needs them; if every plane is in use,
- * compile (or a just-in-time fill) fails with XG2_EOVERFLOW.                                     */
+ * compile (or a just-in-time fill) fails with XG2_EOVERFLOW.
+ * The device memory of pools and mask caches that are destroyed stays with their vocabulary, up to
+ * 1 GiB, for the pools and caches to come (it counts towards the max_bytes of the pool that gets it,
+ * not of the one that had it); what is more, and all of it when the vocabulary and everything made
+ * with it is gone, goes back to the device.                                                       */
 int32_t xg2_pool_create(size_t max_bytes, xg2_pool** out);
 void    xg2_pool_destroy(xg2_pool*);
 int32_t xg2_pool_stats(const xg2_pool*, int64_t* n_positions, int64_t* device_bytes);

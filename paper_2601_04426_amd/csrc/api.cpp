@@ -89,11 +89,6 @@ struct HipMemory {
 };
 using BlockList = BlockListOf<HipMemory>;
 using Block = BlockList::Block;
-inline Block get_block(BlockList& list, size_t n) {
-    const Block b = list.get(n);
-    if (!b.p) throw HipError("no device memory left");
-    return b;
-}
 
 // Whether the event that says that a launch is done may ride on the launch itself (hipExtLaunchKernel; 1 us on the host and
 // in the queue, where a recorded event is a packet of its own and takes 3): not while the stream is captured into a graph.
@@ -187,7 +182,7 @@ struct Packer {
         }
         host = S.host;
         if (own) {
-            dev_block = get_block(*own, n_dev);
+            dev_block = own->get(n_dev);
             dev = static_cast<uint8_t*>(dev_block.p);
         } else {
             if (S.dev_cap < n_dev) {
@@ -439,7 +434,6 @@ struct BuildChain { std::mutex mu; std::shared_ptr<BuildTicket> last; };
 BuildChain& build_chain() { static BuildChain* c = new BuildChain(); return *c; }
 
 struct PoolImpl {
-    size_t max_bytes = 0;
     std::mutex mu;
     std::shared_ptr<VocabImpl> vocab;           // bound at first use
     // An interned rule in its canonical form: the automaton (shared with the grammars that hold it), the canonical numbering
@@ -492,7 +486,7 @@ struct PoolImpl {
     std::vector<PlaneRow*> free_rows;
     uint64_t clock = 0;
     int64_t n_evicted = 0;
-    std::vector<Block> slabs;
+    SlabsOf<BlockList> slabs;
     // memory to clear before the next build writes to it: the rows handed out since the one before (neighbours as one
     // range).  The build enqueues the clearing inside its timed region (skipped tokens rely on the zeros).
     std::vector<std::pair<void*, size_t>> to_zero;
@@ -500,11 +494,9 @@ struct PoolImpl {
         for (auto& z : to_zero) HIP_CHECK(hipMemsetAsync(z.first, 0, z.second, stream));
         to_zero.clear();
     }
-    uint8_t* slab_cur = nullptr; size_t slab_left = 0;
-    size_t device_bytes = 0;
     int64_t n_rows = 0;
     ~PoolImpl() {
-        for (const Block& b : slabs) vocab->blocks.put(b);
+        for (const Block& b : slabs.blocks) vocab->blocks.put(b);
     }
 
     // exact interning: same hash AND same canonical form
@@ -547,23 +539,14 @@ struct PoolImpl {
     }
     // rows_ahead: how many rows the caller is about to ask for, this one included (sizes a new slab)
     PlaneRow* alloc_row(const PlaneKey& key, size_t row_bytes, size_t rows_ahead = 1) {
-        if (free_rows.empty() && slab_left < row_bytes) {
-            size_t want = std::min<size_t>(std::max<size_t>({row_bytes * 64, (size_t)8 << 20, rows_ahead * row_bytes}), (size_t)256 << 20);
-            want = std::max(want, row_bytes);
-            if (max_bytes && device_bytes + want > max_bytes) want = row_bytes * 16;
-            if (max_bytes && device_bytes + want > max_bytes) want = row_bytes;
-            if (max_bytes && device_bytes + want > max_bytes) {
-                // full: give up the least recently used rows that no live cache uses (a batch, so that the scan is rare)
-                std::vector<std::pair<uint64_t, PlaneRow*>> idle;
-                for (PlaneRow& r : row_store) if (r.in_use && r.refs == 0 && r.stamp != 0) idle.emplace_back(r.stamp, &r);
-                if (idle.empty()) throw std::length_error("cross-grammar pool is full (max_bytes reached and every row is in use)");
-                const size_t batch = std::min<size_t>(idle.size(), std::max<size_t>(64, idle.size() / 8));
-                std::partial_sort(idle.begin(), idle.begin() + (long)batch, idle.end());
-                for (size_t k = 0; k < batch; ++k) { forget(idle[k].second); ++n_evicted; }
-            } else {
-                slabs.push_back(get_block(vocab->blocks, want));
-                slab_cur = (uint8_t*)slabs.back().p; slab_left = want; device_bytes += want;
-            }
+        if (free_rows.empty() && slabs.left < row_bytes && !slabs.add(vocab->blocks, row_bytes, rows_ahead)) {
+            // full: give up the least recently used rows that no live cache uses (a batch, so that the scan is rare)
+            std::vector<std::pair<uint64_t, PlaneRow*>> idle;
+            for (PlaneRow& r : row_store) if (r.in_use && r.refs == 0 && r.stamp != 0) idle.emplace_back(r.stamp, &r);
+            if (idle.empty()) throw std::length_error("cross-grammar pool is full (max_bytes reached and every row is in use)");
+            const size_t batch = std::min<size_t>(idle.size(), std::max<size_t>(64, idle.size() / 8));
+            std::partial_sort(idle.begin(), idle.begin() + (long)batch, idle.end());
+            for (size_t k = 0; k < batch; ++k) { forget(idle[k].second); ++n_evicted; }
         }
         PlaneRow* row;
         if (!free_rows.empty()) {
@@ -572,10 +555,10 @@ struct PoolImpl {
         } else {
             row_store.emplace_back();
             row = &row_store.back();
-            row->mem = (uint32_t*)slab_cur;
-            if (!to_zero.empty() && (uint8_t*)to_zero.back().first + to_zero.back().second == slab_cur) to_zero.back().second += row_bytes;
-            else to_zero.emplace_back(slab_cur, row_bytes);
-            slab_cur += row_bytes; slab_left -= row_bytes;
+            row->mem = (uint32_t*)slabs.cur;
+            if (!to_zero.empty() && (uint8_t*)to_zero.back().first + to_zero.back().second == slabs.cur) to_zero.back().second += row_bytes;
+            else to_zero.emplace_back(slabs.cur, row_bytes);
+            slabs.cur += row_bytes; slabs.left -= row_bytes;
         }
         row->key = key; row->refs = 0; row->stamp = 0; row->no_uncertain = false; row->in_use = true;
         ++n_rows;
@@ -819,6 +802,7 @@ int32_t guarded(F&& f) {
     catch (const GrammarError& e) { return fail(XG2_EINVAL, e.what()); }
     catch (const HipError& e) { return fail(XG2_EHIP, e.what()); }
     catch (const std::length_error& e) { return fail(XG2_EOVERFLOW, e.what()); }
+    catch (const NoDeviceMemory& e) { return fail(XG2_EHIP, e.what()); }
     catch (const std::bad_alloc&) { return fail(XG2_EOVERFLOW, "out of host memory"); }
     catch (const std::exception& e) { return fail(XG2_EINVAL, e.what()); }
 }
@@ -1539,7 +1523,7 @@ int32_t xg2_pool_create(size_t max_bytes, xg2_pool** out) {
     return guarded([&]() -> int32_t {
         if (!out) return fail(XG2_EINVAL, "xg2_pool_create: null out");
         auto p = std::make_shared<PoolImpl>();
-        p->max_bytes = max_bytes;
+        p->slabs.max_bytes = max_bytes;
         *out = new xg2_pool{p};
         return XG2_OK;
     });
@@ -1549,7 +1533,7 @@ int32_t xg2_pool_stats(const xg2_pool* p, int64_t* n_positions, int64_t* device_
     if (!p) return fail(XG2_EINVAL, "xg2_pool_stats: null pool");
     std::lock_guard<std::mutex> lk(p->p->mu);
     if (n_positions) *n_positions = p->p->n_rows;
-    if (device_bytes) *device_bytes = (int64_t)p->p->device_bytes;
+    if (device_bytes) *device_bytes = (int64_t)p->p->slabs.device_bytes;
     return XG2_OK;
 }
 

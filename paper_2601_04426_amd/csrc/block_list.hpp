@@ -1,12 +1,16 @@
 // Device blocks kept between the pools and caches of a vocabulary.  What touches the device goes through Memory, so that the
 // rules of keeping and handing out can be run on the host.
 #pragma once
+#include <algorithm>
 #include <cstddef>
 #include <cstdint>
 #include <mutex>
+#include <new>
 #include <vector>
 
 namespace xg2 {
+
+struct NoDeviceMemory : std::bad_alloc { const char* what() const noexcept override { return "no device memory left"; } };
 
 // A request's planes and tables come and go, and allocating and freeing them in the driver costs 50 - 350 us a block (it maps
 // and unmaps the memory), as much as building the planes of a small grammar.  Bounded (kMaxSpare bytes are kept, the rest is
@@ -28,18 +32,19 @@ class BlockListOf {
     BlockListOf& operator=(const BlockListOf&) = delete;
     ~BlockListOf() { drop_all(); }
 
-    // a block of at least n bytes, contents unspecified (n: what it really holds); p null if there is no memory left
-    Block get(size_t n) {
-        n = (n + 0xFFFF) & ~(size_t)0xFFFF;
+    // a block of n to `most` bytes, contents unspecified (Block::n: what it really holds); throws NoDeviceMemory
+    Block get(size_t n, size_t most = ~(size_t)0) {
+        n = std::max(n, std::min(most, (n + 0xFFFF) & ~(size_t)0xFFFF));
         Block b;
         b.device = mem_.device();
-        if (take(n, b) || (release_held() && take(n, b))) return b;
+        if (take(n, most, b) || (release_held() && take(n, most, b))) return b;
         b.p = mem_.alloc(n);
         if (!b.p) {
             drop_all();
             b.p = mem_.alloc(n);
+            if (!b.p) throw NoDeviceMemory();
         }
-        b.n = b.p ? n : 0;
+        b.n = n;
         return b;
     }
     void put(const Block& b) {
@@ -60,11 +65,12 @@ class BlockListOf {
     std::vector<Block> spare_, held_;                // nothing in flight uses them; work in flight may
     size_t kept_bytes_ = 0;                          // of both
 
-    bool take(size_t n, Block& b) {
+    bool take(size_t n, size_t most, Block& b) {
         std::lock_guard<std::mutex> lk(mu_);
+        most = std::min(most, 2 * n + ((size_t)1 << 20));
         size_t best = spare_.size();
         for (size_t k = 0; k < spare_.size(); ++k)                  // the smallest that fits, unless it is far too large
-            if (spare_[k].device == b.device && spare_[k].n >= n && spare_[k].n <= 2 * n + ((size_t)1 << 20) && (best == spare_.size() || spare_[k].n < spare_[best].n)) best = k;
+            if (spare_[k].device == b.device && spare_[k].n >= n && spare_[k].n <= most && (best == spare_.size() || spare_[k].n < spare_[best].n)) best = k;
         if (best == spare_.size()) return false;
         b = spare_[best];
         kept_bytes_ -= b.n;
@@ -98,6 +104,29 @@ class BlockListOf {
             if (freed) kept_bytes_ -= b.n;
             else held_.push_back(b);
         }
+    }
+};
+
+// The memory a pool's rows lie in: slabs from the list, together never more than max_bytes (0: no bound).
+template <class List>
+struct SlabsOf {
+    size_t max_bytes = 0;
+    std::vector<typename List::Block> blocks;
+    uint8_t* cur = nullptr; size_t left = 0;         // the part of the latest slab that no row has yet
+    size_t device_bytes = 0;                         // of all slabs, as large as they really are
+
+    // a new slab with room for a row at least, sized by the rows the caller is about to ask for; false: max_bytes is reached
+    bool add(List& list, size_t row_bytes, size_t rows_ahead) {
+        const size_t room = max_bytes ? max_bytes - device_bytes : ~(size_t)0;
+        size_t want = std::min<size_t>(std::max<size_t>({row_bytes * 64, (size_t)8 << 20, rows_ahead * row_bytes}), (size_t)256 << 20);
+        want = std::max(want, row_bytes);
+        if (want > room) want = row_bytes * 16;
+        if (want > room) want = row_bytes;
+        if (want > room) return false;
+        const typename List::Block b = list.get(want, room);
+        blocks.push_back(b);
+        cur = static_cast<uint8_t*>(b.p); left = b.n; device_bytes += b.n;
+        return true;
     }
 };
 

@@ -114,7 +114,9 @@ void bounds() {
         CHECK(d.taken <= List::kMaxSpare && d.taken >= (size_t)900 << 20);
         const List::Block all = list.get((size_t)3 << 30);
         CHECK(all.p && list.spare_blocks() == 0);
-        CHECK(!list.get((size_t)1 << 20).p);
+        bool none = false;
+        try { list.get((size_t)1 << 20); } catch (const NoDeviceMemory&) { none = true; }
+        CHECK(none);
         list.put(all);
         d.refuses = true;                             // nor does a block go amiss that can neither be kept nor freed
         const List::Block b = list.get((size_t)2 << 30);
@@ -128,6 +130,33 @@ void bounds() {
     CHECK(d.live.empty());
 }
 
+// a pool with a bound takes no more than that from the list, whatever sizes the list has to spare, and counts what it takes
+void bounded_pool() {
+    Device d;
+    {
+        List list(FakeMemory{&d});
+        const size_t row = 57040;
+        for (size_t max_bytes : {row, 3 * row, 10 * row, (size_t)1 << 20, (size_t)5 << 20, (size_t)9 << 20, (size_t)40 << 20, (size_t)0}) {
+            std::vector<List::Block> spare;           // as the tables and planes of earlier requests leave them
+            for (size_t n : {(size_t)100 << 10, (size_t)900 << 10, (size_t)1100 << 10, (size_t)9 << 20, (size_t)12 << 20, (size_t)70 << 20}) spare.push_back(list.get(n));
+            for (const List::Block& b : spare) list.put(b);
+            SlabsOf<List> pool;
+            pool.max_bytes = max_bytes;
+            size_t rows = 0, want = max_bytes ? max_bytes / row : 2000;
+            for (;; ++rows) {
+                if (pool.left < row && (rows == 2000 || !pool.add(list, row, want > rows ? want - rows : 1))) break;
+                pool.cur += row; pool.left -= row;
+                size_t taken = 0;
+                for (const List::Block& b : pool.blocks) taken += d.live[b.p].first;
+                CHECK(taken == pool.device_bytes && (!max_bytes || taken <= max_bytes));
+            }
+            CHECK(rows >= 1 && pool.device_bytes - rows * row < (pool.blocks.size() + 1) * row);   // and nothing of a slab is left unused but its remainder
+            for (const List::Block& b : pool.blocks) list.put(b);
+        }
+    }
+    CHECK(d.live.empty());
+}
+
 }  // namespace
 
 int main() {
@@ -135,6 +164,7 @@ int main() {
     failed_wait();
     devices();
     bounds();
+    bounded_pool();
     std::puts("ok");
     return 0;
 }
