@@ -44,24 +44,6 @@ struct HipError : std::runtime_error { using std::runtime_error::runtime_error; 
         if (e_ != hipSuccess) throw HipError(std::string(#expr) + ": " + hipGetErrorString(e_));     \
     } while (0)
 
-template <typename T>
-struct DevBuf {                                    // owning device array
-    T* p = nullptr; size_t n = 0;
-    DevBuf() = default;
-    DevBuf(const DevBuf&) = delete;
-    DevBuf& operator=(const DevBuf&) = delete;
-    ~DevBuf() { if (p) (void)hipFree(p); }
-    void alloc(size_t count) {
-        if (p) { (void)hipFree(p); p = nullptr; }
-        n = count;
-        if (count) HIP_CHECK(hipMalloc((void**)&p, count * sizeof(T)));
-    }
-    void upload(const std::vector<T>& v, hipStream_t s) {
-        alloc(std::max<size_t>(v.size(), 1));
-        if (!v.empty()) HIP_CHECK(hipMemcpyAsync(p, v.data(), v.size() * sizeof(T), hipMemcpyHostToDevice, s));
-    }
-};
-
 // The device's memory as BlockListOf wants it.  The wait is a small block allocated and freed (1.4 us on an idle device, where
 // hipDeviceSynchronize takes 0.3): hipFree waits for the device too, but leaves a capture alone that another thread makes in
 // thread-local mode or anybody in relaxed mode; hipDeviceSynchronize breaks every capture there is.
@@ -89,6 +71,25 @@ struct HipMemory {
 };
 using BlockList = BlockListOf<HipMemory>;
 using Block = BlockList::Block;
+
+template <typename T>
+struct DevBuf {                                    // owning device array
+    T* p = nullptr; size_t n = 0;
+    DevBuf() = default;
+    DevBuf(const DevBuf&) = delete;
+    DevBuf& operator=(const DevBuf&) = delete;
+    ~DevBuf() { if (p) (void)hipFree(p); }
+    void alloc(size_t count) {
+        if (p) { (void)hipFree(p); p = nullptr; }
+        n = 0;                                     // (an allocation that fails leaves no size behind)
+        if (count) p = static_cast<T*>(BlockList::allocate(HipMemory(), count * sizeof(T)));
+        n = count;
+    }
+    void upload(const std::vector<T>& v, hipStream_t s) {
+        alloc(std::max<size_t>(v.size(), 1));
+        if (!v.empty()) HIP_CHECK(hipMemcpyAsync(p, v.data(), v.size() * sizeof(T), hipMemcpyHostToDevice, s));
+    }
+};
 
 // Whether the event that says that a launch is done may ride on the launch itself (hipExtLaunchKernel; 1 us on the host and
 // in the queue, where a recorded event is a packet of its own and takes 3): not while the stream is captured into a graph.
@@ -189,7 +190,7 @@ struct Packer {
                 if (S.dev) (void)hipFree(S.dev);
                 S.dev = nullptr; S.dev_cap = 0;
                 const size_t cap = std::max<size_t>(n_dev + n_dev / 2, (size_t)1 << 20);
-                HIP_CHECK(hipMalloc((void**)&S.dev, cap));
+                S.dev = static_cast<uint8_t*>(BlockList::allocate(HipMemory(), cap));
                 S.dev_cap = cap;
             }
             dev = S.dev;
@@ -724,9 +725,11 @@ struct FillWorkspace {
         if (s.cap < bytes) {
             if (s.host) (void)hipHostFree(s.host);
             if (s.dev) (void)hipFree(s.dev);
-            s.cap = std::max(bytes * 2, (size_t)1 << 20);
-            HIP_CHECK(hipHostMalloc((void**)&s.host, s.cap, hipHostMallocDefault));
-            HIP_CHECK(hipMalloc((void**)&s.dev, s.cap));
+            s.host = nullptr; s.dev = nullptr; s.cap = 0;
+            const size_t cap = std::max(bytes * 2, (size_t)1 << 20);
+            HIP_CHECK(hipHostMalloc((void**)&s.host, cap, hipHostMallocDefault));
+            s.dev = static_cast<uint8_t*>(BlockList::allocate(HipMemory(), cap));
+            s.cap = cap;
         }
         return s;
     }

@@ -10,11 +10,12 @@
 
 namespace xg2 {
 
-struct NoDeviceMemory : std::bad_alloc { const char* what() const noexcept override { return "no device memory left"; } };
+struct NoDeviceMemory : std::bad_alloc { const char* what() const noexcept override { return "device memory could not be allocated"; } };
 
 // A request's planes and tables come and go, and allocating and freeing them in the driver costs 50 - 350 us a block (it maps
 // and unmaps the memory), as much as building the planes of a small grammar.  Bounded (kMaxSpare bytes are kept, the rest is
-// freed); what is kept goes back to the driver with the vocabulary that owns the list, or when an allocation fails.
+// freed); what is kept goes back to the driver with the vocabulary that owns the list, or when an allocation fails, of this
+// list or of anything else that asks through allocate().
 // Work in flight may still use a block that is handed in, so it is handed out again only after a wait for its device, which is
 // what freeing it would have done; where the wait fails (another thread is capturing a stream), the block is held until one
 // succeeds.
@@ -27,10 +28,33 @@ class BlockListOf {
     struct Block { void* p = nullptr; size_t n = 0; int device = 0; };
     static constexpr size_t kMaxSpare = (size_t)1 << 30;
 
-    explicit BlockListOf(Memory mem = Memory()) : mem_(mem) {}
+    explicit BlockListOf(Memory mem = Memory()) : mem_(mem) {
+        std::lock_guard<std::mutex> lk(lists().mu);
+        lists().all.push_back(this);
+    }
     BlockListOf(const BlockListOf&) = delete;
     BlockListOf& operator=(const BlockListOf&) = delete;
-    ~BlockListOf() { drop_all(); }
+    ~BlockListOf() {
+        {
+            std::lock_guard<std::mutex> lk(lists().mu);
+            lists().all.erase(std::find(lists().all.begin(), lists().all.end(), this));
+        }
+        drop_all();
+    }
+
+    // n bytes of device memory that no list looks after; what the lists keep spare makes room for them
+    static void* allocate(Memory mem, size_t n) {
+        void* p = mem.alloc(n);
+        if (!p) {
+            {
+                std::lock_guard<std::mutex> lk(lists().mu);
+                for (BlockListOf* list : lists().all) list->drop_all();
+            }
+            p = mem.alloc(n);
+            if (!p) throw NoDeviceMemory();
+        }
+        return p;
+    }
 
     // a block of n to `most` bytes, contents unspecified (Block::n: what it really holds); throws NoDeviceMemory
     Block get(size_t n, size_t most = ~(size_t)0) {
@@ -38,12 +62,7 @@ class BlockListOf {
         Block b;
         b.device = mem_.device();
         if (take(n, most, b) || (release_held() && take(n, most, b))) return b;
-        b.p = mem_.alloc(n);
-        if (!b.p) {
-            drop_all();
-            b.p = mem_.alloc(n);
-            if (!b.p) throw NoDeviceMemory();
-        }
+        b.p = allocate(mem_, n);
         b.n = n;
         return b;
     }
@@ -60,6 +79,9 @@ class BlockListOf {
     size_t held_blocks() { std::lock_guard<std::mutex> lk(mu_); return held_.size(); }
 
   private:
+    struct Lists { std::mutex mu; std::vector<BlockListOf*> all; };
+    static Lists& lists() { static Lists* l = new Lists(); return *l; }      // of the process, until it ends
+
     Memory mem_;
     std::mutex mu_;                                  // not held while the device is waited for
     std::vector<Block> spare_, held_;                // nothing in flight uses them; work in flight may

@@ -130,6 +130,26 @@ void bounds() {
     CHECK(d.live.empty());
 }
 
+// memory that other buffers need is not kept from them, by this vocabulary's list or another's
+void makes_room() {
+    Device d;
+    d.left = (size_t)1 << 30;
+    {
+        List one(FakeMemory{&d}), other(FakeMemory{&d});
+        const List::Block a = one.get((size_t)400 << 20), b = other.get((size_t)400 << 20);
+        one.put(a); other.put(b);
+        void* p = List::allocate(FakeMemory{&d}, (size_t)900 << 20);
+        CHECK(p && one.spare_blocks() == 0 && other.spare_blocks() == 0);
+        bool none = false;
+        try { other.get((size_t)400 << 20); } catch (const NoDeviceMemory&) { none = true; }
+        CHECK(none);
+        CHECK(FakeMemory{&d}.free(p));
+        one.put(one.get((size_t)800 << 20));
+        other.put(other.get((size_t)800 << 20));     // from the other list's spare memory
+    }
+    CHECK(d.live.empty());
+}
+
 // a pool with a bound takes no more than that from the list, whatever sizes the list has to spare, and counts what it takes
 void bounded_pool() {
     Device d;
@@ -164,6 +184,7 @@ int main() {
     failed_wait();
     devices();
     bounds();
+    makes_room();
     bounded_pool();
     std::puts("ok");
     return 0;
