@@ -235,9 +235,10 @@ int32_t xg2_fill_next_token_bitmask_noalloc(xg2_matcher* const* matchers, int32_
 int32_t xg2_fill_last_device_us(float* out);
 
 /* What became of the re-checks of the latest fill call of this process (waits for its device work): how
- * many (row, token) pairs needed the large-capacity kernel, and whether one of them exceeded even its
- * item lists (256 items, 1024 wait entries, tokens of 1024 bytes) -- such a token's bit is left 0 although
- * the token might be allowed.  fill itself returns before the device work runs and cannot report this.   */
+ * many (row, token) pairs did not fit the short lists that one lane parses with (8 items, 12 wait entries,
+ * tokens of 16 bytes), and whether one of them exceeded even the largest (256 items, 1024 wait entries,
+ * tokens of 1024 bytes) -- such a token's bit is left 0 although the token might be allowed.  fill itself
+ * returns before the device work runs and cannot report this.                                             */
 int32_t xg2_fill_last_status(int32_t* large_capacity_tokens, int32_t* overflowed);
 
 /* A fill call returns before its kernels run, so it cannot itself report that the large-capacity re-check left a (row,

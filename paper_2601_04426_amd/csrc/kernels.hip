@@ -888,7 +888,8 @@ __device__ __forceinline__ void wave_sync() {                       // orders a 
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
 }
-// One candidate token (the same in all lanes), one wavefront.  *large: it would not have fitted the short lists of a lane.
+// One candidate token (the same in all lanes), one wavefront.  *large: it would not have fitted the short lists of a lane,
+// whatever became of it (so that the count does not depend on the way a row takes).
 __device__ __forceinline__ int recheck_wave(const DevVocab& Vd, const SlowScratch& S, const DevTables& T, const FillCtx& X, FillOwn& own, uint32_t H, uint32_t item_n, uint32_t my_item,
                                             uint32_t id, uint32_t lane, bool* large) {
     const uint32_t rank = uniform_load(Vd.rank + id);
@@ -896,6 +897,7 @@ __device__ __forceinline__ int recheck_wave(const DevVocab& Vd, const SlowScratc
     const uint32_t at = uniform_load(Vd.off + rank), n_bytes = uniform_load(Vd.off + rank + 1) - at;
     const uint4 tok16 = uniform_load(Vd.tok16 + rank);
     if (n_bytes > FILL_WAVE_BYTES) return RECHECK_OVER;
+    *large = n_bytes > 16 || item_n > (uint32_t)FILL_K;
     const uint32_t words[4] = {tok16.x, tok16.y, tok16.z, tok16.w};
     uint32_t byte = (words[(lane >> 2) & 3] >> (8 * (lane & 3))) & 0xFF;
     if (n_bytes > 16) byte = lane < n_bytes ? tab(Vd.bytes + at + lane) : 0u;
@@ -904,7 +906,7 @@ __device__ __forceinline__ int recheck_wave(const DevVocab& Vd, const SlowScratc
     WaveScan A{T, X.wait, X.off, H, own.wait, own.off, lane, max_items, 0, 0, 0, 0, 0, 0, 0, 0, false, false};
     if (item_n > max_items) return RECHECK_OVER;
     A.la = lane_value(cls_of, 0);
-    uint32_t cur = my_item, cur_n = item_n, cur_to = A.next_of(lane < cur_n, cur), n_own = 0, most = item_n;
+    uint32_t cur = my_item, cur_n = item_n, cur_to = A.next_of(lane < cur_n, cur), n_own = 0;
     if (lane == 0) own.off[0] = 0;
     for (uint32_t i = 0; i < n_bytes; ++i) {
         A.set_idx = H + i;
@@ -913,15 +915,14 @@ __device__ __forceinline__ int recheck_wave(const DevVocab& Vd, const SlowScratc
         const bool alive = A.step(cur, cur_to, cur_n);
         if (A.full) return RECHECK_OVER;
         if (!alive) return RECHECK_NO;
+        *large |= A.n > (uint32_t)FILL_K || n_own + A.n_w > (uint32_t)FILL_WM;
         if (n_own + A.n_w > max_waits) return RECHECK_OVER;
         wave_sync();
         if (lane < A.n_w) own.wait[n_own + lane] = make_uint2(A.w_rule, A.w_tgt);
         n_own += A.n_w;
         if (lane == 0) own.off[i + 1] = n_own;
         cur = A.item; cur_to = A.to; cur_n = A.n;
-        if (cur_n > most) most = cur_n;
     }
-    *large = most > (uint32_t)FILL_K || n_own > (uint32_t)FILL_WM || n_bytes > 16;
     return RECHECK_YES;
 }
 
@@ -1140,8 +1141,9 @@ __global__ __launch_bounds__(FILL_THREADS) __attribute__((amdgpu_waves_per_eu(6)
                 if (v == FILL_NONE || !(v & FILL_OVER)) continue;
                 id = v & ~FILL_OVER;
             }
-            bool large = !wave_way;
+            bool large = false;
             const int res = __any(accepts) ? RECHECK_NO : recheck_wave(Vd, S, T, ctx, sh_own[wave], r.H, r.item_n, my_item, id, lane, &large);
+            large |= !wave_way;
             if (lane == 0) {
                 sh_surv[t] = res == RECHECK_YES ? id : res == RECHECK_OVER ? (id | FILL_OVER) : FILL_NONE;
                 if (large && res != RECHECK_OVER) atomicAdd(S.count, 1u);
