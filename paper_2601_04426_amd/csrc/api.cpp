@@ -399,12 +399,13 @@ using PlaneKey = std::array<int64_t, 5>;   // the fifth word: number of the oute
 struct PlaneKeyHash { uint64_t operator()(const PlaneKey& k) const { uint64_t h = 0; for (int64_t w : k) { h = (h ^ (uint64_t)w) * 0x9FB21C651E98DF25ull; h ^= h >> 32; } return h; } };
 struct PoolImpl;
 struct BuildTicket;
+constexpr uint32_t kNotCounted = 0xFFFFFFFFu;   // uncertain tokens of a plane whose build nobody has looked at yet
 // A row of device memory that holds a plane (accepted; uncertain at + W words, left early at + 2 W, list of uncertain tokens).
 struct PlaneRow {
     uint32_t* mem = nullptr;
     PlaneKey key{};
     int32_t refs = 0; uint64_t stamp = 0;       // live caches that use it, and when one last took it
-    bool no_uncertain = false;                  // its uncertain plane is all zero (need not be read)
+    uint32_t n_uncertain = kNotCounted;         // tokens in its uncertain row (none: it need not be read)
     bool in_use = false;                        // it holds a plane (listed under its key unless the build failed), else it is free
     std::shared_ptr<BuildTicket> building;      // the build that writes it, until that is finalised
     uint64_t build_serial = 0; uint32_t build_index = 0;   // its place in the build being planned
@@ -561,7 +562,7 @@ struct PoolImpl {
             else to_zero.emplace_back(slabs.cur, row_bytes);
             slabs.cur += row_bytes; slabs.left -= row_bytes;
         }
-        row->key = key; row->refs = 0; row->stamp = 0; row->no_uncertain = false; row->in_use = true;
+        row->key = key; row->refs = 0; row->stamp = 0; row->n_uncertain = kNotCounted; row->in_use = true;
         ++n_rows;
         return row;
     }
@@ -571,7 +572,7 @@ struct PoolImpl {
 struct PlaneInfo {
     int32_t rule, state, parent_rule, parent_state;         // the representative it is built for
     PlaneRow* row;                                          // null until built
-    bool no_uncertain;
+    uint32_t n_uncertain;                                   // as in the row, once its build has been looked at
     PlaneKey key;                                           // identity in the pool
     uint32_t sid; int64_t waiter_sid;                       // start of the build: position, and the waiting parent state or -1
     int32_t site = -1;                                      // which of the rule's sites the parent is (index into site_keys), or -1
@@ -593,8 +594,8 @@ struct CacheImpl {
     std::vector<std::shared_ptr<BuildTicket>> jit_tickets;  // builds issued by fill calls whose device time has not been added up yet
     double host_lower_ms = 0;                               // EBNF -> tables and plan, of the compile call
     int64_t compile_built = 0;
-    // Some state's expansion alone has more items than the short lists of the re-check hold: in such a grammar many candidates
-    // of a row may outgrow them, and the fill leaves those to a launch of its own instead of to the row's workgroup.
+    // Some state's expansion alone does not fit the short lists of the re-check: in such a grammar many candidates of a row may
+    // outgrow them.
     bool wide = false;
     std::vector<uint32_t> site_off, site_tgt;               // per rule: states in which referencing rules continue
     int64_t n_built = 0, jit_calls = 0;                     // planes holding a row; build launches issued by fill
@@ -615,7 +616,7 @@ struct CacheImpl {
         DevBuf<uint32_t> pair_off, pair_key, site_rep, site_of_off, start_items, start_wait_off;
         DevBuf<uint2> start_wait, site_of;
         CacheDev cd{};
-        uint32_t n_start_wait = 0;
+        uint32_t n_start_wait = 0, most_uncertain = 0;       // (of a plane)
     } on_device;
     std::vector<std::array<uint32_t, 8>> fb_same;           // first-byte sets that planes share with the plane of their rule's start state
     std::vector<int32_t> plain_plane;                       // [sid] -> plane without context, or -1
@@ -653,12 +654,19 @@ struct MatcherImpl {
     }
 };
 
-constexpr uint32_t kWideExpansion = 12;
-// How many lanes of the large-capacity scratch each row of a fill gets for itself (its workgroup has six wavefronts; the
-// sequential way of a row needs two), or 0 if the rows are too many or a grammar is wide: k_recheck_slow is launched then.
-inline uint32_t lanes_per_row(uint32_t n_lanes, size_t B, bool wide) {
-    const size_t per = n_lanes / B;
-    return wide || per < 2 ? 0u : (uint32_t)std::min<size_t>(per, 6);
+// What the rows of a fill may ask of k_fill: the most uncertain tokens of a frontier plane and (if they are known) of a whole
+// frontier, whether some context is too large to parse from in a row's workgroup, and whether tokens may outgrow a lane's lists
+// in numbers (a wide grammar, tokens longer than a lane takes).
+struct FillLoad { uint32_t plane_tokens = 0, row_tokens = 0; bool deep = false, large = false; };
+// How many lanes of the large-capacity scratch each row of a fill gets for itself (its workgroup has six wavefronts), and whether
+// k_recheck_slow is launched behind k_fill.  That costs every call 2.5 - 4 us, so it is done only where there are too few lanes,
+// where a row goes word by word or its context is too large, or where the batch is small enough that a row's many large tokens
+// are better spread over the device (k_fill has the figures).
+inline void share_out(FillBatch& F, uint32_t n_lanes, const FillLoad& load) {
+    const uint32_t per = n_lanes / F.B;
+    F.own_lanes = per < 2 ? 0u : std::min<uint32_t>(per, 6);
+    F.follows = F.own_lanes == 0 || load.deep || load.plane_tokens > kFillPlaneTokens || load.row_tokens > kFillRowTokens
+                || (F.B <= kFillSpreadRows && load.large && std::max(load.plane_tokens, load.row_tokens) > kFillWaveTokens);
 }
 
 // ---- fill workspace: pinned staging ring + device mirror ---------------------------------------------------
@@ -697,7 +705,7 @@ struct FillWorkspace {
     // the latest fill is F, preceded by an upload kernel or not
     void stamped(const FillBatch& F, const SlowScratch& S, bool uploaded) {
         stamps_from = uploaded ? 0 : kStampsRows;
-        n_stamps = kStampsRows + kStampsPerRow * F.B + (F.own_lanes ? 0 : S.n_lanes / 64);
+        n_stamps = kStampsRows + kStampsPerRow * F.B + (F.follows ? S.n_lanes / 64 : 0);
     }
     // microseconds from the first of them to the last
     float stamped_us() {
@@ -853,7 +861,7 @@ void finalize_ticket(BuildTicket& T) {
             pool.unlist(row);
         } else {
             const uint32_t n_acc = S.res[4 + 2 * k], n_unc = S.res[5 + 2 * k];
-            row->no_uncertain = n_unc == 0;
+            row->n_uncertain = n_unc;
             if (row->key[4] != 0) pool.by_structure.emplace(PoolImpl::structure_of(row->key), row);
             T.n_accepted += n_acc; T.n_uncertain += n_unc;
         }
@@ -880,7 +888,7 @@ void finalize_cache(CacheImpl& cache) {
     cache.tickets.clear();
     for (int32_t k : cache.fresh_planes) {
         PlaneInfo& pi = cache.planes[(size_t)k];
-        pi.no_uncertain = pi.row && pi.row->no_uncertain;
+        pi.n_uncertain = pi.row ? pi.row->n_uncertain : kNotCounted;
     }
     cache.fresh_planes.clear();
 }
@@ -936,7 +944,7 @@ int32_t build_planes(CacheImpl& cache, const std::vector<int32_t>& todo, hipStre
         if (pi.row) continue;
         if (PlaneRow** have = pool.rows.find(pi.key)) {          // another grammar built it, or is building it
             PlaneRow* row = *have;
-            pi.row = row; pi.no_uncertain = row->no_uncertain; pool.take(row); ++cache.n_built;
+            pi.row = row; pi.n_uncertain = row->n_uncertain; pool.take(row); ++cache.n_built;
             if (row->building) {
                 if (cache.tickets.empty() || cache.tickets.back() != row->building)
                     if (std::find(cache.tickets.begin(), cache.tickets.end(), row->building) == cache.tickets.end()) cache.tickets.push_back(row->building);
@@ -1274,7 +1282,7 @@ int32_t build_planes(CacheImpl& cache, const std::vector<int32_t>& todo, hipStre
     for (size_t k = 0; k < n_build; ++k) {
         PlaneInfo& pi = cache.planes[(size_t)build[k]];
         pi.row = rows[k];
-        pi.no_uncertain = false;                                    // not known yet
+        pi.n_uncertain = kNotCounted;
         pool.take(rows[k]);
         rows[k]->building = ticket;
     }
@@ -1358,7 +1366,7 @@ struct BatchImpl {
     std::vector<std::shared_ptr<CacheImpl>> caches;
     std::vector<uint8_t> assigned;
     int32_t n_assigned = 0;
-    bool wide = false;                                      // some cache is
+    FillLoad load;                                          // of the caches (a slot's context and frontier always fit)
 };
 
 struct xg2_batch { std::unique_ptr<BatchImpl> p; };
@@ -1376,7 +1384,7 @@ void ensure_cache_on_device(const std::shared_ptr<CacheImpl>& cp) {
     const size_t n_states = (size_t)C.gram->g.n_states;
     auto row_word = [&](int32_t plane, bool accepted_only) {
         const PlaneInfo& pi = C.planes[(size_t)plane];
-        return (uint64_t)(uintptr_t)pi.row->mem | ((accepted_only || pi.no_uncertain) ? 1u : 0u);
+        return (uint64_t)(uintptr_t)pi.row->mem | ((accepted_only || pi.n_uncertain == 0) ? 1u : 0u);
     };
     std::vector<uint64_t> plain(n_states, 0);
     for (size_t sid = 0; sid < n_states; ++sid) if (C.plain_plane[sid] >= 0) plain[sid] = row_word(C.plain_plane[sid], false);
@@ -1437,6 +1445,7 @@ void ensure_cache_on_device(const std::shared_ptr<CacheImpl>& cp) {
     D.cd.start_flags = M.chart.last().root_done ? 1u : 0u;
     D.cd.start_items = D.start_items.p; D.cd.start_wait = D.start_wait.p; D.cd.start_wait_off = D.start_wait_off.p; D.cd.start_front = D.start_front.p;
     D.n_start_wait = (uint32_t)s_wait.size();
+    for (const PlaneInfo& pi : C.planes) D.most_uncertain = std::max(D.most_uncertain, pi.n_uncertain);
     D.ready = true;
 }
 
@@ -1560,7 +1569,7 @@ int32_t xg2_compile_grammar(xg2_vocab* vocab, const char* ebnf, size_t len, cons
         cache->gram = make_grammar(ebnf, len, root_rule);
         const Grammar& g = cache->gram->g;
         const FlatTables& ft = cache->gram->ft;
-        for (const DevState& ds : ft.dev_state) cache->wide |= ds.n_items > kWideExpansion;
+        for (const DevState& ds : ft.dev_state) cache->wide |= ds.n_items > kFillLaneItems || ds.n_triples > kFillLaneWaits;
         VocabImpl& V = *vocab->p;
         V.ensure_device();
         cache->pool = pool_h ? pool_h->p : std::make_shared<PoolImpl>();
@@ -1690,7 +1699,7 @@ int32_t xg2_compile_grammar(xg2_vocab* vocab, const char* ebnf, size_t len, cons
             }
             const auto lp = local_plane.emplace(key, (int32_t)cache->planes.size());
             if (!lp.second) return *lp.first;
-            cache->planes.push_back({rp, sp_rep, site ? site->q : -1, site ? site->x : -1, nullptr, false, key, (uint32_t)g.sid(rp, sp_rep),
+            cache->planes.push_back({rp, sp_rep, site ? site->q : -1, site ? site->x : -1, nullptr, kNotCounted, key, (uint32_t)g.sid(rp, sp_rep),
                                      site ? (int64_t)g.sid(site->q, site->waiter) : -1, site_index, cost});
             return *lp.first;
         };
@@ -2177,12 +2186,14 @@ int32_t fill_common(xg2_matcher* const* matchers, int32_t B, int32_t* bitmask_de
         std::vector<uint32_t> items, wait, wait_off;
         std::vector<DevTables> tables;
         std::map<const CacheImpl*, uint32_t> table_idx;
+        FillLoad load;
+        load.large = V.max_len > kFillLaneBytes;
         for (int32_t b = 0; b < B; ++b) {
             const MatcherImpl& M = *matchers[b]->p;
             FillRow& r = rows[(size_t)b];
             std::memset(&r, 0, sizeof(r));
             auto ti = table_idx.find(M.cache.get());
-            if (ti == table_idx.end()) { ti = table_idx.emplace(M.cache.get(), (uint32_t)tables.size()).first; tables.push_back(M.cache->dt); }
+            if (ti == table_idx.end()) { ti = table_idx.emplace(M.cache.get(), (uint32_t)tables.size()).first; tables.push_back(M.cache->dt); load.large |= M.cache->wide; }
             r.tables_idx = ti->second;
             r.front_off = (uint32_t)front.size();
             r.item_off = (uint32_t)items.size();
@@ -2192,14 +2203,23 @@ int32_t fill_common(xg2_matcher* const* matchers, int32_t B, int32_t* bitmask_de
             r.flags = M.chart.last().root_done ? 1u : 0u;
             const ScanContext& ctx = M.prep.ctx;
             size_t f0 = front.size();
+            uint64_t tokens = 0;
             for (auto& pl : M.prep.planes) {
                 const PlaneInfo& pi = M.cache->planes[(size_t)pl.first];
-                uint64_t row = (uint64_t)(uintptr_t)pi.row->mem | ((pl.second || pi.no_uncertain) ? 1u : 0u);
+                if (!pl.second) {
+                    // not counted yet (being built for this very call): few where the follow language filters them inside a parent
+                    const uint32_t n = pi.n_uncertain == kNotCounted && M.cache->follow && M.cache->context_depth == 2 ? 0u : pi.n_uncertain;
+                    load.plane_tokens = std::max(load.plane_tokens, n);
+                    tokens += n;
+                }
+                uint64_t row = (uint64_t)(uintptr_t)pi.row->mem | ((pl.second || pi.n_uncertain == 0) ? 1u : 0u);
                 if (std::find(front.begin() + (long)f0, front.end(), row) == front.end()) front.push_back(row);
             }
+            load.row_tokens = (uint32_t)std::max<uint64_t>(load.row_tokens, std::min<uint64_t>(tokens, kNotCounted));
             r.front_n = (uint32_t)(front.size() - f0);
             r.item_n = (uint32_t)ctx.items.size();
             r.H = ctx.H;
+            load.deep |= r.front_n > 64 || r.item_n > kFillContextItems || r.H > kFillContextSets || ctx.wait.size() / 2 > kFillContextWaits;
             items.insert(items.end(), ctx.items.begin(), ctx.items.end());
             wait.insert(wait.end(), ctx.wait.begin(), ctx.wait.end());
             wait_off.insert(wait_off.end(), ctx.wait_off.begin(), ctx.wait_off.end());
@@ -2284,12 +2304,10 @@ int32_t fill_common(xg2_matcher* const* matchers, int32_t B, int32_t* bitmask_de
         F.tables = reinterpret_cast<const DevTables*>(dev + o_tabs);
         F.eos_id = (uint32_t)V.eos;
         S.count = reinterpret_cast<uint32_t*>(dev + o_zero);               // this call's overflow counter and flag, zero on arrival
-        bool wide = false;
-        for (auto& t : table_idx) wide |= t.first->wide;
-        F.own_lanes = lanes_per_row(S.n_lanes, (size_t)B, wide);
-        const bool ride = slot && F.own_lanes && events_ride(stream);    // (k_fill is the last launch)
+        share_out(F, S.n_lanes, load);
+        const bool ride = slot && !F.follows && events_ride(stream);    // (k_fill is the last launch)
         launch_fill(F, V.dv, bitmask_dev, row_stride_words, S, stream, ride ? slot->done : nullptr);
-        if (!F.own_lanes) launch_recheck_slow(F, V.dv, bitmask_dev, row_stride_words, S, stream);
+        if (F.follows) launch_recheck_slow(F, V.dv, bitmask_dev, row_stride_words, S, stream);
         HIP_CHECK(hipGetLastError());
         fill_ws().last_flags = S.count;
         fill_ws().last_counts = F.row_count;
@@ -2389,9 +2407,9 @@ int32_t xg2_fill_last_status(int32_t* large_capacity_tokens, int32_t* overflowed
         std::lock_guard<std::mutex> ws_lock(fill_ws().mu);
         if (!fill_ws().any) return fail(XG2_EINVAL, "xg2_fill_last_status: no fill call yet");
         fill_ws().wait_last();
-        uint32_t words[2] = {0, 0};
+        uint32_t words[4] = {0, 0, 0, 0};
         HIP_CHECK(hipMemcpy(words, fill_ws().last_flags, sizeof(words), hipMemcpyDeviceToHost));
-        if (large_capacity_tokens) *large_capacity_tokens = (int32_t)words[0];
+        if (large_capacity_tokens) *large_capacity_tokens = (int32_t)words[3];
         if (overflowed) *overflowed = words[1] ? 1 : 0;
         return XG2_OK;
     });
@@ -2478,7 +2496,8 @@ int32_t xg2_batch_assign(xg2_batch* batch, const int32_t* rows_host, int32_t n, 
         if (ci == Bt.caches.size()) {
             if (ci >= BatchImpl::kMaxCaches) return fail(XG2_EOVERFLOW, "xg2_batch_assign: too many different caches in one batch");
             Bt.caches.push_back(cache->p);                      // kept alive while the batch lives
-            Bt.wide |= cache->p->wide;
+            Bt.load.large |= cache->p->wide || Bt.vocab->max_len > kFillLaneBytes;
+            Bt.load.plane_tokens = std::max(Bt.load.plane_tokens, od.most_uncertain);
             HIP_CHECK(hipMemcpyAsync(Bt.caches_dev.p + ci, &od.cd, sizeof(CacheDev), hipMemcpyHostToDevice, stream));
             HIP_CHECK(hipMemcpyAsync(Bt.tables_dev.p + ci, &od.cd.T, sizeof(DevTables), hipMemcpyHostToDevice, stream));
         }
@@ -2531,11 +2550,11 @@ int32_t xg2_batch_fill_next_token_bitmask(xg2_batch* batch, int32_t* bitmask_dev
         Bt.flag_turn ^= 1;
         F.zero_words = Bt.flag_words.p + 4 * Bt.flag_turn;
         S.mark_rows = Bt.d.rows;                                // an undecided pair makes its slot unusable: the next accept says so
-        F.own_lanes = lanes_per_row(S.n_lanes, (size_t)Bt.B, Bt.wide);
+        share_out(F, S.n_lanes, Bt.load);
         // no event is recorded: the two that used to time the call held up the kernels behind it by 6 - 7 us a step
         F.stamps = fill_ws().stamps.p;
         launch_fill(F, V.dv, bitmask_dev, row_stride_words, S, stream);
-        if (!F.own_lanes) launch_recheck_slow(F, V.dv, bitmask_dev, row_stride_words, S, stream);
+        if (F.follows) launch_recheck_slow(F, V.dv, bitmask_dev, row_stride_words, S, stream);
         HIP_CHECK(hipGetLastError());
         fill_ws().stamped(F, S, false);
         fill_ws().last_flags = S.count; fill_ws().last_counts = F.row_count; fill_ws().last_B = Bt.B;

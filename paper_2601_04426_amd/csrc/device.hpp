@@ -65,7 +65,8 @@ struct FillRow;
 struct SlowScratch {                     // large-capacity per-lane Earley scratch in device memory
     uint32_t* mem; uint32_t n_lanes;     // mem holds n_lanes * kSlowSlots words
     uint32_t* list; uint32_t list_cap;   // overflow work list: pairs (a, b)
-    uint32_t* count;                     // [0] = entries in list, [1] = sticky error flag
+    uint32_t* count;                     // [0] = entries in list, [1] = sticky error flag; fill only: [2] = undecided pairs, [3] = pairs
+                                         // that did not fit a lane's lists, whoever took them
     uint32_t k_cap, wm_cap;              // item and wait-entry capacity in use (at most kSlowK, kSlowWM; smaller only in tests
                                          // of the overflow handling); below the LDS lists' 16 / 32 those are skipped
     // fill only: where the (row, token) pairs that even these lists could not decide are reported: a counter and a list in
@@ -145,12 +146,20 @@ struct FillBatch {
     uint32_t* row_count;                 // [B], written by the fill kernel: candidate tokens of the row
     uint32_t* zero_words;                // if not null: four words the fill kernel clears for the next call (the overflow list's length
                                          // and flag, where no upload brings them in as zeros: two sets take turns)
-    uint32_t own_lanes;                  // lanes of the large-capacity scratch that are a row's own: it then decides every token itself;
-                                         // 0: what outgrows the short lists is left to k_recheck_slow
+    uint32_t own_lanes;                  // lanes of the large-capacity scratch that are a row's own while k_fill runs, or 0: there are too few
+    uint32_t follows;                    // k_recheck_slow is launched behind it and takes what the rows leave on the overflow list (always
+                                         // if own_lanes is 0)
     uint64_t* stamps;                    // if not null: when the call's work started and ended, on the device's constant-rate clock:
                                          // [0] the upload kernel's start; kStampsPerRow words for each row (start, end of each of
                                          // its wavefronts); the end of each workgroup of k_recheck_slow
 };
+// What k_fill handles how (the host decides by the same numbers whether k_recheck_slow follows).
+constexpr uint32_t kFillLaneItems = 8, kFillLaneWaits = 12, kFillLaneBytes = 16;    // lists and bytes of a lane that parses a token by itself
+constexpr uint32_t kFillWaveTokens = 24;                     // up to that many tokens of a row get a wavefront each
+constexpr uint32_t kFillSpreadRows = 192;                    // in batches up to that size, a row with more tokens that outgrow a lane leaves them to k_recheck_slow
+constexpr uint32_t kFillPlaneTokens = kUncListWords - 1;     // with more uncertain tokens in a frontier plane (than its list holds), or in a
+constexpr uint32_t kFillRowTokens = 2048;                    //   frontier (than any slot's can have otherwise), a row is worked through word by word
+constexpr uint32_t kFillContextItems = 64, kFillContextSets = 240, kFillContextWaits = 512;   // contexts that wavefronts parse from (every slot's)
 constexpr uint32_t kStampsRows = 1, kStampsPerRow = 7;
 void launch_fill(const FillBatch& F, const DevVocab& Vd, int32_t* bitmask_dev, int64_t row_stride_words,
                  const SlowScratch& S, hipStream_t stream, hipEvent_t done = nullptr);
@@ -180,6 +189,8 @@ struct CacheDev {
 // wait_off[(c * B + b) * (KH + 1) ..].  Accepting a token writes the other buffer and switches.  rows[b].pad[1] holds a
 // sticky error (a capacity was exceeded: the slot is unusable until it is reset), rows[b].tables_idx the slot's cache.
 constexpr uint32_t kSlotItems = 64, kSlotSets = 240, kSlotWaits = 512, kSlotPlanes = 32;   // capacities of a matcher slot
+static_assert(kSlotItems <= kFillContextItems && kSlotSets <= kFillContextSets && kSlotWaits <= kFillContextWaits, "wavefronts can parse from every slot's context");
+static_assert(kSlotPlanes * kFillPlaneTokens <= kFillRowTokens, "a slot's row goes word by word only for a plane without a list");
 struct BatchDev {
     uint32_t B, KI, KH, KW, KF;                          // KI .. KF: the four capacities above
     FillRow* rows;

@@ -162,6 +162,15 @@ __device__ __forceinline__ void push_overflow(const SlowScratch& S, uint32_t a, 
     else atomicOr(S.count + 1, 1u);
 }
 
+// The same for a fill: no room left is the caller's business.
+__device__ __forceinline__ bool try_push(const SlowScratch& S, uint32_t b, uint32_t id) {
+    if (*reinterpret_cast<volatile uint32_t*>(S.count) >= S.list_cap) return false;      // (the count does not run on and on)
+    const uint32_t at = atomicAdd(S.count, 1u);
+    if (at >= S.list_cap) return false;
+    S.list[2 * at] = b; S.list[2 * at + 1] = id;
+    return true;
+}
+
 __device__ __forceinline__ DevCtx position_ctx(const BuildPlan& P, uint32_t p) {
     const uint4 d = P.plane_ctx[p];
     DevCtx C;
@@ -821,10 +830,15 @@ struct WaveScan {
 // takes several dependent accesses), the union team joining in when it is done; a row with more gives each a lane.
 // A row with a frontier plane whose uncertain tokens do not fit its list (or with more candidates than the LDS list
 // holds) takes the sequential way: the union team also reads the uncertain rows and lists the words with candidates,
-// the re-check team starts when the union is done.
-// A token that outgrows the short lists (or 16 bytes) is tried by a wavefront, then with lists in device memory, by the
-// row's own workgroup (own_lanes): a second launch for the few such tokens cost 2.5 - 4 us on every call.  Where they are
-// many (a grammar with wide expansions, see launch_fill's caller) they are left to k_recheck_slow.
+// the re-check team starts when the union is done, a lane each.
+// A token that outgrows a lane's lists (or 16 bytes) goes to a wavefront, one that outgrows that too to lists in device memory,
+// all in the row's own workgroup (own_lanes): a second launch for the few such tokens cost 2.5 - 4 us on every call.
+// A workgroup has six wavefronts, though, and k_recheck_slow 4,096 lanes over the device.  Where a row of a small batch may
+// have many such tokens the host launches it behind this kernel, and a row with more than FILL_WAVE_TOKENS of them leaves them
+// to it.  Tokens of 20 - 40 bytes, us a call, all by wavefronts / by the launch behind:
+// 63 a row, 1 row 325 / 107, 256 rows 329 / 421, 1,024 rows 685 / 1,611 (six wavefronts a row against 4,096 lanes in all), so the
+// line lies at FILL_SPREAD_ROWS.  The sequential way, which has no bound on its tokens, leaves all of them to it (100 a row,
+// 1 row: 112 us; one lane of the workgroup after another took 5,433).
 // Four wavefronts stream, two re-check with half of their lanes at work (measured: fewer lanes per wavefront, more
 // wavefronts or another split of the six gain nothing; a larger workgroup lowers the number of rows a compute unit holds).
 constexpr int FILL_OR_WAVES = 4, FILL_RECHECK_WAVES = 2;
@@ -833,11 +847,13 @@ constexpr int FILL_COLS = FILL_RECHECK_WAVES * FILL_RECHECK_LANES;  // tokens th
 constexpr int FILL_OR_THREADS = 64 * FILL_OR_WAVES;
 constexpr int FILL_THREADS = 64 * (FILL_OR_WAVES + FILL_RECHECK_WAVES);
 constexpr int FILL_BLOCK = 5;                          // steps of the union whose loads are issued together
-constexpr int FILL_K = 8, FILL_WM = 12;
-constexpr uint32_t FILL_SPARSE_CAP = 512;              // candidates of a row that the side-by-side way handles
+constexpr int FILL_K = kFillLaneItems, FILL_WM = kFillLaneWaits;
+constexpr uint32_t FILL_SPREAD_ROWS = kFillSpreadRows;
+constexpr uint32_t FILL_SPARSE_CAP = kFillRowTokens;   // candidates of a row that the side-by-side way handles
 constexpr uint32_t FILL_NONE = 0xFFFFFFFFu, FILL_OVER = 0x80000000u;   // what became of a candidate: rejected; did not fit the lists tried
-constexpr uint32_t FILL_WAVE_TOKENS = 24;              // up to that many candidates get a wavefront each (six at a time, ~3 us each; a lane each: ~12 us for any number)
-constexpr uint32_t FILL_CTX_WAITS = 128, FILL_CTX_SETS = 64, FILL_OWN_WAITS = 128, FILL_WAVE_BYTES = 64;   // what a wavefront's parse has room for
+// Up to that many candidates get a wavefront each (six at a time, ~3 us each; a lane each: ~12 us for any number).
+constexpr uint32_t FILL_WAVE_TOKENS = kFillWaveTokens;
+constexpr uint32_t FILL_CTX_WAITS = kFillContextWaits, FILL_CTX_SETS = kFillContextSets, FILL_OWN_WAITS = 128, FILL_WAVE_BYTES = 64;   // what a wavefront's parse has room for
 using FillStore = LdsStore<FILL_K, FILL_WM, FILL_COLS>;
 
 __device__ __forceinline__ DevCtx row_ctx(const FillBatch& F, const FillRow& r) {
@@ -926,9 +942,19 @@ __device__ __forceinline__ int recheck_wave(const DevVocab& Vd, const SlowScratc
     return RECHECK_YES;
 }
 
-// One (row, token) pair that outgrew every shorter list: one lane, item lists in device memory (lane gl of the scratch).  A
-// pair that even these cannot decide keeps its bit 0, and the call must not pass for complete: the pair goes to the host's
-// list (it can decide it with its own parser), a slot on the device is marked unusable.
+// A pair that nobody decides keeps its bit 0, and the call must not pass for complete: the pair goes to the host's list (it can
+// decide it with its own parser), a slot on the device is marked unusable.
+__device__ __forceinline__ void leave_undecided(const SlowScratch& S, uint32_t b, uint32_t id) {
+    atomicOr(S.count + 1, 2u);
+    if (S.mark_rows) S.mark_rows[b].pad[1] = 2u;
+    if (S.unresolved) {                                              // plain stores only: the list is host memory
+        const uint32_t at = atomicAdd(S.count + 2, 1u);
+        S.unresolved[0] = 1u;
+        if (at < S.unresolved_cap) { S.unresolved[2 + 2 * at] = b; S.unresolved[3 + 2 * at] = id; }
+        else S.unresolved[1] = 1u;
+    }
+}
+// One (row, token) pair that outgrew every shorter list: one lane, item lists in device memory (lane gl of the scratch).
 __device__ __forceinline__ bool recheck_large(const FillBatch& F, const DevVocab& Vd, const SlowScratch& S, const FillRow& r, uint32_t b, uint32_t id, uint32_t gl) {
     const uint32_t rank = Vd.rank[id];
     if (rank >= Vd.n_sorted) return false;
@@ -941,14 +967,7 @@ __device__ __forceinline__ bool recheck_large(const FillBatch& F, const DevVocab
     st.reset();
     const int res = scan_token<GlobalStore, false, MemBytes>(T, T.byte_class_words, row_ctx(F, r), tok, n, st);
     if (!(res & RES_OVERFLOW)) return (res & RES_ALIVE) != 0;
-    atomicOr(S.count + 1, 2u);
-    if (S.mark_rows) S.mark_rows[b].pad[1] = 2u;
-    if (S.unresolved) {                                              // plain stores only: the list is host memory
-        const uint32_t at = atomicAdd(S.count + 2, 1u);
-        S.unresolved[0] = 1u;
-        if (at < S.unresolved_cap) { S.unresolved[2 + 2 * at] = b; S.unresolved[3 + 2 * at] = id; }
-        else S.unresolved[1] = 1u;
-    }
+    leave_undecided(S, b, id);
     return false;
 }
 
@@ -1034,14 +1053,14 @@ __global__ __launch_bounds__(FILL_THREADS) __attribute__((amdgpu_waves_per_eu(6)
     __shared__ uint32_t sh_surv[FILL_SPARSE_CAP];
     __shared__ FillCtx ctx;
     __shared__ FillOwn sh_own[FILL_THREADS / 64];
-    __shared__ uint32_t n_listed, n_cand, n_over, next_token;
+    __shared__ uint32_t n_listed, n_cand, n_over, n_large, next_token, list_at;
     const uint32_t b = blockIdx.x, lane = threadIdx.x & 63, wave = same_in_all(threadIdx.x >> 6);
     if (F.stamps && threadIdx.x == 0) F.stamps[kStampsRows + kStampsPerRow * b] = wall_clock64();
     auto stamp_end = [&]() { if (F.stamps && lane == 0) F.stamps[kStampsRows + kStampsPerRow * b + 1 + wave] = wall_clock64(); };
     const FillRow r = uniform_load(F.rows + b);
     const uint32_t front_off = r.front_off, front_n = r.front_n, flags = r.flags;
     const bool live = !(flags & 2u);
-    if (threadIdx.x == 0) { n_listed = 0; n_cand = 0; n_over = 0; next_token = 0; }
+    if (threadIdx.x == 0) { n_listed = 0; n_cand = 0; n_over = 0; n_large = 0; next_token = 0; }
     if (F.zero_words && b == 0 && threadIdx.x < 4) F.zero_words[threadIdx.x] = 0;      // the words the next call counts in
     // the plan, worked out by every wavefront for itself: lane k looks at frontier plane k
     uint64_t addr = 1;
@@ -1062,19 +1081,18 @@ __global__ __launch_bounds__(FILL_THREADS) __attribute__((amdgpu_waves_per_eu(6)
     // whether wavefronts can parse from this row's context, and then the context in LDS
     bool ctx_fits = false;
     uint32_t n_wait = 0, my_item = 0;
-    if (parses && F.own_lanes && r.item_n <= WaveScan::N && r.H <= FILL_CTX_SETS) {
+    static_assert(kFillContextItems <= WaveScan::N, "a context's items lie across the lanes");
+    if (parses && !listed_way && r.item_n <= kFillContextItems && r.H <= FILL_CTX_SETS) {
         n_wait = uniform_load(F.ctx_wait_off + r.waitoff_off + r.H);
         ctx_fits = n_wait <= FILL_CTX_WAITS;
         if (ctx_fits) {
             if (lane < r.item_n) my_item = tab(F.ctx_items + r.item_off + lane);
             if (wave >= FILL_OR_WAVES) {
-                const uint32_t t = threadIdx.x - FILL_OR_THREADS;
-                if (t < n_wait) ctx.wait[t] = tab(F.ctx_wait + r.wait_base + t);
-                if (t <= r.H) ctx.off[t] = tab(F.ctx_wait_off + r.waitoff_off + t);
+                for (uint32_t t = threadIdx.x - FILL_OR_THREADS; t < n_wait; t += FILL_THREADS - FILL_OR_THREADS) ctx.wait[t] = tab(F.ctx_wait + r.wait_base + t);
+                for (uint32_t t = threadIdx.x - FILL_OR_THREADS; t <= r.H; t += FILL_THREADS - FILL_OR_THREADS) ctx.off[t] = tab(F.ctx_wait_off + r.waitoff_off + t);
             }
         }
     }
-    static_assert(64 * FILL_RECHECK_WAVES >= FILL_CTX_WAITS && 64 * FILL_RECHECK_WAVES > FILL_CTX_SETS, "the re-check team copies a context in one step");
     const bool wave_way = ctx_fits && !listed_way && total <= FILL_WAVE_TOKENS;
     if (parses && wave == FILL_OR_WAVES) ctx.cls_words[lane] = tab(uniform_load(&F.tables[r.tables_idx].byte_class_words) + lane);
     uint32_t* out = reinterpret_cast<uint32_t*>(bitmask) + (long long)b * row_stride;
@@ -1112,66 +1130,87 @@ __global__ __launch_bounds__(FILL_THREADS) __attribute__((amdgpu_waves_per_eu(6)
             }
         }
     }
-    bool waves_parse = wave_way && total != 0;
-    if (!listed_way && total != 0 && !wave_way) {                   // (the same for the whole row)
-        __syncthreads();
-        waves_parse = ctx_fits && n_over != 0;
-    }
-    if (waves_parse) {
-        // a wavefront per candidate, the union team joining in when its row is stored; or per token that did not fit a lane's lists
-        const DevTables T = uniform_load(F.tables + r.tables_idx);
-        for (;;) {
-            // The wavefront stays together from token to token: with nothing between "lane 0 stores a result" below and "lane 0
-            // takes the next token" here the compiler may send the other lanes round the loop without lane 0.
-            wave_sync();
-            uint32_t t = 0;
-            if (lane == 0) t = atomicAdd(&next_token, 1u);
-            wave_sync();
-            t = same_in_all(t);
-            if (t >= total) break;
-            uint32_t id;
-            bool accepts = false;
-            if (wave_way) {
-                const uint32_t k = (uint32_t)__ffsll((long long)__ballot(incl > t)) - 1;
-                const uint64_t a_k = ((uint64_t)lane_value((uint32_t)(addr >> 32), k) << 32) | lane_value((uint32_t)addr, k);
-                id = uniform_load(reinterpret_cast<const uint32_t*>(a_k) + 3 * (size_t)Vd.W + 1 + (t - (lane_value(incl, k) - lane_value(n_unc, k))));
-                if (lane < front_n) accepts = (tab(reinterpret_cast<const uint32_t*>(addr & ~(uint64_t)1) + (id >> 5)) >> (id & 31)) & 1u;
-            } else {
-                const uint32_t v = same_in_all(sh_surv[t]);
-                if (v == FILL_NONE || !(v & FILL_OVER)) continue;
-                id = v & ~FILL_OVER;
+    if (!listed_way) {
+        bool left = false;                                          // what does not fit a lane's lists, to k_recheck_slow
+        if (total != 0 && !wave_way) {                              // (the same for the whole row)
+            __syncthreads();
+            const uint32_t over = n_over;
+            if (F.follows && over > FILL_WAVE_TOKENS && (gridDim.x <= FILL_SPREAD_ROWS || !ctx_fits)) {
+                if (threadIdx.x == 0) {
+                    list_at = S.list_cap;
+                    if (*reinterpret_cast<volatile uint32_t*>(S.count) < S.list_cap) list_at = atomicAdd(S.count, over);
+                }
+                __syncthreads();
+                const uint32_t at = list_at;
+                left = at < S.list_cap && over <= S.list_cap - at;   // there is room for all of them
+                if (left)
+                    for (uint32_t t = threadIdx.x; t < total; t += FILL_THREADS) {
+                        const uint32_t id = sh_surv[t];
+                        if (id == FILL_NONE || !(id & FILL_OVER)) continue;
+                        const uint32_t k = at + atomicAdd(&next_token, 1u);
+                        S.list[2 * k] = b; S.list[2 * k + 1] = id & ~FILL_OVER;
+                        sh_surv[t] = FILL_NONE;
+                    }
+                else                                                 // what there is of it names a token that is never parsed
+                    for (uint32_t k = threadIdx.x; k < over && at < S.list_cap && k < S.list_cap - at; k += FILL_THREADS) { S.list[2 * (at + k)] = b; S.list[2 * (at + k) + 1] = F.eos_id; }
             }
-            bool large = false;
-            const int res = __any(accepts) ? RECHECK_NO : recheck_wave(Vd, S, T, ctx, sh_own[wave], r.H, r.item_n, my_item, id, lane, &large);
-            large |= !wave_way;
-            if (lane == 0) {
-                sh_surv[t] = res == RECHECK_YES ? id : res == RECHECK_OVER ? (id | FILL_OVER) : FILL_NONE;
-                if (large && res != RECHECK_OVER) atomicAdd(S.count, 1u);
-                if (res == RECHECK_OVER && wave_way) atomicAdd(&n_over, 1u);
+            if (threadIdx.x == 0) n_large = over;
+        }
+        if (wave_way ? total != 0 : ctx_fits && n_over != 0 && !left) {
+            // a wavefront per candidate, the union team joining in when its row is stored; or per token that did not fit a lane's lists
+            const DevTables T = uniform_load(F.tables + r.tables_idx);
+            for (;;) {
+                // The wavefront stays together from token to token: with nothing between "lane 0 stores a result" below and "lane 0
+                // takes the next token" here the compiler may send the other lanes round the loop without lane 0.
+                wave_sync();
+                uint32_t t = 0;
+                if (lane == 0) t = atomicAdd(&next_token, 1u);
+                wave_sync();
+                t = same_in_all(t);
+                if (t >= total) break;
+                uint32_t id;
+                bool accepts = false;
+                if (wave_way) {
+                    const uint32_t k = (uint32_t)__ffsll((long long)__ballot(incl > t)) - 1;
+                    const uint64_t a_k = ((uint64_t)lane_value((uint32_t)(addr >> 32), k) << 32) | lane_value((uint32_t)addr, k);
+                    id = uniform_load(reinterpret_cast<const uint32_t*>(a_k) + 3 * (size_t)Vd.W + 1 + (t - (lane_value(incl, k) - lane_value(n_unc, k))));
+                    if (lane < front_n) accepts = (tab(reinterpret_cast<const uint32_t*>(addr & ~(uint64_t)1) + (id >> 5)) >> (id & 31)) & 1u;
+                } else {
+                    const uint32_t v = same_in_all(sh_surv[t]);
+                    if (v == FILL_NONE || !(v & FILL_OVER)) continue;
+                    id = v & ~FILL_OVER;
+                }
+                bool large = false;
+                const int res = __any(accepts) ? RECHECK_NO : recheck_wave(Vd, S, T, ctx, sh_own[wave], r.H, r.item_n, my_item, id, lane, &large);
+                if (lane == 0) {
+                    sh_surv[t] = res == RECHECK_YES ? id : res == RECHECK_OVER ? (id | FILL_OVER) : FILL_NONE;
+                    if (wave_way && res == RECHECK_OVER) atomicAdd(&n_over, 1u);
+                    if (wave_way && (large || res == RECHECK_OVER)) atomicAdd(&n_large, 1u);
+                }
             }
         }
-    }
-    __syncthreads();
-
-    if (!listed_way) {
+        __syncthreads();
         for (uint32_t t = threadIdx.x; t < total; t += FILL_THREADS) {
             const uint32_t id = sh_surv[t];
-            if (id == FILL_NONE) continue;
-            if (!(id & FILL_OVER)) atomicOr(out + (id >> 5), 1u << (id & 31));
-            else if (!F.own_lanes) push_overflow(S, b, id & ~FILL_OVER);
+            if (id != FILL_NONE && !(id & FILL_OVER)) atomicOr(out + (id >> 5), 1u << (id & 31));
         }
-        if (threadIdx.x == 0) F.row_count[b] = total;                   // every row writes its count: nothing to clear beforehand
-        // what did not fit there either: one lane of every wavefront that has a lane of the large-capacity scratch
-        if (n_over != 0 && lane == 0 && wave < F.own_lanes)
-            for (uint32_t t = wave; t < total; t += F.own_lanes) {
-                const uint32_t id = sh_surv[t];
-                if (id == FILL_NONE || !(id & FILL_OVER)) continue;
-                atomicAdd(S.count, 1u);
-                if (recheck_large(F, Vd, S, r, b, id & ~FILL_OVER, b * F.own_lanes + wave)) atomicOr(out + ((id & ~FILL_OVER) >> 5), 1u << (id & 31));
+        if (threadIdx.x == 0) {
+            F.row_count[b] = total;                                 // every row writes its count: nothing to clear beforehand
+            if (n_large) atomicAdd(S.count + 3, n_large);
+        }
+        // what did not fit there either: to k_recheck_slow, or one lane of every wavefront that has a lane of the large-capacity scratch
+        const uint32_t teams = F.own_lanes ? F.own_lanes : FILL_THREADS / 64;
+        if (n_over != 0 && !left && lane == 0 && wave < teams)
+            for (uint32_t t = wave; t < total; t += teams) {
+                const uint32_t v = sh_surv[t], id = v & ~FILL_OVER;
+                if (v == FILL_NONE || !(v & FILL_OVER) || (F.follows && try_push(S, b, id))) continue;
+                if (!F.own_lanes) leave_undecided(S, b, id);
+                else if (recheck_large(F, Vd, S, r, b, id, b * F.own_lanes + wave)) atomicOr(out + (id >> 5), 1u << (id & 31));
             }
         stamp_end();
         return;
     }
+    __syncthreads();
     if (threadIdx.x == 0) F.row_count[b] = n_cand;
     if (wave < FILL_OR_WAVES) { stamp_end(); return; }
     // the sequential way: each wave of the re-check team takes as many listed words at a time as it has lanes at work
@@ -1181,6 +1220,7 @@ __global__ __launch_bounds__(FILL_THREADS) __attribute__((amdgpu_waves_per_eu(6)
     const uint32_t* cands = F.cand_words + b * Vd.W;
     const DevTables T = uniform_load(F.tables + r.tables_idx);
     const DevCtx C = row_ctx(F, r);
+    uint32_t large = 0;
     for (uint32_t base = (wave - FILL_OR_WAVES) * FILL_RECHECK_LANES; base < count; base += FILL_COLS) {
         uint32_t idx = 0, cand = 0;
         if (lane < FILL_RECHECK_LANES && base + lane < count) { idx = wlist[base + lane]; cand = cands[idx]; }
@@ -1202,16 +1242,26 @@ __global__ __launch_bounds__(FILL_THREADS) __attribute__((amdgpu_waves_per_eu(6)
                 if (res == RECHECK_YES) atomicOr(out + w, 1u << (id & 31));
                 over = res == RECHECK_OVER;
             }
-            if (!F.own_lanes) { if (over) push_overflow(S, b, id); continue; }
-            for (unsigned long long m = __ballot(over); m;) {
+            unsigned long long m = __ballot(over);
+            if (!m) continue;
+            large += (uint32_t)__popcll(m);
+            if (F.follows) {                                           // to k_recheck_slow; if its list is full, to one lane with its lists in device memory
+                uint32_t at = 0;
+                if (lane == 0) at = atomicAdd(S.count, (uint32_t)__popcll(m));
+                at = lane_value(at, 0) + (uint32_t)__popcll(m & ((1ull << lane) - 1));
+                const bool fits = over && at < S.list_cap;
+                if (fits) { S.list[2 * at] = b; S.list[2 * at + 1] = id; }
+                m = __ballot(over && !fits);
+            }
+            while (m) {
                 const uint32_t id2 = lane_value(id, next_bit(m));
-                if (lane == 0) {
-                    atomicAdd(S.count, 1u);
-                    if (recheck_large(F, Vd, S, r, b, id2, b * F.own_lanes + (wave - FILL_OR_WAVES))) atomicOr(out + (id2 >> 5), 1u << (id2 & 31));
-                }
+                if (lane != 0) continue;
+                if (!F.own_lanes) leave_undecided(S, b, id2);
+                else if (recheck_large(F, Vd, S, r, b, id2, b * F.own_lanes + (wave - FILL_OR_WAVES))) atomicOr(out + (id2 >> 5), 1u << (id2 & 31));
             }
         }
     }
+    if (lane == 0 && large) atomicAdd(S.count + 3, large);
     stamp_end();
 }
 

@@ -2,8 +2,11 @@
 their item sets do not fit a lane's lists: same masks, same counts, and no way that costs many times another."""
 import random
 
+import numpy as np
 import pytest
 
+import oracle
+from helpers import diff_words
 
 pytestmark = pytest.mark.gpu
 
@@ -41,11 +44,11 @@ def _tokens(n_uncertain, shortest, longest):
     return toks
 
 
-def _batch(xg, toks, starts, **options):
+def _batch(xg, toks, starts, ebnf=EBNF):
     """Slots that have seen `starts`, on the device."""
     import torch
     vocab = xg.Vocab(toks, 0, [0])
-    cache = xg.compile_grammar(vocab, EBNF, "root", stream=_stream(), context_depth=1, follow_filter=False, **options)
+    cache = xg.compile_grammar(vocab, ebnf, "root", stream=_stream(), context_depth=1, follow_filter=False)
     B = len(starts)
     db = xg.DeviceBatch(vocab, B)
     db.assign(cache, stream=_stream())
@@ -67,3 +70,78 @@ def test_count_of_large_tokens_does_not_depend_on_the_way(xg, n):
     db.fill_next_token_bitmask(bm.data_ptr(), vocab.words, _stream())
     assert xg.fill_last_recheck_tokens(len(starts)).tolist() == [n] * len(starts)
     assert xg.fill_last_status() == (len(starts) * n, False)
+
+
+# a rule that one of twelve rules or another instance of itself can stand in: entering it brings more than a lane's list holds
+WIDE = ('root ::= p\np ::= "(" (p | ' + " | ".join("r%d" % k for k in range(12)) + ') ")"\n'
+        + "".join('r%d ::= "%s" [a-z]*\n' % (k, "abz"[k % 3] * (1 + k // 3)) for k in range(12)))
+
+
+@pytest.mark.parametrize("rows", [1, 20])                             # in batches below and above kFillSpreadRows
+@pytest.mark.parametrize("ebnf,n,shortest,longest", [
+    (EBNF, 18, 9, 40), (EBNF, 19, 17, 40), (EBNF, 40, 9, 80),         # a wavefront each, and more; beyond what a wavefront takes
+    (EBNF, 63, 17, 40), (EBNF, 64, 17, 40), (EBNF, 600, 9, 80),       # a plane's list, and more
+    (WIDE, 18, 4, 16), (WIDE, 40, 4, 16), (WIDE, 100, 4, 24),         # item sets that outgrow a lane
+], ids=lambda v: "wide" if v is WIDE else "nest" if v is EBNF else str(v))
+def test_masks_with_large_tokens(xg, ebnf, n, shortest, longest, rows):
+    import torch
+    toks = _tokens(n, shortest, longest)
+    # contexts around 64 sets and 128 wait entries, and (on the host) beyond the 512 entries and 240 sets of a matcher slot
+    depths = [1, 8, 42, 43, 63, 64, 65, 118] if ebnf is EBNF else [1, 5, 12]
+    starts = [b"(" * d + b"z" for d in depths]
+    deep = [b"(" * d + b"z" for d in (175, 245)]
+    orc, va = oracle.Oracle(ebnf, "root"), oracle.VocabArrays(toks, 0, [0])
+    want = {s: oracle.pack_bitmask(orc.mask(s, va)) for s in starts + deep}
+    vocab, cache, db = _batch(xg, toks, starts * rows, ebnf)
+    W = vocab.words
+
+    def check(fill, hist):
+        bm = torch.full((len(hist), W), -1, dtype=torch.int32, device="cuda")
+        fill(bm)
+        assert not xg.fill_last_status()[1]
+        torch.cuda.synchronize()
+        got = bm.cpu().numpy()
+        for b, s in enumerate(hist):
+            assert np.array_equal(got[b], want[s]), (b, s, diff_words(got[b], want[s], toks))
+
+    for _ in range(2):
+        check(lambda bm: db.fill_next_token_bitmask(bm.data_ptr(), W, _stream()), starts * rows)
+    at = {t: k for k, t in enumerate(toks)}
+    for hist in (starts * rows, deep * rows + starts):
+        matchers = [xg.Matcher(cache) for _ in hist]
+        for m, s in zip(matchers, hist):
+            for c in s:
+                assert m.accept_token(at[bytes([c])])
+        check(lambda bm: xg.fill_next_token_bitmask(matchers, bm.data_ptr(), W, _stream()), hist)
+        few = matchers[:120]                                          # its fixed scratch has lanes of its own for the rows of that many
+        check(lambda bm: xg.fill_next_token_bitmask_noalloc(few, bm.data_ptr(), W, _stream()), hist[:120])
+
+
+def _us(f):
+    import torch
+    f()
+    best = 1e9
+    for _ in range(5):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        for _ in range(5):
+            f()
+        b.record()
+        torch.cuda.synchronize()
+        best = min(best, a.elapsed_time(b) * 1e3 / 5)
+    return best
+
+
+def test_large_tokens_are_not_parsed_one_after_another(xg):
+    """A row's tokens beyond a lane's lists, on either side of what a plane's list holds (63): within small factors of tokens that
+    fit, measured 2.4 and 3; one after another they took 8 and 130 times as long."""
+    import torch
+
+    def us(n, shortest, longest):
+        vocab, _, db = _batch(xg, _tokens(n, shortest, longest), [b"(" * 8 + b"z"])
+        bm = torch.zeros((1, vocab.words), dtype=torch.int32, device="cuda")
+        return _us(lambda: db.fill_next_token_bitmask(bm.data_ptr(), vocab.words, _stream()))
+
+    fit = us(63, 9, 14)
+    assert us(63, 20, 40) < 5 * fit
+    assert us(100, 20, 40) < 10 * fit
