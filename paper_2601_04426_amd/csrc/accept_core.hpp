@@ -5,6 +5,7 @@
 // planes of the new scannable frontier.  Written once for device and host (a CPU test steps it against the host parser).
 #pragma once
 #include "earley_core.hpp"
+#include "tables.hpp"
 
 namespace xg2 {
 namespace core {
@@ -19,6 +20,18 @@ struct MatcherOut {                  // where the next context goes, and how muc
 };
 constexpr int ACC_OK = 0, ACC_REJECTED = 1, ACC_RETRY = 2 /* the recogniser's lists were too short */, ACC_OVERFLOW = 3 /* the slot is */,
               ACC_NO_PLANE = 4;
+
+// The number that a site table (tables.hpp) holds for `rule` in the row of `state`, or kNoRule: two loads and about one probe,
+// however many rules the row has.
+__device__ __forceinline__ uint32_t find_site(const uint32_t* off, const uint2* slot, uint32_t state, uint32_t rule) {
+    const uint32_t first = tab(off + state), size = tab(off + state + 1) - first;
+    for (uint32_t i = 0, k = site_home(rule, size); i < size; ++i, k = (k + 1) & (size - 1)) {
+        const uint2 s = tab(slot + first + k);
+        if (s.x == rule) return s.y;
+        if (s.x == kNoRule) break;
+    }
+    return kNoRule;
+}
 
 // X: per-lane scratch: a byte per item set (renumbering) and a few 64-bit words (frontier planes before they are stored).
 //   uint32_t map_get(uint32_t i), void map_set(uint32_t i, uint32_t v); uint64_t front_get(uint32_t k), void front_set(uint32_t k, uint64_t v);

@@ -1400,23 +1400,13 @@ void ensure_cache_on_device(const std::shared_ptr<CacheImpl>& cp) {
     }
     if (pair_key.empty()) { pair_key.push_back(0); pair_row.push_back(0); }
     // per state, the rules it is a site of, with its place among their sites: the look-up of the accept kernel
-    std::vector<uint32_t> site_of_off(n_states + 1, 0);
-    std::vector<uint2> site_of;
-    {
-        const FlatTables& ft = C.gram->ft;
-        for (const RefEdgeP& e : ft.ref_edges) ++site_of_off[(size_t)e.tgt + 1];
-        for (size_t sid = 0; sid < n_states; ++sid) site_of_off[sid + 1] += site_of_off[sid];
-        site_of.assign(std::max<size_t>(ft.ref_edges.size(), 1), make_uint2(0xFFFFFFFFu, 0u));
-        std::vector<uint32_t> at(site_of_off.begin(), site_of_off.end() - 1);
-        for (const RefEdgeP& e : ft.ref_edges) {
-            if (C.pair_base.empty()) break;
-            bool seen = false;
-            for (uint32_t k = site_of_off[e.tgt]; k < at[e.tgt]; ++k) seen |= site_of[k].x == e.rule;
-            if (seen) continue;                                     // (the rows keep the room of the repeated edges)
-            const Span<uint32_t> keys = C.site_keys[e.rule];
-            site_of[at[e.tgt]++] = make_uint2(e.rule, (uint32_t)(std::lower_bound(keys.begin(), keys.end(), C.site_rep[e.tgt]) - keys.begin()));
-        }
-    }
+    const SiteTable site_of = site_table(C.gram->ft, [&](const RefEdgeP& e) -> uint32_t {
+        if (C.pair_base.empty()) return 0;
+        const Span<uint32_t> keys = C.site_keys[e.rule];
+        return (uint32_t)(std::lower_bound(keys.begin(), keys.end(), C.site_rep[e.tgt]) - keys.begin());
+    });
+    std::vector<uint2> site_slots(std::max<size_t>(site_of.slot.size() / 2, 1), make_uint2(kNoRule, 0u));
+    if (!site_of.slot.empty()) std::memcpy(site_slots.data(), site_of.slot.data(), site_of.slot.size() * sizeof(uint32_t));
     // the start state, through the host parser
     MatcherImpl M(C.gram, C.vocab);
     M.cache = cp;
@@ -1434,7 +1424,7 @@ void ensure_cache_on_device(const std::shared_ptr<CacheImpl>& cp) {
     std::vector<uint2> s_wait(M.prep.ctx.wait.size() / 2);
     for (size_t k = 0; k < s_wait.size(); ++k) s_wait[k] = make_uint2(M.prep.ctx.wait[2 * k], M.prep.ctx.wait[2 * k + 1]);
     D.plain_row.upload(plain, nullptr); D.pair_off.upload(pair_off, nullptr); D.pair_key.upload(pair_key, nullptr); D.pair_row.upload(pair_row, nullptr);
-    D.site_rep.upload(C.site_rep, nullptr); D.site_of_off.upload(site_of_off, nullptr); D.site_of.upload(site_of, nullptr);
+    D.site_rep.upload(C.site_rep, nullptr); D.site_of_off.upload(site_of.off, nullptr); D.site_of.upload(site_slots, nullptr);
     D.start_items.upload(s_items, nullptr); D.start_front.upload(s_front, nullptr); D.start_wait.upload(s_wait, nullptr);
     D.start_wait_off.upload(M.prep.ctx.wait_off, nullptr);
     HIP_CHECK(hipStreamSynchronize(nullptr));

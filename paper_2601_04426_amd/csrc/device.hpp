@@ -177,8 +177,8 @@ struct CacheDev {
     const uint32_t* pair_key;            //   state id the referencing rule continues in (its class: site_rep), ascending within a state
     const uint64_t* pair_row;
     const uint32_t* site_rep;            // [n_states] the state that stands for each state's class as a site; null: every state for itself
-    const uint32_t* site_of_off;         // [n_states + 1] CSR over states x: the rules after which a rule continues in x,
-    const uint2* site_of;                //   as pairs {rule, which of the rule's sites x is}: plane of (state, x) = pair_row[pair_off[state] + that]
+    const uint32_t* site_of_off;         // [n_states + 1] site table (tables.hpp) over states x: for a rule after which a referencing rule
+    const uint2* site_of;                //   continues in x, which of the rule's sites x is: plane of (state, x) = pair_row[pair_off[state] + that]
     uint32_t context_depth;
     uint32_t start_n_items, start_H, start_n_front, start_flags;
     const uint32_t* start_items; const uint2* start_wait; const uint32_t* start_wait_off; const uint64_t* start_front;

@@ -1458,11 +1458,8 @@ __device__ __forceinline__ int accept_wave(const BatchDev& D, const CacheDev* Cp
             if (row && (v >> REF_BITS) == ROOT_ORIGIN) row |= 1u;
         } else {
             const uint32_t rule = tab(&T.state[sid].x), base = tab(pair_off + sid), end = tab(pair_off + sid + 1);
-            const uint32_t k1 = tab(site_of_off + (t & SID_MASK) + 1);
-            for (uint32_t k = tab(site_of_off + (t & SID_MASK)); k < k1; ++k) {
-                const uint2 s = tab(site_of + k);
-                if (s.x == rule) { if (base + s.y < end) row = tab(pair_row + base + s.y); break; }
-            }
+            const uint32_t place = find_site(site_of_off, site_of, t & SID_MASK, rule);
+            if (place < end - base) row = tab(pair_row + base + place);
         }
     }
     if (__ballot(lane < n_pairs && row == 0)) return ACC_NO_PLANE;

@@ -140,6 +140,29 @@ FlatTables flatten(const Grammar& g) {
     return t;
 }
 
+SiteTable site_table(const FlatTables& t, const std::function<uint32_t(const RefEdgeP&)>& number) {
+    const size_t n = t.state_info.size();
+    std::vector<uint32_t> edges(n, 0);
+    for (const RefEdgeP& e : t.ref_edges) ++edges[e.tgt];
+    SiteTable s;
+    s.off.assign(n + 1, 0);
+    for (size_t x = 0; x < n; ++x) {
+        uint32_t size = edges[x] < 2 ? edges[x] : 4;
+        while (size > 1 && size < 2 * edges[x]) size *= 2;
+        s.off[x + 1] = s.off[x] + size;
+    }
+    s.slot.resize(2 * (size_t)s.off[n]);
+    for (size_t k = 0; k < s.off[n]; ++k) { s.slot[2 * k] = kNoRule; s.slot[2 * k + 1] = 0; }
+    for (const RefEdgeP& e : t.ref_edges) {
+        const uint32_t size = s.off[(size_t)e.tgt + 1] - s.off[e.tgt];
+        uint32_t k = site_home(e.rule, size);
+        auto at = [&] { return s.slot.data() + 2 * (size_t)(s.off[e.tgt] + k); };
+        while (at()[0] != kNoRule && at()[0] != e.rule) k = (k + 1) & (size - 1);
+        if (at()[0] == kNoRule) { at()[0] = e.rule; at()[1] = number(e); }
+    }
+    return s;
+}
+
 namespace {
 inline bool has(const std::vector<ChartItem>& v, ChartItem it) {
     for (auto& x : v) if (x.sid == it.sid && x.origin == it.origin) return true;

@@ -59,6 +59,18 @@ struct FlatTables {
 
 FlatTables flatten(const Grammar& g);
 
+// Per state, the rules after which a referencing rule continues in it, each with a number that the caller gives the pair: the
+// row of state x is a hash table, slots off[x] .. off[x + 1) (none, one, or a power of two at least twice the references that
+// lead to x), of pairs {rule, number} or {kNoRule, 0}; a rule lies at or, cyclically, behind its home.  (The state that free
+// text returns to is the site of every tool's rule, so a row can have as many rules as the grammar.)
+struct SiteTable {
+    std::vector<uint32_t> off;                   // [n_states + 1]
+    std::vector<uint32_t> slot;                  // two words a slot
+};
+constexpr uint32_t kNoRule = 0xFFFFFFFFu;
+constexpr uint32_t site_home(uint32_t rule, uint32_t size) { return (rule * 0x9E3779B1u >> 12) & (size - 1); }
+SiteTable site_table(const FlatTables& t, const std::function<uint32_t(const RefEdgeP&)>& number);
+
 // One closed Earley item set of the host parser.  `scan` holds the items whose state has a byte
 // edge or no edge at all, `wait` those whose state has a rule edge (an item can be in both).
 // Origins are chart indices; -1 marks the root instance.

@@ -413,3 +413,35 @@ extern "C" long long xg2hc_check_accept(const char* ebnf, size_t len, const char
         return -1;
     }
 }
+
+// The site tables of a grammar against a plain list of its references: every (state, rule) with its number, pairs that do not
+// exist with none.  Returns the most slots a look-up of an existing pair reads, or -1.
+extern "C" long long xg2hc_check_sites(const char* ebnf, size_t len, const char* root, char* msg, size_t msg_cap) {
+    try {
+        const Grammar g = lower_grammar(std::string(ebnf, len), root);
+        const FlatTables ft = flatten(g);
+        std::map<std::pair<uint32_t, uint32_t>, uint32_t> want;   // (state, rule) -> number, the first reference's
+        auto number = [&](const RefEdgeP& e) { return 7 * e.rule + 3 * e.tgt + 1; };
+        for (const RefEdgeP& e : ft.ref_edges) want.emplace(std::make_pair(e.tgt, e.rule), number(e));
+        const SiteTable s = site_table(ft, number);
+        std::vector<uint2> slot(s.slot.size() / 2);
+        for (size_t k = 0; k < slot.size(); ++k) slot[k] = make_uint2(s.slot[2 * k], s.slot[2 * k + 1]);
+        long long most = 0;
+        for (uint32_t x = 0; x < ft.state_info.size(); ++x) {
+            const uint32_t size = s.off[x + 1] - s.off[x];
+            for (uint32_t r = 0; r < ft.rule_info.size(); ++r) {
+                const auto it = want.find({x, r});
+                const uint32_t got = find_site(s.off.data(), slot.data(), x, r);
+                if (got != (it == want.end() ? kNoRule : it->second)) { snprintf(msg, msg_cap, "state %u rule %u: %u", x, r, got); return -1; }
+                if (it == want.end()) continue;
+                long long n = 1;
+                for (uint32_t k = site_home(r, size); slot[s.off[x] + k].x != r; k = (k + 1) & (size - 1)) ++n;
+                most = std::max(most, n);
+            }
+        }
+        return most;
+    } catch (const std::exception& e) {
+        snprintf(msg, msg_cap, "exception: %s", e.what());
+        return -1;
+    }
+}

@@ -239,3 +239,19 @@ def test_device_accept_step_matches_host_parser_on_tiny_grammars(hostcheck, case
     seq.append(-1)
     for small in (True, False):
         assert run_accept(hostcheck, ebnf, root, toks, seq, list(range(len(toks))), small) > len(sentence)
+
+
+@pytest.mark.parametrize("n_tools", [0, 1, 2, 12, 64, 512])
+def test_site_tables(hostcheck, n_tools):
+    """Every site of every rule is found under its state, and next to nothing is read for it however many rules share the state
+    (the state that free text returns to: one rule a tool)."""
+    if n_tools:
+        ebnf = "root ::= TagDispatch(%s)\n" % ", ".join('("<f%d>", t%d)' % (k, k) for k in range(n_tools))
+        ebnf += "".join('t%d ::= ws ("[" ws t%d{0,3} "]")* ws "!"\n' % (k, max(k - 1, 0) if k % 5 else k) for k in range(n_tools)) + 'ws ::= " "*\n'
+    else:
+        ebnf = 'root ::= "a"*\n'
+    e, msg = ebnf.encode(), ctypes.create_string_buffer(512)
+    hostcheck.xg2hc_check_sites.restype = ctypes.c_longlong
+    most = hostcheck.xg2hc_check_sites(e, ctypes.c_size_t(len(e)), b"root", msg, ctypes.c_size_t(512))
+    assert 0 <= most <= 8, (most, msg.value.decode())
+    assert (most > 0) == (n_tools > 0)
