@@ -667,6 +667,7 @@ inline void share_out(FillBatch& F, uint32_t n_lanes, const FillLoad& load) {
     F.own_lanes = per < 2 ? 0u : std::min<uint32_t>(per, 6);
     F.follows = F.own_lanes == 0 || load.deep || load.plane_tokens > kFillPlaneTokens || load.row_tokens > kFillRowTokens
                 || (F.B <= kFillSpreadRows && load.large && std::max(load.plane_tokens, load.row_tokens) > kFillWaveTokens);
+    F.leave_above = F.follows && F.B <= kFillSpreadRows ? kFillWaveTokens : 0xFFFFFFFFu;
 }
 
 // ---- fill workspace: pinned staging ring + device mirror ---------------------------------------------------

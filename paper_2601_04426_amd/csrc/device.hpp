@@ -149,6 +149,7 @@ struct FillBatch {
     uint32_t own_lanes;                  // lanes of the large-capacity scratch that are a row's own while k_fill runs, or 0: there are too few
     uint32_t follows;                    // k_recheck_slow is launched behind it and takes what the rows leave on the overflow list (always
                                          // if own_lanes is 0)
+    uint32_t leave_above;                // a row with more tokens than that beyond a lane's lists leaves them there
     uint64_t* stamps;                    // if not null: when the call's work started and ended, on the device's constant-rate clock:
                                          // [0] the upload kernel's start; kStampsPerRow words for each row (start, end of each of
                                          // its wavefronts); the end of each workgroup of k_recheck_slow

@@ -837,7 +837,7 @@ struct WaveScan {
 // have many such tokens the host launches it behind this kernel, and a row with more than FILL_WAVE_TOKENS of them leaves them
 // to it.  Tokens of 20 - 40 bytes, us a call, all by wavefronts / by the launch behind:
 // 63 a row, 1 row 325 / 107, 256 rows 329 / 421, 1,024 rows 685 / 1,611 (six wavefronts a row against 4,096 lanes in all), so the
-// line lies at FILL_SPREAD_ROWS.  The sequential way, which has no bound on its tokens, leaves all of them to it (100 a row,
+// line lies at kFillSpreadRows.  The sequential way, which has no bound on its tokens, leaves all of them to it (100 a row,
 // 1 row: 112 us; one lane of the workgroup after another took 5,433).
 // Four wavefronts stream, two re-check with half of their lanes at work (measured: fewer lanes per wavefront, more
 // wavefronts or another split of the six gain nothing; a larger workgroup lowers the number of rows a compute unit holds).
@@ -848,7 +848,6 @@ constexpr int FILL_OR_THREADS = 64 * FILL_OR_WAVES;
 constexpr int FILL_THREADS = 64 * (FILL_OR_WAVES + FILL_RECHECK_WAVES);
 constexpr int FILL_BLOCK = 5;                          // steps of the union whose loads are issued together
 constexpr int FILL_K = kFillLaneItems, FILL_WM = kFillLaneWaits;
-constexpr uint32_t FILL_SPREAD_ROWS = kFillSpreadRows;
 constexpr uint32_t FILL_SPARSE_CAP = kFillRowTokens;   // candidates of a row that the side-by-side way handles
 constexpr uint32_t FILL_NONE = 0xFFFFFFFFu, FILL_OVER = 0x80000000u;   // what became of a candidate: rejected; did not fit the lists tried
 // Up to that many candidates get a wavefront each, six at a time, 3 - 12 us each by the depth of the grammar; with a lane each
@@ -1054,7 +1053,7 @@ __global__ __launch_bounds__(FILL_THREADS) __attribute__((amdgpu_waves_per_eu(6)
     __shared__ uint32_t sh_surv[FILL_SPARSE_CAP];
     __shared__ FillCtx ctx;
     __shared__ FillOwn sh_own[FILL_THREADS / 64];
-    __shared__ uint32_t n_listed, n_cand, n_over, n_large, next_token, list_at;
+    __shared__ uint32_t n_listed, n_cand, n_over, n_large, next_token;
     const uint32_t b = blockIdx.x, lane = threadIdx.x & 63, wave = same_in_all(threadIdx.x >> 6);
     if (F.stamps && threadIdx.x == 0) F.stamps[kStampsRows + kStampsPerRow * b] = wall_clock64();
     auto stamp_end = [&]() { if (F.stamps && lane == 0) F.stamps[kStampsRows + kStampsPerRow * b + 1 + wave] = wall_clock64(); };
@@ -1131,87 +1130,72 @@ __global__ __launch_bounds__(FILL_THREADS) __attribute__((amdgpu_waves_per_eu(6)
             }
         }
     }
-    if (!listed_way) {
-        bool left = false;                                          // what does not fit a lane's lists, to k_recheck_slow
-        if (total != 0 && !wave_way) {                              // (the same for the whole row)
-            __syncthreads();
-            const uint32_t over = n_over;
-            if (F.follows && over > FILL_WAVE_TOKENS && (gridDim.x <= FILL_SPREAD_ROWS || !ctx_fits)) {
-                if (threadIdx.x == 0) {
-                    list_at = S.list_cap;
-                    if (*reinterpret_cast<volatile uint32_t*>(S.count) < S.list_cap) list_at = atomicAdd(S.count, over);
-                }
-                __syncthreads();
-                const uint32_t at = list_at;
-                left = at < S.list_cap && over <= S.list_cap - at;   // there is room for all of them
-                if (left)
-                    for (uint32_t t = threadIdx.x; t < total; t += FILL_THREADS) {
-                        const uint32_t id = sh_surv[t];
-                        if (id == FILL_NONE || !(id & FILL_OVER)) continue;
-                        const uint32_t k = at + atomicAdd(&next_token, 1u);
-                        S.list[2 * k] = b; S.list[2 * k + 1] = id & ~FILL_OVER;
-                        sh_surv[t] = FILL_NONE;
-                    }
-                else                                                 // what there is of it names a token that is never parsed
-                    for (uint32_t k = threadIdx.x; k < over && at < S.list_cap && k < S.list_cap - at; k += FILL_THREADS) { S.list[2 * (at + k)] = b; S.list[2 * (at + k) + 1] = F.eos_id; }
-            }
-            if (threadIdx.x == 0) n_large = over;
-        }
-        if (wave_way ? total != 0 : ctx_fits && n_over != 0 && !left) {
-            // a wavefront per candidate, the union team joining in when its row is stored; or per token that did not fit a lane's lists
-            const DevTables T = uniform_load(F.tables + r.tables_idx);
-            for (;;) {
-                // The wavefront stays together from token to token: with nothing between "lane 0 stores a result" below and "lane 0
-                // takes the next token" here the compiler may send the other lanes round the loop without lane 0.
-                wave_sync();
-                uint32_t t = 0;
-                if (lane == 0) t = atomicAdd(&next_token, 1u);
-                wave_sync();
-                t = same_in_all(t);
-                if (t >= total) break;
-                uint32_t id;
-                bool accepts = false;
-                if (wave_way) {
-                    const uint32_t k = (uint32_t)__ffsll((long long)__ballot(incl > t)) - 1;
-                    const uint64_t a_k = ((uint64_t)lane_value((uint32_t)(addr >> 32), k) << 32) | lane_value((uint32_t)addr, k);
-                    id = uniform_load(reinterpret_cast<const uint32_t*>(a_k) + 3 * (size_t)Vd.W + 1 + (t - (lane_value(incl, k) - lane_value(n_unc, k))));
-                    if (lane < front_n) accepts = (tab(reinterpret_cast<const uint32_t*>(addr & ~(uint64_t)1) + (id >> 5)) >> (id & 31)) & 1u;
-                } else {
-                    const uint32_t v = same_in_all(sh_surv[t]);
-                    if (v == FILL_NONE || !(v & FILL_OVER)) continue;
-                    id = v & ~FILL_OVER;
-                }
-                bool large = false;
-                const int res = __any(accepts) ? RECHECK_NO : recheck_wave(Vd, S, T, ctx, sh_own[wave], r.H, r.item_n, my_item, id, lane, &large);
-                if (lane == 0) {
-                    sh_surv[t] = res == RECHECK_YES ? id : res == RECHECK_OVER ? (id | FILL_OVER) : FILL_NONE;
-                    if (wave_way && res == RECHECK_OVER) atomicAdd(&n_over, 1u);
-                    if (wave_way && (large || res == RECHECK_OVER)) atomicAdd(&n_large, 1u);
-                }
-            }
-        }
+    bool waves_parse = wave_way && total != 0;
+    if (!listed_way && total != 0 && !wave_way) {                   // (the same for the whole row)
         __syncthreads();
+        if (threadIdx.x == 0) n_large = n_over;
+        waves_parse = ctx_fits && n_over != 0 && n_over <= F.leave_above;
+    }
+    if (waves_parse) {
+        // a wavefront per candidate, the union team joining in when its row is stored; or per token that did not fit a lane's lists
+        const DevTables T = uniform_load(F.tables + r.tables_idx);
+        for (;;) {
+            // The wavefront stays together from token to token: with nothing between "lane 0 stores a result" below and "lane 0
+            // takes the next token" here the compiler may send the other lanes round the loop without lane 0.
+            wave_sync();
+            uint32_t t = 0;
+            if (lane == 0) t = atomicAdd(&next_token, 1u);
+            wave_sync();
+            t = same_in_all(t);
+            if (t >= total) break;
+            uint32_t id;
+            bool accepts = false;
+            if (wave_way) {
+                const uint32_t k = (uint32_t)__ffsll((long long)__ballot(incl > t)) - 1;
+                const uint64_t a_k = ((uint64_t)lane_value((uint32_t)(addr >> 32), k) << 32) | lane_value((uint32_t)addr, k);
+                id = uniform_load(reinterpret_cast<const uint32_t*>(a_k) + 3 * (size_t)Vd.W + 1 + (t - (lane_value(incl, k) - lane_value(n_unc, k))));
+                if (lane < front_n) accepts = (tab(reinterpret_cast<const uint32_t*>(addr & ~(uint64_t)1) + (id >> 5)) >> (id & 31)) & 1u;
+            } else {
+                const uint32_t v = same_in_all(sh_surv[t]);
+                if (v == FILL_NONE || !(v & FILL_OVER)) continue;
+                id = v & ~FILL_OVER;
+            }
+            bool large = false;
+            const int res = __any(accepts) ? RECHECK_NO : recheck_wave(Vd, S, T, ctx, sh_own[wave], r.H, r.item_n, my_item, id, lane, &large);
+            if (lane == 0) {
+                sh_surv[t] = res == RECHECK_YES ? id : res == RECHECK_OVER ? (id | FILL_OVER) : FILL_NONE;
+                if (wave_way && res == RECHECK_OVER) atomicAdd(&n_over, 1u);
+                if (wave_way && (large || res == RECHECK_OVER)) atomicAdd(&n_large, 1u);
+            }
+        }
+    }
+    __syncthreads();
+
+    if (!listed_way) {
         for (uint32_t t = threadIdx.x; t < total; t += FILL_THREADS) {
             const uint32_t id = sh_surv[t];
-            if (id != FILL_NONE && !(id & FILL_OVER)) atomicOr(out + (id >> 5), 1u << (id & 31));
+            if (id == FILL_NONE) continue;
+            if (!(id & FILL_OVER)) atomicOr(out + (id >> 5), 1u << (id & 31));
+            else if (F.follows && try_push(S, b, id & ~FILL_OVER)) sh_surv[t] = FILL_NONE;
+            else if (!F.own_lanes) leave_undecided(S, b, id & ~FILL_OVER);
         }
         if (threadIdx.x == 0) {
             F.row_count[b] = total;                                 // every row writes its count: nothing to clear beforehand
             if (n_large) atomicAdd(S.count + 3, n_large);
         }
-        // what did not fit there either: to k_recheck_slow, or one lane of every wavefront that has a lane of the large-capacity scratch
-        const uint32_t teams = F.own_lanes ? F.own_lanes : FILL_THREADS / 64;
-        if (n_over != 0 && !left && lane == 0 && wave < teams)
-            for (uint32_t t = wave; t < total; t += teams) {
-                const uint32_t v = sh_surv[t], id = v & ~FILL_OVER;
-                if (v == FILL_NONE || !(v & FILL_OVER) || (F.follows && try_push(S, b, id))) continue;
-                if (!F.own_lanes) leave_undecided(S, b, id);
-                else if (recheck_large(F, Vd, S, r, b, id, b * F.own_lanes + wave)) atomicOr(out + (id >> 5), 1u << (id & 31));
-            }
+        // what fits nowhere else: one lane of every wavefront that has a lane of the large-capacity scratch
+        if (n_over != 0 && F.own_lanes != 0) {
+            if (F.follows) __syncthreads();
+            if (lane == 0 && wave < F.own_lanes)
+                for (uint32_t t = wave; t < total; t += F.own_lanes) {
+                    const uint32_t id = sh_surv[t];
+                    if (id == FILL_NONE || !(id & FILL_OVER)) continue;
+                    if (recheck_large(F, Vd, S, r, b, id & ~FILL_OVER, b * F.own_lanes + wave)) atomicOr(out + ((id & ~FILL_OVER) >> 5), 1u << (id & 31));
+                }
+        }
         stamp_end();
         return;
     }
-    __syncthreads();
     if (threadIdx.x == 0) F.row_count[b] = n_cand;
     if (wave < FILL_OR_WAVES) { stamp_end(); return; }
     // the sequential way: each wave of the re-check team takes as many listed words at a time as it has lanes at work
