@@ -156,7 +156,7 @@ struct FillBatch {
 };
 // What k_fill handles how (the host decides by the same numbers whether k_recheck_slow follows).
 constexpr uint32_t kFillLaneItems = 8, kFillLaneWaits = 12, kFillLaneBytes = 16;    // lists and bytes of a lane that parses a token by itself
-constexpr uint32_t kFillWaveTokens = 18;                     // up to that many tokens of a row get a wavefront each
+constexpr uint32_t kFillWaveTokens = 24;                     // up to that many tokens of a row get a wavefront each
 constexpr uint32_t kFillSpreadRows = 192;                    // in batches up to that size, a row with more tokens that outgrow a lane leaves them to k_recheck_slow
 constexpr uint32_t kFillPlaneTokens = kUncListWords - 1;     // with more uncertain tokens in a frontier plane (than its list holds), or in a
 constexpr uint32_t kFillRowTokens = 2048;                    //   frontier (than any slot's can have otherwise), a row is worked through word by word

@@ -850,8 +850,7 @@ constexpr int FILL_BLOCK = 5;                          // steps of the union who
 constexpr int FILL_K = kFillLaneItems, FILL_WM = kFillLaneWaits;
 constexpr uint32_t FILL_SPARSE_CAP = kFillRowTokens;   // candidates of a row that the side-by-side way handles
 constexpr uint32_t FILL_NONE = 0xFFFFFFFFu, FILL_OVER = 0x80000000u;   // what became of a candidate: rejected; did not fit the lists tried
-// Up to that many candidates get a wavefront each, six at a time, 3 - 12 us each by the depth of the grammar; with a lane each
-// any number up to 64 takes 12 - 38 us (24 candidates of the deep one: 49 us by wavefronts, 39 by lanes).
+// Up to that many candidates get a wavefront each (six at a time, ~3 us each; a lane each: ~12 us for any number).
 constexpr uint32_t FILL_WAVE_TOKENS = kFillWaveTokens;
 constexpr uint32_t FILL_CTX_WAITS = kFillContextWaits, FILL_CTX_SETS = kFillContextSets, FILL_OWN_WAITS = 128, FILL_WAVE_BYTES = 64;   // what a wavefront's parse has room for
 using FillStore = LdsStore<FILL_K, FILL_WM, FILL_COLS>;

@@ -145,16 +145,3 @@ def test_large_tokens_are_not_parsed_one_after_another(xg):
     fit = us(63, 9, 14)
     assert us(63, 20, 40) < 5 * fit
     assert us(100, 20, 40) < 10 * fit
-
-
-def test_few_tokens_are_not_slower_than_more(xg):
-    """24 candidates take no longer than 32 of the same kind: the number up to which each gets a wavefront is not too large
-    (measured 1.03; with 24 wavefronts 1.29)."""
-    import torch
-
-    def us(n):
-        vocab, _, db = _batch(xg, _tokens(n, 9, 14), [b"(" * 8 + b"z"])
-        bm = torch.zeros((1, vocab.words), dtype=torch.int32, device="cuda")
-        return _us(lambda: db.fill_next_token_bitmask(bm.data_ptr(), vocab.words, _stream()))
-
-    assert us(24) < 1.15 * us(32)
