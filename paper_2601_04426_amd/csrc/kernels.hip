@@ -1592,7 +1592,7 @@ typedef uint32_t Vec4 __attribute__((ext_vector_type(4)));
 
 template <class E, bool STREAM>
 __global__ __launch_bounds__(64 * APPLY_WAVES) void k_apply_vec(E* logits, long long row_stride, int V, const uint32_t* bitmask, long long bm_stride) {
-    constexpr int EPV = 16 / sizeof(E), STEPS = 32 / EPV, LINE = 128 / sizeof(E);
+    constexpr int EPV = 16 / sizeof(E), STEPS = 32 / EPV;
     constexpr uint32_t ALL = (1u << EPV) - 1, NI = ApplyE<E>::NINF_WORD;
     const long long b = blockIdx.y;
     E* const row = logits + b * row_stride;
