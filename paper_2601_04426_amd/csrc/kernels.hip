@@ -849,7 +849,9 @@ constexpr int FILL_THREADS = 64 * (FILL_OR_WAVES + FILL_RECHECK_WAVES);
 constexpr int FILL_BLOCK = 5;                          // steps of the union whose loads are issued together
 constexpr int FILL_K = kFillLaneItems, FILL_WM = kFillLaneWaits;
 constexpr uint32_t FILL_SPARSE_CAP = kFillRowTokens;   // candidates of a row that the side-by-side way handles
-constexpr uint32_t FILL_NONE = 0xFFFFFFFFu, FILL_OVER = 0x80000000u;   // what became of a candidate: rejected; did not fit the lists tried
+// What became of a candidate: the token, or FILL_NONE if it was rejected; FILL_OVER: it did not fit the lists tried so far;
+// FILL_LARGE: it did not fit a lane's, and a wavefront has decided it.
+constexpr uint32_t FILL_OVER = 0x80000000u, FILL_LARGE = 0x40000000u, FILL_NONE = 0x3FFFFFFFu;
 // Up to that many candidates get a wavefront each, six at a time; with a lane each any number up to 64 takes one round.  Which
 // is less depends on the grammar: by wavefronts / by lanes from 19 on, two fills and a step, 37 rows of a JSON schema 27 / 32 us,
 // 64 rows of records 72 / 67; 24 candidates deep in nested parentheses, 1 row, 49 / 39.
@@ -914,7 +916,7 @@ __device__ __forceinline__ int recheck_wave(const DevVocab& Vd, const SlowScratc
     const uint32_t at = uniform_load(Vd.off + rank), n_bytes = uniform_load(Vd.off + rank + 1) - at;
     const uint4 tok16 = uniform_load(Vd.tok16 + rank);
     if (n_bytes > FILL_WAVE_BYTES) return RECHECK_OVER;
-    *large = n_bytes > 16 || item_n > (uint32_t)FILL_K;
+    *large |= n_bytes > 16 || item_n > (uint32_t)FILL_K;
     const uint32_t words[4] = {tok16.x, tok16.y, tok16.z, tok16.w};
     uint32_t byte = (words[(lane >> 2) & 3] >> (8 * (lane & 3))) & 0xFF;
     if (n_bytes > 16) byte = lane < n_bytes ? tab(Vd.bytes + at + lane) : 0u;
@@ -1054,14 +1056,14 @@ __global__ __launch_bounds__(FILL_THREADS) __attribute__((amdgpu_waves_per_eu(6)
     __shared__ uint32_t sh_surv[FILL_SPARSE_CAP];
     __shared__ FillCtx ctx;
     __shared__ FillOwn sh_own[FILL_THREADS / 64];
-    __shared__ uint32_t n_listed, n_cand, n_over, n_large, next_token;
+    __shared__ uint32_t n_listed, n_cand, n_over, next_token;
     const uint32_t b = blockIdx.x, lane = threadIdx.x & 63, wave = same_in_all(threadIdx.x >> 6);
     if (F.stamps && threadIdx.x == 0) F.stamps[kStampsRows + kStampsPerRow * b] = wall_clock64();
     auto stamp_end = [&]() { if (F.stamps && lane == 0) F.stamps[kStampsRows + kStampsPerRow * b + 1 + wave] = wall_clock64(); };
     const FillRow r = uniform_load(F.rows + b);
     const uint32_t front_off = r.front_off, front_n = r.front_n, flags = r.flags;
     const bool live = !(flags & 2u);
-    if (threadIdx.x == 0) { n_listed = 0; n_cand = 0; n_over = 0; n_large = 0; next_token = 0; }
+    if (threadIdx.x == 0) { n_listed = 0; n_cand = 0; n_over = 0; next_token = 0; }
     if (F.zero_words && b == 0 && threadIdx.x < 4) F.zero_words[threadIdx.x] = 0;      // the words the next call counts in
     // the plan, worked out by every wavefront for itself: lane k looks at frontier plane k
     uint64_t addr = 1;
@@ -1134,7 +1136,6 @@ __global__ __launch_bounds__(FILL_THREADS) __attribute__((amdgpu_waves_per_eu(6)
     bool waves_parse = wave_way && total != 0;
     if (!listed_way && total != 0 && !wave_way) {                   // (the same for the whole row)
         __syncthreads();
-        if (threadIdx.x == 0) n_large = n_over;
         waves_parse = ctx_fits && n_over != 0 && n_over <= F.leave_above;
     }
     if (waves_parse) {
@@ -1158,40 +1159,38 @@ __global__ __launch_bounds__(FILL_THREADS) __attribute__((amdgpu_waves_per_eu(6)
                 if (lane < front_n) accepts = (tab(reinterpret_cast<const uint32_t*>(addr & ~(uint64_t)1) + (id >> 5)) >> (id & 31)) & 1u;
             } else {
                 const uint32_t v = same_in_all(sh_surv[t]);
-                if (v == FILL_NONE || !(v & FILL_OVER)) continue;
+                if (!(v & FILL_OVER)) continue;
                 id = v & ~FILL_OVER;
             }
-            bool large = false;
+            bool large = !wave_way;
             const int res = __any(accepts) ? RECHECK_NO : recheck_wave(Vd, S, T, ctx, sh_own[wave], r.H, r.item_n, my_item, id, lane, &large);
             if (lane == 0) {
-                sh_surv[t] = res == RECHECK_YES ? id : res == RECHECK_OVER ? (id | FILL_OVER) : FILL_NONE;
+                sh_surv[t] = (res == RECHECK_NO ? FILL_NONE : id) | (res == RECHECK_OVER ? FILL_OVER : large ? FILL_LARGE : 0u);
                 if (wave_way && res == RECHECK_OVER) atomicAdd(&n_over, 1u);
-                if (wave_way && (large || res == RECHECK_OVER)) atomicAdd(&n_large, 1u);
             }
         }
     }
     __syncthreads();
 
     if (!listed_way) {
-        for (uint32_t t = threadIdx.x; t < total; t += FILL_THREADS) {
-            const uint32_t id = sh_surv[t];
-            if (id == FILL_NONE) continue;
-            if (!(id & FILL_OVER)) atomicOr(out + (id >> 5), 1u << (id & 31));
-            else if (F.follows && try_push(S, b, id & ~FILL_OVER)) sh_surv[t] = FILL_NONE;
-            else if (!F.own_lanes) leave_undecided(S, b, id & ~FILL_OVER);
+        uint32_t n_large = 0;
+        for (uint32_t t0 = wave * 64; t0 < total; t0 += FILL_THREADS) {
+            const uint32_t t = t0 + lane, v = t < total ? sh_surv[t] : FILL_NONE, id = v & FILL_NONE;
+            n_large += (uint32_t)__popcll(__ballot((v & (FILL_OVER | FILL_LARGE)) != 0));
+            if (v & FILL_OVER) {
+                if (F.follows && try_push(S, b, id)) sh_surv[t] = FILL_NONE;
+                else if (!F.own_lanes) leave_undecided(S, b, id);
+            } else if (id != FILL_NONE) atomicOr(out + (id >> 5), 1u << (id & 31));
         }
-        if (threadIdx.x == 0) {
-            F.row_count[b] = total;                                 // every row writes its count: nothing to clear beforehand
-            if (n_large) atomicAdd(S.count + 3, n_large);
-        }
+        if (n_large != 0 && lane == 0) atomicAdd(S.count + 3, n_large);
+        if (threadIdx.x == 0) F.row_count[b] = total;               // every row writes its count: nothing to clear beforehand
         // what fits nowhere else: one lane of every wavefront that has a lane of the large-capacity scratch
         if (n_over != 0 && F.own_lanes != 0) {
             if (F.follows) __syncthreads();
             if (lane == 0 && wave < F.own_lanes)
                 for (uint32_t t = wave; t < total; t += F.own_lanes) {
-                    const uint32_t id = sh_surv[t];
-                    if (id == FILL_NONE || !(id & FILL_OVER)) continue;
-                    if (recheck_large(F, Vd, S, r, b, id & ~FILL_OVER, b * F.own_lanes + wave)) atomicOr(out + ((id & ~FILL_OVER) >> 5), 1u << (id & 31));
+                    const uint32_t v = sh_surv[t], id = v & FILL_NONE;
+                    if ((v & FILL_OVER) && recheck_large(F, Vd, S, r, b, id, b * F.own_lanes + wave)) atomicOr(out + (id >> 5), 1u << (id & 31));
                 }
         }
         stamp_end();
