@@ -2542,6 +2542,8 @@ int32_t xg2_batch_fill_next_token_bitmask(xg2_batch* batch, int32_t* bitmask_dev
         F.zero_words = Bt.flag_words.p + 4 * Bt.flag_turn;
         S.mark_rows = Bt.d.rows;                                // an undecided pair makes its slot unusable: the next accept says so
         share_out(F, S.n_lanes, Bt.load);
+        // a captured fill is replayed without the one that would clear its words, and its overflow list would grow from replay to replay
+        if (F.follows && !events_ride(stream)) launch_clear(S.count, 4, stream);
         // no event is recorded: the two that used to time the call held up the kernels behind it by 6 - 7 us a step
         F.stamps = fill_ws().stamps.p;
         launch_fill(F, V.dv, bitmask_dev, row_stride_words, S, stream);

@@ -212,6 +212,9 @@ void launch_batch_assign(const BatchDev& D, const int32_t* rows_dev, uint32_t n,
 // a kernel, or the other way: for the small per-call transfers this has less latency than the copy engine.
 void launch_upload(void* dst_dev, const void* src_host_mapped, size_t bytes, hipStream_t stream, uint64_t* stamp = nullptr, hipEvent_t done = nullptr);
 
+// Up to 64 words := 0.
+void launch_clear(uint32_t* words_dev, uint32_t n, hipStream_t stream);
+
 // The entry point that allocates nothing works in a fixed device array of the library (one per GPU, kept until the
 // process ends) instead of buffers that grow with the batch: staging of the per-row records, candidate words and
 // work lists, row counts, the overflow list and the large-capacity item lists.  noalloc_scratch gives the array's

@@ -5,6 +5,7 @@
 //   k_copy_masked  short tokens of a plane taken from the plane of a state they cannot tell apart (section 3.6)
 //   k_copy_first_byte  tokens of a plane taken from the plane of a state that moves alike on their first byte
 //   k_upload       per-call plan and tables from pinned host memory
+//   k_clear        a fill's counter words, where the fill of the call before did not clear them
 //   k_stage        the same for a build, together with the clearing of fresh rows and the chunk records
 //   k_plane_summary  per built plane: bit counts, and the short list of its uncertain tokens that the fill reads
 //   k_finish_planes  the copy kernels and the summary in one pass, when no derived plane leans on another derived one
@@ -511,6 +512,10 @@ __global__ __launch_bounds__(64) void k_build_slow(DevTables T, DevVocab Vd, Bui
 __global__ __launch_bounds__(256) void k_upload(uint4* dst, const uint4* src, size_t n, uint64_t* stamp) {
     if (stamp && blockIdx.x == 0 && threadIdx.x == 0) *stamp = wall_clock64();
     for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (size_t)gridDim.x * 256) dst[i] = src[i];
+}
+
+__global__ __launch_bounds__(64) void k_clear(uint32_t* words, uint32_t n) {
+    if (threadIdx.x < n) words[threadIdx.x] = 0;
 }
 
 __device__ __forceinline__ void expand_range(const uint4* range_a, const uint4* range_b, const uint32_t* first, uint32_t r, uint4* chunk) {
@@ -1751,6 +1756,10 @@ void launch_upload(void* dst_dev, const void* src_host_mapped, size_t bytes, hip
     const uint4* src = static_cast<const uint4*>(src_host_mapped);
     if (done) hipExtLaunchKernelGGL(k_upload, dim3(grid), dim3(256), 0, stream, nullptr, done, 0, dst, src, n, stamp);
     else hipLaunchKernelGGL(k_upload, dim3(grid), dim3(256), 0, stream, dst, src, n, stamp);
+}
+
+void launch_clear(uint32_t* words_dev, uint32_t n, hipStream_t stream) {
+    hipLaunchKernelGGL(k_clear, dim3(1), dim3(64), 0, stream, words_dev, n);
 }
 
 void launch_copy_masked(const CopyJob* jobs_dev, uint32_t n_jobs, uint32_t W, hipStream_t stream) {

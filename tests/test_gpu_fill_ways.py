@@ -145,3 +145,26 @@ def test_large_tokens_are_not_parsed_one_after_another(xg):
     fit = us(63, 9, 14)
     assert us(63, 20, 40) < 5 * fit
     assert us(100, 20, 40) < 10 * fit
+
+
+def test_captured_fill(xg):
+    """Replays of one captured fill whose rows leave tokens to the launch behind it: each as if it were the first."""
+    import torch
+    toks, starts = _tokens(100, 17, 40), [b"(" * 8 + b"z", b"(" * 3 + b"a", b"[([(" + b"b"]
+    vocab, cache, db = _batch(xg, toks, starts)
+    orc, va = oracle.Oracle(EBNF, "root"), oracle.VocabArrays(toks, 0, [0])
+    want = np.stack([oracle.pack_bitmask(orc.mask(s, va)) for s in starts])
+    bm = torch.zeros((len(starts), vocab.words), dtype=torch.int32, device="cuda")
+    db.fill_next_token_bitmask(bm.data_ptr(), vocab.words, _stream())
+    torch.cuda.synchronize()
+    once = xg.fill_last_status()
+    assert once == (3 * 100, False)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        db.fill_next_token_bitmask(bm.data_ptr(), vocab.words, _stream())
+    for _ in range(4):
+        bm.fill_(-1)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(bm.cpu().numpy(), want)
+        assert xg.fill_last_status() == once
