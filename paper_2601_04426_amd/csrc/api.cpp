@@ -594,9 +594,6 @@ struct CacheImpl {
     std::vector<std::shared_ptr<BuildTicket>> jit_tickets;  // builds issued by fill calls whose device time has not been added up yet
     double host_lower_ms = 0;                               // EBNF -> tables and plan, of the compile call
     int64_t compile_built = 0;
-    // Some state's expansion alone does not fit the short lists of the re-check: in such a grammar many candidates of a row may
-    // outgrow them.
-    bool wide = false;
     std::vector<uint32_t> site_off, site_tgt;               // per rule: states in which referencing rules continue
     int64_t n_built = 0, jit_calls = 0;                     // planes holding a row; build launches issued by fill
     double jit_device_ms = 0;
@@ -607,6 +604,7 @@ struct CacheImpl {
     ~CacheImpl();
     DevTables dt{};
     int32_t context_depth = 2;
+    bool filtered() const { return follow && context_depth == 2; }      // its planes have few uncertain tokens
     std::vector<PlaneInfo> planes;
     // for matchers that live on the device: plane look-up tables and the start state, made at first use
     struct OnDevice {
@@ -655,19 +653,21 @@ struct MatcherImpl {
 };
 
 // What the rows of a fill may ask of k_fill: the most uncertain tokens of a frontier plane and (if they are known) of a whole
-// frontier, whether some context is too large to parse from in a row's workgroup, and whether tokens may outgrow a lane's lists
-// in numbers (a wide grammar, tokens longer than a lane takes).
-struct FillLoad { uint32_t plane_tokens = 0, row_tokens = 0; bool deep = false, large = false; };
+// frontier, whether some context is too large to parse from in a row's workgroup, and whether many of a row's uncertain tokens
+// may be longer than a lane takes: the vocabulary has such tokens, and no follow language inside a parent filters them.
+struct FillLoad { uint32_t plane_tokens = 0, row_tokens = 0; bool deep = false, long_tokens = false; };
 // How many lanes of the large-capacity scratch each row of a fill gets for itself (its workgroup has six wavefronts), and whether
 // k_recheck_slow is launched behind k_fill.  That costs every call 2.5 - 4 us, so it is done only where there are too few lanes,
-// where a row goes word by word or its context is too large, or where the batch is small enough that a row's many large tokens
+// where a row goes word by word or its context is too large, or where the batch is small enough that a row's many long tokens
 // are better spread over the device (k_fill has the figures).
 inline void share_out(FillBatch& F, uint32_t n_lanes, const FillLoad& load) {
     const uint32_t per = n_lanes / F.B;
+    const bool spread = F.B <= kFillSpreadRows && load.long_tokens;
     F.own_lanes = per < 2 ? 0u : std::min<uint32_t>(per, 6);
     F.follows = F.own_lanes == 0 || load.deep || load.plane_tokens > kFillPlaneTokens || load.row_tokens > kFillRowTokens
-                || (F.B <= kFillSpreadRows && load.large && std::max(load.plane_tokens, load.row_tokens) > kFillWaveTokens);
-    F.leave_above = F.follows && F.B <= kFillSpreadRows ? kFillWaveTokens : 0xFFFFFFFFu;
+                || (spread && std::max(load.plane_tokens, load.row_tokens) > kFillSpreadTokens);
+    F.wave_tokens = spread ? kFillSpreadTokens : kFillWaveTokens;
+    F.leave_above = spread && F.follows ? kFillSpreadTokens : 0xFFFFFFFFu;
 }
 
 // ---- fill workspace: pinned staging ring + device mirror ---------------------------------------------------
@@ -1560,7 +1560,6 @@ int32_t xg2_compile_grammar(xg2_vocab* vocab, const char* ebnf, size_t len, cons
         cache->gram = make_grammar(ebnf, len, root_rule);
         const Grammar& g = cache->gram->g;
         const FlatTables& ft = cache->gram->ft;
-        for (const DevState& ds : ft.dev_state) cache->wide |= ds.n_items > kFillLaneItems || ds.n_triples > kFillLaneWaits;
         VocabImpl& V = *vocab->p;
         V.ensure_device();
         cache->pool = pool_h ? pool_h->p : std::make_shared<PoolImpl>();
@@ -2178,13 +2177,12 @@ int32_t fill_common(xg2_matcher* const* matchers, int32_t B, int32_t* bitmask_de
         std::vector<DevTables> tables;
         std::map<const CacheImpl*, uint32_t> table_idx;
         FillLoad load;
-        load.large = V.max_len > kFillLaneBytes;
         for (int32_t b = 0; b < B; ++b) {
             const MatcherImpl& M = *matchers[b]->p;
             FillRow& r = rows[(size_t)b];
             std::memset(&r, 0, sizeof(r));
             auto ti = table_idx.find(M.cache.get());
-            if (ti == table_idx.end()) { ti = table_idx.emplace(M.cache.get(), (uint32_t)tables.size()).first; tables.push_back(M.cache->dt); load.large |= M.cache->wide; }
+            if (ti == table_idx.end()) { ti = table_idx.emplace(M.cache.get(), (uint32_t)tables.size()).first; tables.push_back(M.cache->dt); load.long_tokens |= V.max_len > kFillLaneBytes && !M.cache->filtered(); }
             r.tables_idx = ti->second;
             r.front_off = (uint32_t)front.size();
             r.item_off = (uint32_t)items.size();
@@ -2199,7 +2197,7 @@ int32_t fill_common(xg2_matcher* const* matchers, int32_t B, int32_t* bitmask_de
                 const PlaneInfo& pi = M.cache->planes[(size_t)pl.first];
                 if (!pl.second) {
                     // not counted yet (being built for this very call): few where the follow language filters them inside a parent
-                    const uint32_t n = pi.n_uncertain == kNotCounted && M.cache->follow && M.cache->context_depth == 2 ? 0u : pi.n_uncertain;
+                    const uint32_t n = pi.n_uncertain == kNotCounted && M.cache->filtered() ? 0u : pi.n_uncertain;
                     load.plane_tokens = std::max(load.plane_tokens, n);
                     tokens += n;
                 }
@@ -2487,7 +2485,7 @@ int32_t xg2_batch_assign(xg2_batch* batch, const int32_t* rows_host, int32_t n, 
         if (ci == Bt.caches.size()) {
             if (ci >= BatchImpl::kMaxCaches) return fail(XG2_EOVERFLOW, "xg2_batch_assign: too many different caches in one batch");
             Bt.caches.push_back(cache->p);                      // kept alive while the batch lives
-            Bt.load.large |= cache->p->wide || Bt.vocab->max_len > kFillLaneBytes;
+            Bt.load.long_tokens |= Bt.vocab->max_len > kFillLaneBytes && !cache->p->filtered();
             Bt.load.plane_tokens = std::max(Bt.load.plane_tokens, od.most_uncertain);
             HIP_CHECK(hipMemcpyAsync(Bt.caches_dev.p + ci, &od.cd, sizeof(CacheDev), hipMemcpyHostToDevice, stream));
             HIP_CHECK(hipMemcpyAsync(Bt.tables_dev.p + ci, &od.cd.T, sizeof(DevTables), hipMemcpyHostToDevice, stream));

@@ -831,19 +831,23 @@ struct WaveScan {
 // table loads) hides behind the streaming and the other way round.  A token that another frontier plane accepts is in
 // the mask anyway and is not parsed: its bit is looked up in the accepted rows, without waiting for the union.
 // Most rows have no candidate and a few have a handful, but the launch lasts as long as its slowest row.  A row with few
-// candidates (FILL_WAVE_TOKENS) gives each a wavefront (WaveScan: a byte costs about one gather, where a lane of its own
+// candidates (wave_tokens) gives each a wavefront (WaveScan: a byte costs about one gather, where a lane of its own
 // takes several dependent accesses), the union team joining in when it is done; a row with more gives each a lane.
+// Wavefronts take six at a time, lanes any number up to 64 in one round.  Which is less depends on the grammar: by wavefronts /
+// by lanes from 19 on, two fills and a step, 37 rows of a JSON schema 27 / 32 us, 64 rows of records 72 / 67; 24 candidates deep in
+// nested parentheses, 1 row, 49 / 39, and of 20 - 40 bytes 129 / 95.
 // A row with a frontier plane whose uncertain tokens do not fit its list (or with more candidates than the LDS list
 // holds) takes the sequential way: the union team also reads the uncertain rows and lists the words with candidates,
 // the re-check team starts when the union is done, a lane each.
 // A token that outgrows a lane's lists (or 16 bytes) goes to a wavefront, one that outgrows that too to lists in device memory,
 // all in the row's own workgroup (own_lanes): a second launch for the few such tokens cost 2.5 - 4 us on every call.
-// A workgroup has six wavefronts, though, and k_recheck_slow 4,096 lanes over the device.  Where a row of a small batch may
-// have many such tokens the host launches it behind this kernel, and a row with more than FILL_WAVE_TOKENS of them leaves them
-// to it.  Tokens of 20 - 40 bytes, us a call, all by wavefronts / by the launch behind:
-// 63 a row, 1 row 325 / 107, 256 rows 329 / 421, 1,024 rows 685 / 1,611 (six wavefronts a row against 4,096 lanes in all), so the
-// line lies at kFillSpreadRows.  The sequential way, which has no bound on its tokens, leaves all of them to it (100 a row,
-// 1 row: 112 us; one lane of the workgroup after another took 5,433).
+// A workgroup has six wavefronts, though, and k_recheck_slow 4,096 lanes over the device.  Where rows of a small batch may have
+// many tokens of more than 16 bytes the host launches it behind this kernel, and a row with more than leave_above of them leaves
+// them to it.  Tokens of 20 - 40 bytes, us a call, all by wavefronts / by the launch behind: 63 a row, 1 row
+// 325 / 107, 256 rows 329 / 421, 1,024 rows 685 / 1,611 (six wavefronts a row against 4,096 lanes in all), so the line lies at
+// kFillSpreadRows.  Short tokens whose item sets outgrow a lane are the wavefronts' in any batch (expansions of 25 items, 33
+// tokens a row, 1 row: 64 / 128).  The sequential way, which has no bound on its tokens, leaves all of them to that launch (100
+// long ones a row, 1 row: 112 us; one lane of the workgroup after another took 5,433).
 // Four wavefronts stream, two re-check with half of their lanes at work (measured: fewer lanes per wavefront, more
 // wavefronts or another split of the six gain nothing; a larger workgroup lowers the number of rows a compute unit holds).
 constexpr int FILL_OR_WAVES = 4, FILL_RECHECK_WAVES = 2;
@@ -857,10 +861,6 @@ constexpr uint32_t FILL_SPARSE_CAP = kFillRowTokens;   // candidates of a row th
 // What became of a candidate: the token, or FILL_NONE if it was rejected; FILL_OVER: it did not fit the lists tried so far;
 // FILL_LARGE: it did not fit a lane's, and a wavefront has decided it.
 constexpr uint32_t FILL_OVER = 0x80000000u, FILL_LARGE = 0x40000000u, FILL_NONE = 0x3FFFFFFFu;
-// Up to that many candidates get a wavefront each, six at a time; with a lane each any number up to 64 takes one round.  Which
-// is less depends on the grammar: by wavefronts / by lanes from 19 on, two fills and a step, 37 rows of a JSON schema 27 / 32 us,
-// 64 rows of records 72 / 67; 24 candidates deep in nested parentheses, 1 row, 49 / 39.
-constexpr uint32_t FILL_WAVE_TOKENS = kFillWaveTokens;
 constexpr uint32_t FILL_CTX_WAITS = kFillContextWaits, FILL_CTX_SETS = kFillContextSets, FILL_OWN_WAITS = 128, FILL_WAVE_BYTES = 64;   // what a wavefront's parse has room for
 using FillStore = LdsStore<FILL_K, FILL_WM, FILL_COLS>;
 
@@ -1101,7 +1101,7 @@ __global__ __launch_bounds__(FILL_THREADS) __attribute__((amdgpu_waves_per_eu(6)
             }
         }
     }
-    const bool wave_way = ctx_fits && !listed_way && total <= FILL_WAVE_TOKENS;
+    const bool wave_way = ctx_fits && !listed_way && total <= F.wave_tokens;
     if (parses && wave == FILL_OR_WAVES) ctx.cls_words[lane] = tab(uniform_load(&F.tables[r.tables_idx].byte_class_words) + lane);
     uint32_t* out = reinterpret_cast<uint32_t*>(bitmask) + (long long)b * row_stride;
     FillStore st;

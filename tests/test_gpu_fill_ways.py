@@ -79,7 +79,7 @@ WIDE = ('root ::= p\np ::= "(" (p | ' + " | ".join("r%d" % k for k in range(12))
 
 @pytest.mark.parametrize("rows", [1, 20])                             # in batches below and above kFillSpreadRows
 @pytest.mark.parametrize("ebnf,n,shortest,longest", [
-    (EBNF, 24, 9, 40), (EBNF, 25, 17, 40), (EBNF, 40, 9, 80),         # a wavefront each, and more; beyond what a wavefront takes
+    (EBNF, 18, 9, 40), (EBNF, 19, 17, 40), (EBNF, 24, 9, 40), (EBNF, 25, 9, 80),         # a wavefront each, and more; beyond what a wavefront takes
     (EBNF, 63, 17, 40), (EBNF, 64, 17, 40), (EBNF, 600, 9, 80),       # a plane's list, and more
     (WIDE, 24, 4, 16), (WIDE, 40, 4, 16), (WIDE, 100, 4, 24),         # item sets that outgrow a lane
 ], ids=lambda v: "wide" if v is WIDE else "nest" if v is EBNF else str(v))
