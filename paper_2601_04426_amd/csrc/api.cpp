@@ -2177,6 +2177,8 @@ int32_t fill_common(xg2_matcher* const* matchers, int32_t B, int32_t* bitmask_de
         std::vector<DevTables> tables;
         std::map<const CacheImpl*, uint32_t> table_idx;
         FillLoad load;
+        uint32_t most_plane = 0;
+        uint64_t most_row = 0;
         for (int32_t b = 0; b < B; ++b) {
             const MatcherImpl& M = *matchers[b]->p;
             FillRow& r = rows[(size_t)b];
@@ -2195,24 +2197,25 @@ int32_t fill_common(xg2_matcher* const* matchers, int32_t B, int32_t* bitmask_de
             uint64_t tokens = 0;
             for (auto& pl : M.prep.planes) {
                 const PlaneInfo& pi = M.cache->planes[(size_t)pl.first];
-                if (!pl.second) {
-                    // not counted yet (being built for this very call): few where the follow language filters them inside a parent
-                    const uint32_t n = pi.n_uncertain == kNotCounted && M.cache->filtered() ? 0u : pi.n_uncertain;
-                    load.plane_tokens = std::max(load.plane_tokens, n);
-                    tokens += n;
-                }
-                uint64_t row = (uint64_t)(uintptr_t)pi.row->mem | ((pl.second || pi.n_uncertain == 0) ? 1u : 0u);
+                uint32_t n = pl.second ? 0u : pi.n_uncertain;
+                const uint64_t row = (uint64_t)(uintptr_t)pi.row->mem | (n == 0 ? 1u : 0u);
+                // not counted yet (being built for this very call): few where the follow language filters them inside a parent
+                if (n == kNotCounted && M.cache->filtered()) n = 0;
+                most_plane = std::max(most_plane, n);
+                tokens += n;
                 if (std::find(front.begin() + (long)f0, front.end(), row) == front.end()) front.push_back(row);
             }
-            load.row_tokens = (uint32_t)std::max<uint64_t>(load.row_tokens, std::min<uint64_t>(tokens, kNotCounted));
+            most_row = std::max(most_row, tokens);
             r.front_n = (uint32_t)(front.size() - f0);
             r.item_n = (uint32_t)ctx.items.size();
             r.H = ctx.H;
-            load.deep |= r.front_n > 64 || r.item_n > kFillContextItems || r.H > kFillContextSets || ctx.wait.size() / 2 > kFillContextWaits;
+            load.deep |= (r.front_n > 64) | (r.item_n > kFillContextItems) | (r.H > kFillContextSets) | (ctx.wait.size() > 2 * kFillContextWaits);
             items.insert(items.end(), ctx.items.begin(), ctx.items.end());
             wait.insert(wait.end(), ctx.wait.begin(), ctx.wait.end());
             wait_off.insert(wait_off.end(), ctx.wait_off.begin(), ctx.wait_off.end());
         }
+        load.plane_tokens = most_plane;
+        load.row_tokens = (uint32_t)std::min<uint64_t>(most_row, kNotCounted);
         auto align = [](size_t x) { return (x + 255) & ~(size_t)255; };
         size_t o_rows = 0;
         size_t o_front = align(o_rows + rows.size() * sizeof(FillRow));
