@@ -113,8 +113,9 @@ def test_masks_with_large_tokens(xg, ebnf, n, shortest, longest, rows):
             for c in s:
                 assert m.accept_token(at[bytes([c])])
         check(lambda bm: xg.fill_next_token_bitmask(matchers, bm.data_ptr(), W, _stream()), hist)
-        few = matchers[:120]                                          # its fixed scratch has lanes of its own for the rows of that many
-        check(lambda bm: xg.fill_next_token_bitmask_noalloc(few, bm.data_ptr(), W, _stream()), hist[:120])
+        few = matchers[:128]                                          # the most rows that its fixed scratch has lanes of their own for;
+        #                                                               with 600 tokens a row they fill its overflow list
+        check(lambda bm: xg.fill_next_token_bitmask_noalloc(few, bm.data_ptr(), W, _stream()), hist[:128])
 
 
 def _us(f):
