@@ -21,16 +21,20 @@ struct MatcherOut {                  // where the next context goes, and how muc
 constexpr int ACC_OK = 0, ACC_REJECTED = 1, ACC_RETRY = 2 /* the recogniser's lists were too short */, ACC_OVERFLOW = 3 /* the slot is */,
               ACC_NO_PLANE = 4;
 
-// The number that a site table (tables.hpp) holds for `rule` in the row of `state`, or kNoRule: two loads and about one probe,
-// however many rules the row has.
-__device__ __forceinline__ uint32_t find_site(const uint32_t* off, const uint2* slot, uint32_t state, uint32_t rule) {
-    const uint32_t first = tab(off + state), size = tab(off + state + 1) - first;
+// The number that the row of a site table (tables.hpp), `size` slots from `first` on, holds for `rule`, or kNoRule: about one
+// probe, however many rules the row has.
+__device__ __forceinline__ uint32_t find_in_row(const uint2* slot, uint32_t first, uint32_t size, uint32_t rule) {
     for (uint32_t i = 0, k = site_home(rule, size); i < size; ++i, k = (k + 1) & (size - 1)) {
         const uint2 s = tab(slot + first + k);
         if (s.x == rule) return s.y;
         if (s.x == kNoRule) break;
     }
     return kNoRule;
+}
+// The same for the row of `state`.
+__device__ __forceinline__ uint32_t find_site(const uint32_t* off, const uint2* slot, uint32_t state, uint32_t rule) {
+    const uint32_t first = tab(off + state);
+    return find_in_row(slot, first, tab(off + state + 1) - first, rule);
 }
 
 // X: per-lane scratch: a byte per item set (renumbering) and a few 64-bit words (frontier planes before they are stored).

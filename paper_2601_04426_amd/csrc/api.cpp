@@ -251,7 +251,7 @@ struct VocabImpl {
     // device copy (made at first use)
     std::mutex mu;
     bool on_device = false;
-    DevBuf<uint8_t> d_bytes; DevBuf<uint32_t> d_off, d_perm, d_rank; DevBuf<uint4> d_tok16;
+    DevBuf<uint8_t> d_bytes; DevBuf<uint32_t> d_off, d_perm, d_rank; DevBuf<uint4> d_tok16; DevBuf<TokenRecord> d_rec;
     DevVocab dv{};
     // per length bound d = 1 .. near_depths: the sorted ranks of the tokens longer than d bytes (ascending; list d is
     // long_rank[long_off[d] .. long_off[d + 1])), and on the device also the mask, in token ids, of the checkable tokens
@@ -345,11 +345,15 @@ struct VocabImpl {
         std::vector<uint8_t> first_byte((size_t)W * 32, 0);
         for (int32_t i = 0; i < V; ++i) if (len(i)) first_byte[(size_t)i] = tok(i)[0];
         d_first_byte.upload(first_byte, nullptr);
-        HIP_CHECK(hipStreamSynchronize(nullptr));
         dv.long_rank = d_long_rank.p;
         dv.tok16 = d_tok16.p;
         dv.bytes = d_bytes.p; dv.off = d_off.p; dv.perm = d_perm.p; dv.rank = d_rank.p;
         dv.n_sorted = n_sorted; dv.V = (uint32_t)V; dv.W = W;
+        d_rec.alloc((size_t)V);
+        launch_token_records(dv, d_rec.p, nullptr);
+        HIP_CHECK(hipGetLastError());
+        dv.rec = d_rec.p;
+        HIP_CHECK(hipStreamSynchronize(nullptr));
         noalloc_host().setup();
         on_device = true;
     }
@@ -1430,6 +1434,7 @@ void ensure_cache_on_device(const std::shared_ptr<CacheImpl>& cp) {
     D.start_wait_off.upload(M.prep.ctx.wait_off, nullptr);
     HIP_CHECK(hipStreamSynchronize(nullptr));
     D.cd.T = C.dt;
+    std::copy(C.gram->ft.byte_class_words.begin(), C.gram->ft.byte_class_words.end(), D.cd.cls_words);
     D.cd.plain_row = D.plain_row.p; D.cd.pair_off = D.pair_off.p; D.cd.pair_key = D.pair_key.p; D.cd.pair_row = D.pair_row.p; D.cd.site_rep = D.site_rep.p; D.cd.site_of_off = D.site_of_off.p; D.cd.site_of = D.site_of.p;
     D.cd.context_depth = (uint32_t)C.context_depth;
     D.cd.start_n_items = (uint32_t)s_items.size(); D.cd.start_H = M.prep.ctx.H; D.cd.start_n_front = (uint32_t)s_front.size();

@@ -18,6 +18,12 @@ struct DevTables {                       // packed grammar tables (see tables.hp
     const uint32_t* site_tgt;
 };
 
+// A token by its id: what a parse of it starts from, in one load.
+struct alignas(16) TokenRecord {
+    uint4 head;                          // its first 16 bytes, zero padded
+    uint32_t off, n_bytes;               // its place in DevVocab::bytes; 0 bytes: never checked (special or empty)
+    uint32_t pad[2];
+};
 struct DevVocab {                        // byte-sorted vocabulary in HBM
     const uint8_t* bytes;                // concatenated token bytes in sorted order
     const uint32_t* off;                 // [n_sorted + 1]
@@ -26,6 +32,7 @@ struct DevVocab {                        // byte-sorted vocabulary in HBM
     const uint32_t* perm;                // sorted rank -> token id
     const uint32_t* rank;                // token id -> sorted rank, 0xFFFFFFFF for tokens never checked
     const uint32_t* long_rank;           // per length bound d, ascending: the sorted ranks of the tokens longer than d bytes
+    const TokenRecord* rec;              // [V] by token id
     uint32_t n_sorted;                   // checkable tokens (non-special, non-empty)
     uint32_t V, W;
 };
@@ -183,6 +190,7 @@ struct CacheDev {
     const uint2* site_of;                //   continues in x, which of the rule's sites x is: plane of (state, x) = pair_row[pair_off[state] + that]
     uint32_t context_depth;
     uint32_t start_n_items, start_H, start_n_front, start_flags;
+    uint32_t cls_words[64];              // T's byte classes: here, too, so that accepting a token need not wait for T to find them
     const uint32_t* start_items; const uint2* start_wait; const uint32_t* start_wait_off; const uint64_t* start_front;
 };
 // B matcher slots of fixed capacity.  Slot b's state is what FillRow b points at: its frontier planes at front[b * KF ..],
@@ -205,6 +213,8 @@ struct BatchDev {
 constexpr int32_t kTokenReset = -2;      // xg2_batch_accept_tokens: "start a new sequence in this slot"
 // status codes written per slot (the XG2_* values of the C ABI)
 constexpr int32_t kAccOk = 0, kAccInvalid = -1, kAccRejected = -3, kAccOverflow = -4;
+// rec_dev[id] for every token, from the other arrays of Vd.
+void launch_token_records(const DevVocab& Vd, TokenRecord* rec_dev, hipStream_t stream);
 void launch_accept(const BatchDev& D, const DevVocab& Vd, uint32_t eos_id, const int32_t* token_ids_dev, int32_t* status_dev, hipStream_t stream);
 // rows_dev (n of them; nullptr = slots 0 .. n - 1) start a new sequence of cache `cache_idx`
 void launch_batch_assign(const BatchDev& D, const int32_t* rows_dev, uint32_t n, uint32_t cache_idx, hipStream_t stream);

@@ -5,6 +5,7 @@
 //   k_copy_masked  short tokens of a plane taken from the plane of a state they cannot tell apart (section 3.6)
 //   k_copy_first_byte  tokens of a plane taken from the plane of a state that moves alike on their first byte
 //   k_upload       per-call plan and tables from pinned host memory
+//   k_token_records  the vocabulary by token id, when it goes to the device
 //   k_clear        a fill's counter words, where the fill of the call before did not clear them
 //   k_stage        the same for a build, together with the clearing of fresh rows and the chunk records
 //   k_plane_summary  per built plane: bit counts, and the short list of its uncertain tokens that the fill reads
@@ -514,6 +515,16 @@ __global__ __launch_bounds__(256) void k_upload(uint4* dst, const uint4* src, si
     for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (size_t)gridDim.x * 256) dst[i] = src[i];
 }
 
+// The vocabulary's records by token id, from its arrays by sorted rank.
+__global__ __launch_bounds__(256) void k_token_records(DevVocab Vd, TokenRecord* rec) {
+    const uint32_t id = blockIdx.x * 256 + threadIdx.x;
+    if (id >= Vd.V) return;
+    TokenRecord t{};
+    const uint32_t rank = Vd.rank[id];
+    if (rank < Vd.n_sorted) { t.head = Vd.tok16[rank]; t.off = Vd.off[rank]; t.n_bytes = Vd.off[rank + 1] - t.off; }
+    rec[id] = t;
+}
+
 __global__ __launch_bounds__(64) void k_clear(uint32_t* words, uint32_t n) {
     if (threadIdx.x < n) words[threadIdx.x] = 0;
 }
@@ -710,113 +721,157 @@ __device__ __forceinline__ uint32_t lane_value(uint32_t v, uint32_t k) { return 
 // A value that is the same in all lanes, as the compiler cannot know where it came from memory.
 __device__ __forceinline__ uint32_t same_in_all(uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); }
 // A load whose address is the same in all lanes, from memory that no kernel writes while this one runs: the scalar cache
-// serves it, and the compiler knows that the value is uniform.
+// serves it, and the compiler knows that the value is uniform.  Word by word (the compiler joins them): a struct copied as such
+// is fetched by vector loads, and every use of a pointer in it then pays for bringing it back to scalar registers.
 template <class P>
 __device__ __forceinline__ P uniform_load(const P* p) {
 #if defined(__HIP_DEVICE_COMPILE__)
-    return *(const __attribute__((address_space(4))) P*)p;
+    static_assert(sizeof(P) % 4 == 0, "scalar loads are of words");
+    const auto* q = (const __attribute__((address_space(4))) uint32_t*)p;
+    uint32_t w[sizeof(P) / 4];
+    _Pragma("unroll") for (unsigned k = 0; k < sizeof(P) / 4; ++k) w[k] = q[k];
+    P v;
+    __builtin_memcpy(&v, w, sizeof(P));
+    return v;
 #else
     return *p;
 #endif
 }
+// The lanes in which x holds: one compare.  (Of two conditions joined by && the compiler makes three vector instructions more than of
+// two sets of lanes joined by &.)
+__device__ __forceinline__ unsigned long long lanes_of(bool x) { return __builtin_amdgcn_ballot_w64(x); }
+// Sets of lanes as 64 bits: whether this lane is one of them, how many of them are below it, and n < 64 lanes from `first` on.
+__device__ __forceinline__ bool has_lane(unsigned long long m) { return __builtin_amdgcn_inverse_ballot_w64(m); }
+__device__ __forceinline__ uint32_t count_below(unsigned long long m) { return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0)); }
+__device__ __forceinline__ unsigned long long lane_range(uint32_t first, uint32_t n) { return ((1ull << n) - 1) << first; }
 __device__ __forceinline__ uint32_t next_bit(unsigned long long& m) { const uint32_t j = (uint32_t)__ffsll((long long)m) - 1; m &= m - 1; return j; }
+
+// A word of a table, by its index; the byte offset is worked out in 32 bits (no table reaches 4 GB), so that the load takes it as
+// an offset to the uniform base address.
+template <class P>
+__device__ __forceinline__ P tab_at(const P* base, uint32_t index) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    return *(const __attribute__((address_space(1))) P*)((const __attribute__((address_space(1))) char*)base + index * (uint32_t)sizeof(P));
+#else
+    return base[index];
+#endif
+}
 
 // The Earley steps of earley_core.hpp with one wavefront per token: lane k holds item k of the set at hand together with the
 // state it goes to on the next byte (looked up when the item is entered: it is the lookahead and the next scanner step in
-// one).  Control flow is the same in all lanes; values picked out of a lane are wave-uniform.
+// one) and its rule.  Control flow is the same in all lanes; values picked out of a lane are wave-uniform.
+// A step is bound by its chain of dependent loads (about 500 cycles each beside the logits that pass through the caches; a
+// slot's wavefront waits three quarters of its time), so what can be asked for together is: a state that is entered has its
+// record (rule, expansion) fetched beside its transition, and an item keeps its rule for the completer.
+// Wait entries, REG: all in registers, the context's and the token's own: lane k < n_w holds entry k, lane s <= the set at
+// hand where set s starts.  Not REG: in LDS, and in registers those of the set at hand.
+template <bool REG>
 struct WaveScan {
     static constexpr uint32_t N = 64;
+    static constexpr uint32_t NO_ITEM = SID_MASK;  // what lanes without an item hold: no state has this number (it would be the sink's), no flags
     const DevTables T;
     const uint2* ctx_wait; const uint32_t* ctx_off; const uint32_t H;   // LDS: wait entries of the context's H sets, and where each set's start
     const uint2* own_wait; const uint32_t* own_off;                     // LDS: the same for the sets made during the token (numbered from H)
     const uint32_t lane;
     const uint32_t max_items;                     // at most N: more is an overflow
-    uint32_t item, to;                            // the set under construction: lane k < n holds item k, and where it goes on the next byte
-    uint32_t n;
-    uint32_t w_rule, w_tgt, n_w;                  // its wait entries so far: lane k < n_w holds entry k
+    uint32_t item, to, rule;                      // the set under construction: lane k < n holds item k, where it goes on the next byte, and its rule
+    uint32_t n;                                   //   (not of an item that starts in the set: it completes nothing)
+    uint32_t w_rule, w_tgt, w_beg, n_w;           // its wait entries so far: lane w_beg <= k < n_w holds entry k
+    uint32_t set_off;                             // REG: lane s holds the first entry of set s
     uint32_t set_idx, la;                         // its number; class of the next byte, or NO_TARGET after the last one
     bool full, root_done;
 
-    __device__ __forceinline__ bool add(uint32_t v, uint32_t v_to) {
-        if (__ballot(lane < n && item == v)) return false;
+    __device__ __forceinline__ bool add(uint32_t v, uint32_t v_to, uint32_t v_rule) {
+        if (lanes_of(item == v)) return false;
         if (n == max_items) { full = true; return false; }
-        if (lane == n) { item = v; to = v_to; }
+        if (lane == n) { item = v; to = v_to; rule = v_rule; }
         ++n;
         return true;
     }
-    __device__ __forceinline__ void add_wait(uint32_t rule, uint32_t tgt) {
-        if (__ballot(lane < n_w && w_tgt == tgt && w_rule == rule)) return;
+    __device__ __forceinline__ void add_wait(uint32_t w, uint32_t tgt) {
+        if (lanes_of(w_tgt == tgt) & lanes_of(w_rule == w) & lanes_of(lane < n_w) & (REG ? lanes_of(lane >= w_beg) : ~0ull)) return;
         if (n_w == N) { full = true; return; }
-        if (lane == n_w) { w_rule = rule; w_tgt = tgt; }
+        if (lane == n_w) { w_rule = w; w_tgt = tgt; }
         ++n_w;
     }
     // where a state goes on the next byte (a gather over the lanes that ask)
     __device__ __forceinline__ uint32_t next_of(bool mine, uint32_t ref) const {
         uint32_t t = NO_TARGET;
-        if (mine && (ref & F_BYTE) && la != NO_TARGET) t = tab(T.trans + (ref & SID_MASK) * T.n_classes + la);
+        if (mine && (ref & F_BYTE) && la != NO_TARGET) t = tab_at(T.trans, (ref & SID_MASK) * T.n_classes + la);
         return t;
     }
     // byte edges only, not final, and none of them for the next byte: the item can do nothing
-    __device__ __forceinline__ bool is_inert(uint32_t ref, uint32_t t) const { return (ref & (F_BYTE | F_REF | F_FINAL)) == F_BYTE && t == T.sink; }
-    __device__ __forceinline__ void expand(uint32_t ref, uint32_t origin) {
-        const uint4 d = uniform_load(T.state + (ref & SID_MASK));
-        const uint32_t* e = T.exp_list + d.y;
-        const uint32_t* e2 = e + d.z;
-        const uint32_t most = d.z > d.w ? d.z : d.w;
+    __device__ __forceinline__ unsigned long long inert(uint32_t ref, uint32_t t) const { return lanes_of((ref & (F_BYTE | F_REF | F_FINAL)) == F_BYTE) & lanes_of(t == T.sink); }
+    // what entering a state with record {of, at, n_items, n_waits} adds besides the item itself
+    __device__ __forceinline__ void expand(uint32_t of, uint32_t at, uint32_t n_items, uint32_t n_waits, uint32_t origin) {
+        const uint32_t* e = T.exp_list + at;
+        const uint32_t* e2 = e + n_items;
+        const uint32_t most = n_items > n_waits ? n_items : n_waits;
         for (uint32_t base = 0; base < most; base += N) {
-            const bool has_item = base + lane < d.z, has_wait = base + lane < d.w;
-            uint32_t w = 0, rule = 0, tgt = 0;
-            if (has_item) w = tab(e + base + lane);
-            if (has_wait) { rule = tab(e2 + 2 * (base + lane)); tgt = tab(e2 + 2 * (base + lane) + 1); }
-            const uint32_t t = next_of(has_item, w);
-            for (unsigned long long m = __ballot(has_item && !is_inert(w, t)); m;) {
-                const uint32_t j = next_bit(m), v = lane_value(w, j);
-                add((v & REF_MASK) | (((v & EXP_CURRENT) ? set_idx : origin) << REF_BITS), lane_value(t, j));
+            const bool has_item = base + lane < n_items, has_wait = base + lane < n_waits;
+            uint32_t v = 0, w = 0, tgt = 0;
+            if (has_item) v = tab_at(e, base + lane);
+            if (has_wait) { w = tab_at(e2, 2 * (base + lane)); tgt = tab_at(e2, 2 * (base + lane) + 1); }
+            const uint32_t t = next_of(has_item, v);
+            // the wait entries while the transitions are on their way
+            for (unsigned long long m = lanes_of(base + lane < n_waits); m;) {
+                const uint32_t j = next_bit(m), x = lane_value(tgt, j);
+                add_wait(lane_value(w, j), (x & REF_MASK) | (((x & EXP_CURRENT) ? set_idx : origin) << REF_BITS));
             }
-            for (unsigned long long m = __ballot(has_wait); m;) {
-                const uint32_t j = next_bit(m), v = lane_value(tgt, j);
-                add_wait(lane_value(rule, j), (v & REF_MASK) | (((v & EXP_CURRENT) ? set_idx : origin) << REF_BITS));
+            for (unsigned long long m = lanes_of(base + lane < n_items) & ~inert(v, t); m;) {
+                const uint32_t j = next_bit(m), x = lane_value(v, j);
+                add((x & REF_MASK) | (((x & EXP_CURRENT) ? set_idx : origin) << REF_BITS), lane_value(t, j), of);   // (an advance stays in its rule)
             }
         }
     }
     // the lanes of m each enter the state `ref` with their origin
     __device__ __forceinline__ void enter(unsigned long long m, uint32_t ref, uint32_t origin) {
-        const uint32_t t = next_of((m >> lane) & 1, ref);
-        m &= ~__ballot(is_inert(ref, t));
+        const bool mine = has_lane(m);
+        uint4 d = make_uint4(0, 0, 0, 0);
+        if (mine && (ref & (F_REF | F_FINAL))) d = tab_at(T.state, ref & SID_MASK);
+        const uint32_t t = next_of(mine, ref);
+        m &= ~inert(ref, t);
         while (m) {
-            const uint32_t j = next_bit(m), r = lane_value(ref, j), o = lane_value(origin, j);
-            if ((r & (F_BYTE | F_FINAL)) || !(r & F_REF)) { if (!add(r | (o << REF_BITS), lane_value(t, j))) continue; }
-            if (r & F_REF) expand(r, o);
+            const uint32_t j = next_bit(m), r = lane_value(ref, j), o = lane_value(origin, j), of = lane_value(d.x, j);
+            if ((r & (F_BYTE | F_FINAL)) || !(r & F_REF)) { if (!add(r | (o << REF_BITS), lane_value(t, j), of)) continue; }
+            if (r & F_REF) expand(of, lane_value(d.y, j), lane_value(d.z, j), lane_value(d.w, j), o);
         }
     }
-    // One byte: scanner and completer over the set held in (cur_item, cur_to, cur_n).  False: nothing survives.
-    __device__ __forceinline__ bool step(uint32_t cur_item, uint32_t cur_to, uint32_t cur_n) {
-        n = 0; n_w = 0; root_done = false;
-        enter(__ballot(lane < cur_n && (cur_item & F_BYTE) && cur_to != T.sink), cur_to, cur_item >> REF_BITS);
+    // One byte: scanner and completer over the set held in (cur_item, cur_to), NO_ITEM beyond its items.  False: nothing survives.
+    __device__ __forceinline__ bool step(uint32_t cur_item, uint32_t cur_to) {
+        n = 0; root_done = false;
+        item = NO_ITEM;
+        if (REG) { w_beg = n_w; if (lane == set_idx) set_off = n_w; }
+        else n_w = 0;
+        enter(lanes_of((cur_item & F_BYTE) != 0) & lanes_of(cur_to != T.sink), cur_to, cur_item >> REF_BITS);
         unsigned long long done = 0;
         for (;;) {
-            unsigned long long m = __ballot(lane < n && (item & F_FINAL) && (item >> REF_BITS) != set_idx) & ~done;
+            unsigned long long m = lanes_of((item & F_FINAL) != 0) & lanes_of((item >> REF_BITS) != set_idx) & ~done;
             if (!m) break;
             done |= m;
-            uint32_t rule_of = 0;
-            if (((m >> lane) & 1) && (item >> REF_BITS) != ROOT_ORIGIN) rule_of = tab(&T.state[item & SID_MASK].x);
-            const uint32_t held = item;                             // entering below only appends
-            while (m) {
-                const uint32_t j = next_bit(m), o = lane_value(held, j) >> REF_BITS;
+            while (m) {                                              // (entering below only appends to the items)
+                const uint32_t j = next_bit(m), o = lane_value(item, j) >> REF_BITS;
                 if (o == ROOT_ORIGIN) { root_done = true; continue; }
+                const uint32_t of = lane_value(rule, j);
+                if (REG) {
+                    const uint32_t lo = lane_value(set_off, o), hi = lane_value(set_off, o + 1);
+                    const unsigned long long hit = lanes_of(w_rule == of) & lanes_of(lane >= lo) & lanes_of(lane < hi);
+                    if (hit) enter(hit, w_tgt & REF_MASK, w_tgt >> REF_BITS);
+                    continue;
+                }
                 const bool own = o >= H;
                 const uint2* wait = own ? own_wait : ctx_wait;
                 const uint32_t* off = own ? own_off + (o - H) : ctx_off + o;
-                const uint32_t rule = lane_value(rule_of, j), lo = same_in_all(off[0]), hi = same_in_all(off[1]);
+                const uint32_t lo = same_in_all(off[0]), hi = same_in_all(off[1]);
                 for (uint32_t base = lo; base < hi; base += N) {
                     uint2 w = make_uint2(0, 0);
                     if (base + lane < hi) w = wait[base + lane];
-                    const unsigned long long hit = __ballot(base + lane < hi && w.x == rule);
+                    const unsigned long long hit = lanes_of(base + lane < hi) & lanes_of(w.x == of);
                     if (hit) enter(hit, w.y & REF_MASK, w.y >> REF_BITS);
                 }
             }
         }
-        return n != 0 || n_w != 0;
+        return n != 0 || n_w != w_beg;
     }
 };
 
@@ -895,13 +950,12 @@ __device__ __forceinline__ void list_candidates(const FillBatch& F, uint32_t* n_
 constexpr int RECHECK_NO = 0, RECHECK_YES = 1, RECHECK_OVER = 2;
 // One candidate token, one lane, against the row's full context.
 __device__ __forceinline__ int recheck_lane(const DevVocab& Vd, const DevTables& T, const uint32_t* cls_words, const DevCtx& C, uint32_t id, FillStore& st) {
-    const uint32_t rank = Vd.rank[id];
-    if (rank >= Vd.n_sorted) return RECHECK_NO;
-    const int n = (int)(Vd.off[rank + 1] - Vd.off[rank]);
+    const TokenRecord rec = tab(Vd.rec + id);
+    if (rec.n_bytes == 0) return RECHECK_NO;
     RegBytes tok;
-    tok.v = Vd.tok16[rank];
+    tok.v = rec.head;
     st.reset();
-    const int res = scan_token(T, cls_words, C, tok, n, st);
+    const int res = scan_token(T, cls_words, C, tok, (int)rec.n_bytes, st);
     return (res & RES_OVERFLOW) ? RECHECK_OVER : (res & RES_ALIVE) ? RECHECK_YES : RECHECK_NO;
 }
 
@@ -916,27 +970,27 @@ __device__ __forceinline__ void wave_sync() {                       // orders a 
 // whatever became of it (so that the count does not depend on the way a row takes).
 __device__ __forceinline__ int recheck_wave(const DevVocab& Vd, const SlowScratch& S, const DevTables& T, const FillCtx& X, FillOwn& own, uint32_t H, uint32_t item_n, uint32_t my_item,
                                             uint32_t id, uint32_t lane, bool* large) {
-    const uint32_t rank = uniform_load(Vd.rank + id);
-    if (rank >= Vd.n_sorted) return RECHECK_NO;
-    const uint32_t at = uniform_load(Vd.off + rank), n_bytes = uniform_load(Vd.off + rank + 1) - at;
-    const uint4 tok16 = uniform_load(Vd.tok16 + rank);
+    const TokenRecord rec = uniform_load(Vd.rec + id);
+    const uint32_t at = rec.off, n_bytes = rec.n_bytes;
+    const uint4 tok16 = rec.head;
+    if (n_bytes == 0) return RECHECK_NO;
     if (n_bytes > FILL_WAVE_BYTES) return RECHECK_OVER;
     *large |= n_bytes > 16 || item_n > (uint32_t)FILL_K;
     const uint32_t words[4] = {tok16.x, tok16.y, tok16.z, tok16.w};
     uint32_t byte = (words[(lane >> 2) & 3] >> (8 * (lane & 3))) & 0xFF;
     if (n_bytes > 16) byte = lane < n_bytes ? tab(Vd.bytes + at + lane) : 0u;
     const uint32_t cls_of = reinterpret_cast<const uint8_t*>(X.cls_words)[byte];
-    const uint32_t max_items = S.k_cap < WaveScan::N ? S.k_cap : WaveScan::N, max_waits = S.wm_cap < FILL_OWN_WAITS ? S.wm_cap : FILL_OWN_WAITS;
-    WaveScan A{T, X.wait, X.off, H, own.wait, own.off, lane, max_items, 0, 0, 0, 0, 0, 0, 0, 0, false, false};
+    const uint32_t max_items = S.k_cap < WaveScan<false>::N ? S.k_cap : WaveScan<false>::N, max_waits = S.wm_cap < FILL_OWN_WAITS ? S.wm_cap : FILL_OWN_WAITS;
+    WaveScan<false> A{T, X.wait, X.off, H, own.wait, own.off, lane, max_items, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, false, false};
     if (item_n > max_items) return RECHECK_OVER;
     A.la = lane_value(cls_of, 0);
-    uint32_t cur = my_item, cur_n = item_n, cur_to = A.next_of(lane < cur_n, cur), n_own = 0;
+    uint32_t cur = lane < item_n ? my_item : A.NO_ITEM, cur_to = A.next_of(true, cur), n_own = 0;
     if (lane == 0) own.off[0] = 0;
     for (uint32_t i = 0; i < n_bytes; ++i) {
         A.set_idx = H + i;
         A.la = i + 1 < n_bytes ? lane_value(cls_of, i + 1) : NO_TARGET;
         wave_sync();
-        const bool alive = A.step(cur, cur_to, cur_n);
+        const bool alive = A.step(cur, cur_to);
         if (A.full) return RECHECK_OVER;
         if (!alive) return RECHECK_NO;
         *large |= A.n > (uint32_t)FILL_K || n_own + A.n_w > (uint32_t)FILL_WM;
@@ -945,7 +999,7 @@ __device__ __forceinline__ int recheck_wave(const DevVocab& Vd, const SlowScratc
         if (lane < A.n_w) own.wait[n_own + lane] = make_uint2(A.w_rule, A.w_tgt);
         n_own += A.n_w;
         if (lane == 0) own.off[i + 1] = n_own;
-        cur = A.item; cur_to = A.to; cur_n = A.n;
+        cur = A.item; cur_to = A.to;
     }
     return RECHECK_YES;
 }
@@ -964,12 +1018,11 @@ __device__ __forceinline__ void leave_undecided(const SlowScratch& S, uint32_t b
 }
 // One (row, token) pair that outgrew every shorter list: one lane, item lists in device memory (lane gl of the scratch).
 __device__ __forceinline__ bool recheck_large(const FillBatch& F, const DevVocab& Vd, const SlowScratch& S, const FillRow& r, uint32_t b, uint32_t id, uint32_t gl) {
-    const uint32_t rank = Vd.rank[id];
-    if (rank >= Vd.n_sorted) return false;
-    const uint32_t off = Vd.off[rank];
-    const int n = (int)(Vd.off[rank + 1] - off);
+    const TokenRecord rec = tab(Vd.rec + id);
+    const int n = (int)rec.n_bytes;
+    if (n == 0) return false;
     const DevTables T = F.tables[r.tables_idx];
-    MemBytes tok{Vd.bytes + off};
+    MemBytes tok{Vd.bytes + rec.off};
     GlobalStore st;
     st.init(S.mem + gl, S.n_lanes, S.k_cap, S.wm_cap);
     st.reset();
@@ -1089,7 +1142,7 @@ __global__ __launch_bounds__(FILL_THREADS) __attribute__((amdgpu_waves_per_eu(6)
     // whether wavefronts can parse from this row's context, and then the context in LDS
     bool ctx_fits = false;
     uint32_t n_wait = 0, my_item = 0;
-    static_assert(kFillContextItems <= WaveScan::N, "a context's items lie across the lanes");
+    static_assert(kFillContextItems <= WaveScan<false>::N, "a context's items lie across the lanes");
     if (parses && !listed_way && r.item_n <= kFillContextItems && r.H <= FILL_CTX_SETS) {
         n_wait = uniform_load(F.ctx_wait_off + r.waitoff_off + r.H);
         ctx_fits = n_wait <= FILL_CTX_WAITS;
@@ -1265,15 +1318,14 @@ __global__ __launch_bounds__(64) void k_recheck_slow(FillBatch F, DevVocab Vd, i
     for (uint32_t idx = gl; idx < count; idx += S.n_lanes) {
         const uint32_t b = S.list[2 * idx], id = S.list[2 * idx + 1];
         const FillRow r = F.rows[b];
-        const uint32_t rank = Vd.rank[id];
-        if (rank >= Vd.n_sorted) continue;
-        const uint32_t off = Vd.off[rank];
-        const int n = (int)(Vd.off[rank + 1] - off);
+        const TokenRecord rec = tab(Vd.rec + id);
+        const int n = (int)rec.n_bytes;
+        if (n == 0) continue;
         bool alive;
         int res = RES_OVERFLOW;
         if (S.k_cap >= (uint32_t)MidStore::K) {
             const DevTables T = F.tables[r.tables_idx];
-            MemBytes tok{Vd.bytes + off};
+            MemBytes tok{Vd.bytes + rec.off};
             mid.reset();
             res = scan_token<MidStore, false, MemBytes>(T, T.byte_class_words, row_ctx(F, r), tok, n, mid);
         }
@@ -1289,7 +1341,11 @@ __global__ __launch_bounds__(64) void k_recheck_slow(FillBatch F, DevVocab Vd, i
 // dependent steps, so the wavefront works on one slot as a whole (WaveScan above): items, wait entries and expansions lie
 // across the lanes, a set's look-ups in the transition table are one gather, a prediction is one load, and what remains in
 // order are list insertions in registers.  (With lane 0 doing everything on lists in LDS the same steps took 16 us at 16 - 64
-// slots and 24 us at 1,024; one lane per slot 458 us.)  A token or context that does not fit across 64 lanes takes the
+// slots and 24 us at 1,024; one lane per slot 458 us.)  Bound by the latency of a dozen dependent loads (300 - 850 cycles each;
+// the wavefront waits three quarters of its time), so everything that can be asked for at once is: a token comes as one record by
+// its id, the slot's context straight into registers, pointers by scalar loads.  Against vector loads of the structs, contexts in
+// LDS and three loads in a row to find a token's bytes, us at 1 / 64 / 1,024 slots (JSON schemas, records): 6.0 / 9.4 / 12.1 -> 5.0 / 7.6 / 9.6.
+// A token or context that does not fit across 64 lanes takes the
 // recogniser of accept_core.hpp on lane 0, with its lists, the renumbering table and the frontier staging in LDS, and one
 // too large for that the same with everything in device memory.  A slot whose capacity is exceeded gets a sticky error and
 // answers XG2_EOVERFLOW until it is reset.
@@ -1356,190 +1412,233 @@ __global__ __launch_bounds__(256) void k_batch_assign(BatchDev D, const int32_t*
 
 constexpr uint32_t ACC_KI = kSlotItems, ACC_KH = kSlotSets, ACC_KW = kSlotWaits, ACC_KF = kSlotPlanes;     // the slot capacities the LDS staging is laid out for
 
-// The slot's next state from token `tok16` (1 .. 16 bytes), written to the slot's other buffer; results in out_n (items, sets,
-// planes, root can end).  ACC_RETRY: something does not fit across the lanes, nothing has been written that counts.
-__device__ __forceinline__ int accept_wave(const BatchDev& D, const CacheDev* Cp, const uint8_t* cls_bytes, uint32_t b, const FillRow& r, size_t slot, uint4 tok16, uint32_t n_bytes,
-                                           uint32_t in_item, uint2* wait, uint32_t* off, uint32_t* pair_sid, uint32_t* pair_tgt, uint32_t lane, uint32_t out_n[4]) {
-    const DevTables T = uniform_load(&Cp->T);
-    const bool depth1 = uniform_load(&Cp->context_depth) == 1;
-    const uint32_t H = r.H, n_sets = H + n_bytes;
-    if (n_sets > 64 || r.item_n > 64) return ACC_RETRY;
+// What the kernel is launched with.  args_again() reads it anew from the launch's own memory: the way out below is rarely taken, and
+// what only it needs must not take up registers on the way that nearly every token goes.
+struct AcceptArgs { BatchDev D; DevVocab Vd; uint32_t eos_id; const int32_t* token_ids; int32_t* status; };
+template <class A>
+__device__ __forceinline__ A args_again() {
+#if defined(__HIP_DEVICE_COMPILE__)
+    auto p = (const __attribute__((address_space(4))) A*)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    return *p;
+#else
+    return A{};
+#endif
+}
+
+// Values that are wanted here: loads whose results are named are asked for before this point, all together, and not one after the
+// other where the compiler would rather have them (behind the branch on an earlier one).
+#if defined(__HIP_DEVICE_COMPILE__)
+#define PIN(...) asm volatile("" : __VA_ARGS__)
+#else
+#define PIN(...) (void)0
+#endif
+// What accepting a token needs of a cache.
+struct CacheView {
+    DevTables T;
+    const uint64_t* plain_row; const uint32_t* pair_off; const uint64_t* pair_row; const uint32_t* site_of_off; const uint2* site_of;
+    bool depth1;
+};
+__device__ __forceinline__ CacheView cache_view(const CacheDev* p) {
+    CacheView c;
+    c.T = uniform_load(&p->T);
+    c.plain_row = uniform_load(&p->plain_row); c.pair_off = uniform_load(&p->pair_off); c.pair_row = uniform_load(&p->pair_row);
+    c.site_of_off = uniform_load(&p->site_of_off); c.site_of = uniform_load(&p->site_of);
+    c.depth1 = uniform_load(&p->context_depth) == 1;
+    return c;
+}
+
+// The slot's next state from token `tok16` (1 .. 16 bytes), written to the slot's other buffer `slot`; results in out_n (items,
+// sets, planes, root can end).  Lane k has the context's item k, wait entry k and start of set k (what lies beyond the counts is
+// not looked at), and the classes of bytes 4 k .. 4 k + 3.  ACC_RETRY: something does not fit across the lanes, nothing has been
+// written that counts.
+__device__ __forceinline__ int accept_wave(const BatchDev& D, const CacheView& C, uint32_t b, size_t slot, uint4 tok16, uint32_t n_bytes, uint32_t H, uint32_t item_n,
+                                           uint32_t in_item, uint2 in_wait, uint32_t in_off, uint32_t cls_word, uint32_t lane, uint32_t out_n[4]) {
+    const DevTables& T = C.T;
+    const bool depth1 = C.depth1;
+    const uint32_t n_sets = H + n_bytes;
+    const uint32_t n_wait_in = lane_value(in_off, H < 64 ? H : 0);
+    if (n_sets > 64 || H > 63 || item_n > 64 || n_wait_in > 64) return ACC_RETRY;
     // classes of the token's bytes, one a lane
     const uint32_t words[4] = {tok16.x, tok16.y, tok16.z, tok16.w};
-    const uint32_t byte = (words[(lane >> 2) & 3] >> (8 * (lane & 3))) & 0xFF, cls_of = cls_bytes[byte];
-    uint32_t n_wait = same_in_all(off[H]);
-    if (n_wait > 64) return ACC_RETRY;
-    WaveScan A{T, wait, off, H, wait, off + H, lane, 64, 0, 0, 0, 0, 0, 0, 0, 0, false, false};
-    uint32_t cur = in_item, cur_n = r.item_n;
+    const uint32_t byte = (words[(lane >> 2) & 3] >> (8 * (lane & 3))) & 0xFF;
+    const uint32_t cls_of = ((uint32_t)__shfl((int)cls_word, (int)(byte >> 2)) >> (8 * (byte & 3))) & 0xFF;
+    WaveScan<true> A{T, nullptr, nullptr, H, nullptr, nullptr, lane, 64, 0, 0, 0, 0, in_wait.x, in_wait.y, 0, n_wait_in, in_off, 0, 0, false, false};
+    uint32_t cur = lane < item_n ? in_item : A.NO_ITEM;
     A.la = lane_value(cls_of, 0);
-    uint32_t cur_to = A.next_of(lane < cur_n, cur);
+    uint32_t cur_to = A.next_of(true, cur);
     for (uint32_t i = 0; i < n_bytes; ++i) {
         A.set_idx = H + i;
         A.la = i + 1 < n_bytes ? lane_value(cls_of, i + 1) : NO_TARGET;
-        const bool alive = A.step(cur, cur_to, cur_n);
+        const bool alive = A.step(cur, cur_to);
         if (A.full) return ACC_RETRY;
         if (!alive) return ACC_REJECTED;
-        if (n_wait + A.n_w > 64) return ACC_RETRY;
-        if (lane < A.n_w) wait[n_wait + lane] = make_uint2(A.w_rule, A.w_tgt);
-        n_wait += A.n_w;
-        if (lane == 0) off[H + i + 1] = n_wait;
-        __syncthreads();                                            // one wave: orders the LDS traffic
-        cur = A.item; cur_to = A.to; cur_n = A.n;
+        cur = A.item; cur_to = A.to;
     }
-    // Which sets are still reachable: the current one, the origins of its items, and on from there through the wait entries
-    // (an entry's origin is never above its own set, so one pass downwards settles it).  Entry e is lane e's, set s lane s's.
-    const uint2 my_wait = lane < n_wait ? wait[lane] : make_uint2(0, 0);
-    const uint32_t my_off = lane <= n_sets ? off[lane] : 0u, w_origin = my_wait.y >> REF_BITS;
-    uint32_t my_set = 0;
-    for (uint32_t s = 1; s < n_sets; ++s) my_set += lane_value(my_off, s) <= lane ? 1u : 0u;
-    const bool scans = lane < cur_n && (cur & F_BYTE);              // final-only items have done their work in the closure
-    unsigned long long reach = 1ull << (n_sets - 1);
-    for (unsigned long long m = __ballot(scans && (cur >> REF_BITS) != ROOT_ORIGIN); m;) reach |= 1ull << (lane_value(cur, next_bit(m)) >> REF_BITS);
-    for (uint32_t s = n_sets; s-- > 0;) {
-        if (!((reach >> s) & 1)) continue;
-        for (unsigned long long m = __ballot(lane < n_wait && my_set == s && w_origin != ROOT_ORIGIN); m;) reach |= 1ull << lane_value(w_origin, next_bit(m));
+    const uint32_t n_wait = A.n_w;
+    const uint2 my_wait = make_uint2(A.w_rule, A.w_tgt);
+    const uint32_t my_off = lane < n_sets ? A.set_off : n_wait, w_origin = my_wait.y >> REF_BITS, c_origin = cur >> REF_BITS;
+    const unsigned long long scanning = lanes_of((cur & F_BYTE) != 0);   // final-only items have done their work in the closure
+    const unsigned long long alone = depth1 ? scanning : lanes_of(c_origin == ROOT_ORIGIN) & scanning;   // items whose plane has no context
+    // The planes of the frontier hang on three loads, one after the other; the first of them is under way while the sets are
+    // renumbered: of every item its rule and its state's row of planes (or its plane), of every wait entry the row of sites of
+    // the state it continues in.
+    uint32_t rule_of = 0, planes_at = 0, planes_end = 0, sites_at = 0, sites_end = 0;
+    uint64_t row = 0;
+    if (has_lane(alone)) row = tab_at(C.plain_row, cur & SID_MASK);
+    if (has_lane(scanning & ~alone)) {
+        rule_of = tab_at(T.state, cur & SID_MASK).x;
+        planes_at = tab_at(C.pair_off, cur & SID_MASK); planes_end = tab_at(C.pair_off, (cur & SID_MASK) + 1);
+    }
+    if (lane < n_wait && !depth1) {
+        sites_at = tab_at(C.site_of_off, my_wait.y & SID_MASK); sites_end = tab_at(C.site_of_off, (my_wait.y & SID_MASK) + 1);
+    }
+    // Which sets are still reachable: the current one, the origins of its items, and on from there through the wait entries (an
+    // entry's origin is never above its own set, so one pass downwards settles it); `kept`: their wait entries.
+    unsigned long long reach = 0, kept = 0;
+    for (uint32_t s = n_sets, end = n_wait; s-- > 0;) {
+        const uint32_t begin = lane_value(my_off, s);
+        if (s + 1 == n_sets || ((lanes_of(c_origin == s) & scanning) | (lanes_of(w_origin == s) & kept)) != 0) {
+            reach |= 1ull << s;
+            kept |= end - begin < 64 ? lane_range(begin, end - begin) : ~0ull;
+        }
+        end = begin;
     }
     // renumbered in their old order: the wait entries and starts of the sets that are kept, the items that can scan
-    auto renumber = [&](uint32_t o) { return o == ROOT_ORIGIN ? ROOT_ORIGIN : (uint32_t)__popcll(reach & ((1ull << o) - 1)); };
-    const uint32_t newH = (uint32_t)__popcll(reach);
-    const unsigned long long below = (1ull << lane) - 1;
-    const bool keep = lane < n_wait && ((reach >> my_set) & 1);
-    const unsigned long long kept = __ballot(keep), scanning = __ballot(scans);
-    if (keep) D.wait[slot * D.KW + (uint32_t)__popcll(kept & below)] = make_uint2(my_wait.x, (my_wait.y & REF_MASK) | (renumber(w_origin) << REF_BITS));
-    if (lane < n_sets && ((reach >> lane) & 1))
-        D.wait_off[slot * (D.KH + 1) + renumber(lane)] = (uint32_t)__popcll(my_off < 64 ? kept & ((1ull << my_off) - 1) : kept);
-    if (lane == 0) D.wait_off[slot * (D.KH + 1) + newH] = (uint32_t)__popcll(kept);
-    if (scans) D.items[slot * D.KI + (uint32_t)__popcll(scanning & below)] = (cur & REF_MASK) | (renumber(cur >> REF_BITS) << REF_BITS);
-    // the frontier's planes: of every item alone (root instance, or context depth 1), else under every entry of the item's
-    // origin that waits for its rule; the pairs are listed in LDS and looked up one a lane
-    constexpr uint32_t ALONE = 0xFFFFFFFFu;
-    const bool alone = (cur >> REF_BITS) == ROOT_ORIGIN || depth1;
-    uint32_t rule_of = 0;
-    if (scans && !alone) rule_of = tab(&T.state[cur & SID_MASK].x);
-    uint32_t n_pairs = 0;
-    for (unsigned long long m = scanning; m;) {
-        const uint32_t j = next_bit(m), v = lane_value(cur, j), o = v >> REF_BITS;
-        if (o == ROOT_ORIGIN || depth1) {
-            if (n_pairs >= 64) return ACC_RETRY;
-            if (lane == 0) { pair_sid[n_pairs] = v; pair_tgt[n_pairs] = ALONE; }
-            ++n_pairs;
-            continue;
+    uint32_t newH = 0, n_kept = 0, w_new = ROOT_ORIGIN, c_new = ROOT_ORIGIN, new_off = 0;
+    for (unsigned long long m = reach; m; ++newH) {
+        const uint32_t s = next_bit(m), begin = lane_value(my_off, s), end = s + 1 < 64 ? lane_value(my_off, s + 1) : n_wait;
+        w_new = w_origin == s ? newH : w_new;
+        c_new = c_origin == s ? newH : c_new;
+        new_off = lane == newH ? n_kept : new_off;
+        n_kept += end - begin;
+    }
+    uint2* const wait_out = D.wait + slot * ACC_KW;
+    uint32_t* const off_out = D.wait_off + slot * (ACC_KH + 1);
+    uint32_t* const items_out = D.items + slot * ACC_KI;
+    if (has_lane(kept)) wait_out[count_below(kept)] = make_uint2(my_wait.x, (my_wait.y & REF_MASK) | (w_new << REF_BITS));
+    if (lane < newH) off_out[lane] = new_off;
+    if (lane == 0) off_out[newH] = n_kept;
+    if (has_lane(scanning)) items_out[count_below(scanning)] = (cur & REF_MASK) | (c_new << REF_BITS);
+    // The frontier's planes: of every item alone (root instance, or context depth 1), then under every entry of the item's origin
+    // that waits for its rule, an entry a lane.  (An entry that two items wait at is looked up in two rounds.)  Each plane once;
+    // where it is listed with and without its uncertain tokens, they count.
+    uint32_t nf = 0, f_lo = 0, f_hi = 0;
+    // the root instance: leaving the rule leaves the grammar, so its uncertain tokens are never allowed
+    if (c_origin == ROOT_ORIGIN && row != 0) row |= 1u;
+    unsigned long long todo = scanning & ~alone, found = alone;
+    for (;;) {
+        if (lanes_of(row == 0) & found) return ACC_NO_PLANE;
+        while (found) {
+            const uint32_t j = (uint32_t)__ffsll((long long)found) - 1, lo = lane_value((uint32_t)row, j), hi = lane_value((uint32_t)(row >> 32), j);
+            const unsigned long long same = lanes_of((((uint32_t)row ^ lo) & ~1u) == 0) & lanes_of((uint32_t)(row >> 32) == hi) & found;
+            const uint32_t counts = (lanes_of(((uint32_t)row & 1u) == 0) & same) ? ~1u : ~0u;
+            const unsigned long long listed = lanes_of(lane < nf) & lanes_of(((f_lo ^ lo) & ~1u) == 0) & lanes_of(f_hi == hi);
+            if (listed) { if (has_lane(listed)) f_lo &= counts; }
+            else {
+                if (nf >= ACC_KF) return ACC_OVERFLOW;
+                if (lane == nf) { f_lo = lo & counts; f_hi = hi; }
+                ++nf;
+            }
+            found &= ~same;
         }
-        const uint32_t rule = lane_value(rule_of, j);
-        const bool mine = lane < n_wait && my_set == o && my_wait.x == rule;
-        const unsigned long long hit = __ballot(mine);
-        if (!hit) return ACC_NO_PLANE;
-        if (n_pairs + (uint32_t)__popcll(hit) > 64) return ACC_RETRY;
-        if (mine) { const uint32_t at = n_pairs + (uint32_t)__popcll(hit & below); pair_sid[at] = v; pair_tgt[at] = my_wait.y; }
-        n_pairs += (uint32_t)__popcll(hit);
-    }
-    __syncthreads();
-    uint64_t row = 0;
-    const uint32_t* pair_off = uniform_load(&Cp->pair_off);
-    const uint64_t* pair_row = uniform_load(&Cp->pair_row);
-    const uint32_t* site_of_off = uniform_load(&Cp->site_of_off);
-    const uint2* site_of = uniform_load(&Cp->site_of);
-    if (lane < n_pairs) {
-        const uint32_t v = pair_sid[lane], t = pair_tgt[lane], sid = v & SID_MASK;
-        if (t == ALONE) {
-            row = tab(uniform_load(&Cp->plain_row) + sid);
-            // the root instance: leaving the rule leaves the grammar, so its uncertain tokens are never allowed
-            if (row && (v >> REF_BITS) == ROOT_ORIGIN) row |= 1u;
-        } else {
-            const uint32_t rule = tab(&T.state[sid].x), base = tab(pair_off + sid), end = tab(pair_off + sid + 1);
-            const uint32_t place = find_site(site_of_off, site_of, t & SID_MASK, rule);
-            if (place < end - base) row = tab(pair_row + base + place);
+        if (!todo) break;
+        uint32_t at = 0, end = 0;
+        do {
+            const uint32_t j = (uint32_t)__ffsll((long long)todo) - 1, o = lane_value(c_origin, j), of = lane_value(rule_of, j);
+            const uint32_t first = lane_value(my_off, o), n = (o + 1 < 64 ? lane_value(my_off, o + 1) : n_wait) - first;
+            const unsigned long long hit = lanes_of(my_wait.x == of) & (n < 64 ? lane_range(first, n) : ~0ull);
+            if (!hit) return ACC_NO_PLANE;
+            if (hit & found) break;
+            found |= hit;
+            if (has_lane(hit)) { at = lane_value(planes_at, j); end = lane_value(planes_end, j); }
+            todo &= todo - 1;
+        } while (todo);
+        row = 0;
+        if (has_lane(found)) {
+            const uint32_t place = find_in_row(C.site_of, sites_at, sites_end - sites_at, my_wait.x);
+            if (place < end - at) row = tab_at(C.pair_row, at + place);
         }
     }
-    if (__ballot(lane < n_pairs && row == 0)) return ACC_NO_PLANE;
-    // each plane once; where it is listed with and without its uncertain tokens, they count
-    uint32_t nf = 0;
-    uint64_t front = 0;
-    for (uint32_t p = 0; p < n_pairs; ++p) {
-        const uint64_t v = ((uint64_t)lane_value((uint32_t)(row >> 32), p) << 32) | lane_value((uint32_t)row, p);
-        const bool same = lane < nf && (front & ~(uint64_t)1) == (v & ~(uint64_t)1);
-        if (__ballot(same)) { if (same) front &= v | ~(uint64_t)1; continue; }
-        if (nf >= D.KF) return ACC_OVERFLOW;
-        if (lane == nf) front = v;
-        ++nf;
-    }
-    if (lane < nf) D.front[(size_t)b * D.KF + lane] = front;
+    if (lane < nf) D.front[(size_t)b * ACC_KF + lane] = ((uint64_t)f_hi << 32) | f_lo;
     out_n[0] = (uint32_t)__popcll(scanning); out_n[1] = newH; out_n[2] = nf; out_n[3] = A.root_done ? 1u : 0u;
     return ACC_OK;
 }
 
-__global__ __launch_bounds__(64) void k_accept(BatchDev D, DevVocab Vd, uint32_t eos_id, const int32_t* token_ids, int32_t* status) {
+__global__ __launch_bounds__(64) void k_accept(AcceptArgs A) {
     __shared__ uint32_t in_items[ACC_KI], in_wait_off[ACC_KH + 1], out_items[ACC_KI], out_wait_off[ACC_KH + 1];
     __shared__ uint2 in_wait[ACC_KW], out_wait[ACC_KW];
     __shared__ uint64_t out_front[ACC_KF], x_front[ACC_KF];
     __shared__ uint32_t lists[OneLaneStore::WORDS];
     __shared__ uint8_t x_map[ACC_KH + ACCEPT_MAXLEN + 4];
-    __shared__ uint32_t cls_words[64];
     __shared__ int sh_acc;
     __shared__ uint32_t sh_out[4];                                 // n_items, H, n_front, root_done
     const uint32_t lane = threadIdx.x, b = blockIdx.x;              // one wavefront per slot: everything below is the same in all lanes
-    const int32_t tok = (int32_t)same_in_all((uint32_t)token_ids[b]);
+    int32_t* status = A.status;
+    const TokenRecord* records = A.Vd.rec;
+    uint32_t V = A.Vd.V, eos_id = A.eos_id, B = A.D.B;
+    PIN("+s"(status), "+s"(records), "+s"(V), "+s"(eos_id), "+s"(B));
+    const int32_t tok = uniform_load(A.token_ids + b);
+    FillRow r = uniform_load(A.D.rows + b);                         // (no other workgroup writes this row)
+    PIN("+s"(r.pad[1]), "+s"(r.flags), "+s"(r.tables_idx));
     int32_t code = kAccOk;
-    FillRow r = D.rows[b];
-    r.item_off = same_in_all(r.item_off); r.item_n = same_in_all(r.item_n); r.wait_base = same_in_all(r.wait_base);
-    r.waitoff_off = same_in_all(r.waitoff_off); r.H = same_in_all(r.H); r.tables_idx = same_in_all(r.tables_idx);
-    r.flags = same_in_all(r.flags); r.pad[0] = same_in_all(r.pad[0]); r.pad[1] = same_in_all(r.pad[1]);
-    if (tok == kTokenReset) start_sequence(D, b, r.tables_idx, lane, 64);
+    if (tok == kTokenReset) start_sequence(A.D, b, r.tables_idx, lane, 64);
     else if (tok < 0) code = kAccOk;                                 // nothing for this slot
     else if (r.pad[1]) code = kAccOverflow;                          // unusable until reset
-    else if ((r.flags & 2u) || (uint32_t)tok >= Vd.V) code = kAccInvalid;
+    else if ((r.flags & 2u) || (uint32_t)tok >= V) code = kAccInvalid;
     else if ((uint32_t)tok == eos_id) {
         if (!(r.flags & 1u)) code = kAccRejected;
-        else if (lane == 0) D.rows[b].flags = r.flags | 2u;          // the sequence ends here
+        else if (lane == 0) A.D.rows[b].flags = r.flags | 2u;        // the sequence ends here
     } else {
-        const uint32_t rank = uniform_load(Vd.rank + tok);
-        if (rank >= Vd.n_sorted) code = kAccRejected;                // special and empty tokens are never allowed
+        // everything the parse starts from, asked for at once: the token, the grammar, and the first 64 of everything in the
+        // slot's context, without waiting for the counts (a slot has room for that many and more)
+        const CacheDev* const Cp = A.D.caches + r.tables_idx;
+        TokenRecord rec = uniform_load(records + tok);
+        CacheView C = cache_view(Cp);
+        uint32_t cls_word = tab(Cp->cls_words + lane);
+        uint32_t my_item = tab_at(A.D.items, r.item_off + lane), my_off = tab_at(A.D.wait_off, r.waitoff_off + lane);
+        uint2 my_wait = tab_at(A.D.wait, r.wait_base + lane);
+        PIN("+s"(rec.head.x), "+s"(rec.n_bytes), "+s"(C.T.trans), "+s"(C.T.state), "+s"(C.T.exp_list), "+s"(C.T.n_classes), "+s"(C.T.sink), "+s"(C.plain_row), "+s"(C.pair_off), "+s"(C.pair_row), "+s"(C.site_of_off), "+s"(C.site_of), "+v"(cls_word), "+v"(my_item), "+v"(my_off),
+            "+v"(my_wait.x), "+v"(my_wait.y));
+        const uint32_t nb = r.pad[0] ^ 1u;
+        const size_t slot = (size_t)nb * B + b;
+        if (rec.n_bytes == 0) code = kAccRejected;                   // special and empty tokens are never allowed
         else {
-            const uint32_t nb = r.pad[0] ^ 1u;
-            const CacheDev* const Cp = D.caches + r.tables_idx;
-            const size_t slot = (size_t)nb * D.B + b;
-            // the byte classes and the first 64 of everything in the slot's context, without waiting for the counts (a slot
-            // has room for that many and more)
-            const uint32_t my_item = D.items[r.item_off + lane], my_off = D.wait_off[r.waitoff_off + lane];
-            const uint2 my_wait = D.wait[r.wait_base + lane];
-            const uint32_t off = uniform_load(Vd.off + rank);
-            const int n = (int)(uniform_load(Vd.off + rank + 1) - off);
-            const uint4 tok16 = uniform_load(Vd.tok16 + rank);
-            cls_words[lane] = tab(uniform_load(&Cp->T.byte_class_words) + lane);
-            in_wait[lane] = my_wait;
-            in_wait_off[lane] = my_off;
-            __syncthreads();
             uint32_t got[4] = {0, 0, 0, 0};
             int acc = ACC_RETRY;
-            if (n <= 16 && r.H + (uint32_t)n <= 64)
-                acc = accept_wave(D, Cp, reinterpret_cast<const uint8_t*>(cls_words), b, r, slot, tok16, (uint32_t)n, my_item, in_wait, in_wait_off,
-                                  out_items, lists, lane, got);
-            bool copied = acc == ACC_OK;
+            if (rec.n_bytes <= 16)
+                acc = accept_wave(A.D, C, b, slot, rec.head, rec.n_bytes, r.H, r.item_n, my_item, my_wait, my_off, cls_word, lane, got);
             if (acc == ACC_RETRY) {
                 // lane 0, with the slot's whole context in LDS
+                const AcceptArgs Z = args_again<AcceptArgs>();
+                const BatchDev& D = Z.D;
+                const FillRow q = uniform_load(D.rows + b);
+                const TokenRecord t = uniform_load(Z.Vd.rec + uniform_load(Z.token_ids + b));
+                const int n = (int)t.n_bytes;
+                const CacheDev* const C0 = D.caches + q.tables_idx;
                 __syncthreads();
-                for (uint32_t k = lane; k < r.item_n; k += 64) in_items[k] = D.items[r.item_off + k];
-                for (uint32_t k = lane; k <= r.H; k += 64) in_wait_off[k] = D.wait_off[r.waitoff_off + k];
-                const uint32_t n_wait_in = D.wait_off[r.waitoff_off + r.H];
-                for (uint32_t k = lane; k < n_wait_in; k += 64) in_wait[k] = D.wait[r.wait_base + k];
+                for (uint32_t k = lane; k < q.item_n; k += 64) in_items[k] = D.items[q.item_off + k];
+                for (uint32_t k = lane; k <= q.H; k += 64) in_wait_off[k] = D.wait_off[q.waitoff_off + k];
+                const uint32_t n_wait_in = D.wait_off[q.waitoff_off + q.H];
+                for (uint32_t k = lane; k < n_wait_in; k += 64) in_wait[k] = D.wait[q.wait_base + k];
                 __syncthreads();
                 if (lane == 0) {
-                    const CacheDev Cd = *Cp;
-                    MatcherIn in{in_items, r.item_n, in_wait, in_wait_off, r.H};
+                    const CacheDev& Cd = *C0;
+                    MatcherIn in{in_items, q.item_n, in_wait, in_wait_off, q.H};
                     MatcherOut out{out_items, out_wait, out_wait_off, out_front, ACC_KI, ACC_KH, ACC_KW, ACC_KF, 0, 0, 0, 0};
                     OneLaneStore st;
                     st.init(lists);
                     OneLaneScratchX<ACC_KH + ACCEPT_MAXLEN, ACC_KF> x{x_map, x_front};
-                    int a = accept_token(Cd, cls_words, in, Vd.bytes + off, n, st, x, out);
+                    int a = accept_token(Cd, Cd.cls_words, in, Z.Vd.bytes + t.off, n, st, x, out);
                     if (a == ACC_RETRY) {
                         // lists in device memory, results straight to the slot's other buffer
-                        MatcherIn gin{D.items + r.item_off, r.item_n, D.wait + r.wait_base, D.wait_off + r.waitoff_off, r.H};
+                        MatcherIn gin{D.items + q.item_off, q.item_n, D.wait + q.wait_base, D.wait_off + q.waitoff_off, q.H};
                         MatcherOut gout{D.items + slot * D.KI, D.wait + slot * D.KW, D.wait_off + slot * (D.KH + 1), D.front + (size_t)b * D.KF,
                                         D.KI, D.KH, D.KW, D.KF, 0, 0, 0, 0};
                         GlobalStore gs;
                         gs.init(D.slow_mem + b, D.B);
                         GlobalScratchX gx{D.slow_map + b, D.slow_front + b, D.B, D.KH + kSlowMaxLen + 1, D.KF};
-                        a = accept_token(Cd, cls_words, gin, Vd.bytes + off, n, gs, gx, gout);
+                        a = accept_token(Cd, Cd.cls_words, gin, Z.Vd.bytes + t.off, n, gs, gx, gout);
                         out.n_items = gout.n_items; out.H = gout.H; out.n_front = gout.n_front; out.root_done = gout.root_done;
                         if (a == ACC_OK) a = -1;                     // done, nothing to copy out
                     }
@@ -1548,29 +1647,26 @@ __global__ __launch_bounds__(64) void k_accept(BatchDev D, DevVocab Vd, uint32_t
                 }
                 __syncthreads();
                 acc = sh_acc;
-                copied = acc == -1;
-                if (copied) acc = ACC_OK;
                 for (int k = 0; k < 4; ++k) got[k] = sh_out[k];
+                if (acc == ACC_OK) {
+                    for (uint32_t k = lane; k < got[0]; k += 64) D.items[slot * D.KI + k] = out_items[k];
+                    for (uint32_t k = lane; k <= got[1]; k += 64) D.wait_off[slot * (D.KH + 1) + k] = out_wait_off[k];
+                    const uint32_t n_wait = out_wait_off[got[1]];
+                    for (uint32_t k = lane; k < n_wait; k += 64) D.wait[slot * D.KW + k] = out_wait[k];
+                    for (uint32_t k = lane; k < got[2]; k += 64) D.front[(size_t)b * D.KF + k] = out_front[k];
+                } else if (acc == -1) acc = ACC_OK;
             }
             if (acc == ACC_OK) {
-                const uint32_t n_items = got[0], H = got[1], n_front = got[2];
-                if (!copied) {
-                    for (uint32_t k = lane; k < n_items; k += 64) D.items[slot * D.KI + k] = out_items[k];
-                    for (uint32_t k = lane; k <= H; k += 64) D.wait_off[slot * (D.KH + 1) + k] = out_wait_off[k];
-                    const uint32_t n_wait = out_wait_off[H];
-                    for (uint32_t k = lane; k < n_wait; k += 64) D.wait[slot * D.KW + k] = out_wait[k];
-                    for (uint32_t k = lane; k < n_front; k += 64) D.front[(size_t)b * D.KF + k] = out_front[k];
-                }
                 if (lane == 0) {
-                    r.front_n = n_front;
-                    r.item_off = (uint32_t)(slot * D.KI); r.item_n = n_items;
-                    r.wait_base = (uint32_t)(slot * D.KW); r.waitoff_off = (uint32_t)(slot * (D.KH + 1)); r.H = H;
-                    r.flags = got[3];
-                    r.pad[0] = nb;
-                    D.rows[b] = r;
+                    FillRow w{};
+                    w.front_off = b * ACC_KF; w.front_n = got[2];
+                    w.item_off = (uint32_t)(slot * ACC_KI); w.item_n = got[0];
+                    w.wait_base = (uint32_t)(slot * ACC_KW); w.waitoff_off = (uint32_t)(slot * (ACC_KH + 1)); w.H = got[1];
+                    w.tables_idx = r.tables_idx; w.flags = got[3]; w.pad[0] = nb;
+                    A.D.rows[b] = w;
                 }
             } else if (acc == ACC_REJECTED) code = kAccRejected;
-            else { if (lane == 0) D.rows[b].pad[1] = 1u; code = kAccOverflow; }   // a capacity of the slot (or of the device-memory lists) was exceeded
+            else { if (lane == 0) A.D.rows[b].pad[1] = 1u; code = kAccOverflow; }   // a capacity of the slot (or of the device-memory lists) was exceeded
         }
     }
     if (status && lane == 0) status[b] = code;
@@ -1740,7 +1836,11 @@ void launch_build_slow(const DevTables& T, const DevVocab& Vd, const BuildPlan& 
 
 void launch_accept(const BatchDev& D, const DevVocab& Vd, uint32_t eos_id, const int32_t* token_ids_dev, int32_t* status_dev, hipStream_t stream) {
     if (!D.B || D.KI != ACC_KI || D.KH != ACC_KH || D.KW != ACC_KW || D.KF != ACC_KF) return;
-    hipLaunchKernelGGL(k_accept, dim3(D.B), dim3(64), 0, stream, D, Vd, eos_id, token_ids_dev, status_dev);
+    hipLaunchKernelGGL(k_accept, dim3(D.B), dim3(64), 0, stream, AcceptArgs{D, Vd, eos_id, token_ids_dev, status_dev});
+}
+
+void launch_token_records(const DevVocab& Vd, TokenRecord* rec_dev, hipStream_t stream) {
+    if (Vd.V) hipLaunchKernelGGL(k_token_records, dim3((Vd.V + 255) / 256), dim3(256), 0, stream, Vd, rec_dev);
 }
 
 void launch_batch_assign(const BatchDev& D, const int32_t* rows_dev, uint32_t n, uint32_t cache_idx, hipStream_t stream) {
