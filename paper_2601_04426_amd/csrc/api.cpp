@@ -660,17 +660,18 @@ struct MatcherImpl {
 // frontier, whether some context is too large to parse from in a row's workgroup, and whether many of a row's uncertain tokens
 // may be longer than a lane takes: the vocabulary has such tokens, and no follow language inside a parent filters them.
 struct FillLoad { uint32_t plane_tokens = 0, row_tokens = 0; bool deep = false, long_tokens = false; };
-// How many lanes of the large-capacity scratch each row of a fill gets for itself (its workgroup has six wavefronts), and whether
-// k_recheck_slow is launched behind k_fill.  That costs every call 2.5 - 4 us, so it is done only where there are too few lanes,
-// where a row goes word by word or its context is too large, or where the batch is small enough that a row's many long tokens
-// are better spread over the device (k_fill has the figures).
+// How many wavefronts a row's workgroup has, how many lanes of the large-capacity scratch each row of a fill gets for itself (a
+// workgroup has six wavefronts at least), and whether k_recheck_slow is launched behind k_fill.  That costs every call 2.5 - 4 us, so
+// it is done only where there are too few lanes, where a row goes word by word or its context is too large, or where the batch is small
+// enough that a row's many long tokens are better spread over the device (k_fill has the figures).
 inline void share_out(FillBatch& F, uint32_t n_lanes, const FillLoad& load) {
     const uint32_t per = n_lanes / F.B;
     const bool spread = F.B <= kFillSpreadRows && load.long_tokens;
     F.own_lanes = per < 2 ? 0u : std::min<uint32_t>(per, 6);
     F.follows = F.own_lanes == 0 || load.deep || load.plane_tokens > kFillPlaneTokens || load.row_tokens > kFillRowTokens
                 || (spread && std::max(load.plane_tokens, load.row_tokens) > kFillSpreadTokens);
-    F.wave_tokens = spread ? kFillSpreadTokens : kFillWaveTokens;
+    F.row_waves = fill_row_waves(F.B, std::max(load.plane_tokens, load.row_tokens));
+    F.wave_tokens = spread ? kFillSpreadTokens : kFillWaveTokens * F.row_waves;
     F.leave_above = spread && F.follows ? kFillSpreadTokens : 0xFFFFFFFFu;
 }
 
@@ -703,14 +704,14 @@ struct FillWorkspace {
     }
     void ensure_scratch(size_t words, size_t rows) {
         if (row_count.n < rows) row_count.alloc(rows * 2);
-        const size_t n = kStampsRows + kStampsPerRow * rows + kSlowLanes / 64;
+        const size_t n = kStampsRows + (kFillMostWaves + 1) * rows + kSlowLanes / 64;
         if (stamps.n < n) stamps.alloc(n * 2);
         if (cand_words.n < words) { cand_words.alloc(words * 5 / 4); work_list.alloc(words * 5 / 4); }
     }
     // the latest fill is F, preceded by an upload kernel or not
     void stamped(const FillBatch& F, const SlowScratch& S, bool uploaded) {
         stamps_from = uploaded ? 0 : kStampsRows;
-        n_stamps = kStampsRows + kStampsPerRow * F.B + (F.follows ? S.n_lanes / 64 : 0);
+        n_stamps = kStampsRows + (F.row_waves + 1) * F.B + (F.follows ? S.n_lanes / 64 : 0);
     }
     // microseconds from the first of them to the last
     float stamped_us() {

@@ -156,20 +156,25 @@ struct FillBatch {
     uint32_t own_lanes;                  // lanes of the large-capacity scratch that are a row's own while k_fill runs, or 0: there are too few
     uint32_t follows;                    // k_recheck_slow is launched behind it and takes what the rows leave on the overflow list (always
                                          // if own_lanes is 0)
+    uint32_t row_waves;                  // wavefronts of a row's workgroup: fill_row_waves()
     uint32_t wave_tokens;                // up to that many candidates of a row get a wavefront each
     uint32_t leave_above;                // a row with more tokens than that beyond a lane's lists leaves them to k_recheck_slow
     uint64_t* stamps;                    // if not null: when the call's work started and ended, on the device's constant-rate clock:
-                                         // [0] the upload kernel's start; kStampsPerRow words for each row (start, end of each of
+                                         // [0] the upload kernel's start; row_waves + 1 words for each row (start, end of each of
                                          // its wavefronts); the end of each workgroup of k_recheck_slow
 };
 // What k_fill handles how (the host decides by the same numbers whether k_recheck_slow follows).
 constexpr uint32_t kFillLaneItems = 8, kFillLaneWaits = 12, kFillLaneBytes = 16;    // lists and bytes of a lane that parses a token by itself
-constexpr uint32_t kFillWaveTokens = 24;                     // FillBatch::wave_tokens, as a rule
+constexpr uint32_t kFillWaveTokens = 4;                      // FillBatch::wave_tokens for each wavefront of the workgroup, as a rule
+// Wavefronts of a row's workgroup, in a batch of `rows` rows that have up to `tokens` uncertain tokens (k_fill has the figures).
+constexpr uint32_t kFillMostWaves = 16;
+constexpr uint32_t kComputeUnits = 256;
+constexpr uint32_t fill_row_waves(uint32_t rows, uint32_t tokens) { return rows <= kComputeUnits ? 16 : tokens > 2 ? 12 : 6; }
 constexpr uint32_t kFillSpreadRows = 192, kFillSpreadTokens = 18;    // batches of up to that many rows, where tokens may be long in numbers: wave_tokens, leave_above
 constexpr uint32_t kFillPlaneTokens = kUncListWords - 1;     // with more uncertain tokens in a frontier plane (than its list holds), or in a
 constexpr uint32_t kFillRowTokens = 2048;                    //   frontier (than any slot's can have otherwise), a row is worked through word by word
 constexpr uint32_t kFillContextItems = 64, kFillContextSets = 240, kFillContextWaits = 512;   // contexts that wavefronts parse from (every slot's)
-constexpr uint32_t kStampsRows = 1, kStampsPerRow = 7;
+constexpr uint32_t kStampsRows = 1;
 void launch_fill(const FillBatch& F, const DevVocab& Vd, int32_t* bitmask_dev, int64_t row_stride_words,
                  const SlowScratch& S, hipStream_t stream, hipEvent_t done = nullptr);
 void launch_recheck_slow(const FillBatch& F, const DevVocab& Vd, int32_t* bitmask_dev, int64_t row_stride_words,

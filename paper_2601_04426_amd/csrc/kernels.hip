@@ -737,6 +737,25 @@ __device__ __forceinline__ P uniform_load(const P* p) {
     return *p;
 #endif
 }
+// Values that are wanted here: loads whose results are named are asked for before this point, all together, and not one after the
+// other where the compiler would rather have them (behind the branch on an earlier one).
+#if defined(__HIP_DEVICE_COMPILE__)
+#define PIN(...) asm volatile("" : __VA_ARGS__)
+#else
+#define PIN(...) (void)0
+#endif
+// What a kernel was launched with, read anew from the launch's own memory (A: all its arguments, as one struct): what only a way
+// that is rarely taken needs must not take up registers on the way that nearly every row or token goes.
+template <class A>
+__device__ __forceinline__ A args_again() {
+#if defined(__HIP_DEVICE_COMPILE__)
+    auto p = (const __attribute__((address_space(4))) A*)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    return *p;
+#else
+    return A{};
+#endif
+}
 // The lanes in which x holds: one compare.  (Of two conditions joined by && the compiler makes three vector instructions more than of
 // two sets of lanes joined by &.)
 __device__ __forceinline__ unsigned long long lanes_of(bool x) { return __builtin_amdgcn_ballot_w64(x); }
@@ -888,9 +907,17 @@ struct WaveScan {
 // Most rows have no candidate and a few have a handful, but the launch lasts as long as its slowest row.  A row with few
 // candidates (wave_tokens) gives each a wavefront (WaveScan: a byte costs about one gather, where a lane of its own
 // takes several dependent accesses), the union team joining in when it is done; a row with more gives each a lane.
-// Wavefronts take six at a time, lanes any number up to 64 in one round.  Which is less depends on the grammar: by wavefronts /
-// by lanes from 19 on, two fills and a step, 37 rows of a JSON schema 27 / 32 us, 64 rows of records 72 / 67; 24 candidates deep in
-// nested parentheses, 1 row, 49 / 39, and of 20 - 40 bytes 129 / 95.
+// Wavefronts take as many at a time as the row has, lanes any number in one round.  Which is less depends on the grammar: six
+// wavefronts / lanes from 19 on, two fills and a step, 37 rows of a JSON schema 27 / 32 us, 64 rows of records 72 / 67; 24 candidates
+// deep in nested parentheses, 1 row, 49 / 39, and of 20 - 40 bytes 129 / 95.
+// How many wavefronts a row's workgroup has (fill_row_waves): six where the device is full of rows anyway and no plane has more
+// than two uncertain tokens.  A compute unit that has one row has room for sixteen; where rows have candidates, twelve also pay with
+// more rows than compute units.  Six / twelve / sixteen, us, rows with up to 47 candidates: 64 rows of records 23.8 / 17.1 / 15.8,
+// 256 rows of tools 20.9 / 16.5 / 15.0; 512 rows of tools 20.7 / 18.9 / 18.7, of records 26.0 / 23.5 / 24.8; 1,024 rows of tools
+// 23.5 / 22.5 / 26.4, of records 30.4 / 30.4 / 36.8.  No candidates: 1 row 4.3 with any, 512 rows of JSON 5.7 / 5.9 / 8.0, 1,024 rows
+// 8.4 / 9.4 / 14.
+// Everything that is asked for before the plan is known (the context, the tables, the first planes' lists, the first block of the
+// union) used to wait for it: 0.5 - 1.5 us of every row.
 // A row with a frontier plane whose uncertain tokens do not fit its list (or with more candidates than the LDS list
 // holds) takes the sequential way: the union team also reads the uncertain rows and lists the words with candidates,
 // the re-check team starts when the union is done, a lane each.
@@ -903,21 +930,23 @@ struct WaveScan {
 // kFillSpreadRows.  Short tokens whose item sets outgrow a lane are the wavefronts' in any batch (expansions of 25 items, 33
 // tokens a row, 1 row: 64 / 128).  The sequential way, which has no bound on its tokens, leaves all of them to that launch (100
 // long ones a row, 1 row: 112 us; one lane of the workgroup after another took 5,433).
-// Four wavefronts stream, two re-check with half of their lanes at work (measured: fewer lanes per wavefront, more
-// wavefronts or another split of the six gain nothing; a larger workgroup lowers the number of rows a compute unit holds).
-constexpr int FILL_OR_WAVES = 4, FILL_RECHECK_WAVES = 2;
-constexpr int FILL_RECHECK_LANES = 32;                               // lanes at work in a wavefront of the re-check team
-constexpr int FILL_COLS = FILL_RECHECK_WAVES * FILL_RECHECK_LANES;  // tokens the team parses at a time
-constexpr int FILL_OR_THREADS = 64 * FILL_OR_WAVES;
-constexpr int FILL_THREADS = 64 * (FILL_OR_WAVES + FILL_RECHECK_WAVES);
-constexpr int FILL_BLOCK = 5;                          // steps of the union whose loads are issued together
+// Four wavefronts stream, the others re-check: two with half of their lanes at work (measured: fewer lanes per wavefront or another
+// split of the six gain nothing), more with a quarter.
+constexpr int FILL_OR_WAVES = 4, FILL_OR_THREADS = 64 * FILL_OR_WAVES;
+template <int WAVES> struct FillTeam {
+    static constexpr int THREADS = 64 * WAVES;
+    static constexpr int BLOCK = WAVES == 16 ? 5 : 4;                // vectors of the union a thread asks for together
+    static constexpr int LANES = WAVES == 6 ? 32 : 16;               // lanes at work in a wavefront of the re-check team
+    static constexpr int COLS = (WAVES - FILL_OR_WAVES) * LANES;     // tokens the team parses at a time
+    using Store = LdsStore<kFillLaneItems, kFillLaneWaits, COLS>;
+};
+constexpr uint32_t FILL_LISTS = 2;                     // planes whose lists are asked for before their lengths are known
 constexpr int FILL_K = kFillLaneItems, FILL_WM = kFillLaneWaits;
 constexpr uint32_t FILL_SPARSE_CAP = kFillRowTokens;   // candidates of a row that the side-by-side way handles
 // What became of a candidate: the token, or FILL_NONE if it was rejected; FILL_OVER: it did not fit the lists tried so far;
 // FILL_LARGE: it did not fit a lane's, and a wavefront has decided it.
 constexpr uint32_t FILL_OVER = 0x80000000u, FILL_LARGE = 0x40000000u, FILL_NONE = 0x3FFFFFFFu;
 constexpr uint32_t FILL_CTX_WAITS = kFillContextWaits, FILL_CTX_SETS = kFillContextSets, FILL_OWN_WAITS = 128, FILL_WAVE_BYTES = 64;   // what a wavefront's parse has room for
-using FillStore = LdsStore<FILL_K, FILL_WM, FILL_COLS>;
 
 __device__ __forceinline__ DevCtx row_ctx(const FillBatch& F, const FillRow& r) {
     DevCtx C;
@@ -949,7 +978,8 @@ __device__ __forceinline__ void list_candidates(const FillBatch& F, uint32_t* n_
 
 constexpr int RECHECK_NO = 0, RECHECK_YES = 1, RECHECK_OVER = 2;
 // One candidate token, one lane, against the row's full context.
-__device__ __forceinline__ int recheck_lane(const DevVocab& Vd, const DevTables& T, const uint32_t* cls_words, const DevCtx& C, uint32_t id, FillStore& st) {
+template <class Store>
+__device__ __forceinline__ int recheck_lane(const DevVocab& Vd, const DevTables& T, const uint32_t* cls_words, const DevCtx& C, uint32_t id, Store& st) {
     const TokenRecord rec = tab(Vd.rec + id);
     if (rec.n_bytes == 0) return RECHECK_NO;
     RegBytes tok;
@@ -961,6 +991,8 @@ __device__ __forceinline__ int recheck_lane(const DevVocab& Vd, const DevTables&
 
 // A row's context in LDS for the wavefronts that parse from it, and each wavefront's room for what its token adds.
 struct FillCtx { uint2 wait[FILL_CTX_WAITS]; uint32_t off[FILL_CTX_SETS + 1]; uint32_t cls_words[64]; };
+struct WaveToken { uint32_t words[4], id, off, n_bytes; };           // a token that a wavefront parses: its first 16 bytes, ...
+constexpr uint32_t FILL_WAVE_MOST = 64;
 struct FillOwn { uint2 wait[FILL_OWN_WAITS]; uint32_t off[FILL_WAVE_BYTES + 1]; };
 __device__ __forceinline__ void wave_sync() {                       // orders a wavefront's LDS traffic (which completes in order) for the compiler
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -969,15 +1001,11 @@ __device__ __forceinline__ void wave_sync() {                       // orders a 
 // One candidate token (the same in all lanes), one wavefront.  *large: it would not have fitted the short lists of a lane,
 // whatever became of it (so that the count does not depend on the way a row takes).
 __device__ __forceinline__ int recheck_wave(const DevVocab& Vd, const SlowScratch& S, const DevTables& T, const FillCtx& X, FillOwn& own, uint32_t H, uint32_t item_n, uint32_t my_item,
-                                            uint32_t id, uint32_t lane, bool* large) {
-    const TokenRecord rec = uniform_load(Vd.rec + id);
-    const uint32_t at = rec.off, n_bytes = rec.n_bytes;
-    const uint4 tok16 = rec.head;
+                                            uint32_t tok_word, uint32_t at, uint32_t n_bytes, uint32_t lane, bool* large) {
     if (n_bytes == 0) return RECHECK_NO;
     if (n_bytes > FILL_WAVE_BYTES) return RECHECK_OVER;
     *large |= n_bytes > 16 || item_n > (uint32_t)FILL_K;
-    const uint32_t words[4] = {tok16.x, tok16.y, tok16.z, tok16.w};
-    uint32_t byte = (words[(lane >> 2) & 3] >> (8 * (lane & 3))) & 0xFF;
+    uint32_t byte = ((uint32_t)__shfl((int)tok_word, (int)(lane >> 2) & 3) >> (8 * (lane & 3))) & 0xFF;
     if (n_bytes > 16) byte = lane < n_bytes ? tab(Vd.bytes + at + lane) : 0u;
     const uint32_t cls_of = reinterpret_cast<const uint8_t*>(X.cls_words)[byte];
     const uint32_t max_items = S.k_cap < WaveScan<false>::N ? S.k_cap : WaveScan<false>::N, max_waits = S.wm_cap < FILL_OWN_WAITS ? S.wm_cap : FILL_OWN_WAITS;
@@ -1065,41 +1093,77 @@ __device__ __forceinline__ void store4(uint32_t* row, uint32_t w, uint32_t W, co
     }
 }
 
-// The union of a row: BLOCK steps at a time, first every load of the block (plane after plane, so that a thread has several
-// independent loads in flight), then the stores.  UNC: also the uncertain rows, whose tokens that no plane accepts are listed.
-template <int BLOCK, bool UNC>
-__device__ __forceinline__ void fill_union(const FillBatch& F, uint32_t W, uint32_t b, uint32_t front_off, uint32_t front_n, bool live, bool eos, uint32_t* out, uint32_t* n_listed, uint32_t* n_cand) {
-    const uint32_t eos_word = F.eos_id >> 5, eos_bit = 1u << (F.eos_id & 31);
-    const uint32_t n_vec = (W + 3) / 4, n_steps = (n_vec + FILL_OR_THREADS - 1) / FILL_OR_THREADS;      // same for every thread: the ballots see whole waves
-    for (uint32_t step0 = 0; step0 < n_steps; step0 += BLOCK) {
-        uint32_t acc[BLOCK][4] = {}, unc[UNC ? BLOCK : 1][4] = {};
-        if (live)
-            for (uint32_t k = 0; k < front_n; ++k) {
-                const uint64_t pa = uniform_load(F.front_planes + front_off + k);
-                const uint32_t* row = reinterpret_cast<const uint32_t*>(pa & ~(uint64_t)1);
+// One block of a row's union: BLOCK vectors of four words a thread, FILL_OR_THREADS apart, from v0 (of thread 0) on.  What lies
+// beyond the row holds other bits of the plane: nobody may look at it.
+template <int BLOCK>
+__device__ __forceinline__ void union_load(const uint32_t* row, uint32_t n_vec, uint32_t v0, uint32_t (&x)[BLOCK][4]) {
 #pragma unroll
-                for (int s = 0; s < BLOCK; ++s) {
-                    const uint32_t v = (step0 + s) * FILL_OR_THREADS + threadIdx.x;
-                    if (v >= n_vec) continue;
-                    uint32_t x[4];
-                    load4(row, 4 * v, W, x);
-                    _Pragma("unroll") for (int c = 0; c < 4; ++c) acc[s][c] |= x[c];
-                    if (UNC && !(pa & 1)) {
-                        load4(row + W, 4 * v, W, x);
-                        _Pragma("unroll") for (int c = 0; c < 4; ++c) unc[s][c] |= x[c];
-                    }
-                }
-            }
+    for (int s = 0; s < BLOCK; ++s) {
+        if (v0 + s * FILL_OR_THREADS >= n_vec) break;               // the same for every thread
+        const uint32_t v = v0 + s * FILL_OR_THREADS + threadIdx.x;
+        const Words4 y = *(const __attribute__((address_space(1))) Words4*)((const __attribute__((address_space(1))) char*)row + 16 * (v < n_vec ? v : n_vec - 1));
+        x[s][0] = y.x; x[s][1] = y.y; x[s][2] = y.z; x[s][3] = y.w;
+    }
+}
+template <int BLOCK>
+__device__ __forceinline__ void union_add(uint32_t (&acc)[BLOCK][4], const uint32_t (&x)[BLOCK][4]) {
+    _Pragma("unroll") for (int s = 0; s < BLOCK; ++s)
+        _Pragma("unroll") for (int c = 0; c < 4; ++c) acc[s][c] |= x[s][c];
+}
+__device__ __forceinline__ uint64_t lane_address(uint64_t a, uint32_t k) { return ((uint64_t)lane_value((uint32_t)(a >> 32), k) << 32) | lane_value((uint32_t)a, k); }
+__device__ __forceinline__ const uint32_t* plane_row(uint64_t a) { return reinterpret_cast<const uint32_t*>(a & ~(uint64_t)1); }
+// Whole blocks: all loads of a block and a plane are issued before the first is used.  Lane k holds the address of frontier plane k.
+// The first block of the first plane has been asked for already (acc), as soon as its address was known, so that it is on its way
+// while the rest of the row's plan is worked out.
+template <int BLOCK>
+__device__ __forceinline__ void fill_union(const FillBatch& F, uint32_t W, uint64_t addr, uint32_t front_n, bool eos, uint32_t* out, uint32_t (&acc)[BLOCK][4]) {
+    const uint32_t eos_word = F.eos_id >> 5, eos_bit = 1u << (F.eos_id & 31), n_vec = (W + 3) / 4;
+    uint32_t k = 1;
+    for (uint32_t v0 = 0; v0 < n_vec; v0 += BLOCK * FILL_OR_THREADS) {
+        for (; k < front_n; ++k) {
+            uint32_t x[BLOCK][4] = {};
+            union_load(plane_row(lane_address(addr, k)), n_vec, v0, x);
+            union_add(acc, x);
+        }
+        k = 0;
 #pragma unroll
         for (int s = 0; s < BLOCK; ++s) {
-            if (step0 + s >= n_steps) break;                        // same for every thread
-            const uint32_t v = (step0 + s) * FILL_OR_THREADS + threadIdx.x;
-            if (UNC) {
-                uint32_t cand[4], any = 0;
-                _Pragma("unroll") for (int c = 0; c < 4; ++c) { cand[c] = v < n_vec ? (unc[s][c] & ~acc[s][c]) : 0u; any |= cand[c]; }
-                if (__any(any != 0))                                // candidates are few: most wavefronts have none
-                    _Pragma("unroll") for (int c = 0; c < 4; ++c) list_candidates(F, n_listed, n_cand, cand[c], b * W, v * 4 + c);
+            const uint32_t v = v0 + s * FILL_OR_THREADS + threadIdx.x;
+            if (eos && eos_word / 4 == v) {
+                _Pragma("unroll") for (int c = 0; c < 4; ++c) if (eos_word % 4 == (uint32_t)c) acc[s][c] |= eos_bit;
             }
+            if (v < n_vec) store4(out, 4 * v, W, acc[s]);
+            _Pragma("unroll") for (int c = 0; c < 4; ++c) acc[s][c] = 0;
+        }
+    }
+}
+// The same for a frontier of any length, with the uncertain rows: the tokens of theirs that no plane accepts are listed.
+template <int BLOCK>
+__device__ __forceinline__ void fill_union_listing(const FillBatch& F, uint32_t W, uint32_t b, uint32_t front_off, uint32_t front_n, bool eos, uint32_t* out, uint32_t* n_listed, uint32_t* n_cand) {
+    const uint32_t eos_word = F.eos_id >> 5, eos_bit = 1u << (F.eos_id & 31), n_vec = (W + 3) / 4;
+    for (uint32_t v0 = threadIdx.x; v0 - threadIdx.x < n_vec; v0 += BLOCK * FILL_OR_THREADS) {       // same rounds for every thread: the ballots see whole waves
+        uint32_t acc[BLOCK][4] = {}, unc[BLOCK][4] = {};
+        for (uint32_t k = 0; k < front_n; ++k) {
+            const uint64_t pa = uniform_load(F.front_planes + front_off + k);
+#pragma unroll
+            for (int s = 0; s < BLOCK; ++s) {
+                const uint32_t v = v0 + s * FILL_OR_THREADS;
+                if (v >= n_vec) continue;
+                uint32_t x[4];
+                load4(plane_row(pa), 4 * v, W, x);
+                _Pragma("unroll") for (int c = 0; c < 4; ++c) acc[s][c] |= x[c];
+                if (pa & 1) continue;
+                load4(plane_row(pa) + W, 4 * v, W, x);
+                _Pragma("unroll") for (int c = 0; c < 4; ++c) unc[s][c] |= x[c];
+            }
+        }
+#pragma unroll
+        for (int s = 0; s < BLOCK; ++s) {
+            const uint32_t v = v0 + s * FILL_OR_THREADS;
+            uint32_t cand[4], any = 0;
+            _Pragma("unroll") for (int c = 0; c < 4; ++c) { cand[c] = v < n_vec ? (unc[s][c] & ~acc[s][c]) : 0u; any |= cand[c]; }
+            if (__any(any != 0))                                    // candidates are few: most wavefronts have none
+                _Pragma("unroll") for (int c = 0; c < 4; ++c) list_candidates(F, n_listed, n_cand, cand[c], b * W, v * 4 + c);
             if (eos && eos_word / 4 == v) {
                 _Pragma("unroll") for (int c = 0; c < 4; ++c) if (eos_word % 4 == (uint32_t)c) acc[s][c] |= eos_bit;
             }
@@ -1108,16 +1172,23 @@ __device__ __forceinline__ void fill_union(const FillBatch& F, uint32_t W, uint3
     }
 }
 
-// Six wavefronts a SIMD at least: a compute unit then holds four rows, i.e. the device 1,024 at once.
-__global__ __launch_bounds__(FILL_THREADS) __attribute__((amdgpu_waves_per_eu(6))) void k_fill(FillBatch F, DevVocab Vd, int32_t* bitmask, long long row_stride, SlowScratch S) {
-    __shared__ uint32_t lds_store[FillStore::SLOTS * FILL_COLS];
+// Six wavefronts a SIMD at least: a compute unit then holds four rows of six wavefronts, i.e. the device 1,024 at once.
+struct FillArgs { FillBatch F; DevVocab Vd; int32_t* bitmask; long long row_stride; SlowScratch S; };
+template <int WAVES>
+__global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVES == 16 ? 4 : 6))) void k_fill(FillArgs A) {
+    const FillBatch& F = A.F;
+    const DevVocab& Vd = A.Vd;
+    using Team = FillTeam<WAVES>;
+    constexpr uint32_t THREADS = Team::THREADS, LANES = Team::LANES, COLS = Team::COLS;
+    __shared__ uint32_t lds_store[Team::Store::SLOTS * COLS];
     __shared__ uint32_t sh_surv[FILL_SPARSE_CAP];
     __shared__ FillCtx ctx;
-    __shared__ FillOwn sh_own[FILL_THREADS / 64];
-    __shared__ uint32_t n_listed, n_cand, n_over, next_token;
+    __shared__ FillOwn sh_own[WAVES];
+    __shared__ uint32_t n_listed, n_cand, n_over, next_token, n_to_parse;
+    __shared__ WaveToken sh_tok[FILL_WAVE_MOST];
     const uint32_t b = blockIdx.x, lane = threadIdx.x & 63, wave = same_in_all(threadIdx.x >> 6);
-    if (F.stamps && threadIdx.x == 0) F.stamps[kStampsRows + kStampsPerRow * b] = wall_clock64();
-    auto stamp_end = [&]() { if (F.stamps && lane == 0) F.stamps[kStampsRows + kStampsPerRow * b + 1 + wave] = wall_clock64(); };
+    if (F.stamps && threadIdx.x == 0) F.stamps[kStampsRows + (WAVES + 1) * b] = wall_clock64();
+    auto stamp_end = [&]() { if (F.stamps && lane == 0) F.stamps[kStampsRows + (WAVES + 1) * b + 1 + wave] = wall_clock64(); };
     const FillRow r = uniform_load(F.rows + b);
     const uint32_t front_off = r.front_off, front_n = r.front_n, flags = r.flags;
     const bool live = !(flags & 2u);
@@ -1126,9 +1197,30 @@ __global__ __launch_bounds__(FILL_THREADS) __attribute__((amdgpu_waves_per_eu(6)
     // the plan, worked out by every wavefront for itself: lane k looks at frontier plane k
     uint64_t addr = 1;
     uint32_t n_unc = 0;
-    if (live && front_n <= 64 && lane < front_n) {
-        addr = F.front_planes[front_off + lane];
-        if (!(addr & 1)) n_unc = tab(reinterpret_cast<const uint32_t*>(addr) + 3 * (size_t)Vd.W);
+    if (live && front_n <= 64 && lane < front_n) addr = F.front_planes[front_off + lane];
+    // What a parse starts from does not hang on the frontier, and is asked for together with it: the grammar's tables, the context.
+    static_assert(kFillContextItems <= WaveScan<false>::N, "a context's items lie across the lanes");
+    DevTables T = uniform_load(F.tables + r.tables_idx);
+    uint32_t n_wait = live ? uniform_load(F.ctx_wait_off + r.waitoff_off + r.H) : 0u;
+    PIN("+s"(T.trans), "+s"(n_wait));
+    const bool ctx_fits = live && r.item_n <= kFillContextItems && r.H <= FILL_CTX_SETS && n_wait <= FILL_CTX_WAITS;
+    uint32_t my_item = 0, x0[Team::BLOCK][4] = {}, list[FILL_LISTS] = {};
+    if (lane < front_n && !(addr & 1)) n_unc = tab(plane_row(addr) + 3 * (size_t)Vd.W);
+    if (ctx_fits && lane < r.item_n) my_item = tab(F.ctx_items + r.item_off + lane);
+    if (wave < FILL_OR_WAVES) {
+        if (live && front_n != 0 && front_n <= 64) union_load(plane_row(lane_address(addr, 0)), (Vd.W + 3) / 4, 0, x0);
+    } else {
+        if (wave == FILL_OR_WAVES) {
+            // the first planes' lists, whose lengths are on their way (a plane has room for a whole list, whatever it holds)
+            if (live && front_n != 0 && front_n <= 64)
+                _Pragma("unroll") for (uint32_t k = 0; k < FILL_LISTS; ++k)
+                    if (k < front_n) { const uint64_t a = lane_address(addr, k); if (!(a & 1)) list[k] = tab(plane_row(a) + 3 * (size_t)Vd.W + lane); }
+            ctx.cls_words[lane] = tab(T.byte_class_words + lane);
+        }
+        if (ctx_fits) {
+            for (uint32_t t = threadIdx.x - FILL_OR_THREADS; t < n_wait; t += THREADS - FILL_OR_THREADS) ctx.wait[t] = tab(F.ctx_wait + r.wait_base + t);
+            for (uint32_t t = threadIdx.x - FILL_OR_THREADS; t <= r.H; t += THREADS - FILL_OR_THREADS) ctx.off[t] = tab(F.ctx_wait_off + r.waitoff_off + t);
+        }
     }
     const bool no_list = n_unc > kUncListWords - 1;                   // more uncertain tokens than the plane's list holds
     uint32_t incl = no_list ? 0u : n_unc, total = 0;
@@ -1138,39 +1230,50 @@ __global__ __launch_bounds__(FILL_THREADS) __attribute__((amdgpu_waves_per_eu(6)
         total = lane_value(incl, 63);
     }
     const bool listed_way = live && front_n != 0 && (front_n > 64 || __any(no_list) || total > FILL_SPARSE_CAP);
-    const bool parses = listed_way || total != 0;
-    // whether wavefronts can parse from this row's context, and then the context in LDS
-    bool ctx_fits = false;
-    uint32_t n_wait = 0, my_item = 0;
-    static_assert(kFillContextItems <= WaveScan<false>::N, "a context's items lie across the lanes");
-    if (parses && !listed_way && r.item_n <= kFillContextItems && r.H <= FILL_CTX_SETS) {
-        n_wait = uniform_load(F.ctx_wait_off + r.waitoff_off + r.H);
-        ctx_fits = n_wait <= FILL_CTX_WAITS;
-        if (ctx_fits) {
-            if (lane < r.item_n) my_item = tab(F.ctx_items + r.item_off + lane);
-            if (wave >= FILL_OR_WAVES) {
-                for (uint32_t t = threadIdx.x - FILL_OR_THREADS; t < n_wait; t += FILL_THREADS - FILL_OR_THREADS) ctx.wait[t] = tab(F.ctx_wait + r.wait_base + t);
-                for (uint32_t t = threadIdx.x - FILL_OR_THREADS; t <= r.H; t += FILL_THREADS - FILL_OR_THREADS) ctx.off[t] = tab(F.ctx_wait_off + r.waitoff_off + t);
-            }
+    const bool wave_way = ctx_fits && !listed_way && total <= F.wave_tokens && total <= FILL_WAVE_MOST;
+    if (wave_way && total != 0 && wave == FILL_OR_WAVES) {
+        // every candidate at once, one a lane: its token, its bytes, whether a frontier plane accepts it (then it is in the mask already)
+        const uint32_t k = prefix_owner(incl, lane);
+        const uint32_t end_k = (uint32_t)__shfl((int)incl, (int)k), n_k = (uint32_t)__shfl((int)n_unc, (int)k), at = 1 + (lane - (end_k - n_k));
+        uint32_t id = 0, accepted = 1;
+        _Pragma("unroll") for (uint32_t p = 0; p < FILL_LISTS; ++p) {
+            const uint32_t x = (uint32_t)__shfl((int)list[p], (int)at);
+            if (k == p) id = x;
         }
+        if (front_n > FILL_LISTS) {
+            const uint32_t a_lo = (uint32_t)__shfl((int)(uint32_t)addr, (int)k), a_hi = (uint32_t)__shfl((int)(uint32_t)(addr >> 32), (int)k);
+            if (lane < total && k >= FILL_LISTS) id = tab(plane_row(((uint64_t)a_hi << 32) | a_lo) + 3 * (size_t)Vd.W + at);
+        }
+        TokenRecord rec{};
+        if (lane < total) {
+            rec = tab(Vd.rec + id);
+            accepted = 0;
+            for (uint32_t k2 = 0; k2 < front_n; ++k2) accepted |= tab(plane_row(lane_address(addr, k2)) + (id >> 5)) >> (id & 31);
+            accepted |= rec.n_bytes == 0;
+        }
+        const unsigned long long parse = lanes_of(!(accepted & 1u));
+        if (has_lane(parse)) {
+            WaveToken& x = sh_tok[count_below(parse)];
+            x.words[0] = rec.head.x; x.words[1] = rec.head.y; x.words[2] = rec.head.z; x.words[3] = rec.head.w;
+            x.id = id; x.off = rec.off; x.n_bytes = rec.n_bytes;
+        }
+        if (lane == 0) n_to_parse = (uint32_t)__popcll(parse);
     }
-    const bool wave_way = ctx_fits && !listed_way && total <= F.wave_tokens;
-    if (parses && wave == FILL_OR_WAVES) ctx.cls_words[lane] = tab(uniform_load(&F.tables[r.tables_idx].byte_class_words) + lane);
-    uint32_t* out = reinterpret_cast<uint32_t*>(bitmask) + (long long)b * row_stride;
-    FillStore st;
-    const uint32_t col = (wave - FILL_OR_WAVES) * FILL_RECHECK_LANES + lane;      // re-check team: this lane's place among the lanes at work
-    const bool at_work = wave >= FILL_OR_WAVES && lane < FILL_RECHECK_LANES;
+    uint32_t* out = reinterpret_cast<uint32_t*>(A.bitmask) + (long long)b * A.row_stride;
+    typename Team::Store st;
+    const uint32_t col = (wave - FILL_OR_WAVES) * LANES + lane;      // re-check team: this lane's place among the lanes at work
+    const bool at_work = wave >= FILL_OR_WAVES && lane < LANES;
     if (at_work) st.init(lds_store + col);
     __syncthreads();
 
     if (wave < FILL_OR_WAVES) {
-        if (listed_way) fill_union<2, true>(F, Vd.W, b, front_off, front_n, live, (flags & 3u) != 0, out, &n_listed, &n_cand);
-        else fill_union<FILL_BLOCK, false>(F, Vd.W, b, front_off, front_n, live, (flags & 3u) != 0, out, &n_listed, &n_cand);
+        if (listed_way) fill_union_listing<2>(F, Vd.W, b, front_off, front_n, (flags & 3u) != 0, out, &n_listed, &n_cand);
+        else fill_union(F, Vd.W, addr, live ? front_n : 0u, (flags & 3u) != 0, out, x0);
     } else if (!listed_way && total != 0 && !wave_way) {
         // side by side with the union, a lane per candidate: candidate t is entry t - (tokens of the planes before) of its plane's list
-        const DevTables T = uniform_load(F.tables + r.tables_idx);
-        const DevCtx C = row_ctx(F, r);
-        for (uint32_t t0 = 0; t0 < total; t0 += FILL_COLS) {
+        const FillArgs Z = args_again<FillArgs>();
+        const DevCtx C = row_ctx(Z.F, uniform_load(Z.F.rows + b));
+        for (uint32_t t0 = 0; t0 < total; t0 += COLS) {
             const uint32_t t = t0 + col;
             const bool mine = at_work && t < total;
             const uint32_t k = prefix_owner(incl, t);
@@ -1191,6 +1294,8 @@ __global__ __launch_bounds__(FILL_THREADS) __attribute__((amdgpu_waves_per_eu(6)
             }
         }
     }
+    // (the wavefronts' way: of the tokens that no plane accepts; below, sh_surv is theirs)
+    const uint32_t n_tokens = wave_way && total != 0 ? same_in_all(n_to_parse) : total;
     bool waves_parse = wave_way && total != 0;
     if (!listed_way && total != 0 && !wave_way) {                   // (the same for the whole row)
         __syncthreads();
@@ -1198,7 +1303,6 @@ __global__ __launch_bounds__(FILL_THREADS) __attribute__((amdgpu_waves_per_eu(6)
     }
     if (waves_parse) {
         // a wavefront per candidate, the union team joining in when its row is stored; or per token that did not fit a lane's lists
-        const DevTables T = uniform_load(F.tables + r.tables_idx);
         for (;;) {
             // The wavefront stays together from token to token: with nothing between "lane 0 stores a result" below and "lane 0
             // takes the next token" here the compiler may send the other lanes round the loop without lane 0.
@@ -1207,21 +1311,21 @@ __global__ __launch_bounds__(FILL_THREADS) __attribute__((amdgpu_waves_per_eu(6)
             if (lane == 0) t = atomicAdd(&next_token, 1u);
             wave_sync();
             t = same_in_all(t);
-            if (t >= total) break;
-            uint32_t id;
-            bool accepts = false;
+            if (t >= n_tokens) break;
+            uint32_t id, at, n_bytes;
+            uint32_t tok_word;                                       // lane k: bytes 4 k .. 4 k + 3 (of the first 16)
             if (wave_way) {
-                const uint32_t k = (uint32_t)__ffsll((long long)__ballot(incl > t)) - 1;
-                const uint64_t a_k = ((uint64_t)lane_value((uint32_t)(addr >> 32), k) << 32) | lane_value((uint32_t)addr, k);
-                id = uniform_load(reinterpret_cast<const uint32_t*>(a_k) + 3 * (size_t)Vd.W + 1 + (t - (lane_value(incl, k) - lane_value(n_unc, k))));
-                if (lane < front_n) accepts = (tab(reinterpret_cast<const uint32_t*>(addr & ~(uint64_t)1) + (id >> 5)) >> (id & 31)) & 1u;
+                id = same_in_all(sh_tok[t].id); at = same_in_all(sh_tok[t].off); n_bytes = same_in_all(sh_tok[t].n_bytes);
+                tok_word = sh_tok[t].words[lane & 3];
             } else {
                 const uint32_t v = same_in_all(sh_surv[t]);
                 if (!(v & FILL_OVER)) continue;
                 id = v & ~FILL_OVER;
+                at = uniform_load(&Vd.rec[id].off); n_bytes = uniform_load(&Vd.rec[id].n_bytes);
+                tok_word = tab(reinterpret_cast<const uint32_t*>(Vd.rec + id) + (lane & 3));
             }
             bool large = !wave_way;
-            const int res = __any(accepts) ? RECHECK_NO : recheck_wave(Vd, S, T, ctx, sh_own[wave], r.H, r.item_n, my_item, id, lane, &large);
+            const int res = recheck_wave(Vd, A.S, T, ctx, sh_own[wave], r.H, r.item_n, my_item, tok_word, at, n_bytes, lane, &large);
             if (lane == 0) {
                 sh_surv[t] = (res == RECHECK_NO ? FILL_NONE : id) | (res == RECHECK_OVER ? FILL_OVER : large ? FILL_LARGE : 0u);
                 if (wave_way && res == RECHECK_OVER) atomicAdd(&n_over, 1u);
@@ -1232,23 +1336,26 @@ __global__ __launch_bounds__(FILL_THREADS) __attribute__((amdgpu_waves_per_eu(6)
 
     if (!listed_way) {
         uint32_t n_large = 0;
-        for (uint32_t t0 = wave * 64; t0 < total; t0 += FILL_THREADS) {
-            const uint32_t t = t0 + lane, v = t < total ? sh_surv[t] : FILL_NONE, id = v & FILL_NONE;
+        for (uint32_t t0 = wave * 64; t0 < n_tokens; t0 += THREADS) {
+            const uint32_t t = t0 + lane, v = t < n_tokens ? sh_surv[t] : FILL_NONE, id = v & FILL_NONE;
             n_large += (uint32_t)__popcll(__ballot((v & (FILL_OVER | FILL_LARGE)) != 0));
             if (v & FILL_OVER) {
-                if (F.follows && try_push(S, b, id)) sh_surv[t] = FILL_NONE;
-                else if (!F.own_lanes) leave_undecided(S, b, id);
+                const FillArgs Z = args_again<FillArgs>();
+                if (Z.F.follows && try_push(Z.S, b, id)) sh_surv[t] = FILL_NONE;
+                else if (!Z.F.own_lanes) leave_undecided(Z.S, b, id);
             } else if (id != FILL_NONE) atomicOr(out + (id >> 5), 1u << (id & 31));
         }
-        if (n_large != 0 && lane == 0) atomicAdd(S.count + 3, n_large);
+        if (n_large != 0 && lane == 0) atomicAdd(args_again<FillArgs>().S.count + 3, n_large);
         if (threadIdx.x == 0) F.row_count[b] = total;               // every row writes its count: nothing to clear beforehand
         // what fits nowhere else: one lane of every wavefront that has a lane of the large-capacity scratch
-        if (n_over != 0 && F.own_lanes != 0) {
-            if (F.follows) __syncthreads();
-            if (lane == 0 && wave < F.own_lanes)
-                for (uint32_t t = wave; t < total; t += F.own_lanes) {
+        if (n_over != 0 && args_again<FillArgs>().F.own_lanes != 0) {
+            const FillArgs Z = args_again<FillArgs>();
+            const FillRow q = uniform_load(Z.F.rows + b);
+            if (Z.F.follows) __syncthreads();
+            if (lane == 0 && wave < Z.F.own_lanes)
+                for (uint32_t t = wave; t < n_tokens; t += Z.F.own_lanes) {
                     const uint32_t v = sh_surv[t], id = v & FILL_NONE;
-                    if ((v & FILL_OVER) && recheck_large(F, Vd, S, r, b, id, b * F.own_lanes + wave)) atomicOr(out + (id >> 5), 1u << (id & 31));
+                    if ((v & FILL_OVER) && recheck_large(Z.F, Z.Vd, Z.S, q, b, id, b * Z.F.own_lanes + wave)) atomicOr(out + (id >> 5), 1u << (id & 31));
                 }
         }
         stamp_end();
@@ -1258,53 +1365,55 @@ __global__ __launch_bounds__(FILL_THREADS) __attribute__((amdgpu_waves_per_eu(6)
     if (wave < FILL_OR_WAVES) { stamp_end(); return; }
     // the sequential way: each wave of the re-check team takes as many listed words at a time as it has lanes at work
     // and spreads their set bits densely over those lanes
+    const FillArgs Z = args_again<FillArgs>();
+    const FillRow q = uniform_load(Z.F.rows + b);
+    const DevTables T2 = uniform_load(Z.F.tables + q.tables_idx);
     const uint32_t count = n_listed;
-    const uint32_t* wlist = F.work_list + b * Vd.W;
-    const uint32_t* cands = F.cand_words + b * Vd.W;
-    const DevTables T = uniform_load(F.tables + r.tables_idx);
-    const DevCtx C = row_ctx(F, r);
+    const uint32_t* wlist = Z.F.work_list + b * Z.Vd.W;
+    const uint32_t* cands = Z.F.cand_words + b * Z.Vd.W;
+    const DevCtx C = row_ctx(Z.F, q);
     uint32_t large = 0;
-    for (uint32_t base = (wave - FILL_OR_WAVES) * FILL_RECHECK_LANES; base < count; base += FILL_COLS) {
+    for (uint32_t base = (wave - FILL_OR_WAVES) * LANES; base < count; base += COLS) {
         uint32_t idx = 0, cand = 0;
-        if (lane < FILL_RECHECK_LANES && base + lane < count) { idx = wlist[base + lane]; cand = cands[idx]; }
+        if (lane < LANES && base + lane < count) { idx = wlist[base + lane]; cand = cands[idx]; }
         uint32_t pre = (uint32_t)__popc(cand);
         for (int d = 1; d < 64; d <<= 1) { const uint32_t up = (uint32_t)__shfl_up((int)pre, d); if ((int)lane >= d) pre += up; }
         const uint32_t n_tok = lane_value(pre, 63);
-        for (uint32_t t0 = 0; t0 < n_tok; t0 += FILL_RECHECK_LANES) {
+        for (uint32_t t0 = 0; t0 < n_tok; t0 += LANES) {
             const uint32_t my = t0 + lane;
             const uint32_t j = prefix_owner(pre, my);
             uint32_t c = (uint32_t)__shfl((int)cand, (int)j);
             const uint32_t end_j = (uint32_t)__shfl((int)pre, (int)j), w = (uint32_t)__shfl((int)idx, (int)j);
             bool over = false;
             uint32_t id = 0;
-            if (lane < FILL_RECHECK_LANES && my < n_tok) {
+            if (lane < LANES && my < n_tok) {
                 uint32_t skip = my - (end_j - (uint32_t)__popc(c));
                 while (skip--) c &= c - 1;                             // drop the lowest set bits that other lanes take
                 id = w * 32 + (uint32_t)__ffs(c) - 1;
-                const int res = recheck_lane(Vd, T, ctx.cls_words, C, id, st);
+                const int res = recheck_lane(Z.Vd, T2, ctx.cls_words, C, id, st);
                 if (res == RECHECK_YES) atomicOr(out + w, 1u << (id & 31));
                 over = res == RECHECK_OVER;
             }
             unsigned long long m = __ballot(over);
             if (!m) continue;
             large += (uint32_t)__popcll(m);
-            if (F.follows) {                                           // to k_recheck_slow; if its list is full, to one lane with its lists in device memory
+            if (Z.F.follows) {                                           // to k_recheck_slow; if its list is full, to one lane with its lists in device memory
                 uint32_t at = 0;
-                if (lane == 0) at = atomicAdd(S.count, (uint32_t)__popcll(m));
+                if (lane == 0) at = atomicAdd(Z.S.count, (uint32_t)__popcll(m));
                 at = lane_value(at, 0) + (uint32_t)__popcll(m & ((1ull << lane) - 1));
-                const bool fits = over && at < S.list_cap;
-                if (fits) { S.list[2 * at] = b; S.list[2 * at + 1] = id; }
+                const bool fits = over && at < Z.S.list_cap;
+                if (fits) { Z.S.list[2 * at] = b; Z.S.list[2 * at + 1] = id; }
                 m = __ballot(over && !fits);
             }
             while (m) {
                 const uint32_t id2 = lane_value(id, next_bit(m));
                 if (lane != 0) continue;
-                if (!F.own_lanes) leave_undecided(S, b, id2);
-                else if (recheck_large(F, Vd, S, r, b, id2, b * F.own_lanes + (wave - FILL_OR_WAVES))) atomicOr(out + (id2 >> 5), 1u << (id2 & 31));
+                if (!Z.F.own_lanes) leave_undecided(Z.S, b, id2);
+                else if (recheck_large(Z.F, Z.Vd, Z.S, q, b, id2, b * Z.F.own_lanes + (wave - FILL_OR_WAVES))) atomicOr(out + (id2 >> 5), 1u << (id2 & 31));
             }
         }
     }
-    if (lane == 0 && large) atomicAdd(S.count + 3, large);
+    if (lane == 0 && large) atomicAdd(Z.S.count + 3, large);
     stamp_end();
 }
 
@@ -1333,7 +1442,7 @@ __global__ __launch_bounds__(64) void k_recheck_slow(FillBatch F, DevVocab Vd, i
         else alive = (res & RES_ALIVE) != 0;
         if (alive) atomicOr(reinterpret_cast<uint32_t*>(bitmask) + (long long)b * row_stride + (id >> 5), 1u << (id & 31));
     }
-    if (F.stamps && threadIdx.x == 0) F.stamps[kStampsRows + kStampsPerRow * F.B + blockIdx.x] = wall_clock64();
+    if (F.stamps && threadIdx.x == 0) F.stamps[kStampsRows + (F.row_waves + 1) * F.B + blockIdx.x] = wall_clock64();
 }
 
 // ---- matchers on the device ------------------------------------------------------------------------
@@ -1412,27 +1521,9 @@ __global__ __launch_bounds__(256) void k_batch_assign(BatchDev D, const int32_t*
 
 constexpr uint32_t ACC_KI = kSlotItems, ACC_KH = kSlotSets, ACC_KW = kSlotWaits, ACC_KF = kSlotPlanes;     // the slot capacities the LDS staging is laid out for
 
-// What the kernel is launched with.  args_again() reads it anew from the launch's own memory: the way out below is rarely taken, and
-// what only it needs must not take up registers on the way that nearly every token goes.
+// What the kernel is launched with (read anew where a way is rarely taken).
 struct AcceptArgs { BatchDev D; DevVocab Vd; uint32_t eos_id; const int32_t* token_ids; int32_t* status; };
-template <class A>
-__device__ __forceinline__ A args_again() {
-#if defined(__HIP_DEVICE_COMPILE__)
-    auto p = (const __attribute__((address_space(4))) A*)__builtin_amdgcn_kernarg_segment_ptr();
-    asm volatile("" : "+s"(p));
-    return *p;
-#else
-    return A{};
-#endif
-}
 
-// Values that are wanted here: loads whose results are named are asked for before this point, all together, and not one after the
-// other where the compiler would rather have them (behind the branch on an earlier one).
-#if defined(__HIP_DEVICE_COMPILE__)
-#define PIN(...) asm volatile("" : __VA_ARGS__)
-#else
-#define PIN(...) (void)0
-#endif
 // What accepting a token needs of a cache.
 struct CacheView {
     DevTables T;
@@ -1901,8 +1992,11 @@ void launch_finish_planes(uint32_t* const* plane_ptr_dev, const FinishJob* jobs_
 void launch_fill(const FillBatch& F, const DevVocab& Vd, int32_t* bitmask_dev, int64_t row_stride_words,
                  const SlowScratch& S, hipStream_t stream, hipEvent_t done) {
     if (F.B == 0) return;
-    if (done) hipExtLaunchKernelGGL(k_fill, dim3(F.B), dim3(FILL_THREADS), 0, stream, nullptr, done, 0, F, Vd, bitmask_dev, (long long)row_stride_words, S);
-    else hipLaunchKernelGGL(k_fill, dim3(F.B), dim3(FILL_THREADS), 0, stream, F, Vd, bitmask_dev, (long long)row_stride_words, S);
+    auto* const kernel = F.row_waves == 16 ? k_fill<16> : F.row_waves == 12 ? k_fill<12> : k_fill<6>;
+    const dim3 block(64 * F.row_waves);
+    const FillArgs A{F, Vd, bitmask_dev, (long long)row_stride_words, S};
+    if (done) hipExtLaunchKernelGGL(kernel, dim3(F.B), block, 0, stream, nullptr, done, 0, A);
+    else hipLaunchKernelGGL(kernel, dim3(F.B), block, 0, stream, A);
 }
 
 void launch_recheck_slow(const FillBatch& F, const DevVocab& Vd, int32_t* bitmask_dev, int64_t row_stride_words,

@@ -118,6 +118,54 @@ def test_masks_with_large_tokens(xg, ebnf, n, shortest, longest, rows):
         check(lambda bm: xg.fill_next_token_bitmask_noalloc(few, bm.data_ptr(), W, _stream()), hist[:128])
 
 
+# two rules for the same text: every uncertain token is a candidate twice
+TWICE = ('root ::= p | b\n'
+         'p ::= "(" (p | b | x | y) ")"\n'
+         'b ::= "[" (p | b | x) "]"\n'
+         'x ::= [a-z]+\n'
+         'y ::= [a-z]+ "."?\n')
+
+
+@pytest.mark.parametrize("rows", [1, 256, 257, 600])                  # a workgroup of 16, 16, and of 12 wavefronts, or 6 with two tokens
+@pytest.mark.parametrize("ebnf,n", [(EBNF, 2), (EBNF, 3), (EBNF, 48), (EBNF, 49), (EBNF, 63),
+                                    (TWICE, 24), (TWICE, 25), (TWICE, 32), (TWICE, 33), (TWICE, 60)],
+                         ids=lambda v: "twice" if v is TWICE else "nest" if v is EBNF else str(v))
+def test_masks_by_size_of_the_workgroup(xg, ebnf, n, rows):
+    """Up to four candidates for each wavefront of a row, and more: 24, 48, 64 and the next of each, in a row's one plane or in two."""
+    import torch
+    toks = _tokens(n, 3, 14)
+    kinds = [b"(", b"(z", b"([z", b"((((b", b"(" * 12 + b"a"]
+    starts = [kinds[(k * 7) % len(kinds)] for k in range(rows)]
+    vocab, cache, db = _batch(xg, toks, starts, ebnf)
+    orc, va = oracle.Oracle(ebnf, "root"), oracle.VocabArrays(toks, 0, [0])
+    want = {s: oracle.pack_bitmask(orc.mask(s, va)) for s in set(starts)}
+    bm = torch.full((rows, vocab.words), -1, dtype=torch.int32, device="cuda")
+    for _ in range(2):
+        db.fill_next_token_bitmask(bm.data_ptr(), vocab.words, _stream())
+        assert not xg.fill_last_status()[1]
+        assert np.array_equal(bm.cpu().numpy(), np.stack([want[s] for s in starts]))
+
+
+@pytest.mark.parametrize("rows", [2, 300])
+@pytest.mark.parametrize("V", [131071, 131072 + 33, 163840, 163840 + 1])
+def test_masks_of_rows_beyond_one_block(xg, V, rows):
+    """The union asks for 4,096 or 5,120 words of a row at a time: rows of that many and a few more."""
+    import itertools
+    import torch
+    toks = [b""] + [bytes([c]) for c in b"()[]"]
+    for n in (1, 2, 3, 4):
+        toks += [bytes(t) for t in itertools.islice(itertools.product(b"abcdefghijklmnopqrstuvwxyz", repeat=n), V - len(toks) - 2)]
+    toks += [b"zz)", b"a]"]
+    assert len(toks) == V and len(set(toks)) == V
+    starts = [[b"(z", b"[", b"([", b""][k % 4] for k in range(rows)]
+    vocab, cache, db = _batch(xg, toks, starts)
+    orc, va = oracle.Oracle(EBNF, "root"), oracle.VocabArrays(toks, 0, [0])
+    want = {s: oracle.pack_bitmask(orc.mask(s, va)) for s in set(starts)}
+    bm = torch.full((rows, vocab.words), -1, dtype=torch.int32, device="cuda")
+    db.fill_next_token_bitmask(bm.data_ptr(), vocab.words, _stream())
+    assert np.array_equal(bm.cpu().numpy(), np.stack([want[s] for s in starts]))
+
+
 def _us(f):
     import torch
     f()
