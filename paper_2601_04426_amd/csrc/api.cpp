@@ -774,7 +774,6 @@ int32_t report_undecided_pairs() {
 class HostWorkers {
     std::mutex call_mu, mu;
     std::condition_variable cv_work, cv_done;
-    std::vector<std::thread> threads;
     const std::function<void(int32_t)>* job = nullptr;
     int32_t n_parts = 0, next = 0, pending = 0;
     void worker() {
@@ -795,8 +794,12 @@ class HostWorkers {
         }
     }
   public:
-    explicit HostWorkers(int32_t n) { for (int32_t k = 0; k < n; ++k) threads.emplace_back([this] { worker(); }); for (auto& t : threads) t.detach(); }
-    int32_t size() const { return (int32_t)threads.size(); }
+    // a thread that cannot be started is done without: the caller takes every part that nobody else takes
+    HostWorkers() {
+        const int32_t n = std::max<int32_t>(0, std::min<int32_t>((int32_t)std::thread::hardware_concurrency(), 8) - 1);
+        try { for (int32_t k = 0; k < n; ++k) std::thread([this] { worker(); }).detach(); }
+        catch (const std::exception&) {}
+    }
     void run(int32_t parts, const std::function<void(int32_t)>& f) {
         if (parts <= 0) return;
         std::lock_guard<std::mutex> one_call(call_mu);
@@ -808,11 +811,16 @@ class HostWorkers {
     }
 };
 HostWorkers& host_workers() {
-    static HostWorkers* w = new HostWorkers(std::max<int32_t>(0, std::min<int32_t>((int32_t)std::thread::hardware_concurrency(), 8) - 1));
+    static HostWorkers* w = new HostWorkers;
+    return *w;
+}
+// The compile calls' own: a decoding step never waits for the analysis of a grammar that another thread compiles.
+HostWorkers& compile_workers() {
+    static HostWorkers* w = new HostWorkers;
     return *w;
 }
 
-// The analyses of the rules `which` (they do not depend on one another), on the host threads where that is worth waking them.
+// The analyses of the rules `which` (they do not depend on one another), on host threads where that is worth waking them.
 void analyse_rules(const Grammar& g, std::vector<int> which, int32_t budget, const std::vector<uint64_t>& identity,
                    std::vector<std::shared_ptr<const RuleAnalysis>>& out) {
     auto states = [&](int r) { return g.rules[(size_t)r].n_states(); };
@@ -830,7 +838,7 @@ void analyse_rules(const Grammar& g, std::vector<int> which, int32_t budget, con
         if ((in_part += states(which[k])) >= 64 || k + 1 == which.size()) { part.push_back(k + 1); in_part = 0; }
     std::mutex mu;
     std::exception_ptr failed;
-    host_workers().run((int32_t)part.size() - 1, [&](int32_t p) {
+    compile_workers().run((int32_t)part.size() - 1, [&](int32_t p) {
         try { for (size_t k = part[(size_t)p]; k < part[(size_t)p + 1]; ++k) one(which[k]); }
         catch (...) { std::lock_guard<std::mutex> lk(mu); failed = std::current_exception(); }
     });
