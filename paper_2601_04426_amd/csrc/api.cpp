@@ -1194,18 +1194,21 @@ int32_t build_planes(CacheImpl& cache, const std::vector<int32_t>& todo, hipStre
     std::vector<uint32_t> range_first;
     range_a.reserve(ranges.size() + 64); range_b.reserve(ranges.size() + 64); range_first.reserve(ranges.size() + 64);
     size_t n_chunks = 0;
+    size_t n_full = 0;                                           // chunks, if all were of kBuildChunk ranks
+    for (const uint4& r : ranges) if (!(r.w & kChunkDerive)) n_full += (r.z - r.y + kBuildChunk - 1) / kBuildChunk;
+    const uint32_t ranks = build_chunk(n_full);
     for (uint32_t pass_heavy : {kChunkHeavy, 0u})
         for (const uint4& r : ranges) {
             if ((r.w & kChunkHeavy) != pass_heavy) continue;
             const bool derive = r.w & kChunkDerive;
-            const uint32_t step = derive ? kDeriveChunk : pass_heavy ? kHeavyChunk : kBuildChunk;
+            const uint32_t step = derive ? kDeriveChunk : ranks;
             const uint4& pc = plane_ctx[r.x];
             const uint64_t row = derive ? derive_base[r.x] : (uint64_t)(uintptr_t)rows[r.x]->mem;
             const uint4 second = derive ? make_uint4(0u, 0u, (uint32_t)row, (uint32_t)(row >> 32))
                                         : make_uint4(ctx_items[pc.x], pc.y, (uint32_t)row, (uint32_t)(row >> 32));
             for (uint32_t lo = r.y; lo < r.z; lo += 32 * step) {
                 const uint32_t hi = std::min(r.z, lo + 32 * step);
-                range_a.push_back(make_uint4(r.x, lo, hi, r.w));
+                range_a.push_back(make_uint4(r.x, lo, hi, r.w | step << kChunkStepShift));
                 range_b.push_back(second);
                 range_first.push_back((uint32_t)n_chunks);
                 n_chunks += (hi - lo + step - 1) / step;

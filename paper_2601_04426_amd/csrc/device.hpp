@@ -41,7 +41,7 @@ struct DevVocab {                        // byte-sorted vocabulary in HBM
 // second what the automaton walk needs of the plane without a further load {first item of the start set, number of
 // its items, row address low, row address high}.  Below, chunk[c] stands for the first half of record c.
 // Chunk c covers sorted ranks [chunk[c].y, chunk[c].z) of plane chunk[c].x
-// (at most kBuildChunk tokens, all with a first byte the plane's start set can read); with bit 0 of chunk[c].w
+// (at most build_chunk() tokens, all with a first byte the plane's start set can read); with bit 0 of chunk[c].w
 // set, y and z index DevVocab::long_rank instead and the ranks are read from there (a plane that needs only
 // its long tokens checked).  The workgroups of a persistent grid take chunks round-robin.  plane_ctx[k] = {first item, number of items, first wait offset, H} describes the closed start
 // set of plane k as a scan context (H = 1: the position alone; H = 2: the position inside one level of
@@ -54,11 +54,16 @@ struct DevVocab {                        // byte-sorted vocabulary in HBM
 #define XG2_BUILD_CHUNK 128
 #endif
 constexpr uint32_t kBuildChunk = XG2_BUILD_CHUNK;
-#ifndef XG2_HEAVY_CHUNK
-#define XG2_HEAVY_CHUNK XG2_BUILD_CHUNK
-#endif
-constexpr uint32_t kHeavyChunk = XG2_HEAVY_CHUNK;             // chunk size of planes whose tokens all take the Earley steps
-static_assert(kHeavyChunk <= kBuildChunk && kBuildChunk <= 256, "the deferred list is sized for kBuildChunk and holds one-byte offsets");
+// Ranks of a chunk, for a launch that has n_full chunks of kBuildChunk.  Where the device holds all of them at once the launch lasts
+// as long as its slowest workgroup, and one of half a chunk goes through each phase once (64 tokens, a wavefront's lanes) and not
+// twice.  With more, workgroups take several in turn, and a chunk's fixed costs and part-filled batches count.  k_build, us, 128 / 64
+// ranks: 16 - 740 chunks of a just-in-time build 29.7 / 21.7 on average, 1,901 chunks 53.5 / 44.3, 3,509 67.7 / 48.6, 6,248 64.9 / 49.4,
+// 6,506 64.3 / 52.6, but 9,892 82.7 / 86.6, 9,963 66.0 / 79.1, 13,000 123.7 / 133.8 (17,000 - 30,000: 6 - 14 % less again).  32 ranks: no
+// gain just in time (22.0), 77.6 at 6,506.
+constexpr uint32_t kBuildSlots = 256 * 32;                   // wavefronts that the device holds
+constexpr uint32_t build_chunk(size_t n_full) { return n_full <= kBuildSlots ? 64 : kBuildChunk; }
+static_assert(kBuildChunk >= 64, "build_chunk makes chunks smaller, not larger");
+static_assert(kBuildChunk <= 256, "the deferred list is sized for kBuildChunk and holds one-byte offsets");
 struct BuildPlan {
     const uint4* chunk; uint32_t n_chunks;                      // 2 * n_chunks uint4
     const uint4* plane_ctx;                                     // [n_planes]
@@ -86,7 +91,8 @@ constexpr uint32_t kSlowSearchBudget = 1u << 20;     // list entries one token m
 constexpr uint32_t kSlowLanes = 64 * 64;                      // lanes of the large-capacity scratch (the fixed array's has fewer)
 constexpr uint32_t kSlowSlots = 2 * kSlowK + 2 * kSlowWM + kSlowMaxLen + 1;
 
-constexpr uint32_t kChunkListed = 1u, kChunkHeavy = 2u, kChunkThreads = 4u, kChunkDerive = 8u;   // bits of chunk[c].w
+constexpr uint32_t kChunkListed = 1u, kChunkHeavy = 2u, kChunkThreads = 4u, kChunkDerive = 8u;   // bits of chunk[c].w,
+constexpr uint32_t kChunkStepShift = 8;                      //   and from this one on the ranks (words) that the chunks of its range have
 constexpr uint32_t kDeriveChunk = 64;                        // mask words of a derive chunk: y and z are word indices there, and the second
                                                              // half of the record holds the address of the base plane's third row
 constexpr uint32_t kNoThread = 0xFFFFFFFFu;                  // an empty slot of the thread walk (what the transition table holds for "no edge")
@@ -103,7 +109,7 @@ struct FirstByteCopyJob { uint32_t* dst; const uint32_t* src; uint32_t bytes[8];
 void launch_copy_first_byte(const FirstByteCopyJob* jobs_dev, uint32_t n_jobs, const uint8_t* first_byte_dev, uint32_t W, hipStream_t stream);
 
 // Writes the chunk records of a build: thread r cuts range_a[r] = {plane, first rank, end rank, flags} into chunks of
-// kBuildChunk (kHeavyChunk with kChunkHeavy) ranks, records first[r], first[r] + 1, ..., each followed by range_b[r].
+// range_a[r].w >> kChunkStepShift ranks, records first[r], first[r] + 1, ..., each followed by range_b[r].
 void launch_expand_chunks(const uint4* range_a_dev, const uint4* range_b_dev, const uint32_t* first_dev, uint32_t n_ranges,
                           uint4* chunk_dev, hipStream_t stream);
 // One launch for what a build needs first: the copy of `bytes` (a multiple of 16) from pinned host memory (given by its

@@ -531,7 +531,7 @@ __global__ __launch_bounds__(64) void k_clear(uint32_t* words, uint32_t n) {
 
 __device__ __forceinline__ void expand_range(const uint4* range_a, const uint4* range_b, const uint32_t* first, uint32_t r, uint4* chunk) {
     const uint4 a = range_a[r], b = range_b[r];
-    const uint32_t step = (a.w & kChunkDerive) ? kDeriveChunk : (a.w & kChunkHeavy) ? kHeavyChunk : kBuildChunk;
+    const uint32_t step = a.w >> kChunkStepShift;
     uint4* out = chunk + 2 * (size_t)first[r];
     for (uint32_t lo = a.y; lo < a.z; lo += step, out += 2) {
         out[0] = make_uint4(a.x, lo, min(a.z, lo + step), a.w);
