@@ -667,7 +667,7 @@ struct FillLoad { uint32_t plane_tokens = 0, row_tokens = 0; bool deep = false, 
 inline void share_out(FillBatch& F, uint32_t n_lanes, const FillLoad& load) {
     const uint32_t per = n_lanes / F.B;
     const bool spread = F.B <= kFillSpreadRows && load.long_tokens;
-    F.own_lanes = per < 2 ? 0u : std::min<uint32_t>(per, 6);
+    F.own_lanes = per < 2 ? 0u : std::min(per, kFillOwnLanes);
     F.follows = F.own_lanes == 0 || load.deep || load.plane_tokens > kFillPlaneTokens || load.row_tokens > kFillRowTokens
                 || (spread && std::max(load.plane_tokens, load.row_tokens) > kFillSpreadTokens);
     F.row_waves = fill_row_waves(F.B, std::max(load.plane_tokens, load.row_tokens));

@@ -159,7 +159,9 @@ struct FillBatch {
     uint32_t* row_count;                 // [B], written by the fill kernel: candidate tokens of the row
     uint32_t* zero_words;                // if not null: four words the fill kernel clears for the next call (the overflow list's length
                                          // and flag, where no upload brings them in as zeros: two sets take turns)
-    uint32_t own_lanes;                  // lanes of the large-capacity scratch that are a row's own while k_fill runs, or 0: there are too few
+    uint32_t own_lanes;                  // lanes of the large-capacity scratch that are a row's own while k_fill runs (at most kFillOwnLanes: a
+                                         // wavefront of it uses lane own_lanes * row + its number, and only if that is below own_lanes), or 0:
+                                         // there are too few
     uint32_t follows;                    // k_recheck_slow is launched behind it and takes what the rows leave on the overflow list (always
                                          // if own_lanes is 0)
     uint32_t row_waves;                  // wavefronts of a row's workgroup: fill_row_waves()
@@ -173,7 +175,7 @@ struct FillBatch {
 constexpr uint32_t kFillLaneItems = 8, kFillLaneWaits = 12, kFillLaneBytes = 16;    // lists and bytes of a lane that parses a token by itself
 constexpr uint32_t kFillWaveTokens = 4;                      // FillBatch::wave_tokens for each wavefront of the workgroup, as a rule
 // Wavefronts of a row's workgroup, in a batch of `rows` rows that have up to `tokens` uncertain tokens (k_fill has the figures).
-constexpr uint32_t kFillMostWaves = 16;
+constexpr uint32_t kFillMostWaves = 16, kFillOwnLanes = 6;
 constexpr uint32_t kComputeUnits = 256;
 constexpr uint32_t fill_row_waves(uint32_t rows, uint32_t tokens) { return rows <= kComputeUnits ? 16 : tokens > 2 ? 12 : 6; }
 constexpr uint32_t kFillSpreadRows = 192, kFillSpreadTokens = 18;    // batches of up to that many rows, where tokens may be long in numbers: wave_tokens, leave_above

@@ -1180,6 +1180,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVE
     const DevVocab& Vd = A.Vd;
     using Team = FillTeam<WAVES>;
     constexpr uint32_t THREADS = Team::THREADS, LANES = Team::LANES, COLS = Team::COLS;
+    static_assert(WAVES >= kFillOwnLanes, "each of a row's own lanes of the large-capacity scratch is a wavefront's");
     __shared__ uint32_t lds_store[Team::Store::SLOTS * COLS];
     __shared__ uint32_t sh_surv[FILL_SPARSE_CAP];
     __shared__ FillCtx ctx;
@@ -1362,58 +1363,74 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVE
         return;
     }
     if (threadIdx.x == 0) F.row_count[b] = n_cand;
-    if (wave < FILL_OR_WAVES) { stamp_end(); return; }
     // the sequential way: each wave of the re-check team takes as many listed words at a time as it has lanes at work
     // and spreads their set bits densely over those lanes
     const FillArgs Z = args_again<FillArgs>();
     const FillRow q = uniform_load(Z.F.rows + b);
-    const DevTables T2 = uniform_load(Z.F.tables + q.tables_idx);
     const uint32_t count = n_listed;
     const uint32_t* wlist = Z.F.work_list + b * Z.Vd.W;
-    const uint32_t* cands = Z.F.cand_words + b * Z.Vd.W;
-    const DevCtx C = row_ctx(Z.F, q);
-    uint32_t large = 0;
-    for (uint32_t base = (wave - FILL_OR_WAVES) * LANES; base < count; base += COLS) {
-        uint32_t idx = 0, cand = 0;
-        if (lane < LANES && base + lane < count) { idx = wlist[base + lane]; cand = cands[idx]; }
-        uint32_t pre = (uint32_t)__popc(cand);
-        for (int d = 1; d < 64; d <<= 1) { const uint32_t up = (uint32_t)__shfl_up((int)pre, d); if ((int)lane >= d) pre += up; }
-        const uint32_t n_tok = lane_value(pre, 63);
-        for (uint32_t t0 = 0; t0 < n_tok; t0 += LANES) {
-            const uint32_t my = t0 + lane;
-            const uint32_t j = prefix_owner(pre, my);
-            uint32_t c = (uint32_t)__shfl((int)cand, (int)j);
-            const uint32_t end_j = (uint32_t)__shfl((int)pre, (int)j), w = (uint32_t)__shfl((int)idx, (int)j);
-            bool over = false;
-            uint32_t id = 0;
-            if (lane < LANES && my < n_tok) {
-                uint32_t skip = my - (end_j - (uint32_t)__popc(c));
-                while (skip--) c &= c - 1;                             // drop the lowest set bits that other lanes take
-                id = w * 32 + (uint32_t)__ffs(c) - 1;
-                const int res = recheck_lane(Z.Vd, T2, ctx.cls_words, C, id, st);
-                if (res == RECHECK_YES) atomicOr(out + w, 1u << (id & 31));
-                over = res == RECHECK_OVER;
+    uint32_t* cands = Z.F.cand_words + b * Z.Vd.W;
+    if (wave >= FILL_OR_WAVES) {
+        const DevTables T2 = uniform_load(Z.F.tables + q.tables_idx);
+        const DevCtx C = row_ctx(Z.F, q);
+        uint32_t large = 0, n_left = 0;
+        for (uint32_t base = (wave - FILL_OR_WAVES) * LANES; base < count; base += COLS) {
+            uint32_t idx = 0, cand = 0, left = 0;                      // left: the tokens of this lane's word that are for the end
+            if (lane < LANES && base + lane < count) { idx = wlist[base + lane]; cand = cands[idx]; }
+            uint32_t pre = (uint32_t)__popc(cand);
+            for (int d = 1; d < 64; d <<= 1) { const uint32_t up = (uint32_t)__shfl_up((int)pre, d); if ((int)lane >= d) pre += up; }
+            const uint32_t n_tok = lane_value(pre, 63);
+            for (uint32_t t0 = 0; t0 < n_tok; t0 += LANES) {
+                const uint32_t my = t0 + lane;
+                const uint32_t j = prefix_owner(pre, my);
+                uint32_t c = (uint32_t)__shfl((int)cand, (int)j);
+                const uint32_t end_j = (uint32_t)__shfl((int)pre, (int)j), w = (uint32_t)__shfl((int)idx, (int)j);
+                bool over = false;
+                uint32_t id = 0;
+                if (lane < LANES && my < n_tok) {
+                    uint32_t skip = my - (end_j - (uint32_t)__popc(c));
+                    while (skip--) c &= c - 1;                         // drop the lowest set bits that other lanes take
+                    id = w * 32 + (uint32_t)__ffs(c) - 1;
+                    const int res = recheck_lane(Z.Vd, T2, ctx.cls_words, C, id, st);
+                    if (res == RECHECK_YES) atomicOr(out + w, 1u << (id & 31));
+                    over = res == RECHECK_OVER;
+                }
+                unsigned long long m = __ballot(over);
+                if (!m) continue;
+                large += (uint32_t)__popcll(m);
+                if (Z.F.follows) {                                     // to k_recheck_slow, if its list has room
+                    uint32_t at = 0;
+                    if (lane == 0) at = atomicAdd(Z.S.count, (uint32_t)__popcll(m));
+                    at = lane_value(at, 0) + (uint32_t)__popcll(m & ((1ull << lane) - 1));
+                    const bool fits = over && at < Z.S.list_cap;
+                    if (fits) { Z.S.list[2 * at] = b; Z.S.list[2 * at + 1] = id; }
+                    m = __ballot(over && !fits);
+                }
+                n_left += (uint32_t)__popcll(m);
+                while (m) {
+                    const uint32_t k = next_bit(m), id2 = lane_value(id, k);
+                    if (Z.F.own_lanes) left |= lane == lane_value(j, k) ? 1u << (id2 & 31) : 0u;
+                    else if (lane == 0) leave_undecided(Z.S, b, id2);
+                }
             }
-            unsigned long long m = __ballot(over);
-            if (!m) continue;
-            large += (uint32_t)__popcll(m);
-            if (Z.F.follows) {                                           // to k_recheck_slow; if its list is full, to one lane with its lists in device memory
-                uint32_t at = 0;
-                if (lane == 0) at = atomicAdd(Z.S.count, (uint32_t)__popcll(m));
-                at = lane_value(at, 0) + (uint32_t)__popcll(m & ((1ull << lane) - 1));
-                const bool fits = over && at < Z.S.list_cap;
-                if (fits) { Z.S.list[2 * at] = b; Z.S.list[2 * at + 1] = id; }
-                m = __ballot(over && !fits);
-            }
-            while (m) {
-                const uint32_t id2 = lane_value(id, next_bit(m));
-                if (lane != 0) continue;
-                if (!Z.F.own_lanes) leave_undecided(Z.S, b, id2);
-                else if (recheck_large(Z.F, Z.Vd, Z.S, q, b, id2, b * Z.F.own_lanes + (wave - FILL_OR_WAVES))) atomicOr(out + (id2 >> 5), 1u << (id2 & 31));
-            }
+            if (Z.F.own_lanes && lane < LANES && base + lane < count) cands[idx] = left;
         }
+        if (lane == 0 && large) atomicAdd(Z.S.count + 3, large);
+        if (lane == 0 && n_left) atomicAdd(&n_over, n_left);
     }
-    if (lane == 0 && large) atomicAdd(Z.S.count + 3, large);
+    if (Z.F.own_lanes) {
+        // what is left: one lane of every wavefront that has a lane of the large-capacity scratch.  (A wavefront without one must
+        // not parse with its lists in device memory: there are more of them than lanes, and the next lane is the next row's.)
+        __syncthreads();
+        if (n_over != 0 && lane == 0 && wave < Z.F.own_lanes)
+            for (uint32_t k = wave; k < count; k += Z.F.own_lanes) {
+                const uint32_t w = wlist[k];
+                for (uint32_t m = cands[w]; m; m &= m - 1) {
+                    const uint32_t bit = (uint32_t)__ffs(m) - 1;
+                    if (recheck_large(Z.F, Z.Vd, Z.S, q, b, w * 32 + bit, b * Z.F.own_lanes + wave)) atomicOr(out + w, 1u << bit);
+                }
+            }
+    }
     stamp_end();
 }
 

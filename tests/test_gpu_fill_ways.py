@@ -118,6 +118,69 @@ def test_masks_with_large_tokens(xg, ebnf, n, shortest, longest, rows):
         check(lambda bm: xg.fill_next_token_bitmask_noalloc(few, bm.data_ptr(), W, _stream()), hist[:128])
 
 
+def _apart(toks, n):
+    """Tokens that are nowhere allowed (no rule reads a "#") behind every token of more than a byte: ids n apart."""
+    out = []
+    for t in toks:
+        out.append(t)
+        if len(t) > 1:
+            out += [b"#%d" % (len(out) + k) for k in range(n - 1)]
+    return out
+
+
+def _matchers(xg, cache, toks, hist):
+    at = {t: k for k, t in enumerate(toks)}
+    matchers = [xg.Matcher(cache) for _ in hist]
+    for m, s in zip(matchers, hist):
+        for c in s:
+            assert m.accept_token(at[bytes([c])])
+    return matchers
+
+
+# rows, uncertain tokens: with two, four and six lanes of the large-capacity scratch for each row, fewer than the row has
+# wavefronts that take candidate words (here more of them than 16 for each wavefront)
+@pytest.mark.parametrize("rows,n,apart", [(128, 600, 16), (64, 1100, 8), (42, 1700, 8)])
+def test_full_list_and_candidates_far_apart(xg, rows, n, apart):
+    """More large tokens than the overflow list of the call that allocates nothing holds, from words that all wavefronts have a share of."""
+    import torch
+    toks = _apart(_tokens(n, 17, 40), apart)
+    kinds = [b"(" * d + b"z" for d in (1, 8, 42, 43, 63, 64, 65, 118)]
+    starts = [kinds[k % len(kinds)] for k in range(rows)]
+    orc, va = oracle.Oracle(EBNF, "root"), oracle.VocabArrays(toks, 0, [0])
+    want = {s: oracle.pack_bitmask(orc.mask(s, va)) for s in kinds}
+    vocab = xg.Vocab(toks, 0, [0])
+    cache = xg.compile_grammar(vocab, EBNF, "root", stream=_stream(), context_depth=1, follow_filter=False)
+    matchers, W = _matchers(xg, cache, toks, starts), vocab.words
+    for _ in range(2):
+        bm = torch.full((rows, W), -1, dtype=torch.int32, device="cuda")
+        xg.fill_next_token_bitmask_noalloc(matchers, bm.data_ptr(), W, _stream())
+        assert xg.fill_last_status() == (rows * n, False) and rows * n > 1 << 16
+        got = bm.cpu().numpy()
+        for b, s in enumerate(starts):
+            assert np.array_equal(got[b], want[s]), (b, s, diff_words(got[b], want[s], toks))
+
+
+@pytest.mark.parametrize("rows", [1, 24, 300])
+def test_large_tokens_of_a_plane_built_by_the_fill(xg, rows):
+    """Nobody has counted the plane's uncertain tokens when the fill is launched: it has more than its list holds, and no launch behind."""
+    import torch
+    toks = _apart(_tokens(3000, 17, 40), 4)
+    kinds = [b"(" * d + b"z" for d in (2, 9, 30, 61)]
+    starts = [kinds[k % len(kinds)] for k in range(rows)]
+    orc, va = oracle.Oracle(EBNF, "root"), oracle.VocabArrays(toks, 0, [0])
+    want = {s: oracle.pack_bitmask(orc.mask(s, va)) for s in kinds}
+    vocab = xg.Vocab(toks, 0, [0])
+    cache = xg.compile_grammar(vocab, EBNF, "root", stream=_stream(), jit=True, jit_prebuild=0)
+    matchers, W = _matchers(xg, cache, toks, starts), vocab.words
+    for _ in range(2):                                               # while the plane is built, and when it is counted
+        bm = torch.full((rows, W), -1, dtype=torch.int32, device="cuda")
+        xg.fill_next_token_bitmask(matchers, bm.data_ptr(), W, _stream())
+        assert min(xg.fill_last_recheck_tokens(rows)) > 12 * 16 * 2 and not xg.fill_last_status()[1]
+        got = bm.cpu().numpy()
+        for b, s in enumerate(starts):
+            assert np.array_equal(got[b], want[s]), (b, s, diff_words(got[b], want[s], toks))
+
+
 # two rules for the same text: every uncertain token is a candidate twice
 TWICE = ('root ::= p | b\n'
          'p ::= "(" (p | b | x | y) ")"\n'
