@@ -2486,7 +2486,7 @@ int32_t xg2_apply_token_bitmask(void* logits_dev, int32_t dtype, int32_t B, int3
 
 int32_t xg2_batch_create(xg2_vocab* vocab, int32_t B, xg2_batch** out) {
     return guarded([&]() -> int32_t {
-        if (!vocab || !out || B <= 0 || B > (1 << 20)) return fail(XG2_EINVAL, "xg2_batch_create: bad argument");
+        if (!vocab || !out || B <= 0 || (uint32_t)B > kMostSlots) return fail(XG2_EINVAL, "xg2_batch_create: bad argument");
         vocab->p->ensure_device();
         auto b = std::make_unique<BatchImpl>();
         b->vocab = vocab->p;

@@ -212,6 +212,8 @@ struct CacheDev {
 // wait_off[(c * B + b) * (KH + 1) ..].  Accepting a token writes the other buffer and switches.  rows[b].pad[1] holds a
 // sticky error (a capacity was exceeded: the slot is unusable until it is reset), rows[b].tables_idx the slot's cache.
 constexpr uint32_t kSlotItems = 64, kSlotSets = 240, kSlotWaits = 512, kSlotPlanes = 32;   // capacities of a matcher slot
+constexpr uint32_t kMostSlots = 1u << 20;                    // slots of a batch
+static_assert(2ull * kMostSlots * kSlotWaits <= 0xFFFFFFFFull, "places of items, sets and wait entries in a batch's arrays are 32-bit numbers of entries");
 static_assert(kSlotItems <= kFillContextItems && kSlotSets <= kFillContextSets && kSlotWaits <= kFillContextWaits, "wavefronts can parse from every slot's context");
 static_assert(kSlotPlanes * kFillPlaneTokens <= kFillRowTokens, "a slot's row goes word by word only for a plane without a list");
 struct BatchDev {

@@ -765,8 +765,9 @@ __device__ __forceinline__ uint32_t count_below(unsigned long long m) { return _
 __device__ __forceinline__ unsigned long long lane_range(uint32_t first, uint32_t n) { return ((1ull << n) - 1) << first; }
 __device__ __forceinline__ uint32_t next_bit(unsigned long long& m) { const uint32_t j = (uint32_t)__ffsll((long long)m) - 1; m &= m - 1; return j; }
 
-// A word of a table, by its index; the byte offset is worked out in 32 bits (no table reaches 4 GB), so that the load takes it as
-// an offset to the uniform base address.
+// A word of a grammar's table, by its index; the byte offset is worked out in 32 bits, so that the load takes it as an offset to
+// the uniform base address.  (The largest, transitions of 2^18 states to 256 classes, is 256 MiB.)  For arrays that can reach 4 GiB
+// the base address has to be that of the part at hand.
 template <class P>
 __device__ __forceinline__ P tab_at(const P* base, uint32_t index) {
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -1704,8 +1705,9 @@ __global__ __launch_bounds__(64) void k_accept(AcceptArgs A) {
         TokenRecord rec = uniform_load(records + tok);
         CacheView C = cache_view(Cp);
         uint32_t cls_word = tab(Cp->cls_words + lane);
-        uint32_t my_item = tab_at(A.D.items, r.item_off + lane), my_off = tab_at(A.D.wait_off, r.waitoff_off + lane);
-        uint2 my_wait = tab_at(A.D.wait, r.wait_base + lane);
+        // (a whole batch's wait entries can reach 8 GiB)
+        uint32_t my_item = tab_at(A.D.items + r.item_off, lane), my_off = tab_at(A.D.wait_off + r.waitoff_off, lane);
+        uint2 my_wait = tab_at(A.D.wait + r.wait_base, lane);
         PIN("+s"(rec.head.x), "+s"(rec.n_bytes), "+s"(C.T.trans), "+s"(C.T.state), "+s"(C.T.exp_list), "+s"(C.T.n_classes), "+s"(C.T.sink), "+s"(C.plain_row), "+s"(C.pair_off), "+s"(C.pair_row), "+s"(C.site_of_off), "+s"(C.site_of), "+v"(cls_word), "+v"(my_item), "+v"(my_off),
             "+v"(my_wait.x), "+v"(my_wait.y));
         const uint32_t nb = r.pad[0] ^ 1u;
