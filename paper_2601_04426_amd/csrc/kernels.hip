@@ -961,7 +961,7 @@ __device__ __forceinline__ DevCtx row_ctx(const FillBatch& F, const FillRow& r) 
 
 // Candidate bits of one mask word of row b go to the scratch word; the word's index goes to the row's own
 // work list (one LDS atomic per wave with candidates: no atomics on device memory).
-__device__ __forceinline__ void list_candidates(const FillBatch& F, uint32_t* n_listed, uint32_t* n_cand, uint32_t cand, uint32_t row_base, uint32_t w) {
+__device__ __forceinline__ void list_candidates(const FillBatch& F, uint32_t* n_listed, uint32_t* n_cand, uint32_t cand, size_t row_base, uint32_t w) {
     const unsigned long long has = __ballot(cand != 0);
     if (has) {
         const uint32_t lane = threadIdx.x & 63;
@@ -1164,7 +1164,7 @@ __device__ __forceinline__ void fill_union_listing(const FillBatch& F, uint32_t 
             uint32_t cand[4], any = 0;
             _Pragma("unroll") for (int c = 0; c < 4; ++c) { cand[c] = v < n_vec ? (unc[s][c] & ~acc[s][c]) : 0u; any |= cand[c]; }
             if (__any(any != 0))                                    // candidates are few: most wavefronts have none
-                _Pragma("unroll") for (int c = 0; c < 4; ++c) list_candidates(F, n_listed, n_cand, cand[c], b * W, v * 4 + c);
+                _Pragma("unroll") for (int c = 0; c < 4; ++c) list_candidates(F, n_listed, n_cand, cand[c], (size_t)b * W, v * 4 + c);
             if (eos && eos_word / 4 == v) {
                 _Pragma("unroll") for (int c = 0; c < 4; ++c) if (eos_word % 4 == (uint32_t)c) acc[s][c] |= eos_bit;
             }
@@ -1369,8 +1369,8 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVE
     const FillArgs Z = args_again<FillArgs>();
     const FillRow q = uniform_load(Z.F.rows + b);
     const uint32_t count = n_listed;
-    const uint32_t* wlist = Z.F.work_list + b * Z.Vd.W;
-    uint32_t* cands = Z.F.cand_words + b * Z.Vd.W;
+    const uint32_t* wlist = Z.F.work_list + (size_t)b * Z.Vd.W;
+    uint32_t* cands = Z.F.cand_words + (size_t)b * Z.Vd.W;
     if (wave >= FILL_OR_WAVES) {
         const DevTables T2 = uniform_load(Z.F.tables + q.tables_idx);
         const DevCtx C = row_ctx(Z.F, q);
