@@ -1364,8 +1364,10 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVE
         return;
     }
     if (threadIdx.x == 0) F.row_count[b] = n_cand;
-    // the sequential way: each wave of the re-check team takes as many listed words at a time as it has lanes at work
-    // and spreads their set bits densely over those lanes
+    // the sequential way: each wave of the re-check team takes its share of the listed words, at a time at most as many as it has lanes
+    // at work, and spreads their set bits densely over those lanes.  (As many words as lanes, however few there are, leave all of them
+    // to the first waves: 64 / 100 / 300 / 600 neighbouring tokens of up to 14 bytes, 1 row, 120 / 186 / 541 / 880 us against 73 / 68 /
+    // 94 / 170; 512 rows, twelve wavefronts, 142 / 236 / 661 / 1,127 against 92 / 91 / 186 / 296.)
     const FillArgs Z = args_again<FillArgs>();
     const FillRow q = uniform_load(Z.F.rows + b);
     const uint32_t count = n_listed;
@@ -1375,9 +1377,12 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVE
         const DevTables T2 = uniform_load(Z.F.tables + q.tables_idx);
         const DevCtx C = row_ctx(Z.F, q);
         uint32_t large = 0, n_left = 0;
-        for (uint32_t base = (wave - FILL_OR_WAVES) * LANES; base < count; base += COLS) {
+        constexpr uint32_t TEAM = WAVES - FILL_OR_WAVES;
+        const uint32_t n_words = min(LANES, (count + TEAM - 1) / TEAM);
+        for (uint32_t base = (wave - FILL_OR_WAVES) * n_words; base < count; base += TEAM * n_words) {
             uint32_t idx = 0, cand = 0, left = 0;                      // left: the tokens of this lane's word that are for the end
-            if (lane < LANES && base + lane < count) { idx = wlist[base + lane]; cand = cands[idx]; }
+            const bool has_word = lane < n_words && base + lane < count;
+            if (has_word) { idx = wlist[base + lane]; cand = cands[idx]; }
             uint32_t pre = (uint32_t)__popc(cand);
             for (int d = 1; d < 64; d <<= 1) { const uint32_t up = (uint32_t)__shfl_up((int)pre, d); if ((int)lane >= d) pre += up; }
             const uint32_t n_tok = lane_value(pre, 63);
@@ -1414,7 +1419,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVE
                     else if (lane == 0) leave_undecided(Z.S, b, id2);
                 }
             }
-            if (Z.F.own_lanes && lane < LANES && base + lane < count) cands[idx] = left;
+            if (Z.F.own_lanes && has_word) cands[idx] = left;
         }
         if (lane == 0 && large) atomicAdd(Z.S.count + 3, large);
         if (lane == 0 && n_left) atomicAdd(&n_over, n_left);
