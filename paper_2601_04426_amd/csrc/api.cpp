@@ -1196,7 +1196,7 @@ int32_t build_planes(CacheImpl& cache, const std::vector<int32_t>& todo, hipStre
     size_t n_chunks = 0;
     size_t n_full = 0;                                           // chunks, if all were of kBuildChunk ranks
     for (const uint4& r : ranges) if (!(r.w & kChunkDerive)) n_full += (r.z - r.y + kBuildChunk - 1) / kBuildChunk;
-    const uint32_t ranks = build_chunk(n_full);
+    const uint32_t ranks = build_chunk(n_full, wave_slots());
     for (uint32_t pass_heavy : {kChunkHeavy, 0u})
         for (const uint4& r : ranges) {
             if ((r.w & kChunkHeavy) != pass_heavy) continue;

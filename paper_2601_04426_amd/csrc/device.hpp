@@ -54,14 +54,15 @@ struct DevVocab {                        // byte-sorted vocabulary in HBM
 #define XG2_BUILD_CHUNK 128
 #endif
 constexpr uint32_t kBuildChunk = XG2_BUILD_CHUNK;
-// Ranks of a chunk, for a launch that has n_full chunks of kBuildChunk.  Where the device holds all of them at once the launch lasts
-// as long as its slowest workgroup, and one of half a chunk goes through each phase once (64 tokens, a wavefront's lanes) and not
-// twice.  With more, workgroups take several in turn, and a chunk's fixed costs and part-filled batches count.  k_build, us, 128 / 64
+// Ranks of a chunk, for a launch that has n_full chunks of kBuildChunk.  In a small launch workgroups take one or two chunks and it
+// lasts as long as its slowest, and a chunk of half the size goes through each phase once (64 tokens, a wavefront's lanes) and not
+// twice.  In a large one a chunk's fixed costs and part-filled batches count.  The line is the number of wavefront slots of the
+// device (wave_slots), where the measured times change sides.  k_build, us, 128 / 64
 // ranks: 16 - 740 chunks of a just-in-time build 29.7 / 21.7 on average, 1,901 chunks 53.5 / 44.3, 3,509 67.7 / 48.6, 6,248 64.9 / 49.4,
 // 6,506 64.3 / 52.6, but 9,892 82.7 / 86.6, 9,963 66.0 / 79.1, 13,000 123.7 / 133.8 (17,000 - 30,000: 6 - 14 % less again).  32 ranks: no
 // gain just in time (22.0), 77.6 at 6,506.
-constexpr uint32_t kBuildSlots = 256 * 32;                   // wavefronts that the device holds
-constexpr uint32_t build_chunk(size_t n_full) { return n_full <= kBuildSlots ? 64 : kBuildChunk; }
+uint32_t wave_slots();                                       // wavefronts that the device has slots for: 32 a compute unit
+constexpr uint32_t build_chunk(size_t n_full, uint32_t slots) { return n_full <= slots ? 64 : kBuildChunk; }
 static_assert(kBuildChunk >= 64, "build_chunk makes chunks smaller, not larger");
 static_assert(kBuildChunk <= 256, "the deferred list is sized for kBuildChunk and holds one-byte offsets");
 struct BuildPlan {

@@ -1914,19 +1914,23 @@ void launch_stage(void* dst_dev, const void* src_host_mapped, size_t bytes, cons
                        nb_up, Z, nb_zero, range_a_host_mapped, range_b_host_mapped, first_host_mapped, n_ranges, chunk_dev);
 }
 
+uint32_t wave_slots() {
+    static const uint32_t n = [] {
+        int dev = 0, cus = 0;
+        if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
+            cus = 256;
+        return (uint32_t)cus * 32u;                                 // 4 SIMDs of 8 wave slots each
+    }();
+    return n;
+}
+
 void launch_build(const DevTables& T, const DevVocab& Vd, BuildPlan P, const SlowScratch& S, hipStream_t stream) {
     if (P.n_chunks == 0) return;
     // Short item lists let a compute unit hold more workgroups, which is what hides the latency of the automaton
     // walks' dependent table loads when there is far more work than the device holds at once; long ones spare the
     // tokens that need them a second run at half width, which is what counts when the launch is a few chunks per
     // wave slot and lasts as long as its slowest workgroup.
-    static const uint32_t wave_slots = [] {
-        int dev = 0, cus = 0;
-        if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
-            cus = 256;
-        return (uint32_t)cus * 32u;                                 // 4 SIMDs of 8 wave slots each
-    }();
-    P.large_lists = P.n_chunks <= 4 * wave_slots ? 1u : 0u;
+    P.large_lists = P.n_chunks <= 4 * wave_slots() ? 1u : 0u;
 #ifdef XG2_BUILD_FORCE_LISTS
     P.large_lists = XG2_BUILD_FORCE_LISTS;
 #endif
@@ -1937,7 +1941,7 @@ void launch_build(const DevTables& T, const DevVocab& Vd, BuildPlan P, const Slo
     // into shares of about a dozen chunks, small enough for the hardware to even out the load as workgroups end and
     // large enough for a workgroup's tokens for the follow-language run to fill whole batches (measured: 8,192 for the
     // 10,063 chunks of the repetition workload, 65,536 for the 856,956 of the dispatch workload).
-    uint32_t grid = std::min(P.n_chunks, std::max(wave_slots, std::min(P.n_chunks / 12, 8 * wave_slots)));
+    uint32_t grid = std::min(P.n_chunks, std::max(wave_slots(), std::min(P.n_chunks / 12, 8 * wave_slots())));
 #ifdef XG2_TUNE
     if (const char* e = getenv("XG2_BUILD_GRID")) grid = std::min<uint32_t>(P.n_chunks, (uint32_t)atoi(e));
     if (getenv("XG2_DEBUG_PLAN")) fprintf(stderr, "launch: chunks %u grid %u lds %u\n", P.n_chunks, grid, lds_bytes);
