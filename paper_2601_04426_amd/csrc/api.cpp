@@ -670,7 +670,9 @@ inline void share_out(FillBatch& F, uint32_t n_lanes, const FillLoad& load) {
     F.own_lanes = per < 2 ? 0u : std::min(per, kFillOwnLanes);
     F.follows = F.own_lanes == 0 || load.deep || load.plane_tokens > kFillPlaneTokens || load.row_tokens > kFillRowTokens
                 || (spread && std::max(load.plane_tokens, load.row_tokens) > kFillSpreadTokens);
-    F.row_waves = fill_row_waves(F.B, std::max(load.plane_tokens, load.row_tokens));
+    // slots' rows are not known: the largest planes of tool sets and JSON schemas have about two thirds of a row's candidates
+    const uint32_t candidates = load.row_tokens ? load.row_tokens : load.plane_tokens + load.plane_tokens / 2;
+    F.row_waves = fill_row_waves(F.B, wave_slots() / 32, std::max(load.plane_tokens, load.row_tokens), candidates);
     F.wave_tokens = spread ? kFillSpreadTokens : kFillWaveTokens * F.row_waves;
     F.leave_above = spread && F.follows ? kFillSpreadTokens : 0xFFFFFFFFu;
 }

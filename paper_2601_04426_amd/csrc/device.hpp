@@ -175,10 +175,15 @@ struct FillBatch {
 // What k_fill handles how (the host decides by the same numbers whether k_recheck_slow follows).
 constexpr uint32_t kFillLaneItems = 8, kFillLaneWaits = 12, kFillLaneBytes = 16;    // lists and bytes of a lane that parses a token by itself
 constexpr uint32_t kFillWaveTokens = 4;                      // FillBatch::wave_tokens for each wavefront of the workgroup, as a rule
-// Wavefronts of a row's workgroup, in a batch of `rows` rows that have up to `tokens` uncertain tokens (k_fill has the figures).
+// Wavefronts of a row's workgroup, in a batch of `rows` rows on a device of `units` compute units: some frontier plane has `tokens`
+// uncertain tokens, and rows have up to about `candidates` in all (k_fill has the figures).
 constexpr uint32_t kFillMostWaves = 16, kFillOwnLanes = 6;
-constexpr uint32_t kComputeUnits = 256;
-constexpr uint32_t fill_row_waves(uint32_t rows, uint32_t tokens) { return rows <= kComputeUnits ? 16 : tokens > 2 ? 12 : 6; }
+constexpr uint32_t fill_row_waves(uint32_t rows, uint32_t units, uint32_t tokens, uint32_t candidates) {
+    if (rows <= units) return 16;
+    if (candidates > 64) return 12;
+    if (rows > 4 * units || candidates > 12 * kFillWaveTokens) return 6;
+    return tokens > (rows <= 2 * units ? 2 : 6 * kFillWaveTokens) ? 12 : 6;
+}
 constexpr uint32_t kFillSpreadRows = 192, kFillSpreadTokens = 18;    // batches of up to that many rows, where tokens may be long in numbers: wave_tokens, leave_above
 constexpr uint32_t kFillPlaneTokens = kUncListWords - 1;     // with more uncertain tokens in a frontier plane (than its list holds), or in a
 constexpr uint32_t kFillRowTokens = 2048;                    //   frontier (than any slot's can have otherwise), a row is worked through word by word

@@ -911,12 +911,20 @@ struct WaveScan {
 // Wavefronts take as many at a time as the row has, lanes any number in one round.  Which is less depends on the grammar: six
 // wavefronts / lanes from 19 on, two fills and a step, 37 rows of a JSON schema 27 / 32 us, 64 rows of records 72 / 67; 24 candidates
 // deep in nested parentheses, 1 row, 49 / 39, and of 20 - 40 bytes 129 / 95.
-// How many wavefronts a row's workgroup has (fill_row_waves): six where the device is full of rows anyway and no plane has more
-// than two uncertain tokens.  A compute unit that has one row has room for sixteen; where rows have candidates, twelve also pay with
-// more rows than compute units.  Six / twelve / sixteen, us, rows with up to 47 candidates: 64 rows of records 23.8 / 17.1 / 15.8,
-// 256 rows of tools 20.9 / 16.5 / 15.0; 512 rows of tools 20.7 / 18.9 / 18.7, of records 26.0 / 23.5 / 24.8; 1,024 rows of tools
-// 23.5 / 22.5 / 26.4, of records 30.4 / 30.4 / 36.8.  No candidates: 1 row 4.3 with any, 512 rows of JSON 5.7 / 5.9 / 8.0, 1,024 rows
-// 8.4 / 9.4 / 14.
+// How many wavefronts a row's workgroup has (fill_row_waves).  A compute unit that has one row has room for sixteen: 64 rows of
+// records with up to 47 candidates 23.8 / 17.1 / 15.8 us (six / twelve / sixteen wavefronts), 256 rows of tools 20.9 / 16.5 / 15.0.
+// With more rows than compute units, six / twelve, us, grammars and vocabularies of the decoding cases:
+//   25 - 48 candidates are a lane's each with six and a wavefront's each with twelve, of which the device holds two rows a compute
+//   unit and not four.  300 / 512 / 1,024 / 2,048 rows of tools 18.9 / 20.8 / 24.9 / 33.9 against 16.4 / 16.7 / 21.6 / 34.9, of a
+//   nested schema 20.3 / 20.6 / 24.8 / 31.6 against 18.1 / 18.4 / 24.7 / 34.5, of records 24.2 / 24.9 / 28.2 / 37.0 against 18.6 /
+//   20.1 / 24.9 / 37.6: twelve up to four rows a compute unit.
+//   Up to 24 are a wavefront's each with either.  300 / 512 / 600 / 1,024 / 2,048 rows of records (19) 13.5 / 14.6 / 14.5 / 18.3 / 28.1
+//   against 13.6 / 14.5 / 16.6 / 21.1 / 33.2, of a nested schema (20) 14.2 / 16.4 / - / 17.4 / 22.3 against 12.6 / 13.5 / - / 17.5 /
+//   23.9; none at all, 512 / 1,024 rows, 6.0 / 8.6 against 6.3 / 9.8: twelve up to two rows a compute unit, if there are any.
+//   49 - 64 are a lane's each with either, in one round.  300 / 512 / 1,024 / 2,048 rows of repetitions (59) 26.4 / 29.0 / 32.5 / 47.9
+//   against 28.1 / 32.0 / 37.2 / 58.9: six.
+//   More take a second round with six and, up to 128, not with twelve.  Nested parentheses (80), 300 / 1,024 / 2,048 rows, 105.9 / 197.6 /
+//   310.7 against 73.0 / 134.4 / 250.5; 600 word by word, 512 / 1,024 rows, 408 / 774 against 296 / 570: twelve.
 // Everything that is asked for before the plan is known (the context, the tables, the first planes' lists, the first block of the
 // union) used to wait for it: 0.5 - 1.5 us of every row.
 // A row with a frontier plane whose uncertain tokens do not fit its list (or with more candidates than the LDS list

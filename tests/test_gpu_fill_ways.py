@@ -189,12 +189,13 @@ TWICE = ('root ::= p | b\n'
          'y ::= [a-z]+ "."?\n')
 
 
-@pytest.mark.parametrize("rows", [1, 256, 257, 600])                  # a workgroup of 16, 16, and of 12 wavefronts, or 6 with two tokens
-@pytest.mark.parametrize("ebnf,n", [(EBNF, 2), (EBNF, 3), (EBNF, 48), (EBNF, 49), (EBNF, 63),
-                                    (TWICE, 24), (TWICE, 25), (TWICE, 32), (TWICE, 33), (TWICE, 60)],
+@pytest.mark.parametrize("rows", [1, 256, 257, 512, 513, 600, 1024, 1025])  # a workgroup of 16 wavefronts, or of 12 or 6
+@pytest.mark.parametrize("ebnf,n", [(EBNF, 2), (EBNF, 3), (EBNF, 24), (EBNF, 25), (EBNF, 32), (EBNF, 33), (EBNF, 42), (EBNF, 43), (EBNF, 48), (EBNF, 49),
+                                    (EBNF, 63), (TWICE, 12), (TWICE, 13), (TWICE, 24), (TWICE, 25), (TWICE, 32), (TWICE, 33), (TWICE, 43), (TWICE, 60)],
                          ids=lambda v: "twice" if v is TWICE else "nest" if v is EBNF else str(v))
 def test_masks_by_size_of_the_workgroup(xg, ebnf, n, rows):
-    """Up to four candidates for each wavefront of a row, and more: 24, 48, 64 and the next of each, in a row's one plane or in two."""
+    """Up to four candidates for each wavefront of a row, and more: 24, 48, 64 and the next of each, in a row's one plane or in two;
+    planes on both sides of the lines that decide on the number of wavefronts (2, 24, 32 and 42 tokens)."""
     import torch
     toks = _tokens(n, 3, 14)
     kinds = [b"(", b"(z", b"([z", b"((((b", b"(" * 12 + b"a"]
