@@ -658,23 +658,20 @@ struct MatcherImpl {
 
 // What the rows of a fill may ask of k_fill: the most uncertain tokens of a frontier plane and (if they are known) of a whole
 // frontier, whether some context is too large to parse from in a row's workgroup, and whether many of a row's uncertain tokens
-// may be longer than a lane takes: the vocabulary has such tokens, and no follow language inside a parent filters them.
+// may be longer than a wavefront takes: the vocabulary has such tokens, and no follow language inside a parent filters them.
 struct FillLoad { uint32_t plane_tokens = 0, row_tokens = 0; bool deep = false, long_tokens = false; };
 // How many wavefronts a row's workgroup has, how many lanes of the large-capacity scratch each row of a fill gets for itself (a
-// workgroup has six wavefronts at least), and whether k_recheck_slow is launched behind k_fill.  That costs every call 2.5 - 4 us, so
+// workgroup has six wavefronts at least), and whether k_recheck_slow is launched behind k_fill.  That costs every call 2 - 4 us, so
 // it is done only where there are too few lanes, where a row goes word by word or its context is too large, or where the batch is small
 // enough that a row's many long tokens are better spread over the device (k_fill has the figures).
 inline void share_out(FillBatch& F, uint32_t n_lanes, const FillLoad& load) {
-    const uint32_t per = n_lanes / F.B;
-    const bool spread = F.B <= kFillSpreadRows && load.long_tokens;
+    const uint32_t per = n_lanes / F.B, tokens = std::max(load.plane_tokens, load.row_tokens);
     F.own_lanes = per < 2 ? 0u : std::min(per, kFillOwnLanes);
     F.follows = F.own_lanes == 0 || load.deep || load.plane_tokens > kFillPlaneTokens || load.row_tokens > kFillRowTokens
-                || (spread && std::max(load.plane_tokens, load.row_tokens) > kFillSpreadTokens);
+                || (load.long_tokens && F.B <= kFillSpreadRows && tokens > kFillSpreadTokens);
     // slots' rows are not known: the largest planes of tool sets and JSON schemas have about two thirds of a row's candidates
     const uint32_t candidates = load.row_tokens ? load.row_tokens : load.plane_tokens + load.plane_tokens / 2;
-    F.row_waves = fill_row_waves(F.B, wave_slots() / 32, std::max(load.plane_tokens, load.row_tokens), candidates);
-    F.wave_tokens = spread ? kFillSpreadTokens : kFillWaveTokens * F.row_waves;
-    F.leave_above = spread && F.follows ? kFillSpreadTokens : 0xFFFFFFFFu;
+    F.row_waves = fill_row_waves(F.B, wave_slots() / 32, tokens, candidates);
 }
 
 // ---- fill workspace: pinned staging ring + device mirror ---------------------------------------------------
@@ -2234,7 +2231,7 @@ int32_t fill_common(xg2_matcher* const* matchers, int32_t B, int32_t* bitmask_de
             FillRow& r = rows[(size_t)b];
             std::memset(&r, 0, sizeof(r));
             auto ti = table_idx.find(M.cache.get());
-            if (ti == table_idx.end()) { ti = table_idx.emplace(M.cache.get(), (uint32_t)tables.size()).first; tables.push_back(M.cache->dt); load.long_tokens |= V.max_len > kFillLaneBytes && !M.cache->filtered(); }
+            if (ti == table_idx.end()) { ti = table_idx.emplace(M.cache.get(), (uint32_t)tables.size()).first; tables.push_back(M.cache->dt); load.long_tokens |= V.max_len > kFillWaveBytes && !M.cache->filtered(); }
             r.tables_idx = ti->second;
             r.front_off = (uint32_t)front.size();
             r.item_off = (uint32_t)items.size();
@@ -2538,7 +2535,7 @@ int32_t xg2_batch_assign(xg2_batch* batch, const int32_t* rows_host, int32_t n, 
         if (ci == Bt.caches.size()) {
             if (ci >= BatchImpl::kMaxCaches) return fail(XG2_EOVERFLOW, "xg2_batch_assign: too many different caches in one batch");
             Bt.caches.push_back(cache->p);                      // kept alive while the batch lives
-            Bt.load.long_tokens |= Bt.vocab->max_len > kFillLaneBytes && !cache->p->filtered();
+            Bt.load.long_tokens |= Bt.vocab->max_len > kFillWaveBytes && !cache->p->filtered();
             Bt.load.plane_tokens = std::max(Bt.load.plane_tokens, od.most_uncertain);
             HIP_CHECK(hipMemcpyAsync(Bt.caches_dev.p + ci, &od.cd, sizeof(CacheDev), hipMemcpyHostToDevice, stream));
             HIP_CHECK(hipMemcpyAsync(Bt.tables_dev.p + ci, &od.cd.T, sizeof(DevTables), hipMemcpyHostToDevice, stream));

@@ -166,15 +166,14 @@ struct FillBatch {
     uint32_t follows;                    // k_recheck_slow is launched behind it and takes what the rows leave on the overflow list (always
                                          // if own_lanes is 0)
     uint32_t row_waves;                  // wavefronts of a row's workgroup: fill_row_waves()
-    uint32_t wave_tokens;                // up to that many candidates of a row get a wavefront each
-    uint32_t leave_above;                // a row with more tokens than that beyond a lane's lists leaves them to k_recheck_slow
     uint64_t* stamps;                    // if not null: when the call's work started and ended, on the device's constant-rate clock:
                                          // [0] the upload kernel's start; row_waves + 1 words for each row (start, end of each of
                                          // its wavefronts); the end of each workgroup of k_recheck_slow
 };
 // What k_fill handles how (the host decides by the same numbers whether k_recheck_slow follows).
-constexpr uint32_t kFillLaneItems = 8, kFillLaneWaits = 12, kFillLaneBytes = 16;    // lists and bytes of a lane that parses a token by itself
-constexpr uint32_t kFillWaveTokens = 4;                      // FillBatch::wave_tokens for each wavefront of the workgroup, as a rule
+constexpr uint32_t kFillLaneItems = 8, kFillLaneWaits = 12;  // lists of a lane that parses a token (of up to 16 bytes) by itself
+constexpr uint32_t kFillWaveTokens = 4;                      // up to that many candidates for each wavefront of the workgroup get a wavefront each
+constexpr uint32_t kFillWaveBytes = 64;                      // bytes of a token that a wavefront parses
 // Wavefronts of a row's workgroup, in a batch of `rows` rows on a device of `units` compute units: some frontier plane has `tokens`
 // uncertain tokens, and rows have up to about `candidates` in all (k_fill has the figures).
 constexpr uint32_t kFillMostWaves = 16, kFillOwnLanes = 6;
@@ -184,7 +183,7 @@ constexpr uint32_t fill_row_waves(uint32_t rows, uint32_t units, uint32_t tokens
     if (rows > 4 * units || candidates > 12 * kFillWaveTokens) return 6;
     return tokens > (rows <= 2 * units ? 2 : 6 * kFillWaveTokens) ? 12 : 6;
 }
-constexpr uint32_t kFillSpreadRows = 192, kFillSpreadTokens = 18;    // batches of up to that many rows, where tokens may be long in numbers: wave_tokens, leave_above
+constexpr uint32_t kFillSpreadRows = 192, kFillSpreadTokens = 18;    // up to that many rows with more tokens than that, which may be longer than a wavefront takes
 constexpr uint32_t kFillPlaneTokens = kUncListWords - 1;     // with more uncertain tokens in a frontier plane (than its list holds), or in a
 constexpr uint32_t kFillRowTokens = 2048;                    //   frontier (than any slot's can have otherwise), a row is worked through word by word
 constexpr uint32_t kFillContextItems = 64, kFillContextSets = 240, kFillContextWaits = 512;   // contexts that wavefronts parse from (every slot's)

@@ -906,7 +906,7 @@ struct WaveScan {
 // table loads) hides behind the streaming and the other way round.  A token that another frontier plane accepts is in
 // the mask anyway and is not parsed: its bit is looked up in the accepted rows, without waiting for the union.
 // Most rows have no candidate and a few have a handful, but the launch lasts as long as its slowest row.  A row with few
-// candidates (wave_tokens) gives each a wavefront (WaveScan: a byte costs about one gather, where a lane of its own
+// candidates (kFillWaveTokens) gives each a wavefront (WaveScan: a byte costs about one gather, where a lane of its own
 // takes several dependent accesses), the union team joining in when it is done; a row with more gives each a lane.
 // Wavefronts take as many at a time as the row has, lanes any number in one round.  Which is less depends on the grammar: six
 // wavefronts / lanes from 19 on, two fills and a step, 37 rows of a JSON schema 27 / 32 us, 64 rows of records 72 / 67; 24 candidates
@@ -930,15 +930,16 @@ struct WaveScan {
 // A row with a frontier plane whose uncertain tokens do not fit its list (or with more candidates than the LDS list
 // holds) takes the sequential way: the union team also reads the uncertain rows and lists the words with candidates,
 // the re-check team starts when the union is done, a lane each.
-// A token that outgrows a lane's lists (or 16 bytes) goes to a wavefront, one that outgrows that too to lists in device memory,
-// all in the row's own workgroup (own_lanes): a second launch for the few such tokens cost 2.5 - 4 us on every call.
-// A workgroup has six wavefronts, though, and k_recheck_slow 4,096 lanes over the device.  Where rows of a small batch may have
-// many tokens of more than 16 bytes the host launches it behind this kernel, and a row with more than leave_above of them leaves
-// them to it.  Tokens of 20 - 40 bytes, us a call, all by wavefronts / by the launch behind: 63 a row, 1 row
-// 325 / 107, 256 rows 329 / 421, 1,024 rows 685 / 1,611 (six wavefronts a row against 4,096 lanes in all), so the line lies at
-// kFillSpreadRows.  Short tokens whose item sets outgrow a lane are the wavefronts' in any batch (expansions of 25 items, 33
-// tokens a row, 1 row: 64 / 128).  The sequential way, which has no bound on its tokens, leaves all of them to that launch (100
-// long ones a row, 1 row: 112 us; one lane of the workgroup after another took 5,433).
+// A token that outgrows a lane's lists (or 16 bytes) goes to a wavefront, one that outgrows that too (or 64 bytes) to lists in device
+// memory, in the row's own workgroup (own_lanes, up to six) or in the launch behind, which has 4,096 lanes over the device but costs
+// every call 2 - 4 us.  Nested parentheses, us a call, without / with that launch: 63 tokens of 65 - 80 bytes, 1 / 64 / 192 rows
+// 1,865 / 2,138 / 2,142 against 195 / 199 / 574; of 9 - 80 bytes 797 / 844 / 850 against 303 / 316 / 320; 18 of 3 - 14 bytes
+// 15.9 / 18.4 / 20.0 against 18.3 / 20.5 / 22.3.  So where rows of a small batch may have more than kFillSpreadTokens tokens and the
+// vocabulary has such long ones the host launches it.  What a wavefront can take is the wavefronts' in any case: 63 tokens of 20 - 40 bytes
+// take 126 / 131 / 137 us that way and 104 / 110 / 315 in the launch behind, 24 of them 52 / 55 / 58 and 92 / 99 / 190; short tokens whose
+// item sets outgrow a lane 64 and 128 (33 a row, 1 row, expansions of 25 items; six wavefronts a row).  The sequential way, which has no
+// bound on its tokens, leaves all that a lane cannot take to that launch (100 of 20 - 40 bytes, 1 row: 112 us; one lane of the workgroup
+// after another took 5,433).
 // Four wavefronts stream, the others re-check: two with half of their lanes at work (measured: fewer lanes per wavefront or another
 // split of the six gain nothing), more with a quarter.
 constexpr int FILL_OR_WAVES = 4, FILL_OR_THREADS = 64 * FILL_OR_WAVES;
@@ -955,7 +956,7 @@ constexpr uint32_t FILL_SPARSE_CAP = kFillRowTokens;   // candidates of a row th
 // What became of a candidate: the token, or FILL_NONE if it was rejected; FILL_OVER: it did not fit the lists tried so far;
 // FILL_LARGE: it did not fit a lane's, and a wavefront has decided it.
 constexpr uint32_t FILL_OVER = 0x80000000u, FILL_LARGE = 0x40000000u, FILL_NONE = 0x3FFFFFFFu;
-constexpr uint32_t FILL_CTX_WAITS = kFillContextWaits, FILL_CTX_SETS = kFillContextSets, FILL_OWN_WAITS = 128, FILL_WAVE_BYTES = 64;   // what a wavefront's parse has room for
+constexpr uint32_t FILL_CTX_WAITS = kFillContextWaits, FILL_CTX_SETS = kFillContextSets, FILL_OWN_WAITS = 128, FILL_WAVE_BYTES = kFillWaveBytes;   // what a wavefront's parse has room for
 
 __device__ __forceinline__ DevCtx row_ctx(const FillBatch& F, const FillRow& r) {
     DevCtx C;
@@ -1001,7 +1002,6 @@ __device__ __forceinline__ int recheck_lane(const DevVocab& Vd, const DevTables&
 // A row's context in LDS for the wavefronts that parse from it, and each wavefront's room for what its token adds.
 struct FillCtx { uint2 wait[FILL_CTX_WAITS]; uint32_t off[FILL_CTX_SETS + 1]; uint32_t cls_words[64]; };
 struct WaveToken { uint32_t words[4], id, off, n_bytes; };           // a token that a wavefront parses: its first 16 bytes, ...
-constexpr uint32_t FILL_WAVE_MOST = 64;
 struct FillOwn { uint2 wait[FILL_OWN_WAITS]; uint32_t off[FILL_WAVE_BYTES + 1]; };
 __device__ __forceinline__ void wave_sync() {                       // orders a wavefront's LDS traffic (which completes in order) for the compiler
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -1189,13 +1189,15 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVE
     const DevVocab& Vd = A.Vd;
     using Team = FillTeam<WAVES>;
     constexpr uint32_t THREADS = Team::THREADS, LANES = Team::LANES, COLS = Team::COLS;
+    constexpr uint32_t FILL_WAVE_TOKENS = kFillWaveTokens * WAVES;
+    static_assert(FILL_WAVE_TOKENS <= 64, "a row's candidates lie across the lanes");
     static_assert(WAVES >= kFillOwnLanes, "each of a row's own lanes of the large-capacity scratch is a wavefront's");
     __shared__ uint32_t lds_store[Team::Store::SLOTS * COLS];
     __shared__ uint32_t sh_surv[FILL_SPARSE_CAP];
     __shared__ FillCtx ctx;
     __shared__ FillOwn sh_own[WAVES];
     __shared__ uint32_t n_listed, n_cand, n_over, next_token, n_to_parse;
-    __shared__ WaveToken sh_tok[FILL_WAVE_MOST];
+    __shared__ WaveToken sh_tok[FILL_WAVE_TOKENS];
     const uint32_t b = blockIdx.x, lane = threadIdx.x & 63, wave = same_in_all(threadIdx.x >> 6);
     if (F.stamps && threadIdx.x == 0) F.stamps[kStampsRows + (WAVES + 1) * b] = wall_clock64();
     auto stamp_end = [&]() { if (F.stamps && lane == 0) F.stamps[kStampsRows + (WAVES + 1) * b + 1 + wave] = wall_clock64(); };
@@ -1240,7 +1242,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVE
         total = lane_value(incl, 63);
     }
     const bool listed_way = live && front_n != 0 && (front_n > 64 || __any(no_list) || total > FILL_SPARSE_CAP);
-    const bool wave_way = ctx_fits && !listed_way && total <= F.wave_tokens && total <= FILL_WAVE_MOST;
+    const bool wave_way = ctx_fits && !listed_way && total <= FILL_WAVE_TOKENS;
     if (wave_way && total != 0 && wave == FILL_OR_WAVES) {
         // every candidate at once, one a lane: its token, its bytes, whether a frontier plane accepts it (then it is in the mask already)
         const uint32_t k = prefix_owner(incl, lane);
@@ -1309,7 +1311,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVE
     bool waves_parse = wave_way && total != 0;
     if (!listed_way && total != 0 && !wave_way) {                   // (the same for the whole row)
         __syncthreads();
-        waves_parse = ctx_fits && n_over != 0 && n_over <= F.leave_above;
+        waves_parse = ctx_fits && n_over != 0;
     }
     if (waves_parse) {
         // a wavefront per candidate, the union team joining in when its row is stored; or per token that did not fit a lane's lists

@@ -47,9 +47,9 @@ def _tokens(n_uncertain, lengths):
 
 
 @pytest.mark.parametrize("n_uncertain,lengths", [
-    (1, (4,)), (24, (8, 16)), (25, (8, 16)),              # the most that get a wavefront each, and one more
+    (1, (4,)), (24, (8, 16)), (25, (8, 16)),              # a wavefront each, up to four in turn
     (24, (15, 16, 17, 48, 63, 64, 65, 70)),               # token lengths: a vector load, a wavefront's bytes, beyond
-    (25, (15, 16, 17, 48, 63, 64, 65, 70)),
+    (25, (15, 16, 17, 48, 63, 64, 65, 70)), (48, (15, 16, 17, 48, 63, 64, 65, 70)), (49, (15, 16, 17, 48, 63, 64, 65, 70)),
     (63, (12,)), (64, (12, 20)),                          # the length of a plane's list, and one more
     (600, (9, 12)),                                       # more than the row's list
 ])
