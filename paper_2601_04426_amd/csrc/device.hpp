@@ -174,18 +174,19 @@ struct FillBatch {
 constexpr uint32_t kFillLaneItems = 8, kFillLaneWaits = 12;  // lists of a lane that parses a token (of up to 16 bytes) by itself
 constexpr uint32_t kFillWaveTokens = 4;                      // up to that many candidates for each wavefront of the workgroup get a wavefront each
 constexpr uint32_t kFillWaveBytes = 64;                      // bytes of a token that a wavefront parses
+constexpr uint32_t kFillPlaneTokens = kUncListWords - 1;     // with more uncertain tokens in a frontier plane (than its list holds), or in a
+constexpr uint32_t kFillRowTokens = 2048;                    //   frontier (than any slot's can have otherwise), a row is worked through word by word
 // Wavefronts of a row's workgroup, in a batch of `rows` rows on a device of `units` compute units: some frontier plane has `tokens`
 // uncertain tokens, and rows have up to about `candidates` in all (k_fill has the figures).
 constexpr uint32_t kFillMostWaves = 16, kFillOwnLanes = 6;
 constexpr uint32_t fill_row_waves(uint32_t rows, uint32_t units, uint32_t tokens, uint32_t candidates) {
     if (rows <= units) return 16;
+    if (tokens > kFillPlaneTokens) return rows <= 2 * units ? 12 : 6;
     if (candidates > 64) return 12;
     if (rows > 4 * units || candidates > 12 * kFillWaveTokens) return 6;
     return tokens > (rows <= 2 * units ? 2 : 6 * kFillWaveTokens) ? 12 : 6;
 }
 constexpr uint32_t kFillSpreadRows = 192, kFillSpreadTokens = 18;    // up to that many rows with more tokens than that, which may be longer than a wavefront takes
-constexpr uint32_t kFillPlaneTokens = kUncListWords - 1;     // with more uncertain tokens in a frontier plane (than its list holds), or in a
-constexpr uint32_t kFillRowTokens = 2048;                    //   frontier (than any slot's can have otherwise), a row is worked through word by word
 constexpr uint32_t kFillContextItems = 64, kFillContextSets = 240, kFillContextWaits = 512;   // contexts that wavefronts parse from (every slot's)
 constexpr uint32_t kStampsRows = 1;
 void launch_fill(const FillBatch& F, const DevVocab& Vd, int32_t* bitmask_dev, int64_t row_stride_words,

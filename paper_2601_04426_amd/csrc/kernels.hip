@@ -924,7 +924,9 @@ struct WaveScan {
 //   49 - 64 are a lane's each with either, in one round.  300 / 512 / 1,024 / 2,048 rows of repetitions (59) 26.4 / 29.0 / 32.5 / 47.9
 //   against 28.1 / 32.0 / 37.2 / 58.9: six.
 //   More take a second round with six and, up to 128, not with twelve.  Nested parentheses (80), 300 / 1,024 / 2,048 rows, 105.9 / 197.6 /
-//   310.7 against 73.0 / 134.4 / 250.5; 600 word by word, 512 / 1,024 rows, 408 / 774 against 296 / 570: twelve.
+//   310.7 against 73.0 / 134.4 / 250.5: twelve.
+//   Word by word, 64 / 300 / 600 tokens a plane, 512 rows 81 / 201 / 398 against 91 / 182 / 290, 1,024 rows 137 / 351 / 679 against 172 /
+//   354 / 558, 2,048 rows 210 / 523 / 1,015 against 332 / 688 / 1,057: twelve up to two rows a compute unit.
 // Everything that is asked for before the plan is known (the context, the tables, the first planes' lists, the first block of the
 // union) used to wait for it: 0.5 - 1.5 us of every row.
 // A row with a frontier plane whose uncertain tokens do not fit its list (or with more candidates than the LDS list
@@ -1374,76 +1376,78 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVE
         return;
     }
     if (threadIdx.x == 0) F.row_count[b] = n_cand;
+    if (wave < FILL_OR_WAVES) { stamp_end(); return; }                // (a barrier below is for the wavefronts that have not ended)
     // the sequential way: each wave of the re-check team takes its share of the listed words, at a time at most as many as it has lanes
     // at work, and spreads their set bits densely over those lanes.  (As many words as lanes, however few there are, leave all of them
     // to the first waves: 64 / 100 / 300 / 600 neighbouring tokens of up to 14 bytes, 1 row, 120 / 186 / 541 / 880 us against 73 / 68 /
-    // 94 / 170; 512 rows, twelve wavefronts, 142 / 236 / 661 / 1,127 against 92 / 91 / 186 / 296.)
+    // 94 / 170; 512 rows, twelve wavefronts, 142 / 236 / 661 / 1,127 against 91 / 88 / 182 / 290.
+    // The streaming wavefronts end before: were they kept for the barrier, 800 / 1,024 / 2,048 rows of six wavefronts with 64 tokens took
+    // 144 / 156 / 275 us instead of 94 / 137 / 210.)
     const FillArgs Z = args_again<FillArgs>();
     const FillRow q = uniform_load(Z.F.rows + b);
     const uint32_t count = n_listed;
     const uint32_t* wlist = Z.F.work_list + (size_t)b * Z.Vd.W;
     uint32_t* cands = Z.F.cand_words + (size_t)b * Z.Vd.W;
-    if (wave >= FILL_OR_WAVES) {
-        const DevTables T2 = uniform_load(Z.F.tables + q.tables_idx);
-        const DevCtx C = row_ctx(Z.F, q);
-        uint32_t large = 0, n_left = 0;
-        constexpr uint32_t TEAM = WAVES - FILL_OR_WAVES;
-        const uint32_t n_words = min(LANES, (count + TEAM - 1) / TEAM);
-        for (uint32_t base = (wave - FILL_OR_WAVES) * n_words; base < count; base += TEAM * n_words) {
-            uint32_t idx = 0, cand = 0, left = 0;                      // left: the tokens of this lane's word that are for the end
-            const bool has_word = lane < n_words && base + lane < count;
-            if (has_word) { idx = wlist[base + lane]; cand = cands[idx]; }
-            uint32_t pre = (uint32_t)__popc(cand);
-            for (int d = 1; d < 64; d <<= 1) { const uint32_t up = (uint32_t)__shfl_up((int)pre, d); if ((int)lane >= d) pre += up; }
-            const uint32_t n_tok = lane_value(pre, 63);
-            for (uint32_t t0 = 0; t0 < n_tok; t0 += LANES) {
-                const uint32_t my = t0 + lane;
-                const uint32_t j = prefix_owner(pre, my);
-                uint32_t c = (uint32_t)__shfl((int)cand, (int)j);
-                const uint32_t end_j = (uint32_t)__shfl((int)pre, (int)j), w = (uint32_t)__shfl((int)idx, (int)j);
-                bool over = false;
-                uint32_t id = 0;
-                if (lane < LANES && my < n_tok) {
-                    uint32_t skip = my - (end_j - (uint32_t)__popc(c));
-                    while (skip--) c &= c - 1;                         // drop the lowest set bits that other lanes take
-                    id = w * 32 + (uint32_t)__ffs(c) - 1;
-                    const int res = recheck_lane(Z.Vd, T2, ctx.cls_words, C, id, st);
-                    if (res == RECHECK_YES) atomicOr(out + w, 1u << (id & 31));
-                    over = res == RECHECK_OVER;
-                }
-                unsigned long long m = __ballot(over);
-                if (!m) continue;
-                large += (uint32_t)__popcll(m);
-                if (Z.F.follows) {                                     // to k_recheck_slow, if its list has room
-                    uint32_t at = 0;
-                    if (lane == 0) at = atomicAdd(Z.S.count, (uint32_t)__popcll(m));
-                    at = lane_value(at, 0) + (uint32_t)__popcll(m & ((1ull << lane) - 1));
-                    const bool fits = over && at < Z.S.list_cap;
-                    if (fits) { Z.S.list[2 * at] = b; Z.S.list[2 * at + 1] = id; }
-                    m = __ballot(over && !fits);
-                }
-                n_left += (uint32_t)__popcll(m);
-                while (m) {
-                    const uint32_t k = next_bit(m), id2 = lane_value(id, k);
-                    if (Z.F.own_lanes) left |= lane == lane_value(j, k) ? 1u << (id2 & 31) : 0u;
-                    else if (lane == 0) leave_undecided(Z.S, b, id2);
-                }
+    const DevTables T2 = uniform_load(Z.F.tables + q.tables_idx);
+    const DevCtx C = row_ctx(Z.F, q);
+    uint32_t large = 0, n_left = 0;
+    constexpr uint32_t TEAM = WAVES - FILL_OR_WAVES;
+    const uint32_t n_words = min(LANES, (count + TEAM - 1) / TEAM);
+    for (uint32_t base = (wave - FILL_OR_WAVES) * n_words; base < count; base += TEAM * n_words) {
+        uint32_t idx = 0, cand = 0, left = 0;                      // left: the tokens of this lane's word that are for the end
+        const bool has_word = lane < n_words && base + lane < count;
+        if (has_word) { idx = wlist[base + lane]; cand = cands[idx]; }
+        uint32_t pre = (uint32_t)__popc(cand);
+        for (int d = 1; d < 64; d <<= 1) { const uint32_t up = (uint32_t)__shfl_up((int)pre, d); if ((int)lane >= d) pre += up; }
+        const uint32_t n_tok = lane_value(pre, 63);
+        for (uint32_t t0 = 0; t0 < n_tok; t0 += LANES) {
+            const uint32_t my = t0 + lane;
+            const uint32_t j = prefix_owner(pre, my);
+            uint32_t c = (uint32_t)__shfl((int)cand, (int)j);
+            const uint32_t end_j = (uint32_t)__shfl((int)pre, (int)j), w = (uint32_t)__shfl((int)idx, (int)j);
+            bool over = false;
+            uint32_t id = 0;
+            if (lane < LANES && my < n_tok) {
+                uint32_t skip = my - (end_j - (uint32_t)__popc(c));
+                while (skip--) c &= c - 1;                         // drop the lowest set bits that other lanes take
+                id = w * 32 + (uint32_t)__ffs(c) - 1;
+                const int res = recheck_lane(Z.Vd, T2, ctx.cls_words, C, id, st);
+                if (res == RECHECK_YES) atomicOr(out + w, 1u << (id & 31));
+                over = res == RECHECK_OVER;
             }
-            if (Z.F.own_lanes && has_word) cands[idx] = left;
+            unsigned long long m = __ballot(over);
+            if (!m) continue;
+            large += (uint32_t)__popcll(m);
+            if (Z.F.follows) {                                     // to k_recheck_slow, if its list has room
+                uint32_t at = 0;
+                if (lane == 0) at = atomicAdd(Z.S.count, (uint32_t)__popcll(m));
+                at = lane_value(at, 0) + (uint32_t)__popcll(m & ((1ull << lane) - 1));
+                const bool fits = over && at < Z.S.list_cap;
+                if (fits) { Z.S.list[2 * at] = b; Z.S.list[2 * at + 1] = id; }
+                m = __ballot(over && !fits);
+            }
+            n_left += (uint32_t)__popcll(m);
+            while (m) {
+                const uint32_t k = next_bit(m), id2 = lane_value(id, k);
+                if (Z.F.own_lanes) left |= lane == lane_value(j, k) ? 1u << (id2 & 31) : 0u;
+                else if (lane == 0) leave_undecided(Z.S, b, id2);
+            }
         }
-        if (lane == 0 && large) atomicAdd(Z.S.count + 3, large);
-        if (lane == 0 && n_left) atomicAdd(&n_over, n_left);
+        if (Z.F.own_lanes && has_word) cands[idx] = left;
     }
+    if (lane == 0 && large) atomicAdd(Z.S.count + 3, large);
+    if (lane == 0 && n_left) atomicAdd(&n_over, n_left);
     if (Z.F.own_lanes) {
         // what is left: one lane of every wavefront that has a lane of the large-capacity scratch.  (A wavefront without one must
         // not parse with its lists in device memory: there are more of them than lanes, and the next lane is the next row's.)
         __syncthreads();
-        if (n_over != 0 && lane == 0 && wave < Z.F.own_lanes)
-            for (uint32_t k = wave; k < count; k += Z.F.own_lanes) {
+        const uint32_t n_own = min(Z.F.own_lanes, TEAM), me = wave - FILL_OR_WAVES;
+        if (n_over != 0 && lane == 0 && me < n_own)
+            for (uint32_t k = me; k < count; k += n_own) {
                 const uint32_t w = wlist[k];
                 for (uint32_t m = cands[w]; m; m &= m - 1) {
                     const uint32_t bit = (uint32_t)__ffs(m) - 1;
-                    if (recheck_large(Z.F, Z.Vd, Z.S, q, b, w * 32 + bit, b * Z.F.own_lanes + wave)) atomicOr(out + w, 1u << bit);
+                    if (recheck_large(Z.F, Z.Vd, Z.S, q, b, w * 32 + bit, b * Z.F.own_lanes + me)) atomicOr(out + w, 1u << bit);
                 }
             }
     }
