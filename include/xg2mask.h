@@ -272,7 +272,7 @@ int32_t xg2_fill_last_recheck_tokens(int32_t* tokens_host, int32_t cap, int32_t*
  * A batch holds B matcher slots in device memory: per slot the scannable items of the current closed Earley set, what the
  * waiting items of every older set still reachable wait for, and the planes of the scannable frontier.  A decoding step
  * then needs nothing from the host: xg2_batch_accept_tokens runs the sampled tokens (a device array, e.g. the sampler's
- * output) through the Earley recogniser, one lane per slot, and leaves each slot's next state in place;
+ * output) through the Earley recogniser, one wavefront per slot, and leaves each slot's next state in place;
  * xg2_batch_fill_next_token_bitmask reads the slots directly.  Both only enqueue kernels on the caller's stream.
  * Capacities of a slot: 64 scannable items, 240 reachable sets, 512 wait entries, 32 frontier planes (a grammar whose
  * parse needs more, e.g. deeply right-recursive rules, makes the slot fail with XG2_EOVERFLOW until it is reassigned: use
