@@ -30,16 +30,16 @@ HBM_PEAK_GBS = 8000.0
 
 # HBM traffic per launch from rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE (counter values per dispatch, default workload and
 # batch; k_build_tagdispatch: the one build of the TagDispatch workload), valid only for the kernel sources they were taken
-# with.  The same counters read 303,890 (FETCH_SIZE) and 607,744 (WRITE_SIZE) for a device-to-device copy of 607,744 KiB,
+# with.  The same counters read 303,884 (FETCH_SIZE) and 607,744 (WRITE_SIZE) for a device-to-device copy of 607,744 KiB,
 # hence the scale factors to KiB.  The summaries under profiles/ hold the commands and the full tables.
 PMC = {
-    "sources_sha256": "11983afd5d0e1458d6e282ddfe48e1e6907cad4e9c7e797788bc2e9ff50b78e9",
+    "sources_sha256": "17bcad990806d3c3e54d17b8951a803ff2842b90d2641eb2e59c3beca182eca9",
     "fetch_scale": 2.00, "write_scale": 1.00,
-    "k_build": (11020.4, 4800.5),
-    "k_fill": (3353.1, 19285.3),
-    "k_apply_vec<bf16>": (97593.9, 303897.6),
-    "k_apply_vec<fp32>": (179385.9, 605717.7),
-    "k_build_tagdispatch": (144056.8, 689897.5),
+    "k_build": (11019.0, 4800.5),
+    "k_fill": (3557.6, 19288.9),
+    "k_apply_vec<bf16>": (97592.9, 303893.9),
+    "k_apply_vec<fp32>": (179386.4, 605733.8),
+    "k_build_tagdispatch": (144073.0, 689897.5),
     # wave instructions of one k_build launch (rocprofv3 --pmc SQ_INSTS_VALU; SQ_INSTS_SALU + SQ_INSTS_SMEM + SQ_INSTS_BRANCH)
     "k_build_valu_instructions": 12898560.0, "k_build_scalar_and_branch_instructions": 17288610.0,
     "k_build_tagdispatch_valu_instructions": 848041696.0, "k_build_tagdispatch_scalar_and_branch_instructions": 1115408341.0,
