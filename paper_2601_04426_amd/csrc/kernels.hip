@@ -1813,14 +1813,26 @@ __global__ __launch_bounds__(64) void k_accept(AcceptArgs A) {
 // 16-byte boundary done by the element, against now, us at 1,024 rows of V = 151,936 / 151,937, bf16: nothing masked 9.8 / 130
 // -> 6.2 / 7.3; nearly everything 80 / 204 -> 52 / 53; 5 % of the tokens 107 / 252 -> 97 / 98 (four
 // fifths of the 64-byte sectors hold a masked token and are read and written).
+// Where the mixed vectors of a piece hold few masked tokens these are stored one by one: nothing is read, a store need not wait for a
+// load, and a piece nearly all of which is allowed writes what it masks and no more.  Each lane goes through its own word, so the most
+// in one word counts.  Read and merged / one by one, us, random masks of V = 151,936, masked 0.05 / 0.5 / 2 / 5 %: 1,024 rows bf16
+// 18.3 / 34.9 / 70.6 / 97.4 -> 11.6 / 15.5 / 36.1 / 85.2, 256 rows fp32 7.2 / 13.1 / 22.3 / 35.2 -> 5.2 / 6.9 / 12.6 / 30.7.  Where nearly all is
+// masked the same spares small logits a wait (64 rows of a JSON schema, fp32, V = 32,000: the step 18.4 -> 17.5 us), but the memory pays
+// for a line that arrives in parts: 256 rows, fp32, over three sets of logits, 1 % allowed 43 -> 52 us, and beyond the last-level cache
+// 52 -> 72.  So beyond APPLY_LARGE_BYTES all masked tokens of a word count, and fewer of them.
 constexpr int APPLY_WAVE = 64 * 32, APPLY_WAVES = 4;
+// Where the logits of a call end up: small ones stay in the caches, large ones fit the last-level cache (256 MB) but share it with what
+// else the program touches between two steps, and what is beyond it is streamed past it.
+enum ApplySize { APPLY_SMALL, APPLY_LARGE, APPLY_STREAM };
+constexpr uint32_t APPLY_FEW_SMALL = 8, APPLY_FEW_LARGE = 4;
 template <class E> struct ApplyE;
 template <> struct ApplyE<uint32_t> { static constexpr uint32_t NINF = 0xFF800000u, NINF_WORD = 0xFF800000u; };
 template <> struct ApplyE<uint16_t> { static constexpr uint16_t NINF = 0xFF80; static constexpr uint32_t NINF_WORD = 0xFF80FF80u; };
 typedef uint32_t Vec4 __attribute__((ext_vector_type(4)));
 
-template <class E, bool STREAM>
+template <class E, ApplySize SIZE>
 __global__ __launch_bounds__(64 * APPLY_WAVES) void k_apply_vec(E* logits, long long row_stride, int V, const uint32_t* bitmask, long long bm_stride) {
+    constexpr bool STREAM = SIZE == APPLY_STREAM;
     constexpr int EPV = 16 / sizeof(E), STEPS = 32 / EPV;
     constexpr uint32_t ALL = (1u << EPV) - 1, NI = ApplyE<E>::NINF_WORD;
     const long long b = blockIdx.y;
@@ -1841,13 +1853,37 @@ __global__ __launch_bounds__(64 * APPLY_WAVES) void k_apply_vec(E* logits, long 
     if (first + 32 > V) word |= first >= V ? ~0u : ~0u << (V - first);
     if (__ballot(word != ~0u) == 0) return;
     E* const piece = row + e0;
+    // the word's masked tokens: those of vectors that are masked as a whole, and the others
+    const uint32_t masked = ~word;
+    uint32_t whole = masked & (masked >> 1);
+    whole &= whole >> 2;
+    if (EPV == 8) whole &= whole >> 4;
+    whole = (whole & (EPV == 8 ? 0x01010101u : 0x11111111u)) * ALL;
+    uint32_t part = masked & ~whole;
+    const Vec4 none{NI, NI, NI, NI};
+    if (__ballot((uint32_t)__popc(SIZE == APPLY_SMALL ? part : masked) > (SIZE == APPLY_SMALL ? APPLY_FEW_SMALL : APPLY_FEW_LARGE)) == 0) {
+#pragma unroll
+        for (int j = 0; j < STEPS; ++j) {
+            const int v = j * 64 + lane;
+            if (((uint32_t)__shfl((int)whole, v / STEPS) >> (v % STEPS * EPV)) & 1u) {
+                Vec4* const to = reinterpret_cast<Vec4*>(piece) + v;
+                if (STREAM) __builtin_nontemporal_store(none, to);
+                else *to = none;
+            }
+        }
+        E* const mine = piece + 32 * lane;
+        while (__ballot(part != 0) != 0) {
+            if (part != 0) { mine[__ffs(part) - 1] = ApplyE<E>::NINF; part &= part - 1; }
+        }
+        return;
+    }
     Vec4 x[STEPS];
     uint32_t bits[STEPS];
 #pragma unroll
     for (int j = 0; j < STEPS; ++j) {
         const int v = j * 64 + lane;
         bits[j] = ((uint32_t)__shfl((int)word, v / STEPS) >> (v % STEPS * EPV)) & ALL;
-        x[j] = Vec4{NI, NI, NI, NI};
+        x[j] = none;
         const int e = (int)e0 + v * EPV;
         if (bits[j] != 0 && bits[j] != ALL && e >= 0 && e + EPV <= V) x[j] = reinterpret_cast<const Vec4*>(piece)[v];
     }
@@ -2049,7 +2085,7 @@ void launch_recheck_slow(const FillBatch& F, const DevVocab& Vd, int32_t* bitmas
 // Ordinary stores leave the logits in the last-level cache (256 MB), where the next pass over them finds them; logits that do
 // not fit there push each other out, and streaming stores take them straight to memory.  Ordinary / streaming, us, nearly
 // everything masked: 205 MB 33 / 39, 233 MB 39 / 40, 266 MB (below the line) 46 / 51, 273 MB (above) 57 / 46, 311 MB 70 / 52.
-constexpr long long APPLY_STREAM_BYTES = 256ll << 20;
+constexpr long long APPLY_STREAM_BYTES = 256ll << 20, APPLY_LARGE_BYTES = 64ll << 20;
 
 template <class E>
 static void launch_apply_as(E* logits, int32_t B, int32_t V, int64_t row_stride_elems, const uint32_t* bm, int64_t bm_row_stride_words, hipStream_t stream) {
@@ -2062,7 +2098,8 @@ static void launch_apply_as(E* logits, int32_t B, int32_t V, int64_t row_stride_
     // few pieces: a workgroup each, to reach as many compute units (one row, V = 32,000, fp32: 3.7 us against 4.0); many: four share one
     // (1,024 rows, V = 151,936, bf16, nothing masked: 6.2 us against 17.5, which is how long it takes to start the workgroups)
     const uint32_t waves = (uint64_t)pieces * (uint32_t)B <= 512 ? 1 : APPLY_WAVES;
-    auto* const kernel = (long long)B * V * (int)sizeof(E) > APPLY_STREAM_BYTES ? k_apply_vec<E, true> : k_apply_vec<E, false>;
+    const long long bytes = (long long)B * V * (int)sizeof(E);
+    auto* const kernel = bytes > APPLY_STREAM_BYTES ? k_apply_vec<E, APPLY_STREAM> : bytes > APPLY_LARGE_BYTES ? k_apply_vec<E, APPLY_LARGE> : k_apply_vec<E, APPLY_SMALL>;
     hipLaunchKernelGGL(kernel, dim3((pieces + waves - 1) / waves, B), dim3(64 * waves), 0, stream, logits, (long long)row_stride_elems, V, bm,
                        (long long)bm_row_stride_words);
 }
