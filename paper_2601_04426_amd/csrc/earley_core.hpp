@@ -96,7 +96,11 @@ __device__ __forceinline__ void add_wait(S& st, uint32_t rule, uint32_t tgt, int
 
 // One byte of lookahead keeps the lists short: an item whose state has byte edges only and is not final can do nothing
 // but scan, so if it has no edge for the byte that comes next it is left out (`la` = class of that byte, or NO_TARGET
-// after the token's last byte, where every item counts because only "is the set empty" is asked).
+// after the token's last byte, where every item counts because only "is the set empty" is asked).  Of an item that starts in
+// the set under construction, the end means nothing either: what it would complete without a byte has been advanced over on
+// entering.  (Every optional whitespace in front of something else is such an item.  Without them the recogniser is back at the plain
+// automaton walk more often: k_build of 16 tools 608 -> 596 us, of 12 others 828 -> 808, of a list of records 102 -> 99.)
+__device__ __forceinline__ uint32_t entered(uint32_t w) { return (w & EXP_CURRENT) ? w & ~F_FINAL : w; }   // of an expansion's item: flags that count here
 __device__ __forceinline__ bool inert(const DevTables& T, uint32_t ref, uint32_t la) {
     return la != NO_TARGET && (ref & (F_BYTE | F_REF | F_FINAL)) == F_BYTE && tab(T.trans + (ref & SID_MASK) * T.n_classes + la) == T.sink;
 }
@@ -112,7 +116,7 @@ __device__ __forceinline__ void enter(const DevTables& T, S& st, uint32_t ref, u
         const uint32_t* e = T.exp_list + d.y;
         for (uint32_t k = 0; k < d.z; ++k) {
             const uint32_t w = tab(e + k);
-            if (inert(T, w, la)) continue;
+            if (inert(T, entered(w), la)) continue;
             add_nxt(st, (w & REF_MASK) | (((w & EXP_CURRENT) ? set_idx : origin) << REF_BITS), nn, full);
         }
         e += d.z;

@@ -838,7 +838,7 @@ struct WaveScan {
                 const uint32_t j = next_bit(m), x = lane_value(tgt, j);
                 add_wait(lane_value(w, j), (x & REF_MASK) | (((x & EXP_CURRENT) ? set_idx : origin) << REF_BITS));
             }
-            for (unsigned long long m = lanes_of(base + lane < n_items) & ~inert(v, t); m;) {
+            for (unsigned long long m = lanes_of(base + lane < n_items) & ~inert(entered(v), t); m;) {
                 const uint32_t j = next_bit(m), x = lane_value(v, j);
                 add((x & REF_MASK) | (((x & EXP_CURRENT) ? set_idx : origin) << REF_BITS), lane_value(t, j), of);   // (an advance stays in its rule)
             }
