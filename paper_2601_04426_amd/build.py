@@ -16,6 +16,7 @@ def build(verbose: bool = False) -> str:
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     cmd = [hipcc, f"--offload-arch={ARCH}", "-O3", "-Xarch_device", "-Os", "-std=c++17", "-fPIC", "-shared",
            "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+           "-mllvm", "-amdgpu-kernarg-preload-count=14",             # words of a kernel's first arguments that start in registers
            "-Wall", "-Wno-unused-command-line-argument",
            "-o", LIB] + [os.path.join(CSRC, s) for s in SOURCES]
     if verbose:

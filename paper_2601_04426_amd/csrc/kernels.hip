@@ -744,12 +744,16 @@ __device__ __forceinline__ P uniform_load(const P* p) {
 #else
 #define PIN(...) (void)0
 #endif
-// What a kernel was launched with, read anew from the launch's own memory (A: all its arguments, as one struct): what only a way
-// that is rarely taken needs must not take up registers on the way that nearly every row or token goes.
+// What a kernel was launched with, read anew from the launch's own memory (A: the struct that follows two pointers among its
+// arguments): what only a way that is rarely taken needs must not take up registers on the way that nearly every row or token goes.
+// The two pointers are those that a kernel's first loads need: the device has them in registers when it starts (build.py says how
+// many words of arguments), where a load of them takes 560 - 700 cycles of the slowest row's chain.  (The
+// decoding steps of 16 rows of tools, 64 of a JSON schema and 256 of tools 16.96 / 19.1 / 57.7 -> 16.7 / 18.8 / 57.1 us.)
 template <class A>
 __device__ __forceinline__ A args_again() {
 #if defined(__HIP_DEVICE_COMPILE__)
-    auto p = (const __attribute__((address_space(4))) A*)__builtin_amdgcn_kernarg_segment_ptr();
+    static_assert(alignof(A) == 8, "the struct lies right behind the two pointers");
+    auto p = (const __attribute__((address_space(4))) A*)((const __attribute__((address_space(4))) char*)__builtin_amdgcn_kernarg_segment_ptr() + 16);
     asm volatile("" : "+s"(p));
     return *p;
 #else
@@ -1186,7 +1190,7 @@ __device__ __forceinline__ void fill_union_listing(const FillBatch& F, uint32_t 
 // Six wavefronts a SIMD at least: a compute unit then holds four rows of six wavefronts, i.e. the device 1,024 at once.
 struct FillArgs { FillBatch F; DevVocab Vd; int32_t* bitmask; long long row_stride; SlowScratch S; };
 template <int WAVES>
-__global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVES == 16 ? 4 : 6))) void k_fill(FillArgs A) {
+__global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVES == 16 ? 4 : 6))) void k_fill(const FillRow* rows, const uint64_t* front_planes, FillArgs A) {
     const FillBatch& F = A.F;
     const DevVocab& Vd = A.Vd;
     using Team = FillTeam<WAVES>;
@@ -1201,17 +1205,16 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVE
     __shared__ uint32_t n_listed, n_cand, n_over, next_token, n_to_parse;
     __shared__ WaveToken sh_tok[FILL_WAVE_TOKENS];
     const uint32_t b = blockIdx.x, lane = threadIdx.x & 63, wave = same_in_all(threadIdx.x >> 6);
-    if (F.stamps && threadIdx.x == 0) F.stamps[kStampsRows + (WAVES + 1) * b] = wall_clock64();
+    FillRow r = uniform_load(rows + b);
+    uint64_t started = wall_clock64();
+    PIN("+s"(r.front_off), "+s"(r.flags), "+s"(started));            // nothing that other arguments are waited for stands before these
     auto stamp_end = [&]() { if (F.stamps && lane == 0) F.stamps[kStampsRows + (WAVES + 1) * b + 1 + wave] = wall_clock64(); };
-    const FillRow r = uniform_load(F.rows + b);
     const uint32_t front_off = r.front_off, front_n = r.front_n, flags = r.flags;
     const bool live = !(flags & 2u);
-    if (threadIdx.x == 0) { n_listed = 0; n_cand = 0; n_over = 0; next_token = 0; }
-    if (F.zero_words && b == 0 && threadIdx.x < 4) F.zero_words[threadIdx.x] = 0;      // the words the next call counts in
     // the plan, worked out by every wavefront for itself: lane k looks at frontier plane k
     uint64_t addr = 1;
     uint32_t n_unc = 0;
-    if (live && front_n <= 64 && lane < front_n) addr = F.front_planes[front_off + lane];
+    if (live && front_n <= 64 && lane < front_n) addr = front_planes[front_off + lane];
     // What a parse starts from does not hang on the frontier, and is asked for together with it: the grammar's tables, the context.
     static_assert(kFillContextItems <= WaveScan<false>::N, "a context's items lie across the lanes");
     DevTables T = uniform_load(F.tables + r.tables_idx);
@@ -1236,6 +1239,11 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVE
             for (uint32_t t = threadIdx.x - FILL_OR_THREADS; t <= r.H; t += THREADS - FILL_OR_THREADS) ctx.off[t] = tab(F.ctx_wait_off + r.waitoff_off + t);
         }
     }
+    if (threadIdx.x == 0) {
+        n_listed = 0; n_cand = 0; n_over = 0; next_token = 0;
+        if (F.stamps) F.stamps[kStampsRows + (WAVES + 1) * b] = started;
+    }
+    if (F.zero_words && b == 0 && threadIdx.x < 4) F.zero_words[threadIdx.x] = 0;      // the words the next call counts in
     const bool no_list = n_unc > kUncListWords - 1;                   // more uncertain tokens than the plane's list holds
     uint32_t incl = no_list ? 0u : n_unc, total = 0;
     const bool some_list = __any(incl != 0);
@@ -1558,7 +1566,7 @@ __global__ __launch_bounds__(256) void k_batch_assign(BatchDev D, const int32_t*
 
 constexpr uint32_t ACC_KI = kSlotItems, ACC_KH = kSlotSets, ACC_KW = kSlotWaits, ACC_KF = kSlotPlanes;     // the slot capacities the LDS staging is laid out for
 
-// What the kernel is launched with (read anew where a way is rarely taken).
+// What the kernel is launched with besides rows and tokens (read anew where a way is rarely taken).
 struct AcceptArgs { BatchDev D; DevVocab Vd; uint32_t eos_id; const int32_t* token_ids; int32_t* status; };
 
 // What accepting a token needs of a cache.
@@ -1693,7 +1701,7 @@ __device__ __forceinline__ int accept_wave(const BatchDev& D, const CacheView& C
     return ACC_OK;
 }
 
-__global__ __launch_bounds__(64) void k_accept(AcceptArgs A) {
+__global__ __launch_bounds__(64) void k_accept(const FillRow* rows, const int32_t* token_ids, AcceptArgs A) {
     __shared__ uint32_t in_items[ACC_KI], in_wait_off[ACC_KH + 1], out_items[ACC_KI], out_wait_off[ACC_KH + 1];
     __shared__ uint2 in_wait[ACC_KW], out_wait[ACC_KW];
     __shared__ uint64_t out_front[ACC_KF], x_front[ACC_KF];
@@ -1705,10 +1713,9 @@ __global__ __launch_bounds__(64) void k_accept(AcceptArgs A) {
     int32_t* status = A.status;
     const TokenRecord* records = A.Vd.rec;
     uint32_t V = A.Vd.V, eos_id = A.eos_id, B = A.D.B;
-    PIN("+s"(status), "+s"(records), "+s"(V), "+s"(eos_id), "+s"(B));
-    const int32_t tok = uniform_load(A.token_ids + b);
-    FillRow r = uniform_load(A.D.rows + b);                         // (no other workgroup writes this row)
-    PIN("+s"(r.pad[1]), "+s"(r.flags), "+s"(r.tables_idx));
+    int32_t tok = uniform_load(token_ids + b);
+    FillRow r = uniform_load(rows + b);                             // (no other workgroup writes this row)
+    PIN("+s"(tok), "+s"(r.pad[1]), "+s"(r.flags), "+s"(r.tables_idx), "+s"(status), "+s"(records), "+s"(V), "+s"(eos_id), "+s"(B));
     int32_t code = kAccOk;
     if (tok == kTokenReset) start_sequence(A.D, b, r.tables_idx, lane, 64);
     else if (tok < 0) code = kAccOk;                                 // nothing for this slot
@@ -2005,7 +2012,7 @@ void launch_build_slow(const DevTables& T, const DevVocab& Vd, const BuildPlan& 
 
 void launch_accept(const BatchDev& D, const DevVocab& Vd, uint32_t eos_id, const int32_t* token_ids_dev, int32_t* status_dev, hipStream_t stream) {
     if (!D.B || D.KI != ACC_KI || D.KH != ACC_KH || D.KW != ACC_KW || D.KF != ACC_KF) return;
-    hipLaunchKernelGGL(k_accept, dim3(D.B), dim3(64), 0, stream, AcceptArgs{D, Vd, eos_id, token_ids_dev, status_dev});
+    hipLaunchKernelGGL(k_accept, dim3(D.B), dim3(64), 0, stream, D.rows, token_ids_dev, AcceptArgs{D, Vd, eos_id, token_ids_dev, status_dev});
 }
 
 void launch_token_records(const DevVocab& Vd, TokenRecord* rec_dev, hipStream_t stream) {
@@ -2073,8 +2080,8 @@ void launch_fill(const FillBatch& F, const DevVocab& Vd, int32_t* bitmask_dev, i
     auto* const kernel = F.row_waves == 16 ? k_fill<16> : F.row_waves == 12 ? k_fill<12> : k_fill<6>;
     const dim3 block(64 * F.row_waves);
     const FillArgs A{F, Vd, bitmask_dev, (long long)row_stride_words, S};
-    if (done) hipExtLaunchKernelGGL(kernel, dim3(F.B), block, 0, stream, nullptr, done, 0, A);
-    else hipLaunchKernelGGL(kernel, dim3(F.B), block, 0, stream, A);
+    if (done) hipExtLaunchKernelGGL(kernel, dim3(F.B), block, 0, stream, nullptr, done, 0, F.rows, F.front_planes, A);
+    else hipLaunchKernelGGL(kernel, dim3(F.B), block, 0, stream, F.rows, F.front_planes, A);
 }
 
 void launch_recheck_slow(const FillBatch& F, const DevVocab& Vd, int32_t* bitmask_dev, int64_t row_stride_words,
