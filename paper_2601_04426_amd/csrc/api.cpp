@@ -2254,6 +2254,8 @@ int32_t fill_common(xg2_matcher* const* matchers, int32_t B, int32_t* bitmask_de
             }
             most_row = std::max(most_row, tokens);
             r.front_n = (uint32_t)(front.size() - f0);
+            std::copy(front.begin() + (long)f0, front.begin() + (long)std::min(front.size(), f0 + kRowPlanes), r.planes);
+            r.n_wait = (uint32_t)(ctx.wait.size() / 2);
             r.item_n = (uint32_t)ctx.items.size();
             r.H = ctx.H;
             load.deep |= (r.front_n > 64) | (r.item_n > kFillContextItems) | (r.H > kFillContextSets) | (ctx.wait.size() > 2 * kFillContextWaits);
@@ -2296,7 +2298,7 @@ int32_t fill_common(xg2_matcher* const* matchers, int32_t B, int32_t* bitmask_de
         FillSlot* slot = nullptr;
         if (no_alloc) {
             // everything lives in the fixed array: [staging | candidate words | work lists | row counts | overflow list | item lists]
-            if (total > kNoAllocStagingBytes)
+            if (total - (o_front - align(rows.size() * (sizeof(FillRow) - sizeof(FillRow::planes)))) > kNoAllocStagingLimit)
                 return fail(XG2_EOVERFLOW, "xg2_fill_next_token_bitmask_noalloc: the matchers' parser contexts exceed the fixed staging area");
             NoAllocHost& NH = noalloc_host();
             if (!NH.ready) return fail(XG2_EINVAL, "xg2_fill_next_token_bitmask_noalloc: the library has not been set up on this device");

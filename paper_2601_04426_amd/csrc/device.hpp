@@ -138,14 +138,18 @@ constexpr size_t plane_words(uint32_t W) { return (3 * (size_t)W + kUncListWords
 void launch_plane_summary(uint32_t* const* plane_ptr_dev, uint32_t n_pos, uint32_t W, uint32_t* counts_dev, hipStream_t stream);
 
 // One row of a fill batch.
-struct FillRow {
+constexpr uint32_t kRowPlanes = 2;       // planes of the frontier that a row's record names itself
+struct alignas(16) FillRow {
     uint32_t front_off, front_n;         // into front_planes
     uint32_t item_off, item_n;           // into ctx_items
     uint32_t wait_base;                  // into ctx_wait (pairs)
     uint32_t waitoff_off, H;             // into ctx_wait_off ([H + 1] entries, relative to wait_base)
     uint32_t tables_idx;                 // into tables
     uint32_t flags;                      // bit 0: root can end, bit 1: terminated
-    uint32_t pad[3];
+    uint32_t pad[2];
+    uint32_t n_wait;                     // wait entries of the context: ctx_wait_off[waitoff_off + H]
+    uint64_t planes[kRowPlanes];         // front_planes[front_off], ... again (as many as there are), so that their loads need wait for nothing
+                                         // but the record
 };
 struct FillBatch {
     const FillRow* rows; uint32_t B;
@@ -251,9 +255,10 @@ void launch_clear(uint32_t* words_dev, uint32_t n, hipStream_t stream);
 // process ends) instead of buffers that grow with the batch: staging of the per-row records, candidate words and
 // work lists, row counts, the overflow list and the large-capacity item lists.  noalloc_scratch gives the array's
 // device address on the current device (looked up once per device).
-constexpr size_t kNoAllocStagingBytes = (size_t)1 << 20;            // per-row records, frontier planes, context slices
+constexpr size_t kNoAllocStagingLimit = (size_t)1 << 20;            // per-row records (without the planes they repeat), frontier planes, context slices
 constexpr size_t kNoAllocMaskWords = (size_t)1 << 20;               // rows x ceil(V/32) of one call
 constexpr size_t kNoAllocMaxRows = 4096;
+constexpr size_t kNoAllocStagingBytes = kNoAllocStagingLimit + kNoAllocMaxRows * sizeof(uint64_t) * kRowPlanes + 256;
 constexpr uint32_t kNoAllocSlowLanes = 256, kNoAllocListCap = 1u << 16;
 constexpr size_t kNoAllocScratchBytes = kNoAllocStagingBytes + 2 * kNoAllocMaskWords * 4 + kNoAllocMaxRows * 4
                                         + (size_t)kNoAllocListCap * 8 + (size_t)kNoAllocSlowLanes * kSlowSlots * 4;

@@ -1109,14 +1109,14 @@ __device__ __forceinline__ void store4(uint32_t* row, uint32_t w, uint32_t W, co
 }
 
 // One block of a row's union: BLOCK vectors of four words a thread, FILL_OR_THREADS apart, from v0 (of thread 0) on.  What lies
-// beyond the row holds other bits of the plane: nobody may look at it.
+// beyond the row holds other bits of the plane: nobody may look at it.  (Asked for whether the row reaches that far or not: with a way
+// round the loads of a short row the compiler waited for the first before it sent the second.)
 template <int BLOCK>
 __device__ __forceinline__ void union_load(const uint32_t* row, uint32_t n_vec, uint32_t v0, uint32_t (&x)[BLOCK][4]) {
 #pragma unroll
     for (int s = 0; s < BLOCK; ++s) {
-        if (v0 + s * FILL_OR_THREADS >= n_vec) break;               // the same for every thread
-        const uint32_t v = v0 + s * FILL_OR_THREADS + threadIdx.x;
-        const Words4 y = *(const __attribute__((address_space(1))) Words4*)((const __attribute__((address_space(1))) char*)row + 16 * (v < n_vec ? v : n_vec - 1));
+        const uint32_t v = min(v0 + s * FILL_OR_THREADS + threadIdx.x, n_vec - 1);
+        const Words4 y = *(const __attribute__((address_space(1))) Words4*)((const __attribute__((address_space(1))) char*)row + 16 * v);
         x[s][0] = y.x; x[s][1] = y.y; x[s][2] = y.z; x[s][3] = y.w;
     }
 }
@@ -1207,31 +1207,40 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVE
     const uint32_t b = blockIdx.x, lane = threadIdx.x & 63, wave = same_in_all(threadIdx.x >> 6);
     FillRow r = uniform_load(rows + b);
     uint64_t started = wall_clock64();
-    PIN("+s"(r.front_off), "+s"(r.flags), "+s"(started));            // nothing that other arguments are waited for stands before these
-    auto stamp_end = [&]() { if (F.stamps && lane == 0) F.stamps[kStampsRows + (WAVES + 1) * b + 1 + wave] = wall_clock64(); };
+    // (all that the first loads of planes and context go by, waited for once)
+    const DevTables* tables = F.tables;
+    const uint32_t* ctx_items = F.ctx_items;
+    uint64_t* stamps = F.stamps;
+    uint32_t W = Vd.W;
+    PIN("+s"(stamps), "+s"(r.front_off), "+s"(r.flags), "+s"(r.planes[0]), "+s"(r.planes[1]), "+s"(r.n_wait), "+s"(started), "+s"(tables), "+s"(ctx_items), "+s"(W));
+    auto stamp_end = [&]() { if (stamps && lane == 0) stamps[kStampsRows + (WAVES + 1) * b + 1 + wave] = wall_clock64(); };
     const uint32_t front_off = r.front_off, front_n = r.front_n, flags = r.flags;
     const bool live = !(flags & 2u);
-    // the plan, worked out by every wavefront for itself: lane k looks at frontier plane k
+    // the plan, worked out by every wavefront for itself: lane k looks at frontier plane k.  (The first two planes' addresses come with the
+    // row: to find them behind it took a load of 300 - 900 cycles more before anything of a plane could be asked for.)
     uint64_t addr = 1;
     uint32_t n_unc = 0;
-    if (live && front_n <= 64 && lane < front_n) addr = front_planes[front_off + lane];
+    if (live && front_n <= 64) {
+        static_assert(kRowPlanes == 2, "lanes 0 and 1 below");
+        if (lane < front_n) addr = lane == 0 ? r.planes[0] : r.planes[1];
+        if (front_n > kRowPlanes && lane >= kRowPlanes && lane < front_n) addr = front_planes[front_off + lane];
+    }
     // What a parse starts from does not hang on the frontier, and is asked for together with it: the grammar's tables, the context.
     static_assert(kFillContextItems <= WaveScan<false>::N, "a context's items lie across the lanes");
-    DevTables T = uniform_load(F.tables + r.tables_idx);
-    uint32_t n_wait = live ? uniform_load(F.ctx_wait_off + r.waitoff_off + r.H) : 0u;
-    PIN("+s"(T.trans), "+s"(n_wait));
+    DevTables T = uniform_load(tables + r.tables_idx);
+    const uint32_t n_wait = live ? r.n_wait : 0u;
     const bool ctx_fits = live && r.item_n <= kFillContextItems && r.H <= FILL_CTX_SETS && n_wait <= FILL_CTX_WAITS;
     uint32_t my_item = 0, x0[Team::BLOCK][4] = {}, list[FILL_LISTS] = {};
-    if (lane < front_n && !(addr & 1)) n_unc = tab(plane_row(addr) + 3 * (size_t)Vd.W);
-    if (ctx_fits && lane < r.item_n) my_item = tab(F.ctx_items + r.item_off + lane);
+    if (lane < front_n && !(addr & 1)) n_unc = tab(plane_row(addr) + 3 * (size_t)W);
+    if (ctx_fits && lane < r.item_n) my_item = tab(ctx_items + r.item_off + lane);
     if (wave < FILL_OR_WAVES) {
-        if (live && front_n != 0 && front_n <= 64) union_load(plane_row(lane_address(addr, 0)), (Vd.W + 3) / 4, 0, x0);
+        if (live && front_n != 0 && front_n <= 64) union_load(plane_row(lane_address(addr, 0)), (W + 3) / 4, 0, x0);
     } else {
         if (wave == FILL_OR_WAVES) {
             // the first planes' lists, whose lengths are on their way (a plane has room for a whole list, whatever it holds)
             if (live && front_n != 0 && front_n <= 64)
                 _Pragma("unroll") for (uint32_t k = 0; k < FILL_LISTS; ++k)
-                    if (k < front_n) { const uint64_t a = lane_address(addr, k); if (!(a & 1)) list[k] = tab(plane_row(a) + 3 * (size_t)Vd.W + lane); }
+                    if (k < front_n) { const uint64_t a = lane_address(addr, k); if (!(a & 1)) list[k] = tab(plane_row(a) + 3 * (size_t)W + lane); }
             ctx.cls_words[lane] = tab(T.byte_class_words + lane);
         }
         if (ctx_fits) {
@@ -1239,9 +1248,10 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVE
             for (uint32_t t = threadIdx.x - FILL_OR_THREADS; t <= r.H; t += THREADS - FILL_OR_THREADS) ctx.off[t] = tab(F.ctx_wait_off + r.waitoff_off + t);
         }
     }
+    PIN("+s"(T.trans));                                              // (asked for above, and not where the compiler needs it first)
     if (threadIdx.x == 0) {
         n_listed = 0; n_cand = 0; n_over = 0; next_token = 0;
-        if (F.stamps) F.stamps[kStampsRows + (WAVES + 1) * b] = started;
+        if (stamps) stamps[kStampsRows + (WAVES + 1) * b] = started;
     }
     if (F.zero_words && b == 0 && threadIdx.x < 4) F.zero_words[threadIdx.x] = 0;      // the words the next call counts in
     const bool no_list = n_unc > kUncListWords - 1;                   // more uncertain tokens than the plane's list holds
@@ -1548,12 +1558,12 @@ __device__ __forceinline__ void start_sequence(const BatchDev& D, uint32_t b, ui
     r.item_off = b * D.KI; r.item_n = Cd.start_n_items;
     r.wait_base = b * D.KW; r.waitoff_off = b * (D.KH + 1); r.H = Cd.start_H;
     r.tables_idx = cache_idx; r.flags = Cd.start_flags;
-    r.pad[0] = 0; r.pad[1] = 0; r.pad[2] = 0;
+    r.n_wait = Cd.start_wait_off[Cd.start_H];
+    _Pragma("unroll") for (uint32_t k = 0; k < kRowPlanes; ++k) if (k < Cd.start_n_front) r.planes[k] = Cd.start_front[k];
     for (uint32_t k = lane; k < Cd.start_n_front; k += n_lanes) D.front[r.front_off + k] = Cd.start_front[k];
     for (uint32_t k = lane; k < Cd.start_n_items; k += n_lanes) D.items[r.item_off + k] = Cd.start_items[k];
     for (uint32_t k = lane; k <= Cd.start_H; k += n_lanes) D.wait_off[r.waitoff_off + k] = Cd.start_wait_off[k];
-    const uint32_t n_wait = Cd.start_wait_off[Cd.start_H];
-    for (uint32_t k = lane; k < n_wait; k += n_lanes) D.wait[r.wait_base + k] = Cd.start_wait[k];
+    for (uint32_t k = lane; k < r.n_wait; k += n_lanes) D.wait[r.wait_base + k] = Cd.start_wait[k];
     if (lane == 0) D.rows[b] = r;
 }
 
@@ -1573,25 +1583,25 @@ struct AcceptArgs { BatchDev D; DevVocab Vd; uint32_t eos_id; const int32_t* tok
 struct CacheView {
     DevTables T;
     const uint64_t* plain_row; const uint32_t* pair_off; const uint64_t* pair_row; const uint32_t* site_of_off; const uint2* site_of;
-    bool depth1;
+    uint32_t context_depth;
 };
 __device__ __forceinline__ CacheView cache_view(const CacheDev* p) {
     CacheView c;
     c.T = uniform_load(&p->T);
     c.plain_row = uniform_load(&p->plain_row); c.pair_off = uniform_load(&p->pair_off); c.pair_row = uniform_load(&p->pair_row);
     c.site_of_off = uniform_load(&p->site_of_off); c.site_of = uniform_load(&p->site_of);
-    c.depth1 = uniform_load(&p->context_depth) == 1;
+    c.context_depth = uniform_load(&p->context_depth);
     return c;
 }
 
 // The slot's next state from token `tok16` (1 .. 16 bytes), written to the slot's other buffer `slot`; results in out_n (items,
-// sets, planes, root can end).  Lane k has the context's item k, wait entry k and start of set k (what lies beyond the counts is
+// sets, planes, root can end, wait entries) and, if all went well, out_planes (the first of the planes).  Lane k has the context's item k, wait entry k and start of set k (what lies beyond the counts is
 // not looked at), and the classes of bytes 4 k .. 4 k + 3.  ACC_RETRY: something does not fit across the lanes, nothing has been
 // written that counts.
 __device__ __forceinline__ int accept_wave(const BatchDev& D, const CacheView& C, uint32_t b, size_t slot, uint4 tok16, uint32_t n_bytes, uint32_t H, uint32_t item_n,
-                                           uint32_t in_item, uint2 in_wait, uint32_t in_off, uint32_t cls_word, uint32_t lane, uint32_t out_n[4]) {
+                                           uint32_t in_item, uint2 in_wait, uint32_t in_off, uint32_t cls_word, uint32_t lane, uint32_t out_n[5], uint64_t out_planes[kRowPlanes]) {
     const DevTables& T = C.T;
-    const bool depth1 = C.depth1;
+    const bool depth1 = C.context_depth == 1;
     const uint32_t n_sets = H + n_bytes;
     const uint32_t n_wait_in = lane_value(in_off, H < 64 ? H : 0);
     if (n_sets > 64 || H > 63 || item_n > 64 || n_wait_in > 64) return ACC_RETRY;
@@ -1705,7 +1715,8 @@ __device__ __forceinline__ int accept_wave(const BatchDev& D, const CacheView& C
     if (lane == 0) off_out[newH] = n_kept;
     if (has_lane(scanning)) items_out[count_below(scanning)] = (cur & REF_MASK) | (c_new << REF_BITS);
     if (lane < nf) D.front[(size_t)b * ACC_KF + lane] = ((uint64_t)f_hi << 32) | f_lo;
-    out_n[0] = (uint32_t)__popcll(scanning); out_n[1] = newH; out_n[2] = nf; out_n[3] = A.root_done ? 1u : 0u;
+    out_n[0] = (uint32_t)__popcll(scanning); out_n[1] = newH; out_n[2] = nf; out_n[3] = A.root_done ? 1u : 0u; out_n[4] = n_kept;
+    _Pragma("unroll") for (uint32_t k = 0; k < kRowPlanes; ++k) out_planes[k] = ((uint64_t)lane_value(f_hi, k) << 32) | lane_value(f_lo, k);
     return ACC_OK;
 }
 
@@ -1716,7 +1727,8 @@ __global__ __launch_bounds__(64) void k_accept(const FillRow* rows, const int32_
     __shared__ uint32_t lists[OneLaneStore::WORDS];
     __shared__ uint8_t x_map[ACC_KH + ACCEPT_MAXLEN + 4];
     __shared__ int sh_acc;
-    __shared__ uint32_t sh_out[4];                                 // n_items, H, n_front, root_done
+    __shared__ uint32_t sh_out[5];                                 // n_items, H, n_front, root_done, wait entries
+    __shared__ uint64_t sh_planes[kRowPlanes];
     const uint32_t lane = threadIdx.x, b = blockIdx.x;              // one wavefront per slot: everything below is the same in all lanes
     int32_t* status = A.status;
     const TokenRecord* records = A.Vd.rec;
@@ -1742,16 +1754,17 @@ __global__ __launch_bounds__(64) void k_accept(const FillRow* rows, const int32_
         // (a whole batch's wait entries can reach 8 GiB)
         uint32_t my_item = tab_at(A.D.items + r.item_off, lane), my_off = tab_at(A.D.wait_off + r.waitoff_off, lane);
         uint2 my_wait = tab_at(A.D.wait + r.wait_base, lane);
-        PIN("+s"(rec.head.x), "+s"(rec.n_bytes), "+s"(C.T.trans), "+s"(C.T.state), "+s"(C.T.exp_list), "+s"(C.T.n_classes), "+s"(C.T.sink), "+s"(C.plain_row), "+s"(C.pair_off), "+s"(C.pair_row), "+s"(C.site_of_off), "+s"(C.site_of), "+v"(cls_word), "+v"(my_item), "+v"(my_off),
+        PIN("+s"(rec.head.x), "+s"(rec.n_bytes), "+s"(C.T.trans), "+s"(C.T.state), "+s"(C.T.exp_list), "+s"(C.T.n_classes), "+s"(C.T.sink), "+s"(C.plain_row), "+s"(C.pair_off), "+s"(C.pair_row), "+s"(C.site_of_off), "+s"(C.site_of), "+s"(C.context_depth), "+v"(cls_word), "+v"(my_item), "+v"(my_off),
             "+v"(my_wait.x), "+v"(my_wait.y));
         const uint32_t nb = r.pad[0] ^ 1u;
         const size_t slot = (size_t)nb * B + b;
         if (rec.n_bytes == 0) code = kAccRejected;                   // special and empty tokens are never allowed
         else {
-            uint32_t got[4] = {0, 0, 0, 0};
+            uint32_t got[5] = {0, 0, 0, 0, 0};
+            uint64_t planes[kRowPlanes] = {0, 0};
             int acc = ACC_RETRY;
             if (rec.n_bytes <= 16)
-                acc = accept_wave(A.D, C, b, slot, rec.head, rec.n_bytes, r.H, r.item_n, my_item, my_wait, my_off, cls_word, lane, got);
+                acc = accept_wave(A.D, C, b, slot, rec.head, rec.n_bytes, r.H, r.item_n, my_item, my_wait, my_off, cls_word, lane, got, planes);
             if (acc == ACC_RETRY) {
                 // lane 0, with the slot's whole context in LDS
                 const AcceptArgs Z = args_again<AcceptArgs>();
@@ -1788,10 +1801,15 @@ __global__ __launch_bounds__(64) void k_accept(const FillRow* rows, const int32_
                     }
                     sh_acc = a;
                     sh_out[0] = out.n_items; sh_out[1] = out.H; sh_out[2] = out.n_front; sh_out[3] = out.root_done;
+                    if (a == ACC_OK || a == -1) {
+                        sh_out[4] = a == ACC_OK ? out_wait_off[out.H] : D.wait_off[slot * (D.KH + 1) + out.H];
+                        for (uint32_t k = 0; k < kRowPlanes && k < out.n_front; ++k) sh_planes[k] = a == ACC_OK ? out_front[k] : D.front[(size_t)b * D.KF + k];
+                    }
                 }
                 __syncthreads();
                 acc = sh_acc;
-                for (int k = 0; k < 4; ++k) got[k] = sh_out[k];
+                _Pragma("unroll") for (int k = 0; k < 5; ++k) got[k] = sh_out[k];
+                _Pragma("unroll") for (uint32_t k = 0; k < kRowPlanes; ++k) planes[k] = sh_planes[k];
                 if (acc == ACC_OK) {
                     for (uint32_t k = lane; k < got[0]; k += 64) D.items[slot * D.KI + k] = out_items[k];
                     for (uint32_t k = lane; k <= got[1]; k += 64) D.wait_off[slot * (D.KH + 1) + k] = out_wait_off[k];
@@ -1806,7 +1824,8 @@ __global__ __launch_bounds__(64) void k_accept(const FillRow* rows, const int32_
                     w.front_off = b * ACC_KF; w.front_n = got[2];
                     w.item_off = (uint32_t)(slot * ACC_KI); w.item_n = got[0];
                     w.wait_base = (uint32_t)(slot * ACC_KW); w.waitoff_off = (uint32_t)(slot * (ACC_KH + 1)); w.H = got[1];
-                    w.tables_idx = r.tables_idx; w.flags = got[3]; w.pad[0] = nb;
+                    w.tables_idx = r.tables_idx; w.flags = got[3]; w.pad[0] = nb; w.n_wait = got[4];
+                    _Pragma("unroll") for (uint32_t k = 0; k < kRowPlanes; ++k) w.planes[k] = planes[k];
                     A.D.rows[b] = w;
                 }
             } else if (acc == ACC_REJECTED) code = kAccRejected;
