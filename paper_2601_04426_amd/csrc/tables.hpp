@@ -103,6 +103,7 @@ class EarleyChart {
     bool advance(const uint8_t* bytes, size_t n);    // all or nothing: false leaves the chart unchanged
     const ChartSet& last() const { return chart_.back(); }
     size_t length() const { return chart_.size(); }
+    void cut(size_t length) { chart_.resize(length); }           // back to where it had that many sets
     // false if more than kMaxLocalSets sets are reachable
     bool context(ScanContext& out) const;
     // appends the triples of waiting item `w` (origin already renumbered) to `out`
