@@ -1280,7 +1280,12 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVE
         if (lane < total) {
             rec = tab(Vd.rec + id);
             accepted = 0;
-            for (uint32_t k2 = 0; k2 < front_n; ++k2) accepted |= tab(plane_row(lane_address(addr, k2)) + (id >> 5)) >> (id & 31);
+            // four planes at a time: their words are asked for together (256 rows of tools, the step 56.5 -> 55.9 us)
+            for (uint32_t k2 = 0; k2 < front_n; k2 += 4) {
+                uint32_t w[4];
+                _Pragma("unroll") for (uint32_t c = 0; c < 4; ++c) w[c] = tab(plane_row(lane_address(addr, min(k2 + c, front_n - 1))) + (id >> 5));
+                accepted |= (w[0] | w[1] | w[2] | w[3]) >> (id & 31);
+            }
             accepted |= rec.n_bytes == 0;
         }
         const unsigned long long parse = lanes_of(!(accepted & 1u));
@@ -1315,9 +1320,10 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVE
             if (mine) id = tab(reinterpret_cast<const uint32_t*>(((uint64_t)a_hi << 32) | a_lo) + 3 * (size_t)Vd.W + 1 + (t - (end_k - n_k)));
             // a token that a frontier plane accepts is in the mask already: no need to parse it
             uint32_t accepted = 0;
-            for (uint32_t k2 = 0; k2 < front_n; ++k2) {
-                const uint32_t p_lo = (uint32_t)__shfl((int)(uint32_t)addr, (int)k2), p_hi = (uint32_t)__shfl((int)(uint32_t)(addr >> 32), (int)k2);
-                accepted |= tab(reinterpret_cast<const uint32_t*>((((uint64_t)p_hi << 32) | p_lo) & ~(uint64_t)1) + (id >> 5)) >> (id & 31);
+            for (uint32_t k2 = 0; k2 < front_n; k2 += 4) {
+                uint32_t w[4];
+                _Pragma("unroll") for (uint32_t c = 0; c < 4; ++c) w[c] = tab(plane_row(lane_address(addr, min(k2 + c, front_n - 1))) + (id >> 5));
+                accepted |= (w[0] | w[1] | w[2] | w[3]) >> (id & 31);
             }
             if (mine) {
                 const int res = (accepted & 1u) ? RECHECK_NO : recheck_lane(Vd, T, ctx.cls_words, C, id, st);
