@@ -1860,11 +1860,21 @@ __global__ __launch_bounds__(64) void k_accept(const FillRow* rows, const int32_
 // masked the same spares small logits a wait (64 rows of a JSON schema, fp32, V = 32,000: the step 18.4 -> 17.5 us), but the memory pays
 // for a line that arrives in parts: 256 rows, fp32, over three sets of logits, 1 % allowed 43 -> 52 us, and beyond the last-level cache
 // 52 -> 72.  So beyond APPLY_LARGE_BYTES all masked tokens of a word count, and fewer of them.
+// Logits beyond the last-level cache, a piece many of whose vectors are mixed: all that are not masked as a whole are read, and all
+// are written, both past the caches.  A line that a store leaves with holes is merged in memory, which costs more than reading and writing
+// what was allowed; a line that is written whole need not stay in the second-level cache from load to store.  bf16, V = 151,936, masked 10 /
+// 50 / 90 %, us: the mixed ones alone against this, 1,024 rows, the same logits again 112 / 99 / 99 against 98, two sets in turn 135 / 120 / 120
+// against 98, with the pass that writes the logits and the one that reads them 206 / 193 / 193 against 196; 2,048 rows 290 / 247 / 249 against 196,
+// 288 / 251 / 251 against 196, 531 / 490 / 489 against 400.  The decoding step of 1,024 rows of records 131 -> 113.  (A quarter of the loads through the
+// caches: 93 at 1,024 rows and 184 - 218 at 2,048.)  Where more than half of a piece's vectors are allowed, or few are mixed (fp32, 512 rows, 2 %
+// allowed, 69 -> 78), the old way is the better one.  Within the last-level cache, 256 rows, fp32: 48 / 60 / 97 against 50 / 52 / 100 in the three
+// settings: left as it was.
 constexpr int APPLY_WAVE = 64 * 32, APPLY_WAVES = 4;
 // Where the logits of a call end up: small ones stay in the caches, large ones fit the last-level cache (256 MB) but share it with what
 // else the program touches between two steps, and what is beyond it is streamed past it.
 enum ApplySize { APPLY_SMALL, APPLY_LARGE, APPLY_STREAM };
 constexpr uint32_t APPLY_FEW_SMALL = 8, APPLY_FEW_LARGE = 4;
+constexpr int APPLY_DENSE_MIXED = 40, APPLY_DENSE_OPEN = 32;
 template <class E> struct ApplyE;
 template <> struct ApplyE<uint32_t> { static constexpr uint32_t NINF = 0xFF800000u, NINF_WORD = 0xFF800000u; };
 template <> struct ApplyE<uint16_t> { static constexpr uint16_t NINF = 0xFF80; static constexpr uint32_t NINF_WORD = 0xFF80FF80u; };
@@ -1917,6 +1927,39 @@ __global__ __launch_bounds__(64 * APPLY_WAVES) void k_apply_vec(E* logits, long 
         }
         return;
     }
+    auto merge = [](Vec4& v, uint32_t b) {
+        if (sizeof(E) == 4) {
+            _Pragma("unroll") for (int c = 0; c < 4; ++c) if (!((b >> c) & 1)) v[c] = NI;
+        } else {
+            _Pragma("unroll") for (int c = 0; c < 4; ++c) {
+                if (!((b >> (2 * c)) & 1)) v[c] = (v[c] & 0xFFFF0000u) | 0xFF80u;
+                if (!((b >> (2 * c)) & 2)) v[c] = (v[c] & 0x0000FFFFu) | 0xFF800000u;
+            }
+        }
+    };
+    if (STREAM && e0 >= 0 && e0 + APPLY_WAVE <= V) {
+        uint32_t mixed = part | (part >> 1), open = word & (word >> 1);
+        mixed |= mixed >> 2; open &= open >> 2;
+        if (EPV == 8) { mixed |= mixed >> 4; open &= open >> 4; }
+        constexpr uint32_t FIRST = EPV == 8 ? 0x01010101u : 0x11111111u;
+        if (__popcll(__ballot((mixed & FIRST) != 0)) >= APPLY_DENSE_MIXED && __popcll(__ballot(2 * __popc(open & FIRST) > STEPS)) <= APPLY_DENSE_OPEN) {
+            Vec4 x[STEPS];
+            uint32_t bits[STEPS];
+#pragma unroll
+            for (int j = 0; j < STEPS; ++j) {
+                const int v = j * 64 + lane;
+                bits[j] = ((uint32_t)__shfl((int)word, v / STEPS) >> (v % STEPS * EPV)) & ALL;
+                x[j] = none;
+                if (bits[j] != 0) x[j] = __builtin_nontemporal_load(reinterpret_cast<const Vec4*>(piece) + v);
+            }
+#pragma unroll
+            for (int j = 0; j < STEPS; ++j) {
+                merge(x[j], bits[j]);
+                __builtin_nontemporal_store(x[j], reinterpret_cast<Vec4*>(piece) + j * 64 + lane);
+            }
+            return;
+        }
+    }
     Vec4 x[STEPS];
     uint32_t bits[STEPS];
 #pragma unroll
@@ -1935,14 +1978,7 @@ __global__ __launch_bounds__(64 * APPLY_WAVES) void k_apply_vec(E* logits, long 
             for (int c = 0; c < EPV; ++c) if (!((bits[j] >> c) & 1)) row[e + c] = ApplyE<E>::NINF;
             continue;
         }
-        if (sizeof(E) == 4) {
-            _Pragma("unroll") for (int c = 0; c < 4; ++c) if (!((bits[j] >> c) & 1)) x[j][c] = NI;
-        } else {
-            _Pragma("unroll") for (int c = 0; c < 4; ++c) {
-                if (!((bits[j] >> (2 * c)) & 1)) x[j][c] = (x[j][c] & 0xFFFF0000u) | 0xFF80u;
-                if (!((bits[j] >> (2 * c)) & 2)) x[j][c] = (x[j][c] & 0x0000FFFFu) | 0xFF800000u;
-            }
-        }
+        merge(x[j], bits[j]);
         Vec4* const to = reinterpret_cast<Vec4*>(piece) + v;
         if (STREAM) __builtin_nontemporal_store(x[j], to);
         else *to = x[j];
