@@ -33,16 +33,16 @@ HBM_PEAK_GBS = 8000.0
 # with.  The same counters read 303,884 (FETCH_SIZE) and 607,744 (WRITE_SIZE) for a device-to-device copy of 607,744 KiB,
 # hence the scale factors to KiB.  The summaries under profiles/ hold the commands and the full tables.
 PMC = {
-    "sources_sha256": "17bcad990806d3c3e54d17b8951a803ff2842b90d2641eb2e59c3beca182eca9",
+    "sources_sha256": "6aa4a0f6d16be9274b5df79f0e0b5f249214b9677b87bbc37d0d181c439cfdd5",
     "fetch_scale": 2.00, "write_scale": 1.00,
-    "k_build": (11019.0, 4800.5),
-    "k_fill": (3557.6, 19288.9),
-    "k_apply_vec<bf16>": (97592.9, 303893.9),
-    "k_apply_vec<fp32>": (179386.4, 605733.8),
-    "k_build_tagdispatch": (144073.0, 689897.5),
+    "k_build": (11022.0, 4800.5),
+    "k_fill": (3407.7, 19286.7),
+    "k_apply_vec<bf16>": (97602.5, 303876.0),
+    "k_apply_vec<fp32>": (179397.0, 607881.8),
+    "k_build_tagdispatch": (144203.5, 689897.5),
     # wave instructions of one k_build launch (rocprofv3 --pmc SQ_INSTS_VALU; SQ_INSTS_SALU + SQ_INSTS_SMEM + SQ_INSTS_BRANCH)
-    "k_build_valu_instructions": 12898560.0, "k_build_scalar_and_branch_instructions": 17288610.0,
-    "k_build_tagdispatch_valu_instructions": 848041696.0, "k_build_tagdispatch_scalar_and_branch_instructions": 1115408341.0,
+    "k_build_valu_instructions": 12736009.0, "k_build_scalar_and_branch_instructions": 16452309.0,
+    "k_build_tagdispatch_valu_instructions": 837465160.0, "k_build_tagdispatch_scalar_and_branch_instructions": 1065553567.0,
 }
 KERNEL_SOURCES = ("csrc/kernels.hip", "csrc/earley_core.hpp", "csrc/device.hpp", "build.py")   # code and compiler flags
 
