@@ -758,13 +758,16 @@ int32_t report_undecided_pairs() {
     std::lock_guard<std::mutex> lk(W.mu);
     if (!W.pending.active) return XG2_OK;
     if (hipEventSynchronize(W.pending.slot->done) != hipSuccess) return XG2_OK;
-    W.pending.active = false;
-    if (!W.pending.slot->res_host[0]) return XG2_OK;
-    uint32_t n = 0;
-    while (n < kUnresolvedCap && W.pending.slot->res_host[2 + 2 * n] != 0xFFFFFFFFu) ++n;
-    return fail(XG2_EOVERFLOW, "the previous xg2_fill_next_token_bitmask call left " + std::to_string(n) + (W.pending.slot->res_host[1] ? "+" : "") +
-                               " (row, token) pairs undecided: their Earley item sets exceed the large-capacity lists, and their mask bits are 0 "
-                               "(xg2_fill_resolve_overflow decides them with the host parser)");
+    int32_t rc = XG2_OK;
+    if (W.pending.slot->res_host[0]) {
+        uint32_t n = 0;
+        while (n < kUnresolvedCap && W.pending.slot->res_host[2 + 2 * n] != 0xFFFFFFFFu) ++n;
+        rc = fail(XG2_EOVERFLOW, "the previous xg2_fill_next_token_bitmask call left " + std::to_string(n) + (W.pending.slot->res_host[1] ? "+" : "") +
+                                 " (row, token) pairs undecided: their Earley item sets exceed the large-capacity lists, and their mask bits are 0 "
+                                 "(xg2_fill_resolve_overflow decides them with the host parser)");
+    }
+    W.pending.active = false;                               // (after the message, which may find no memory: then the next call reports it)
+    return rc;
 }
 
 // Whether the call above would wait: there is such a fill, and it has not ended.
@@ -2076,58 +2079,66 @@ static int32_t accept_one(xg2_matcher* m, int32_t token_id) {
     });
 }
 int32_t xg2_matcher_accept_tokens(xg2_matcher* const* matchers, const int32_t* token_ids, int32_t B, int32_t* status_host) {
-    if (B < 0 || (B > 0 && (!matchers || !token_ids || !status_host))) return fail(XG2_EINVAL, "xg2_matcher_accept_tokens: bad argument");
-    for (int32_t b = 0; b < B; ++b) if (!matchers[b]) return fail(XG2_EINVAL, "xg2_matcher_accept_tokens: null matcher");
-    // While the fill before is still running the tokens are parsed beside it, and what it left undecided is asked for afterwards: if
-    // anything, the matchers go back to where they were and the call fails as if it had asked first.  (Waiting first, a just-in-time
-    // step of 64 rows took the device's 55 - 70 us and then the parser's: a compile and twelve steps 2,490 - 2,550 us, now 2,210 - 2,330.
-    // Of 256 rows the parser's shares begin after the fill all the same: 172 / 166 and 175 / 174.)
-    const bool beside = fill_under_way();
-    if (!beside) if (int32_t rc = report_undecided_pairs()) return rc;
-    struct Before { size_t sets; bool terminated; };
-    std::vector<Before> before;
-    std::vector<int32_t> status_beside;
-    if (beside) {
-        before.reserve((size_t)B);
-        for (int32_t b = 0; b < B; ++b) before.push_back({matchers[b]->p->chart.length(), matchers[b]->p->terminated});
-        status_beside.resize((size_t)B);
-    }
-    int32_t* const status = beside ? status_beside.data() : status_host;
-    // matchers are independent: a few host threads each take a contiguous share (a handle listed twice would race)
-    std::atomic<bool> failed{false};
-    std::string what;
-    std::mutex what_mu;
-    const int32_t share = 32;                                   // matchers per part: small enough to balance, large enough to amortise the hand-over
-    const int32_t parts = (B + share - 1) / share;
-    const std::function<void(int32_t)> work = [&](int32_t part) {
-        try {
-            for (int32_t b = part * share; b < std::min(B, (part + 1) * share); ++b) {
-                status[b] = token_ids[b] < 0 ? XG2_OK : accept_one(matchers[b], token_ids[b]);
-                prepare_matcher(*matchers[b]->p);               // the next fill finds the state ready
+    return guarded([&]() -> int32_t {
+        if (B < 0 || (B > 0 && (!matchers || !token_ids || !status_host))) return fail(XG2_EINVAL, "xg2_matcher_accept_tokens: bad argument");
+        for (int32_t b = 0; b < B; ++b) if (!matchers[b]) return fail(XG2_EINVAL, "xg2_matcher_accept_tokens: null matcher");
+        // While the fill before is still running the tokens are parsed beside it, and what it left undecided is asked for afterwards: if
+        // anything, the matchers go back to where they were and the call fails as if it had asked first.  (Waiting first, a just-in-time
+        // step of 64 rows took the device's 55 - 70 us and then the parser's: a compile and twelve steps 2,490 - 2,550 us, now 2,210 - 2,330.
+        // Of 256 rows the parser's shares begin after the fill all the same: 172 / 166 and 175 / 174.)
+        const bool beside = fill_under_way();
+        if (!beside) if (int32_t rc = report_undecided_pairs()) return rc;
+        struct Before { size_t sets; bool terminated; };
+        struct Undo {
+            xg2_matcher* const* matchers;
+            std::vector<Before> before;
+            bool wanted = false;
+            ~Undo() {
+                for (size_t b = 0; wanted && b < before.size(); ++b) {
+                    MatcherImpl& M = *matchers[b]->p;
+                    if (M.chart.length() == before[b].sets && M.terminated == before[b].terminated) continue;
+                    M.chart.cut(before[b].sets);
+                    M.terminated = before[b].terminated;
+                    M.prep.valid = false;
+                }
             }
-        } catch (const std::exception& e) {
-            failed = true;
-            std::lock_guard<std::mutex> lk(what_mu);
-            what = e.what();
+        } undo{matchers, {}};
+        std::vector<int32_t> status_beside;
+        if (beside) {
+            undo.before.reserve((size_t)B);
+            for (int32_t b = 0; b < B; ++b) undo.before.push_back({matchers[b]->p->chart.length(), matchers[b]->p->terminated});
+            status_beside.resize((size_t)B);
+            undo.wanted = true;
         }
-    };
-    if (parts <= 2) { for (int32_t p = 0; p < parts; ++p) work(p); }
-    else host_workers().run(parts, work);
-    if (beside) {
-        if (int32_t rc = report_undecided_pairs()) {
-            for (int32_t b = 0; b < B; ++b) {
-                MatcherImpl& M = *matchers[b]->p;
-                if (M.chart.length() == before[(size_t)b].sets && M.terminated == before[(size_t)b].terminated) continue;
-                M.chart.cut(before[(size_t)b].sets);
-                M.terminated = before[(size_t)b].terminated;
-                M.prep.valid = false;
+        int32_t* const status = beside ? status_beside.data() : status_host;
+        // matchers are independent: a few host threads each take a contiguous share (a handle listed twice would race)
+        std::atomic<bool> failed{false};
+        std::string what;
+        std::mutex what_mu;
+        const int32_t share = 32;                               // matchers per part: small enough to balance, large enough to amortise the hand-over
+        const int32_t parts = (B + share - 1) / share;
+        const std::function<void(int32_t)> work = [&](int32_t part) {
+            try {
+                for (int32_t b = part * share; b < std::min(B, (part + 1) * share); ++b) {
+                    status[b] = token_ids[b] < 0 ? XG2_OK : accept_one(matchers[b], token_ids[b]);
+                    prepare_matcher(*matchers[b]->p);           // the next fill finds the state ready
+                }
+            } catch (const std::exception& e) {
+                failed = true;
+                std::lock_guard<std::mutex> lk(what_mu);
+                what = e.what();
             }
-            return rc;
+        };
+        if (parts <= 2) { for (int32_t p = 0; p < parts; ++p) work(p); }
+        else host_workers().run(parts, work);
+        if (beside) {
+            if (int32_t rc = report_undecided_pairs()) return rc;
+            undo.wanted = false;
+            std::copy(status_beside.begin(), status_beside.end(), status_host);
         }
-        std::copy(status_beside.begin(), status_beside.end(), status_host);
-    }
-    if (failed) return fail(XG2_EINVAL, "xg2_matcher_accept_tokens: " + what);
-    return XG2_OK;
+        if (failed) return fail(XG2_EINVAL, "xg2_matcher_accept_tokens: " + what);
+        return XG2_OK;
+    });
 }
 int32_t xg2_matcher_reset(xg2_matcher* m) {
     if (!m) return fail(XG2_EINVAL, "xg2_matcher_reset: null matcher");
