@@ -2088,29 +2088,26 @@ int32_t xg2_matcher_accept_tokens(xg2_matcher* const* matchers, const int32_t* t
         // Of 256 rows the parser's shares begin after the fill all the same: 172 / 166 and 175 / 174.)
         const bool beside = fill_under_way();
         if (!beside) if (int32_t rc = report_undecided_pairs()) return rc;
-        struct Before { size_t sets; bool terminated; };
+        struct Row { size_t sets; bool terminated; int32_t status; };    // where the matcher was; and until the call is settled what the caller will read
         struct Undo {
             xg2_matcher* const* matchers;
-            std::vector<Before> before;
+            std::vector<Row> rows;
             bool wanted = false;
             ~Undo() {
-                for (size_t b = 0; wanted && b < before.size(); ++b) {
+                for (size_t b = 0; wanted && b < rows.size(); ++b) {
                     MatcherImpl& M = *matchers[b]->p;
-                    if (M.chart.length() == before[b].sets && M.terminated == before[b].terminated) continue;
-                    M.chart.cut(before[b].sets);
-                    M.terminated = before[b].terminated;
+                    if (M.chart.length() == rows[b].sets && M.terminated == rows[b].terminated) continue;
+                    M.chart.cut(rows[b].sets);
+                    M.terminated = rows[b].terminated;
                     M.prep.valid = false;
                 }
             }
         } undo{matchers, {}};
-        std::vector<int32_t> status_beside;
         if (beside) {
-            undo.before.reserve((size_t)B);
-            for (int32_t b = 0; b < B; ++b) undo.before.push_back({matchers[b]->p->chart.length(), matchers[b]->p->terminated});
-            status_beside.resize((size_t)B);
+            undo.rows.reserve((size_t)B);
+            for (int32_t b = 0; b < B; ++b) undo.rows.push_back({matchers[b]->p->chart.length(), matchers[b]->p->terminated, status_host[b]});
             undo.wanted = true;
         }
-        int32_t* const status = beside ? status_beside.data() : status_host;
         // matchers are independent: a few host threads each take a contiguous share (a handle listed twice would race)
         std::atomic<bool> failed{false};
         std::string what;
@@ -2120,7 +2117,7 @@ int32_t xg2_matcher_accept_tokens(xg2_matcher* const* matchers, const int32_t* t
         const std::function<void(int32_t)> work = [&](int32_t part) {
             try {
                 for (int32_t b = part * share; b < std::min(B, (part + 1) * share); ++b) {
-                    status[b] = token_ids[b] < 0 ? XG2_OK : accept_one(matchers[b], token_ids[b]);
+                    (beside ? undo.rows[(size_t)b].status : status_host[b]) = token_ids[b] < 0 ? XG2_OK : accept_one(matchers[b], token_ids[b]);
                     prepare_matcher(*matchers[b]->p);           // the next fill finds the state ready
                 }
             } catch (const std::exception& e) {
@@ -2134,7 +2131,7 @@ int32_t xg2_matcher_accept_tokens(xg2_matcher* const* matchers, const int32_t* t
         if (beside) {
             if (int32_t rc = report_undecided_pairs()) return rc;
             undo.wanted = false;
-            std::copy(status_beside.begin(), status_beside.end(), status_host);
+            for (int32_t b = 0; b < B; ++b) status_host[b] = undo.rows[(size_t)b].status;    // (of a row that was not reached, what was there)
         }
         if (failed) return fail(XG2_EINVAL, "xg2_matcher_accept_tokens: " + what);
         return XG2_OK;

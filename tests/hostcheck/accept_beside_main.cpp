@@ -144,10 +144,40 @@ static void allocations() {
         }
 }
 
+// Where the call ends early, the statuses of the rows it has not come to are left as the caller had them, and so for a fill that has ended.
+static void statuses() {
+    int ended_early = 0;
+    for (bool running : {false, true})
+        for (long n = 0;; ++n) {
+            CHECK(n < 1000);
+            auto ms = some_matchers(3);
+            fill(ms);
+            if (!running) ended = enqueued.load();
+            const int32_t ids[3] = {LONG, LONG, LONG};
+            int32_t status[3] = {77, 78, 79};
+            const size_t before = length(ms[0]);
+            countdown = n;
+            const int32_t rc = xg2_matcher_accept_tokens(ms.data(), ids, 3, status);
+            const bool reached = countdown < 0;
+            countdown = -1;
+            if (rc != XG2_OK) {
+                ++ended_early;
+                for (int b = 0; b < 3; ++b) {
+                    if (length(ms[(size_t)b]) == before) CHECK(status[b] == 77 + b || status[b] == XG2_EOVERFLOW);
+                    else CHECK(status[b] == XG2_OK || status[b] == XG2_EOVERFLOW);
+                }
+            }
+            for (xg2_matcher* m : ms) xg2_matcher_destroy(m);
+            if (!reached) break;
+        }
+    CHECK(ended_early > 6);
+}
+
 int main(int argc, char** argv) {
     setup();
     const std::string mode = argc > 1 ? argv[1] : "";
     if (mode == "allocations") allocations();
+    else if (mode == "statuses") statuses();
     else return 2;
     std::printf("ok\n");
     std::fflush(stdout);
