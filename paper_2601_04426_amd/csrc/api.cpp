@@ -680,6 +680,7 @@ struct FillSlot {
     uint8_t* host = nullptr; uint8_t* dev = nullptr; size_t cap = 0;
     hipEvent_t done = nullptr; bool in_flight = false;
     uint32_t* res_host = nullptr;                           // pinned: {any, more than fit, pairs ...} written by the large-capacity re-check
+    bool claimed = false;                                   // a call has yet to read them (ClaimedFill): the slot is not handed out
 };
 struct MatcherImpl;
 struct FillWorkspace {
@@ -697,6 +698,7 @@ struct FillWorkspace {
     bool any = false;                                       // there has been a fill
     // the latest fill whose undecided pairs nobody has looked at yet: its slot and its matchers
     struct Pending { bool active = false; FillSlot* slot = nullptr; std::vector<MatcherImpl*> matchers; } pending;
+    std::condition_variable released;                       // a slot is no longer claimed
     // waits for the device work of the latest fill
     void wait_last() {
         HIP_CHECK(hipDeviceSynchronize());                  // its stream may be gone by now
@@ -729,7 +731,7 @@ struct FillWorkspace {
         }
         return (float)((double)(last - first) / stamps_per_us);
     }
-    FillSlot& acquire(size_t bytes) {
+    FillSlot& acquire(size_t bytes) {                       // (the caller has waited until slots[next] is not claimed)
         FillSlot& s = slots[next];
         next = (next + 1) % 4;
         if (!s.done) HIP_CHECK(hipEventCreateWithFlags(&s.done, hipEventDisableTiming));
@@ -752,30 +754,63 @@ FillWorkspace& fill_ws() { static FillWorkspace* w = new FillWorkspace(); return
 // A fill call returns before its kernels run.  If the large-capacity re-check could not decide some (row, token) pair
 // (item sets beyond even its lists), the mask has a 0 where a 1 may belong: the next call that touches matchers or masks
 // fails with XG2_EOVERFLOW, once, unless xg2_fill_resolve_overflow has decided the pairs on the host in between.
+// Of a fill that has ended; the caller holds the workspace's lock.
+int32_t undecided_pairs(const FillSlot& slot) {
+    if (!slot.res_host[0]) return XG2_OK;
+    uint32_t n = 0;
+    while (n < kUnresolvedCap && slot.res_host[2 + 2 * n] != 0xFFFFFFFFu) ++n;
+    return fail(XG2_EOVERFLOW, "the previous xg2_fill_next_token_bitmask call left " + std::to_string(n) + (slot.res_host[1] ? "+" : "") +
+                               " (row, token) pairs undecided: their Earley item sets exceed the large-capacity lists, and their mask bits are 0 "
+                               "(xg2_fill_resolve_overflow decides them with the host parser)");
+}
 // The caller holds no lock.
 int32_t report_undecided_pairs() {
     FillWorkspace& W = fill_ws();
     std::lock_guard<std::mutex> lk(W.mu);
     if (!W.pending.active) return XG2_OK;
     if (hipEventSynchronize(W.pending.slot->done) != hipSuccess) return XG2_OK;
-    int32_t rc = XG2_OK;
-    if (W.pending.slot->res_host[0]) {
-        uint32_t n = 0;
-        while (n < kUnresolvedCap && W.pending.slot->res_host[2 + 2 * n] != 0xFFFFFFFFu) ++n;
-        rc = fail(XG2_EOVERFLOW, "the previous xg2_fill_next_token_bitmask call left " + std::to_string(n) + (W.pending.slot->res_host[1] ? "+" : "") +
-                                 " (row, token) pairs undecided: their Earley item sets exceed the large-capacity lists, and their mask bits are 0 "
-                                 "(xg2_fill_resolve_overflow decides them with the host parser)");
-    }
+    const int32_t rc = undecided_pairs(*W.pending.slot);
     W.pending.active = false;                               // (after the message, which may find no memory: then the next call reports it)
     return rc;
 }
-
-// Whether the call above would wait: there is such a fill, and it has not ended.
-bool fill_under_way() {
-    FillWorkspace& W = fill_ws();
-    std::lock_guard<std::mutex> lk(W.mu);
-    return W.pending.active && hipEventQuery(W.pending.slot->done) == hipErrorNotReady;
-}
+// The same in two halves: a call that finds the fill still running takes its report over, works beside it and asks afterwards.  To
+// other threads' calls the fill is reported from then on: none of them takes this call's report, nor this call that of a fill of theirs.
+class ClaimedFill {
+    FillSlot* slot = nullptr;
+    void release(bool reported) {
+        FillWorkspace& W = fill_ws();
+        slot->claimed = false;
+        if (!reported && W.pending.slot == slot) W.pending.active = true;       // (else a later fill stands there)
+        slot = nullptr;
+        W.released.notify_all();
+    }
+  public:
+    ClaimedFill() = default;
+    ClaimedFill(const ClaimedFill&) = delete;
+    ClaimedFill& operator=(const ClaimedFill&) = delete;
+    ~ClaimedFill() {
+        if (!slot) return;
+        std::lock_guard<std::mutex> lk(fill_ws().mu);
+        release(false);
+    }
+    // false: there is no fill to report, or it has ended (report_undecided_pairs() need not wait)
+    bool take() {
+        FillWorkspace& W = fill_ws();
+        std::lock_guard<std::mutex> lk(W.mu);
+        if (!W.pending.active || hipEventQuery(W.pending.slot->done) != hipErrorNotReady) return false;
+        slot = W.pending.slot;
+        slot->claimed = true;
+        W.pending.active = false;
+        return true;
+    }
+    int32_t report() {
+        if (hipEventSynchronize(slot->done) != hipSuccess) return XG2_OK;
+        std::lock_guard<std::mutex> lk(fill_ws().mu);
+        const int32_t rc = undecided_pairs(*slot);
+        release(true);
+        return rc;
+    }
+};
 
 // A few host threads that stay around between calls (starting threads costs more than the work of a decode step).
 // run(parts, job) calls job(0 .. parts - 1), the caller taking shares too, and returns when all are done; calls are
@@ -2086,7 +2121,8 @@ int32_t xg2_matcher_accept_tokens(xg2_matcher* const* matchers, const int32_t* t
         // anything, the matchers go back to where they were and the call fails as if it had asked first.  (Waiting first, a just-in-time
         // step of 64 rows took the device's 55 - 70 us and then the parser's: a compile and twelve steps 2,490 - 2,550 us, now 2,210 - 2,330.
         // Of 256 rows the parser's shares begin after the fill all the same: 172 / 166 and 175 / 174.)
-        const bool beside = fill_under_way();
+        ClaimedFill fill;
+        const bool beside = fill.take();
         if (!beside) if (int32_t rc = report_undecided_pairs()) return rc;
         struct Row { size_t sets; bool terminated; int32_t status; };    // where the matcher was; and until the call is settled what the caller will read
         struct Undo {
@@ -2129,7 +2165,7 @@ int32_t xg2_matcher_accept_tokens(xg2_matcher* const* matchers, const int32_t* t
         if (parts <= 2) { for (int32_t p = 0; p < parts; ++p) work(p); }
         else host_workers().run(parts, work);
         if (beside) {
-            if (int32_t rc = report_undecided_pairs()) return rc;
+            if (int32_t rc = fill.report()) return rc;
             undo.wanted = false;
             for (int32_t b = 0; b < B; ++b) status_host[b] = undo.rows[(size_t)b].status;    // (of a row that was not reached, what was there)
         }
@@ -2323,7 +2359,9 @@ int32_t fill_common(xg2_matcher* const* matchers, int32_t B, int32_t* bitmask_de
             const std::shared_ptr<BuildTicket>& last = build_chain().last;
             if (last && last != waited && last->state == 0 && last->staging && last->stream != stream) HIP_CHECK(hipStreamWaitEvent(stream, last->staging->ev[4], 0));
         }
-        std::lock_guard<std::mutex> ws_lock(fill_ws().mu);
+        std::unique_lock<std::mutex> ws_lock(fill_ws().mu);
+        // (before the scratch is locked: whoever holds a claim needs only the workspace to give it back)
+        if (!no_alloc) fill_ws().released.wait(ws_lock, [] { FillWorkspace& W = fill_ws(); return !W.slots[W.next].claimed; });
         std::lock_guard<std::mutex> slow_lock(slow().mu);
         auto pack = [&](uint8_t* host) {
             std::memcpy(host + o_rows, rows.data(), rows.size() * sizeof(FillRow));

@@ -173,11 +173,54 @@ static void statuses() {
     CHECK(ended_early > 6);
 }
 
+// Another thread's calls while this one parses: the fill that was under way is this call's to report, and no other fill is.
+static xg2_matcher* other;
+static std::thread other_thread;
+static std::atomic<int> other_fills{0};
+static int32_t other_rc;
+static void threads() {
+    auto ms = some_matchers(2), theirs = some_matchers(1);
+    other = theirs[0];
+    const int32_t ids[2] = {LONG, A};
+    int32_t status[2];
+    const size_t before = length(ms[0]);
+
+    // a call that would have taken the report
+    leave_undecided = true;
+    fill(ms);
+    leave_undecided = false;
+    after_query = [] { std::thread([] { other_rc = xg2_matcher_accept_token(other, A); }).join(); };
+    CHECK(undecided_error(xg2_matcher_accept_tokens(ms.data(), ids, 2, status)));
+    CHECK(after_query == nullptr && other_rc == XG2_OK && length(other) == before + 1);
+    CHECK(length(ms[0]) == before && length(ms[1]) == before);
+
+    // a fill of its own, with undecided pairs: reported to the call after
+    fill(ms);
+    after_query = [] { std::thread([] { leave_undecided = true; fill({other}); leave_undecided = false; }).join(); };
+    CHECK(xg2_matcher_accept_tokens(ms.data(), ids, 2, status) == XG2_OK && status[0] == XG2_OK && status[1] == XG2_OK);
+    CHECK(after_query == nullptr && length(ms[0]) == before + 4 && length(ms[1]) == before + 1);
+    CHECK(undecided_error(xg2_matcher_accept_token(other, A)) && xg2_matcher_accept_token(other, A) == XG2_OK);
+
+    // more fills than there are staging slots: the one whose outcome this call has yet to read is not handed out again
+    leave_undecided = true;
+    fill(ms);
+    leave_undecided = false;
+    after_query = [] {
+        other_thread = std::thread([] { for (int k = 0; k < 9; ++k) { fill({other}); ++other_fills; } });
+        while (other_fills < 3) std::this_thread::yield();
+    };
+    CHECK(undecided_error(xg2_matcher_accept_tokens(ms.data(), ids, 2, status)));
+    CHECK(after_query == nullptr && length(ms[0]) == before + 4);
+    other_thread.join();
+    CHECK(other_fills == 9 && xg2_matcher_accept_tokens(ms.data(), ids, 2, status) == XG2_OK);
+}
+
 int main(int argc, char** argv) {
     setup();
     const std::string mode = argc > 1 ? argv[1] : "";
     if (mode == "allocations") allocations();
     else if (mode == "statuses") statuses();
+    else if (mode == "threads") threads();
     else return 2;
     std::printf("ok\n");
     std::fflush(stdout);

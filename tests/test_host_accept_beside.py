@@ -21,7 +21,7 @@ def exe(tmp_path_factory):
     return out
 
 
-@pytest.mark.parametrize("mode", ["allocations", "statuses"])
+@pytest.mark.parametrize("mode", ["allocations", "statuses", "threads"])
 def test_accept_beside_a_fill(exe, mode):
     env = dict(os.environ, ASAN_OPTIONS="detect_leaks=0:alloc_dealloc_mismatch=0")
     env.pop("LD_PRELOAD", None)
