@@ -241,19 +241,20 @@ def main() -> int:
         acc["build_kernel_ms"].append(ck.stats.kernel_ms)
         del ck
 
-    # the last step's bitmask: fraction of logits masked, and the bytes the apply kernel moves for it (a 16-byte vector of
-    # logits whose tokens are all allowed is neither read nor written, one whose tokens are all masked is written
-    # without a read, a mixed one is read and written back)
+    # the last step's bitmask: fraction of logits masked, and a reference count of bytes for it by whole 16-byte vectors of
+    # logits: nothing for one whose tokens are all allowed, one write for one whose tokens are all masked, a read and a write for a
+    # mixed one.  (Not what the kernel moves: it stores few masked tokens one by one, and reads and writes pieces with many
+    # mixed vectors whole; `traffic` is what the counters say.)
     bm = bitmask.cpu().numpy().view(np.uint32)
     bm_bytes = bm.view(np.uint8).reshape(B, W * 4)[:, :V // 8]       # one byte = the 8 tokens of one bf16 vector
     allowed = int(np.unpackbits(bm.view(np.uint8)).sum())
     masked = B * V - allowed
-    moved = {}
+    by_vector = {}
     n8_zero, n8_full = int((bm_bytes == 0).sum()), int((bm_bytes == 0xFF).sum())
-    moved[2] = B * W * 4 + 16 * n8_zero + 32 * (bm_bytes.size - n8_zero - n8_full) + 2 * B * (V % 8)
+    by_vector[2] = B * W * 4 + 16 * n8_zero + 32 * (bm_bytes.size - n8_zero - n8_full) + 2 * B * (V % 8)
     nib = np.stack([bm_bytes & 0xF, bm_bytes >> 4])
     n4_zero, n4_full = int((nib == 0).sum()), int((nib == 0xF).sum())
-    moved[4] = B * W * 4 + 16 * n4_zero + 32 * (nib.size - n4_zero - n4_full) + 4 * B * (V % 8)
+    by_vector[4] = B * W * 4 + 16 * n4_zero + 32 * (nib.size - n4_zero - n4_full) + 4 * B * (V % 8)
 
     mean = lambda xs: float(sum(xs) / len(xs))
     med = lambda xs: float(sorted(xs)[len(xs) // 2])
@@ -331,25 +332,26 @@ def main() -> int:
                            "note": "instruction counts from rocprofv3 SQ counters, valid for the kernel sources they were taken with (null otherwise)"}
     for name, key, e in (("roofline_apply_bf16", "apply_bf16_us", 2), ("roofline_apply_f32", "apply_f32_us", 4)):
         t = med(acc[key]) * 1e-6
-        gbs = moved[e] / t / 1e9
+        gbs = by_vector[e] / t / 1e9
         out[name] = {"kernel": "k_apply_vec", "bound": "hbm", "achieved": gbs, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": gbs / HBM_PEAK_GBS, "traffic": measured_traffic("k_apply_vec<bf16>" if e == 2 else "k_apply_vec<fp32>", default_workload),
-                     "algorithmic_bytes_per_launch": moved[e],
-                     "accounting": "bytes the kernel has to move for this bitmask: bitmask read + 16 B written per fully masked vector + 32 B read and "
-                                   "written per mixed vector (last step's bitmask)",
+                     "algorithmic_bytes_per_launch": by_vector[e],
+                     "accounting": "a reference count for this bitmask by whole vectors: bitmask read + 16 B written per fully masked vector + 32 B read and "
+                                   "written per mixed vector (last step's bitmask); the kernel moves less where few tokens are masked and more where it "
+                                   "reads and writes whole pieces: see traffic",
                      "achieved_read_modify_write_accounting": (B * W * 4 + 2 * B * V * e) / t / 1e9,
                      "achieved_store_only_accounting": (B * W * 4 + masked * e) / t / 1e9}
     tf = med(acc["fill_us"]) * 1e-6
     out["roofline_fill"] = {"kernel": "k_fill", "bound": "hbm", "achieved": B * W * 4 / tf / 1e9, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                             "frac": B * W * 4 / tf / 1e9 / HBM_PEAK_GBS, "traffic": measured_traffic("k_fill", default_workload),
                             "accounting": "bitmask write only, over the time between events around the fill call (union and re-check in one launch)"}
-    # fill + apply as one unit (the decode half of the metric): bitmask written once, then what apply moves
+    # fill + apply as one unit (the decode half of the metric): bitmask written once, then apply's reference count
     for name, key, e in (("roofline_fill_apply_bf16", "apply_bf16_us", 2), ("roofline_fill_apply_f32", "apply_f32_us", 4)):
         t = (med(acc["fill_us"]) + med(acc[key])) * 1e-6
-        gbs = (B * W * 4 + moved[e]) / t / 1e9
+        gbs = (B * W * 4 + by_vector[e]) / t / 1e9
         out[name] = {"kernel": "k_fill + k_apply_vec", "bound": "hbm", "achieved": gbs, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": gbs / HBM_PEAK_GBS, "traffic": None, "us_per_step": t * 1e6,
-                     "accounting": "bitmask write + the bytes apply moves (see roofline_apply_*), over the times between events around fill and apply"}
+                     "accounting": "bitmask write + the reference count of apply's bytes (see roofline_apply_*), over the times between events around fill and apply"}
 
     if not args.no_tagdispatch_build:
         # one cache build of the TagDispatch workload (64 tools, V = 128,256): a millisecond-scale launch of the same kernel
