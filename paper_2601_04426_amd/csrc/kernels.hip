@@ -1844,37 +1844,50 @@ __global__ __launch_bounds__(64) void k_accept(const FillRow* rows, const int32_
 // ---- apply -----------------------------------------------------------------------------------------
 // One wavefront per 2,048 tokens of a row (APPLY_WAVE), counted from the 128-byte boundary of memory at or before the row's
 // begin, so that rows of any length and base are accessed in whole aligned cache lines.  Each lane takes one mask word: a
-// piece that is allowed as a whole (most of free text) ends there, after one coalesced load.  Then 16-byte vectors (4 fp32 or
+// piece that is allowed as a whole (most of free text) ends there, after one coalesced load.  Otherwise a piece goes one of three ways.
+// Vector by vector, where neither of the two below is the better one: 16-byte vectors (4 fp32 or
 // 8 bf16), 64 a step, their bits from the lane that holds the word: a vector whose tokens are all allowed is left alone (no
 // read, no write); one whose tokens are all disallowed is overwritten without a read; only mixed vectors are read, merged and
 // written back, all reads before the first store.  Vectors that the row shares with its neighbours are done by the element.
 // Bound by memory (a large copy moves 5.4 TB/s on this card, a large fill 6.9), and where nothing is masked by instructions
 // issued, which is why a mask word is loaded once and not once per vector.  With a mask look-up per vector, and rows off a
 // 16-byte boundary done by the element, against now, us at 1,024 rows of V = 151,936 / 151,937, bf16: nothing masked 9.8 / 130
-// -> 6.2 / 7.3; nearly everything 80 / 204 -> 52 / 53; 5 % of the tokens 107 / 252 -> 97 / 98 (four
-// fifths of the 64-byte sectors hold a masked token and are read and written).
-// Where the mixed vectors of a piece hold few masked tokens these are stored one by one: nothing is read, a store need not wait for a
-// load, and a piece nearly all of which is allowed writes what it masks and no more.  Each lane goes through its own word, so the most
-// in one word counts.  Read and merged / one by one, us, random masks of V = 151,936, masked 0.05 / 0.5 / 2 / 5 %: 1,024 rows bf16
-// 18.3 / 34.9 / 70.6 / 97.4 -> 11.6 / 15.5 / 36.1 / 85.2, 256 rows fp32 7.2 / 13.1 / 22.3 / 35.2 -> 5.2 / 6.9 / 12.6 / 30.7.  Where nearly all is
-// masked the same spares small logits a wait (64 rows of a JSON schema, fp32, V = 32,000: the step 18.4 -> 17.5 us), but the memory pays
-// for a line that arrives in parts: 256 rows, fp32, over three sets of logits, 1 % allowed 43 -> 52 us, and beyond the last-level cache
-// 52 -> 72.  So beyond APPLY_LARGE_BYTES all masked tokens of a word count, and fewer of them.
-// Logits beyond the last-level cache, a piece many of whose vectors are mixed: all that are not masked as a whole are read, and all
-// are written, both past the caches.  A line that a store leaves with holes is merged in memory, which costs more than reading and writing
-// what was allowed; a line that is written whole need not stay in the second-level cache from load to store.  bf16, V = 151,936, masked 10 /
-// 50 / 90 %, us: the mixed ones alone against this, 1,024 rows, the same logits again 112 / 99 / 99 against 98, two sets in turn 135 / 120 / 120
-// against 98, with the pass that writes the logits and the one that reads them 206 / 193 / 193 against 196; 2,048 rows 290 / 247 / 249 against 196,
-// 288 / 251 / 251 against 196, 531 / 490 / 489 against 400.  The decoding step of 1,024 rows of records 131 -> 113.  (A quarter of the loads through the
-// caches: 93 at 1,024 rows and 184 - 218 at 2,048.)  Where more than half of a piece's vectors are allowed, or few are mixed (fp32, 512 rows, 2 %
-// allowed, 69 -> 78), the old way is the better one.  Within the last-level cache, 256 rows, fp32: 48 / 60 / 97 against 50 / 52 / 100 in the three
-// settings: left as it was.
+// -> 6.2 / 7.3; nearly everything 80 / 204 -> 52 / 53.
+// One by one, where the mixed vectors of a piece hold few masked tokens: nothing is read, a store need not wait for a
+// load, and a piece nearly all of which is allowed writes what it masks and no more; vectors masked as a whole are still stored as such.
+// Each lane goes through its own word, so the most in one word counts (APPLY_FEW_WORD), and every token is a store of its own, so their sum
+// counts too (of logits beyond 64 MB with the vectors masked as a whole: memory pays for lines that arrive in parts).
+// All, where many words of a piece of logits beyond the last-level cache are mixed and few are allowed as a whole: all that is not
+// masked as a whole is read, and all is written.  A line that a store leaves with holes is merged in memory, which costs more than reading
+// and writing what was allowed; a line that is written whole need not stay in the second-level cache from load to store.
+// Where the lines lie.  us, V = 151,936, medians of one process with the kernels in turn, in two settings: the same logits again / with the
+// copy that writes the logits and the maximum that reads them around the call, as an engine has it.
+// One by one, 64 words of a piece with k masked tokens each, by vectors -> one by one: bf16, 58 MB, k = 3, 4, 6: 21.8 -> 18.3 / 71.6 -> 68.1,
+// 22.0 -> 22.5 / 71.8 -> 72.2, 21.2 -> 30.8 / 71.1 -> 80.5; 32 words, k = 4, 6: 15.4 -> 12.9 / 65.5 -> 62.5, 15.2 -> 17.4 / 65.1 -> 66.9; so 40 tokens
+// and three a word.  fp32, 58 MB, 64 words, k = 4, 6, 8: 19.3 -> 15.9 / 66.2 -> 62.7, 19.8 -> 18.4 / 66.9 -> 65.2, 19.8 -> 22.1 / 67.0 -> 69.1;
+// 32 words, k = 4, 6, 8: 10.4 -> 9.2 / 58.7 -> 56.0, 10.3 -> 11.4 / 58.8 -> 58.1, 10.3 -> 13.7 / 58.6 -> 60.4: 80 and three.  148 MB, 64 words, k = 2, 3:
+// 43.6 -> 28.5 / 129.9 -> 128.2, 47.1 -> 34.0 / 131.6 -> 123.4, but over three sets of logits in turn 71.8 -> 68.8, 75.0 -> 78.6: 96 and one.
+// Beyond 256 MB: bf16, 297 MB, 16 words, k = 4, 6: 46.7 -> 27.2 / 241 -> 243, 46.3 -> 37.7 / 241 -> 250; 32 words, k = 3, 4: 72.6 -> 40.2 / 271 -> 274,
+// 73.2 -> 50.1 / 271 -> 277: 32 tokens and two a word.  fp32, 32 words, k = 3, 4: 52.1 -> 31.2 / 241 -> 237, 53.9 -> 32.9 / 240 -> 238, over three sets
+// 75 -> 80; 64 words, k = 1, 2: 82 -> 35 / 298 -> 276, 92 -> 53 / 296 -> 305 (all: 91 / 276): 96.
+// Up to 8 MB no sum is needed (fp32, 64 rows of 32,000, 64 words with 8: 5.5 -> 5.7 / 22.2 -> 20.9; counting cost the smallest steps 0.2 - 0.3).
+// All, by vectors -> all; words that are not named are allowed as a whole: bf16, 297 MB, 36 and 40 half masked words (others masked): not
+// taken 88.8 / 282, 90.5 -> 85.9 / 287 -> 271; 40 and 48 half masked (24 and 16 allowed): 76.9 -> 97.3 / 284 -> 273, 86.5 -> 91.8 / 297 -> 280.
+// 408 MB, 40 half masked (24 allowed): 146 -> 135 / 427 -> 397.  fp32, 297 MB, 48, 52 and 60 half masked (16, 12, 4 allowed): 78.1 -> 99.5 / 261 -> 271,
+// 83.7 -> 100.1 / even, 93.9 -> 89.6 / 294 -> 275 at 408 MB 393 -> 373: 8.  Half masked throughout, bf16, 297, 408 and 594 MB: 300 -> 278, 443 -> 395, 629 -> 553 (the second setting).
+// Half of a piece's loads go through the caches up to 384 MB, and none beyond: what the program wrote before the call is partly still in the
+// last-level cache.  By vectors / half through / none, masks of a list of records, second setting, bf16: 297 MB 257 / 258 / 266, 371 MB
+// 352 / 346 / 350, 445 MB 417 / 406 / 411, 594 MB 558 / 540 / 534; fp32: 254 / 256 / 266, 322 / 321 / 330, 396 / 389 / 392, 546 / 532 / 520; the same records
+// beside rows with a third masked at random, 445 MB, bf16 458 / 430 / 426, fp32 427 / 412 / 405.  (Masks of tools, few pieces of which are
+// mixed, gain nothing: 237 / 238 at 297 MB, and with the same logits again 38 / 42.)  Within the last-level cache, 256 rows, fp32, by vectors
+// and all: 48 and 50, over three sets 60 and 52, second setting 97 and 100: left as it was.
 constexpr int APPLY_WAVE = 64 * 32, APPLY_WAVES = 4;
-// Where the logits of a call end up: small ones stay in the caches, large ones fit the last-level cache (256 MB) but share it with what
-// else the program touches between two steps, and what is beyond it is streamed past it.
-enum ApplySize { APPLY_SMALL, APPLY_LARGE, APPLY_STREAM };
-constexpr uint32_t APPLY_FEW_SMALL = 8, APPLY_FEW_LARGE = 4;
-constexpr int APPLY_DENSE_MIXED = 40, APPLY_DENSE_OPEN = 32;
+// Where the logits of a call end up: tiny and small ones stay in the caches, large ones fit the last-level cache (256 MB) but share it
+// with what else the program touches between two steps, what is beyond it is streamed past it, and of a huge one hardly anything is
+// left in it when it is asked for again.
+enum ApplySize { APPLY_TINY, APPLY_SMALL, APPLY_LARGE, APPLY_STREAM, APPLY_HUGE };
+constexpr uint32_t APPLY_FEW_WORD = 8;
+constexpr int APPLY_DENSE_MIXED = 40;
 template <class E> struct ApplyE;
 template <> struct ApplyE<uint32_t> { static constexpr uint32_t NINF = 0xFF800000u, NINF_WORD = 0xFF800000u; };
 template <> struct ApplyE<uint16_t> { static constexpr uint16_t NINF = 0xFF80; static constexpr uint32_t NINF_WORD = 0xFF80FF80u; };
@@ -1882,7 +1895,7 @@ typedef uint32_t Vec4 __attribute__((ext_vector_type(4)));
 
 template <class E, ApplySize SIZE>
 __global__ __launch_bounds__(64 * APPLY_WAVES) void k_apply_vec(E* logits, long long row_stride, int V, const uint32_t* bitmask, long long bm_stride) {
-    constexpr bool STREAM = SIZE == APPLY_STREAM;
+    constexpr bool STREAM = SIZE >= APPLY_STREAM, HALVES = sizeof(E) == 2;
     constexpr int EPV = 16 / sizeof(E), STEPS = 32 / EPV;
     constexpr uint32_t ALL = (1u << EPV) - 1, NI = ApplyE<E>::NINF_WORD;
     const long long b = blockIdx.y;
@@ -1911,7 +1924,19 @@ __global__ __launch_bounds__(64 * APPLY_WAVES) void k_apply_vec(E* logits, long 
     whole = (whole & (EPV == 8 ? 0x01010101u : 0x11111111u)) * ALL;
     uint32_t part = masked & ~whole;
     const Vec4 none{NI, NI, NI, NI};
-    if (__ballot((uint32_t)__popc(SIZE == APPLY_SMALL ? part : masked) > (SIZE == APPLY_SMALL ? APPLY_FEW_SMALL : APPLY_FEW_LARGE)) == 0) {
+    const uint32_t count = (uint32_t)__popc(SIZE <= APPLY_SMALL ? part : masked);
+    bool singly = __ballot(count > APPLY_FEW_WORD) == 0;
+    if (SIZE != APPLY_TINY && singly) {
+        const uint32_t words = (uint32_t)__popcll(__ballot(count != 0));
+        const uint32_t most = HALVES ? (!STREAM ? 40 + 3 * words : words < APPLY_DENSE_MIXED ? 32 + 2 * words : 48) : STREAM ? 96 : SIZE == APPLY_LARGE ? 96 + words : 80 + 3 * words;
+        if (APPLY_FEW_WORD * words > most) {                         // (else there is no need to count)
+            static_assert(APPLY_FEW_WORD < 16, "a count is four bits");
+            uint32_t total = 0;
+            _Pragma("unroll") for (int k = 0; k < 4; ++k) total += (uint32_t)__popcll(__ballot((count >> k) & 1u)) << k;
+            singly = total <= most;
+        }
+    }
+    if (singly) {
 #pragma unroll
         for (int j = 0; j < STEPS; ++j) {
             const int v = j * 64 + lane;
@@ -1938,20 +1963,19 @@ __global__ __launch_bounds__(64 * APPLY_WAVES) void k_apply_vec(E* logits, long 
         }
     };
     if (STREAM && e0 >= 0 && e0 + APPLY_WAVE <= V) {
-        uint32_t mixed = part | (part >> 1), open = word & (word >> 1);
-        mixed |= mixed >> 2; open &= open >> 2;
-        if (EPV == 8) { mixed |= mixed >> 4; open &= open >> 4; }
-        constexpr uint32_t FIRST = EPV == 8 ? 0x01010101u : 0x11111111u;
-        if (__popcll(__ballot((mixed & FIRST) != 0)) >= APPLY_DENSE_MIXED && __popcll(__ballot(2 * __popc(open & FIRST) > STEPS)) <= APPLY_DENSE_OPEN) {
+        if (__popcll(__ballot(part != 0)) >= APPLY_DENSE_MIXED && __popcll(__ballot(word == ~0u)) <= (!HALVES ? 8 : SIZE == APPLY_HUGE ? 24 : 16)) {
             Vec4 x[STEPS];
             uint32_t bits[STEPS];
+            const Vec4* const from = reinterpret_cast<const Vec4*>(piece) + lane;
 #pragma unroll
             for (int j = 0; j < STEPS; ++j) {
-                const int v = j * 64 + lane;
-                bits[j] = ((uint32_t)__shfl((int)word, v / STEPS) >> (v % STEPS * EPV)) & ALL;
+                bits[j] = ((uint32_t)__shfl((int)word, (j * 64 + lane) / STEPS) >> (lane % STEPS * EPV)) & ALL;
                 x[j] = none;
-                if (bits[j] != 0) x[j] = __builtin_nontemporal_load(reinterpret_cast<const Vec4*>(piece) + v);
             }
+            // (two loops: a load that the compiler makes of one through the caches and one past them goes through them)
+            constexpr int PAST = SIZE == APPLY_HUGE ? STEPS : STEPS / 2;
+            _Pragma("unroll") for (int j = 0; j < PAST; ++j) if (bits[j] != 0) x[j] = __builtin_nontemporal_load(from + j * 64);
+            _Pragma("unroll") for (int j = PAST; j < STEPS; ++j) if (bits[j] != 0) x[j] = from[j * 64];
 #pragma unroll
             for (int j = 0; j < STEPS; ++j) {
                 merge(x[j], bits[j]);
@@ -2161,7 +2185,7 @@ void launch_recheck_slow(const FillBatch& F, const DevVocab& Vd, int32_t* bitmas
 // Ordinary stores leave the logits in the last-level cache (256 MB), where the next pass over them finds them; logits that do
 // not fit there push each other out, and streaming stores take them straight to memory.  Ordinary / streaming, us, nearly
 // everything masked: 205 MB 33 / 39, 233 MB 39 / 40, 266 MB (below the line) 46 / 51, 273 MB (above) 57 / 46, 311 MB 70 / 52.
-constexpr long long APPLY_STREAM_BYTES = 256ll << 20, APPLY_LARGE_BYTES = 64ll << 20;
+constexpr long long APPLY_STREAM_BYTES = 256ll << 20, APPLY_HUGE_BYTES = 384ll << 20, APPLY_LARGE_BYTES = 64ll << 20, APPLY_TINY_BYTES = 8ll << 20;
 
 template <class E>
 static void launch_apply_as(E* logits, int32_t B, int32_t V, int64_t row_stride_elems, const uint32_t* bm, int64_t bm_row_stride_words, hipStream_t stream) {
@@ -2175,7 +2199,8 @@ static void launch_apply_as(E* logits, int32_t B, int32_t V, int64_t row_stride_
     // (1,024 rows, V = 151,936, bf16, nothing masked: 6.2 us against 17.5, which is how long it takes to start the workgroups)
     const uint32_t waves = (uint64_t)pieces * (uint32_t)B <= 512 ? 1 : APPLY_WAVES;
     const long long bytes = (long long)B * V * (int)sizeof(E);
-    auto* const kernel = bytes > APPLY_STREAM_BYTES ? k_apply_vec<E, APPLY_STREAM> : bytes > APPLY_LARGE_BYTES ? k_apply_vec<E, APPLY_LARGE> : k_apply_vec<E, APPLY_SMALL>;
+    auto* const kernel = bytes > APPLY_HUGE_BYTES ? k_apply_vec<E, APPLY_HUGE> : bytes > APPLY_STREAM_BYTES ? k_apply_vec<E, APPLY_STREAM>
+                         : bytes > APPLY_LARGE_BYTES ? k_apply_vec<E, APPLY_LARGE> : bytes > APPLY_TINY_BYTES ? k_apply_vec<E, APPLY_SMALL> : k_apply_vec<E, APPLY_TINY>;
     hipLaunchKernelGGL(kernel, dim3((pieces + waves - 1) / waves, B), dim3(64 * waves), 0, stream, logits, (long long)row_stride_elems, V, bm,
                        (long long)bm_row_stride_words);
 }

@@ -57,7 +57,7 @@ def test_few_masked_or_allowed(xg, dtype, kind, V):
 
 
 # 64 and 256 MB: what counts as few changes there
-@pytest.mark.parametrize("dtype,B,V", [("bf16", 220, 152001), ("bf16", 221, 152001), ("f32", 111, 150001), ("f32", 112, 150001), ("f32", 448, 150001)])
+@pytest.mark.parametrize("dtype,B,V", [("bf16", 220, 152001), ("bf16", 221, 152001), ("bf16", 884, 152001), ("f32", 111, 150001), ("f32", 112, 150001), ("f32", 448, 150001)])
 def test_few_in_large_logits(xg, dtype, B, V):
     import torch
     dev = torch.device("cuda:0")
@@ -71,6 +71,56 @@ def test_few_in_large_logits(xg, dtype, B, V):
     bm = torch.where(words >= 2 ** 31, words - 2 ** 32, words).to(torch.int32)
     want = logits.clone()
     want[masked[:, :V]] = ninf
+    xg.apply_token_bitmask(logits.data_ptr(), xg.XG2_BF16 if dtype == "bf16" else xg.XG2_F32, B, V, V, bm.data_ptr(), W,
+                           torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    assert torch.equal(logits, want)
+
+
+def _pieces(rng):
+    """[n, 64] words: pieces of 2,048 tokens around the numbers that decide how one is written, each three times with its words at other places:
+    (words with single masked tokens, how many such tokens in all, what the other words hold) and (half masked words, words allowed as a
+    whole, the others masked)."""
+    few = [(w, t, rest) for w, t in [(1, 8), (1, 9), (8, 48), (8, 49), (14, 110), (14, 111), (16, 64), (16, 65), (16, 88), (16, 89), (16, 128), (20, 100), (20, 101),
+                                     (20, 140), (20, 141), (32, 96), (32, 97), (39, 49), (39, 96), (39, 110), (39, 111), (40, 48), (40, 49), (48, 48), (49, 49),
+                                     (64, 64), (64, 96), (64, 97), (64, 160), (64, 161), (64, 232), (64, 233), (64, 272), (64, 273), (60, 480)] for rest in (0xFFFFFFFF, 0)]
+    half = [(n, o) for n in (38, 39, 40, 41, 56) for o in (0, 8, 9, 16, 17, 24, 25) if n + o <= 64] + [(47, 17), (48, 16), (55, 9)]
+    out = []
+    for _ in range(3):
+        for w, total, rest in few:
+            p = np.full(64, rest, dtype=np.uint32)
+            n = np.full(w, total // w) + (np.arange(w) < total % w)
+            for k, at in zip(n, rng.choice(64, size=w, replace=False)):
+                p[at] = 0xFFFFFFFF & ~sum(1 << int(b) for b in rng.choice(32, size=k, replace=False))
+            out.append(p)
+        for n, o in half:
+            p = np.zeros(64, dtype=np.uint32)
+            at = rng.permutation(64)
+            for a in at[:n]:
+                p[a] = sum(1 << int(b) for b in rng.choice(32, size=16, replace=False))
+            p[at[n:n + o]] = 0xFFFFFFFF
+            out.append(p)
+    return np.stack(out)
+
+
+# the last number of rows of one size of logits and the first of the next: 8, 64, 256 and 384 MB
+@pytest.mark.parametrize("dtype,B", [("bf16", 27), ("bf16", 28), ("bf16", 220), ("bf16", 221), ("bf16", 883), ("bf16", 884), ("bf16", 1325), ("bf16", 1326),
+                                     ("f32", 13), ("f32", 14), ("f32", 110), ("f32", 111), ("f32", 441), ("f32", 442), ("f32", 662), ("f32", 663)])
+def test_pieces_around_the_lines(xg, dtype, B):
+    import torch
+    dev = torch.device("cuda:0")
+    V, rng = 151936, np.random.default_rng(B)                       # (rows of whole 128-byte lines: words 64 k .. 64 k + 63 are a piece)
+    W = V // 32
+    pieces = torch.from_numpy(_pieces(rng).view(np.int32)).to(dev)
+    n = (W + 63) // 64
+    which = torch.from_numpy((np.arange(B * n) + rng.integers(len(pieces))).reshape(B, n) % len(pieces)).to(dev)
+    bm = pieces[which].reshape(B, n * 64)[:, :W].contiguous()
+    tt, ninf = (torch.int16, -128) if dtype == "bf16" else (torch.int32, -8388608)     # 0xFF80, 0xFF800000
+    logits = torch.randint(-2 ** 15, 2 ** 15, (B, V), generator=torch.Generator(device=dev).manual_seed(B), device=dev, dtype=tt)
+    want = torch.empty_like(logits)
+    for b in range(0, B, 128):
+        allowed = ((bm[b:b + 128, :, None] >> torch.arange(32, device=dev, dtype=torch.int32)) & 1).view(-1, V).bool()
+        want[b:b + 128] = torch.where(allowed, logits[b:b + 128], torch.tensor(ninf, device=dev, dtype=tt))
     xg.apply_token_bitmask(logits.data_ptr(), xg.XG2_BF16 if dtype == "bf16" else xg.XG2_F32, B, V, V, bm.data_ptr(), W,
                            torch.cuda.current_stream().cuda_stream)
     torch.cuda.synchronize()
