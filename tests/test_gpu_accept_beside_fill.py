@@ -53,12 +53,16 @@ def test_accept_beside_a_running_fill(xg, B, undecided):
     ids = np.array([[0, TOKS.index(b"b,a"), TOKS.index(b"x"), -1][b % 4] for b in range(B)], dtype=np.int32)
     ok = [np.unpackbits(oracle.pack_bitmask(orc.mask(h, va)).view(np.uint8), bitorder="little") for h in hist]
     want_status = np.array([0 if i < 0 or ok[b][i] else -3 for b, i in enumerate(ids)], dtype=np.int32)
+    xg.fill_next_token_bitmask(batch, bm.data_ptr(), vocab.words, stream)       # what the library allocates for such a batch is there
     torch.cuda.synchronize()
     try:
         if undecided:
             xg.debug_set_large_capacity(8, 12)
         keep = _busy(torch)
         xg.fill_next_token_bitmask(batch, bm.data_ptr(), vocab.words, stream)
+        filled = torch.cuda.Event()
+        filled.record()
+        assert not filled.query()               # the fill has not ended: the tokens below are parsed beside it
         if undecided:
             with pytest.raises(xg.Xg2Error) as err:
                 batch.accept_tokens(ids)
