@@ -33,13 +33,13 @@ HBM_PEAK_GBS = 8000.0
 # with.  The same counters read 303,884 (FETCH_SIZE) and 607,744 (WRITE_SIZE) for a device-to-device copy of 607,744 KiB,
 # hence the scale factors to KiB.  The summaries under profiles/ hold the commands and the full tables.
 PMC = {
-    "sources_sha256": "6aa4a0f6d16be9274b5df79f0e0b5f249214b9677b87bbc37d0d181c439cfdd5",
+    "sources_sha256": "0b6ab2dce900fa4a48f3ecb531ed80aceade5e926bdd75eaeed1adee0352575e",
     "fetch_scale": 2.00, "write_scale": 1.00,
     "k_build": (11022.0, 4800.5),
-    "k_fill": (3407.7, 19286.7),
-    "k_apply_vec<bf16>": (97602.5, 303876.0),
-    "k_apply_vec<fp32>": (179397.0, 607881.8),
-    "k_build_tagdispatch": (144203.5, 689897.5),
+    "k_fill": (3409.4, 19287.3),
+    "k_apply_vec<bf16>": (97610.0, 303874.4),
+    "k_apply_vec<fp32>": (179404.1, 607840.5),
+    "k_build_tagdispatch": (144026.9, 689897.5),
     # wave instructions of one k_build launch (rocprofv3 --pmc SQ_INSTS_VALU; SQ_INSTS_SALU + SQ_INSTS_SMEM + SQ_INSTS_BRANCH)
     "k_build_valu_instructions": 12736009.0, "k_build_scalar_and_branch_instructions": 16452309.0,
     "k_build_tagdispatch_valu_instructions": 837465160.0, "k_build_tagdispatch_scalar_and_branch_instructions": 1065553567.0,
