@@ -2092,8 +2092,10 @@ void xg2_matcher_destroy(xg2_matcher* m) { delete m; }
 
 static int32_t accept_one(xg2_matcher* m, int32_t token_id);
 int32_t xg2_matcher_accept_token(xg2_matcher* m, int32_t token_id) {
-    if (int32_t rc = report_undecided_pairs()) return rc;
-    return accept_one(m, token_id);
+    return guarded([&]() -> int32_t {
+        if (int32_t rc = report_undecided_pairs()) return rc;
+        return accept_one(m, token_id);
+    });
 }
 static int32_t accept_one(xg2_matcher* m, int32_t token_id) {
     return guarded([&]() -> int32_t {

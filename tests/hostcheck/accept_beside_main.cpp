@@ -142,6 +142,26 @@ static void allocations() {
             for (xg2_matcher* m : ms) xg2_matcher_destroy(m);
             if (!reached) break;
         }
+    // the same of a single token
+    for (long n = 0;; ++n) {
+        CHECK(n < 1000);
+        auto ms = some_matchers(1);
+        leave_undecided = true;
+        fill(ms);
+        leave_undecided = false;
+        const size_t before = length(ms[0]);
+        bool threw = false;
+        int32_t rc = XG2_OK;
+        countdown = n;
+        try { rc = xg2_matcher_accept_token(ms[0], A); } catch (...) { threw = true; }
+        const bool reached = countdown < 0;
+        countdown = -1;
+        CHECK(!threw);
+        if (!undecided_error(rc)) { CHECK(rc != XG2_OK); CHECK(undecided_error(xg2_matcher_accept_token(ms[0], A))); }
+        CHECK(length(ms[0]) == before);
+        for (xg2_matcher* m : ms) xg2_matcher_destroy(m);
+        if (!reached) break;
+    }
 }
 
 // Where the call ends early, the statuses of the rows it has not come to are left as the caller had them, and so for a fill that has ended.
